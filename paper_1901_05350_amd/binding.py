@@ -104,6 +104,24 @@ def lib():
     return _lib
 
 
+_call = None
+
+
+def _load_call():
+    """The native host path of the entry points below (csrc/call.cpp), loaded with the library on first use."""
+    global _call
+    lib()
+    import torch  # noqa: F401  (the extension uses torch's libraries)
+    from . import _call as module
+    _call = module
+    return module
+
+
+# Each entry point first hands its arguments to its namesake in the extension, which does the whole call for plain
+# arguments and returns None, with nothing enqueued, for all others; the checks below then say what is wrong with them
+# (or make the call, where the arguments are merely unusual).
+
+
 def _shape(dims):
     return (ctypes.c_int64 * len(dims))(*[int(d) for d in dims])
 
@@ -176,6 +194,9 @@ def tfx_depthwise_conv2d_out_shape(x_shape, f_shape, stride, pad):
 
 
 def tfx_matmul(a, b, transpose_a=False, transpose_b=False, out=None):
+    c = (_call or _load_call()).matmul(a, b, transpose_a, transpose_b, out)
+    if c is not None:
+        return c
     import torch
     _rank(a, "a", (2,)), _rank(b, "b", (2,))
     m, n = tfx_matmul_out_shape(a.shape, b.shape, transpose_a, transpose_b)
@@ -189,6 +210,9 @@ def tfx_matmul(a, b, transpose_a=False, transpose_b=False, out=None):
 
 
 def tfx_batch_matmul(a, b, transpose_a=False, transpose_b=False, out=None):
+    c = (_call or _load_call()).batch_matmul(a, b, transpose_a, transpose_b, out)
+    if c is not None:
+        return c
     import torch
     _rank(a, "a", (3,)), _rank(b, "b", (3,))
     m, n = tfx_matmul_out_shape(a.shape[1:], b.shape[1:], transpose_a, transpose_b)
@@ -215,18 +239,27 @@ def _add(fn_name, dtype, a, b, out):
 
 def tfx_add(a, b, out=None):
     """c = a + b element-wise, float32; out may be a or b."""
+    c = (_call or _load_call()).add(a, b, out)
+    if c is not None:
+        return c
     import torch
     return _add("tfx_add", torch.float32, a, b, out)
 
 
 def tfx_add_f16(a, b, out=None):
     """c = a + b element-wise on float16 storage; out may be a or b."""
+    c = (_call or _load_call()).add_f16(a, b, out)
+    if c is not None:
+        return c
     import torch
     return _add("tfx_add_f16", torch.float16, a, b, out)
 
 
 def tfx_batch_matmul_f16(a, b, transpose_a=False, transpose_b=False, bias=None, act=ACT_NONE, out=None):
     """float16 [B,rows,cols] operands, float16 bias [N] or None, float16 result [B,M,N]."""
+    c = (_call or _load_call()).batch_matmul_f16(a, b, transpose_a, transpose_b, bias, act, out)
+    if c is not None:
+        return c
     import torch
     h = torch.float16
     _rank(a, "a", (3,)), _rank(b, "b", (3,))
@@ -267,19 +300,31 @@ def _conv(fn_name, shape_fn, x, filt, bias, stride, pad, act, out, dtype=None):
 
 
 def tfx_conv2d(x, filt, bias=None, stride=1, pad=PAD_SAME, act=ACT_NONE, out=None):
+    y = (_call or _load_call()).conv2d(x, filt, bias, stride, pad, act, out)
+    if y is not None:
+        return y
     return _conv("tfx_conv2d", tfx_conv2d_out_shape, x, filt, bias, stride, pad, act, out)
 
 
 def tfx_depthwise_conv2d(x, filt, bias=None, stride=1, pad=PAD_SAME, act=ACT_NONE, out=None):
+    y = (_call or _load_call()).depthwise_conv2d(x, filt, bias, stride, pad, act, out)
+    if y is not None:
+        return y
     return _conv("tfx_depthwise_conv2d", tfx_depthwise_conv2d_out_shape, x, filt, bias, stride, pad, act, out)
 
 
 def tfx_conv2d_f16(x, filt, bias=None, stride=1, pad=PAD_SAME, act=ACT_NONE, out=None):
+    y = (_call or _load_call()).conv2d_f16(x, filt, bias, stride, pad, act, out)
+    if y is not None:
+        return y
     import torch
     return _conv("tfx_conv2d_f16", tfx_conv2d_out_shape, x, filt, bias, stride, pad, act, out, torch.float16)
 
 
 def tfx_depthwise_conv2d_f16(x, filt, bias=None, stride=1, pad=PAD_SAME, act=ACT_NONE, out=None):
+    y = (_call or _load_call()).depthwise_conv2d_f16(x, filt, bias, stride, pad, act, out)
+    if y is not None:
+        return y
     import torch
     return _conv("tfx_depthwise_conv2d_f16", tfx_depthwise_conv2d_out_shape, x, filt, bias, stride, pad, act, out,
                  torch.float16)
@@ -373,6 +418,9 @@ class MobileNetV1:
 
     def forward(self, image):
         """Enqueue one forward pass on the current stream; returns (probs, logits) device tensors."""
+        if (_call or _load_call()).net(image, ctypes.addressof(self.variant), ctypes.addressof(self.struct), self.workspace,
+                                       self.probs, self.logits):
+            return self.probs, self.logits
         _dev(image, "image")
         size = int(self.variant.image_size)
         if tuple(image.shape) != (self.batch, size, size, 3):
@@ -487,6 +535,9 @@ class MobileNetV1F16:
 
     def forward(self, image):
         """Enqueue one forward pass on the current stream; returns (probs, logits) float16 device tensors."""
+        if (_call or _load_call()).net_f16(image, ctypes.addressof(self.variant), ctypes.addressof(self.struct),
+                                           self.workspace, self.probs, self.logits):
+            return self.probs, self.logits
         import torch
         _check_forward_buffers(image, self.workspace, self.probs, self.logits, self.batch, int(self.variant.image_size),
                                int(self.variant.classes), torch.float16)

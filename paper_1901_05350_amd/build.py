@@ -1,4 +1,5 @@
-"""Build libtfx.so (HIP kernels + C ABI) for gfx950 with hipcc, in-tree.
+"""Build libtfx.so (HIP kernels + C ABI) for gfx950 with hipcc, and _call.so (the Python entry points' host path,
+against the installed PyTorch's C++ headers) with g++, in-tree.
 
 Usage: python -m paper_1901_05350_amd.build [--force]
 """
@@ -11,6 +12,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libtfx.so")
+CALL = os.path.join(HERE, "_call.so")
 SOURCES = ["api.hip", "gemm.hip", "pointwise.hip", "conv.hip", "depthwise.hip", "tail.hip", "elementwise.hip", "gemm_f16.hip", "conv_f16.hip", "pointwise_f16.hip", "pointwise_slab_f16.hip", "conv_gemm_f16.hip", "conv_stream_f16.hip", "chain.hip", "block.hip", "block_stream.hip", "block_stream_f16.hip"]
 HEADERS = [os.path.join(CSRC, "tfx_internal.h"), os.path.join(CSRC, "stream_f16.h"), os.path.join(HERE, "..", "include", "tfx.h")]
 FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-Wall", "-Wno-unused-function",
@@ -37,14 +39,32 @@ def _compile(src, force):
     return obj
 
 
+def _compile_call(force):
+    """The extension module links against libtfx.so beside it and torch's libraries, which `import torch` has loaded
+    by the time the module is imported."""
+    src = os.path.join(CSRC, "call.cpp")
+    if not force and not _stale(CALL, [src, LIB] + HEADERS):
+        return
+    import sysconfig
+    import torch
+    base = os.path.dirname(torch.__file__)
+    subprocess.run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1",
+                    "-DUSE_ROCM=1", "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI,
+                    "-isystem", os.path.join(base, "include"), "-isystem", os.path.join(base, "include/torch/csrc/api/include"),
+                    "-isystem", "/opt/rocm/include", "-isystem", sysconfig.get_paths()["include"], src, "-o", CALL,
+                    "-L" + os.path.join(base, "lib"), "-ltorch_python", "-ltorch_hip", "-ltorch_cpu", "-lc10_hip", "-lc10",
+                    "-L" + HERE, "-ltfx", "-Wl,-rpath,$ORIGIN"], check=True)
+
+
 def build(force=False, verbose=False):
     os.makedirs(OBJ, exist_ok=True)
     with concurrent.futures.ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as ex:
         objs = list(ex.map(lambda s: _compile(s, force), SOURCES))
     if force or _stale(LIB, objs):
         subprocess.run([_hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + objs, check=True)
+    _compile_call(force)
     if verbose:
-        print("built", LIB)
+        print("built", LIB, CALL)
     return LIB
 
 
