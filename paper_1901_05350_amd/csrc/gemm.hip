@@ -15,7 +15,7 @@
 // The contraction index may be permuted freely as long as A and B agree, so within a
 // group of 8 consecutive k a lane with h = l/32 takes k = 8g + 4h + s in step s = 0..3.
 // That makes a lane's four steps one contiguous float4 in a K-contiguous LDS tile.
-#include "tfx_internal.h"
+#include "ragged.h"
 
 #include <type_traits>
 
@@ -36,60 +36,31 @@ struct Tile {
   static constexpr int kSlots = ROWS * BK / 4;  // float4 slots per tile
 };
 
-// Global -> registers for one operand tile.  Slot s of the tile is one float4:
+// Global -> registers for one operand tile whose rows are 16-byte aligned (the 16-row kernel).  Slot s of the tile is one
+// float4:
 //   KC : row r = s / (BK/4), k = 4 * (s % (BK/4))       -> g[(row0 + r) * ld + k0 + k .. +3]
 //   !KC: k = s / (ROWS/4),   r = 4 * (s % (ROWS/4))     -> g[(k0 + k) * ld + row0 + r .. +3]
 // Out-of-range elements read as zero, so ragged M, N and K tails add nothing.
-template <int ROWS, int BK, bool KC, bool VEC, int NT, int NSLOT>
+template <int ROWS, int BK, bool KC, int NT, int NSLOT>
 __device__ __forceinline__ void load_tile(const float* __restrict__ g, int ld, int rows_total, int k_total, int row0,
                                           int k0, int tid, float4 (&reg)[NSLOT]) {
 #pragma unroll
   for (int it = 0; it < NSLOT; ++it) {
     const int s = tid + it * NT;
-    int r, k;
-    if (KC) {
-      r = s / (BK / 4);
-      k = 4 * (s % (BK / 4));
-    } else {
-      k = s / (ROWS / 4);
-      r = 4 * (s % (ROWS / 4));
-    }
-    const int gr = row0 + r, gk = k0 + k;
-    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (KC) {
-      if (gr < rows_total) {
-        const float* p = g + (size_t)gr * ld + gk;
-        if (VEC) {
-          if (gk < k_total) v = *reinterpret_cast<const float4*>(p);
-        } else {
-          if (gk + 0 < k_total) v.x = p[0];
-          if (gk + 1 < k_total) v.y = p[1];
-          if (gk + 2 < k_total) v.z = p[2];
-          if (gk + 3 < k_total) v.w = p[3];
-        }
-      }
-    } else {
-      if (gk < k_total) {
-        const float* p = g + (size_t)gk * ld + gr;
-        if (VEC) {
-          if (gr < rows_total) v = *reinterpret_cast<const float4*>(p);
-        } else {
-          if (gr + 0 < rows_total) v.x = p[0];
-          if (gr + 1 < rows_total) v.y = p[1];
-          if (gr + 2 < rows_total) v.z = p[2];
-          if (gr + 3 < rows_total) v.w = p[3];
-        }
-      }
-    }
-    reg[it] = v;
+    const int gr = row0 + (KC ? s / (BK / 4) : 4 * (s % (ROWS / 4))), gk = k0 + (KC ? 4 * (s % (BK / 4)) : s / (ROWS / 4));
+    reg[it] = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (gr < rows_total && gk < k_total)
+      reg[it] = *reinterpret_cast<const float4*>(g + (KC ? (size_t)gr * ld + gk : (size_t)gk * ld + gr));
   }
 }
 
-// Branch-free variant for k-slices that lie entirely inside K (vector loads only).  A thread's slots keep a
+// Branch-free variant for k-slices that lie entirely inside K.  A thread's slots keep a
 // pointer each, set up once: rows past the end of the operand are clamped to a valid row instead of masked --
 // they only feed output rows / columns that are never stored -- so a k-slice is NSLOT unconditional loads and
 // no other vector instruction (on this chip every vector-ALU instruction takes issue time away from the
-// matrix cores: the masked loader's compares, zero fills and branches cost ~10% of the main loop).
+// matrix cores: the masked loader's compares, zero fills and branches cost ~10% of the main loop).  The loads need no
+// alignment; a slot of a row-contiguous operand may reach past the end of its row into the next one, so the slice with
+// the last row is not one of these when the row length is no multiple of 4.
 template <int ROWS, int BK, bool KC, int NT, int NSLOT>
 __device__ __forceinline__ void slot_pointers(const float* __restrict__ g, int ld, int rows_total, int row0, int tid,
                                               const float* (&ptr)[NSLOT]) {
@@ -100,16 +71,77 @@ __device__ __forceinline__ void slot_pointers(const float* __restrict__ g, int l
       const int gr = min(row0 + s / (BK / 4), rows_total - 1);
       ptr[it] = g + (size_t)gr * ld + 4 * (s % (BK / 4));
     } else {
-      int gr = row0 + 4 * (s % (ROWS / 4));  // 4 consecutive rows, all inside or all outside (rows_total % 4 == 0)
+      int gr = row0 + 4 * (s % (ROWS / 4));
       if (gr >= rows_total) gr = 0;
       ptr[it] = g + (size_t)(s / (ROWS / 4)) * ld + gr;
     }
   }
 }
+__device__ __forceinline__ float4 load_quad(const float* p) { return __builtin_bit_cast(float4, load16(p)); }
 template <int NSLOT>
 __device__ __forceinline__ void load_tile_full(const float* (&ptr)[NSLOT], size_t k_offset, float4 (&reg)[NSLOT]) {
 #pragma unroll
-  for (int it = 0; it < NSLOT; ++it) reg[it] = *reinterpret_cast<const float4*>(ptr[it] + k_offset);
+  for (int it = 0; it < NSLOT; ++it) reg[it] = load_quad(ptr[it] + k_offset);
+}
+
+// The same for any k-slice and operand of at least 4 elements: the loads of a slice (every one unconditional, from a
+// valid place) and, when its registers are consumed, what makes them the slice: quads that would have left the operand
+// were fetched a few elements early and are shifted down, elements past K are zeroed.
+// CV: the operand is a convolution's filter [taps * Ci, N] seen with the channels of a tap padded to a multiple of 4
+// (`by_cp.d`), k_total channels per tap.
+struct FilterK {
+  FastDiv by_cp;
+  int taps;
+};
+template <int ROWS, int BK, bool KC, bool CV, int NT>
+__device__ __forceinline__ unsigned slot_offset(int ld, int rows_total, int k_total, int row0, int k0, int tid, int it,
+                                                unsigned total, const FilterK& fk, unsigned* early, int* valid) {
+  const int s = tid + it * NT;
+  unsigned off;
+  if (KC) {
+    const int gr = min(row0 + s / (BK / 4), rows_total - 1), gk = k0 + 4 * (s % (BK / 4));
+    *valid = k_total - gk;
+    off = (unsigned)gr * (unsigned)ld + (unsigned)(*valid > 0 ? gk : 0);
+  } else {
+    int gr = row0 + 4 * (s % (ROWS / 4)), gk = k0 + s / (ROWS / 4);
+    if (gr >= rows_total) gr = 0;
+    bool in;
+    if constexpr (CV) {
+      const int tap = (int)div_by((unsigned)gk, fk.by_cp), c = gk - tap * (int)fk.by_cp.d;
+      in = tap < fk.taps && c < k_total;
+      gk = tap * k_total + c;
+    } else {
+      in = gk < k_total;
+    }
+    *valid = in ? 4 : 0;
+    off = (unsigned)(in ? gk : 0) * (unsigned)ld + (unsigned)gr;
+  }
+  const unsigned at = min(off, total - 4u);
+  *early = off - at;
+  return at;
+}
+template <int ROWS, int BK, bool KC, bool CV, int NT, int NSLOT>
+__device__ __forceinline__ void load_tile_any(const float* __restrict__ g, int ld, int rows_total, int k_total, int row0, int k0,
+                                              int tid, unsigned total, const FilterK& fk, float4 (&reg)[NSLOT]) {
+#pragma unroll
+  for (int it = 0; it < NSLOT; ++it) {
+    unsigned early;
+    int valid;
+    reg[it] = load_quad(g + slot_offset<ROWS, BK, KC, CV, NT>(ld, rows_total, k_total, row0, k0, tid, it, total, fk, &early, &valid));
+  }
+}
+template <int ROWS, int BK, bool KC, bool CV, int NT, int NSLOT>
+__device__ __forceinline__ void settle_tile(int ld, int rows_total, int k_total, int row0, int k0, int tid, unsigned total,
+                                            const FilterK& fk, float4 (&reg)[NSLOT]) {
+#pragma unroll
+  for (int it = 0; it < NSLOT; ++it) {
+    unsigned early;
+    int valid;
+    slot_offset<ROWS, BK, KC, CV, NT>(ld, rows_total, k_total, row0, k0, tid, it, total, fk, &early, &valid);
+    ragged_u32x4 v = __builtin_bit_cast(ragged_u32x4, reg[it]);
+    if (__builtin_amdgcn_ballot_w64(early != 0) != 0) v = shift_down<float>(v, early);
+    reg[it] = __builtin_bit_cast(float4, v & first_elements<float>(valid));
+  }
 }
 
 template <int ROWS, int BK, bool KC, int NT, int NSLOT>
@@ -134,66 +166,81 @@ __device__ __forceinline__ void store_tile(float* __restrict__ lds, int tid, con
 struct ConvA {
   const float* x;
   int H, W, Ci, OH, OW, fw, sh, sw, pt, pl;
+  unsigned total;  // elements of x
+  FastDiv by_fw, by_ow, by_oh;
+  FilterK fk;      // channels of a tap padded to a multiple of 4
 };
 
-// What a thread needs to know about the output pixel of one of its A-tile slots.
-struct ConvRow {
-  int ih0, iw0;      // input coordinates of filter tap (0, 0)
-  long long base;    // element offset of image n, or -1 if the row is past M
+// A-tile loader of the implicit GEMM for any channel count.  k runs over (tap, channel) with the channels of a tap
+// padded to a multiple of 4, so a quad never crosses a filter tap; all slots of a thread share the same k offset (NT is
+// a multiple of BK/4), which is decoded once per thread and slice (two multiplications by reciprocals).  Every load is
+// unconditional: for a quad outside the image or past K from the first element of x, zeroed when the registers are
+// consumed; one that would leave x is fetched early and shifted (load_tile_any).
+struct ConvRow {  // what a thread knows about the output pixel of one of its slots
+  int ih0, iw0;   // input coordinates of filter tap (0, 0)
+  int origin;     // element offset of that tap's channel 0 (negative or past x where the tap is outside the image)
 };
-
 template <int BM, int BK, int NT, int NSLOT>
 __device__ __forceinline__ void conv_rows(const ConvA& cv, int M, int m0, int tid, ConvRow (&rows)[NSLOT]) {
 #pragma unroll
   for (int it = 0; it < NSLOT; ++it) {
-    const int r = m0 + (tid + it * NT) / (BK / 4);
-    const int ow = r % cv.OW;
-    const int t = r / cv.OW;
-    const int oh = t % cv.OH;
-    const int n = t / cv.OH;
-    rows[it].ih0 = oh * cv.sh - cv.pt;
-    rows[it].iw0 = ow * cv.sw - cv.pl;
-    rows[it].base = r < M ? (long long)n * cv.H * cv.W * cv.Ci : -1;
+    const unsigned r = (unsigned)min(m0 + (tid + it * NT) / (BK / 4), M - 1);  // rows past M repeat the last one
+    const unsigned t = div_by(r, cv.by_ow), n = div_by(t, cv.by_oh);
+    rows[it].ih0 = (int)(t - n * cv.by_oh.d) * cv.sh - cv.pt;
+    rows[it].iw0 = (int)(r - t * cv.by_ow.d) * cv.sw - cv.pl;
+    rows[it].origin = (((int)n * cv.H + rows[it].ih0) * cv.W + rows[it].iw0) * cv.Ci;
   }
 }
-
-// A-tile loader of the implicit GEMM.  All slots of a thread share the same k offset (NT is a
-// multiple of BK/4), so (kh, kw, c) is decoded once per thread per k-slice.  With VEC, Ci % 4 == 0
-// and a float4 never crosses a filter tap; otherwise each of the 4 elements is decoded on its own.
-template <int BM, int BK, bool VEC, int NT, int NSLOT>
-__device__ __forceinline__ void load_tile_conv(const ConvA& cv, int K, int k0, int tid, const ConvRow (&rows)[NSLOT],
-                                               float4 (&reg)[NSLOT]) {
-  static_assert(NT % (BK / 4) == 0, "k offset must be the same for all slots of a thread");
+struct ConvK {  // a thread's k position in a slice
+  int kh, kw, add, valid;
+};
+template <int BK>
+__device__ __forceinline__ ConvK conv_k(const ConvA& cv, int k0, int tid) {
   const int gk = k0 + 4 * (tid % (BK / 4));
-  int kh[4], kw[4], c[4];
-#pragma unroll
-  for (int e = 0; e < (VEC ? 1 : 4); ++e) {
-    const int k = gk + e;
-    c[e] = k % cv.Ci;
-    const int t = k / cv.Ci;
-    kw[e] = t % cv.fw;
-    kh[e] = t / cv.fw;
-  }
+  const int tap = (int)div_by((unsigned)gk, cv.fk.by_cp), c = gk - tap * (int)cv.fk.by_cp.d;
+  ConvK p;
+  p.kh = (int)div_by((unsigned)tap, cv.by_fw);
+  p.kw = tap - p.kh * cv.fw;
+  p.add = (p.kh * cv.W + p.kw) * cv.Ci + c;
+  p.valid = tap < cv.fk.taps ? cv.Ci - c : 0;
+  return p;
+}
+__device__ __forceinline__ unsigned conv_offset(const ConvA& cv, const ConvRow& row, const ConvK& p, unsigned* early, bool* in) {
+  const int ih = row.ih0 + p.kh, iw = row.iw0 + p.kw;
+  *in = p.valid > 0 && ih >= 0 && ih < cv.H && iw >= 0 && iw < cv.W;
+  const unsigned off = *in ? (unsigned)(row.origin + p.add) : 0u, at = min(off, cv.total - 4u);
+  *early = off - at;
+  return at;
+}
+template <int BK, int NSLOT>
+__device__ __forceinline__ void load_tile_conv(const ConvA& cv, int k0, int tid, const ConvRow (&rows)[NSLOT],
+                                               float4 (&reg)[NSLOT]) {
+  const ConvK p = conv_k<BK>(cv, k0, tid);
 #pragma unroll
   for (int it = 0; it < NSLOT; ++it) {
-    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (rows[it].base >= 0) {
-      if (VEC) {
-        const int ih = rows[it].ih0 + kh[0], iw = rows[it].iw0 + kw[0];
-        if (gk < K && ih >= 0 && ih < cv.H && iw >= 0 && iw < cv.W)
-          v = *reinterpret_cast<const float4*>(cv.x + rows[it].base + ((long long)ih * cv.W + iw) * cv.Ci + c[0]);
-      } else {
-        float e4[4] = {0.f, 0.f, 0.f, 0.f};
+    unsigned early;
+    bool in;
+    reg[it] = load_quad(cv.x + conv_offset(cv, rows[it], p, &early, &in));
+  }
+}
+// RAGGED: Ci % 4 != 0 (else a quad inside the image is valid as it is)
+template <int BK, bool RAGGED, int NSLOT>
+__device__ __forceinline__ void settle_tile_conv(const ConvA& cv, int k0, int tid, const ConvRow (&rows)[NSLOT],
+                                                 float4 (&reg)[NSLOT]) {
+  const ConvK p = conv_k<BK>(cv, k0, tid);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int ih = rows[it].ih0 + kh[e], iw = rows[it].iw0 + kw[e];
-          if (gk + e < K && ih >= 0 && ih < cv.H && iw >= 0 && iw < cv.W)
-            e4[e] = cv.x[rows[it].base + ((long long)ih * cv.W + iw) * cv.Ci + c[e]];
-        }
-        v = make_float4(e4[0], e4[1], e4[2], e4[3]);
-      }
+  for (int it = 0; it < NSLOT; ++it) {
+    unsigned early;
+    bool in;
+    conv_offset(cv, rows[it], p, &early, &in);
+    ragged_u32x4 v = __builtin_bit_cast(ragged_u32x4, reg[it]);
+    if constexpr (RAGGED) {
+      if (__builtin_amdgcn_ballot_w64(early != 0) != 0) v = shift_down<float>(v, early);
+      v &= first_elements<float>(in ? p.valid : 0);
+    } else {
+      v &= in ? ~0u : 0u;
     }
-    reg[it] = v;
+    reg[it] = __builtin_bit_cast(float4, v);
   }
 }
 
@@ -260,13 +307,15 @@ __device__ __forceinline__ float f4_get(const float4& v, int s) {
 // Tiled kernel for medium and large problems: BM x BN tile, BK-deep k-slices double-buffered in LDS
 // (one barrier per slice), WAVES_M x WAVES_N wavefronts each owning a (BM/WAVES_M) x (BN/WAVES_N) sub-tile.
 // CONV: the A operand is the implicit im2col view `cv` of a convolution input instead of a matrix.
-template <int BM, int BN, int BK, int WAVES_M, int WAVES_N, bool A_KC, bool B_KC, bool VEC, bool CONV, bool LEAN>
+// (A convolution: its output channels contiguous in B.)  CONV_RAGGED: its channel count is no multiple of 4.
+enum ConvForm { kNoConv, kConvLean, kConvAligned, kConvRagged };
+template <int BM, int BN, int BK, int WAVES_M, int WAVES_N, bool A_KC, bool B_KC, ConvForm FORM>
 __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_mfma_kernel(
     const float* __restrict__ A, const float* __restrict__ B, float* __restrict__ C, const float* __restrict__ bias,
-    int M, int N, int K, int tiles_m, int tiles_n, int total_blocks, long long strideA, long long strideB,
-    long long strideC, int act, int m_fastest, ConvA cv) {
-  static_assert(!CONV || A_KC, "the im2col view is K-contiguous");
-  static_assert(!LEAN || (CONV && VEC), "the lean loader is the vector form of the convolution loader");
+    int M, int N, int K, int nk, int nk_full, int tiles_m, int tiles_n, int total_blocks, long long strideA,
+    long long strideB, long long strideC, int act, int m_fastest, ConvA cv) {
+  constexpr bool CONV = FORM != kNoConv, LEAN = FORM == kConvLean;
+  static_assert(!CONV || (A_KC && !B_KC), "the im2col view is K-contiguous, the filter [K,N]");
   constexpr int NT = 64 * WAVES_M * WAVES_N;
   constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;
   constexpr int TM = WM / 32, TN = WN / 32;
@@ -324,7 +373,6 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_mfma_kernel(
   }
 
   float4 ra[SA], rb[SB];
-  const int nk = (K + BK - 1) / BK;
   ConvRow crow[CONV && !LEAN ? SA : 1];
   if constexpr (CONV && !LEAN) conv_rows<BM, BK, NT, SA>(cv, M, m0, tid, crow);
   const float* cp0[SA];  // lean loader only
@@ -333,15 +381,15 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_mfma_kernel(
   // requested in order 0, 1, 2, ...); uniform across the workgroup
   int tap_c0 = 0, tap_kh = 0, tap_kw = 0, tap_idx = 0;
   if constexpr (LEAN) conv_lean_rows<BM, BK, NT, SA>(cv, M, K, m0, tid, cp0, cok);
-  // k-slices that lie entirely inside K take the branch-free loaders (vector layouts only)
-  constexpr bool FAST_A = VEC && !CONV, FAST_B = VEC;
-  const int nk_full = K / BK;
+  // k-slices that lie entirely inside K take the branch-free loaders
   const float* pa[SA];
   const float* pb[SB];
-  if constexpr (FAST_A) slot_pointers<BM, BK, A_KC, NT, SA>(A, lda, M, m0, tid, pa);
-  if constexpr (FAST_B) slot_pointers<BN, BK, B_KC, NT, SB>(B, ldb, N, n0, tid, pb);
+  if constexpr (!CONV) slot_pointers<BM, BK, A_KC, NT, SA>(A, lda, M, m0, tid, pa);
+  if constexpr (FORM != kConvRagged) slot_pointers<BN, BK, B_KC, NT, SB>(B, ldb, N, n0, tid, pb);
   const size_t step_a = A_KC ? (size_t)BK : (size_t)BK * lda, step_b = B_KC ? (size_t)BK : (size_t)BK * ldb;
-  // FULL: k-slice kt is known to lie inside K
+  const unsigned total_a = (unsigned)strideA, total_b = (unsigned)strideB;
+  const int kb = FORM == kConvRagged ? cv.Ci : K;  // valid k of B (per tap)
+  // FULL: k-slice kt is known to lie inside K (for both operands)
   auto load_a = [&](int kt, auto full) {
     if constexpr (LEAN) {
       load_tile_conv_lean<SA>(cp0, cok, tap_idx, ((long long)tap_kh * cv.W + tap_kw) * cv.Ci + tap_c0, ra);
@@ -354,18 +402,30 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_mfma_kernel(
           ++tap_kh;
         }
       }
-    } else if constexpr (CONV) load_tile_conv<BM, BK, VEC, NT, SA>(cv, K, kt * BK, tid, crow, ra);
-    else if constexpr (FAST_A && decltype(full)::value) load_tile_full<SA>(pa, kt * step_a, ra);
-    else load_tile<BM, BK, A_KC, VEC, NT, SA>(A, lda, M, K, m0, kt * BK, tid, ra);
+    } else if constexpr (CONV) load_tile_conv<BK, SA>(cv, kt * BK, tid, crow, ra);
+    else if constexpr (decltype(full)::value) load_tile_full<SA>(pa, kt * step_a, ra);
+    else load_tile_any<BM, BK, A_KC, false, NT, SA>(A, lda, M, K, m0, kt * BK, tid, total_a, cv.fk, ra);
   };
   auto load_b = [&](int kt, auto full) {
-    if constexpr (FAST_B && decltype(full)::value) load_tile_full<SB>(pb, kt * step_b, rb);
-    else load_tile<BN, BK, B_KC, VEC, NT, SB>(B, ldb, N, K, n0, kt * BK, tid, rb);
+    if constexpr (FORM != kConvRagged && decltype(full)::value) load_tile_full<SB>(pb, kt * step_b, rb);
+    else load_tile_any<BN, BK, B_KC, FORM == kConvRagged, NT, SB>(B, ldb, N, kb, n0, kt * BK, tid, total_b, cv.fk, rb);
   };
-  load_a(0, std::false_type{});
-  load_b(0, std::false_type{});
-  store_tile<BM, BK, A_KC, NT, SA>(lds_a, tid, ra);
-  store_tile<BN, BK, B_KC, NT, SB>(lds_b, tid, rb);
+  auto store = [&](int kt, int buf, auto full) {
+    if constexpr (CONV && !LEAN) settle_tile_conv<BK, FORM == kConvRagged, SA>(cv, kt * BK, tid, crow, ra);
+    else if constexpr (!CONV && !decltype(full)::value)
+      settle_tile<BM, BK, A_KC, false, NT, SA>(lda, M, K, m0, kt * BK, tid, total_a, cv.fk, ra);
+    if constexpr (FORM == kConvRagged || !decltype(full)::value)
+      settle_tile<BN, BK, B_KC, FORM == kConvRagged, NT, SB>(ldb, N, kb, n0, kt * BK, tid, total_b, cv.fk, rb);
+    store_tile<BM, BK, A_KC, NT, SA>(lds_a + buf * TA::kFloats, tid, ra);
+    store_tile<BN, BK, B_KC, NT, SB>(lds_b + buf * TB::kFloats, tid, rb);
+  };
+  auto first = [&](auto full) {
+    load_a(0, full);
+    load_b(0, full);
+    store(0, 0, full);
+  };
+  if (nk_full > 0) first(std::true_type{});
+  else first(std::false_type{});
   __syncthreads();
 
   // One k-slice: fetch slice kt + 1 into registers, multiply slice kt from LDS, hand the registers to the other
@@ -406,10 +466,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_mfma_kernel(
                                                              0, 0, 0);
     }
     __builtin_amdgcn_s_setprio(0);
-    if (NEXT_FULL || kt + 1 < nk) {
-      store_tile<BM, BK, A_KC, NT, SA>(lds_a + nxt * TA::kFloats, tid, ra);
-      store_tile<BN, BK, B_KC, NT, SB>(lds_b + nxt * TB::kFloats, tid, rb);
-    }
+    if (NEXT_FULL || kt + 1 < nk) store(kt + 1, nxt, next_full);
     __syncthreads();
   };
   int kt = 0;
@@ -432,42 +489,39 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_mfma_kernel(
   }
 }
 
-template <int BM, int BN, int BK, int WAVES_M, int WAVES_N, bool A_KC, bool B_KC, bool VEC, bool CONV = false,
-          bool LEAN = false>
+template <int BM, int BN, int BK, int WAVES_M, int WAVES_N, bool A_KC, bool B_KC, ConvForm FORM = kNoConv>
 int launch_cfg(const float* a, const float* b, float* c, const float* bias, int batch, int m, int n, int k, int act,
                hipStream_t stream, const ConvA& cv = ConvA{}) {
   using TA = Tile<BM, BK, A_KC>;
   using TB = Tile<BN, BK, B_KC>;
   constexpr size_t lds_bytes = 2 * (TA::kFloats + TB::kFloats) * sizeof(float);
   static_assert(lds_bytes <= 160 * 1024, "LDS budget per workgroup");
-  auto kern = gemm_mfma_kernel<BM, BN, BK, WAVES_M, WAVES_N, A_KC, B_KC, VEC, CONV, LEAN>;
+  auto kern = gemm_mfma_kernel<BM, BN, BK, WAVES_M, WAVES_N, A_KC, B_KC, FORM>;
   static std::atomic<uint64_t> lds_allowed{0};
   if (allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds_bytes, lds_allowed) != TFX_OK) return TFX_ERR_LAUNCH;
   const int tiles_m = (m + BM - 1) / BM, tiles_n = (n + BN - 1) / BN;
   const long long total = (long long)batch * tiles_m * tiles_n;
   if (total > 0x7fffffffLL) return TFX_ERR_UNSUPPORTED;
+  // k-slices, and how many of them lie inside K and (rows of no multiple of 4 elements) before a row-contiguous
+  // operand's last row; with fewer than 4 rows / columns a quad reaches past more than one row: none
+  const int kp = FORM == kConvRagged ? cv.fk.taps * (int)cv.fk.by_cp.d : k;
+  const bool whole = (FORM != kNoConv || A_KC || m % 4 == 0) && (B_KC || n % 4 == 0);
+  int full = whole ? k / BK : (k - 1) / BK;
+  if ((FORM == kNoConv && !A_KC && m < 4) || (!B_KC && n < 4) || FORM == kConvRagged) full = 0;
   hipLaunchKernelGGL(kern, dim3((unsigned)total), dim3(64 * WAVES_M * WAVES_N), lds_bytes, stream, a, b, c,
-                     bias, m, n, k, tiles_m, tiles_n, (int)total, (long long)m * k, (long long)n * k, (long long)m * n,
-                     act, n > m ? 1 : 0, cv);
+                     bias, m, n, k, (kp + BK - 1) / BK, full, tiles_m, tiles_n, (int)total, (long long)m * k, (long long)n * k,
+                     (long long)m * n, act, n > m ? 1 : 0, cv);
   return check_launch();
 }
 
 template <int BM, int BN, int BK, int WAVES_M, int WAVES_N>
 int launch_layout(const float* a, const float* b, float* c, const float* bias, int batch, int m, int n, int k,
-                  bool a_kc, bool b_kc, bool vec, int act, hipStream_t stream) {
-#define TFX_GEMM_CASE(AK, BKC, V)                                                                              \
-  if (a_kc == AK && b_kc == BKC && vec == V)                                                                   \
-    return launch_cfg<BM, BN, BK, WAVES_M, WAVES_N, AK, BKC, V>(a, b, c, bias, batch, m, n, k, act, stream);
-  TFX_GEMM_CASE(true, true, true)
-  TFX_GEMM_CASE(true, false, true)
-  TFX_GEMM_CASE(false, true, true)
-  TFX_GEMM_CASE(false, false, true)
-  TFX_GEMM_CASE(true, true, false)
-  TFX_GEMM_CASE(true, false, false)
-  TFX_GEMM_CASE(false, true, false)
-  TFX_GEMM_CASE(false, false, false)
-#undef TFX_GEMM_CASE
-  return TFX_ERR_ARG;
+                  bool a_kc, bool b_kc, int act, hipStream_t stream) {
+  if (a_kc)
+    return b_kc ? launch_cfg<BM, BN, BK, WAVES_M, WAVES_N, true, true>(a, b, c, bias, batch, m, n, k, act, stream)
+                : launch_cfg<BM, BN, BK, WAVES_M, WAVES_N, true, false>(a, b, c, bias, batch, m, n, k, act, stream);
+  return b_kc ? launch_cfg<BM, BN, BK, WAVES_M, WAVES_N, false, true>(a, b, c, bias, batch, m, n, k, act, stream)
+              : launch_cfg<BM, BN, BK, WAVES_M, WAVES_N, false, false>(a, b, c, bias, batch, m, n, k, act, stream);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -492,7 +546,7 @@ __device__ __forceinline__ float4 read_frag16(const float* __restrict__ lds, int
   }
 }
 
-template <int TN, int BK, int WAVES_K, bool A_KC, bool B_KC, bool VEC>
+template <int TN, int BK, int WAVES_K, bool A_KC, bool B_KC>
 __global__ __launch_bounds__(64 * WAVES_K) void gemm_m16_kernel(
     const float* __restrict__ A, const float* __restrict__ B, float* __restrict__ C, const float* __restrict__ bias,
     int M, int N, int K, int tiles_m, int tiles_n, int total_blocks, long long strideA, long long strideB,
@@ -551,16 +605,16 @@ __global__ __launch_bounds__(64 * WAVES_K) void gemm_m16_kernel(
 
   float4 ra[SA], rb[SB];
   const int nk = (K + BK - 1) / BK;
-  load_tile<BM, BK, A_KC, VEC, NT, SA>(A, lda, M, K, m0, 0, tid, ra);
-  load_tile<BN, BK, B_KC, VEC, NT, SB>(B, ldb, N, K, n0, 0, tid, rb);
+  load_tile<BM, BK, A_KC, NT, SA>(A, lda, M, K, m0, 0, tid, ra);
+  load_tile<BN, BK, B_KC, NT, SB>(B, ldb, N, K, n0, 0, tid, rb);
   for (int kt = 0; kt < nk; ++kt) {
     if (kt > 0) __syncthreads();  // everyone has finished reading the previous tile
     store_tile<BM, BK, A_KC, NT, SA>(lds_a, tid, ra);
     store_tile<BN, BK, B_KC, NT, SB>(lds_b, tid, rb);
     __syncthreads();
     if (kt + 1 < nk) {
-      load_tile<BM, BK, A_KC, VEC, NT, SA>(A, lda, M, K, m0, (kt + 1) * BK, tid, ra);
-      load_tile<BN, BK, B_KC, VEC, NT, SB>(B, ldb, N, K, n0, (kt + 1) * BK, tid, rb);
+      load_tile<BM, BK, A_KC, NT, SA>(A, lda, M, K, m0, (kt + 1) * BK, tid, ra);
+      load_tile<BN, BK, B_KC, NT, SB>(B, ldb, N, K, n0, (kt + 1) * BK, tid, rb);
     }
 #pragma unroll
     for (int gg = 0; gg < GROUPS; ++gg) {
@@ -600,14 +654,14 @@ __global__ __launch_bounds__(64 * WAVES_K) void gemm_m16_kernel(
   }
 }
 
-template <int TN, int BK, int WAVES_K, bool A_KC, bool B_KC, bool VEC>
+template <int TN, int BK, int WAVES_K, bool A_KC, bool B_KC>
 int launch_m16_cfg(const float* a, const float* b, float* c, const float* bias, int batch, int m, int n, int k, int act,
                    hipStream_t stream) {
   using TA = Tile<16, BK, A_KC>;
   using TB = Tile<16 * TN, BK, B_KC>;
   constexpr size_t lds_bytes = (TA::kFloats + TB::kFloats) * sizeof(float);
   static_assert(lds_bytes <= 160 * 1024, "LDS budget per workgroup");
-  auto kern = gemm_m16_kernel<TN, BK, WAVES_K, A_KC, B_KC, VEC>;
+  auto kern = gemm_m16_kernel<TN, BK, WAVES_K, A_KC, B_KC>;
   static std::atomic<uint64_t> lds_allowed{0};
   if (allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds_bytes, lds_allowed) != TFX_OK) return TFX_ERR_LAUNCH;
   const int tiles_m = (m + 15) / 16, tiles_n = (n + 16 * TN - 1) / (16 * TN);
@@ -771,20 +825,28 @@ int launch_m16_direct(const float* a, const float* b, float* c, const float* bia
 
 template <int TN, int BK, int WAVES_K>
 int launch_m16_layout(const float* a, const float* b, float* c, const float* bias, int batch, int m, int n, int k,
-                      bool a_kc, bool b_kc, bool vec, int act, hipStream_t stream) {
-#define TFX_GEMM_CASE(AK, BKC, V)                                                                  \
-  if (a_kc == AK && b_kc == BKC && vec == V)                                                       \
-    return launch_m16_cfg<TN, BK, WAVES_K, AK, BKC, V>(a, b, c, bias, batch, m, n, k, act, stream);
-  TFX_GEMM_CASE(true, true, true)
-  TFX_GEMM_CASE(true, false, true)
-  TFX_GEMM_CASE(false, true, true)
-  TFX_GEMM_CASE(false, false, true)
-  TFX_GEMM_CASE(true, true, false)
-  TFX_GEMM_CASE(true, false, false)
-  TFX_GEMM_CASE(false, true, false)
-  TFX_GEMM_CASE(false, false, false)
-#undef TFX_GEMM_CASE
-  return TFX_ERR_ARG;
+                      bool a_kc, bool b_kc, int act, hipStream_t stream) {
+  if (a_kc)
+    return b_kc ? launch_m16_cfg<TN, BK, WAVES_K, true, true>(a, b, c, bias, batch, m, n, k, act, stream)
+                : launch_m16_cfg<TN, BK, WAVES_K, true, false>(a, b, c, bias, batch, m, n, k, act, stream);
+  return b_kc ? launch_m16_cfg<TN, BK, WAVES_K, false, true>(a, b, c, bias, batch, m, n, k, act, stream)
+              : launch_m16_cfg<TN, BK, WAVES_K, false, false>(a, b, c, bias, batch, m, n, k, act, stream);
+}
+
+// One thread per output element: operands of fewer elements than a 16-byte load.
+__global__ __launch_bounds__(256) void gemm_tiny_kernel(const float* __restrict__ A, const float* __restrict__ B,
+                                                        float* __restrict__ C, const float* __restrict__ bias, int M, int N, int K,
+                                                        int a_kc, int b_kc, long long total, int act) {
+  const long long e = (long long)blockIdx.x * 256 + threadIdx.x;
+  if (e >= total) return;
+  const int col = (int)(e % N);
+  const long long r = e / N, batch = r / M;
+  const int row = (int)(r % M);
+  float sum = 0.f;
+  for (int k = 0; k < K; ++k)
+    sum += A[batch * M * K + (a_kc ? (long long)row * K + k : (long long)k * M + row)] *
+           B[batch * N * K + (b_kc ? (long long)col * K + k : (long long)k * N + col)];
+  C[e] = apply_act(sum + (bias != nullptr ? bias[col] : 0.f), act);
 }
 
 // Fraction of a tiling's multiply-adds that land inside the m x n output (the rest is padding).
@@ -810,17 +872,23 @@ bool prefer_128(int batch, long long m, long long n) {
 
 int launch_gemm(const float* a, const float* b, float* c, const float* bias, int batch, int m, int n, int k, bool a_kc,
                 bool b_kc, int act, hipStream_t stream) {
-  // float4 global loads need 16-byte aligned rows: base pointers aligned and the contiguous
-  // extent of each operand a multiple of 4 (which also keeps every batch slice aligned).
+  if ((long long)m * k < 4 || (long long)n * k < 4) {
+    const long long total = (long long)batch * m * n;
+    hipLaunchKernelGGL(gemm_tiny_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, stream, a, b, c, bias, m, n, k,
+                       a_kc ? 1 : 0, b_kc ? 1 : 0, total, act);
+    return check_launch();
+  }
+  // 16-byte aligned rows: base pointers aligned and the contiguous extent of each operand a multiple of 4 (which also
+  // keeps every batch slice aligned)
   const int a_inner = a_kc ? k : m, b_inner = b_kc ? k : n;
   const bool vec = (reinterpret_cast<uintptr_t>(a) % 16 == 0) && (reinterpret_cast<uintptr_t>(b) % 16 == 0) &&
                    (a_inner % 4 == 0) && (b_inner % 4 == 0);
   // Tile choice.  Large problems: 128 x 128 tiles (best reuse).  Medium: 64 x 64.
   const long long blocks64 = (long long)batch * ((m + 63) / 64) * ((n + 63) / 64);
   if (prefer_128(batch, m, n))
-    return launch_layout<128, 128, 32, 2, 2>(a, b, c, bias, batch, m, n, k, a_kc, b_kc, vec, act, stream);
+    return launch_layout<128, 128, 32, 2, 2>(a, b, c, bias, batch, m, n, k, a_kc, b_kc, act, stream);
   if (blocks64 >= 192 || k <= 32)
-    return launch_layout<64, 64, 32, 2, 2>(a, b, c, bias, batch, m, n, k, a_kc, b_kc, vec, act, stream);
+    return launch_layout<64, 64, 32, 2, 2>(a, b, c, bias, batch, m, n, k, a_kc, b_kc, act, stream);
   // Small M x N (too few 64 x 64 tiles for the 256 CUs): 16-row tiles, 16 x 32 or, when even those are
   // few, 16 x 16, so that every CU gets a workgroup; the tile depth covers K in one step when K <= 512.
   // These problems are bound by memory latency and by the matrix-core time of a single tile, not by
@@ -832,17 +900,22 @@ int launch_gemm(const float* a, const float* b, float* c, const float* bias, int
   if (m16_direct_supported(a, b, c, bias, batch, n, k, a_kc, b_kc) && (blocks16x32 <= 512 || k <= 512))
     return wide ? launch_m16_direct<2>(a, b, c, bias, m, n, k, act, stream)
                 : launch_m16_direct<1>(a, b, c, bias, m, n, k, act, stream);
+  // rows at any address, or more than two tiles' depth of K: split over up to 16 wavefronts without staging
+  // (513 x 515 x 511: 9.0 us against 13.5 with 64 x 64 tiles; 301 x 2088 x 613: 26.7 against 16.7)
+  if ((!vec || k > 1024) && deep_tiles(batch, m, n) < 1000)
+    return launch_gemm_deep(a, b, c, bias, batch, m, n, k, a_kc, b_kc, act, stream);
+  if (!vec) return launch_layout<64, 64, 32, 2, 2>(a, b, c, bias, batch, m, n, k, a_kc, b_kc, act, stream);
   // more tiles than fit on the chip at once (one 512-deep tile per CU): 128-deep tiles, so that several
   // workgroups share a CU and one's loads overlap another's MFMAs (M = 392, 512 -> 1024: 15.8 -> 11.2 us)
   const int kcap = blocks16x32 > 512 ? 128 : 1 << 30;
   if (k <= 128 || kcap <= 128)
-    return wide ? launch_m16_layout<2, 128, 8>(a, b, c, bias, batch, m, n, k, a_kc, b_kc, vec, act, stream)
-                : launch_m16_layout<1, 128, 8>(a, b, c, bias, batch, m, n, k, a_kc, b_kc, vec, act, stream);
+    return wide ? launch_m16_layout<2, 128, 8>(a, b, c, bias, batch, m, n, k, a_kc, b_kc, act, stream)
+                : launch_m16_layout<1, 128, 8>(a, b, c, bias, batch, m, n, k, a_kc, b_kc, act, stream);
   if (k <= 256 || kcap <= 256)
-    return wide ? launch_m16_layout<2, 256, 8>(a, b, c, bias, batch, m, n, k, a_kc, b_kc, vec, act, stream)
-                : launch_m16_layout<1, 256, 8>(a, b, c, bias, batch, m, n, k, a_kc, b_kc, vec, act, stream);
-  return wide ? launch_m16_layout<2, 512, 8>(a, b, c, bias, batch, m, n, k, a_kc, b_kc, vec, act, stream)
-              : launch_m16_layout<1, 512, 8>(a, b, c, bias, batch, m, n, k, a_kc, b_kc, vec, act, stream);
+    return wide ? launch_m16_layout<2, 256, 8>(a, b, c, bias, batch, m, n, k, a_kc, b_kc, act, stream)
+                : launch_m16_layout<1, 256, 8>(a, b, c, bias, batch, m, n, k, a_kc, b_kc, act, stream);
+  return wide ? launch_m16_layout<2, 512, 8>(a, b, c, bias, batch, m, n, k, a_kc, b_kc, act, stream)
+              : launch_m16_layout<1, 512, 8>(a, b, c, bias, batch, m, n, k, a_kc, b_kc, act, stream);
 }
 
 // 3x3 convolution of a small feature map (few 16 x 32 output tiles) with 16 / 32 / 64 / 128 input channels: one
@@ -857,11 +930,18 @@ int launch_conv3x3_direct(const ConvA& cv, const float* w, const float* bias, fl
   return check_launch();
 }
 
+// Any geometry and channel counts with at least 8 elements of x and filter (conv2d_gemm_supported).
+bool conv2d_gemm_supported(long long x_elems, int fh, int fw, int ci, int co) {
+  const long long k = (long long)fh * fw * ci;
+  return x_elems >= 8 && k * co >= 8 && k * co < (1LL << 31) && (long long)fh * fw * (ci + 7) < (1LL << 24);
+}
+
 int launch_conv2d_gemm(const float* x, const float* w, const float* bias, float* y, int n, int h, int wd, int ci, int fh,
                        int fw, int co, int oh, int ow, int sh, int sw, int pt, int pl, int act, hipStream_t stream) {
   const long long m = (long long)n * oh * ow, k = (long long)fh * fw * ci;
   if (m > 0x7fffffffLL || k > 0x7fffffffLL) return TFX_ERR_UNSUPPORTED;
-  const ConvA cv{x, h, wd, ci, oh, ow, fw, sh, sw, pt, pl};
+  const ConvA cv{x,  h,  wd, ci, oh, ow, fw, sh, sw, pt, pl, (unsigned)((long long)n * h * wd * ci), fast_div((unsigned)fw),
+                 fast_div((unsigned)ow), fast_div((unsigned)oh), FilterK{fast_div((unsigned)((ci + 3) / 4 * 4)), fh * fw}};
   const bool vec = reinterpret_cast<uintptr_t>(x) % 16 == 0 && reinterpret_cast<uintptr_t>(w) % 16 == 0 &&
                    ci % 4 == 0 && co % 4 == 0;
   // small maps (at most 512 tiles of 16 x 32: the tiled kernel would leave most CUs idle and run its 9 Ci / 32 k-slices
@@ -874,18 +954,17 @@ int launch_conv2d_gemm(const float* x, const float* w, const float* bias, float*
     if (ci == 64) return launch_conv3x3_direct<64>(cv, w, bias, y, (int)m, co, act, stream);
     if (ci == 128) return launch_conv3x3_direct<128>(cv, w, bias, y, (int)m, co, act, stream);
   }
+  // few output tiles (or next to nothing to contract): split the contraction over the wavefronts of a workgroup
+  // (gemm_deep.hip; 3x3, 14x14x512 -> 512 at batch 4: 92 against 111 us; 5x5 s2, 112x112x3 -> 24 at batch 16: 11.5
+  // against 16.2; 3x3, 14x14x256 -> 256 at batch 16: 98 against 58)
+  if (deep_tiles(1, (int)m, co) < (k <= 128 ? 3200 : 1000))
+    return launch_conv2d_deep(x, w, bias, y, n, h, wd, ci, fh, fw, co, oh, ow, sh, sw, pt, pl, act, stream);
   // k-slices of 32 inside one filter tap, one validity bit per tap: the lean loader
   const bool lean = vec && ci % 32 == 0 && fh * fw <= 32;
-  if (lean)
-    return prefer_128(1, m, co)
-               ? launch_cfg<128, 128, 32, 2, 2, true, false, true, true, true>(nullptr, w, y, bias, 1, (int)m, co, (int)k, act, stream, cv)
-               : launch_cfg<64, 64, 32, 2, 2, true, false, true, true, true>(nullptr, w, y, bias, 1, (int)m, co, (int)k, act, stream, cv);
-  if (prefer_128(1, m, co)) {
-    return vec ? launch_cfg<128, 128, 32, 2, 2, true, false, true, true>(nullptr, w, y, bias, 1, (int)m, co, (int)k, act, stream, cv)
-               : launch_cfg<128, 128, 32, 2, 2, true, false, false, true>(nullptr, w, y, bias, 1, (int)m, co, (int)k, act, stream, cv);
-  }
-  return vec ? launch_cfg<64, 64, 32, 2, 2, true, false, true, true>(nullptr, w, y, bias, 1, (int)m, co, (int)k, act, stream, cv)
-             : launch_cfg<64, 64, 32, 2, 2, true, false, false, true>(nullptr, w, y, bias, 1, (int)m, co, (int)k, act, stream, cv);
+#define TFX_CONV(T, FORM) launch_cfg<T, T, 32, 2, 2, true, false, FORM>(nullptr, w, y, bias, 1, (int)m, co, (int)k, act, stream, cv)
+  if (prefer_128(1, m, co)) return lean ? TFX_CONV(128, kConvLean) : ci % 4 == 0 ? TFX_CONV(128, kConvAligned) : TFX_CONV(128, kConvRagged);
+  return lean ? TFX_CONV(64, kConvLean) : ci % 4 == 0 ? TFX_CONV(64, kConvAligned) : TFX_CONV(64, kConvRagged);
+#undef TFX_CONV
 }
 
 }  // namespace tfx

@@ -9,9 +9,9 @@
 // padding: the 16-byte fragment reads of 32 consecutive rows fall on distinct banks).  The MFMA is
 // issued with the operands swapped (B's fragment first), so a lane's accumulator registers hold 4
 // consecutive output columns of one row and the epilogue stores 8 bytes at a time.
-// Two kernels: a software-pipelined one for K-contiguous, 16-byte aligned operands (A stored
-// [M,K], B stored [N,K]) and a general one with an element-wise loader for everything else.
-#include "tfx_internal.h"
+// One software-pipelined kernel takes every layout, size and alignment (ragged.h has the loads); small outputs with a
+// long contraction go to gemm_deep.hip.
+#include "ragged.h"
 
 #include <type_traits>
 
@@ -27,170 +27,40 @@ constexpr int kBK = 64;       // halfs per k-slice
 constexpr int kLd = kBK + 8;  // LDS row stride in halfs
 constexpr int kXcds = 8;
 
-// ---- element-wise global -> register loader for one ROWS x 64 slice of an operand ----------------
-// Any layout, any K, any alignment.  kc: K is the contiguous dimension in memory
-// (element (row, k) at row * ld + k), else the row index is (element at k * ld + row).
-// Consecutive threads walk along the contiguous dimension.
-template <int ROWS, int NT>
-__device__ __forceinline__ void load_scalar(const half_t* __restrict__ g, bool kc, int ld, int rows, int K, int row0,
-                                            int k0, int tid, half_t (&r)[ROWS * kBK / NT]) {
-#pragma unroll
-  for (int i = 0; i < ROWS * kBK / NT; ++i) {
-    const int e = tid + i * NT;
-    const int row = row0 + (kc ? e / kBK : e % ROWS), k = k0 + (kc ? e % kBK : e / ROWS);
-    const size_t idx = kc ? (size_t)row * ld + k : (size_t)k * ld + row;
-    r[i] = (row < rows && k < K) ? g[idx] : (half_t)0;
-  }
-}
-template <int ROWS, int NT>
-__device__ __forceinline__ void store_scalar(half_t* lds, bool kc, int tid, const half_t (&r)[ROWS * kBK / NT]) {
-#pragma unroll
-  for (int i = 0; i < ROWS * kBK / NT; ++i) {
-    const int e = tid + i * NT;
-    const int row = kc ? e / kBK : e % ROWS, k = kc ? e % kBK : e / ROWS;
-    lds[row * kLd + k] = r[i];
-  }
+// One thread per output element: operands of fewer elements than a 16-byte load (gemm_any_f16.hip has everything else
+// that the pipelined kernel does not take).
+__global__ __launch_bounds__(256) void gemm_tiny_f16_kernel(const half_t* __restrict__ A, const half_t* __restrict__ B,
+                                                            half_t* __restrict__ C, const half_t* __restrict__ bias, int M, int N,
+                                                            int K, int a_kc, int b_kc, long long total, int act) {
+  const long long e = (long long)blockIdx.x * 256 + threadIdx.x;
+  if (e >= total) return;
+  const int col = (int)(e % N);
+  const long long r = e / N, batch = r / M;
+  const int row = (int)(r % M);
+  float sum = 0.f;
+  for (int k = 0; k < K; ++k)
+    sum += (float)A[batch * M * K + (a_kc ? (long long)row * K + k : (long long)k * M + row)] *
+           (float)B[batch * N * K + (b_kc ? (long long)col * K + k : (long long)k * N + col)];
+  C[e] = (half_t)apply_act(sum + (bias != nullptr ? (float)bias[col] : 0.f), act);
 }
 
-// General kernel: operands of any layout and alignment through the element-wise loader; the slice
-// kt+1 is fetched into registers before the MFMAs of slice kt and written to LDS after them.
-template <int WAVES_M, int WAVES_N, int TM, int TN>
-__global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_f16_kernel(
-    const half_t* __restrict__ A, const half_t* __restrict__ B, half_t* __restrict__ C, const half_t* __restrict__ bias,
-    int M, int N, int K, int a_kc, int b_kc, int tiles_m, int tiles_n, int total_blocks, long long strideA,
-    long long strideB, long long strideC, int act, int group_m, int c_vec) {
-  constexpr int kNT = 64 * WAVES_M * WAVES_N;
-  constexpr int WM = 32 * TM, WN = 32 * TN;
-  constexpr int BM = WM * WAVES_M, BN = WN * WAVES_N;
-  constexpr int kTileA = BM * kLd, kTileB = BN * kLd;  // halfs per LDS buffer
-  extern __shared__ __align__(16) half_t smem_h[];
-  half_t* const lds_a = smem_h;  // two A buffers, then two B buffers
-  half_t* const lds_b = smem_h + 2 * kTileA;
-
-  // Hardware block id x lands on XCD x % 8: give each XCD (own L2) a contiguous range of tiles.
-  const int bid = blockIdx.x;
-  const int q = total_blocks / kXcds, rem = total_blocks % kXcds;
-  const int xcd = bid % kXcds;
-  const int vid = xcd * q + (xcd < rem ? xcd : rem) + bid / kXcds;
-  const int tiles = tiles_m * tiles_n;
-  const int batch = vid / tiles;
-  const int t = vid % tiles;
-  // within a batch, tiles are walked in bands of group_m tile rows, column by column, so that the
-  // tiles an XCD works on at the same time form a compact block (few distinct A and B panels)
-  const int band = t / (group_m * tiles_n);
-  const int band_rows = min(group_m, tiles_m - band * group_m);
-  const int tb = t - band * group_m * tiles_n;
-  const int tile_m = band * group_m + tb % band_rows;
-  const int tile_n = tb / band_rows;
-
-  const int lda = a_kc ? K : M, ldb = b_kc ? K : N;
-  A += (size_t)batch * strideA;
-  B += (size_t)batch * strideB;
-  C += (size_t)batch * strideC;
-
-  const int tid = threadIdx.x;
-  const int wave = tid / 64, lane = tid % 64;
-  const int wm0 = (wave / WAVES_N) * WM, wn0 = (wave % WAVES_N) * WN;
-  const int li = lane % 32, hh = lane / 32;
-  const int m0 = tile_m * BM, n0 = tile_n * BN;
-
-  f32x16 acc[TM][TN];
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
-
-  half_t ra[BM * kBK / kNT], rb[BN * kBK / kNT];
-  auto load = [&](int k0) {
-    load_scalar<BM, kNT>(A, a_kc != 0, lda, M, K, m0, k0, tid, ra);
-    load_scalar<BN, kNT>(B, b_kc != 0, ldb, N, K, n0, k0, tid, rb);
-  };
-  auto store = [&](int buf) {
-    store_scalar<BM, kNT>(lds_a + buf * kTileA, a_kc != 0, tid, ra);
-    store_scalar<BN, kNT>(lds_b + buf * kTileB, b_kc != 0, tid, rb);
-  };
-
-  const int nk = (K + kBK - 1) / kBK;
-  load(0);
-  store(0);
-  __syncthreads();
-
-  for (int kt = 0; kt < nk; ++kt) {
-    const int cur = kt & 1;
-    if (kt + 1 < nk) load((kt + 1) * kBK);
-    const half_t* la = lds_a + cur * kTileA + (wm0 + li) * kLd + 8 * hh;
-    const half_t* lb = lds_b + cur * kTileB + (wn0 + li) * kLd + 8 * hh;
-    h8 fa[2][TM], fb[2][TN];
-#pragma unroll
-    for (int i = 0; i < TM; ++i) fa[0][i] = *reinterpret_cast<const h8*>(la + 32 * i * kLd);
-#pragma unroll
-    for (int j = 0; j < TN; ++j) fb[0][j] = *reinterpret_cast<const h8*>(lb + 32 * j * kLd);
-#pragma unroll
-    for (int s = 0; s < kBK / 16; ++s) {
-      if (s + 1 < kBK / 16) {
-#pragma unroll
-        for (int i = 0; i < TM; ++i) fa[(s + 1) & 1][i] = *reinterpret_cast<const h8*>(la + 32 * i * kLd + 16 * (s + 1));
-#pragma unroll
-        for (int j = 0; j < TN; ++j) fb[(s + 1) & 1][j] = *reinterpret_cast<const h8*>(lb + 32 * j * kLd + 16 * (s + 1));
-      }
-      __builtin_amdgcn_sched_barrier(0);  // keep those LDS reads ahead of this step's MFMAs
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fb[s & 1][j], fa[s & 1][i], acc[i][j], 0, 0, 0);
-    }
-    if (kt + 1 < nk) store(cur ^ 1);
-    __syncthreads();
-  }
-
-  // Epilogue.  acc[i][j][v] is the output at row m0 + wm0 + 32 i + li, column
-  // n0 + wn0 + 32 j + 8 (v / 4) + 4 hh + v % 4: four consecutive columns per register quad.
-  const ActClamp clamp = make_act(act);
-#pragma unroll
-  for (int i = 0; i < TM; ++i) {
-    const int row = m0 + wm0 + 32 * i + li;
-    if (row >= M) continue;
-    half_t* crow = C + (size_t)row * N;
-#pragma unroll
-    for (int j = 0; j < TN; ++j) {
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const int col = n0 + wn0 + 32 * j + 8 * g + 4 * hh;
-        if (col >= N) continue;
-        float o[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const float bv = (bias != nullptr && col + e < N) ? (float)bias[col + e] : 0.f;
-          o[e] = apply_act(acc[i][j][4 * g + e] + bv, clamp);
-        }
-        if (c_vec && col + 3 < N) {
-          h4 pk = {(half_t)o[0], (half_t)o[1], (half_t)o[2], (half_t)o[3]};
-          *reinterpret_cast<h4*>(crow + col) = pk;
-        } else {
-#pragma unroll
-          for (int e = 0; e < 4; ++e)
-            if (col + e < N) crow[col + e] = (half_t)o[e];
-        }
-      }
-    }
-  }
-}
-
-// Software-pipelined variant for K-contiguous, 16-byte aligned operands.  The vector memory
+// Software-pipelined tile kernel.  The vector memory
 // path delivers 64 bytes per clock to a CU, so a k-slice's global loads take a large part of the
 // slice's MFMA time and must be spread evenly through it; the same holds for the LDS writes.
 // Iteration kt (slice kt in LDS buffer kt & 1):
 // after every few MFMAs one 16-byte slot of slice kt+1 (loaded a whole iteration earlier) moves from
 // its registers to the other LDS buffer and the same registers are refilled with that slot of slice
 // kt+2; one barrier per slice.
-template <int WAVES_M, int WAVES_N, int TM, int TN, bool B_KC>
+//
+// Alignment and remainders cost nothing in that loop: the 16-byte loads and stores work at any address (rows that start
+// at an odd half cost about 30 % of the kernel's time, 4-byte aligned ones nothing), and only slices that reach past K,
+// or hold a [K,N] operand's last row when N % 8 != 0, go through the masked form.  (They used to be fetched half by half:
+// 1999 x 1001 x 1023 42 us.)
+template <int WAVES_M, int WAVES_N, int TM, int TN, bool A_KC, bool B_KC>
 __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_f16_pipe_kernel(
     const half_t* __restrict__ A, const half_t* __restrict__ B, half_t* __restrict__ C, const half_t* __restrict__ bias,
-    int M, int N, int K, int tiles_m, int tiles_n, int total_blocks, long long strideA, long long strideB,
-    long long strideC, int act, int group_m, int c_vec) {
+    int M, int N, int K, int tiles_m, int tiles_n, int total_blocks, int full_slices, long long strideA, long long strideB,
+    long long strideC, int act, int group_m) {
   constexpr int kNT = 64 * WAVES_M * WAVES_N;
   constexpr int WM = 32 * TM, WN = 32 * TN;
   constexpr int BM = WM * WAVES_M, BN = WN * WAVES_N;
@@ -199,6 +69,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_f16_pipe_kernel(
   constexpr int STEPS = kBK / 16, MF = TM * TN;  // k-steps per slice, MFMAs per step
   static_assert(BM * 8 % kNT == 0 && BN * 8 % kNT == 0, "loader shape");
   static_assert(B_KC || (SB == 4 && kNT / 16 == BN / 8), "the [K,N] loader moves 4 k-rows x 8 columns per thread");
+  static_assert(A_KC || (SA == 4 && kNT / 16 == BM / 8), "and so does the [K,M] loader");
   extern __shared__ __align__(16) half_t smem_h[];
   half_t* const lds_a = smem_h;
   half_t* const lds_b = smem_h + 2 * kTileA;
@@ -234,93 +105,111 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_f16_pipe_kernel(
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
 
-  // slot w of a slice: w < SA is A's slot w, else B's slot w - SA; slot i of an operand covers
+  // slot w of a slice: w < SA is A's slot w, else B's slot w - SA; slot i of a K-contiguous operand covers
   // tile row (tid + i * kNT) / 8, halfs 8 * ((tid + i * kNT) % 8) ... + 7.  Rows past the matrix
   // are clamped to its last row (they only feed outputs that are never stored) and k-slices are
   // clamped to the last one, so every load is unconditional and in bounds; halfs past K are zeroed
   // with a mask.  The loop body therefore has no branch.
-  const int srow = tid / 8, scol = 8 * (tid % 8);
-  constexpr int kRowStep = kNT / 8;
-  typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
   //
-  // B stored [K,N] (!B_KC, N % 8 == 0): thread (kq = tid % 16, nb = tid / 16) loads k-rows 4 kq ... + 3 of
+  // An operand stored [K,N] or [K,M]: thread (kq = tid % 16, nb = tid / 16) loads k-rows 4 kq ... + 3 of
   // columns 8 nb ... + 7 as four 16-byte slots (16 lanes with consecutive kq: the 8-byte LDS writes of
   // one row are contiguous), transposes the 4 x 8 block in registers and writes, for each of the 8
   // columns, 4 consecutive k to the K-contiguous LDS row of that column.  The block is written when
   // its first slot comes up in the schedule, its slots are refilled one by one.
+  const int srow = tid / 8, scol = 8 * (tid % 8);
+  constexpr int kRowStep = kNT / 8;
+  typedef ragged_u32x4 u32x4;
   u32x4 reg[SLOTS];
   unsigned boff[SLOTS];  // byte offset of the slot at k0 = 0 from its operand's base (operands hold < 2^31 elements)
   const int kq = tid % 16, nb = tid / 16;
-  const unsigned bcol = n0 + 8 * nb < N ? (unsigned)(n0 + 8 * nb) : 0u;  // past N: any valid column block
+  // past the matrix: any valid column block
+  const unsigned acol = m0 + 8 * nb < M ? (unsigned)(m0 + 8 * nb) : 0u, bcol = n0 + 8 * nb < N ? (unsigned)(n0 + 8 * nb) : 0u;
 #pragma unroll
   for (int w = 0; w < SLOTS; ++w) {
     const bool is_a = w < SA;
     const int i = is_a ? w : w - SA;
-    if (is_a || B_KC) {
+    if (is_a ? A_KC : B_KC) {
       const int row = min((is_a ? m0 : n0) + srow + i * kRowStep, (is_a ? M : N) - 1);
       boff[w] = 2u * ((unsigned)row * (unsigned)K + (unsigned)scol);
     } else {
-      boff[w] = 2u * ((unsigned)(4 * kq + i) * (unsigned)N + bcol);
+      boff[w] = 2u * ((unsigned)(4 * kq + i) * (unsigned)(is_a ? M : N) + (is_a ? acol : bcol));
     }
   }
   const int nk = (K + kBK - 1) / kBK;
   const int k_last = (nk - 1) * kBK;
+  // Where the masked form of slot w of the slice at k0 starts (element offset; any valid place for a slot past K), and
+  // how many halfs early it is fetched so as not to leave the operand.
+  auto masked_offset = [&](int w, int k0, unsigned* early) {
+    const bool is_a = w < SA;
+    unsigned off;
+    if (is_a ? A_KC : B_KC) {
+      off = boff[w] / 2u + (k0 + scol < K ? (unsigned)k0 : 0u - (unsigned)scol);
+    } else {
+      const int k = k0 + 4 * kq + (is_a ? w : w - SA);
+      off = (k < K ? (unsigned)k : 0u) * (unsigned)(is_a ? M : N) + (is_a ? acol : bcol);
+    }
+    const unsigned at = min(off, (unsigned)(is_a ? strideA : strideB) - 8u);
+    *early = off - at;
+    return at;
+  };
   // FULL: the slice starting at k0 lies inside K.  Then a load is the operand's base advanced by the slice
   // (uniform, scalar registers) plus the slot's constant 32-bit offset, and a store needs no mask: no vector
   // ALU instruction per slot (each one would take issue time from the matrix cores).
   auto load_slot = [&](int w, int k0, auto full) {
-    const char* g = reinterpret_cast<const char*>(w < SA ? A : B);
-    if (w < SA || B_KC) {
-      if constexpr (decltype(full)::value) {
-        reg[w] = *reinterpret_cast<const u32x4*>(g + 2 * (size_t)k0 + boff[w]);
-      } else {
-        // past K: the start of the slot's row (a valid address), zeroed when stored
-        const unsigned off = k0 + scol < K ? boff[w] + 2u * (unsigned)k0 : boff[w] - 2u * (unsigned)scol;
-        reg[w] = *reinterpret_cast<const u32x4*>(g + off);
-      }
+    const bool is_a = w < SA;
+    const half_t* g = is_a ? A : B;
+    if constexpr (decltype(full)::value) {
+      const size_t advance = (is_a ? A_KC : B_KC) ? (size_t)k0 : (size_t)k0 * (size_t)(is_a ? M : N);
+      reg[w] = load16(reinterpret_cast<const half_t*>(reinterpret_cast<const char*>(g + advance) + boff[w]));
     } else {
-      if constexpr (decltype(full)::value) {
-        reg[w] = *reinterpret_cast<const u32x4*>(g + 2 * (size_t)k0 * (size_t)N + boff[w]);
-      } else {
-        const int k = k0 + 4 * kq + (w - SA);
-        const unsigned off = k < K ? boff[w] + 2u * (unsigned)k0 * (unsigned)N : 2u * bcol;  // past K: row 0
-        reg[w] = *reinterpret_cast<const u32x4*>(g + off);
-      }
+      unsigned early;
+      reg[w] = load16(g + masked_offset(w, k0, &early));
     }
   };
   // k0: first k of the slice the registers hold; the zeroing of halfs past K happens here, when the
   // registers are consumed, so that nothing waits on a load right after issuing it
+  auto settled = [&](int w, int k0) {
+    unsigned early;
+    masked_offset(w, k0, &early);
+    return __builtin_amdgcn_ballot_w64(early != 0) != 0 ? shift_down<half_t>(reg[w], early) : reg[w];
+  };
   auto store_slot = [&](int w, int buf, int k0, auto full) {
     constexpr bool FULL = decltype(full)::value;
-    if (w < SA || B_KC) {
-      const bool is_a = w < SA;
-      const int i = is_a ? w : w - SA;
-      half_t* l = is_a ? lds_a + buf * kTileA : lds_b + buf * kTileB;
-      const unsigned mask = (FULL || k0 + scol < K) ? 0xffffffffu : 0u;
-      *reinterpret_cast<u32x4*>(l + (srow + i * kRowStep) * kLd + scol) = FULL ? reg[w] : reg[w] & mask;
-    } else if (w == SA) {
+    const bool is_a = w < SA;
+    const int i = is_a ? w : w - SA;
+    half_t* const l = is_a ? lds_a + buf * kTileA : lds_b + buf * kTileB;
+    if (is_a ? A_KC : B_KC) {
+      *reinterpret_cast<u32x4*>(l + (srow + i * kRowStep) * kLd + scol) =
+          FULL ? reg[w] : settled(w, k0) & first_elements<half_t>(K - (k0 + scol));
+    } else if (i == 0) {
       h8 r[4];
 #pragma unroll
       for (int kk = 0; kk < 4; ++kk) {
         const unsigned mask = (FULL || k0 + 4 * kq + kk < K) ? 0xffffffffu : 0u;
-        r[kk] = __builtin_bit_cast(h8, FULL ? reg[SA + kk] : reg[SA + kk] & mask);
+        r[kk] = __builtin_bit_cast(h8, FULL ? reg[w + kk] : settled(w + kk, k0) & mask);
       }
-      half_t* l = lds_b + buf * kTileB + (8 * nb) * kLd + 4 * kq;
+      half_t* const lt = l + (8 * nb) * kLd + 4 * kq;
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const h4 o = {r[0][i], r[1][i], r[2][i], r[3][i]};
-        *reinterpret_cast<h4*>(l + i * kLd) = o;
+      for (int c = 0; c < 8; ++c) {
+        const h4 o = {r[0][c], r[1][c], r[2][c], r[3][c]};
+        *reinterpret_cast<h4*>(lt + c * kLd) = o;
       }
     }
   };
   constexpr std::false_type kMasked{};
 
+  auto prologue = [&](auto full) {
 #pragma unroll
-  for (int w = 0; w < SLOTS; ++w) load_slot(w, 0, kMasked);
+    for (int w = 0; w < SLOTS; ++w) load_slot(w, 0, full);
 #pragma unroll
-  for (int w = 0; w < SLOTS; ++w) store_slot(w, 0, 0, kMasked);
-#pragma unroll
-  for (int w = 0; w < SLOTS; ++w) load_slot(w, min(kBK, k_last), kMasked);
+    for (int w = 0; w < SLOTS; ++w) {
+      store_slot(w, 0, 0, full);
+      // (the block of a [K,N] operand is stored when its first slot comes up: refill only behind that)
+      load_slot(w, decltype(full)::value ? kBK : min(kBK, k_last), full);
+    }
+  };
+  if (full_slices >= 2) prologue(std::true_type{});
+  else prologue(kMasked);
   __syncthreads();
 
   // One k-slice.  FULL: slices kt + 1 (stored) and kt + 2 (fetched) both lie inside K.
@@ -366,113 +255,72 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_f16_pipe_kernel(
     __syncthreads();
   };
   int kt = 0;
-  for (; (kt + 3) * kBK <= K; ++kt) k_slice(kt, std::true_type{});
+  for (; kt + 2 < full_slices; ++kt) k_slice(kt, std::true_type{});
   for (; kt < nk; ++kt) k_slice(kt, kMasked);
 
+  // Epilogue: every wavefront converts its WM x WN block to binary16 in a private LDS region (all k-slice buffers are
+  // free after the loop's last barrier), then reads it back row-wise and stores 16 bytes per lane, 128 bytes of a row at
+  // a time, at whatever address that is.
   const ActClamp clamp = make_act(act);
-  if (c_vec == 2) {
-    // Staged epilogue (N % 8 == 0, C 16-byte aligned): every wavefront converts its WM x WN block to
-    // binary16 in a private LDS region (all k-slice buffers are free after the loop's last barrier),
-    // then reads it back row-wise and stores 16 bytes per lane, whole 128-byte lines per row.
-    constexpr int kLs = WN + 8;  // staging row stride in halfs
-    static_assert((size_t)WAVES_M * WAVES_N * WM * kLs <= 2 * (size_t)(BM + BN) * kLd, "staging fits in the slice buffers");
-    half_t* stage = smem_h + wave * WM * kLs;
+  constexpr int kLs = WN + 8;  // staging row stride in halfs
+  static_assert((size_t)WAVES_M * WAVES_N * WM * kLs <= 2 * (size_t)(BM + BN) * kLd, "staging fits in the slice buffers");
+  half_t* stage = smem_h + wave * WM * kLs;
 #pragma unroll
-    for (int j = 0; j < TN; ++j) {
+  for (int j = 0; j < TN; ++j) {
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const int cl = 32 * j + 8 * g + 4 * hh;  // column inside the wave's block
-        const int col = n0 + wn0 + cl;
-        float bv[4];
+    for (int g = 0; g < 4; ++g) {
+      const int cl = 32 * j + 8 * g + 4 * hh;  // column inside the wave's block
+      const int col = n0 + wn0 + cl;
+      float bv[4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) bv[e] = (bias != nullptr && col + e < N) ? (float)bias[col + e] : 0.f;
+      for (int e = 0; e < 4; ++e) bv[e] = (bias != nullptr && col + e < N) ? (float)bias[col + e] : 0.f;
 #pragma unroll
-        for (int i = 0; i < TM; ++i) {
-          h4 pk;
+      for (int i = 0; i < TM; ++i) {
+        h4 pk;
 #pragma unroll
-          for (int e = 0; e < 4; ++e) pk[e] = (half_t)apply_act(acc[i][j][4 * g + e] + bv[e], clamp);
-          *reinterpret_cast<h4*>(stage + (32 * i + li) * kLs + cl) = pk;
-        }
+        for (int e = 0; e < 4; ++e) pk[e] = (half_t)apply_act(acc[i][j][4 * g + e] + bv[e], clamp);
+        *reinterpret_cast<h4*>(stage + (32 * i + li) * kLs + cl) = pk;
       }
     }
-    constexpr int kLanesPerRow = WN / 8, kRowsPerStep = 64 / kLanesPerRow;
-    const int rr = lane / kLanesPerRow, cc = 8 * (lane % kLanesPerRow);
-    const int col = n0 + wn0 + cc;
-#pragma unroll
-    for (int r0 = 0; r0 < WM; r0 += kRowsPerStep) {
-      const int row = m0 + wm0 + r0 + rr;
-      const h8 v = *reinterpret_cast<const h8*>(stage + (r0 + rr) * kLs + cc);
-      if (row < M && col < N) *reinterpret_cast<h8*>(C + (size_t)row * N + col) = v;
-    }
-    return;
   }
+  constexpr int kLanesPerRow = WN / 8, kRowsPerStep = 64 / kLanesPerRow;
+  const int rr = lane / kLanesPerRow, cc = 8 * (lane % kLanesPerRow);
+  const int col = n0 + wn0 + cc;
 #pragma unroll
-  for (int i = 0; i < TM; ++i) {
-    const int row = m0 + wm0 + 32 * i + li;
-    if (row >= M) continue;
-    half_t* crow = C + (size_t)row * N;
+  for (int r0 = 0; r0 < WM; r0 += kRowsPerStep) {
+    const int row = m0 + wm0 + r0 + rr;
+    const h8 v = *reinterpret_cast<const h8*>(stage + (r0 + rr) * kLs + cc);
+    if (row >= M || col >= N) continue;
+    half_t* const cp = C + (size_t)row * N + col;
+    if (col + 8 <= N) {
+      *reinterpret_cast<ragged_u32x4_any*>(cp) = __builtin_bit_cast(u32x4, v);
+    } else {
 #pragma unroll
-    for (int j = 0; j < TN; ++j) {
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const int col = n0 + wn0 + 32 * j + 8 * g + 4 * hh;
-        if (col >= N) continue;
-        float o[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const float bv = (bias != nullptr && col + e < N) ? (float)bias[col + e] : 0.f;
-          o[e] = apply_act(acc[i][j][4 * g + e] + bv, clamp);
-        }
-        if (c_vec && col + 3 < N) {
-          h4 pk = {(half_t)o[0], (half_t)o[1], (half_t)o[2], (half_t)o[3]};
-          *reinterpret_cast<h4*>(crow + col) = pk;
-        } else {
-#pragma unroll
-          for (int e = 0; e < 4; ++e)
-            if (col + e < N) crow[col + e] = (half_t)o[e];
-        }
-      }
+      for (int e = 0; e < 8; ++e)
+        if (col + e < N) cp[e] = v[e];
     }
   }
 }
 
-template <int WAVES_M, int WAVES_N, int TM, int TN, bool B_KC = true>
-int launch_pipe(const half_t* a, const half_t* b, half_t* c, const half_t* bias, int batch, int m, int n, int k,
-                bool, bool, int act, hipStream_t stream, int group_m = 4) {
+template <int WAVES_M, int WAVES_N, int TM, int TN, bool A_KC, bool B_KC>
+int launch_pipe(const half_t* a, const half_t* b, half_t* c, const half_t* bias, int batch, int m, int n, int k, int act,
+                hipStream_t stream) {
   constexpr int BM = 32 * TM * WAVES_M, BN = 32 * TN * WAVES_N, NT = 64 * WAVES_M * WAVES_N;
   constexpr size_t lds_bytes = 2 * (size_t)(BM + BN) * kLd * sizeof(half_t);
   static_assert(lds_bytes <= 160 * 1024, "LDS budget per workgroup");
-  auto kern = gemm_f16_pipe_kernel<WAVES_M, WAVES_N, TM, TN, B_KC>;
+  auto kern = gemm_f16_pipe_kernel<WAVES_M, WAVES_N, TM, TN, A_KC, B_KC>;
   static std::atomic<uint64_t> lds_allowed{0};
   if (allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds_bytes, lds_allowed) != TFX_OK) return TFX_ERR_LAUNCH;
   const int tiles_m = (m + BM - 1) / BM, tiles_n = (n + BN - 1) / BN;
   const long long total = (long long)batch * tiles_m * tiles_n;
   if (total > 0x7fffffffLL) return TFX_ERR_UNSUPPORTED;
-  // 2: staged 16-byte stores (every row of C starts 16-byte aligned), 1: direct 8-byte stores, 0: element stores
-  const int c_vec = (n % 8 == 0 && reinterpret_cast<uintptr_t>(c) % 16 == 0) ? 2
-                    : (n % 4 == 0 && reinterpret_cast<uintptr_t>(c) % 8 == 0) ? 1 : 0;
+  // slices that need no mask: inside K, and without the last row of an operand whose rows end inside a 16-byte load
+  // (fewer than 8 columns: every load of a row reaches into later ones, so none)
+  auto rows_of_8 = [](bool kc, int inner) { return kc || inner % 8 == 0; };
+  int full = rows_of_8(A_KC, m) && rows_of_8(B_KC, n) ? k / kBK : (k - 1) / kBK;
+  if ((!A_KC && m < 8) || (!B_KC && n < 8)) full = 0;
   hipLaunchKernelGGL(kern, dim3((unsigned)total), dim3(NT), lds_bytes, stream, a, b, c, bias, m, n, k, tiles_m, tiles_n,
-                     (int)total, (long long)m * k, (long long)n * k, (long long)m * n, act, group_m, c_vec);
-  return check_launch();
-}
-
-template <int WAVES_M, int WAVES_N, int TM, int TN>
-int launch_cfg(const half_t* a, const half_t* b, half_t* c, const half_t* bias, int batch, int m, int n, int k,
-               bool a_kc, bool b_kc, int act, hipStream_t stream, int group_m = 4) {
-  constexpr int BM = 32 * TM * WAVES_M, BN = 32 * TN * WAVES_N, NT = 64 * WAVES_M * WAVES_N;
-  constexpr size_t lds_bytes = 2 * (size_t)(BM + BN) * kLd * sizeof(half_t);
-  static_assert(lds_bytes <= 160 * 1024, "LDS budget per workgroup");
-  auto kern = gemm_f16_kernel<WAVES_M, WAVES_N, TM, TN>;
-  static std::atomic<uint64_t> lds_allowed{0};
-  if (allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds_bytes, lds_allowed) != TFX_OK) return TFX_ERR_LAUNCH;
-  const int tiles_m = (m + BM - 1) / BM, tiles_n = (n + BN - 1) / BN;
-  const long long total = (long long)batch * tiles_m * tiles_n;
-  if (total > 0x7fffffffLL) return TFX_ERR_UNSUPPORTED;
-  // 8-byte stores need every row of C to start 8-byte aligned
-  const int c_vec = (n % 4 == 0 && reinterpret_cast<uintptr_t>(c) % 8 == 0) ? 1 : 0;
-  hipLaunchKernelGGL(kern, dim3((unsigned)total), dim3(NT), lds_bytes, stream, a, b, c, bias, m, n, k, a_kc ? 1 : 0,
-                     b_kc ? 1 : 0, tiles_m, tiles_n, (int)total, (long long)m * k, (long long)n * k,
-                     (long long)m * n, act, group_m, c_vec);
+                     (int)total, full, (long long)m * k, (long long)n * k, (long long)m * n, act, 4);
   return check_launch();
 }
 
@@ -612,43 +460,47 @@ int launch_gemm_f16(const uint16_t* a16, const uint16_t* b16, uint16_t* c16, con
   const half_t* b = reinterpret_cast<const half_t*>(b16);
   half_t* c = reinterpret_cast<half_t*>(c16);
   const half_t* bias = reinterpret_cast<const half_t*>(bias16);
-  // 16-byte loads: both operands K-contiguous, K a multiple of 8 (then every row and every batch
-  // starts 16-byte aligned if the base pointers do)
-  const bool aligned = reinterpret_cast<uintptr_t>(a) % 16 == 0 && reinterpret_cast<uintptr_t>(b) % 16 == 0;
-  const bool vec = a_kc && b_kc && k % 8 == 0 && aligned;
-  // A [M,K] with B stored [K,N] (matMul without transposes, a pointwise convolution's filter): 16-byte
-  // loads along N and a register transpose on the way into LDS
-  const bool vec_kn = a_kc && !b_kc && k % 8 == 0 && n % 8 == 0 && aligned;
+  if ((long long)m * k < 8 || (long long)n * k < 8) {
+    const long long total = (long long)batch * m * n;
+    hipLaunchKernelGGL(gemm_tiny_f16_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, stream, a, b, c, bias, m, n, k,
+                       a_kc ? 1 : 0, b_kc ? 1 : 0, total, act);
+    return check_launch();
+  }
   auto tiles = [&](int bm, int bn) { return (long long)batch * ((m + bm - 1) / bm) * ((n + bn - 1) / bn); };
-  // a tile shape is acceptable if it wastes at most 10% more of its area on padding than 128 x 128 tiles do
+  // a tile shape is acceptable if it wastes at most 20% more of its area on padding than 128 x 128 tiles do
   auto fits = [&](int bm, int bn) {
     const double pad = (double)((m + bm - 1) / bm * bm) * ((n + bn - 1) / bn * bn);
     const double pad128 = (double)((m + 127) / 128 * 128) * ((n + 127) / 128 * 128);
-    return pad <= 1.1 * pad128;
+    return pad <= 1.2 * pad128;
   };
-  if (vec) {
-    // 256 x 256 tiles (8 wavefronts) once they fill most of the 256 CUs, then 256 x 128 (8 wavefronts),
-    // 128 x 128 (4 wavefronts, two workgroups per CU) for mid-size problems, 64 x 64 below that
-    if (tiles(256, 256) >= 192 && fits(256, 256))
-      return launch_pipe<2, 4, 4, 2>(a, b, c, bias, batch, m, n, k, true, true, act, stream);
-    if (tiles(256, 128) >= 192 && fits(256, 128))
-      return launch_pipe<4, 2, 2, 2>(a, b, c, bias, batch, m, n, k, true, true, act, stream);
-    if (tiles(128, 128) >= 128) return launch_pipe<2, 2, 2, 2>(a, b, c, bias, batch, m, n, k, true, true, act, stream);
-    return launch_pipe<2, 2, 1, 1>(a, b, c, bias, batch, m, n, k, true, true, act, stream);
-  }
+  // the pointwise-convolution layout, a thin or deep filter held in LDS, or small outputs
   if (batch == 1 && a_kc && !b_kc && pointwise_stream_f16_supported(m, k, n, a, b, c))
     return launch_pointwise_stream_f16(a16, b16, bias16, c16, m, k, n, act, stream);
   if (batch == 1 && a_kc && !b_kc && pointwise_slab_f16_supported(m, k, n, a, b, c))
     return launch_pointwise_slab_f16(a16, b16, bias16, c16, m, k, n, act, stream);
-  if (vec_kn) {
-    if (tiles(256, 256) >= 192 && fits(256, 256))
-      return launch_pipe<2, 4, 4, 2, false>(a, b, c, bias, batch, m, n, k, true, false, act, stream);
-    if (tiles(128, 128) >= 128) return launch_pipe<2, 2, 2, 2, false>(a, b, c, bias, batch, m, n, k, true, false, act, stream);
-    if (tiles(64, 64) >= 128) return launch_pipe<2, 1, 1, 2, false>(a, b, c, bias, batch, m, n, k, true, false, act, stream);
+  const bool aligned = reinterpret_cast<uintptr_t>(a) % 16 == 0 && reinterpret_cast<uintptr_t>(b) % 16 == 0;
+  if (a_kc && !b_kc && k % 8 == 0 && n % 8 == 0 && aligned && tiles(64, 64) < 128)
     return launch_small(a, b, c, bias, batch, m, n, k, act, stream);
-  }
-  if (tiles(128, 128) >= 256) return launch_cfg<2, 2, 2, 2>(a, b, c, bias, batch, m, n, k, a_kc, b_kc, act, stream);
-  return launch_cfg<2, 2, 1, 1>(a, b, c, bias, batch, m, n, k, a_kc, b_kc, act, stream);
+  // few output tiles: split the contraction over the wavefronts of a workgroup (256 x 256 x 1024, B [N,K]: 4.3 against
+  // 6.5 us with 64 x 64 tiles; 512^3: 6.2 against 5.1, A [K,M] 6.4 against 8.2)
+  if (deep_tiles(batch, m, n) < (a_kc && b_kc ? 400 : 580))
+    return launch_gemm_deep_f16(a16, b16, c16, bias16, batch, m, n, k, a_kc, b_kc, act, stream);
+  auto pick = [&](auto akc, auto bkc) {
+    constexpr bool A_KC = decltype(akc)::value, B_KC = decltype(bkc)::value;
+    // 256 x 256 tiles (8 wavefronts) once they fill half of the 256 CUs (3001^3: 144 tiles, 111 us against 159 with
+    // 128 x 128), then 256 x 128 (8 wavefronts), 128 x 128 (4 wavefronts, two workgroups per CU) from one per CU on
+    // (2000 x 1000 x 1024, 128 tiles: 12.6 us against 10.3 with 64 x 64), 64 x 64 below that
+    if (tiles(256, 256) >= 136 && fits(256, 256))
+      return launch_pipe<2, 4, 4, 2, A_KC, B_KC>(a, b, c, bias, batch, m, n, k, act, stream);
+    if constexpr (A_KC && B_KC)
+      if (tiles(256, 128) >= 192 && fits(256, 128))
+        return launch_pipe<4, 2, 2, 2, A_KC, B_KC>(a, b, c, bias, batch, m, n, k, act, stream);
+    if (tiles(128, 128) >= 256) return launch_pipe<2, 2, 2, 2, A_KC, B_KC>(a, b, c, bias, batch, m, n, k, act, stream);
+    if constexpr (A_KC && B_KC) return launch_pipe<2, 2, 1, 1, A_KC, B_KC>(a, b, c, bias, batch, m, n, k, act, stream);
+    else return launch_pipe<2, 1, 1, 2, A_KC, B_KC>(a, b, c, bias, batch, m, n, k, act, stream);
+  };
+  if (a_kc) return b_kc ? pick(std::true_type{}, std::true_type{}) : pick(std::true_type{}, std::false_type{});
+  return b_kc ? pick(std::false_type{}, std::true_type{}) : pick(std::false_type{}, std::false_type{});
 }
 
 }  // namespace tfx
