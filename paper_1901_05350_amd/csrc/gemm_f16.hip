@@ -488,14 +488,14 @@ int launch_gemm_f16(const uint16_t* a16, const uint16_t* b16, uint16_t* c16, con
   auto pick = [&](auto akc, auto bkc) {
     constexpr bool A_KC = decltype(akc)::value, B_KC = decltype(bkc)::value;
     // 256 x 256 tiles (8 wavefronts) once they fill half of the 256 CUs (3001^3: 144 tiles, 111 us against 159 with
-    // 128 x 128), then 256 x 128 (8 wavefronts), 128 x 128 (4 wavefronts, two workgroups per CU) from one per CU on
+    // 128 x 128), then 256 x 128 (8 wavefronts), 128 x 128 (4 wavefronts, two workgroups per CU) from three per four CUs on
     // (2000 x 1000 x 1024, 128 tiles: 12.6 us against 10.3 with 64 x 64), 64 x 64 below that
     if (tiles(256, 256) >= 136 && fits(256, 256))
       return launch_pipe<2, 4, 4, 2, A_KC, B_KC>(a, b, c, bias, batch, m, n, k, act, stream);
     if constexpr (A_KC && B_KC)
       if (tiles(256, 128) >= 192 && fits(256, 128))
         return launch_pipe<4, 2, 2, 2, A_KC, B_KC>(a, b, c, bias, batch, m, n, k, act, stream);
-    if (tiles(128, 128) >= 256) return launch_pipe<2, 2, 2, 2, A_KC, B_KC>(a, b, c, bias, batch, m, n, k, act, stream);
+    if (tiles(128, 128) >= 192) return launch_pipe<2, 2, 2, 2, A_KC, B_KC>(a, b, c, bias, batch, m, n, k, act, stream);
     if constexpr (A_KC && B_KC) return launch_pipe<2, 2, 1, 1, A_KC, B_KC>(a, b, c, bias, batch, m, n, k, act, stream);
     else return launch_pipe<2, 1, 1, 2, A_KC, B_KC>(a, b, c, bias, batch, m, n, k, act, stream);
   };
