@@ -5,75 +5,59 @@
 // "pointwise" conv2d, which is the same contraction with M = N*H*W, K = inC, N = outC.
 // The paper's shader computes one output per fragment with no data sharing; here a
 // workgroup computes a tile, stages A and B k-slices through LDS and feeds the matrix cores
-// (64-wide wavefronts): v_mfma_f32_32x32x2_f32 in the tiled kernel for medium and large
-// problems, v_mfma_f32_16x16x4_f32 in the 16-row kernel for small M x N.
+// (64-wide wavefronts): v_mfma_f32_32x32x16_bf16 on three-way split operands (split.h) in the tiled kernel for
+// medium and large problems, v_mfma_f32_16x16x4_f32 in the 16-row kernel for small M x N.
 //
-// Layout of one MFMA 32x32x2 (wave64), used below:
-//   A operand: lane l holds A[i = l % 32][k = l / 32]
-//   B operand: lane l holds B[k = l / 32][j = l % 32]
+// Layout of one MFMA 32x32x16 (wave64), used below:
+//   A operand: lane l holds A[i = l % 32][k = 8*(l/32) .. + 7]
+//   B operand: lane l holds B[k = 8*(l/32) .. + 7][j = l % 32]
 //   D result : register v of lane l holds D[i = 8*(v/4) + 4*(l/32) + v%4][j = l % 32]
-// The contraction index may be permuted freely as long as A and B agree, so within a
-// group of 8 consecutive k a lane with h = l/32 takes k = 8g + 4h + s in step s = 0..3.
-// That makes a lane's four steps one contiguous float4 in a K-contiguous LDS tile.
 #include "ragged.h"
+#include "split.h"
 
+#include <cmath>
 #include <type_traits>
 
 namespace tfx {
-
-typedef float floatx16 __attribute__((ext_vector_type(16)));
 
 namespace {
 
 constexpr int kXcds = 8;  // workgroups are dealt round-robin to the 8 XCDs, each with its own L2
 
-// LDS tile of one operand.  KC = true : stored [ROWS][BK + 4]  (k contiguous, padded rows)
-//                           KC = false: stored [BK][ROWS]      (row index contiguous)
-template <int ROWS, int BK, bool KC>
-struct Tile {
-  static constexpr int kStride = KC ? (BK + 4) : ROWS;
-  static constexpr int kFloats = KC ? ROWS * (BK + 4) : BK * ROWS;
-  static constexpr int kSlots = ROWS * BK / 4;  // float4 slots per tile
-};
-
-// Global -> registers for one operand tile whose rows are 16-byte aligned (the 16-row kernel).  Slot s of the tile is one
-// float4:
-//   KC : row r = s / (BK/4), k = 4 * (s % (BK/4))       -> g[(row0 + r) * ld + k0 + k .. +3]
-//   !KC: k = s / (ROWS/4),   r = 4 * (s % (ROWS/4))     -> g[(k0 + k) * ld + row0 + r .. +3]
-// Out-of-range elements read as zero, so ragged M, N and K tails add nothing.
-template <int ROWS, int BK, bool KC, int NT, int NSLOT>
-__device__ __forceinline__ void load_tile(const float* __restrict__ g, int ld, int rows_total, int k_total, int row0,
-                                          int k0, int tid, float4 (&reg)[NSLOT]) {
-#pragma unroll
-  for (int it = 0; it < NSLOT; ++it) {
-    const int s = tid + it * NT;
-    const int gr = row0 + (KC ? s / (BK / 4) : 4 * (s % (ROWS / 4))), gk = k0 + (KC ? 4 * (s % (BK / 4)) : s / (ROWS / 4));
-    reg[it] = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (gr < rows_total && gk < k_total)
-      reg[it] = *reinterpret_cast<const float4*>(g + (KC ? (size_t)gr * ld + gk : (size_t)gk * ld + gr));
-  }
-}
-
-// Branch-free variant for k-slices that lie entirely inside K.  A thread's slots keep a
+// Branch-free loads for k-slices that lie entirely inside K.  A thread's slots keep a
 // pointer each, set up once: rows past the end of the operand are clamped to a valid row instead of masked --
 // they only feed output rows / columns that are never stored -- so a k-slice is NSLOT unconditional loads and
 // no other vector instruction (on this chip every vector-ALU instruction takes issue time away from the
 // matrix cores: the masked loader's compares, zero fills and branches cost ~10% of the main loop).  The loads need no
 // alignment; a slot of a row-contiguous operand may reach past the end of its row into the next one, so the slice with
 // the last row is not one of these when the row length is no multiple of 4.
+//
+// Slots of the tiled kernel: s = tid + it * NT;
+//   KC : row s / (BK/4), k = 4 * (s % (BK/4)) .. + 3
+//   !KC: a thread's four slots are four consecutive k of the same four rows (block b = tid: rows 4 * (b % (ROWS/4)),
+//        k = 4 * (b / (ROWS/4)) + it), so that it can hand each row's four k on together
+template <int ROWS, int BK, bool KC, int NT, int NSLOT>
+__device__ __forceinline__ int slot_row(int tid, int it) {
+  static_assert(KC || (NSLOT == 4 && ROWS * BK == 16 * NT), "one 4 x 4 block per thread");
+  return KC ? (tid + it * NT) / (BK / 4) : 4 * (tid % (ROWS / 4));
+}
+template <int ROWS, int BK, bool KC, int NT>
+__device__ __forceinline__ int slot_k(int tid, int it) {
+  return KC ? 4 * ((tid + it * NT) % (BK / 4)) : 4 * (tid / (ROWS / 4)) + it;
+}
 template <int ROWS, int BK, bool KC, int NT, int NSLOT>
 __device__ __forceinline__ void slot_pointers(const float* __restrict__ g, int ld, int rows_total, int row0, int tid,
                                               const float* (&ptr)[NSLOT]) {
 #pragma unroll
   for (int it = 0; it < NSLOT; ++it) {
-    const int s = tid + it * NT;
+    int gr = row0 + slot_row<ROWS, BK, KC, NT, NSLOT>(tid, it);
+    const int k = slot_k<ROWS, BK, KC, NT>(tid, it);
     if (KC) {
-      const int gr = min(row0 + s / (BK / 4), rows_total - 1);
-      ptr[it] = g + (size_t)gr * ld + 4 * (s % (BK / 4));
+      gr = min(gr, rows_total - 1);
+      ptr[it] = g + (size_t)gr * ld + k;
     } else {
-      int gr = row0 + 4 * (s % (ROWS / 4));
       if (gr >= rows_total) gr = 0;
-      ptr[it] = g + (size_t)(s / (ROWS / 4)) * ld + gr;
+      ptr[it] = g + (size_t)k * ld + gr;
     }
   }
 }
@@ -93,17 +77,16 @@ struct FilterK {
   FastDiv by_cp;
   int taps;
 };
-template <int ROWS, int BK, bool KC, bool CV, int NT>
+template <int ROWS, int BK, bool KC, bool CV, int NT, int NSLOT>
 __device__ __forceinline__ unsigned slot_offset(int ld, int rows_total, int k_total, int row0, int k0, int tid, int it,
                                                 unsigned total, const FilterK& fk, unsigned* early, int* valid) {
-  const int s = tid + it * NT;
+  int gr = row0 + slot_row<ROWS, BK, KC, NT, NSLOT>(tid, it), gk = k0 + slot_k<ROWS, BK, KC, NT>(tid, it);
   unsigned off;
   if (KC) {
-    const int gr = min(row0 + s / (BK / 4), rows_total - 1), gk = k0 + 4 * (s % (BK / 4));
+    gr = min(gr, rows_total - 1);
     *valid = k_total - gk;
     off = (unsigned)gr * (unsigned)ld + (unsigned)(*valid > 0 ? gk : 0);
   } else {
-    int gr = row0 + 4 * (s % (ROWS / 4)), gk = k0 + s / (ROWS / 4);
     if (gr >= rows_total) gr = 0;
     bool in;
     if constexpr (CV) {
@@ -127,7 +110,7 @@ __device__ __forceinline__ void load_tile_any(const float* __restrict__ g, int l
   for (int it = 0; it < NSLOT; ++it) {
     unsigned early;
     int valid;
-    reg[it] = load_quad(g + slot_offset<ROWS, BK, KC, CV, NT>(ld, rows_total, k_total, row0, k0, tid, it, total, fk, &early, &valid));
+    reg[it] = load_quad(g + slot_offset<ROWS, BK, KC, CV, NT, NSLOT>(ld, rows_total, k_total, row0, k0, tid, it, total, fk, &early, &valid));
   }
 }
 template <int ROWS, int BK, bool KC, bool CV, int NT, int NSLOT>
@@ -137,26 +120,10 @@ __device__ __forceinline__ void settle_tile(int ld, int rows_total, int k_total,
   for (int it = 0; it < NSLOT; ++it) {
     unsigned early;
     int valid;
-    slot_offset<ROWS, BK, KC, CV, NT>(ld, rows_total, k_total, row0, k0, tid, it, total, fk, &early, &valid);
+    slot_offset<ROWS, BK, KC, CV, NT, NSLOT>(ld, rows_total, k_total, row0, k0, tid, it, total, fk, &early, &valid);
     ragged_u32x4 v = __builtin_bit_cast(ragged_u32x4, reg[it]);
     if (__builtin_amdgcn_ballot_w64(early != 0) != 0) v = shift_down<float>(v, early);
     reg[it] = __builtin_bit_cast(float4, v & first_elements<float>(valid));
-  }
-}
-
-template <int ROWS, int BK, bool KC, int NT, int NSLOT>
-__device__ __forceinline__ void store_tile(float* __restrict__ lds, int tid, const float4 (&reg)[NSLOT]) {
-  using T = Tile<ROWS, BK, KC>;
-#pragma unroll
-  for (int it = 0; it < NSLOT; ++it) {
-    const int s = tid + it * NT;
-    int off;
-    if (KC) {
-      off = (s / (BK / 4)) * T::kStride + 4 * (s % (BK / 4));
-    } else {
-      off = (s / (ROWS / 4)) * T::kStride + 4 * (s % (ROWS / 4));
-    }
-    *reinterpret_cast<float4*>(lds + off) = reg[it];
   }
 }
 
@@ -288,24 +255,54 @@ __device__ __forceinline__ void load_tile_conv_lean(const float* (&p0)[NSLOT], c
   }
 }
 
-// MFMA operand of one 32-row sub-tile for k-group g: four steps' values for this lane.
-template <int ROWS, int BK, bool KC>
-__device__ __forceinline__ float4 read_frag(const float* __restrict__ lds, int row, int g, int h) {
-  using T = Tile<ROWS, BK, KC>;
-  if (KC) {
-    return *reinterpret_cast<const float4*>(lds + row * T::kStride + 8 * g + 4 * h);
-  } else {
-    const float* p = lds + (8 * g + 4 * h) * T::kStride + row;
-    return make_float4(p[0], p[T::kStride], p[2 * T::kStride], p[3 * T::kStride]);
-  }
-}
-
 __device__ __forceinline__ float f4_get(const float4& v, int s) {
   return s == 0 ? v.x : (s == 1 ? v.y : (s == 2 ? v.z : v.w));
 }
 
-// Tiled kernel for medium and large problems: BM x BN tile, BK-deep k-slices double-buffered in LDS
-// (one barrier per slice), WAVES_M x WAVES_N wavefronts each owning a (BM/WAVES_M) x (BN/WAVES_N) sub-tile.
+// LDS tile of one operand of the tiled kernel: three planes (hi, mid, lo) of ROWS rows of 32 k, k contiguous, in
+// pieces of 8 k (16 bytes).  Rows of a !KC operand are stored in the order row % 4, row / 4: then the writes of a
+// wavefront, one row of every thread's 4 x 4 block at a time, and the fragment reads, 32 consecutive rows, both spread
+// over all banks with the piece order rotated as below.
+template <int ROWS, bool KC>
+struct PlaneTile {
+  static constexpr int kPlane = ROWS * 64;  // bytes
+  static constexpr int kBytes = kParts * kPlane;
+  static __device__ __forceinline__ int at(int row, int piece) {  // byte offset of a piece in its plane
+    const int r = KC ? row : (row % 4) * (ROWS / 4) + row / 4;
+    const int turn = KC ? (r / 8) & 3 : ((r / 8) ^ row) & 3;
+    return r * 64 + ((piece ^ turn) * 16);
+  }
+};
+
+// Registers -> LDS: splits a thread's slots and writes four k of a row at a time (8 bytes per plane).
+template <int ROWS, int BK, bool KC, int NT, int NSLOT>
+__device__ __forceinline__ void store_planes(char* __restrict__ lds, int tid, const float4 (&reg)[NSLOT], TinyGuard& guard) {
+  using T = PlaneTile<ROWS, KC>;
+  static_assert(BK == 32, "rows of 32 k");
+#pragma unroll
+  for (int it = 0; it < NSLOT; ++it) {
+    floatx4 v;
+    int row = slot_row<ROWS, BK, KC, NT, NSLOT>(tid, KC ? it : 0), k;
+    if constexpr (KC) {
+      v = floatx4{reg[it].x, reg[it].y, reg[it].z, reg[it].w};
+      k = slot_k<ROWS, BK, KC, NT>(tid, it);
+    } else {
+      row += it;
+      v = floatx4{f4_get(reg[0], it), f4_get(reg[1], it), f4_get(reg[2], it), f4_get(reg[3], it)};
+      k = slot_k<ROWS, BK, KC, NT>(tid, 0);
+    }
+    guard.see(v);
+    splitx4 part[kParts];
+    split4(v, part);
+    char* const p = lds + T::at(row, k / 8) + (k % 8) * 2;
+#pragma unroll
+    for (int q = 0; q < kParts; ++q) *reinterpret_cast<splitx4*>(p + q * T::kPlane) = part[q];
+  }
+}
+
+
+// Tiled kernel for medium and large problems: BM x BN tile, k-slices of 32 in LDS as bf16 planes, the next slice in
+// registers meanwhile; WAVES_M x WAVES_N wavefronts each owning a (BM/WAVES_M) x (BN/WAVES_N) sub-tile.
 // CONV: the A operand is the implicit im2col view `cv` of a convolution input instead of a matrix.
 // (A convolution: its output channels contiguous in B.)  CONV_RAGGED: its channel count is no multiple of 4.
 enum ConvForm { kNoConv, kConvLean, kConvAligned, kConvRagged };
@@ -319,16 +316,14 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_mfma_kernel(
   constexpr int NT = 64 * WAVES_M * WAVES_N;
   constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;
   constexpr int TM = WM / 32, TN = WN / 32;
-  constexpr int GROUPS = BK / 8;  // k-groups of 8 per tile
-  static_assert(WM % 32 == 0 && WN % 32 == 0 && BK % 8 == 0, "tile shape");
-  using TA = Tile<BM, BK, A_KC>;
-  using TB = Tile<BN, BK, B_KC>;
-  static_assert(TA::kSlots % NT == 0 && TB::kSlots % NT == 0, "loader shape");
-  constexpr int SA = TA::kSlots / NT, SB = TB::kSlots / NT;
+  static_assert(WM % 32 == 0 && WN % 32 == 0 && BK == 32, "tile shape");
+  using TA = PlaneTile<BM, A_KC>;
+  using TB = PlaneTile<BN, B_KC>;
+  static_assert(BM * BK / 4 % NT == 0 && BN * BK / 4 % NT == 0, "loader shape");
+  constexpr int SA = BM * BK / 4 / NT, SB = BN * BK / 4 / NT;
 
-  extern __shared__ __align__(16) float smem[];
-  float* const lds_a = smem;                    // two A buffers, then two B buffers
-  float* const lds_b = smem + 2 * TA::kFloats;
+  __shared__ __align__(16) char lds_a[TA::kBytes];
+  __shared__ __align__(16) char lds_b[TB::kBytes];
 
   // XCD-aware block order: hardware block id x lands on XCD x % 8.  Give each XCD a contiguous
   // range of logical tiles (same batch, neighbouring tiles) so that its L2 sees each A / B panel once.
@@ -390,7 +385,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_mfma_kernel(
   const unsigned total_a = (unsigned)strideA, total_b = (unsigned)strideB;
   const int kb = FORM == kConvRagged ? cv.Ci : K;  // valid k of B (per tap)
   // FULL: k-slice kt is known to lie inside K (for both operands)
-  auto load_a = [&](int kt, auto full) {
+  auto load_a = [&](int kt, auto full) __attribute__((always_inline)) {
     if constexpr (LEAN) {
       load_tile_conv_lean<SA>(cp0, cok, tap_idx, ((long long)tap_kh * cv.W + tap_kw) * cv.Ci + tap_c0, ra);
       tap_c0 += BK;
@@ -406,72 +401,109 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_mfma_kernel(
     else if constexpr (decltype(full)::value) load_tile_full<SA>(pa, kt * step_a, ra);
     else load_tile_any<BM, BK, A_KC, false, NT, SA>(A, lda, M, K, m0, kt * BK, tid, total_a, cv.fk, ra);
   };
-  auto load_b = [&](int kt, auto full) {
+  auto load_b = [&](int kt, auto full) __attribute__((always_inline)) {
     if constexpr (FORM != kConvRagged && decltype(full)::value) load_tile_full<SB>(pb, kt * step_b, rb);
     else load_tile_any<BN, BK, B_KC, FORM == kConvRagged, NT, SB>(B, ldb, N, kb, n0, kt * BK, tid, total_b, cv.fk, rb);
   };
-  auto store = [&](int kt, int buf, auto full) {
+  TinyGuard guard;
+  auto store = [&](int kt, auto full) __attribute__((always_inline)) {
     if constexpr (CONV && !LEAN) settle_tile_conv<BK, FORM == kConvRagged, SA>(cv, kt * BK, tid, crow, ra);
     else if constexpr (!CONV && !decltype(full)::value)
       settle_tile<BM, BK, A_KC, false, NT, SA>(lda, M, K, m0, kt * BK, tid, total_a, cv.fk, ra);
     if constexpr (FORM == kConvRagged || !decltype(full)::value)
       settle_tile<BN, BK, B_KC, FORM == kConvRagged, NT, SB>(ldb, N, kb, n0, kt * BK, tid, total_b, cv.fk, rb);
-    store_tile<BM, BK, A_KC, NT, SA>(lds_a + buf * TA::kFloats, tid, ra);
-    store_tile<BN, BK, B_KC, NT, SB>(lds_b + buf * TB::kFloats, tid, rb);
+    store_planes<BM, BK, A_KC, NT, SA>(lds_a, tid, ra, guard);
+    store_planes<BN, BK, B_KC, NT, SB>(lds_b, tid, rb, guard);
   };
-  auto first = [&](auto full) {
+  auto first = [&](auto full) __attribute__((always_inline)) {
     load_a(0, full);
     load_b(0, full);
-    store(0, 0, full);
+    store(0, full);
   };
   if (nk_full > 0) first(std::true_type{});
   else first(std::false_type{});
   __syncthreads();
 
-  // One k-slice: fetch slice kt + 1 into registers, multiply slice kt from LDS, hand the registers to the other
-  // LDS buffer.  NEXT_FULL: slice kt + 1 exists and lies inside K.
-  auto k_slice = [&](int kt, auto next_full) {
+  // where this lane's fragments start: row of the tile, piece h of k-step 0 (piece 2 + h of k-step 1)
+  auto read = [&](const char* lds, auto tile, int row, int step, bf16x8 (&frag)[kParts]) __attribute__((always_inline)) {
+    using T = decltype(tile);
+#pragma unroll
+    for (int p = 0; p < kParts; ++p) frag[p] = *reinterpret_cast<const bf16x8*>(lds + T::at(row, 2 * step + h) + p * T::kPlane);
+  };
+  // One k-slice: fetch slice kt + 1 into registers, multiply slice kt from LDS, hand the registers to LDS once every
+  // wavefront has read it.  NEXT_FULL: slice kt + 1 exists and lies inside K.
+  auto k_slice = [&](int kt, auto next_full) __attribute__((always_inline)) {
     constexpr bool NEXT_FULL = decltype(next_full)::value;
-    const int cur = kt & 1, nxt = cur ^ 1;
     if (NEXT_FULL || kt + 1 < nk) {
       load_a(kt + 1, next_full);
       load_b(kt + 1, next_full);
     }
-    const float* la = lds_a + cur * TA::kFloats;
-    const float* lb = lds_b + cur * TB::kFloats;
-    // fragments of k-group gg+1 are fetched from LDS before the MFMAs of group gg are issued
     __builtin_amdgcn_s_setprio(1);  // MFMA phase: do not let the co-resident workgroup's wave cut in
-    float4 fa[2][TM], fb[2][TN];
 #pragma unroll
-    for (int i = 0; i < TM; ++i) fa[0][i] = read_frag<BM, BK, A_KC>(la, wm0 + 32 * i + li, 0, h);
+    for (int step = 0; step < BK / 16; ++step) {
+      bf16x8 fa[TM][kParts], fb[TN][kParts];
 #pragma unroll
-    for (int j = 0; j < TN; ++j) fb[0][j] = read_frag<BN, BK, B_KC>(lb, wn0 + 32 * j + li, 0, h);
+      for (int i = 0; i < TM; ++i) read(lds_a, TA(), wm0 + 32 * i + li, step, fa[i]);
 #pragma unroll
-    for (int gg = 0; gg < GROUPS; ++gg) {
-      const int g = gg;
-      if (gg + 1 < GROUPS) {
+      for (int j = 0; j < TN; ++j) read(lds_b, TB(), wn0 + 32 * j + li, step, fb[j]);
 #pragma unroll
-        for (int i = 0; i < TM; ++i) fa[(gg + 1) & 1][i] = read_frag<BM, BK, A_KC>(la, wm0 + 32 * i + li, g + 1, h);
-#pragma unroll
-        for (int j = 0; j < TN; ++j) fb[(gg + 1) & 1][j] = read_frag<BN, BK, B_KC>(lb, wn0 + 32 * j + li, g + 1, h);
-      }
-      __builtin_amdgcn_sched_barrier(0);  // keep those LDS reads ahead of this group's MFMAs
-#pragma unroll
-      for (int s = 0; s < 4; ++s)
+      for (int s = 0; s < kSplitPasses; ++s)
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
           for (int j = 0; j < TN; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(f4_get(fa[gg & 1][i], s), f4_get(fb[gg & 1][j], s), acc[i][j],
-                                                             0, 0, 0);
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i][split_pass_a(s)], fb[j][split_pass_b(s)], acc[i][j], 0, 0, 0);
     }
     __builtin_amdgcn_s_setprio(0);
-    if (NEXT_FULL || kt + 1 < nk) store(kt + 1, nxt, next_full);
-    __syncthreads();
+    if (NEXT_FULL || kt + 1 < nk) {
+      __syncthreads();
+      store(kt + 1, next_full);
+      __syncthreads();
+    }
   };
   int kt = 0;
   for (; kt + 1 < nk_full; ++kt) k_slice(kt, std::true_type{});
   for (; kt < nk; ++kt) k_slice(kt, std::false_type{});
+  // Values that the split does not carry: blocks with an Inf or NaN (those results), or all blocks after an operand of
+  // tiny magnitude, once more with the fp32 instructions, operands element by element.
+  const bool tiny = __syncthreads_or(guard.tiny());
+#pragma unroll 1
+  for (int block = 0; block < TM * TN; ++block) {
+    unsigned most = 0;
+#pragma unroll
+    for (int x = 0; x < TM * TN; ++x)
+      if (x == block)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) see_result(most, acc[x / TN][x % TN][v]);
+    if (!tiny && __builtin_amdgcn_ballot_w64(overflowed(most)) == 0) continue;
+    const int row = min(m0 + wm0 + 32 * (block / TN) + li, M - 1), col = min(n0 + wn0 + 32 * (block % TN) + li, N - 1);
+    floatx16 exact;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) exact[v] = 0.f;
+    const int depth = CONV ? cv.Ci : K, taps = CONV ? cv.fk.taps : 1;
+    for (int tap = 0; tap < taps; ++tap) {
+      const float* ap = A + (A_KC ? (size_t)row * lda : (size_t)row);
+      bool inside = true;
+      if constexpr (CONV) {
+        const int t = row / cv.OW, n = t / cv.OH, kh = tap / cv.fw;
+        const int ih = (t - n * cv.OH) * cv.sh - cv.pt + kh, iw = (row - t * cv.OW) * cv.sw - cv.pl + tap - kh * cv.fw;
+        inside = ih >= 0 && ih < cv.H && iw >= 0 && iw < cv.W;
+        ap = cv.x + (inside ? (((size_t)n * cv.H + ih) * cv.W + iw) * cv.Ci : 0);
+      }
+      for (int k0 = 0; k0 < depth; k0 += 2) {
+        const int k = k0 + h;
+        const float fa = inside && k < depth ? ap[A_KC ? (size_t)k : (size_t)k * lda] : 0.f;
+        const float fb = k < depth ? B[B_KC ? (size_t)col * ldb + k : ((size_t)tap * depth + k) * ldb + col] : 0.f;
+        exact = __builtin_amdgcn_mfma_f32_32x32x2f32(fa, fb, exact, 0, 0, 0);
+      }
+    }
+#pragma unroll
+    for (int x = 0; x < TM * TN; ++x)
+      if (x == block)
+#pragma unroll
+        for (int v = 0; v < 16; ++v)
+          if (tiny || !__builtin_isfinite(acc[x / TN][x % TN][v])) acc[x / TN][x % TN][v] = exact[v];
+  }
   const ActClamp clamp = make_act(act);
   // Epilogue: bias[col] then activation, one dword per lane per register (two 128-byte rows per store).
 #pragma unroll
@@ -492,13 +524,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_mfma_kernel(
 template <int BM, int BN, int BK, int WAVES_M, int WAVES_N, bool A_KC, bool B_KC, ConvForm FORM = kNoConv>
 int launch_cfg(const float* a, const float* b, float* c, const float* bias, int batch, int m, int n, int k, int act,
                hipStream_t stream, const ConvA& cv = ConvA{}) {
-  using TA = Tile<BM, BK, A_KC>;
-  using TB = Tile<BN, BK, B_KC>;
-  constexpr size_t lds_bytes = 2 * (TA::kFloats + TB::kFloats) * sizeof(float);
-  static_assert(lds_bytes <= 160 * 1024, "LDS budget per workgroup");
   auto kern = gemm_mfma_kernel<BM, BN, BK, WAVES_M, WAVES_N, A_KC, B_KC, FORM>;
-  static std::atomic<uint64_t> lds_allowed{0};
-  if (allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds_bytes, lds_allowed) != TFX_OK) return TFX_ERR_LAUNCH;
   const int tiles_m = (m + BM - 1) / BM, tiles_n = (n + BN - 1) / BN;
   const long long total = (long long)batch * tiles_m * tiles_n;
   if (total > 0x7fffffffLL) return TFX_ERR_UNSUPPORTED;
@@ -508,7 +534,7 @@ int launch_cfg(const float* a, const float* b, float* c, const float* bias, int 
   const bool whole = (FORM != kNoConv || A_KC || m % 4 == 0) && (B_KC || n % 4 == 0);
   int full = whole ? k / BK : (k - 1) / BK;
   if ((FORM == kNoConv && !A_KC && m < 4) || (!B_KC && n < 4) || FORM == kConvRagged) full = 0;
-  hipLaunchKernelGGL(kern, dim3((unsigned)total), dim3(64 * WAVES_M * WAVES_N), lds_bytes, stream, a, b, c,
+  hipLaunchKernelGGL(kern, dim3((unsigned)total), dim3(64 * WAVES_M * WAVES_N), 0, stream, a, b, c,
                      bias, m, n, k, (kp + BK - 1) / BK, full, tiles_m, tiles_n, (int)total, (long long)m * k, (long long)n * k,
                      (long long)m * n, act, n > m ? 1 : 0, cv);
   return check_launch();
@@ -525,158 +551,14 @@ int launch_layout(const float* a, const float* b, float* c, const float* bias, i
 }
 
 // ---------------------------------------------------------------------------------------------
-// Small-M variant: 16 x (16*TN) output tile with v_mfma_f32_16x16x4_f32.
-// MobileNet's 14x14 and 7x7 pointwise layers have M = 196 or 49: with 32 x 32 tiles only 64-112
-// workgroups exist and each needs >= 1.7 us of matrix-core time on its CU.  A 16-row tile doubles or
-// quadruples the number of workgroups (and wastes fewer padded rows: 208 instead of 224 for M = 196).
-// One BK-deep tile (single LDS stage) is split over WAVES_K wavefronts; the partial tiles are added
-// through LDS by 256*TN threads, which also apply the epilogue.
 // Layout of one MFMA 16x16x4 (wave64): A: lane l holds A[i = l % 16][k = l / 16]; B: lane l holds
 // B[k = l / 16][j = l % 16]; D: register v of lane l holds D[i = 4 * (l / 16) + v][j = l % 16].
 // Within a group of 16 consecutive k, lane quarter q = l / 16 takes k = 16g + 4q + s in step s.
 
-template <int ROWS, int BK, bool KC>
-__device__ __forceinline__ float4 read_frag16(const float* __restrict__ lds, int row, int g, int q) {
-  using T = Tile<ROWS, BK, KC>;
-  if (KC) {
-    return *reinterpret_cast<const float4*>(lds + row * T::kStride + 16 * g + 4 * q);
-  } else {
-    const float* p = lds + (16 * g + 4 * q) * T::kStride + row;
-    return make_float4(p[0], p[T::kStride], p[2 * T::kStride], p[3 * T::kStride]);
-  }
-}
-
-template <int TN, int BK, int WAVES_K, bool A_KC, bool B_KC>
-__global__ __launch_bounds__(64 * WAVES_K) void gemm_m16_kernel(
-    const float* __restrict__ A, const float* __restrict__ B, float* __restrict__ C, const float* __restrict__ bias,
-    int M, int N, int K, int tiles_m, int tiles_n, int total_blocks, long long strideA, long long strideB,
-    long long strideC, int act, int m_fastest) {
-  constexpr int BM = 16, BN = 16 * TN;
-  constexpr int NT = 64 * WAVES_K;
-  constexpr int GROUPS = BK / 16 / WAVES_K;  // k-groups of 16 per wavefront per tile
-  constexpr int NACC = 4 / TN;                // accumulator chains per column tile (4 chains in all)
-  static_assert(BK % (16 * WAVES_K) == 0 && (TN == 1 || TN == 2), "tile shape");
-  using TA = Tile<BM, BK, A_KC>;
-  using TB = Tile<BN, BK, B_KC>;
-  static_assert(TA::kSlots % NT == 0 && TB::kSlots % NT == 0, "loader shape");
-  constexpr int SA = TA::kSlots / NT, SB = TB::kSlots / NT;
-  static_assert(WAVES_K * 256 * TN <= TA::kFloats + TB::kFloats, "split-K reduction reuses the tile buffers");
-  static_assert(256 * TN <= NT, "epilogue threads");
-
-  extern __shared__ __align__(16) float smem[];
-  float* const lds_a = smem;
-  float* const lds_b = smem + TA::kFloats;
-
-  const int bid = blockIdx.x;
-  const int q8 = total_blocks / kXcds, rem = total_blocks % kXcds;
-  const int xcd = bid % kXcds;
-  const int vid = xcd * q8 + (xcd < rem ? xcd : rem) + bid / kXcds;
-  const int tiles = tiles_m * tiles_n;
-  const int batch = vid / tiles;
-  const int t = vid % tiles;
-  const int tile_m = m_fastest ? t % tiles_m : t / tiles_n;
-  const int tile_n = m_fastest ? t / tiles_m : t % tiles_n;
-
-  const int lda = A_KC ? K : M;
-  const int ldb = B_KC ? K : N;
-  A += (size_t)batch * strideA;
-  B += (size_t)batch * strideB;
-  C += (size_t)batch * strideC;
-
-  const int tid = threadIdx.x;
-  const int wk = tid / 64, lane = tid % 64;
-  const int li = lane % 16, q = lane / 16;
-  const int m0 = tile_m * BM, n0 = tile_n * BN;
-
-  // epilogue thread e < 256*TN owns output element (row, col) = the value of register v of lane l of
-  // column tile j with e = (j*4 + v)*64 + l; fetch its bias now
-  const int ej = tid / 256, ev = (tid / 64) % 4, el = tid % 64;
-  const int erow = m0 + 4 * (el / 16) + ev, ecol = n0 + 16 * ej + el % 16;
-  float ebias = 0.f;
-  if (tid < 256 * TN && bias != nullptr && ecol < N) ebias = bias[ecol];
-
-  floatx4 acc[NACC][TN];
-#pragma unroll
-  for (int c = 0; c < NACC; ++c)
-#pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) acc[c][j][v] = 0.f;
-
-  float4 ra[SA], rb[SB];
-  const int nk = (K + BK - 1) / BK;
-  load_tile<BM, BK, A_KC, NT, SA>(A, lda, M, K, m0, 0, tid, ra);
-  load_tile<BN, BK, B_KC, NT, SB>(B, ldb, N, K, n0, 0, tid, rb);
-  for (int kt = 0; kt < nk; ++kt) {
-    if (kt > 0) __syncthreads();  // everyone has finished reading the previous tile
-    store_tile<BM, BK, A_KC, NT, SA>(lds_a, tid, ra);
-    store_tile<BN, BK, B_KC, NT, SB>(lds_b, tid, rb);
-    __syncthreads();
-    if (kt + 1 < nk) {
-      load_tile<BM, BK, A_KC, NT, SA>(A, lda, M, K, m0, (kt + 1) * BK, tid, ra);
-      load_tile<BN, BK, B_KC, NT, SB>(B, ldb, N, K, n0, (kt + 1) * BK, tid, rb);
-    }
-#pragma unroll
-    for (int gg = 0; gg < GROUPS; ++gg) {
-      const int g = wk * GROUPS + gg;
-      if (kt * BK + 16 * g >= K) break;  // k-groups past the end of K hold zeros
-      const float4 fa = read_frag16<BM, BK, A_KC>(lds_a, li, g, q);
-      float4 fb[TN];
-#pragma unroll
-      for (int j = 0; j < TN; ++j) fb[j] = read_frag16<BN, BK, B_KC>(lds_b, 16 * j + li, g, q);
-#pragma unroll
-      for (int s = 0; s < 4; ++s)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-          acc[s % NACC][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(f4_get(fa, s), f4_get(fb[j], s), acc[s % NACC][j], 0, 0, 0);
-    }
-  }
-#pragma unroll
-  for (int c = 1; c < NACC; ++c)
-#pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) acc[0][j][v] += acc[c][j][v];
-
-  // add the WAVES_K partial tiles through LDS: layout [wk][j][v][lane]
-  __syncthreads();
-  float* red = smem;
-#pragma unroll
-  for (int j = 0; j < TN; ++j)
-#pragma unroll
-    for (int v = 0; v < 4; ++v) red[(wk * TN * 4 + j * 4 + v) * 64 + lane] = acc[0][j][v];
-  __syncthreads();
-  if (tid < 256 * TN) {
-    float sum = ebias;
-#pragma unroll
-    for (int w = 0; w < WAVES_K; ++w) sum += red[w * TN * 256 + tid];
-    if (erow < M && ecol < N) C[(size_t)erow * N + ecol] = apply_act(sum, make_act(act));
-  }
-}
-
-template <int TN, int BK, int WAVES_K, bool A_KC, bool B_KC>
-int launch_m16_cfg(const float* a, const float* b, float* c, const float* bias, int batch, int m, int n, int k, int act,
-                   hipStream_t stream) {
-  using TA = Tile<16, BK, A_KC>;
-  using TB = Tile<16 * TN, BK, B_KC>;
-  constexpr size_t lds_bytes = (TA::kFloats + TB::kFloats) * sizeof(float);
-  static_assert(lds_bytes <= 160 * 1024, "LDS budget per workgroup");
-  auto kern = gemm_m16_kernel<TN, BK, WAVES_K, A_KC, B_KC>;
-  static std::atomic<uint64_t> lds_allowed{0};
-  if (allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds_bytes, lds_allowed) != TFX_OK) return TFX_ERR_LAUNCH;
-  const int tiles_m = (m + 15) / 16, tiles_n = (n + 16 * TN - 1) / (16 * TN);
-  const long long total = (long long)batch * tiles_m * tiles_n;
-  if (total > 0x7fffffffLL) return TFX_ERR_UNSUPPORTED;
-  hipLaunchKernelGGL(kern, dim3((unsigned)total), dim3(64 * WAVES_K), lds_bytes, stream, a, b, c, bias, m, n, k,
-                     tiles_m, tiles_n, (int)total, (long long)m * k, (long long)n * k, (long long)m * n, act,
-                     n > m ? 1 : 0);
-  return check_launch();
-}
-
 // 16-row tiles without operand staging, for A stored [M,K], B stored [K,N] (the pointwise-conv layout) and
 // K = 64 ... 1024 (a multiple of 16 per wavefront): the WAVES_K wavefronts of a workgroup split K into chunks of 16 ... 128, and every
 // wavefront loads the MFMA operands of its chunk straight into registers -- its row of A as 128-bit loads (4
-// consecutive k, the contraction order permuted inside groups of 16 as in the other kernels) and, for the same
+// consecutive k, the contraction order permuted inside groups of 16) and, for the same
 // k, TN adjacent columns of B as one load (TN = 2: 16 lanes read 128 contiguous bytes of a row of B; output
 // column 2c + j of the 32-column tile is then column c of MFMA column block j).  All loads of a wavefront are
 // issued before its first MFMA; there is no LDS fill and no barrier before the split-K reduction, which takes
@@ -823,16 +705,6 @@ int launch_m16_direct(const float* a, const float* b, float* c, const float* bia
   return check_launch();
 }
 
-template <int TN, int BK, int WAVES_K>
-int launch_m16_layout(const float* a, const float* b, float* c, const float* bias, int batch, int m, int n, int k,
-                      bool a_kc, bool b_kc, int act, hipStream_t stream) {
-  if (a_kc)
-    return b_kc ? launch_m16_cfg<TN, BK, WAVES_K, true, true>(a, b, c, bias, batch, m, n, k, act, stream)
-                : launch_m16_cfg<TN, BK, WAVES_K, true, false>(a, b, c, bias, batch, m, n, k, act, stream);
-  return b_kc ? launch_m16_cfg<TN, BK, WAVES_K, false, true>(a, b, c, bias, batch, m, n, k, act, stream)
-              : launch_m16_cfg<TN, BK, WAVES_K, false, false>(a, b, c, bias, batch, m, n, k, act, stream);
-}
-
 // One thread per output element: operands of fewer elements than a 16-byte load.
 __global__ __launch_bounds__(256) void gemm_tiny_kernel(const float* __restrict__ A, const float* __restrict__ B,
                                                         float* __restrict__ C, const float* __restrict__ bias, int M, int N, int K,
@@ -849,24 +721,21 @@ __global__ __launch_bounds__(256) void gemm_tiny_kernel(const float* __restrict_
   C[e] = apply_act(sum + (bias != nullptr ? bias[col] : 0.f), act);
 }
 
-// Fraction of a tiling's multiply-adds that land inside the m x n output (the rest is padding).
-double tile_efficiency(long long m, long long n, int bm, int bn) {
-  const long long tm = (m + bm - 1) / bm, tn = (n + bn - 1) / bn;
-  return (double)m * (double)n / ((double)tm * bm * (double)tn * bn);
-}
-
-// 128 x 128 tiles when there is one per CU, they are not mostly padding (e.g. n = 64 would waste half
-// of every tile) and they fill the chip's 512 resident slots (two workgroups per CU) evenly: with 392
-// tiles, 120 CUs would run one workgroup while 136 run two, and the kernel lasts as long as the pairs.
-// 64 x 64 tiles are ~20% less efficient per tile but balance almost perfectly (measured crossover).
-bool prefer_128(int batch, long long m, long long n) {
-  const long long blocks128 = (long long)batch * ((m + 127) / 128) * ((n + 127) / 128);
-  if (blocks128 < 256) return false;
-  if (tile_efficiency(m, n, 128, 128) < 0.8 * tile_efficiency(m, n, 64, 64)) return false;
-  const long long slots = 512;
-  const double imbalance = (double)((blocks128 + slots - 1) / slots * slots) / (double)blocks128;
-  return imbalance <= 1.2;
-}
+// Which kernel: the one that a model of their times says is fastest.  A kernel of bm x bn tiles gives
+// c = batch x tiles / 256 of them to a CU (a whole number of rounds while there are few), each of which walks through k:
+//   us = fixed + per_k k + c (per_tile + per_tile_k k)
+// per_k is the memory round trips of a chain that nothing hides, per_tile_k what k costs the CU.  Fitted to the measured
+// times of 226 products and 190 convolutions (sizes 16 ... 4096, channels 3 ... 512; mean error 4 - 18 %); over these its
+// choice costs 2 - 3 % against the fastest kernel of each.
+struct KernelCost {
+  int bm, bn;
+  double fixed, per_k, per_tile, per_tile_k;
+  double us(long long batch, long long m, long long n, double k) const {
+    const double tiles = (double)(batch * ((m + bm - 1) / bm) * ((n + bn - 1) / bn)) / 256.;
+    const double c = tiles <= 2. ? (tiles <= 1. ? 1. : 2.) : tiles + .5;
+    return fixed + per_k * k + c * (per_tile + per_tile_k * k);
+  }
+};
 
 }  // namespace
 
@@ -878,44 +747,24 @@ int launch_gemm(const float* a, const float* b, float* c, const float* bias, int
                        a_kc ? 1 : 0, b_kc ? 1 : 0, total, act);
     return check_launch();
   }
-  // 16-byte aligned rows: base pointers aligned and the contiguous extent of each operand a multiple of 4 (which also
-  // keeps every batch slice aligned)
-  const int a_inner = a_kc ? k : m, b_inner = b_kc ? k : n;
-  const bool vec = (reinterpret_cast<uintptr_t>(a) % 16 == 0) && (reinterpret_cast<uintptr_t>(b) % 16 == 0) &&
-                   (a_inner % 4 == 0) && (b_inner % 4 == 0);
-  // Tile choice.  Large problems: 128 x 128 tiles (best reuse).  Medium: 64 x 64.
-  const long long blocks64 = (long long)batch * ((m + 63) / 64) * ((n + 63) / 64);
-  if (prefer_128(batch, m, n))
-    return launch_layout<128, 128, 32, 2, 2>(a, b, c, bias, batch, m, n, k, a_kc, b_kc, act, stream);
-  if (blocks64 >= 192 || k <= 32)
-    return launch_layout<64, 64, 32, 2, 2>(a, b, c, bias, batch, m, n, k, a_kc, b_kc, act, stream);
-  // Small M x N (too few 64 x 64 tiles for the 256 CUs): 16-row tiles, 16 x 32 or, when even those are
-  // few, 16 x 16, so that every CU gets a workgroup; the tile depth covers K in one step when K <= 512.
-  // These problems are bound by memory latency and by the matrix-core time of a single tile, not by
-  // throughput (measured on the MobileNet 28x28 .. 7x7 pointwise layers: 3.8-6.1 us each).
-  const long long blocks16x32 = (long long)batch * ((m + 15) / 16) * ((n + 31) / 32);
-  const bool wide = blocks16x32 >= 160;
-  // (with more tiles than the chip holds at once and K = 1024 the staged kernel's 128-deep tiles overlap better:
-  // M = 392, 1024 -> 1024: 18.6 us against 26.0)
-  if (m16_direct_supported(a, b, c, bias, batch, n, k, a_kc, b_kc) && (blocks16x32 <= 512 || k <= 512))
-    return wide ? launch_m16_direct<2>(a, b, c, bias, m, n, k, act, stream)
-                : launch_m16_direct<1>(a, b, c, bias, m, n, k, act, stream);
-  // rows at any address, or more than two tiles' depth of K: split over up to 16 wavefronts without staging
-  // (513 x 515 x 511: 9.0 us against 13.5 with 64 x 64 tiles; 301 x 2088 x 613: 26.7 against 16.7)
-  if ((!vec || k > 1024) && deep_tiles(batch, m, n) < 1000)
-    return launch_gemm_deep(a, b, c, bias, batch, m, n, k, a_kc, b_kc, act, stream);
-  if (!vec) return launch_layout<64, 64, 32, 2, 2>(a, b, c, bias, batch, m, n, k, a_kc, b_kc, act, stream);
-  // more tiles than fit on the chip at once (one 512-deep tile per CU): 128-deep tiles, so that several
-  // workgroups share a CU and one's loads overlap another's MFMAs (M = 392, 512 -> 1024: 15.8 -> 11.2 us)
-  const int kcap = blocks16x32 > 512 ? 128 : 1 << 30;
-  if (k <= 128 || kcap <= 128)
-    return wide ? launch_m16_layout<2, 128, 8>(a, b, c, bias, batch, m, n, k, a_kc, b_kc, act, stream)
-                : launch_m16_layout<1, 128, 8>(a, b, c, bias, batch, m, n, k, a_kc, b_kc, act, stream);
-  if (k <= 256 || kcap <= 256)
-    return wide ? launch_m16_layout<2, 256, 8>(a, b, c, bias, batch, m, n, k, a_kc, b_kc, act, stream)
-                : launch_m16_layout<1, 256, 8>(a, b, c, bias, batch, m, n, k, a_kc, b_kc, act, stream);
-  return wide ? launch_m16_layout<2, 512, 8>(a, b, c, bias, batch, m, n, k, a_kc, b_kc, act, stream)
-              : launch_m16_layout<1, 512, 8>(a, b, c, bias, batch, m, n, k, a_kc, b_kc, act, stream);
+  const double us128 = KernelCost{128, 128, 1.5, .026, 4.7, .027}.us(batch, m, n, k);
+  const double us64 = KernelCost{64, 64, 3.6, .026, 1.27, .0102}.us(batch, m, n, k);
+  const double deep = KernelCost{16, n % 2 == 0 ? 32 : 16, 3.2, 0., .245, .0035}.us(batch, m, n, k);
+  const double direct[3] = {KernelCost{64, 64, 1.33, 0., 3.36, .0148}.us(batch, m, n, k),
+                            KernelCost{32, 64, 3.05, .0010, .88, .0090}.us(batch, m, n, k),
+                            KernelCost{32, 32, 3.48, .0012, .28, .0053}.us(batch, m, n, k)};
+  const int form = direct[0] < direct[1] ? (direct[0] < direct[2] ? 0 : 2) : (direct[1] < direct[2] ? 1 : 2);
+  const double best = fmin(fmin(us128, us64), fmin(deep, direct[form]));
+  if (m16_direct_supported(a, b, c, bias, batch, n, k, a_kc, b_kc)) {
+    const bool wide = (long long)((m + 15) / 16) * ((n + 31) / 32) >= 160;
+    if (KernelCost{16, wide ? 32 : 16, 2.63, 0., 0., .0041}.us(1, m, n, k) <= best)
+      return wide ? launch_m16_direct<2>(a, b, c, bias, m, n, k, act, stream)
+                  : launch_m16_direct<1>(a, b, c, bias, m, n, k, act, stream);
+  }
+  if (us128 == best) return launch_layout<128, 128, 32, 2, 2>(a, b, c, bias, batch, m, n, k, a_kc, b_kc, act, stream);
+  if (us64 == best) return launch_layout<64, 64, 32, 1, 2>(a, b, c, bias, batch, m, n, k, a_kc, b_kc, act, stream);
+  if (deep == best) return launch_gemm_deep(a, b, c, bias, batch, m, n, k, a_kc, b_kc, act, stream);
+  return launch_gemm_direct(a, b, c, bias, batch, m, n, k, a_kc, b_kc, act, stream, form);
 }
 
 // 3x3 convolution of a small feature map (few 16 x 32 output tiles) with 16 / 32 / 64 / 128 input channels: one
@@ -954,15 +803,22 @@ int launch_conv2d_gemm(const float* x, const float* w, const float* bias, float*
     if (ci == 64) return launch_conv3x3_direct<64>(cv, w, bias, y, (int)m, co, act, stream);
     if (ci == 128) return launch_conv3x3_direct<128>(cv, w, bias, y, (int)m, co, act, stream);
   }
-  // few output tiles (or next to nothing to contract): split the contraction over the wavefronts of a workgroup
-  // (gemm_deep.hip; 3x3, 14x14x512 -> 512 at batch 4: 92 against 111 us; 5x5 s2, 112x112x3 -> 24 at batch 16: 11.5
-  // against 16.2; 3x3, 14x14x256 -> 256 at batch 16: 98 against 58)
-  if (deep_tiles(1, (int)m, co) < (k <= 128 ? 3200 : 1000))
-    return launch_conv2d_deep(x, w, bias, y, n, h, wd, ci, fh, fw, co, oh, ow, sh, sw, pt, pl, act, stream);
+  const double kp = (double)fh * fw * ((ci + 7) / 8 * 8);
+  const double us128 = KernelCost{128, 128, 3.84, .031, 2.58, .0335}.us(1, m, co, kp);
+  const double us64 = KernelCost{64, 64, 4.49, .033, .79, .0138}.us(1, m, co, kp);
+  const double deep = KernelCost{16, co % 2 == 0 ? 32 : 16, 2.94, 0., .31, .0046}.us(1, m, co, kp);
+  const double direct[3] = {KernelCost{64, 64, 1.17, 0., 3.72, .0167}.us(1, m, co, kp),
+                            KernelCost{32, 64, 2.74, .0036, 1.16, .0095}.us(1, m, co, kp),
+                            KernelCost{32, 32, 3.12, .0042, .49, .0057}.us(1, m, co, kp)};
+  const int form = direct[0] < direct[1] ? (direct[0] < direct[2] ? 0 : 2) : (direct[1] < direct[2] ? 1 : 2);
+  const double best = fmin(fmin(us128, us64), fmin(deep, direct[form]));
+  if (deep == best) return launch_conv2d_deep(x, w, bias, y, n, h, wd, ci, fh, fw, co, oh, ow, sh, sw, pt, pl, act, stream);
+  if (direct[form] == best)
+    return launch_conv2d_gemm_direct(x, w, bias, y, n, h, wd, ci, fh, fw, co, oh, ow, sh, sw, pt, pl, act, stream, form);
   // k-slices of 32 inside one filter tap, one validity bit per tap: the lean loader
   const bool lean = vec && ci % 32 == 0 && fh * fw <= 32;
-#define TFX_CONV(T, FORM) launch_cfg<T, T, 32, 2, 2, true, false, FORM>(nullptr, w, y, bias, 1, (int)m, co, (int)k, act, stream, cv)
-  if (prefer_128(1, m, co)) return lean ? TFX_CONV(128, kConvLean) : ci % 4 == 0 ? TFX_CONV(128, kConvAligned) : TFX_CONV(128, kConvRagged);
+#define TFX_CONV(T, FORM) launch_cfg<T, T, 32, T / 64, 2, true, false, FORM>(nullptr, w, y, bias, 1, (int)m, co, (int)k, act, stream, cv)
+  if (us128 == best) return lean ? TFX_CONV(128, kConvLean) : ci % 4 == 0 ? TFX_CONV(128, kConvAligned) : TFX_CONV(128, kConvRagged);
   return lean ? TFX_CONV(64, kConvLean) : ci % 4 == 0 ? TFX_CONV(64, kConvAligned) : TFX_CONV(64, kConvRagged);
 #undef TFX_CONV
 }

@@ -146,6 +146,13 @@ int out_extent(int64_t in, int64_t k, int64_t s, int pad, int64_t* out, int64_t*
 int launch_gemm(const float* a, const float* b, float* c, const float* bias, int batch, int m, int n, int k,
                 bool a_kc, bool b_kc, int act, hipStream_t stream);
 
+// Outputs of up to a few tiles per CU (gemm_direct.hip): workgroups of 64 x 64, 32 x 64 or 32 x 32 tiles (form 0, 1, 2)
+// whose wavefronts split the contraction.  Operands of at least 4 elements.
+int launch_gemm_direct(const float* a, const float* b, float* c, const float* bias, int batch, int m, int n, int k, bool a_kc,
+                       bool b_kc, int act, hipStream_t stream, int form);
+int launch_conv2d_gemm_direct(const float* x, const float* w, const float* bias, float* y, int n, int h, int wd, int ci, int fh,
+                              int fw, int co, int oh, int ow, int sh, int sw, int pt, int pl, int act, hipStream_t stream, int form);
+
 // conv2d as an implicit GEMM on the matrix cores: M = n*oh*ow, K = fh*fw*ci, N = co (any filter / stride / channel counts).
 bool conv2d_gemm_supported(long long x_elems, int fh, int fw, int ci, int co);
 int launch_conv2d_gemm(const float* x, const float* w, const float* bias, float* y, int n, int h, int wd, int ci, int fh,

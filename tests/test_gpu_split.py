@@ -1,0 +1,81 @@
+"""GPU parity of the fp32 kernels that multiply three-way split operands on the bf16 matrix cores (split.h): values that the
+split does not carry (Inf, NaN, magnitudes past the largest bf16, magnitudes near and below the smallest normal numbers), the
+bits that only all three parts hold, and the edges of every kernel's tiles."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_1901_05350_amd import inputs
+from util import assert_close, dev, host
+
+pytestmark = pytest.mark.gpu
+
+# (m, n, k): the 128 x 128, 64 x 64, 64 x 64 direct, 32 x 64 direct, 32 x 32 direct and 16 x 32 kernels of the dispatch
+SIZES = [(4096, 1024, 96), (5000, 320, 40), (1100, 900, 700), (1000, 520, 300), (700, 300, 200), (64, 72, 96)]
+
+
+@pytest.mark.parametrize("m,n,k", SIZES)
+def test_values_outside_the_split(m, n, k):
+    import paper_1901_05350_amd as tfx
+    rng = np.random.default_rng(900 + m)
+    a = rng.standard_normal((m, k)).astype(np.float32)
+    b = rng.standard_normal((k, n)).astype(np.float32)
+    clean = host(tfx.tfx_matmul(dev(a), dev(b)))
+    assert_close(clean, oracle.matmul(a, b), "clean")
+    a[1, 3] = np.inf
+    a[m // 2, 0] = np.nan
+    a[m - 1, k - 1] = 3.4e38  # rounds to Inf as a bf16
+    b[k - 1, :] = np.clip(b[k - 1, :], -0.9, 0.9)
+    got, ref = host(tfx.tfx_matmul(dev(a), dev(b))), oracle.matmul(a, b)
+    assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.array_equal(np.isinf(got), np.isinf(ref))
+    fin = np.isfinite(ref)
+    scale = np.maximum(np.abs(a[:, :]).astype(np.float64) @ np.abs(b).astype(np.float64), 1)
+    assert np.all(np.abs(got[fin] - ref[fin].astype(np.float64)) <= 1e-5 * scale[fin])
+
+
+@pytest.mark.parametrize("m,n,k", SIZES)
+@pytest.mark.parametrize("exponent", [-99, -101, -118, -126])
+def test_small_magnitudes(m, n, k, exponent):
+    """Rows of tiny values against columns of huge ones: results of ordinary size, which need every bit of the operands."""
+    import paper_1901_05350_amd as tfx
+    rng = np.random.default_rng(950 + m)
+    a = rng.standard_normal((m, k)).astype(np.float32)
+    b = rng.standard_normal((k, n)).astype(np.float32)
+    a[m - 2] = (1 + rng.random(k)) * 2.0 ** exponent
+    b[:, n - 1] *= np.float32(2.0 ** 100)
+    a[a == 0] = 1
+    got, ref = host(tfx.tfx_matmul(dev(a), dev(b))).astype(np.float64), a.astype(np.float64) @ b.astype(np.float64)
+    bound = 2e-6 * (np.abs(a).astype(np.float64) @ np.abs(b).astype(np.float64))
+    assert np.all(np.abs(got - ref) <= np.maximum(bound, 1e-44))
+
+
+def test_every_bit_counts():
+    """A product with the identity returns the operand bit for bit: hi, mid and lo together are the whole float."""
+    import paper_1901_05350_amd as tfx
+    rng = np.random.default_rng(990)
+    for m, k in ((4096, 128), (640, 512), (33, 40)):
+        a = (rng.standard_normal((m, k)) * 2.0 ** rng.integers(-60, 60, (m, k))).astype(np.float32)
+        assert np.array_equal(host(tfx.tfx_matmul(dev(a), dev(np.eye(k, dtype=np.float32)))), a)
+
+
+# (n, h, w, cin, cout, f, stride): as SIZES, for the window view; channels a multiple of 32, of 4, of nothing
+CONVS = [(30, 58, 57, 32, 128, 3, 1), (30, 58, 57, 36, 120, 3, 1), (20, 58, 57, 33, 130, 3, 1), (8, 56, 56, 64, 64, 3, 1),
+         (3, 30, 31, 250, 130, 3, 1), (2, 27, 28, 256, 250, 3, 1), (4, 40, 40, 33, 65, 5, 1), (9, 33, 34, 16, 40, 3, 2)]
+
+
+@pytest.mark.parametrize("case", CONVS)
+def test_conv2d_values_outside_the_split(case):
+    import paper_1901_05350_amd as tfx
+    n, h, w, ci, co, f, s = case
+    d = inputs.conv_general(1000 + ci, n, h, w, ci, co, f, f)
+    x = d["x"]
+    args = (d["filter"], d["bias"], s, oracle.PAD_SAME, oracle.ACT_NONE)
+    run = lambda: host(tfx.tfx_conv2d(dev(x), dev(args[0]), dev(args[1]), s, oracle.PAD_SAME, oracle.ACT_NONE))
+    assert_close(run(), oracle.conv2d(x, *args), "clean %r" % (case,))
+    x[n - 1, h - 1, w - 1, ci - 1] = np.nan
+    x[0, 2, 2, 0] = np.inf
+    x[n // 2, 0, 0, 1] = 1e-38
+    got, ref = run(), oracle.conv2d(x, *args)
+    assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.array_equal(np.isinf(got), np.isinf(ref))
+    fin = np.isfinite(ref)
+    assert_close(got[fin], ref[fin], "special %r" % (case,))
