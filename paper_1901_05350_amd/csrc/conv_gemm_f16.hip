@@ -18,6 +18,7 @@
 //   kAligned  Ci % 8 == 0 and Co % 8 == 0: a position per thread; taps outside the image and k past the end are fetched from
 //             past the end of a buffer descriptor and arrive as zeros, so nothing is masked;
 //   kRagged   anything else: loads at any address, masked when they are consumed (ragged.h).
+#include "kernel_cost.h"
 #include "ragged.h"
 
 #include <type_traits>
@@ -328,15 +329,11 @@ int launch(ConvArgs& g, hipStream_t stream) {
   return check_launch();
 }
 
-// 128 x 128 tiles from one per CU on (3x3, 28x28x256 -> 256 at batch 64: 105 us, with 64 rows 153); then 64 x 128 while those
-// give most CUs a workgroup (the same layer at batch 8: 25 against 29 us) and 64 x 64: fewer workgroups of more rows
-// leave CUs idle, and a lone one is bound by the latency of its slices.  Outputs of 64 columns or less always take
-// 64-column tiles.
+// The cheapest of the tiled forms by kernel_cost.h (form: 0 = 128 x 128, 1 = 64 x 128, 2 = 64 x 64 tiles).
 template <Form FORM>
-int launch_tiles(ConvArgs& g, hipStream_t stream) {
-  auto tiles = [&](int bm, int bn) { return ((g.M + (long long)bm - 1) / bm) * ((g.N + bn - 1) / bn); };
-  if (g.N > 64 && tiles(128, 128) >= 256) return launch<2, 2, 2, 2, FORM>(g, stream);
-  if (g.N > 64 && (g.N + 127) / 128 * 128 - g.N < 64 && tiles(64, 128) >= 192) return launch<2, 2, 1, 2, FORM>(g, stream);
+int launch_tiles(ConvArgs& g, hipStream_t stream, int form) {
+  if (form == 0) return launch<2, 2, 2, 2, FORM>(g, stream);
+  if (form == 1) return launch<2, 2, 1, 2, FORM>(g, stream);
   return launch<2, 1, 1, 2, FORM>(g, stream);
 }
 
@@ -361,13 +358,22 @@ int launch_conv2d_gemm_f16(const uint16_t* x, const uint16_t* w, const uint16_t*
   g.by_cp = fast_div((unsigned)cp), g.by_fw = fast_div((unsigned)fw), g.by_ow = fast_div((unsigned)ow), g.by_oh = fast_div((unsigned)oh);
   // (the byte offset of a filter row past K stays below 2^32)
   const bool aligned = ci % 8 == 0 && co % 8 == 0 && ((long long)fh * fw * ci + kBK) * co < (1LL << 31) && reinterpret_cast<uintptr_t>(x) % 16 == 0 && reinterpret_cast<uintptr_t>(w) % 16 == 0;
-  // few output tiles: split the contraction over the wavefronts of a workgroup instead (gemm_deep.hip; 3x3, 14x14x512 ->
-  // 512: 26 against 37 us at batch 2, 51 against 39 at batch 4)
-  // (the tiled kernel's slices cost twice the share of their time at the start and when masked)
-  if (deep_tiles(1, g.M, co) < 192000 / (fh * fw * ci) + (aligned ? 600 : 850))
-    return launch_conv2d_deep_f16(x, w, bias, y, n, h, wd, ci, fh, fw, co, oh, ow, sh, sw, pt, pl, act, stream);
-  if (!aligned) return launch_tiles<kRagged>(g, stream);
-  return ci % 64 == 0 && fh * fw <= 32 ? launch_tiles<kLean>(g, stream) : launch_tiles<kAligned>(g, stream);
+  // the fastest by kernel_cost.h: LDS tiles of three sizes, or the contraction split over a workgroup's wavefronts with
+  // 16 x 32, 32 x 64 or 64 x 64 tiles (5x5, 13x20x20x398 -> 192: 137 us with LDS tiles, 92 split; 3x3, 2x56x56x32 -> 64:
+  // 10.8 and 6.4)
+  const double kp = (double)fh * fw * cp;
+  auto us = [&](const KernelCost& c) { return c.us(1, g.M, co, kp); };
+  const double cost[6] = {us({128, 128, 4.44, 0., 3.32, .0116}), us({64, 128, 4.9, 0., 1.35, .0095}),
+                          us({64, 64, 5.07, .0035, 1.36, .0048}), us({16, co % 2 == 0 ? 32 : 16, 3.26, 0., .25, .0024}),
+                          co >= 2 ? us({64, 64, 1.42, 0., 2.77, .0074}) : 1e30, co >= 2 ? us({32, 64, 2.93, .0047, .71, .0044}) : 1e30};
+  int best = 0;
+  for (int i = 1; i < 6; ++i)
+    if (cost[i] < cost[best]) best = i;
+  if (best == 3) return launch_conv2d_deep_f16(x, w, bias, y, n, h, wd, ci, fh, fw, co, oh, ow, sh, sw, pt, pl, act, stream);
+  if (best > 3)
+    return launch_conv2d_gemm_direct_f16(x, w, bias, y, n, h, wd, ci, fh, fw, co, oh, ow, sh, sw, pt, pl, act, stream, best - 4);
+  if (!aligned) return launch_tiles<kRagged>(g, stream, best);
+  return ci % 64 == 0 && fh * fw <= 32 ? launch_tiles<kLean>(g, stream, best) : launch_tiles<kAligned>(g, stream, best);
 }
 
 }  // namespace tfx

@@ -12,6 +12,7 @@
 //   A operand: lane l holds A[i = l % 32][k = 8*(l/32) .. + 7]
 //   B operand: lane l holds B[k = 8*(l/32) .. + 7][j = l % 32]
 //   D result : register v of lane l holds D[i = 8*(v/4) + 4*(l/32) + v%4][j = l % 32]
+#include "kernel_cost.h"
 #include "ragged.h"
 #include "split.h"
 
@@ -720,22 +721,6 @@ __global__ __launch_bounds__(256) void gemm_tiny_kernel(const float* __restrict_
            B[batch * N * K + (b_kc ? (long long)col * K + k : (long long)k * N + col)];
   C[e] = apply_act(sum + (bias != nullptr ? bias[col] : 0.f), act);
 }
-
-// Which kernel: the one that a model of their times says is fastest.  A kernel of bm x bn tiles gives
-// c = batch x tiles / 256 of them to a CU (a whole number of rounds while there are few), each of which walks through k:
-//   us = fixed + per_k k + c (per_tile + per_tile_k k)
-// per_k is the memory round trips of a chain that nothing hides, per_tile_k what k costs the CU.  Fitted to the measured
-// times of 226 products and 190 convolutions (sizes 16 ... 4096, channels 3 ... 512; mean error 4 - 18 %); over these its
-// choice costs 2 - 3 % against the fastest kernel of each.
-struct KernelCost {
-  int bm, bn;
-  double fixed, per_k, per_tile, per_tile_k;
-  double us(long long batch, long long m, long long n, double k) const {
-    const double tiles = (double)(batch * ((m + bm - 1) / bm) * ((n + bn - 1) / bn)) / 256.;
-    const double c = tiles <= 2. ? (tiles <= 1. ? 1. : 2.) : tiles + .5;
-    return fixed + per_k * k + c * (per_tile + per_tile_k * k);
-  }
-};
 
 }  // namespace
 

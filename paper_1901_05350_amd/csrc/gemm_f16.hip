@@ -11,6 +11,7 @@
 // consecutive output columns of one row and the epilogue stores 8 bytes at a time.
 // One software-pipelined kernel takes every layout, size and alignment (ragged.h has the loads); small outputs with a
 // long contraction go to gemm_deep.hip.
+#include "kernel_cost.h"
 #include "ragged.h"
 
 #include <type_traits>
@@ -481,19 +482,37 @@ int launch_gemm_f16(const uint16_t* a16, const uint16_t* b16, uint16_t* c16, con
   const bool aligned = reinterpret_cast<uintptr_t>(a) % 16 == 0 && reinterpret_cast<uintptr_t>(b) % 16 == 0;
   if (a_kc && !b_kc && k % 8 == 0 && n % 8 == 0 && aligned && tiles(64, 64) < 128)
     return launch_small(a, b, c, bias, batch, m, n, k, act, stream);
-  // few output tiles: split the contraction over the wavefronts of a workgroup (256 x 256 x 1024, B [N,K]: 4.3 against
-  // 6.5 us with 64 x 64 tiles; 512^3: 6.2 against 5.1, A [K,M] 6.4 against 8.2)
-  if (deep_tiles(batch, m, n) < (a_kc && b_kc ? 400 : 580))
-    return launch_gemm_deep_f16(a16, b16, c16, bias16, batch, m, n, k, a_kc, b_kc, act, stream);
+  // Fewer than three 128 x 128 tiles per four CUs: the contraction split over a workgroup's wavefronts, 16 x 32, 32 x 64 or
+  // 64 x 64 tiles at a time, or 64 x 64 tiles through LDS (kernel_cost.h; 1024^3: 12.3 us through LDS, 9.8 split).  Rows of
+  // an odd number of halfs along K halve what 16-byte loads deliver to a kernel that does not share them through LDS
+  // (2000 x 1000 x 1024 with B [N,K] 21 us, x 1023 53): none of the two larger ones then.
+  if (tiles(128, 128) < 192) {
+    const bool odd = k % 2 != 0 && (a_kc || b_kc);
+    const double deep = KernelCost{16, n % 2 == 0 ? 32 : 16, 3., 0., .165, .0017}.us(batch, m, n, k);
+    const double lds = a_kc && b_kc ? KernelCost{64, 64, 3.1, .0012, .55, .0027}.us(batch, m, n, k)
+                                    : KernelCost{64, 64, 3.3, .0012, 1.11, .0039}.us(batch, m, n, k);
+    const bool direct = !odd && n >= 2 && m >= 2;
+    const double us[2] = {direct ? KernelCost{64, 64, .86, 0., 2.64, .0052}.us(batch, m, n, k) : 1e30,
+                          direct ? KernelCost{32, 64, 2.75, .0018, .46, .0038}.us(batch, m, n, k) : 1e30};
+    const int form = us[0] <= us[1] ? 0 : 1;
+    if (deep <= us[form] && deep <= lds) return launch_gemm_deep_f16(a16, b16, c16, bias16, batch, m, n, k, a_kc, b_kc, act, stream);
+    if (us[form] <= lds) return launch_gemm_direct_f16(a16, b16, c16, bias16, batch, m, n, k, a_kc, b_kc, act, stream, form);
+  }
   auto pick = [&](auto akc, auto bkc) {
     constexpr bool A_KC = decltype(akc)::value, B_KC = decltype(bkc)::value;
+    // no large tiles whose last round over the CUs would be nearly empty (5 x 848 x 1544 x 720: 32 us with 260 tiles of
+    // 256 x 128, 21 with 128 x 128)
+    auto even = [&](int bm, int bn) {
+      const long long t = tiles(bm, bn);
+      return t <= 256 || t * 10 >= (t + 255) / 256 * 256 * 7;
+    };
     // 256 x 256 tiles (8 wavefronts) once they fill half of the 256 CUs (3001^3: 144 tiles, 111 us against 159 with
     // 128 x 128), then 256 x 128 (8 wavefronts), 128 x 128 (4 wavefronts, two workgroups per CU) from three per four CUs on
     // (2000 x 1000 x 1024, 128 tiles: 12.6 us against 10.3 with 64 x 64), 64 x 64 below that
-    if (tiles(256, 256) >= 136 && fits(256, 256))
+    if (tiles(256, 256) >= 136 && fits(256, 256) && even(256, 256))
       return launch_pipe<2, 4, 4, 2, A_KC, B_KC>(a, b, c, bias, batch, m, n, k, act, stream);
     if constexpr (A_KC && B_KC)
-      if (tiles(256, 128) >= 192 && fits(256, 128))
+      if (tiles(256, 128) >= 192 && fits(256, 128) && even(256, 128))
         return launch_pipe<4, 2, 2, 2, A_KC, B_KC>(a, b, c, bias, batch, m, n, k, act, stream);
     if (tiles(128, 128) >= 192) return launch_pipe<2, 2, 2, 2, A_KC, B_KC>(a, b, c, bias, batch, m, n, k, act, stream);
     if constexpr (A_KC && B_KC) return launch_pipe<2, 2, 1, 1, A_KC, B_KC>(a, b, c, bias, batch, m, n, k, act, stream);

@@ -153,6 +153,13 @@ int launch_gemm_direct(const float* a, const float* b, float* c, const float* bi
 int launch_conv2d_gemm_direct(const float* x, const float* w, const float* bias, float* y, int n, int h, int wd, int ci, int fh,
                               int fw, int co, int oh, int ow, int sh, int sw, int pt, int pl, int act, hipStream_t stream, int form);
 
+// The same on binary16 storage (forms 0 and 1).  Operands of at least 8 elements and two rows / columns.
+int launch_gemm_direct_f16(const uint16_t* a, const uint16_t* b, uint16_t* c, const uint16_t* bias, int batch, int m, int n,
+                           int k, bool a_kc, bool b_kc, int act, hipStream_t stream, int form);
+int launch_conv2d_gemm_direct_f16(const uint16_t* x, const uint16_t* w, const uint16_t* bias, uint16_t* y, int n, int h, int wd,
+                                  int ci, int fh, int fw, int co, int oh, int ow, int sh, int sw, int pt, int pl, int act,
+                                  hipStream_t stream, int form);
+
 // conv2d as an implicit GEMM on the matrix cores: M = n*oh*ow, K = fh*fw*ci, N = co (any filter / stride / channel counts).
 bool conv2d_gemm_supported(long long x_elems, int fh, int fw, int ci, int co);
 int launch_conv2d_gemm(const float* x, const float* w, const float* bias, float* y, int n, int h, int wd, int ci, int fh,
@@ -249,10 +256,6 @@ int launch_gemm_f16(const uint16_t* a, const uint16_t* b, uint16_t* c, const uin
 // Outputs of few tiles with any contraction length, both storage types, any layout and alignment (gemm_deep.hip): the
 // contraction is split over the wavefronts of a workgroup.
 // Operands of at least 8 elements (floats: 4).
-inline long long deep_tiles(int batch, int m, int n) {  // its 16 x 32 tiles; an odd n makes it 16 x 16 ones of more than half the cost
-  const long long t = (long long)batch * ((m + 15) / 16) * ((n + 31) / 32);
-  return n % 2 == 0 ? t : t * 3 / 2;
-}
 int launch_gemm_deep(const float* a, const float* b, float* c, const float* bias, int batch, int m, int n, int k, bool a_kc,
                      bool b_kc, int act, hipStream_t stream);
 int launch_gemm_deep_f16(const uint16_t* a, const uint16_t* b, uint16_t* c, const uint16_t* bias, int batch, int m, int n,

@@ -6,7 +6,7 @@ import pytest
 
 import oracle
 from paper_1901_05350_amd import inputs
-from util import assert_close, dev, host
+from util import assert_close, assert_close_f16, dev, dev16, host
 
 pytestmark = pytest.mark.gpu
 
@@ -79,3 +79,27 @@ def test_conv2d_values_outside_the_split(case):
     assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.array_equal(np.isinf(got), np.isinf(ref))
     fin = np.isfinite(ref)
     assert_close(got[fin], ref[fin], "special %r" % (case,))
+
+
+# binary16 through the kernels whose wavefronts split K (gemm_direct.hip): pairs of rows / columns at odd ends, both tile sizes
+HALVES = [(1, 1025, 1023, 130), (1, 131, 901, 258), (2, 333, 515, 512), (1, 700, 642, 64), (1, 129, 2050, 48), (3, 65, 67, 96)]
+
+
+@pytest.mark.parametrize("ta,tb", [(False, False), (True, False), (False, True), (True, True)])
+def test_matmul_f16_split_over_wavefronts(ta, tb):
+    import paper_1901_05350_amd as tfx
+    for i, (b, m, n, k) in enumerate(HALVES):
+        d = inputs.batch_matmul_f16(seed=1100 + i, batch=b, m=m, n=n, k=k, transpose_a=ta, transpose_b=tb, bias=True)
+        got = host(tfx.tfx_batch_matmul_f16(dev16(d["a"]), dev16(d["b"]), ta, tb, dev16(d["bias"]), oracle.ACT_RELU))
+        assert_close_f16(got, oracle.batch_matmul_f16(d["a"], d["b"], ta, tb, d["bias"], oracle.ACT_RELU), "%r" % ((b, m, n, k),))
+
+
+@pytest.mark.parametrize("case", [(2, 56, 56, 32, 64, 3, 1), (3, 39, 39, 176, 175, 1, 1), (4, 37, 37, 184, 87, 3, 1), (3, 20, 20, 398, 192, 5, 1),
+                                  (4, 39, 41, 54, 71, 3, 2), (5, 28, 28, 16, 2, 3, 1)])
+def test_conv2d_f16_split_over_wavefronts(case):
+    import paper_1901_05350_amd as tfx
+    n, h, w, ci, co, f, s = case
+    d = inputs.conv_general(1150 + ci, n, h, w, ci, co, f, f)
+    d = {key: (v * (30 if key == "bias" else 1)).astype(np.float16) for key, v in d.items()}
+    got = host(tfx.tfx_conv2d_f16(dev16(d["x"]), dev16(d["filter"]), dev16(d["bias"]), s, oracle.PAD_SAME, oracle.ACT_RELU6))
+    assert_close_f16(got, oracle.conv2d_f16(d["x"], d["filter"], d["bias"], s, oracle.PAD_SAME, oracle.ACT_RELU6), "%r" % (case,))
