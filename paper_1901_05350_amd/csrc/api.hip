@@ -163,15 +163,14 @@ void* static_scratch() {
   return p;
 }
 
-// From batch 32 on the fp32 forward pass runs as two parts of the batch, from batch 60 on as three, all but the first
-// on streams of the library's own that are forked from the caller's stream and joined back to it with events: the
-// layers of such a batch are kernels of 10 - 90 us whose last workgroups leave most CUs idle, and independent chains
-// of them fill each other's tails (measured: batch 64 1.03 -> 0.975 ms with two chains, 0.96 with three; batch 128
-// 1.87 -> 1.76 either way; at batch 48 three are no better than two; nothing to gain on binary16 storage).
-constexpr int64_t kSplitBatch = 32, kThreeChains = 60;
-constexpr int kMaxChains = 3;
+// From batch 32 on the fp32 forward pass runs as two halves of the batch, the second on a stream of the library's that is
+// forked from the caller's and joined back to it with events: the layers of such a batch are kernels of 10 - 60 us whose
+// last workgroups leave most CUs idle, and an independent chain of them fills the tails (batch 32 489 -> 449 us, 64
+// 880 -> 803, with the blocks of block_planes.hip; at batch 16 no gain; nothing to gain on binary16 storage).
+constexpr int64_t kSplitBatch = 32;
+constexpr int kMaxChains = 2;
 
-int net_chains(int64_t batch) { return batch < kSplitBatch ? 1 : batch < kThreeChains ? 2 : 3; }
+int net_chains(int64_t batch) { return batch < kSplitBatch ? 1 : 2; }
 // images of part i of `chains`: the first batch % chains parts take one more
 int64_t part_images(int64_t batch, int chains, int i) { return batch / chains + (i < batch % chains ? 1 : 0); }
 
@@ -579,6 +578,30 @@ int forward_impl(const tfx_mobilenet_v1_variant* variant, const float* input, in
       shape[3] = cout;
       cur ^= 1;
       continue;
+    }
+    // from 600 000 outputs on the depthwise output is handed over as bf16 planes (block_planes.hip), which lie at the end of
+    // the buffer that the block's output starts (full width: batch 8 258 -> 223 us, 16 391 -> 303; with fewer outputs the
+    // two single-layer kernels are faster: half width, batch 8: 171 against 183)
+    {
+      const int64_t rows = batch * g.out[1] * g.out[2];
+      const size_t a_bytes = align_up(planes_elems(rows, (int)shape[3]) * 2), b_bytes = align_up(planes_elems(cout, (int)shape[3]) * 2);
+      const size_t need = a_bytes + b_bytes + kAlign, have = plan.act_floats * sizeof(float) / kAlign * kAlign;
+      if (rows * cout >= 600000 && need + align_up((size_t)rows * cout * sizeof(float)) <= have &&
+          separable_planes_supported(rows, (int)shape[3], (int)cout, kStrides[b], buf[cur], weights->dw_w[b], weights->dw_b[b],
+                                     weights->pw_w[b], weights->pw_b[b], block_out)) {
+        static std::atomic<unsigned> calls{0};  // the token of each call
+        char* const region = reinterpret_cast<char*>(buf[cur ^ 1]) + have - need;
+        rc = launch_separable_planes(buf[cur], weights->dw_w[b], weights->dw_b[b], weights->pw_w[b], weights->pw_b[b], block_out, region,
+                                     region + a_bytes, reinterpret_cast<unsigned*>(region + a_bytes + b_bytes), ++calls, (int)batch,
+                                     (int)shape[1], (int)shape[2], (int)shape[3], (int)cout, (int)g.out[1], (int)g.out[2], kStrides[b],
+                                     (int)g.pad[0], (int)g.pad[2], TFX_ACT_RELU6, TFX_ACT_RELU6, static_cast<hipStream_t>(stream));
+        if (rc) return rc;
+        if (end_block == b + 1) return TFX_OK;
+        for (int i = 0; i < 3; ++i) shape[i] = g.out[i];
+        shape[3] = cout;
+        cur ^= 1;
+        continue;
+      }
     }
     rc = tfx_depthwise_conv2d(buf[cur], shape, weights->dw_w[b], fd, weights->dw_b[b], kStrides[b], kStrides[b],
                               TFX_PAD_SAME, TFX_ACT_RELU6, buf[cur ^ 1], stream);

@@ -469,3 +469,37 @@ def test_two_chained_kernels_on_two_streams_at_once(net):
     for i in range(2):
         for o in outs[i]:
             assert np.array_equal(o.cpu().numpy(), p0)
+
+
+@pytest.mark.parametrize("q,size,batch,end_block", [(4, 224, 8, 6), (4, 96, 80, 9), (3, 131, 41, 8), (2, 160, 34, 13), (1, 224, 40, 5)])
+def test_planes_blocks(q, size, batch, end_block):
+    """Blocks handed over as bf16 planes (block_planes.hip): ragged last tiles, channel counts of every width, both strides."""
+    import paper_1901_05350_amd as tfx
+    d = inputs.mobilenet_v1(seed=31 + q, batch=2, image_size=size, width_quarters=q)
+    image = np.concatenate([d["image"]] * (batch // 2) + [d["image"][:batch % 2]])
+    model = tfx.MobileNetV1(d["weights"], batch=batch, image_size=size, width_quarters=q)
+    got = host(model.features(dev(image), end_block))
+    one = tfx.MobileNetV1(d["weights"], batch=1, image_size=size, width_quarters=q)
+    for i in (0, 1):
+        ref = host(one.features(dev(d["image"][i:i + 1]), end_block))
+        for j in range(i, batch, 2):
+            assert_close(got[j:j + 1], ref, "image %d" % j)
+    assert np.array_equal(got[:2], got[batch // 2 * 2 - 2:batch // 2 * 2])
+
+
+@pytest.mark.parametrize("what", ["nan image", "nan filter", "inf filter", "tiny filter", "huge filter"])
+def test_planes_blocks_values_outside_the_split(what):
+    import paper_1901_05350_amd as tfx
+    d = inputs.mobilenet_v1(seed=41, batch=8)
+    w, image = d["weights"], d["image"].copy()
+    if what == "nan image":
+        image[3, 100, 50, 1] = np.nan
+    else:
+        value = {"nan filter": np.nan, "inf filter": np.inf, "tiny filter": 1e-36, "huge filter": 3.4e38}[what]
+        w["pw_w"][7][0, 0, 17, 33] = value
+    got = host(tfx.MobileNetV1(w, batch=8).features(dev(image), 8))
+    for i in (0, 3):
+        ref = host(tfx.MobileNetV1(w, batch=1).features(dev(image[i:i + 1]), 8))
+        assert np.array_equal(np.isnan(got[i:i + 1]), np.isnan(ref))
+        fin = np.isfinite(ref)
+        assert_close(got[i:i + 1][fin], ref[fin], what)
