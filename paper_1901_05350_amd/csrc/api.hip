@@ -579,14 +579,15 @@ int forward_impl(const tfx_mobilenet_v1_variant* variant, const float* input, in
       cur ^= 1;
       continue;
     }
-    // from 600 000 outputs on the depthwise output is handed over as bf16 planes (block_planes.hip), which lie at the end of
-    // the buffer that the block's output starts (full width: batch 8 258 -> 223 us, 16 391 -> 303; with fewer outputs the
-    // two single-layer kernels are faster: half width, batch 8: 171 against 183)
+    // From 800 000 outputs on (3 000 000 where they have few columns to share a split element) the depthwise output is
+    // handed over as bf16 planes (block_planes.hip), which lie at the end of the buffer that the block's output starts.
+    // Full width: batch 8 258 -> 223 us, 16 391 -> 303; with fewer outputs the two single-layer kernels are faster: half
+    // width, batch 8: 171 against 183.
     {
       const int64_t rows = batch * g.out[1] * g.out[2];
       const size_t a_bytes = align_up(planes_elems(rows, (int)shape[3]) * 2), b_bytes = align_up(planes_elems(cout, (int)shape[3]) * 2);
       const size_t need = a_bytes + b_bytes + kAlign, have = plan.act_floats * sizeof(float) / kAlign * kAlign;
-      if (rows * cout >= 600000 && need + align_up((size_t)rows * cout * sizeof(float)) <= have &&
+      if (rows * cout >= (cout >= 256 ? 800000 : 3000000) && need + align_up((size_t)rows * cout * sizeof(float)) <= have &&
           separable_planes_supported(rows, (int)shape[3], (int)cout, kStrides[b], buf[cur], weights->dw_w[b], weights->dw_b[b],
                                      weights->pw_w[b], weights->pw_b[b], block_out)) {
         static std::atomic<unsigned> calls{0};  // the token of each call

@@ -482,6 +482,8 @@ int launch_gemm_f16(const uint16_t* a16, const uint16_t* b16, uint16_t* c16, con
   const bool aligned = reinterpret_cast<uintptr_t>(a) % 16 == 0 && reinterpret_cast<uintptr_t>(b) % 16 == 0;
   if (a_kc && !b_kc && k % 8 == 0 && n % 8 == 0 && aligned && tiles(64, 64) < 128)
     return launch_small(a, b, c, bias, batch, m, n, k, act, stream);
+  if (batch == 1 && a_kc && thin_pays(m, n, k, true))
+    return launch_gemm_thin_f16(a16, b16, c16, bias16, m, n, k, b_kc, act, stream);
   // Fewer than three 128 x 128 tiles per four CUs: the contraction split over a workgroup's wavefronts, 16 x 32, 32 x 64 or
   // 64 x 64 tiles at a time, or 64 x 64 tiles through LDS (kernel_cost.h; 1024^3: 12.3 us through LDS, 9.8 split).  Rows of
   // an odd number of halfs along K halve what 16-byte loads deliver to a kernel that does not share them through LDS

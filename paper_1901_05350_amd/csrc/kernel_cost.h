@@ -19,6 +19,16 @@ struct KernelCost {
   }
 };
 
+// Whether gemm_thin.hip is the fastest: from how many outputs on its start (B into registers, longer with k) is paid back.
+// Measured on 1x1 convolutions of 100 ... 250 000 rows: floats, 8 -> 16 channels, 200704 rows 25 -> 8 us, 40 -> 152, 248292
+// rows 145 -> 80; 48 -> 24, 1700 rows 3.5 -> 5.3 (not taken); halfs, 11 -> 22, 207936 rows 33 -> 7.
+inline bool thin_pays(long long m, long long n, int k, bool half) {
+  const long long outputs = m * n;
+  if (!half) return k <= 16 ? outputs >= 400000 : k <= 32 ? outputs >= 1000000 : k <= 48 && outputs >= 20000000;
+  if (k <= 16) return outputs >= (n <= 32 ? 400000 : 1000000);
+  return k <= 32 ? outputs >= 1300000 : k <= 64 ? outputs >= 3000000 : k <= 128 && outputs >= 10000000;
+}
+
 }  // namespace tfx
 
 #endif  // TFX_KERNEL_COST_H_

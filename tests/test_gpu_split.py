@@ -103,3 +103,26 @@ def test_conv2d_f16_split_over_wavefronts(case):
     d = {key: (v * (30 if key == "bias" else 1)).astype(np.float16) for key, v in d.items()}
     got = host(tfx.tfx_conv2d_f16(dev16(d["x"]), dev16(d["filter"]), dev16(d["bias"]), s, oracle.PAD_SAME, oracle.ACT_RELU6))
     assert_close_f16(got, oracle.conv2d_f16(d["x"], d["filter"], d["bias"], s, oracle.PAD_SAME, oracle.ACT_RELU6), "%r" % (case,))
+
+
+# gemm_thin.hip: one or two column blocks, several groups of them, every depth, k at and beside a k-step, rows that end a tensor
+THIN = [(1, 200, 151, 3, 24, 1), (2, 160, 157, 8, 16, 1), (3, 112, 113, 15, 33, 1), (2, 71, 73, 17, 130, 1), (2, 150, 149, 33, 64, 2),
+        (1, 701, 703, 31, 5, 1), (9, 230, 231, 40, 43, 1), (2, 401, 400, 24, 48, 2), (6, 128, 129, 100, 130, 1)]
+
+
+@pytest.mark.parametrize("half", [False, True])
+@pytest.mark.parametrize("case", THIN)
+def test_thin_products(case, half):
+    import paper_1901_05350_amd as tfx
+    n, h, w, ci, co, s = case
+    d = inputs.conv_general(1200 + ci, n, h, w, ci, co, 1, 1)
+    if half:
+        d = {key: v.astype(np.float16) for key, v in d.items()}
+    x = d["x"]
+    x[0, 0, 0, 0], x[n - 1, h - 1, w - 1, ci - 1], x[0, h // 2 // s * s, s, 0] = np.nan, np.inf, -np.inf
+    up, conv, ref = (dev16, tfx.tfx_conv2d_f16, oracle.conv2d_f16) if half else (dev, tfx.tfx_conv2d, oracle.conv2d)
+    got = host(conv(up(x), up(d["filter"]), up(d["bias"]), s, oracle.PAD_VALID, oracle.ACT_NONE))
+    want = ref(x, d["filter"], d["bias"], s, oracle.PAD_VALID, oracle.ACT_NONE)
+    assert np.array_equal(np.isfinite(got), np.isfinite(want))
+    fin = np.isfinite(want)
+    (assert_close_f16 if half else assert_close)(got[fin], want[fin], "%r" % (case,))
