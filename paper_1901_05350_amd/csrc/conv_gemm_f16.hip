@@ -110,8 +110,9 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void conv_f16_gemm_kernel(C
       tap_ok[i] = ok;
     }
   }
-  // B slots: k-rows 4 kq ... + 3 of the slice, columns n0 + 8 nb ... + 7; past N: any column block (feeds no stored output)
-  const int kq = tid % 16, nb = tid / 16;
+  // B slots: k-rows 4 kq ... + 3 of the slice, columns n0 + 8 nb ... + 7; past N: any column block (feeds no stored output);
+  // four lanes side by side in a row, for the look-ups in L1 (gemm_f16.hip)
+  const int kq = tid / 4 % 16, nb = tid / 64 * 4 + tid % 4;
   const unsigned bcol = n0 + 8 * nb < N ? (unsigned)(n0 + 8 * nb) : 0u;
   const __amdgpu_buffer_rsrc_t xr = __builtin_amdgcn_make_buffer_rsrc(const_cast<half_t*>(g.x), 0, (int)(2u * g.x_total), 0x00020000);
   const __amdgpu_buffer_rsrc_t wr = __builtin_amdgcn_make_buffer_rsrc(const_cast<half_t*>(g.w), 0, (int)(2u * g.w_total), 0x00020000);

@@ -28,8 +28,7 @@ constexpr int kBK = 64;       // halfs per k-slice
 constexpr int kLd = kBK + 8;  // LDS row stride in halfs
 constexpr int kXcds = 8;
 
-// One thread per output element: operands of fewer elements than a 16-byte load (gemm_any_f16.hip has everything else
-// that the pipelined kernel does not take).
+// One thread per output element: operands of fewer elements than a 16-byte load.
 __global__ __launch_bounds__(256) void gemm_tiny_f16_kernel(const half_t* __restrict__ A, const half_t* __restrict__ B,
                                                             half_t* __restrict__ C, const half_t* __restrict__ bias, int M, int N,
                                                             int K, int a_kc, int b_kc, long long total, int act) {
@@ -54,9 +53,9 @@ __global__ __launch_bounds__(256) void gemm_tiny_f16_kernel(const half_t* __rest
 // kt+2; one barrier per slice.
 //
 // Alignment and remainders cost nothing in that loop: the 16-byte loads and stores work at any address (rows that start
-// at an odd half cost about 30 % of the kernel's time, 4-byte aligned ones nothing), and only slices that reach past K,
-// or hold a [K,N] operand's last row when N % 8 != 0, go through the masked form.  (They used to be fetched half by half:
-// 1999 x 1001 x 1023 42 us.)
+// at an odd half cost 5 - 20 % of the kernel's time, 4-byte aligned ones nothing), and only slices that reach past K,
+// or hold a [K,N] operand's last row when N % 8 != 0, go through the masked form.  (Fetched half by half,
+// 1999 x 1001 x 1023 took 42 us, now 17.)
 template <int WAVES_M, int WAVES_N, int TM, int TN, bool A_KC, bool B_KC>
 __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_f16_pipe_kernel(
     const half_t* __restrict__ A, const half_t* __restrict__ B, half_t* __restrict__ C, const half_t* __restrict__ bias,
@@ -112,17 +111,18 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_f16_pipe_kernel(
   // clamped to the last one, so every load is unconditional and in bounds; halfs past K are zeroed
   // with a mask.  The loop body therefore has no branch.
   //
-  // An operand stored [K,N] or [K,M]: thread (kq = tid % 16, nb = tid / 16) loads k-rows 4 kq ... + 3 of
-  // columns 8 nb ... + 7 as four 16-byte slots (16 lanes with consecutive kq: the 8-byte LDS writes of
-  // one row are contiguous), transposes the 4 x 8 block in registers and writes, for each of the 8
-  // columns, 4 consecutive k to the K-contiguous LDS row of that column.  The block is written when
-  // its first slot comes up in the schedule, its slots are refilled one by one.
+  // An operand stored [K,N] or [K,M]: thread (kq, nb) loads k-rows 4 kq ... + 3 of columns 8 nb ... + 7 as four 16-byte
+  // slots, four lanes side by side in a row, transposes the 4 x 8 block in registers and writes, for each of the 8
+  // columns, 4 consecutive k to the K-contiguous LDS row of that column.  The block is written when its first slot comes
+  // up in the schedule, its slots are refilled one by one.  With a row for each of 16 lanes the 8-byte LDS writes would
+  // be contiguous, but L1 looks a line up once per 16 lanes and row, and the look-ups were what the kernel waited for
+  // (1999 x 1001 x 1023: 6.0 million, 23.6 us; now 17.2.  4096^3 in 128 x 128 tiles 180 us, now 160).
   const int srow = tid / 8, scol = 8 * (tid % 8);
   constexpr int kRowStep = kNT / 8;
   typedef ragged_u32x4 u32x4;
   u32x4 reg[SLOTS];
   unsigned boff[SLOTS];  // byte offset of the slot at k0 = 0 from its operand's base (operands hold < 2^31 elements)
-  const int kq = tid % 16, nb = tid / 16;
+  const int kq = tid / 4 % 16, nb = tid / 64 * 4 + tid % 4;
   // past the matrix: any valid column block
   const unsigned acol = m0 + 8 * nb < M ? (unsigned)(m0 + 8 * nb) : 0u, bcol = n0 + 8 * nb < N ? (unsigned)(n0 + 8 * nb) : 0u;
 #pragma unroll
