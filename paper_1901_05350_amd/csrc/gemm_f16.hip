@@ -510,13 +510,24 @@ int launch_gemm_f16(const uint16_t* a16, const uint16_t* b16, uint16_t* c16, con
     };
     // 256 x 256 tiles (8 wavefronts) once they fill half of the 256 CUs (3001^3: 144 tiles, 111 us against 159 with
     // 128 x 128), then 256 x 128 (8 wavefronts), 128 x 128 (4 wavefronts, two workgroups per CU) from three per four CUs on
-    // (2000 x 1000 x 1024, 128 tiles: 12.6 us against 10.3 with 64 x 64), 64 x 64 below that
-    if (tiles(256, 256) >= 136 && fits(256, 256) && even(256, 256))
+    // (2000 x 1000 x 1024, 128 tiles: 12.6 us against 10.3 with 64 x 64), 64 x 64 below that.  With a long K, which pays
+    // back the longer start and end of a larger tile, 128 x 128 from fewer on (3428 x 694 x 1320, 162 tiles: 21.5 us
+    // against 24.2; 14 x 708 x 232 x 3992 with A [K,M], 168: 61.5 against 80).  Of an output of at most 64 rows or columns
+    // a larger tile wastes half (22 x 2070 x 20 x 992: 64 x 64 18.9 us, 256 x 128 23.7).
+    const bool narrow = m <= 64 || n <= 64;
+    if (!narrow && tiles(256, 256) >= 136 && fits(256, 256) && even(256, 256))
       return launch_pipe<2, 4, 4, 2, A_KC, B_KC>(a, b, c, bias, batch, m, n, k, act, stream);
     if constexpr (A_KC && B_KC)
-      if (tiles(256, 128) >= 192 && fits(256, 128) && even(256, 128))
+      if (!narrow && tiles(256, 128) >= 192 && fits(256, 128) && even(256, 128))
         return launch_pipe<4, 2, 2, 2, A_KC, B_KC>(a, b, c, bias, batch, m, n, k, act, stream);
-    if (tiles(128, 128) >= 192) return launch_pipe<2, 2, 2, 2, A_KC, B_KC>(a, b, c, bias, batch, m, n, k, act, stream);
+    const long long t128 = tiles(128, 128), t64 = tiles(64, 64);
+    if (!narrow && (t128 >= 192 || (t128 >= 136 && k >= 1024 && 2 * t64 >= 7 * t128)))
+      return launch_pipe<2, 2, 2, 2, A_KC, B_KC>(a, b, c, bias, batch, m, n, k, act, stream);
+    // 64 x 128 where these are one round over the CUs and 64 x 64 would be two (1999 x 1001 x 1023: 15.3 us against 17.2;
+    // 21 x 202 x 220 x 653 with B [N,K]: 11.9 against 14.9)
+    if constexpr (A_KC)
+      if (k >= 256 && t64 > 256 && tiles(64, 128) <= 256 && 20 * tiles(64, 128) <= 11 * t64)
+        return launch_pipe<2, 2, 1, 2, A_KC, B_KC>(a, b, c, bias, batch, m, n, k, act, stream);
     if constexpr (A_KC && B_KC) return launch_pipe<2, 2, 1, 1, A_KC, B_KC>(a, b, c, bias, batch, m, n, k, act, stream);
     else return launch_pipe<2, 1, 1, 2, A_KC, B_KC>(a, b, c, bias, batch, m, n, k, act, stream);
   };

@@ -94,6 +94,21 @@ def test_matmul_f16_split_over_wavefronts(ta, tb):
         assert_close_f16(got, oracle.batch_matmul_f16(d["a"], d["b"], ta, tb, d["bias"], oracle.ACT_RELU), "%r" % ((b, m, n, k),))
 
 
+# tiles of a long contraction (128 x 128), of one round over the CUs (64 x 128) and of an output of few columns (64 x 64):
+# (batch, m, n, k, transpose_a, transpose_b)
+TILES_F16 = [(18, 325, 325, 1030, False, False), (12, 136, 592, 489, False, False), (21, 202, 220, 259, False, True),
+             (24, 513, 40, 136, False, True)]
+
+
+@pytest.mark.parametrize("case", TILES_F16)
+def test_matmul_f16_tiles(case):
+    import paper_1901_05350_amd as tfx
+    b, m, n, k, ta, tb = case
+    d = inputs.batch_matmul_f16(seed=1200 + n, batch=b, m=m, n=n, k=k, transpose_a=ta, transpose_b=tb, bias=True)
+    got = host(tfx.tfx_batch_matmul_f16(dev16(d["a"]), dev16(d["b"]), ta, tb, dev16(d["bias"]), oracle.ACT_RELU))
+    assert_close_f16(got, oracle.batch_matmul_f16(d["a"], d["b"], ta, tb, d["bias"], oracle.ACT_RELU), "%r" % (case,))
+
+
 @pytest.mark.parametrize("case", [(2, 56, 56, 32, 64, 3, 1), (3, 39, 39, 176, 175, 1, 1), (4, 37, 37, 184, 87, 3, 1), (3, 20, 20, 398, 192, 5, 1),
                                   (4, 39, 41, 54, 71, 3, 2), (5, 28, 28, 16, 2, 3, 1)])
 def test_conv2d_f16_split_over_wavefronts(case):
