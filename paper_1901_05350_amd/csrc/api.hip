@@ -98,7 +98,7 @@ size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 
 struct NetPlan {
   size_t act_floats;  // per ping-pong buffer
-  size_t off_buf[2], off_partial, off_chain, off_head, bytes;
+  size_t off_buf[2], off_partial, off_chain, off_head, off_packed, bytes;  // off_packed: BlockPlan
   bool chain;         // the batch-1 full-width network: room for the chained small-map kernel (chain.hip)
   bool head;          // and for blocks 2 - 4 as stages of one launch (block.hip): their three outputs at once
 };
@@ -106,6 +106,42 @@ struct NetPlan {
 bool valid_variant(const tfx_mobilenet_v1_variant* v) {
   return v && v->image_size >= 32 && v->image_size <= 256 && v->width_quarters >= 1 && v->width_quarters <= 4 &&
          v->classes >= 1 && v->classes <= 1024;
+}
+
+// On binary16 storage, each block's form: depthwise and pointwise layer in one launch, with the filters stationary in LDS
+// (block_stream_f16.hip: large batch, early block) or the depthwise output there (block_tile_f16.hip), or as two.  The
+// pointwise filters of the second kind are put in its order by one launch in front, for which one or two such blocks do
+// not pay.  (All operands are taken to be aligned.)
+enum BlockForm { kTwo, kStream, kTile };
+struct BlockPlan {
+  BlockForm form[kBlocks];
+  int tiles, c[kBlocks], n[kBlocks];  // of all blocks
+  size_t packed[kBlocks], packed_halfs;  // the tile blocks' filters
+};
+BlockPlan plan_blocks_f16(const tfx_mobilenet_v1_variant& v, int64_t batch, int blocks) {
+  BlockPlan p{};
+  const int q = (int)v.width_quarters;
+  int hw = (int)(v.image_size + 1) / 2;
+  for (int b = 0; b < blocks; ++b) {
+    p.c[b] = (b ? kChannels[b - 1] : kStemChannels) * q / 4, p.n[b] = kChannels[b] * q / 4;
+    const int out = (hw + kStrides[b] - 1) / kStrides[b];
+    auto fits = [&](auto supported) {
+      return supported((int)batch, hw, hw, p.c[b], p.n[b], kStrides[b], out, out, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr);
+    };
+    p.form[b] = fits(separable_stream_f16_supported) ? kStream : fits(separable_tile_f16_supported) ? kTile : kTwo;
+    if (p.form[b] == kTile) {
+      ++p.tiles;
+      p.packed[b] = p.packed_halfs;
+      p.packed_halfs += align_up((size_t)p.c[b] * p.n[b] * sizeof(uint16_t)) / sizeof(uint16_t);
+    }
+    hw = out;
+  }
+  if (p.tiles < 3) {
+    for (int b = 0; b < blocks; ++b)
+      if (p.form[b] == kTile) p.form[b] = kTwo;
+    p.tiles = 0, p.packed_halfs = 0;
+  }
+  return p;
 }
 
 NetPlan plan_net(const tfx_mobilenet_v1_variant& v, int64_t batch, size_t elem_bytes = sizeof(float)) {
@@ -130,6 +166,8 @@ NetPlan plan_net(const tfx_mobilenet_v1_variant& v, int64_t batch, size_t elem_b
   p.off_head = off;
   p.head = p.chain && v.width_quarters == 4 && 2 * quarter * quarter * 128 <= p.act_floats;
   if (p.head) off = align_up(off + 2 * eighth * eighth * 256 * sizeof(float));  // outputs of blocks 4 and 5
+  p.off_packed = off;
+  if (elem_bytes == sizeof(uint16_t)) off += plan_blocks_f16(v, batch, kBlocks).packed_halfs * sizeof(uint16_t);
   p.bytes = off;
   return p;
 }
@@ -749,6 +787,28 @@ int forward_f16_impl(const tfx_mobilenet_v1_variant* variant, const uint16_t* in
   uint16_t* buf[2] = {reinterpret_cast<uint16_t*>(ws + plan.off_buf[0]), reinterpret_cast<uint16_t*>(ws + plan.off_buf[1])};
   float* partial = reinterpret_cast<float*>(ws + plan.off_partial);
 
+  hipStream_t const s = static_cast<hipStream_t>(stream);
+
+  const int blocks = end_block ? end_block : kBlocks;
+  const BlockPlan form = plan_blocks_f16(*variant, batch, blocks);
+  bool aligned = true;
+  for (int b = 0; b < blocks; ++b)
+    for (const void* p : {weights->dw_w[b], weights->dw_b[b], weights->pw_w[b], weights->pw_b[b]})
+      aligned = aligned && reinterpret_cast<uintptr_t>(p) % 16 == 0;
+  uint16_t* const packed_base = reinterpret_cast<uint16_t*>(ws + plan.off_packed);
+  if (aligned && form.tiles > 0) {
+    const uint16_t* filters[kBlocks];
+    uint16_t* packed[kBlocks];
+    int tiles = 0, c[kBlocks], n[kBlocks];
+    for (int b = 0; b < blocks; ++b)
+      if (form.form[b] == kTile) {
+        filters[tiles] = weights->pw_w[b], packed[tiles] = packed_base + form.packed[b];
+        c[tiles] = form.c[b], n[tiles] = form.n[b];
+        ++tiles;
+      }
+    if (const int rc = launch_pack_filters_f16(tiles, filters, packed, c, n, s)) return rc;
+  }
+
   int64_t shape[4] = {batch, variant->image_size, variant->image_size, 3};
   const int64_t f0[4] = {3, 3, 3, kStemChannels * q / 4};
   int rc = tfx_conv2d_f16(input, shape, weights->conv0_w, f0, weights->conv0_b, 2, 2, TFX_PAD_SAME, TFX_ACT_RELU6,
@@ -758,19 +818,17 @@ int forward_f16_impl(const tfx_mobilenet_v1_variant* variant, const uint16_t* in
   conv_geometry(shape, f0, 2, 2, TFX_PAD_SAME, false, &g);
   for (int i = 0; i < 4; ++i) shape[i] = g.out[i];
   int cur = 0;
-  for (int b = 0; b < kBlocks; ++b) {
+  for (int b = 0; b < blocks; ++b) {
     const int64_t fd[4] = {3, 3, shape[3], 1};
     const int64_t cout = kChannels[b] * q / 4;
-    uint16_t* const block_out = end_block == b + 1 ? features : buf[cur ^ 1];
     conv_geometry(shape, fd, kStrides[b], kStrides[b], TFX_PAD_SAME, true, &g);
-    // large batch, early block: depthwise and pointwise layer in one filter-stationary launch (block_stream_f16.hip)
-    if (separable_stream_f16_supported((int)batch, (int)shape[1], (int)shape[2], (int)shape[3], (int)cout, kStrides[b],
-                                       (int)g.out[1], (int)g.out[2], buf[cur], weights->dw_w[b], weights->dw_b[b],
-                                       weights->pw_w[b], weights->pw_b[b], block_out)) {
-      rc = launch_separable_stream_f16(buf[cur], weights->dw_w[b], weights->dw_b[b], weights->pw_w[b], weights->pw_b[b],
-                                       block_out, (int)batch, (int)shape[1], (int)shape[2], (int)shape[3], (int)cout,
-                                       (int)g.out[1], (int)g.out[2], kStrides[b], (int)g.pad[0], (int)g.pad[2],
-                                       TFX_ACT_RELU6, TFX_ACT_RELU6, static_cast<hipStream_t>(stream));
+    if (aligned && form.form[b] != kTwo) {
+      const bool tile = form.form[b] == kTile;
+      const auto launch = tile ? launch_separable_tile_f16 : launch_separable_stream_f16;
+      rc = launch(buf[cur], weights->dw_w[b], weights->dw_b[b], tile ? packed_base + form.packed[b] : weights->pw_w[b],
+                  weights->pw_b[b], end_block == b + 1 ? features : buf[cur ^ 1], (int)batch, (int)shape[1], (int)shape[2],
+                  (int)shape[3], (int)cout, (int)g.out[1], (int)g.out[2], kStrides[b], (int)g.pad[0], (int)g.pad[2],
+                  TFX_ACT_RELU6, TFX_ACT_RELU6, s);
       if (rc) return rc;
       if (end_block == b + 1) return TFX_OK;
       for (int i = 0; i < 3; ++i) shape[i] = g.out[i];
@@ -792,8 +850,7 @@ int forward_f16_impl(const tfx_mobilenet_v1_variant* variant, const uint16_t* in
     cur ^= 1;
   }
   return launch_pool_fc_softmax_f16(buf[cur], weights->fc_w, weights->fc_b, partial, logits, probs, (int)batch,
-                                    (int)(shape[1] * shape[2]), (int)shape[3], (int)variant->classes,
-                                    static_cast<hipStream_t>(stream));
+                                    (int)(shape[1] * shape[2]), (int)shape[3], (int)variant->classes, s);
 }
 
 }  // namespace

@@ -1,0 +1,338 @@
+// A depthwise-separable block (depthwise 3x3 + bias + clamp, pointwise 1x1 + bias + clamp) on binary16 storage in one
+// launch, for the layers whose pointwise filter does not fit a workgroup's LDS (Section 4.1 storage format, the 28 x 28 ...
+// 7 x 7 blocks of the Section 3.9 network).
+//
+// A workgroup owns a tile of 32 TM output pixels, as strips of four neighbours in a row of the map, and 64 columns for
+// each of its groups of wavefronts.  First all its threads compute the depthwise output of the tile -- the whole depth of
+// the contraction, up to 132 KB -- into LDS, rounded to binary16 as the separate kernel rounds it (the same bits): an item
+// is 8 channels of two strips, whose 18 16-byte pieces each are all loaded before the first multiply.  Then each wavefront
+// multiplies the tile by its 64 columns of the filter (v_mfma_f32_32x32x16_f16), whose operands it loads straight from L2,
+// four k-steps ahead.  The depthwise output so never goes to memory and back, one launch of two is left, and no barrier
+// stands in the contraction.
+//
+// The filter comes in the order of the operands, 16 bytes for a lane; pack_filters_kernel puts the filters of all such
+// layers of a pass into it, in one launch of 4 us (loaded as it is stored, two columns of a k-row at a time, the
+// contraction took 11 us instead of 7, and more in all layers together than that launch).
+//
+// 64 x 14 x 14 x 512 -> 512, one layer: 18.9 us, of which 6.6 are launch and stores, 6 the depthwise layer (its loads), 7
+// the contraction (6 with its operands at hand); the two separate kernels take 26 back to back and 32 in the network.
+// 64 x 28 x 28 x 256 -> 256 33 -> 26.5, 64 x 28 x 28 x 256 -> 512 at stride 2 20 -> 13.6, 64 x 7 x 7 x 1024 -> 1024 23 -> 20.
+#include "stream_f16.h"
+
+namespace tfx {
+namespace {
+
+using namespace f16s;
+
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+
+constexpr int kXcds = 8, kAhead = 4, kMaxLayers = 13;
+
+struct TileBlockArgs {
+  const half_t *x, *dw_w, *dw_b, *pw_w, *pw_b;
+  half_t* y;
+  int H, W, C, N, OH, OW, pt, pl;
+  int row_strips, strips, tiles_n, total;
+  unsigned x_bytes;
+  int dw_act, pw_act;
+};
+
+// S: stride; TM: 32-pixel blocks of a tile; WK: parts of the contraction (wavefront = column group + WN x part)
+template <int S, int TM, int WK>
+__global__ __launch_bounds__(512) void separable_tile_f16_kernel(TileBlockArgs g) {
+  constexpr int STRIPS = 8 * TM;
+  struct Strip {
+    int out, count, ih, iw, image;  // first output pixel, pixels inside the map; first tap's row and column, image's first row
+  };
+  extern __shared__ __align__(16) half_t tile[];  // the tile's depthwise output, [32 TM][C + 8]; later the parts' sums
+  __shared__ Strip strip[STRIPS];
+
+  const int tid = threadIdx.x, lane = tid % 64, wave = __builtin_amdgcn_readfirstlane(tid / 64);
+  const int li = lane % 32, h = lane / 32;
+  const int waves_n = (int)blockDim.x / 64 / WK, wn = wave % waves_n, part = wave / waves_n;
+  int bid = blockIdx.x;
+  {  // tiles of the same pixels, and neighbouring ones, on one XCD
+    const int q = g.total / kXcds, rem = g.total % kXcds, xcd = bid % kXcds;
+    bid = xcd * q + (xcd < rem ? xcd : rem) + bid / kXcds;
+  }
+  const int tile_n = bid % g.tiles_n, tile_m = bid / g.tiles_n;
+  const int C = g.C, N = g.N, C8 = C / 8, LD = C + 8;
+
+  if (tid < STRIPS) {
+    const int i = tile_m * STRIPS + tid;
+    const int row = i / g.row_strips, ow = 4 * (i % g.row_strips), n = row / g.OH, oh = row % g.OH;
+    Strip s;
+    s.out = row * g.OW + ow;
+    s.count = i < g.strips ? (g.OW - ow < 4 ? g.OW - ow : 4) : 0;
+    s.ih = oh * S - g.pt;
+    s.iw = ow * S - g.pl;
+    s.image = n * g.H;
+    strip[tid] = s;
+  }
+  __syncthreads();
+
+  const __amdgpu_buffer_rsrc_t xr = __builtin_amdgcn_make_buffer_rsrc(const_cast<half_t*>(g.x), 0, (int)g.x_bytes, 0x00020000);
+  const ActClamp dw_clamp = make_act(g.dw_act);
+  for (int item = tid; item < STRIPS / 2 * C8; item += (int)blockDim.x) {
+    const int s = item / C8, c8 = item - s * C8;
+    constexpr int PX = S == 1 ? 4 : 2, COLS = (PX - 1) * S + 3;  // pixels at a time, and the columns that they read
+    constexpr int PER = 4 / PX, CHUNKS = 2 * PER;                // of the strips s and s + STRIPS / 2
+    u32x4 wraw[9];
+#pragma unroll
+    for (int t = 0; t < 9; ++t) wraw[t] = *reinterpret_cast<const u32x4*>(g.dw_w + (size_t)t * C + 8 * c8);
+    const h8 bv = *reinterpret_cast<const h8*>(g.dw_b + 8 * c8);
+    // byte offsets of a row and a column of x; outside the map (and for a strip outside the batch) the largest, which the
+    // saturating sum keeps: such a load is past the end and reads zeros
+    u32x4 win[2][3][COLS];
+    auto load_chunk = [&](int ch, u32x4 (&v)[3][COLS]) __attribute__((always_inline)) {
+      const Strip st = strip[s + STRIPS / 2 * (ch / PER)];
+      unsigned row_off[3];
+#pragma unroll
+      for (int i = 0; i < 3; ++i)
+        row_off[i] = (unsigned)(st.ih + i) < (unsigned)g.H && st.count > 0 ? 2u * ((unsigned)(st.image + st.ih + i) * g.W * C + 8 * c8) : ~0u;
+#pragma unroll
+      for (int j = 0; j < COLS; ++j) {
+        const int iw = st.iw + ch % PER * PX * S + j;
+        const unsigned col_off = (unsigned)iw < (unsigned)g.W ? 2u * (unsigned)(iw * C) : ~0u;
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+          v[i][j] = __builtin_amdgcn_raw_buffer_load_b128(xr, __builtin_elementwise_add_sat(row_off[i], col_off), 0, 0);
+      }
+    };
+    load_chunk(0, win[0]);
+#pragma unroll
+    for (int ch = 0; ch < CHUNKS; ++ch) {
+      if (ch + 1 < CHUNKS) load_chunk(ch + 1, win[(ch + 1) & 1]);
+#pragma unroll
+      for (int p = 0; p < PX; ++p) {
+        f32x4 acc[2];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) acc[e / 4][e % 4] = (float)bv[e];
+#pragma unroll
+        for (int t = 0; t < 9; ++t) {
+          // the filter stays packed: without the empty asm its conversions to fp32 are hoisted into 72 more registers
+          asm volatile("" : "+v"(wraw[t]));
+          const h8 wt = __builtin_bit_cast(h8, wraw[t]), xt = __builtin_bit_cast(h8, win[ch & 1][t / 3][p * S + t % 3]);
+#pragma unroll
+          for (int e = 0; e < 8; ++e) acc[e / 4][e % 4] = fmaf((float)xt[e], (float)wt[e], acc[e / 4][e % 4]);
+        }
+        h8 out[1];
+        activate_and_pack(acc, dw_clamp, out);
+        *reinterpret_cast<h8*>(tile + (4 * (s + STRIPS / 2 * (ch / PER)) + ch % PER * PX + p) * LD + 8 * c8) = out[0];
+      }
+    }
+  }
+
+  // the filter's operands, in the order of pack_filters_kernel
+  const int n0 = 64 * (tile_n * waves_n + wn);
+  const int steps = C / 16, s0 = steps / WK * part, s1 = s0 + steps / WK;
+  const h8* const wp = reinterpret_cast<const h8*>(g.pw_w) + (size_t)(n0 / 64) * steps * 128 + lane;
+  h8 raw[kAhead][2];
+  auto load_step = [&](int s, h8 (&r)[2]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) r[i] = wp[(2 * s + i) * 64];
+  };
+#pragma unroll
+  for (int u = 0; u < kAhead; ++u) load_step(s0 + u, raw[u]);
+  f32x16 acc[TM][2];
+#pragma unroll
+  for (int t = 0; t < TM; ++t)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) acc[t][0][i] = acc[t][1][i] = 0.f;
+  __syncthreads();
+
+  // The scheduling barriers keep the loads of a step together: left to itself the compiler mixes those of four steps, and
+  // the first step then waits for all of them.
+  const half_t* const a_base = tile + li * LD + 8 * h;
+  h8 a[2][TM];
+#pragma unroll
+  for (int t = 0; t < TM; ++t) a[0][t] = *reinterpret_cast<const h8*>(a_base + 32 * t * LD + 16 * s0);
+  for (int s = s0; s < s1; s += kAhead) {
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) {
+      const int next = s + u + 1 < s1 ? s + u + 1 : s0;
+#pragma unroll
+      for (int t = 0; t < TM; ++t) a[(u + 1) & 1][t] = *reinterpret_cast<const h8*>(a_base + 32 * t * LD + 16 * next);
+      const h8 b0 = raw[u][0], b1 = raw[u][1];
+      load_step(s + u + kAhead < s1 ? s + u + kAhead : s1 - 1, raw[u]);  // past the end: the last step again, dropped
+#pragma unroll
+      for (int t = 0; t < TM; ++t) {
+        acc[t][0] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[u & 1][t], b0, acc[t][0], 0, 0, 0);
+        acc[t][1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[u & 1][t], b1, acc[t][1], 0, 0, 0);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+
+  const ActClamp pw_clamp = make_act(g.pw_act);
+  const half_t* const bias = g.pw_b + n0 + 2 * li;
+  const float bias0 = (float)bias[0], bias1 = (float)bias[1];
+  half_t* const yc = g.y + n0 + 2 * li;
+  // group q of the accumulators: the four pixels of strip 2 q + h
+  auto emit = [&](int q, const float (&v0)[4], const float (&v1)[4]) __attribute__((always_inline)) {
+    const Strip st = strip[2 * q + h];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      typedef half_t h2 __attribute__((ext_vector_type(2)));
+      const h2 o = {(half_t)apply_act(v0[r] + bias0, pw_clamp), (half_t)apply_act(v1[r] + bias1, pw_clamp)};
+      if (r < st.count) *reinterpret_cast<h2*>(yc + (size_t)(st.out + r) * N) = o;
+    }
+  };
+  if constexpr (WK == 1) {
+#pragma unroll
+    for (int q = 0; q < 4 * TM; ++q) {
+      float v0[4], v1[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) v0[r] = acc[q / 4][0][4 * (q % 4) + r], v1[r] = acc[q / 4][1][4 * (q % 4) + r];
+      emit(q, v0, v1);
+    }
+  } else {
+    // the parts' sums through LDS: part p adds up groups p QP ... of its columns
+    constexpr int QP = 4 * TM / WK;
+    static_assert(QP >= 1, "a group for every part");
+    float* const sums = reinterpret_cast<float*>(tile);  // [wave][group][8][64]
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 4 * TM; ++q)
+#pragma unroll
+      for (int r = 0; r < 8; ++r)
+        sums[((wave * 4 * TM + q) * 8 + r) * 64 + lane] = acc[q / 4][r / 4][4 * (q % 4) + r % 4];
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < QP; ++i) {
+      const int q = part * QP + i;
+      float v[2][4];
+#pragma unroll
+      for (int r = 0; r < 8; ++r) {
+        float t = 0.f;
+#pragma unroll
+        for (int p = 0; p < WK; ++p) t += sums[(((p * waves_n + wn) * 4 * TM + q) * 8 + r) * 64 + lane];
+        v[r / 4][r % 4] = t;
+      }
+      emit(q, v[0], v[1]);
+    }
+  }
+}
+
+// The operands of the contraction's k-step s (rows 16 s ... + 15) and 64 columns from 64 c on, for each lane: 8 rows from
+// 8 (lane / 32) on of column 2 (lane % 32), then of the next column, at piece 128 (steps c + s) + lane (+ 64).
+struct PackArgs {
+  const half_t* w[kMaxLayers];
+  h8* out[kMaxLayers];
+  int c[kMaxLayers], n[kMaxLayers], first[kMaxLayers + 1];  // first: workgroups of the layers before
+  int layers;
+};
+__global__ __launch_bounds__(256) void pack_filters_kernel(PackArgs g) {
+  int l = 0;
+  while (l + 1 < g.layers && (int)blockIdx.x >= g.first[l + 1]) ++l;
+  const int u = ((int)blockIdx.x - g.first[l]) * 4 + (int)threadIdx.x / 64, lane = threadIdx.x % 64;
+  const int N = g.n[l], groups = N / 64, steps = g.c[l] / 16;
+  if (u >= groups * steps) return;
+  const int c = u % groups, s = u / groups;
+  const half_t* const w = g.w[l] + (size_t)(16 * s + 8 * (lane / 32)) * N + 64 * c + 2 * (lane % 32);
+  unsigned raw[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) raw[i] = *reinterpret_cast<const unsigned*>(w + (size_t)i * N);
+  u32x4 b0, b1;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    b0[j] = __builtin_amdgcn_perm(raw[2 * j + 1], raw[2 * j], 0x05040100u);
+    b1[j] = __builtin_amdgcn_perm(raw[2 * j + 1], raw[2 * j], 0x07060302u);
+  }
+  h8* const out = g.out[l] + (size_t)128 * (steps * c + s) + lane;
+  out[0] = __builtin_bit_cast(h8, b0);
+  out[64] = __builtin_bit_cast(h8, b1);
+}
+
+template <int S, int TM, int WK>
+int launch_tile(const TileBlockArgs& args, int waves_n, hipStream_t stream) {
+  TileBlockArgs g = args;
+  auto kern = separable_tile_f16_kernel<S, TM, WK>;
+  const size_t depth = (size_t)32 * TM * (g.C + 8) * sizeof(half_t), sums = WK == 1 ? 0 : (size_t)waves_n * WK * TM * 32 * 64 * sizeof(float);
+  const size_t lds_bytes = depth > sums ? depth : sums;
+  static std::atomic<uint64_t> lds_allowed{0};
+  if (allow_dynamic_lds(reinterpret_cast<const void*>(kern), 160 * 1024 - 1024, lds_allowed) != TFX_OK) return TFX_ERR_LAUNCH;
+  g.tiles_n = g.N / (64 * waves_n);
+  const int tiles_m = (g.strips + 8 * TM - 1) / (8 * TM);
+  g.total = tiles_m * g.tiles_n;
+  hipLaunchKernelGGL(kern, dim3((unsigned)g.total), dim3(64u * waves_n * WK), lds_bytes, stream, g);
+  return check_launch();
+}
+
+// The largest divisor of `groups` up to `most`.
+int divisor(int groups, int most) {
+  for (int d = groups < most ? groups : most; d > 1; --d)
+    if (groups % d == 0) return d;
+  return 1;
+}
+
+// The tile (32 tm pixels, column groups of wavefronts, parts of the contraction): the largest that gives at least 160
+// workgroups -- one per CU is enough for the long ones -- since every workgroup reads its columns of the filter, and all of
+// a tile's workgroups compute its depthwise layer.  64 x 14 x 14 x 512 with {2, 8, 1} 18.9 us, {2, 4, 1} 23.4, {1, 8, 1}
+// 27.1; 16 images with {1, 4, 2} 9.9 (against {1, 8, 1} 11.7, {2, 8, 1} 16.0), 8 with {1, 2, 4} 8.2 ({1, 8, 1} 11.2).
+struct TileForm {
+  int tm, waves_n, wk;
+};
+TileForm tile_form(long long strips, int c, int n) {
+  const int groups = n / 64;
+  auto blocks = [&](int tm, int waves_n) { return (strips + 8 * tm - 1) / (8 * tm) * (groups / waves_n); };
+  const int wide = divisor(groups, 8), half = divisor(groups, 4), two = divisor(groups, 2);
+  if (blocks(2, wide) >= 160) return {2, wide, 1};
+  if (blocks(1, wide) >= 160 || c % 128 != 0) return {1, wide, 1};
+  if (blocks(1, half) >= 160 || c % 256 != 0) return {1, half, 2};
+  return {1, two, 4};
+}
+
+}  // namespace
+
+bool separable_tile_f16_supported(int batch, int h, int w, int c, int n, int stride, int oh, int ow, const void* x,
+                                  const void* dw_w, const void* dw_b, const void* pw_w, const void* pw_b, const void* y) {
+  const void* ptrs[] = {x, dw_w, dw_b, pw_w, pw_b, y};
+  bool aligned = true;
+  for (const void* p : ptrs) aligned = aligned && reinterpret_cast<uintptr_t>(p) % 16 == 0;
+  const long long strips = (long long)batch * oh * ((ow + 3) / 4), x_bytes = (long long)batch * h * w * c * 2;
+  // output pixels (with the strips' padding) from which it is the faster: every workgroup of a tile's columns computes the
+  // depthwise layer again, so few pixels of a deep layer are not worth it (8 x 7 x 7 x 1024 10.7 us, 4 x 10.4; 7 apart)
+  const long long least = c <= 256 ? 1024 : c <= 512 ? 700 : 850;
+  return aligned && (stride == 1 || stride == 2) && c % 64 == 0 && c <= 1024 && n % 64 == 0 && n <= 1024 &&
+         x_bytes < (1ll << 31) && strips < (1ll << 28) && 4 * strips >= least;
+}
+
+int launch_separable_tile_f16(const uint16_t* x, const uint16_t* dw_w, const uint16_t* dw_b, const uint16_t* packed,
+                              const uint16_t* pw_b, uint16_t* y, int batch, int h, int w, int c, int n, int oh, int ow,
+                              int stride, int pt, int pl, int dw_act, int pw_act, hipStream_t stream) {
+  auto p = [](const uint16_t* q) { return reinterpret_cast<const half_t*>(q); };
+  const int strips = batch * oh * ((ow + 3) / 4);
+  const TileBlockArgs g{p(x), p(dw_w), p(dw_b), p(packed), p(pw_b), reinterpret_cast<half_t*>(y), h, w, c, n, oh, ow, pt, pl,
+                        (ow + 3) / 4, strips, 0, 0, (unsigned)((long long)batch * h * w * c * 2), dw_act, pw_act};
+  const TileForm f = tile_form(strips, c, n);
+#define TFX_TILE(S, TM, WK) \
+  if (stride == S && f.tm == TM && f.wk == WK) return launch_tile<S, TM, WK>(g, f.waves_n, stream);
+  TFX_TILE(1, 2, 1)
+  TFX_TILE(1, 1, 1)
+  TFX_TILE(1, 1, 2)
+  TFX_TILE(1, 1, 4)
+  TFX_TILE(2, 2, 1)
+  TFX_TILE(2, 1, 1)
+  TFX_TILE(2, 1, 2)
+  TFX_TILE(2, 1, 4)
+#undef TFX_TILE
+  return TFX_ERR_UNSUPPORTED;
+}
+
+int launch_pack_filters_f16(int layers, const uint16_t* const* w, uint16_t* const* packed, const int* c, const int* n,
+                            hipStream_t stream) {
+  PackArgs g{};
+  if (layers > kMaxLayers) return TFX_ERR_UNSUPPORTED;
+  for (int i = 0; i < layers; ++i) {
+    g.w[i] = reinterpret_cast<const half_t*>(w[i]);
+    g.out[i] = reinterpret_cast<h8*>(packed[i]);
+    g.c[i] = c[i], g.n[i] = n[i];
+    g.first[i + 1] = g.first[i] + (c[i] / 16 * (n[i] / 64) + 3) / 4;
+  }
+  g.layers = layers;
+  hipLaunchKernelGGL(pack_filters_kernel, dim3((unsigned)g.first[layers]), dim3(256), 0, stream, g);
+  return check_launch();
+}
+
+}  // namespace tfx

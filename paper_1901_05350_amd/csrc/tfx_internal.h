@@ -337,6 +337,16 @@ int launch_separable_stream_f16(const uint16_t* x, const uint16_t* dw_w, const u
                                 const uint16_t* pw_b, uint16_t* y, int batch, int h, int w, int c, int n, int oh, int ow,
                                 int stride, int pt, int pl, int dw_act, int pw_act, hipStream_t stream);
 
+// The same of layers with larger filters: a tile's depthwise output in LDS (block_tile_f16.hip).  `packed`: the pointwise
+// filter in the order of launch_pack_filters_f16 (as many halfs), which takes those of up to 13 layers.
+bool separable_tile_f16_supported(int batch, int h, int w, int c, int n, int stride, int oh, int ow, const void* x,
+                                  const void* dw_w, const void* dw_b, const void* pw_w, const void* pw_b, const void* y);
+int launch_separable_tile_f16(const uint16_t* x, const uint16_t* dw_w, const uint16_t* dw_b, const uint16_t* packed,
+                              const uint16_t* pw_b, uint16_t* y, int batch, int h, int w, int c, int n, int oh, int ow,
+                              int stride, int pt, int pl, int dw_act, int pw_act, hipStream_t stream);
+int launch_pack_filters_f16(int layers, const uint16_t* const* w, uint16_t* const* packed, const int* c, const int* n,
+                            hipStream_t stream);
+
 inline int check_launch() { return hipGetLastError() == hipSuccess ? TFX_OK : TFX_ERR_LAUNCH; }
 
 // A kernel that uses more than 64 KB of dynamic LDS has to be allowed to, once per device (the attribute

@@ -379,6 +379,28 @@ def test_mobilenet_f16_internal_activations(size, batch, blocks):
     end_to_end_bar(host(l), logits, "f16 logits batch %d size %d" % (batch, size), 8)
 
 
+@pytest.mark.parametrize("q,size,batch,blocks", [(4, 224, 8, (6, 7, 12, 13)), (4, 224, 17, (5, 11)), (3, 131, 41, (5, 9, 13)),
+                                                 (2, 160, 64, (4, 8, 12)), (1, 224, 40, (8, 13)), (4, 224, 64, (5, 6, 11, 12, 13))])
+def test_mobilenet_f16_tile_blocks(q, size, batch, blocks):
+    """Blocks whose depthwise output stays in LDS (block_tile_f16.hip) against the single-op kernels that one image takes:
+    every tile form, ragged rows and last tiles, channel counts of every width, both strides, a NaN."""
+    import paper_1901_05350_amd as tfx
+    d = inputs.mobilenet_v1_f16(seed=70 + q, batch=2, image_size=size, width_quarters=q, classes=10)
+    d["image"][1, 60, 37, 1] = np.nan
+    image = np.concatenate([d["image"]] * (batch // 2) + [d["image"][:batch % 2]])
+    model = tfx.MobileNetV1F16(d["weights"], batch=batch, image_size=size, width_quarters=q)
+    one = tfx.MobileNetV1F16(d["weights"], batch=1, image_size=size, width_quarters=q)
+    for k in blocks:
+        got = host(model.features(dev16(image), k))
+        for i in (0, 1):
+            ref = host(one.features(dev16(d["image"][i:i + 1]), k))
+            assert np.array_equal(np.isnan(got[i:i + 1]), np.isnan(ref))
+            keep = ~np.isnan(ref).any(axis=-1)
+            end_to_end_bar(got[i:i + 1][keep], ref[keep], "block %d image %d" % (k, i), 4 if k <= 5 else 8)
+            same = got[i::2]
+            assert np.array_equal(same.view(np.uint16), np.repeat(same[:1], len(same), axis=0).view(np.uint16))
+
+
 @pytest.mark.parametrize("batch,blocks", [(8, (1, 2, 3)), (21, (4,))])
 def test_mobilenet_f16_nan_and_inf_through_the_fused_blocks_at_large_batch(batch, blocks):
     """A NaN in one image reaches exactly the outputs whose windows hold it, block after block, and no other image;
