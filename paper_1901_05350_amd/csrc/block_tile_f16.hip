@@ -2,21 +2,22 @@
 // launch, for the layers whose pointwise filter does not fit a workgroup's LDS (Section 4.1 storage format, the 28 x 28 ...
 // 7 x 7 blocks of the Section 3.9 network).
 //
-// A workgroup owns a tile of 32 TM output pixels, as strips of four neighbours in a row of the map, and 64 columns for
-// each of its groups of wavefronts.  First all its threads compute the depthwise output of the tile -- the whole depth of
-// the contraction, up to 132 KB -- into LDS, rounded to binary16 as the separate kernel rounds it (the same bits): an item
-// is 8 channels of two strips, whose 18 16-byte pieces each are all loaded before the first multiply.  Then each wavefront
-// multiplies the tile by its 64 columns of the filter (v_mfma_f32_32x32x16_f16), whose operands it loads straight from L2,
-// four k-steps ahead.  The depthwise output so never goes to memory and back, one launch of two is left, and no barrier
-// stands in the contraction.
+// A workgroup owns a tile of 32 TM output pixels, as patches of 4 x 2, and 64 columns for each of its groups of wavefronts.
+// First all its threads compute the depthwise output of the tile -- the whole depth of the contraction, up to 132 KB -- into
+// LDS, rounded to binary16 as the separate kernel rounds it (the same bits): an item is 8 channels of a patch, whose 24
+// 16-byte pieces (stride 2: 25 for each half) are all loaded before the first multiply.  Then each wavefront multiplies the
+// tile by its 64 columns of the filter (v_mfma_f32_32x32x16_f16), whose operands it loads straight from L2, four k-steps
+// ahead.  The depthwise output so never goes to memory and back, one launch of two is left, and no barrier stands in the
+// contraction.
 //
 // The filter comes in the order of the operands, 16 bytes for a lane; pack_filters_kernel puts the filters of all such
 // layers of a pass into it, in one launch of 4 us (loaded as it is stored, two columns of a k-row at a time, the
 // contraction took 11 us instead of 7, and more in all layers together than that launch).
 //
-// 64 x 14 x 14 x 512 -> 512, one layer: 18.9 us, of which 6.6 are launch and stores, 6 the depthwise layer (its loads), 7
-// the contraction (6 with its operands at hand); the two separate kernels take 26 back to back and 32 in the network.
-// 64 x 28 x 28 x 256 -> 256 33 -> 26.5, 64 x 28 x 28 x 256 -> 512 at stride 2 20 -> 13.6, 64 x 7 x 7 x 1024 -> 1024 23 -> 20.
+// 64 x 14 x 14 x 512 -> 512, one layer: 17.6 us, of which 6.6 are launch and stores, 5 the depthwise layer (its loads; with
+// strips of 4 x 1, 18 pieces for four pixels, 6) and 7 the contraction (6 with its operands at hand); the two separate
+// kernels take 26 back to back and 32 in the network.
+// 64 x 28 x 28 x 256 -> 256 33 -> 25, 64 x 28 x 28 x 256 -> 512 at stride 2 20 -> 13.6, 64 x 7 x 7 x 1024 -> 1024 23 -> 20.
 #include "stream_f16.h"
 
 namespace tfx {
@@ -32,7 +33,7 @@ struct TileBlockArgs {
   const half_t *x, *dw_w, *dw_b, *pw_w, *pw_b;
   half_t* y;
   int H, W, C, N, OH, OW, pt, pl;
-  int row_strips, strips, tiles_n, total;
+  int row_patches, col_patches, patches, tiles_n, total;
   unsigned x_bytes;
   int dw_act, pw_act;
 };
@@ -40,12 +41,12 @@ struct TileBlockArgs {
 // S: stride; TM: 32-pixel blocks of a tile; WK: parts of the contraction (wavefront = column group + WN x part)
 template <int S, int TM, int WK>
 __global__ __launch_bounds__(512) void separable_tile_f16_kernel(TileBlockArgs g) {
-  constexpr int STRIPS = 8 * TM;
-  struct Strip {
-    int out, count, ih, iw, image;  // first output pixel, pixels inside the map; first tap's row and column, image's first row
+  constexpr int PATCHES = 4 * TM;
+  struct Patch {
+    int out, cols, rows, ih, iw, image;  // first output pixel, extent inside the map; first tap's row and column, image's first row
   };
   extern __shared__ __align__(16) half_t tile[];  // the tile's depthwise output, [32 TM][C + 8]; later the parts' sums
-  __shared__ Strip strip[STRIPS];
+  __shared__ Patch patch[PATCHES];
 
   const int tid = threadIdx.x, lane = tid % 64, wave = __builtin_amdgcn_readfirstlane(tid / 64);
   const int li = lane % 32, h = lane / 32;
@@ -58,53 +59,49 @@ __global__ __launch_bounds__(512) void separable_tile_f16_kernel(TileBlockArgs g
   const int tile_n = bid % g.tiles_n, tile_m = bid / g.tiles_n;
   const int C = g.C, N = g.N, C8 = C / 8, LD = C + 8;
 
-  if (tid < STRIPS) {
-    const int i = tile_m * STRIPS + tid;
-    const int row = i / g.row_strips, ow = 4 * (i % g.row_strips), n = row / g.OH, oh = row % g.OH;
-    Strip s;
-    s.out = row * g.OW + ow;
-    s.count = i < g.strips ? (g.OW - ow < 4 ? g.OW - ow : 4) : 0;
-    s.ih = oh * S - g.pt;
-    s.iw = ow * S - g.pl;
-    s.image = n * g.H;
-    strip[tid] = s;
+  if (tid < PATCHES) {
+    const int i = tile_m * PATCHES + tid, row = i / g.row_patches, n = row / g.col_patches;
+    const int ow = 4 * (i % g.row_patches), oh = 2 * (row % g.col_patches);
+    Patch p;
+    p.out = (n * g.OH + oh) * g.OW + ow;
+    p.cols = i < g.patches ? (g.OW - ow < 4 ? g.OW - ow : 4) : 0;
+    p.rows = g.OH - oh < 2 ? 1 : 2;
+    p.ih = oh * S - g.pt;
+    p.iw = ow * S - g.pl;
+    p.image = n * g.H;
+    patch[tid] = p;
   }
   __syncthreads();
 
   const __amdgpu_buffer_rsrc_t xr = __builtin_amdgcn_make_buffer_rsrc(const_cast<half_t*>(g.x), 0, (int)g.x_bytes, 0x00020000);
   const ActClamp dw_clamp = make_act(g.dw_act);
-  for (int item = tid; item < STRIPS / 2 * C8; item += (int)blockDim.x) {
+  for (int item = tid; item < PATCHES * C8; item += (int)blockDim.x) {
     const int s = item / C8, c8 = item - s * C8;
-    constexpr int PX = S == 1 ? 4 : 2, COLS = (PX - 1) * S + 3;  // pixels at a time, and the columns that they read
-    constexpr int PER = 4 / PX, CHUNKS = 2 * PER;                // of the strips s and s + STRIPS / 2
+    constexpr int PX = S == 1 ? 4 : 2, ROWS = S + 3, COLS = (PX - 1) * S + 3;  // columns at a time, and what they read
     u32x4 wraw[9];
 #pragma unroll
     for (int t = 0; t < 9; ++t) wraw[t] = *reinterpret_cast<const u32x4*>(g.dw_w + (size_t)t * C + 8 * c8);
     const h8 bv = *reinterpret_cast<const h8*>(g.dw_b + 8 * c8);
-    // byte offsets of a row and a column of x; outside the map (and for a strip outside the batch) the largest, which the
+    // byte offsets of a row and a column of x; outside the map (and for a patch outside the batch) the largest, which the
     // saturating sum keeps: such a load is past the end and reads zeros
-    u32x4 win[2][3][COLS];
-    auto load_chunk = [&](int ch, u32x4 (&v)[3][COLS]) __attribute__((always_inline)) {
-      const Strip st = strip[s + STRIPS / 2 * (ch / PER)];
-      unsigned row_off[3];
+    const Patch pt = patch[s];
+    unsigned row_off[ROWS];
 #pragma unroll
-      for (int i = 0; i < 3; ++i)
-        row_off[i] = (unsigned)(st.ih + i) < (unsigned)g.H && st.count > 0 ? 2u * ((unsigned)(st.image + st.ih + i) * g.W * C + 8 * c8) : ~0u;
+    for (int i = 0; i < ROWS; ++i)
+      row_off[i] = (unsigned)(pt.ih + i) < (unsigned)g.H && pt.cols > 0 ? 2u * ((unsigned)(pt.image + pt.ih + i) * g.W * C + 8 * c8) : ~0u;
+#pragma unroll
+    for (int p0 = 0; p0 < 4; p0 += PX) {
+      u32x4 win[ROWS][COLS];
 #pragma unroll
       for (int j = 0; j < COLS; ++j) {
-        const int iw = st.iw + ch % PER * PX * S + j;
+        const int iw = pt.iw + p0 * S + j;
         const unsigned col_off = (unsigned)iw < (unsigned)g.W ? 2u * (unsigned)(iw * C) : ~0u;
 #pragma unroll
-        for (int i = 0; i < 3; ++i)
-          v[i][j] = __builtin_amdgcn_raw_buffer_load_b128(xr, __builtin_elementwise_add_sat(row_off[i], col_off), 0, 0);
+        for (int i = 0; i < ROWS; ++i)
+          win[i][j] = __builtin_amdgcn_raw_buffer_load_b128(xr, __builtin_elementwise_add_sat(row_off[i], col_off), 0, 0);
       }
-    };
-    load_chunk(0, win[0]);
 #pragma unroll
-    for (int ch = 0; ch < CHUNKS; ++ch) {
-      if (ch + 1 < CHUNKS) load_chunk(ch + 1, win[(ch + 1) & 1]);
-#pragma unroll
-      for (int p = 0; p < PX; ++p) {
+      for (int p = 0; p < 2 * PX; ++p) {
         f32x4 acc[2];
 #pragma unroll
         for (int e = 0; e < 8; ++e) acc[e / 4][e % 4] = (float)bv[e];
@@ -112,13 +109,13 @@ __global__ __launch_bounds__(512) void separable_tile_f16_kernel(TileBlockArgs g
         for (int t = 0; t < 9; ++t) {
           // the filter stays packed: without the empty asm its conversions to fp32 are hoisted into 72 more registers
           asm volatile("" : "+v"(wraw[t]));
-          const h8 wt = __builtin_bit_cast(h8, wraw[t]), xt = __builtin_bit_cast(h8, win[ch & 1][t / 3][p * S + t % 3]);
+          const h8 wt = __builtin_bit_cast(h8, wraw[t]), xt = __builtin_bit_cast(h8, win[p % 2 * S + t / 3][p / 2 * S + t % 3]);
 #pragma unroll
           for (int e = 0; e < 8; ++e) acc[e / 4][e % 4] = fmaf((float)xt[e], (float)wt[e], acc[e / 4][e % 4]);
         }
         h8 out[1];
         activate_and_pack(acc, dw_clamp, out);
-        *reinterpret_cast<h8*>(tile + (4 * (s + STRIPS / 2 * (ch / PER)) + ch % PER * PX + p) * LD + 8 * c8) = out[0];
+        *reinterpret_cast<h8*>(tile + (8 * s + 4 * (p % 2) + p0 + p / 2) * LD + 8 * c8) = out[0];
       }
     }
   }
@@ -168,14 +165,15 @@ __global__ __launch_bounds__(512) void separable_tile_f16_kernel(TileBlockArgs g
   const half_t* const bias = g.pw_b + n0 + 2 * li;
   const float bias0 = (float)bias[0], bias1 = (float)bias[1];
   half_t* const yc = g.y + n0 + 2 * li;
-  // group q of the accumulators: the four pixels of strip 2 q + h
+  // group q of the accumulators: the four pixels of row h of patch q
   auto emit = [&](int q, const float (&v0)[4], const float (&v1)[4]) __attribute__((always_inline)) {
-    const Strip st = strip[2 * q + h];
+    const Patch pt = patch[q];
+    const int count = h < pt.rows ? pt.cols : 0, first = pt.out + h * g.OW;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       typedef half_t h2 __attribute__((ext_vector_type(2)));
       const h2 o = {(half_t)apply_act(v0[r] + bias0, pw_clamp), (half_t)apply_act(v1[r] + bias1, pw_clamp)};
-      if (r < st.count) *reinterpret_cast<h2*>(yc + (size_t)(st.out + r) * N) = o;
+      if (r < count) *reinterpret_cast<h2*>(yc + (size_t)(first + r) * N) = o;
     }
   };
   if constexpr (WK == 1) {
@@ -253,7 +251,7 @@ int launch_tile(const TileBlockArgs& args, int waves_n, hipStream_t stream) {
   static std::atomic<uint64_t> lds_allowed{0};
   if (allow_dynamic_lds(reinterpret_cast<const void*>(kern), 160 * 1024 - 1024, lds_allowed) != TFX_OK) return TFX_ERR_LAUNCH;
   g.tiles_n = g.N / (64 * waves_n);
-  const int tiles_m = (g.strips + 8 * TM - 1) / (8 * TM);
+  const int tiles_m = (g.patches + 4 * TM - 1) / (4 * TM);
   g.total = tiles_m * g.tiles_n;
   hipLaunchKernelGGL(kern, dim3((unsigned)g.total), dim3(64u * waves_n * WK), lds_bytes, stream, g);
   return check_launch();
@@ -273,9 +271,9 @@ int divisor(int groups, int most) {
 struct TileForm {
   int tm, waves_n, wk;
 };
-TileForm tile_form(long long strips, int c, int n) {
+TileForm tile_form(long long patches, int c, int n) {
   const int groups = n / 64;
-  auto blocks = [&](int tm, int waves_n) { return (strips + 8 * tm - 1) / (8 * tm) * (groups / waves_n); };
+  auto blocks = [&](int tm, int waves_n) { return (patches + 4 * tm - 1) / (4 * tm) * (groups / waves_n); };
   const int wide = divisor(groups, 8), half = divisor(groups, 4), two = divisor(groups, 2);
   if (blocks(2, wide) >= 160) return {2, wide, 1};
   if (blocks(1, wide) >= 160 || c % 128 != 0) return {1, wide, 1};
@@ -290,22 +288,22 @@ bool separable_tile_f16_supported(int batch, int h, int w, int c, int n, int str
   const void* ptrs[] = {x, dw_w, dw_b, pw_w, pw_b, y};
   bool aligned = true;
   for (const void* p : ptrs) aligned = aligned && reinterpret_cast<uintptr_t>(p) % 16 == 0;
-  const long long strips = (long long)batch * oh * ((ow + 3) / 4), x_bytes = (long long)batch * h * w * c * 2;
-  // output pixels (with the strips' padding) from which it is the faster: every workgroup of a tile's columns computes the
+  const long long patches = (long long)batch * ((oh + 1) / 2) * ((ow + 3) / 4), x_bytes = (long long)batch * h * w * c * 2;
+  // output pixels (with the patches' padding) from which it is the faster: every workgroup of a tile's columns computes the
   // depthwise layer again, so few pixels of a deep layer are not worth it (8 x 7 x 7 x 1024 10.7 us, 4 x 10.4; 7 apart)
   const long long least = c <= 256 ? 1024 : c <= 512 ? 700 : 850;
   return aligned && (stride == 1 || stride == 2) && c % 64 == 0 && c <= 1024 && n % 64 == 0 && n <= 1024 &&
-         x_bytes < (1ll << 31) && strips < (1ll << 28) && 4 * strips >= least;
+         x_bytes < (1ll << 31) && patches < (1ll << 27) && 8 * patches >= least;
 }
 
 int launch_separable_tile_f16(const uint16_t* x, const uint16_t* dw_w, const uint16_t* dw_b, const uint16_t* packed,
                               const uint16_t* pw_b, uint16_t* y, int batch, int h, int w, int c, int n, int oh, int ow,
                               int stride, int pt, int pl, int dw_act, int pw_act, hipStream_t stream) {
   auto p = [](const uint16_t* q) { return reinterpret_cast<const half_t*>(q); };
-  const int strips = batch * oh * ((ow + 3) / 4);
+  const int row_patches = (ow + 3) / 4, col_patches = (oh + 1) / 2, patches = batch * col_patches * row_patches;
   const TileBlockArgs g{p(x), p(dw_w), p(dw_b), p(packed), p(pw_b), reinterpret_cast<half_t*>(y), h, w, c, n, oh, ow, pt, pl,
-                        (ow + 3) / 4, strips, 0, 0, (unsigned)((long long)batch * h * w * c * 2), dw_act, pw_act};
-  const TileForm f = tile_form(strips, c, n);
+                        row_patches, col_patches, patches, 0, 0, (unsigned)((long long)batch * h * w * c * 2), dw_act, pw_act};
+  const TileForm f = tile_form(patches, c, n);
 #define TFX_TILE(S, TM, WK) \
   if (stride == S && f.tm == TM && f.wk == WK) return launch_tile<S, TM, WK>(g, f.waves_n, stream);
   TFX_TILE(1, 2, 1)
