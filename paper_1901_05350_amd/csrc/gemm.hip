@@ -734,8 +734,8 @@ int launch_gemm(const float* a, const float* b, float* c, const float* bias, int
   }
   if (batch == 1 && a_kc && (long long)m * k >= 8 && thin_pays(m, n, k, false))
     return launch_gemm_thin(a, b, c, bias, m, n, k, b_kc, act, stream);
-  const double us128 = KernelCost{128, 128, 1.5, .026, 4.7, .027}.us(batch, m, n, k);
-  const double us64 = KernelCost{64, 64, 3.6, .026, 1.27, .0102}.us(batch, m, n, k);
+  const double us128 = KernelCost{128, 128, 1.5, .026, 4.7, .027, 2}.us(batch, m, n, k);
+  const double us64 = KernelCost{64, 64, 3.6, .026, 1.27, .0102, 4}.us(batch, m, n, k);
   const double deep = KernelCost{16, n % 2 == 0 ? 32 : 16, 3.2, 0., .245, .0035}.us(batch, m, n, k);
   const double direct[3] = {KernelCost{64, 64, 1.33, 0., 3.36, .0148}.us(batch, m, n, k),
                             KernelCost{32, 64, 3.05, .0010, .88, .0090}.us(batch, m, n, k),
@@ -793,8 +793,8 @@ int launch_conv2d_gemm(const float* x, const float* w, const float* bias, float*
   if (fh == 1 && fw == 1 && sh == sw && pt == 0 && pl == 0 && thin_pays(m, co, ci, false))
     return launch_gemm_thin(x, w, y, bias, (int)m, co, ci, false, act, stream, h, wd, oh, ow, sh);
   const double kp = (double)fh * fw * ((ci + 7) / 8 * 8);
-  const double us128 = KernelCost{128, 128, 3.84, .031, 2.58, .0335}.us(1, m, co, kp);
-  const double us64 = KernelCost{64, 64, 4.49, .033, .79, .0138}.us(1, m, co, kp);
+  const double us128 = KernelCost{128, 128, 3.84, .031, 2.58, .0335, 2}.us(1, m, co, kp);
+  const double us64 = KernelCost{64, 64, 4.49, .033, .79, .0138, 4}.us(1, m, co, kp);
   const double deep = KernelCost{16, co % 2 == 0 ? 32 : 16, 2.94, 0., .31, .0046}.us(1, m, co, kp);
   const double direct[3] = {KernelCost{64, 64, 1.17, 0., 3.72, .0167}.us(1, m, co, kp),
                             KernelCost{32, 64, 2.74, .0036, 1.16, .0095}.us(1, m, co, kp),

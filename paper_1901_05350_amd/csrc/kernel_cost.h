@@ -9,12 +9,24 @@ namespace tfx {
 // per_k is the memory round trips of a chain that nothing hides, per_tile_k what k costs the CU.  Fitted to the measured
 // times of 226 products and 190 convolutions of either storage type (sizes 16 ... 4096, channels 3 ... 512; mean error
 // 4 - 18 %); over these its choice costs 2 - 4 % against the fastest kernel of each.
+//
+// `resident`: the tiled kernels keep 2 (128 x 128) or 4 (64 x 64) tiles on a CU at once, which hide each other's waits.
+// The c of a round then grows slowly from its first tile, and the first tile of the next round costs a whole one: of
+// 128 x 128 tiles 256 take 1, 308 1.4, 400 1.8, 512 2.3, and 560 as much as 700, 3.65 (measured on 110 products and 57
+// convolutions of 100 - 4000 tiles; with the plain count 1947 x 2200 x 3862 went to 64 x 64 tiles for 351 us, now 233).
 struct KernelCost {
   int bm, bn;
   double fixed, per_k, per_tile, per_tile_k;
+  int resident = 0;
   double us(long long batch, long long m, long long n, double k) const {
     const double tiles = (double)(batch * ((m + bm - 1) / bm) * ((n + bn - 1) / bn)) / 256.;
-    const double c = tiles <= 2. ? (tiles <= 1. ? 1. : 2.) : tiles + .5;
+    double c = tiles <= 2. ? (tiles <= 1. ? 1. : 2.) : tiles + .5;
+    if (resident != 0) {
+      const bool two = resident == 2;
+      const double rounds = (double)(long long)(tiles / resident), rest = tiles - rounds * resident;
+      c = rounds * (two ? 2.45 : 4.8);
+      if (rest > 0.) c += (rest <= 1. ? 1. : 1. + (two ? 1.3 : .87) * (rest - 1.)) + (rounds == 0. ? 0. : two ? .2 : .6);
+    }
     return fixed + per_k * k + c * (per_tile + per_tile_k * k);
   }
 };
