@@ -22,6 +22,7 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 PEAK_MFMA_F32 = 157.3e12   # FLOP/s, dense fp32 matrix peak of MI355X
+PEAK_SPLIT_F32 = 2.5e15 / 6  # fp32 product as six bf16 products on the matrix cores (csrc/split.h)
 PEAK_MFMA_F16 = 2.5e15     # FLOP/s, dense fp16 matrix peak (fp32 accumulate)
 PEAK_HBM = 8.0e12          # B/s
 
@@ -130,12 +131,12 @@ def main():
     # ---------------- the single-op workloads (each returns its result entry) ----------------
     reps = max(20, min(args.steps, 200))
 
-    def mfma_entry(fn, flop, nbytes, name=None):
+    def mfma_entry(fn, flop, nbytes, name=None, peak=PEAK_MFMA_F32):
         t = time_loop(fn, reps)
         return {"us": round(t * 1e6, 3), "single_launch_us": round(time_single(fn) * 1e6, 2),
                 "TFLOPs": round(flop / t / 1e12, 4), "GBps": round(nbytes / t / 1e9, 1), "algorithmic_bytes": nbytes,
-                "roofline": {"bound": "mfma", "achieved": round(flop / t / 1e12, 4), "peak": PEAK_MFMA_F32 / 1e12,
-                             "unit": "TFLOP/s", "frac": round(flop / t / PEAK_MFMA_F32, 5),
+                "roofline": {"bound": "mfma", "achieved": round(flop / t / 1e12, 4), "peak": round(peak / 1e12, 1),
+                             "unit": "TFLOP/s", "frac": round(flop / t / peak, 5),
                              "traffic": measured_traffic(name)}}
 
     def op_matmul():
@@ -149,7 +150,7 @@ def main():
         a, b = dev(d["a"]), dev(d["b"])
         c = tfx.tfx_batch_matmul(a, b, False, True)
         return mfma_entry(lambda: tfx.tfx_batch_matmul(a, b, False, True, out=c), 2 * 8 * 1024 ** 3, 3 * 8 * 1024 * 1024 * 4,
-                          "batch_matmul_8x1024x1024x1024_tB")
+                          "batch_matmul_8x1024x1024x1024_tB", PEAK_SPLIT_F32)
 
     def op_pointwise(n):
         def build():
@@ -169,7 +170,7 @@ def main():
             yy = tfx.tfx_conv2d(xx, ff, bb, 1, tfx.PAD_SAME, tfx.ACT_RELU6)
             return mfma_entry(lambda: tfx.tfx_conv2d(xx, ff, bb, 1, tfx.PAD_SAME, tfx.ACT_RELU6, out=yy),
                               2 * n * 56 * 56 * 64 * 64 * 9, 4 * (xx.numel() + yy.numel() + 9 * 64 * 64 + 64),
-                              "conv3x3_%dx56x56x64_to_64" % n)
+                              "conv3x3_%dx56x56x64_to_64" % n, PEAK_SPLIT_F32)
         return build
 
     def op_depthwise(n, s, copies):
