@@ -31,21 +31,21 @@ PEAK_HBM = 8.0e12          # B/s
 # source it was measured on, with the digest of that file followed by the shared headers csrc/tfx_internal.h and
 # csrc/stream_f16.h; if any of them has changed since, the entry is reported as null.
 MEASURED_TRAFFIC = {
-    "batch_matmul_8x1024x1024x1024_tB": (100848549, "gemm.hip", "bac39288fc357e2c8673f7ea33783fd405976589242fc0199c98fa77957e03ca"),
-    "pointwise_64x56x56x128_to_128": (206181264, "pointwise.hip", "0a9baa78bfad3ce283cef204e55f924712128b899e78c4fe2fc3060cb0f5c4d8"),
-    "conv3x3_64x56x56x64_to_64": (104528320, "gemm.hip", "bac39288fc357e2c8673f7ea33783fd405976589242fc0199c98fa77957e03ca"),
-    "depthwise_64x112x112x64_s1_cold_rotation": (411139682, "depthwise.hip", "5bf610ceb3e6bbe368ffc0883ae29a9d12cb14357f03d0d20b13db3d36e3b37e"),
-    "depthwise_64x112x112x64_s2_cold_rotation": (257119699, "depthwise.hip", "5bf610ceb3e6bbe368ffc0883ae29a9d12cb14357f03d0d20b13db3d36e3b37e"),
-    "batch_matmul_f16_1x4096x4096x4096_tB": (235078145, "gemm_f16.hip", "924ffb57eaeeb75ba9838b04777ece730400211aedcaf1172be3e0061bfdce75"),
-    "batch_matmul_f16_8x1024x1024x1024_tB": (50493600, "gemm_f16.hip", "924ffb57eaeeb75ba9838b04777ece730400211aedcaf1172be3e0061bfdce75"),
-    "pointwise_f16_64x56x56x128_to_128": (104298589, "pointwise_f16.hip", "ce1b39f22ab2de85935114032f7da23fa19670dd2587c5787ce442e1a65ef9ae"),
-    "depthwise_f16_64x112x112x64_s1_cold_rotation": (205682029, "conv_f16.hip", "afe6f8ef43c1ef8148e17ecfb1317d9bb5da79a3024c8dff8ff47b6ebdc20a4d"),
-    "depthwise_f16_64x112x112x64_s2_cold_rotation": (128552106, "conv_f16.hip", "afe6f8ef43c1ef8148e17ecfb1317d9bb5da79a3024c8dff8ff47b6ebdc20a4d"),
-    "pointwise_f16_64x14x14x512_to_512": (30193140, "pointwise_slab_f16.hip", "af2faf347eb820ccf9a29fb135a9ca89ecf628f4ce49a11949d8b30c7e1a5587"),
-    "conv3x3_f16_64x56x56x64_to_64": (55026506, "conv_stream_f16.hip", "5d25ba83ebb077dcddf0dcaed1a88b53a1395351810b957ba4056c3c06bc7fe9"),
-    "add_f32_64M": (805262989, "elementwise.hip", "7f84a8e7a8ec924bce5600deb9d686a5a76abe82b88ca3d841c7cda5219bee52"),
-    "add_f16_64M": (402651879, "elementwise.hip", "7f84a8e7a8ec924bce5600deb9d686a5a76abe82b88ca3d841c7cda5219bee52"),
-    "mobilenet_chain_kernel": (121651524, "chain.hip", "d6e4fe4eea090fda5555f06e369f20246b30e6da62bbd03727c1832248106007"),
+    "batch_matmul_8x1024x1024x1024_tB": (100981151, "gemm.hip", "d7939dacb9d53741e3e98d689afff0e6268a099a748237194f3934c80a39b9fa"),
+    "pointwise_64x56x56x128_to_128": (206178801, "pointwise.hip", "bd2ffc187a28564fabcb99eaadd568df29dc41bc107f0a69c61f068533a88545"),
+    "conv3x3_64x56x56x64_to_64": (106020132, "gemm.hip", "d7939dacb9d53741e3e98d689afff0e6268a099a748237194f3934c80a39b9fa"),
+    "depthwise_64x112x112x64_s1_cold_rotation": (411135650, "depthwise.hip", "b6cb3b00ef445d7acaff8105567c83d58447115871f8f66472cfec35e840f74f"),
+    "depthwise_64x112x112x64_s2_cold_rotation": (257094017, "depthwise.hip", "b6cb3b00ef445d7acaff8105567c83d58447115871f8f66472cfec35e840f74f"),
+    "batch_matmul_f16_1x4096x4096x4096_tB": (235152325, "gemm_f16.hip", "d6d0ba339801c31485c16445ec998cf7509fcd679963289d893fb6d21557ecab"),
+    "batch_matmul_f16_8x1024x1024x1024_tB": (50539949, "gemm_f16.hip", "d6d0ba339801c31485c16445ec998cf7509fcd679963289d893fb6d21557ecab"),
+    "pointwise_f16_64x56x56x128_to_128": (104159036, "pointwise_f16.hip", "6465bfeaedd1bf57e3bf4a552e519ca8ce2e62fea0b6d07fb1b17dbc0643a591"),
+    "depthwise_f16_64x112x112x64_s1_cold_rotation": (205679923, "conv_f16.hip", "8caf7f66dd82dacebc3db73aa0bdd45b96923dc1817847550c79d1ca62d9cd41"),
+    "depthwise_f16_64x112x112x64_s2_cold_rotation": (128552465, "conv_f16.hip", "8caf7f66dd82dacebc3db73aa0bdd45b96923dc1817847550c79d1ca62d9cd41"),
+    "pointwise_f16_64x14x14x512_to_512": (30195063, "pointwise_slab_f16.hip", "8012b8f425969c51a0fca6bfc389f978bf51906f949d18a5cbc668150f77390b"),
+    "conv3x3_f16_64x56x56x64_to_64": (55026885, "conv_stream_f16.hip", "4a8944769f755fb70f62fd88ff85b7817adc411fa37506b5950eb98ea23c0c26"),
+    "add_f32_64M": (805250660, "elementwise.hip", "195263450a71be67dd8680848f3a6ff70e26ddc1f91b678d57717405d98d32b0"),
+    "add_f16_64M": (402645490, "elementwise.hip", "195263450a71be67dd8680848f3a6ff70e26ddc1f91b678d57717405d98d32b0"),
+    "mobilenet_chain_kernel": (121637893, "chain.hip", "2b0b5176dfd2f26ae0b2e607328375cca869bc44084acb5437d86ae2bb2e68b3"),
 }
 
 
