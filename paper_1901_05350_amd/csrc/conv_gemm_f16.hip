@@ -363,7 +363,7 @@ int launch_conv2d_gemm_f16(const uint16_t* x, const uint16_t* w, const uint16_t*
   // 16 x 32, 32 x 64 or 64 x 64 tiles (5x5, 13x20x20x398 -> 192: 137 us with LDS tiles, 92 split; 3x3, 2x56x56x32 -> 64:
   // 10.8 and 6.4)
   if (fh == 1 && fw == 1 && sh == sw && pt == 0 && pl == 0 && thin_pays(g.M, co, ci, true))
-    return launch_gemm_thin_f16(x, w, y, bias, g.M, co, ci, false, act, stream, h, wd, oh, ow, sh);
+    return launch_conv1x1_thin_f16(x, w, y, bias, g.M, co, ci, act, stream, h, wd, oh, ow, sh);
   const double kp = (double)fh * fw * cp;
   auto us = [&](const KernelCost& c) { return c.us(1, g.M, co, kp); };
   const double cost[6] = {us({128, 128, 4.44, 0., 3.32, .0116}), us({64, 128, 4.9, 0., 1.35, .0095}),

@@ -732,16 +732,31 @@ int launch_gemm(const float* a, const float* b, float* c, const float* bias, int
                        a_kc ? 1 : 0, b_kc ? 1 : 0, total, act);
     return check_launch();
   }
-  if (batch == 1 && a_kc && (long long)m * k >= 8 && thin_pays(m, n, k, false))
-    return launch_gemm_thin(a, b, c, bias, m, n, k, b_kc, act, stream);
-  const double us128 = KernelCost{128, 128, 1.5, .026, 4.7, .027, 2}.us(batch, m, n, k);
-  const double us64 = KernelCost{64, 64, 3.6, .026, 1.27, .0102, 4}.us(batch, m, n, k);
-  const double deep = KernelCost{16, n % 2 == 0 ? 32 : 16, 3.2, 0., .245, .0035}.us(batch, m, n, k);
-  const double direct[3] = {KernelCost{64, 64, 1.33, 0., 3.36, .0148}.us(batch, m, n, k),
-                            KernelCost{32, 64, 3.05, .0010, .88, .0090}.us(batch, m, n, k),
-                            KernelCost{32, 32, 3.48, .0012, .28, .0053}.us(batch, m, n, k)};
+  // Which kernel (kernel_cost.h).  Below 128 the contraction has constants of its own, in whole slices of the LDS tiles and
+  // whole steps of the wavefronts that split it.
+  double us128, us64, deep, direct[3];
+  if (k < 128) {
+    const int k32 = (k + 31) / 32 * 32, k64 = k < 64 ? 64 : k;
+    us128 = KernelCost{128, 128, 5.26, .0258, 2.43, .0331, 2}.us(batch, m, n, k32);
+    us64 = KernelCost{64, 64, 4.34, .0273, .686, .0116, 4}.us(batch, m, n, k32);
+    deep = shallow_deep_us(batch, m, n, k);
+    direct[0] = KernelCost{64, 64, 1.55, 0., 3.6, .0076}.us(batch, m, n, k);
+    direct[1] = KernelCost{32, 64, 2.2, .0071, .69, .0125}.us(batch, m, n, k64);
+    direct[2] = KernelCost{32, 32, 2.8, .0039, .33, .0069}.us(batch, m, n, k64);
+  } else {
+    us128 = KernelCost{128, 128, 1.5, .026, 4.7, .027, 2}.us(batch, m, n, k);
+    us64 = KernelCost{64, 64, 3.6, .026, 1.27, .0102, 4}.us(batch, m, n, k);
+    deep = KernelCost{16, n % 2 == 0 ? 32 : 16, 3.2, 0., .245, .0035}.us(batch, m, n, k);
+    direct[0] = KernelCost{64, 64, 1.33, 0., 3.36, .0148}.us(batch, m, n, k);
+    direct[1] = KernelCost{32, 64, 3.05, .0010, .88, .0090}.us(batch, m, n, k);
+    direct[2] = KernelCost{32, 32, 3.48, .0012, .28, .0053}.us(batch, m, n, k);
+  }
+  // one or two products: the fp32 instructions are the more accurate ones (split.h)
+  if (k <= kFewProducts) us128 = us64 = direct[0] = direct[1] = direct[2] = 1e30;
   const int form = direct[0] < direct[1] ? (direct[0] < direct[2] ? 0 : 2) : (direct[1] < direct[2] ? 1 : 2);
   const double best = fmin(fmin(us128, us64), fmin(deep, direct[form]));
+  if (k <= 32 && (long long)m * k >= 8 && (long long)n * k >= 8 && thin_us(batch, m, n, k) <= best)
+    return launch_gemm_thin(a, b, c, bias, batch, m, n, k, a_kc, b_kc, act, stream);
   if (m16_direct_supported(a, b, c, bias, batch, n, k, a_kc, b_kc)) {
     const bool wide = (long long)((m + 15) / 16) * ((n + 31) / 32) >= 160;
     if (KernelCost{16, wide ? 32 : 16, 2.63, 0., 0., .0041}.us(1, m, n, k) <= best)
@@ -791,7 +806,7 @@ int launch_conv2d_gemm(const float* x, const float* w, const float* bias, float*
     if (ci == 128) return launch_conv3x3_direct<128>(cv, w, bias, y, (int)m, co, act, stream);
   }
   if (fh == 1 && fw == 1 && sh == sw && pt == 0 && pl == 0 && thin_pays(m, co, ci, false))
-    return launch_gemm_thin(x, w, y, bias, (int)m, co, ci, false, act, stream, h, wd, oh, ow, sh);
+    return launch_conv1x1_thin(x, w, y, bias, (int)m, co, ci, act, stream, h, wd, oh, ow, sh);
   const double kp = (double)fh * fw * ((ci + 7) / 8 * 8);
   const double us128 = KernelCost{128, 128, 3.84, .031, 2.58, .0335, 2}.us(1, m, co, kp);
   const double us64 = KernelCost{64, 64, 4.49, .033, .79, .0138, 4}.us(1, m, co, kp);
@@ -801,7 +816,7 @@ int launch_conv2d_gemm(const float* x, const float* w, const float* bias, float*
                             KernelCost{32, 32, 3.12, .0042, .49, .0057}.us(1, m, co, kp)};
   const int form = direct[0] < direct[1] ? (direct[0] < direct[2] ? 0 : 2) : (direct[1] < direct[2] ? 1 : 2);
   const double best = fmin(fmin(us128, us64), fmin(deep, direct[form]));
-  if (deep == best) return launch_conv2d_deep(x, w, bias, y, n, h, wd, ci, fh, fw, co, oh, ow, sh, sw, pt, pl, act, stream);
+  if (deep == best || k <= kFewProducts) return launch_conv2d_deep(x, w, bias, y, n, h, wd, ci, fh, fw, co, oh, ow, sh, sw, pt, pl, act, stream);
   if (direct[form] == best)
     return launch_conv2d_gemm_direct(x, w, bias, y, n, h, wd, ci, fh, fw, co, oh, ow, sh, sw, pt, pl, act, stream, form);
   // k-slices of 32 inside one filter tap, one validity bit per tap: the lean loader

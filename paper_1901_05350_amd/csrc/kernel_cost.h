@@ -8,7 +8,14 @@ namespace tfx {
 //   us = fixed + per_k k + c (per_tile + per_tile_k k)
 // per_k is the memory round trips of a chain that nothing hides, per_tile_k what k costs the CU.  Fitted to the measured
 // times of 226 products and 190 convolutions of either storage type (sizes 16 ... 4096, channels 3 ... 512; mean error
-// 4 - 18 %); over these its choice costs 2 - 4 % against the fastest kernel of each.
+// 4 - 18 %); over these its choice costs 2 - 4 % on average against the fastest kernel of each.
+//
+// Those sizes are bound by their contraction.  For fp32 products of k < 128, which their output bounds, gemm.hip has
+// constants of its own (and the two functions below), fitted to 1000 products of k = 1 ... 127 (2^12 ... 2^26 outputs, batch
+// 1 ... 2000, every layout; rms error 6 - 11 % near the choice): there the choice costs 1.8 % on average against the fastest
+// kernel, more than 10 % for one product in 14 and at most 28 %; with the constants of long contractions it cost 24 % on
+// average and up to 5.2 times.  What makes the difference is that a kernel whose wavefronts split k does not get faster
+// below a step for each of them (16 x 2048 x 2048 x 16: 32 x 32 tiles 202 us, 128 x 128 80, gemm_thin.hip 58).
 //
 // `resident`: the tiled kernels keep 2 (128 x 128) or 4 (64 x 64) tiles on a CU at once, which hide each other's waits.
 // The c of a round then grows slowly from its first tile, and the first tile of the next round costs a whole one: of
@@ -31,14 +38,39 @@ struct KernelCost {
   }
 };
 
-// Whether gemm_thin.hip is the fastest: from how many outputs on its start (B into registers, longer with k) is paid back.
-// Measured on 1x1 convolutions of 100 ... 250 000 rows: floats, 8 -> 16 channels, 200704 rows 25 -> 8 us, 40 -> 152, 248292
-// rows 145 -> 80; 48 -> 24, 1700 rows 3.5 -> 5.3 (not taken); halfs, 11 -> 22, 207936 rows 33 -> 7.
+// gemm_deep.hip on floats, k < 128: 16 x 32 tiles once 160 of them are there, else 16 x 16.
+inline double shallow_deep_us(long long batch, long long m, long long n, int k) {
+  const long long rows = batch * ((m + 15) / 16), wide = rows * ((n + 31) / 32);
+  const bool two = n % 2 == 0 && wide >= 160;
+  const double c = (double)(two ? wide : rows * ((n + 15) / 16)) / 256.;
+  return 3.09 + .0025 * k + (c > 1. ? c : 1.) * (two ? .299 + .0029 * k : .208 + .0017 * k);
+}
+
+// gemm_thin.hip on floats, k <= 32: B into registers once per wavefront (4096 of them at a time), then the speed of
+// writing C, whose rows of no multiple of 4 elements are written in pieces of lines; with two k-steps a wavefront of few
+// tiles shows more of its loads' latency.
+inline double thin_us(long long batch, long long m, long long n, int k) {
+  const int tn = n <= 32 ? 1 : 2, steps = k <= 16 ? 1 : 2;
+  const double chains = (double)(batch * ((n + 32 * tn - 1) / (32 * tn))), tiles = (double)((m + 31) / 32);
+  const double waves = chains >= 4096. ? 1. : 4096. / chains, per_wave = tiles > waves ? tiles / waves : 1.;
+  const double outputs = 1e-6 * (double)(batch * m * n), padded = 1e-6 * chains * tiles * 1024. * tn;
+  return 2.8 + .45 * tn * steps * (chains > 4096. ? chains / 4096. : 1.) +
+         outputs * (.375 + (n % 4 != 0 ? .166 * steps : 0.)) + padded * (steps == 1 ? .53 : .58 + .33 / per_wave);
+}
+
+// Whether gemm_thin.hip is the fastest for a 1x1 convolution with a stride (floats) or a product of one batch with A stored
+// [M,K] (halfs): from how many outputs on its start is paid back.  Measured on 1x1 convolutions of 100 ... 250 000 rows:
+// floats, 8 -> 16 channels, 200704 rows 25 -> 8 us; 40 -> 152, 248292 rows 145 -> 80; 48 -> 24, 1700 rows 3.5 -> 5.3 (not
+// taken); 48 -> 128, 200000 rows 46 us with 128 x 128 tiles, 61 here; halfs, 11 -> 22, 207936 rows 33 -> 7.  With many
+// columns a wavefront has few rows for the B that it loads: halfs, 4096 x 4096 outputs, k = 32 / 64 / 128: 16 / 20 / 28
+// us here, 13.6 / 13.8 / 15.8 with tiles (2048 x 2048 x 32: 6.5 and 7.4); 64 columns from k = 48 on likewise (100000 rows,
+// B stored [N,K]: 10.9 and 8.9; 128 columns 22.5 and 25.9).
 inline bool thin_pays(long long m, long long n, int k, bool half) {
   const long long outputs = m * n;
-  if (!half) return k <= 16 ? outputs >= 400000 : k <= 32 ? outputs >= 1000000 : k <= 48 && outputs >= 20000000;
-  if (k <= 16) return outputs >= (n <= 32 ? 400000 : 1000000);
-  return k <= 32 ? outputs >= 1300000 : k <= 64 ? outputs >= 3000000 : k <= 128 && outputs >= 10000000;
+  if (!half) return k <= 16 ? outputs >= 400000 : k <= 32 && outputs >= 1000000;
+  if (k <= 16) return n <= 2048 && outputs >= (n <= 32 ? 400000 : 1000000);
+  if (k <= 32) return n <= 2048 && outputs >= 1300000;
+  return outputs >= 3000000 && (n <= 32 ? k <= 64 : k <= 48 && n > 64 && n <= 512);
 }
 
 }  // namespace tfx

@@ -9,7 +9,9 @@
 // bf16 instructions adds 16 or 32 products with one rounding, the fp32 ones 2 or 4, so the sum comes out more accurate:
 // against float64, normal operands, relative 2-norm error for K = 128 / 512 / 2048: 1.5e-7 / 3.4e-7 / 6.9e-7 here,
 // 2.0e-7 / 4.1e-7 / 8.1e-7 with v_mfma_f32_16x16x4_f32; operands uniform in [0, 1): 1.2e-7 / 2.4e-7 / 3.8e-7 against
-// 1.6e-7 / 3.1e-7 / 6.0e-7.
+// 1.6e-7 / 3.1e-7 / 6.0e-7.  A sum of one or two products, though, has fewer roundings with the fp32 instructions (normal
+// operands, K = 1 / 2 / 3 / 4 / 8: 3.5e-8 / 3.4e-8 / 3.3e-8 / 3.3e-8 / 3.1e-8 here, 2.5e-8 / 3.1e-8 / 3.6e-8 / 4.0e-8 / 5.3e-8
+// there): contractions of up to kFewProducts take those.
 //
 // Two kinds of values do not survive the split; what they reach is computed again with the fp32 instructions:
 //   - Inf, NaN and magnitudes that round past the largest bf16: a result that they reach is Inf or NaN (so is one that
@@ -25,7 +27,7 @@ namespace tfx {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 
-constexpr int kParts = 3;
+constexpr int kParts = 3, kFewProducts = 2;
 
 // bf16(a) in the low half, bf16(b) in the high half (round to nearest even, one instruction)
 __device__ __forceinline__ unsigned to_bf16_pair(float a, float b) {

@@ -160,13 +160,17 @@ int launch_conv2d_gemm_direct_f16(const uint16_t* x, const uint16_t* w, const ui
                                   int ci, int fh, int fw, int co, int oh, int ow, int sh, int sw, int pt, int pl, int act,
                                   hipStream_t stream, int form);
 
-// Many rows and a short contraction (gemm_thin.hip): A stored [M,K], K <= 64 floats or 128 halfs, one batch, operands of at
-// least 8 elements.  stride > 1: A's rows are the pixels a 1x1 convolution of that stride reads of an [n, h, w, k] image
-// (m = n oh ow, no padding).
-int launch_gemm_thin(const float* a, const float* b, float* c, const float* bias, int m, int n, int k, bool b_kc, int act,
-                     hipStream_t stream, int h = 0, int w = 0, int oh = 0, int ow = 0, int stride = 1);
-int launch_gemm_thin_f16(const uint16_t* a, const uint16_t* b, uint16_t* c, const uint16_t* bias, int m, int n, int k, bool b_kc,
-                         int act, hipStream_t stream, int h = 0, int w = 0, int oh = 0, int ow = 0, int stride = 1);
+// A short contraction (gemm_thin.hip), K <= 32 floats or 64 halfs (one batch, A stored [M,K]), operands of at least 8 elements;
+// the conv form: the pixels that a 1x1 convolution of that stride reads of an [n, h, w, k] image as the rows (m = n oh ow, no
+// padding).
+int launch_gemm_thin(const float* a, const float* b, float* c, const float* bias, int batch, int m, int n, int k, bool a_kc, bool b_kc,
+                     int act, hipStream_t stream);
+int launch_gemm_thin_f16(const uint16_t* a, const uint16_t* b, uint16_t* c, const uint16_t* bias, int m, int n, int k, bool b_kc, int act,
+                         hipStream_t stream);
+int launch_conv1x1_thin(const float* x, const float* w, float* y, const float* bias, int m, int n, int k, int act, hipStream_t stream, int h,
+                        int wd, int oh, int ow, int stride);
+int launch_conv1x1_thin_f16(const uint16_t* x, const uint16_t* w, uint16_t* y, const uint16_t* bias, int m, int n, int k, int act,
+                            hipStream_t stream, int h, int wd, int oh, int ow, int stride);
 
 // conv2d as an implicit GEMM on the matrix cores: M = n*oh*ow, K = fh*fw*ci, N = co (any filter / stride / channel counts).
 bool conv2d_gemm_supported(long long x_elems, int fh, int fw, int ci, int co);

@@ -141,3 +141,80 @@ def test_thin_products(case, half):
     assert np.array_equal(np.isfinite(got), np.isfinite(want))
     fin = np.isfinite(want)
     (assert_close_f16 if half else assert_close)(got[fin], want[fin], "%r" % (case,))
+
+
+# gemm_thin.hip over a batch and with A stored [K,M]: many small matrices, so that it is the kernel taken; tiles of 32 rows and 32
+# or 64 columns, k at and beside a k-step and a vector load: (batch, m, n, k)
+THIN_BATCH = [(3000, 33, 65, 16), (3000, 31, 64, 17), (2500, 32, 33, 32), (9000, 64, 5, 3), (700, 65, 130, 7), (5000, 34, 31, 15),
+              (2000, 40, 63, 31), (400, 129, 96, 1), (1, 2049, 2047, 9), (3, 1025, 1000, 2), (1, 16, 100003, 24)]
+
+
+@pytest.mark.parametrize("ta,tb", [(False, False), (True, False), (False, True), (True, True)])
+def test_thin_products_of_a_batch(ta, tb):
+    import paper_1901_05350_amd as tfx
+    for i, (b, m, n, k) in enumerate(THIN_BATCH):
+        rng = np.random.default_rng(1300 + i)
+        x = rng.uniform(-1, 1, (b, k, m) if ta else (b, m, k)).astype(np.float32)
+        w = rng.uniform(-1, 1, (b, n, k) if tb else (b, k, n)).astype(np.float32)
+        x.reshape(-1)[-1], w.reshape(-1)[-1] = np.inf, -2.0  # the last element of each operand, where a load must not reach past it
+        got, ref = host(tfx.tfx_batch_matmul(dev(x), dev(w), ta, tb)), oracle.batch_matmul(x, w, ta, tb)
+        assert np.array_equal(np.isfinite(got), np.isfinite(ref)), (b, m, n, k)
+        fin = np.isfinite(ref)
+        assert_close(got[fin], ref[fin], "%r ta=%d tb=%d" % ((b, m, n, k), ta, tb))
+
+
+@pytest.mark.parametrize("ta,tb", [(False, False), (True, True)])
+@pytest.mark.parametrize("b,m,n", [(1, 700, 642), (16, 513, 260), (40, 17, 31), (2, 1500, 1030)])
+def test_few_products_are_as_accurate_as_fp32(b, m, n, ta, tb):
+    """One product is rounded once, as the hardware's fp32 multiplication rounds it; k of them at most k times."""
+    import paper_1901_05350_amd as tfx
+    for k in (1, 2, 3, 4):
+        rng = np.random.default_rng(1400 + k)
+        x, w = rng.standard_normal((b, m, k)).astype(np.float32), rng.standard_normal((b, k, n)).astype(np.float32)
+        args = [dev(x.transpose(0, 2, 1)) if ta else dev(x), dev(w.transpose(0, 2, 1)) if tb else dev(w)]
+        got = host(tfx.tfx_batch_matmul(*args, ta, tb))
+        if k == 1:
+            assert np.array_equal(got, x * w)
+        exact, size = x.astype(np.float64) @ w.astype(np.float64), np.abs(x).astype(np.float64) @ np.abs(w).astype(np.float64)
+        assert np.all(np.abs(got - exact) <= k * 2.0 ** -24 * size), k
+
+
+def test_few_products_conv2d():
+    """2 x 2 and 1 x 1 filters of few channels: outputs of one to four products."""
+    import paper_1901_05350_amd as tfx
+    for i, (n, hw, ci, co, f, s) in enumerate([(4, 60, 1, 40, 1, 2), (8, 90, 1, 33, 2, 1), (2, 41, 3, 70, 1, 2), (3, 30, 2, 17, 1, 2)]):
+        d = inputs.conv_general(1450 + i, n, hw, hw, ci, co, f, f)
+        got = host(tfx.tfx_conv2d(dev(d["x"]), dev(d["filter"]), None, s, oracle.PAD_VALID, oracle.ACT_NONE))
+        rows = np.stack([d["x"][:, a:hw - f + 1 + a:s, b:hw - f + 1 + b:s] for a in range(f) for b in range(f)], 3).astype(np.float64)
+        rows = rows.reshape(rows.shape[:3] + (f * f * ci,))
+        flat = d["filter"].reshape(f * f * ci, co).astype(np.float64)
+        assert np.all(np.abs(got - rows @ flat) <= f * f * ci * 2.0 ** -24 * (np.abs(rows) @ np.abs(flat)) + 1e-45)
+
+
+@pytest.mark.parametrize("b,m,n,ta,tb", [(16, 2048, 2048, False, False), (4, 4096, 4096, True, False), (32, 1024, 1024, False, True),
+                                         (1, 4096, 4096, True, True)])
+def test_short_contraction_runs_at_the_speed_of_its_output(b, m, n, ta, tb):
+    """The product's time is that of writing the result: at most twice that of filling it (1.0 ... 1.6 measured)."""
+    import torch
+    import paper_1901_05350_amd as tfx
+    out = torch.empty((b, m, n), device="cuda:0")
+
+    def us(call):
+        call()
+        best = 1e30
+        for _ in range(5):
+            start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            start.record()
+            for _ in range(10):
+                call()
+            end.record()
+            torch.cuda.synchronize()
+            best = min(best, start.elapsed_time(end) * 100)
+        return best
+
+    fill = us(lambda: out.fill_(1.0))
+    for k in (1, 4, 8, 16):
+        x = torch.rand((b, k, m) if ta else (b, m, k), device="cuda:0")
+        w = torch.rand((b, n, k) if tb else (b, k, n), device="cuda:0")
+        got = us(lambda: tfx.tfx_batch_matmul(x, w, ta, tb, out))
+        assert got <= 2 * fill, "k=%d: %.1f us, fill %.1f us" % (k, got, fill)
