@@ -624,16 +624,14 @@ int forward_impl(const tfx_mobilenet_v1_variant* variant, const float* input, in
     {
       const int64_t rows = batch * g.out[1] * g.out[2];
       const size_t a_bytes = align_up(planes_elems(rows, (int)shape[3]) * 2), b_bytes = align_up(planes_elems(cout, (int)shape[3]) * 2);
-      const size_t need = a_bytes + b_bytes + kAlign, have = plan.act_floats * sizeof(float) / kAlign * kAlign;
+      const size_t need = a_bytes + b_bytes, have = plan.act_floats * sizeof(float) / kAlign * kAlign;
       if (rows * cout >= (cout >= 256 ? 800000 : 3000000) && need + align_up((size_t)rows * cout * sizeof(float)) <= have &&
           separable_planes_supported(rows, (int)shape[3], (int)cout, kStrides[b], buf[cur], weights->dw_w[b], weights->dw_b[b],
                                      weights->pw_w[b], weights->pw_b[b], block_out)) {
-        static std::atomic<unsigned> calls{0};  // the token of each call
         char* const region = reinterpret_cast<char*>(buf[cur ^ 1]) + have - need;
         rc = launch_separable_planes(buf[cur], weights->dw_w[b], weights->dw_b[b], weights->pw_w[b], weights->pw_b[b], block_out, region,
-                                     region + a_bytes, reinterpret_cast<unsigned*>(region + a_bytes + b_bytes), ++calls, (int)batch,
-                                     (int)shape[1], (int)shape[2], (int)shape[3], (int)cout, (int)g.out[1], (int)g.out[2], kStrides[b],
-                                     (int)g.pad[0], (int)g.pad[2], TFX_ACT_RELU6, TFX_ACT_RELU6, static_cast<hipStream_t>(stream));
+                                     region + a_bytes, (int)batch, (int)shape[1], (int)shape[2], (int)shape[3], (int)cout, (int)g.out[1],
+                                     (int)g.out[2], kStrides[b], (int)g.pad[0], (int)g.pad[2], TFX_ACT_RELU6, static_cast<hipStream_t>(stream));
         if (rc) return rc;
         if (end_block == b + 1) return TFX_OK;
         for (int i = 0; i < 3; ++i) shape[i] = g.out[i];

@@ -1,4 +1,4 @@
-// A depthwise-separable block of a batch (depthwise 3x3 + bias + clamp, pointwise 1x1 + bias + clamp, fp32) as two launches
+// A depthwise-separable block of a batch (depthwise 3x3 + bias + relu6, pointwise 1x1 + bias + clamp, fp32) as two launches
 // that hand the depthwise output over as bf16 planes: the blocks behind the early ones of the MobileNet forward pass.
 //
 // The pointwise layer is a product on the bf16 matrix cores with three-way split operands (split.h).  There the split costs
@@ -11,10 +11,12 @@
 // Planes are stored by k-slices of 32: plane p, slice s, row r: 32 bf16 at element ((3 s + p) rows + r) 32, so that the
 // rows of a tile are one contiguous piece per plane and slice.
 //
-// Values that the split does not carry (split.h): a result that is Inf or NaN is computed again with the fp32
-// instructions from the block's input.  A depthwise output or filter value of tiny magnitude makes the first kernel store
-// the call's token in `flag`; every tile is then computed again.  (The token differs from call to call, so the word need
-// not be cleared; an old one that happens to match only costs time.)
+// Values that the split does not carry (split.h): results that are Inf or NaN are computed again with the fp32
+// instructions, and so are small ones where one of a wavefront's rows or columns holds a tiny value, which is looked for in
+// the planes when a result is small.  So that it can be seen there, a depthwise output below the smallest bf16 becomes
+// that one (2^-133; it loses no more than other tiny values do).  Depthwise outputs are at most 6; a filter value of 2^20 or
+// more is stored as NaN, which makes its results NaN and has them computed again.  Operands of the second computation are
+// the sums of their planes, which are exact, except for tiny and non-finite ones, computed again from the input.
 #include "split.h"
 
 namespace tfx {
@@ -27,11 +29,9 @@ struct PlanesArgs {
   const float *x, *dw_w, *dw_b, *pw_w, *pw_b;
   float* y;
   unsigned short *a, *b;  // planes of the depthwise output [M, C] and of the filter transposed [N, C]
-  unsigned* flag;
-  unsigned token;
   int H, W, C, OH, OW, N, M, pt, pl;
   int strips, dw_total, dw_blocks;
-  int dw_act, pw_act;
+  int pw_act;
   int tiles_m, tiles_n;
 };
 
@@ -44,14 +44,19 @@ __device__ __forceinline__ float dw_value(const PlanesArgs& g, int S, int row, i
       if (ih >= 0 && ih < g.H && iw >= 0 && iw < g.W)
         acc += g.x[(((size_t)n * g.H + ih) * g.W + iw) * g.C + c] * g.dw_w[(kh * 3 + kw) * g.C + c];
     }
-  return apply_act(acc, g.dw_act);
+  return apply_act(acc, TFX_ACT_RELU6);
+}
+
+// a float of at least +0: positive ones below 2^-133 become 2^-133
+__device__ __forceinline__ float seen_in_planes(float v) {
+  const unsigned bits = __float_as_uint(v);
+  return __uint_as_float(max(bits, min(bits << 16, 1u << 16)));
 }
 
 // Workgroups 0 ... dw_blocks - 1: the depthwise layer as in depthwise.hip (a lane owns four channels of RS output rows of
 // one column).  The others: the pointwise filter, 64 columns x 32 k each.
 template <int S, int RS>
 __global__ __launch_bounds__(256) void depthwise_planes_kernel(PlanesArgs g) {
-  TinyGuard guard;
   int bid = blockIdx.x;
   const int C = g.C;
   if (bid >= g.dw_blocks) {
@@ -66,7 +71,11 @@ __global__ __launch_bounds__(256) void depthwise_planes_kernel(PlanesArgs g) {
     splitx4 part[2][kParts];
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
-      guard.see(v[q]);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float w = v[q][e];  // (a tiny filter value is found in the filter itself)
+        v[q][e] = fabsf(w) < 0x1p20f ? w : NAN;
+      }
       split4(v[q], part[q]);
     }
 #pragma unroll
@@ -108,7 +117,7 @@ __global__ __launch_bounds__(256) void depthwise_planes_kernel(PlanesArgs g) {
 #pragma unroll
       for (int t = 0; t < 9; ++t) wt[t] = *reinterpret_cast<const v4f*>(g.dw_w + (size_t)t * C + 4 * c4);
       const v4f bv = *reinterpret_cast<const v4f*>(g.dw_b + 4 * c4);
-      const ActClamp clamp = make_act(g.dw_act);
+      const ActClamp clamp = make_act(TFX_ACT_RELU6);
       unsigned short* const to = g.a + (size_t)(3 * (c4 / 8)) * g.M * kSlice + 4 * (c4 % 8);
 #pragma unroll
       for (int o = 0; o < RS; ++o) {
@@ -120,8 +129,7 @@ __global__ __launch_bounds__(256) void depthwise_planes_kernel(PlanesArgs g) {
           for (int kw = 0; kw < 3; ++kw) acc += win[o * S + kh][kw] * wt[kh * 3 + kw];
         floatx4 out;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) out[e] = apply_act(acc[e], clamp);
-        guard.see(out);
+        for (int e = 0; e < 4; ++e) out[e] = seen_in_planes(apply_act(acc[e], clamp));
         splitx4 part[kParts];
         split4(out, part);
         const size_t row = ((size_t)n * g.OH + oh0 + o) * g.OW + ow;
@@ -130,7 +138,6 @@ __global__ __launch_bounds__(256) void depthwise_planes_kernel(PlanesArgs g) {
       }
     }
   }
-  if (__builtin_amdgcn_ballot_w64(guard.tiny()) != 0 && threadIdx.x % 64 == 0) *g.flag = g.token;
 }
 
 // y = clamp(A W + bias) from the planes: WAVES_M x WAVES_N wavefronts of TM x TN blocks of 32 x 32, k-slices of 32
@@ -139,7 +146,7 @@ __global__ __launch_bounds__(256) void depthwise_planes_kernel(PlanesArgs g) {
 // LDS: rows of 64 bytes per plane, their four 16-byte pieces turned by row / 8, so that the fragment reads of 32
 // consecutive rows spread over all banks.
 template <int S, int WAVES_M, int WAVES_N, int TM, int TN>
-__global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void pointwise_planes_kernel(PlanesArgs g) {
+__global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 2) void pointwise_planes_kernel(PlanesArgs g) {
   constexpr int NT = 64 * WAVES_M * WAVES_N, BM = 32 * TM * WAVES_M, BN = 32 * TN * WAVES_N;
   constexpr int SA = BM * 4 * kParts / NT, SB = BN * 4 * kParts / NT, SLOTS = SA + SB;
   static_assert(BM * 4 * kParts % NT == 0 && BN * 4 * kParts % NT == 0, "loader shape");
@@ -232,28 +239,90 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void pointwise_planes_kerne
     __syncthreads();
   }
 
-  const bool tiny = *reinterpret_cast<volatile unsigned*>(g.flag) == g.token;
+  const float limit = small_limit(g.C);
+  unsigned most = 0;
+  float least = INFINITY;
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        see_result(most, acc[i][j][v]);
+        least = fminf(least, fabsf(acc[i][j][v] + bv[j]));
+      }
+  // eight depthwise outputs of a row from their planes; `bad`: one of them is tiny or not finite
+  auto depthwise8 = [&](int row, int k, float (&f)[8], bool& bad) __attribute__((always_inline)) {
+    const unsigned short* const p = g.a + ((size_t)(3 * (k / kSlice)) * M + row) * kSlice + k % kSlice;
+    typedef unsigned short u16x8 __attribute__((ext_vector_type(8)));
+    const u16x8 hi = *reinterpret_cast<const u16x8*>(p), mid = *reinterpret_cast<const u16x8*>(p + (size_t)M * kSlice),
+                lo = *reinterpret_cast<const u16x8*>(p + (size_t)2 * M * kSlice);
+    bad = false;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const float top = __uint_as_float((unsigned)hi[e] << 16);
+      f[e] = (__uint_as_float((unsigned)lo[e] << 16) + __uint_as_float((unsigned)mid[e] << 16)) + top;
+      bad = bad || is_tiny(top) || !__builtin_isfinite(top);
+    }
+  };
+  bool tiny = false;
+  if (__builtin_amdgcn_ballot_w64(least < limit) != 0) {  // look through this wavefront's rows and columns
+    bool found = false;
 #pragma unroll 1
-  for (int block = 0; block < TM * TN; ++block) {
-    unsigned most = 0;
+    for (int at = 8 * lane; at < 32 * TM * g.C; at += 8 * 64) {
+      const int row = min(m0 + wm0 + at / g.C, M - 1), k = at % g.C;
+      const u32x4 hi = *reinterpret_cast<const u32x4*>(g.a + ((size_t)(3 * (k / kSlice)) * M + row) * kSlice + k % kSlice);
 #pragma unroll
-    for (int x = 0; x < TM * TN; ++x)
-      if (x == block)
+      for (int e = 0; e < 4; ++e) found = found || is_tiny(__uint_as_float(hi[e] << 16)) || is_tiny(__uint_as_float(hi[e] & 0xffff0000u));
+    }
+#pragma unroll 1
+    for (int at = 4 * lane; at < 32 * TN * g.C; at += 4 * 64)
+      found = found || any_tiny(*reinterpret_cast<const floatx4*>(g.pw_w + (size_t)(at / (32 * TN)) * N + n0 + wn0 + at % (32 * TN)));
+    tiny = __builtin_amdgcn_ballot_w64(found) != 0;
+  }
+  if (tiny || __builtin_amdgcn_ballot_w64(overflowed(most)) != 0) {
+#pragma unroll 1
+    for (int block = 0; block < TM * TN; ++block) {
+      auto wanted = [&](int x, int v) __attribute__((always_inline)) {
+        const float r = acc[x / TN][x % TN][v];
+        return !__builtin_isfinite(r) || (tiny && fabsf(r + bv[x % TN]) < limit);
+      };
+      bool any = false;
 #pragma unroll
-        for (int v = 0; v < 16; ++v) see_result(most, acc[x / TN][x % TN][v]);
-    if (!tiny && __builtin_amdgcn_ballot_w64(overflowed(most)) == 0) continue;
-    const int row = min(m0 + wm0 + 32 * (block / TN) + li, M - 1), col = n0 + wn0 + 32 * (block % TN) + li;
-    floatx16 exact;
+      for (int x = 0; x < TM * TN; ++x)
+        if (x == block)
 #pragma unroll
-    for (int v = 0; v < 16; ++v) exact[v] = 0.f;
-    for (int k = h; k < g.C; k += 2)
-      exact = __builtin_amdgcn_mfma_f32_32x32x2f32(dw_value(g, S, row, k), g.pw_w[(size_t)k * N + col], exact, 0, 0, 0);
+          for (int v = 0; v < 16; ++v) any = any || wanted(x, v);
+      if (__builtin_amdgcn_ballot_w64(any) == 0) continue;
+      const int row = min(m0 + wm0 + 32 * (block / TN) + li, M - 1), col = n0 + wn0 + 32 * (block % TN) + li;
+      floatx16 exact;
 #pragma unroll
-    for (int x = 0; x < TM * TN; ++x)
-      if (x == block)
+      for (int v = 0; v < 16; ++v) exact[v] = 0.f;
+#pragma unroll 1
+      for (int k = 8 * h; k < g.C; k += 16) {
+        float fa[8], fb[8];
+        bool bad;
+        depthwise8(row, k, fa, bad);
 #pragma unroll
-        for (int v = 0; v < 16; ++v)
-          if (tiny || !__builtin_isfinite(acc[x / TN][x % TN][v])) acc[x / TN][x % TN][v] = exact[v];
+        for (int e = 0; e < 8; ++e) fb[e] = g.pw_w[(size_t)(k + e) * N + col];
+        if (bad) {
+#pragma unroll 1
+          for (int e = 0; e < 8; ++e) {
+            const float v = dw_value(g, S, row, k + e);
+#pragma unroll
+            for (int w = 0; w < 8; ++w) fa[w] = w == e ? v : fa[w];
+          }
+        }
+#pragma unroll
+        for (int e = 0; e < 8; ++e) exact = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[e], fb[e], exact, 0, 0, 0);
+      }
+#pragma unroll
+      for (int x = 0; x < TM * TN; ++x)
+        if (x == block)
+#pragma unroll
+          for (int v = 0; v < 16; ++v)
+            if (wanted(x, v)) acc[x / TN][x % TN][v] = exact[v];
+    }
   }
   const ActClamp clamp = make_act(g.pw_act);
 #pragma unroll
@@ -316,14 +385,13 @@ bool separable_planes_supported(long long rows, int c, int n, int stride, const 
 }
 
 int launch_separable_planes(const float* x, const float* dw_w, const float* dw_b, const float* pw_w, const float* pw_b, float* y,
-                            void* a_planes, void* b_planes, unsigned* flag, unsigned token, int batch, int h, int w, int c, int n,
-                            int oh, int ow, int stride, int pt, int pl, int dw_act, int pw_act, hipStream_t stream) {
+                            void* a_planes, void* b_planes, int batch, int h, int w, int c, int n, int oh, int ow, int stride, int pt,
+                            int pl, int pw_act, hipStream_t stream) {
   PlanesArgs g{};
   g.x = x, g.dw_w = dw_w, g.dw_b = dw_b, g.pw_w = pw_w, g.pw_b = pw_b, g.y = y;
   g.a = static_cast<unsigned short*>(a_planes), g.b = static_cast<unsigned short*>(b_planes);
-  g.flag = flag, g.token = token;
   g.H = h, g.W = w, g.C = c, g.OH = oh, g.OW = ow, g.N = n, g.M = batch * oh * ow, g.pt = pt, g.pl = pl;
-  g.dw_act = dw_act, g.pw_act = pw_act;
+  g.pw_act = pw_act;
   return stride == 1 ? launch_block<1>(g, batch, stream) : launch_block<2>(g, batch, stream);
 }
 

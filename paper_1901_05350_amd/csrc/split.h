@@ -66,6 +66,13 @@ struct TinyGuard {
   __device__ __forceinline__ bool tiny() const { return least < (27u << 24) - 1u; }  // biased exponent below 127 - 100
 };
 
+// a sum of K products (plus bias) of at least this magnitude does not depend on what tiny operands lose
+__device__ __forceinline__ float small_limit(int products) { return (float)products * 0x1p-89f; }
+
+// nonzero and below 2^-110
+__device__ __forceinline__ bool is_tiny(float v) { return (__float_as_uint(v) << 1) - 1u < (17u << 24) - 1u; }
+__device__ __forceinline__ bool any_tiny(const floatx4& v) { return is_tiny(v[0]) || is_tiny(v[1]) || is_tiny(v[2]) || is_tiny(v[3]); }
+
 // largest |bits| of accumulators so far; Inf and NaN are the ones with a full exponent
 __device__ __forceinline__ void see_result(unsigned& most, float v) { most = max(most, __float_as_uint(v) << 1); }
 __device__ __forceinline__ bool overflowed(unsigned most) { return most >= 0xff000000u; }

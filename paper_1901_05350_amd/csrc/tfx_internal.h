@@ -324,14 +324,13 @@ int launch_separable_stream(const float* x, const float* dw_w, const float* dw_b
 
 // A depthwise-separable block of a batch as a depthwise kernel that writes bf16 planes and a product of planes
 // (block_planes.hip): any c % 32 == 0, n % 64 == 0.  a_planes / b_planes: planes_elems(rows, c) / planes_elems(n, c)
-// 16-bit words, 16-byte aligned, not overlapping x or y; rows = output pixels.  flag: a word of the workspace, token: a
-// value no other call in flight uses.
+// 16-bit words, 16-byte aligned, not overlapping x or y; rows = output pixels.  The depthwise layer's activation is relu6.
 size_t planes_elems(long long rows, int c);
 bool separable_planes_supported(long long rows, int c, int n, int stride, const void* x, const void* dw_w, const void* dw_b,
                                 const void* pw_w, const void* pw_b, const void* y);
 int launch_separable_planes(const float* x, const float* dw_w, const float* dw_b, const float* pw_w, const float* pw_b, float* y,
-                            void* a_planes, void* b_planes, unsigned* flag, unsigned token, int batch, int h, int w, int c, int n,
-                            int oh, int ow, int stride, int pt, int pl, int dw_act, int pw_act, hipStream_t stream);
+                            void* a_planes, void* b_planes, int batch, int h, int w, int c, int n, int oh, int ow, int stride, int pt,
+                            int pl, int pw_act, hipStream_t stream);
 
 // The same on binary16 storage (block_stream_f16.hip).
 bool separable_stream_f16_supported(int batch, int h, int w, int c, int n, int stride, int oh, int ow, const void* x,

@@ -5,7 +5,7 @@ import pytest
 import oracle
 from oracle import ACT_RELU6, PAD_SAME
 from paper_1901_05350_amd import inputs
-from util import assert_close, dev, host
+from util import assert_close, dev, host, time_ratio
 
 pytestmark = pytest.mark.gpu
 
@@ -503,3 +503,71 @@ def test_planes_blocks_values_outside_the_split(what):
         assert np.array_equal(np.isnan(got[i:i + 1]), np.isnan(ref))
         fin = np.isfinite(ref)
         assert_close(got[i:i + 1][fin], ref[fin], what)
+
+
+def test_planes_blocks_results_made_of_tiny_values():
+    """Columns of a planes block that nothing but tiny values reach: a filter column of tiny weights, and columns that pass
+    depthwise outputs around and below the smallest bf16 on."""
+    import paper_1901_05350_amd as tfx
+    d = inputs.mobilenet_v1(seed=43, batch=8)
+    w, image = d["weights"], d["image"]
+    b = 7
+    w["pw_w"][b][0, 0, :, 33] *= 2.0 ** -118
+    for c, (out, scale) in enumerate(((40, -116), (41, -131), (42, -138))):
+        w["dw_w"][b][:, :, c], w["dw_b"][b][c] = np.abs(w["dw_w"][b][:, :, c]) * 2.0 ** scale, 0
+        w["pw_w"][b][0, 0, :, out] = 0
+        w["pw_w"][b][0, 0, c, out] = 3
+    w["pw_b"][b][[33, 40, 41, 42]] = 0
+    got = host(tfx.MobileNetV1(w, batch=8).features(dev(image), b + 1)).astype(np.float64)
+    for i in (0, 5):
+        ref = host(tfx.MobileNetV1(w, batch=1).features(dev(image[i:i + 1]), b + 1)).astype(np.float64)
+        for col, scale in ((33, -118), (40, -116), (41, -131), (42, -138)):
+            assert (ref[..., col] != 0).any()
+            # roundings of up to 512 products to 24 bits, or of a sum of nine to the smallest float (then times 3)
+            assert np.all(np.abs(got[i, ..., col] - ref[0, ..., col]) <= np.maximum(1e-5 * 2.0 ** scale * 16, 32 * 2.0 ** -149)), col
+        assert_close(got[i:i + 1], ref, "image %d" % i)
+
+
+def test_replays_after_a_tiny_image_have_the_clean_bits():
+    """A pass whose feature maps are tiny leaves nothing behind: every later replay of the captured pass gives the same bits
+    in the same time."""
+    import torch
+    import paper_1901_05350_amd as tfx
+    d = inputs.mobilenet_v1(seed=45, batch=8)
+    w = d["weights"]
+    w["conv0_b"][:] = 0
+    for k in ("dw_b", "pw_b"):
+        for t in w[k][:8]:
+            t[:] = 0
+    model = tfx.MobileNetV1(w, batch=8)
+    image = dev(d["image"])
+    clean, small = image.clone(), image * 1e-36
+    want = [host(t).copy() for t in model.forward(clean)]
+    small_want = [host(t).copy() for t in model.forward(small)]
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        model.forward(image)
+    for x, ref in ((clean, want), (small, small_want), (clean, want), (clean, want), (small, small_want), (clean, want)):
+        image.copy_(x)
+        graph.replay()
+        assert np.array_equal(host(model.probs), ref[0]) and np.array_equal(host(model.logits), ref[1])
+
+
+@pytest.mark.parametrize("batch", [8, 64])
+@pytest.mark.parametrize("value", [1e-32, 1e-38])
+def test_a_few_tiny_filter_values_cost_nothing(batch, value):
+    import torch
+    import paper_1901_05350_amd as tfx
+    d = inputs.mobilenet_v1(seed=46, batch=1)
+    rng = np.random.default_rng(46)
+    models = []
+    for fill in (False, True):
+        w = d["weights"]
+        if fill:
+            for t in w["pw_w"] + w["dw_w"]:
+                t[rng.random(t.shape) < 1e-3] = value
+            for t in w["dw_w"][4:]:
+                t[:, :, ::100] = value  # dead channels
+        models.append(tfx.MobileNetV1(w, batch=batch))
+    image = dev(np.concatenate([d["image"]] * batch))
+    assert time_ratio(lambda m: m.forward(image), *models) < 1.3

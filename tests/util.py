@@ -58,3 +58,20 @@ def host(t):
     import torch
     torch.cuda.synchronize()
     return t.cpu().numpy()
+
+
+def time_ratio(run, clean, tiny):
+    """Time of run(tiny) over that of run(clean), in turn."""
+    import torch
+    best = [1e30, 1e30]
+    for _ in range(8):
+        for i, x in enumerate((clean, tiny)):
+            run(x)
+            start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            start.record()
+            for _ in range(10):
+                run(x)
+            end.record()
+            torch.cuda.synchronize()
+            best[i] = min(best[i], start.elapsed_time(end))
+    return best[1] / best[0]
