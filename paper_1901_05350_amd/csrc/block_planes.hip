@@ -76,7 +76,8 @@ __global__ __launch_bounds__(256) void depthwise_planes_kernel(PlanesArgs g) {
         const float w = v[q][e];  // (a tiny filter value is found in the filter itself)
         v[q][e] = fabsf(w) < 0x1p20f ? w : NAN;
       }
-      split4(v[q], part[q]);
+      unsigned low = 0;  // (what is lost is looked for in the planes and the filter)
+      split4(v[q], part[q], low);
     }
 #pragma unroll
     for (int q = 0; q < kParts; ++q) {
@@ -131,7 +132,8 @@ __global__ __launch_bounds__(256) void depthwise_planes_kernel(PlanesArgs g) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) out[e] = seen_in_planes(apply_act(acc[e], clamp));
         splitx4 part[kParts];
-        split4(out, part);
+        unsigned low = 0;
+        split4(out, part, low);
         const size_t row = ((size_t)n * g.OH + oh0 + o) * g.OW + ow;
 #pragma unroll
         for (int q = 0; q < kParts; ++q) *reinterpret_cast<splitx4*>(to + ((size_t)q * g.M + row) * kSlice) = part[q];

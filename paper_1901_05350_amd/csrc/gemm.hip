@@ -277,7 +277,7 @@ struct PlaneTile {
 
 // Registers -> LDS: splits a thread's slots and writes four k of a row at a time (8 bytes per plane).
 template <int ROWS, int BK, bool KC, int NT, int NSLOT>
-__device__ __forceinline__ void store_planes(char* __restrict__ lds, int tid, const float4 (&reg)[NSLOT], TinyGuard& guard) {
+__device__ __forceinline__ void store_planes(char* __restrict__ lds, int tid, const float4 (&reg)[NSLOT], SplitGuard& guard) {
   using T = PlaneTile<ROWS, KC>;
   static_assert(BK == 32, "rows of 32 k");
 #pragma unroll
@@ -292,9 +292,8 @@ __device__ __forceinline__ void store_planes(char* __restrict__ lds, int tid, co
       v = floatx4{f4_get(reg[0], it), f4_get(reg[1], it), f4_get(reg[2], it), f4_get(reg[3], it)};
       k = slot_k<ROWS, BK, KC, NT>(tid, 0);
     }
-    guard.see(v);
     splitx4 part[kParts];
-    split4(v, part);
+    guard.split(v, part);
     char* const p = lds + T::at(row, k / 8) + (k % 8) * 2;
 #pragma unroll
     for (int q = 0; q < kParts; ++q) *reinterpret_cast<splitx4*>(p + q * T::kPlane) = part[q];
@@ -406,7 +405,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_mfma_kernel(
     if constexpr (FORM != kConvRagged && decltype(full)::value) load_tile_full<SB>(pb, kt * step_b, rb);
     else load_tile_any<BN, BK, B_KC, FORM == kConvRagged, NT, SB>(B, ldb, N, kb, n0, kt * BK, tid, total_b, cv.fk, rb);
   };
-  TinyGuard guard;
+  SplitGuard guard;
   auto store = [&](int kt, auto full) __attribute__((always_inline)) {
     if constexpr (CONV && !LEAN) settle_tile_conv<BK, FORM == kConvRagged, SA>(cv, kt * BK, tid, crow, ra);
     else if constexpr (!CONV && !decltype(full)::value)
@@ -465,46 +464,6 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_mfma_kernel(
   int kt = 0;
   for (; kt + 1 < nk_full; ++kt) k_slice(kt, std::true_type{});
   for (; kt < nk; ++kt) k_slice(kt, std::false_type{});
-  // Values that the split does not carry: blocks with an Inf or NaN (those results), or all blocks after an operand of
-  // tiny magnitude, once more with the fp32 instructions, operands element by element.
-  const bool tiny = __syncthreads_or(guard.tiny());
-#pragma unroll 1
-  for (int block = 0; block < TM * TN; ++block) {
-    unsigned most = 0;
-#pragma unroll
-    for (int x = 0; x < TM * TN; ++x)
-      if (x == block)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) see_result(most, acc[x / TN][x % TN][v]);
-    if (!tiny && __builtin_amdgcn_ballot_w64(overflowed(most)) == 0) continue;
-    const int row = min(m0 + wm0 + 32 * (block / TN) + li, M - 1), col = min(n0 + wn0 + 32 * (block % TN) + li, N - 1);
-    floatx16 exact;
-#pragma unroll
-    for (int v = 0; v < 16; ++v) exact[v] = 0.f;
-    const int depth = CONV ? cv.Ci : K, taps = CONV ? cv.fk.taps : 1;
-    for (int tap = 0; tap < taps; ++tap) {
-      const float* ap = A + (A_KC ? (size_t)row * lda : (size_t)row);
-      bool inside = true;
-      if constexpr (CONV) {
-        const int t = row / cv.OW, n = t / cv.OH, kh = tap / cv.fw;
-        const int ih = (t - n * cv.OH) * cv.sh - cv.pt + kh, iw = (row - t * cv.OW) * cv.sw - cv.pl + tap - kh * cv.fw;
-        inside = ih >= 0 && ih < cv.H && iw >= 0 && iw < cv.W;
-        ap = cv.x + (inside ? (((size_t)n * cv.H + ih) * cv.W + iw) * cv.Ci : 0);
-      }
-      for (int k0 = 0; k0 < depth; k0 += 2) {
-        const int k = k0 + h;
-        const float fa = inside && k < depth ? ap[A_KC ? (size_t)k : (size_t)k * lda] : 0.f;
-        const float fb = k < depth ? B[B_KC ? (size_t)col * ldb + k : ((size_t)tap * depth + k) * ldb + col] : 0.f;
-        exact = __builtin_amdgcn_mfma_f32_32x32x2f32(fa, fb, exact, 0, 0, 0);
-      }
-    }
-#pragma unroll
-    for (int x = 0; x < TM * TN; ++x)
-      if (x == block)
-#pragma unroll
-        for (int v = 0; v < 16; ++v)
-          if (tiny || !__builtin_isfinite(acc[x / TN][x % TN][v])) acc[x / TN][x % TN][v] = exact[v];
-  }
   const ActClamp clamp = make_act(act);
   // Epilogue: bias[col] then activation, one dword per lane per register (two 128-byte rows per store).
 #pragma unroll
@@ -517,6 +476,84 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_mfma_kernel(
       for (int v = 0; v < 16; ++v) {
         const int row = m0 + wm0 + 32 * i + 8 * (v / 4) + 4 * h + (v % 4);
         if (row < M) C[(size_t)row * N + col] = apply_act(acc[i][j][v] + bv[j], clamp);
+      }
+    }
+  }
+  // Values that the split does not carry (split.h): results that are Inf or NaN, and small ones if it lost bits of an operand
+  // of this workgroup, once more with the fp32 instructions,
+  // over what was stored.
+  unsigned most = 0;
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) see_result(most, acc[i][j][v]);
+  bool again = overflowed(most);
+  float limit = 0.f;
+  if (__syncthreads_or(guard.lost())) {
+    limit = __syncthreads_or(guard.large()) ? INFINITY : small_limit(CONV ? cv.Ci * cv.fk.taps : K);
+    float least = INFINITY;
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) least = fminf(least, fabsf(acc[i][j][v] + bv[j]));
+    again = again || least < limit;
+  }
+  auto wanted = [&](float r, float b) __attribute__((always_inline)) { return !__builtin_isfinite(r) || fabsf(r + b) < limit; };
+  if (__builtin_amdgcn_ballot_w64(again) != 0) {
+    const int depth = CONV ? cv.Ci : K, taps = CONV ? cv.fk.taps : 1;
+    // 8 consecutive k of a row or column, next to each other or `ld` elements apart, zeros from `valid` on
+    auto fetch = [&](const float* p, auto contiguous, int ld, int valid, float (&f)[8]) __attribute__((always_inline)) {
+      constexpr bool KC = decltype(contiguous)::value;
+      if (KC && valid >= 8) {
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          const float4 v = load_quad(p + 4 * q);
+          f[4 * q] = v.x, f[4 * q + 1] = v.y, f[4 * q + 2] = v.z, f[4 * q + 3] = v.w;
+        }
+      } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) f[e] = e < valid ? p[KC ? (size_t)e : (size_t)e * ld] : 0.f;
+      }
+    };
+#pragma unroll
+    for (int block = 0; block < TM * TN; ++block) {
+      const floatx16& r = acc[block / TN][block % TN];
+      const float b = bv[block % TN];
+      bool any = false;
+#pragma unroll
+      for (int v = 0; v < 16; ++v) any = any || wanted(r[v], b);
+      if (__builtin_amdgcn_ballot_w64(any) == 0) continue;
+      const int row = min(m0 + wm0 + 32 * (block / TN) + li, M - 1), col = min(n0 + wn0 + 32 * (block % TN) + li, N - 1);
+      floatx16 exact;
+#pragma unroll
+      for (int v = 0; v < 16; ++v) exact[v] = 0.f;
+      for (int tap = 0; tap < taps; ++tap) {
+        const float* ap = A + (A_KC ? (size_t)row * lda : (size_t)row);
+        bool inside = true;
+        if constexpr (CONV) {
+          const int t = row / cv.OW, n = t / cv.OH, kh = tap / cv.fw;
+          const int ih = (t - n * cv.OH) * cv.sh - cv.pt + kh, iw = (row - t * cv.OW) * cv.sw - cv.pl + tap - kh * cv.fw;
+          inside = ih >= 0 && ih < cv.H && iw >= 0 && iw < cv.W;
+          ap = cv.x + (inside ? (((size_t)n * cv.H + ih) * cv.W + iw) * cv.Ci : 0);
+        }
+        const float* bp = B + (B_KC ? (size_t)col * ldb : (size_t)tap * depth * ldb + col);
+#pragma unroll 1
+        for (int k = 8 * h; k - 8 * h < depth; k += 16) {
+          float fa[8], fb[8];
+          fetch(ap + (A_KC ? (size_t)k : (size_t)k * lda), std::bool_constant<A_KC>{}, lda, inside ? depth - k : 0, fa);
+          fetch(bp + (B_KC ? (size_t)k : (size_t)k * ldb), std::bool_constant<B_KC>{}, ldb, depth - k, fb);
+#pragma unroll
+          for (int e = 0; e < 8; ++e) exact = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[e], fb[e], exact, 0, 0, 0);
+        }
+      }
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const int out = m0 + wm0 + 32 * (block / TN) + 8 * (v / 4) + 4 * h + (v % 4);
+        if (wanted(r[v], b) && out < M && n0 + wn0 + 32 * (block % TN) + li < N) C[(size_t)out * N + col] = apply_act(exact[v] + b, clamp);
       }
     }
   }

@@ -46,7 +46,7 @@ typedef _Float16 h8 __attribute__((ext_vector_type(8)));
 typedef unsigned u32_any __attribute__((aligned(2)));
 
 template <typename T, Source A_SRC, bool B_KC, int TM, int TN, int WAVES>
-__global__ __launch_bounds__(64 * WAVES, WAVES / 4) void gemm_direct_kernel(DirectArgs<T> g) {
+__global__ __launch_bounds__(64 * WAVES, TM * TN == 1 && A_SRC == kConv ? 4 : WAVES / 4) void gemm_direct_kernel(DirectArgs<T> g) {
   constexpr bool CONV = A_SRC == kConv, HALF = sizeof(T) == 2;
   typedef Octet<T> Oct;
   constexpr int PER = Oct::kPer;
@@ -244,7 +244,7 @@ __global__ __launch_bounds__(64 * WAVES, WAVES / 4) void gemm_direct_kernel(Dire
   };
 
   floatx16 acc[TM][TN];
-  TinyGuard guard;
+  SplitGuard guard;
   auto clear = [&]() __attribute__((always_inline)) {
 #pragma unroll
     for (int i = 0; i < TM; ++i)
@@ -258,8 +258,7 @@ __global__ __launch_bounds__(64 * WAVES, WAVES / 4) void gemm_direct_kernel(Dire
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
       const floatx4 v = __builtin_bit_cast(floatx4, o.chunk[q % Oct::kChunks]);
-      guard.see(v);
-      split4(v, half[q]);
+      guard.split(v, half[q]);
     }
 #pragma unroll
     for (int p = 0; p < kParts; ++p)
@@ -336,35 +335,45 @@ __global__ __launch_bounds__(64 * WAVES, WAVES / 4) void gemm_direct_kernel(Dire
   floatx4 sum[OWN];
   add_up(sum);
   if constexpr (!HALF) {
+    // values that the split does not carry (split.h): results that are Inf or NaN, and small ones if it lost bits of an operand
+    // of this workgroup, once more with the fp32 instructions
     unsigned most = 0;
 #pragma unroll
     for (int o = 0; o < OWN; ++o)
 #pragma unroll
       for (int v = 0; v < 4; ++v) see_result(most, sum[o][v]);
-    const bool tiny = __syncthreads_or(guard.tiny());
-    if (__syncthreads_or(overflowed(most)) || tiny) {
-      // values that the split does not carry: once more with the fp32 instructions, for the results that are Inf or NaN or,
-      // after an operand of tiny magnitude, for all
-      clear();
-      for (int step = wave; step < g.steps; step += WAVES) {
-        load(step, a[0], b[0]);
-        settle(step, a[0], b[0]);
-#pragma unroll
-        for (int e = 0; e < 8; ++e)
-#pragma unroll
-          for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int j = 0; j < TN; ++j)
-              acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a[0][i].chunk[e / PER][e % PER]),
-                                                               __uint_as_float(b[0][j].chunk[e / PER][e % PER]), acc[i][j], 0, 0, 0);
-      }
-      floatx4 exact[OWN];
-      add_up(exact);
+    if (__syncthreads_or(guard.lost() || overflowed(most))) {
+      const float limit = !__syncthreads_or(guard.lost()) ? 0.f : __syncthreads_or(guard.large()) ? INFINITY : small_limit(CONV ? g.K * g.taps : g.K);
+      auto wanted = [&](int o, int v) __attribute__((always_inline)) {
+        return !__builtin_isfinite(sum[o][v]) || fabsf(sum[o][v] + bias[o]) < limit;
+      };
+      bool any = false;
 #pragma unroll
       for (int o = 0; o < OWN; ++o)
 #pragma unroll
-        for (int v = 0; v < 4; ++v)
-          if (tiny || !__builtin_isfinite(sum[o][v])) sum[o][v] = exact[o][v];
+        for (int v = 0; v < 4; ++v) any = any || wanted(o, v);
+      if (__syncthreads_or(any)) {
+        clear();
+        for (int step = wave; step < g.steps; step += WAVES) {
+          load(step, a[0], b[0]);
+          settle(step, a[0], b[0]);
+#pragma unroll
+          for (int e = 0; e < 8; ++e)
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+              for (int j = 0; j < TN; ++j)
+                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a[0][i].chunk[e / PER][e % PER]),
+                                                                 __uint_as_float(b[0][j].chunk[e / PER][e % PER]), acc[i][j], 0, 0, 0);
+        }
+        floatx4 exact[OWN];
+        add_up(exact);
+#pragma unroll
+        for (int o = 0; o < OWN; ++o)
+#pragma unroll
+          for (int v = 0; v < 4; ++v)
+            if (wanted(o, v)) sum[o][v] = exact[o][v];
+      }
     }
   }
   const ActClamp clamp = make_act(g.act);

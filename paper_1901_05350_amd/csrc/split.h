@@ -16,7 +16,11 @@
 // Two kinds of values do not survive the split; what they reach is computed again with the fp32 instructions:
 //   - Inf, NaN and magnitudes that round past the largest bf16: a result that they reach is Inf or NaN (so is one that
 //     really overflows), which is looked for once, after the loop; the finite results beside it stay;
-//   - nonzero magnitudes below 2^-100, whose parts would be subnormal: TinyGuard watches the operands for them (the whole tile).
+//   - magnitudes below 2^-110 ("tiny"), whose last bits can lie below the smallest bf16, 2^-133 (conversions, subtractions
+//     and matrix instructions of this chip keep subnormals): each loses up to 2^-134.  SplitGuard sees whether any bit was
+//     lost.  With operands below 2^20 a sum of K products then misses less than K 2^-113, which no sum of 2^24 times that
+//     size (small_limit) notices: only smaller results are computed again, all of them after a larger operand.
+//     (8 x 1024^3, 1 value in 1000 at 1e-38: 959 us when every tile with a tiny value was computed again, now as without.)
 #ifndef TFX_SPLIT_H_
 #define TFX_SPLIT_H_
 
@@ -36,18 +40,23 @@ __device__ __forceinline__ unsigned to_bf16_pair(float a, float b) {
   return __builtin_bit_cast(unsigned, __builtin_convertvector(floatx2{a, b}, pair));
 }
 
-// hi, mid and lo of four floats.  (The differences as bf16 dot products with (-1, 0) and (0, -1), one instruction instead
+// hi, mid and lo of four floats; `low` collects the bits of the last remainders, whose lower halves are zeros unless the
+// split loses something.  (The differences as bf16 dot products with (-1, 0) and (0, -1), one instruction instead
 // of two, were slower: that instruction does not overlap with matrix instructions.)
 typedef unsigned splitx4 __attribute__((ext_vector_type(2)));  // four bf16
-__device__ __forceinline__ void split4(floatx4 v, splitx4 (&part)[kParts]) {
+__device__ __forceinline__ void split4(floatx4 v, splitx4 (&part)[kParts], unsigned& low) {
 #pragma unroll
   for (int p = 0; p < kParts; ++p)
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
       const unsigned pair = to_bf16_pair(v[2 * i], v[2 * i + 1]);
       part[p][i] = pair;
-      v[2 * i] -= __uint_as_float(pair << 16);
-      v[2 * i + 1] -= __uint_as_float(pair & 0xffff0000u);
+      if (p == kParts - 1) {
+        low |= __float_as_uint(v[2 * i]) | __float_as_uint(v[2 * i + 1]);
+      } else {
+        v[2 * i] -= __uint_as_float(pair << 16);
+        v[2 * i + 1] -= __uint_as_float(pair & 0xffff0000u);
+      }
     }
 }
 
@@ -56,16 +65,18 @@ __device__ __forceinline__ constexpr int split_pass_a(int s) { return s == 0 ? 1
 __device__ __forceinline__ constexpr int split_pass_b(int s) { return s == 0 ? 1 : s == 1 ? 2 : s == 2 ? 0 : s == 3 ? 0 : s == 4 ? 1 : 0; }
 constexpr int kSplitPasses = 6;  // (mid, mid), (hi, lo), (lo, hi), (mid, hi), (hi, mid), (hi, hi)
 
-struct TinyGuard {
-  unsigned least = ~0u;  // of 2 |bits| - 1: zeros wrap to the largest value
-  __device__ __forceinline__ void see(float a) { least = min(least, (__float_as_uint(a) << 1) - 1u); }
-  __device__ __forceinline__ void see(const floatx4& v) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) see(v[i]);
+// What a thread saw of the operands that it split: one vector instruction per value.
+struct SplitGuard {
+  float most = 0.f;  // largest magnitude; NaN is not seen
+  unsigned low = 0;
+  __device__ __forceinline__ void split(const floatx4& v, splitx4 (&part)[kParts]) {
+    asm("v_max3_f32 %0, %0, |%1|, |%2|" : "+v"(most) : "v"(v[0]), "v"(v[1]));
+    asm("v_max3_f32 %0, %0, |%1|, |%2|" : "+v"(most) : "v"(v[2]), "v"(v[3]));
+    split4(v, part, low);
   }
-  __device__ __forceinline__ bool tiny() const { return least < (27u << 24) - 1u; }  // biased exponent below 127 - 100
+  __device__ __forceinline__ bool large() const { return !(most < 0x1p20f); }
+  __device__ __forceinline__ bool lost() const { return (low & 0xffffu) != 0; }
 };
-
 // a sum of K products (plus bias) of at least this magnitude does not depend on what tiny operands lose
 __device__ __forceinline__ float small_limit(int products) { return (float)products * 0x1p-89f; }
 

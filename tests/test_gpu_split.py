@@ -6,7 +6,7 @@ import pytest
 
 import oracle
 from paper_1901_05350_amd import inputs
-from util import assert_close, assert_close_f16, dev, dev16, host
+from util import assert_close, assert_close_f16, dev, dev16, host, time_ratio
 
 pytestmark = pytest.mark.gpu
 
@@ -47,6 +47,49 @@ def test_small_magnitudes(m, n, k, exponent):
     got, ref = host(tfx.tfx_matmul(dev(a), dev(b))).astype(np.float64), a.astype(np.float64) @ b.astype(np.float64)
     bound = 2e-6 * (np.abs(a).astype(np.float64) @ np.abs(b).astype(np.float64))
     assert np.all(np.abs(got - ref) <= np.maximum(bound, 1e-44))
+
+
+# operands that are both small: ordinary results from small products, subnormal results, results that underflow; and tiny
+# operands against ordinary ones, whose results are tiny and need every bit
+SMALL_PAIRS = [(-60, -60), (-70, -70), (-75, -76), (-120, 0), (-140, 3), (10, -130), (-110, -2), (-112, 19), (-118, 21)]
+
+
+@pytest.mark.parametrize("m,n,k", SIZES)
+@pytest.mark.parametrize("ea,eb", SMALL_PAIRS)
+def test_small_products(m, n, k, ea, eb):
+    import paper_1901_05350_amd as tfx
+    rng = np.random.default_rng(960 + m)
+    a = np.ldexp(rng.standard_normal((m, k)), ea).astype(np.float32)
+    b = np.ldexp(rng.standard_normal((k, n)), eb).astype(np.float32)
+    a[m // 2], b[:, n // 2] = 0, 0
+    got = host(tfx.tfx_matmul(dev(a), dev(b))).astype(np.float64)
+    exact, size = a.astype(np.float64) @ b.astype(np.float64), np.abs(a).astype(np.float64) @ np.abs(b).astype(np.float64)
+    # k roundings to 24 bits, or to the smallest float
+    assert np.all(np.abs(got - exact) <= k * np.maximum(2.0 ** -24 * size, 2.0 ** -149))
+
+
+def test_small_products_conv2d():
+    import paper_1901_05350_amd as tfx
+    for i, (n, h, w, ci, co, f, s) in enumerate(CONVS):
+        d = inputs.conv_general(1020 + i, n, h, w, ci, co, f, f)
+        x, filt, bias = d["x"], d["filter"], d["bias"]
+        x *= np.float32(2.0 ** -115)  # parts of these are below the smallest bf16
+        x[0], filt[..., 0], bias[: co // 2] = 0, 0, 0
+        bias[co // 2:] *= np.float32(2.0 ** -116)
+        got = host(tfx.tfx_conv2d(dev(x), dev(filt), dev(bias), s, oracle.PAD_SAME, oracle.ACT_NONE))
+        up = oracle.conv2d(np.ldexp(x, 115), filt, np.ldexp(bias, 115), s, oracle.PAD_SAME, oracle.ACT_NONE)
+        assert_close(np.ldexp(got, 115), up, "%r" % (CONVS[i],))
+
+
+@pytest.mark.parametrize("value", [1e-32, 1e-38, 1e-44])
+@pytest.mark.parametrize("b,m,n,k,ta,tb", [(8, 1024, 1024, 1024, False, True), (1, 1100, 900, 700, False, False), (1, 700, 300, 600, True, True)])
+def test_a_few_tiny_operands_cost_nothing(b, m, n, k, ta, tb, value):
+    import torch
+    import paper_1901_05350_amd as tfx
+    x = torch.randn((b, k, m) if ta else (b, m, k), device="cuda:0")
+    w = torch.randn((b, n, k) if tb else (b, k, n), device="cuda:0")
+    tiny = torch.where(torch.rand_like(x) < 1e-3, torch.full_like(x, value), x)
+    assert time_ratio(lambda v: tfx.tfx_batch_matmul(v, w, ta, tb), x, tiny) < 1.3
 
 
 def test_every_bit_counts():
