@@ -107,12 +107,26 @@ def lib():
 _call = None
 
 
+class _NoCall:
+    """Stands in for the extension where it cannot be loaded: every call goes through the checks below."""
+
+    def __getattr__(self, name):
+        return lambda *args: None
+
+
 def _load_call():
-    """The native host path of the entry points below (csrc/call.cpp), loaded with the library on first use."""
+    """The native host path of the entry points below (csrc/call.cpp), loaded with the library on first use.  It is built
+    for one PyTorch; where that is another, or it is not built, the library is called through ctypes alone."""
     global _call
     lib()
     import torch  # noqa: F401  (the extension uses torch's libraries)
-    from . import _call as module
+    try:
+        from . import _call as module
+    except ImportError as e:
+        import warnings
+        warnings.warn("paper_1901_05350_amd._call cannot be loaded (%s): calls take about 10 us more on the host until "
+                      "`python -m paper_1901_05350_amd.build --force` has built it" % e, RuntimeWarning)
+        module = _NoCall()
     _call = module
     return module
 

@@ -5,6 +5,7 @@ Usage: python -m paper_1901_05350_amd.build [--force]
 """
 import concurrent.futures
 import os
+import shutil
 import subprocess
 import sys
 
@@ -41,9 +42,12 @@ def _compile(src, force):
 
 def _compile_call(force):
     """The extension module links against libtfx.so beside it and torch's libraries, which `import torch` has loaded
-    by the time the module is imported."""
+    by the time the module is imported.  Without a host compiler there is none (the binding then does without)."""
     src = os.path.join(CSRC, "call.cpp")
     if not force and not _stale(CALL, [src, LIB] + HEADERS):
+        return
+    if shutil.which(os.environ.get("CXX", "g++")) is None:
+        print("no host compiler: _call.so is not built")
         return
     import sysconfig
     import torch
