@@ -118,11 +118,11 @@ struct BlockPlan {
   int tiles, c[kBlocks], n[kBlocks];  // of all blocks
   size_t packed[kBlocks], packed_halfs;  // the tile blocks' filters
 };
-BlockPlan plan_blocks_f16(const tfx_mobilenet_v1_variant& v, int64_t batch, int blocks) {
+BlockPlan plan_blocks_f16(const tfx_mobilenet_v1_variant& v, int64_t batch) {
   BlockPlan p{};
   const int q = (int)v.width_quarters;
   int hw = (int)(v.image_size + 1) / 2;
-  for (int b = 0; b < blocks; ++b) {
+  for (int b = 0; b < kBlocks; ++b) {
     p.c[b] = (b ? kChannels[b - 1] : kStemChannels) * q / 4, p.n[b] = kChannels[b] * q / 4;
     const int out = (hw + kStrides[b] - 1) / kStrides[b];
     auto fits = [&](auto supported) {
@@ -137,7 +137,7 @@ BlockPlan plan_blocks_f16(const tfx_mobilenet_v1_variant& v, int64_t batch, int 
     hw = out;
   }
   if (p.tiles < 3) {
-    for (int b = 0; b < blocks; ++b)
+    for (int b = 0; b < kBlocks; ++b)
       if (p.form[b] == kTile) p.form[b] = kTwo;
     p.tiles = 0, p.packed_halfs = 0;
   }
@@ -167,7 +167,7 @@ NetPlan plan_net(const tfx_mobilenet_v1_variant& v, int64_t batch, size_t elem_b
   p.head = p.chain && v.width_quarters == 4 && 2 * quarter * quarter * 128 <= p.act_floats;
   if (p.head) off = align_up(off + 2 * eighth * eighth * 256 * sizeof(float));  // outputs of blocks 4 and 5
   p.off_packed = off;
-  if (elem_bytes == sizeof(uint16_t)) off += plan_blocks_f16(v, batch, kBlocks).packed_halfs * sizeof(uint16_t);
+  if (elem_bytes == sizeof(uint16_t)) off += plan_blocks_f16(v, batch).packed_halfs * sizeof(uint16_t);
   p.bytes = off;
   return p;
 }
@@ -788,7 +788,7 @@ int forward_f16_impl(const tfx_mobilenet_v1_variant* variant, const uint16_t* in
   hipStream_t const s = static_cast<hipStream_t>(stream);
 
   const int blocks = end_block ? end_block : kBlocks;
-  const BlockPlan form = plan_blocks_f16(*variant, batch, blocks);
+  const BlockPlan form = plan_blocks_f16(*variant, batch);  // of the whole network: a feature map is the one a pass computes
   bool aligned = true;
   for (int b = 0; b < blocks; ++b)
     for (const void* p : {weights->dw_w[b], weights->dw_b[b], weights->pw_w[b], weights->pw_b[b]})
@@ -804,7 +804,8 @@ int forward_f16_impl(const tfx_mobilenet_v1_variant* variant, const uint16_t* in
         c[tiles] = form.c[b], n[tiles] = form.n[b];
         ++tiles;
       }
-    if (const int rc = launch_pack_filters_f16(tiles, filters, packed, c, n, s)) return rc;
+    if (tiles > 0)
+      if (const int rc = launch_pack_filters_f16(tiles, filters, packed, c, n, s)) return rc;
   }
 
   int64_t shape[4] = {batch, variant->image_size, variant->image_size, 3};

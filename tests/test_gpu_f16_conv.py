@@ -1,4 +1,6 @@
 """GPU parity on 16-bit float storage: conv2d, depthwiseConv2d and the MobileNet forward against the CPU oracle."""
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -466,3 +468,43 @@ def test_mobilenet_f16_argument_checks():
     rc = L.tfx_mobilenet_v1_forward_f16(ctypes.byref(V(64, 0, 10)), img.data_ptr(), 1, ctypes.byref(model.struct),
                                         model.workspace.data_ptr(), model.workspace.numel(), model.probs.data_ptr(), None, None)
     assert rc == -3
+
+
+class _KernelNode(ctypes.Structure):
+    _fields_ = [("block", ctypes.c_uint * 3), ("extra", ctypes.c_void_p), ("func", ctypes.c_void_p),
+                ("grid", ctypes.c_uint * 3), ("params", ctypes.c_void_p), ("shared", ctypes.c_uint)]
+
+
+def launches(run):
+    """(kernel, grid, block) of every launch that run() makes, from a capture of it."""
+    import torch
+    run()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph):
+        run()
+    hip = ctypes.CDLL(next(line.split()[-1] for line in open("/proc/self/maps") if "libamdhip64" in line))
+    handle, count = ctypes.c_void_p(graph.raw_cuda_graph()), ctypes.c_size_t(0)
+    assert hip.hipGraphGetNodes(handle, None, ctypes.byref(count)) == 0
+    nodes = (ctypes.c_void_p * count.value)()
+    assert hip.hipGraphGetNodes(handle, nodes, ctypes.byref(count)) == 0
+    out = []
+    for node in nodes:
+        k = _KernelNode()
+        assert hip.hipGraphKernelNodeGetParams(ctypes.c_void_p(node), ctypes.byref(k)) == 0
+        out.append((k.func, tuple(k.grid), tuple(k.block)))
+    return out
+
+
+@pytest.mark.parametrize("q,batch,blocks", [(4, 8, (5, 6, 13)), (2, 32, (3, 7))])
+def test_mobilenet_f16_feature_maps_run_the_kernels_of_the_whole_pass(q, batch, blocks):
+    import paper_1901_05350_amd as tfx
+    d = inputs.mobilenet_v1_f16(seed=75, batch=1, width_quarters=q, classes=10)
+    model = tfx.MobileNetV1F16(d["weights"], batch=batch, width_quarters=q)
+    image = dev16(np.concatenate([d["image"]] * batch))
+    whole = launches(lambda: model.forward(image))
+    for k in blocks:
+        out = model.features(image, k)
+        part = launches(lambda: model.features(image, k, out))
+        # the first launch orders the filters of the blocks that run
+        assert len(part) > k and part[0][0] == whole[0][0] and part[1:] == whole[1:len(part)], k
