@@ -206,6 +206,28 @@ def test_thin_products_of_a_batch(ta, tb):
         assert_close(got[fin], ref[fin], "%r ta=%d tb=%d" % ((b, m, n, k), ta, tb))
 
 
+def fp32_instructions(x, w):
+    """What the fp32 matrix instructions accumulate: one product at a time, rounded to fp32."""
+    acc = np.zeros((len(x), w.shape[1]), np.float32)
+    for k in range(len(w)):
+        acc = (acc + x[:, k:k + 1].astype(np.float64) * w[k].astype(np.float64)).astype(np.float32)
+    return acc
+
+
+@pytest.mark.parametrize("uniform", [False, True])
+@pytest.mark.parametrize("m,n,k", [(4096, 2048, 96), (4096, 1024, 640), (5000, 320, 40), (1100, 900, 700), (1000, 520, 300), (700, 300, 200),
+                                   (700, 300, 2100), (2048, 1100, 16)])
+def test_error_against_float64_is_no_larger_than_with_fp32_instructions(m, n, k, uniform):
+    import paper_1901_05350_amd as tfx
+    rng = np.random.default_rng(1500 + k)
+    draw = (lambda s: rng.random(s)) if uniform else rng.standard_normal
+    x, w = draw((m, k)).astype(np.float32), draw((k, n)).astype(np.float32)
+    rows = slice(m // 2, m // 2 + 96)
+    got, exact = host(tfx.tfx_matmul(dev(x), dev(w)))[rows], x[rows].astype(np.float64) @ w.astype(np.float64)
+    error = lambda v: np.linalg.norm(v - exact) / np.linalg.norm(exact)
+    assert error(got) <= 1.05 * error(fp32_instructions(x[rows], w))  # (5 %: sampling of 96 rows)
+
+
 @pytest.mark.parametrize("ta,tb", [(False, False), (True, True)])
 @pytest.mark.parametrize("b,m,n", [(1, 700, 642), (16, 513, 260), (40, 17, 31), (2, 1500, 1030)])
 def test_few_products_are_as_accurate_as_fp32(b, m, n, ta, tb):
