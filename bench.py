@@ -31,21 +31,21 @@ PEAK_HBM = 8.0e12          # B/s
 # source it was measured on, with the digest of that file followed by the shared headers csrc/tfx_internal.h and
 # csrc/stream_f16.h; if any of them has changed since, the entry is reported as null.
 MEASURED_TRAFFIC = {
-    "batch_matmul_8x1024x1024x1024_tB": (100981151, "gemm.hip", "d7939dacb9d53741e3e98d689afff0e6268a099a748237194f3934c80a39b9fa"),
-    "pointwise_64x56x56x128_to_128": (206178801, "pointwise.hip", "bd2ffc187a28564fabcb99eaadd568df29dc41bc107f0a69c61f068533a88545"),
-    "conv3x3_64x56x56x64_to_64": (106020132, "gemm.hip", "d7939dacb9d53741e3e98d689afff0e6268a099a748237194f3934c80a39b9fa"),
-    "depthwise_64x112x112x64_s1_cold_rotation": (411135650, "depthwise.hip", "b6cb3b00ef445d7acaff8105567c83d58447115871f8f66472cfec35e840f74f"),
-    "depthwise_64x112x112x64_s2_cold_rotation": (257094017, "depthwise.hip", "b6cb3b00ef445d7acaff8105567c83d58447115871f8f66472cfec35e840f74f"),
-    "batch_matmul_f16_1x4096x4096x4096_tB": (235152325, "gemm_f16.hip", "d6d0ba339801c31485c16445ec998cf7509fcd679963289d893fb6d21557ecab"),
-    "batch_matmul_f16_8x1024x1024x1024_tB": (50539949, "gemm_f16.hip", "d6d0ba339801c31485c16445ec998cf7509fcd679963289d893fb6d21557ecab"),
-    "pointwise_f16_64x56x56x128_to_128": (104159036, "pointwise_f16.hip", "6465bfeaedd1bf57e3bf4a552e519ca8ce2e62fea0b6d07fb1b17dbc0643a591"),
-    "depthwise_f16_64x112x112x64_s1_cold_rotation": (205679923, "conv_f16.hip", "8caf7f66dd82dacebc3db73aa0bdd45b96923dc1817847550c79d1ca62d9cd41"),
-    "depthwise_f16_64x112x112x64_s2_cold_rotation": (128552465, "conv_f16.hip", "8caf7f66dd82dacebc3db73aa0bdd45b96923dc1817847550c79d1ca62d9cd41"),
-    "pointwise_f16_64x14x14x512_to_512": (30195063, "pointwise_slab_f16.hip", "8012b8f425969c51a0fca6bfc389f978bf51906f949d18a5cbc668150f77390b"),
-    "conv3x3_f16_64x56x56x64_to_64": (55026885, "conv_stream_f16.hip", "4a8944769f755fb70f62fd88ff85b7817adc411fa37506b5950eb98ea23c0c26"),
-    "add_f32_64M": (805250660, "elementwise.hip", "195263450a71be67dd8680848f3a6ff70e26ddc1f91b678d57717405d98d32b0"),
-    "add_f16_64M": (402645490, "elementwise.hip", "195263450a71be67dd8680848f3a6ff70e26ddc1f91b678d57717405d98d32b0"),
-    "mobilenet_chain_kernel": (121637893, "chain.hip", "2b0b5176dfd2f26ae0b2e607328375cca869bc44084acb5437d86ae2bb2e68b3"),
+    "batch_matmul_8x1024x1024x1024_tB": (100948049, "gemm.hip", "ee000851d7d5260abb5d10fcf7891d61b4c28fdd2acd02e94e51c17813776421"),
+    "pointwise_64x56x56x128_to_128": (206181418, "pointwise.hip", "1637e827044860fec32ccf74a12b605ca8ed91979354dfadbb93414a029ec82d"),
+    "conv3x3_64x56x56x64_to_64": (106084848, "gemm.hip", "ee000851d7d5260abb5d10fcf7891d61b4c28fdd2acd02e94e51c17813776421"),
+    "depthwise_64x112x112x64_s1_cold_rotation": (411139872, "depthwise.hip", "76bed0fac2cbea969f1ba4f325eeee395e641a680de5122b521f4df0b9c19c11"),
+    "depthwise_64x112x112x64_s2_cold_rotation": (257134394, "depthwise.hip", "76bed0fac2cbea969f1ba4f325eeee395e641a680de5122b521f4df0b9c19c11"),
+    "batch_matmul_f16_1x4096x4096x4096_tB": (235157353, "gemm_f16.hip", "e6a2173ed81b175fb73ee7060b12dfe5ae10f608d5047a0a6555fc256046f3a5"),
+    "batch_matmul_f16_8x1024x1024x1024_tB": (50540796, "gemm_f16.hip", "e6a2173ed81b175fb73ee7060b12dfe5ae10f608d5047a0a6555fc256046f3a5"),
+    "pointwise_f16_64x56x56x128_to_128": (104309503, "pointwise_f16.hip", "99ea7211fd61f80abe0a9ebc195f73ceff7204c28282c23baffa4db5e9214605"),
+    "depthwise_f16_64x112x112x64_s1_cold_rotation": (205682558, "conv_f16.hip", "b6b68ed458b6e2d1a33aa925f8bd7ee19660df6f20e6b004ceccc30cf7010b44"),
+    "depthwise_f16_64x112x112x64_s2_cold_rotation": (128559845, "conv_f16.hip", "b6b68ed458b6e2d1a33aa925f8bd7ee19660df6f20e6b004ceccc30cf7010b44"),
+    "pointwise_f16_64x14x14x512_to_512": (30190477, "pointwise_slab_f16.hip", "5d72071505f1671435a2d01d1274c5b416151f856d5c093ed8c91f6c00bf9dd9"),
+    "conv3x3_f16_64x56x56x64_to_64": (55026548, "conv_stream_f16.hip", "8d59dfe37f6d634755008a7a6791dd3ec02d89b6048ee5767a8b35054e14c6b9"),
+    "add_f32_64M": (805263867, "elementwise.hip", "33fca024b6a991f3cdd869bbf66c5939110817e5e34fedeeaa7d6a0b91a1d7e6"),
+    "add_f16_64M": (402652251, "elementwise.hip", "33fca024b6a991f3cdd869bbf66c5939110817e5e34fedeeaa7d6a0b91a1d7e6"),
+    "mobilenet_chain_kernel": (121649614, "chain.hip", "8f3eea3b0d8cf50f90edbdb0675c7edf60557fa622870fc839625a7718df8aab"),
 }
 
 

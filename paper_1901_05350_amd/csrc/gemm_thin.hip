@@ -10,7 +10,7 @@
 // the first operand, so that a lane ends up with four consecutive columns of a row: one 16- (8-) byte store.
 // A lane's operand of a k-step of 16 is 8 consecutive k of its row (column), loaded 16 bytes at a time at any alignment
 // where these are contiguous, one element at a time (32 rows next to each other) where they are not.
-// Bound by the stores: 32 x 1024 x 1024 floats, K = 8: 29.6 us, 1.1 times the bytes at the rate of a large copy
+// Bound by the stores: 32 x 1024 x 1024 floats, K = 8: 28 us, 1.05 times the bytes at the rate of a large copy
 // (LDS tiles 39 and 49, wavefronts splitting K 80 ... 117).
 #include "ragged.h"
 
