@@ -189,7 +189,7 @@ def test_thin_products(case, half):
 # gemm_thin.hip over a batch and with A stored [K,M]: many small matrices, so that it is the kernel taken; tiles of 32 rows and 32
 # or 64 columns, k at and beside a k-step and a vector load: (batch, m, n, k)
 THIN_BATCH = [(3000, 33, 65, 16), (3000, 31, 64, 17), (2500, 32, 33, 32), (9000, 64, 5, 3), (700, 65, 130, 7), (5000, 34, 31, 15),
-              (2000, 40, 63, 31), (400, 129, 96, 1), (1, 2049, 2047, 9), (3, 1025, 1000, 2), (1, 16, 100003, 24)]
+              (6000, 33, 31, 30), (400, 129, 96, 1), (1, 2049, 2047, 9), (3, 1025, 1000, 2), (1, 16, 100003, 24)]
 
 
 @pytest.mark.parametrize("ta,tb", [(False, False), (True, False), (False, True), (True, True)])
