@@ -471,13 +471,76 @@ __global__ __launch_bounds__(256) void pool_f16_kernel(const half_t* __restrict_
   }
 }
 
+// Pool and fully connected layer of few images: a workgroup pools 128 channels of one image and multiplies them by its 128
+// columns of the weights, which are on their way before the pixels are waited for; the slices' sums are added up by the
+// softmax kernel.  VEC: a multiple of 8 classes (16-byte loads of the weights).
+// Up to 32 images: two launches where there were three (network of 8 images 152 -> 148 us, 32 229 -> 228; 64 324 -> 327).
+constexpr int kFcSliceK = 128, kFcSliceClasses = 128, kFcMaxSlices = 8, kFcSliceImages = 32;  // k <= 1024
+template <bool VEC>
+__global__ __launch_bounds__(256) void pool_fc_slice_f16_kernel(const half_t* __restrict__ a, const half_t* __restrict__ w,
+                                                                float* __restrict__ partial, int n, int hw, int k, int classes) {
+  constexpr int GROUPS = 16, PX = 4;  // hw <= 64
+  __shared__ __align__(16) float red[GROUPS][kFcSliceK];  // the pixel groups' sums, then the row groups'
+  __shared__ float pooled[kFcSliceK];
+  const int tid = threadIdx.x, img = blockIdx.z, k0 = kFcSliceK * blockIdx.y, j0 = kFcSliceClasses * blockIdx.x;
+  const int e0 = 8 * (tid % 16), grp = tid / 16;  // channels (classes) e0 ... + 7, pixels (rows) grp, grp + 16, ...
+  h8 v[PX];
+#pragma unroll
+  for (int i = 0; i < PX; ++i) v[i] = *reinterpret_cast<const h8*>(a + ((size_t)img * hw + min(grp + GROUPS * i, hw - 1)) * k + k0 + e0);
+  constexpr int ROWS = kFcSliceK / GROUPS;
+  h8 wv[ROWS];
+#pragma unroll
+  for (int i = 0; i < ROWS; ++i) {
+    const half_t* const row = w + (size_t)(k0 + grp + GROUPS * i) * classes;
+    if constexpr (VEC) wv[i] = *reinterpret_cast<const h8*>(row + (j0 + e0 < classes ? j0 + e0 : 0));
+    else
+#pragma unroll
+      for (int e = 0; e < 8; ++e) wv[i][e] = row[min(j0 + e0 + e, classes - 1)];
+  }
+  float s[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int i = 0; i < PX; ++i)
+    if (grp + GROUPS * i < hw) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) s[e] += (float)v[i][e];
+    }
+#pragma unroll
+  for (int e = 0; e < 8; ++e) red[grp][e0 + e] = s[e];
+  __syncthreads();
+  if (tid < kFcSliceK) {
+    float t = 0.f;
+#pragma unroll
+    for (int g = 0; g < GROUPS; ++g) t += red[g][tid];
+    pooled[tid] = (float)to_half(t / (float)hw);  // the pooled vector is a binary16 tensor
+  }
+  __syncthreads();
+  float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int i = 0; i < ROWS; ++i) {
+    const float p = pooled[grp + GROUPS * i];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) acc[e] = fmaf(p, (float)wv[i][e], acc[e]);
+  }
+#pragma unroll
+  for (int e = 0; e < 8; ++e) red[grp][e0 + e] = acc[e];
+  __syncthreads();
+  const int j = j0 + tid;
+  if (tid < kFcSliceClasses && j < classes) {
+    float t = 0.f;
+#pragma unroll
+    for (int g = 0; g < GROUPS; ++g) t += red[g][tid];
+    partial[((size_t)blockIdx.y * n + img) * classes + j] = t;
+  }
+}
+
 constexpr int kMaxPerThread = 4;  // classes <= 1024
-// logits_in == nullptr: the logits are the sum of the K-slice partial sums plus the bias, rounded to binary16 (and
+// logits_in == nullptr: the logits are the sum of the `slices` (at most SLICES) K-slice partial sums plus the bias, rounded to binary16 (and
 // written to `logits` if asked for); otherwise they are read from logits_in.
+template <int SLICES>
 __global__ __launch_bounds__(256) void softmax_f16_kernel(const float* __restrict__ partial,
                                                           const half_t* __restrict__ bias, half_t* __restrict__ logits,
                                                           half_t* __restrict__ probs, int n, int classes,
-                                                          const half_t* __restrict__ logits_in) {
+                                                          const half_t* __restrict__ logits_in, int slices) {
   __shared__ float scratch[4];
   const int img = blockIdx.x;
   float l[kMaxPerThread];
@@ -490,12 +553,12 @@ __global__ __launch_bounds__(256) void softmax_f16_kernel(const float* __restric
       l[i] = (float)logits_in[(size_t)img * classes + j];
       mx = fmaxf(mx, l[i]);
     } else if (j < classes) {
-      float part[kFcSlices];
+      float part[SLICES];
 #pragma unroll
-      for (int s = 0; s < kFcSlices; ++s) part[s] = partial[((size_t)s * n + img) * classes + j];
+      for (int s = 0; s < SLICES; ++s) part[s] = partial[((size_t)(s < slices ? s : 0) * n + img) * classes + j];
       float v = bias ? (float)bias[j] : 0.f;
 #pragma unroll
-      for (int s = 0; s < kFcSlices; ++s) v += part[s];
+      for (int s = 0; s < SLICES; ++s) v += s < slices ? part[s] : 0.f;
       const half_t lh = to_half(v);  // the logits are a binary16 tensor; the softmax is taken of those
       if (logits) logits[(size_t)img * classes + j] = lh;
       l[i] = (float)lh;
@@ -604,6 +667,19 @@ int launch_pool_fc_softmax_f16(const uint16_t* a, const uint16_t* w, const uint1
                                uint16_t* logits, uint16_t* probs, int n, int hw, int k, int classes,
                                hipStream_t stream) {
   if (classes > 256 * kMaxPerThread) return TFX_ERR_UNSUPPORTED;
+  if (n <= kFcSliceImages && hw <= 64 && k % kFcSliceK == 0 && k <= kFcSliceK * kFcMaxSlices &&
+      reinterpret_cast<uintptr_t>(a) % 16 == 0) {
+    const dim3 grid((classes + kFcSliceClasses - 1) / kFcSliceClasses, k / kFcSliceK, n);
+    if (classes % 8 == 0 && reinterpret_cast<uintptr_t>(w) % 16 == 0)
+      hipLaunchKernelGGL(pool_fc_slice_f16_kernel<true>, grid, dim3(256), 0, stream, H(a), H(w), partial, n, hw, k, classes);
+    else
+      hipLaunchKernelGGL(pool_fc_slice_f16_kernel<false>, grid, dim3(256), 0, stream, H(a), H(w), partial, n, hw, k, classes);
+    const int rc = check_launch();
+    if (rc) return rc;
+    hipLaunchKernelGGL(softmax_f16_kernel<kFcMaxSlices>, dim3(n), dim3(256), 0, stream, (const float*)partial, H(bias), H(logits),
+                       H(probs), n, classes, (const half_t*)nullptr, k / kFcSliceK);
+    return check_launch();
+  }
   // With a class count that is a multiple of 8 (16-byte rows of the weights): pool, then the fully connected layer as
   // a GEMM (bias and the rounding of the logits in its epilogue), then the softmax of the stored logits -- three
   // launches, faster than the two below at every batch (those re-read the weights once per 4 images and write 32 n
@@ -619,8 +695,8 @@ int launch_pool_fc_softmax_f16(const uint16_t* a, const uint16_t* w, const uint1
     if (rc) return rc;
     rc = launch_gemm_f16(pooled, w, lg, bias, 1, n, classes, k, true, false, TFX_ACT_NONE, stream);
     if (rc) return rc;
-    hipLaunchKernelGGL(softmax_f16_kernel, dim3(n), dim3(256), 0, stream, (const float*)nullptr, (const half_t*)nullptr,
-                       (half_t*)nullptr, H(probs), n, classes, H(lg));
+    hipLaunchKernelGGL(softmax_f16_kernel<kFcSlices>, dim3(n), dim3(256), 0, stream, (const float*)nullptr, (const half_t*)nullptr,
+                       (half_t*)nullptr, H(probs), n, classes, H(lg), 0);
     return check_launch();
   }
   const int kslice = (k + kFcSlices - 1) / kFcSlices;
@@ -630,8 +706,8 @@ int launch_pool_fc_softmax_f16(const uint16_t* a, const uint16_t* w, const uint1
                      kslice);
   int rc = check_launch();
   if (rc) return rc;
-  hipLaunchKernelGGL(softmax_f16_kernel, dim3(n), dim3(256), 0, stream, (const float*)partial, H(bias), H(logits),
-                     H(probs), n, classes, (const half_t*)nullptr);
+  hipLaunchKernelGGL(softmax_f16_kernel<kFcSlices>, dim3(n), dim3(256), 0, stream, (const float*)partial, H(bias), H(logits),
+                     H(probs), n, classes, (const half_t*)nullptr, kFcSlices);
   return check_launch();
 }
 
