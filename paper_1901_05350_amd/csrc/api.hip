@@ -108,11 +108,16 @@ bool valid_variant(const tfx_mobilenet_v1_variant* v) {
          v->classes >= 1 && v->classes <= 1024;
 }
 
-// On binary16 storage, each block's form: depthwise and pointwise layer in one launch, with the filters stationary in LDS
-// (block_stream_f16.hip: large batch, early block) or the depthwise output there (block_tile_f16.hip), or as two.  The
-// pointwise filters of the second kind are put in its order by one launch in front, for which one or two such blocks do
-// not pay.  (All operands are taken to be aligned.)
-enum BlockForm { kTwo, kStream, kTile };
+// On binary16 storage, each block's form: depthwise and pointwise layer in one launch, for few pixels with a workgroup per
+// 4 x 4 patch (block_patch_f16.hip), with the filters stationary in LDS (block_stream_f16.hip: large batch, early block) or
+// with the depthwise output there (block_tile_f16.hip), or as two.  The pointwise filters of the tile form are put in its
+// order by one launch in front, for which one or two such blocks do not pay.  (All operands are taken to be aligned.)
+enum BlockForm { kTwo, kPatch, kStream, kTile };
+// Multiplications of the pointwise layer up to which the patch form is the fastest: each column slice of a patch computes its
+// depthwise layer again, so its time grows with both.  Full width, batch 4 (14 x 14 x 512 -> 512 205e6) 102 us against 122
+// without that block, batch 6 (308e6) 150 against 145; 3/4 width, whose other form is two launches for most blocks, batch 16
+// 194 with blocks of 308e6, 212 without, batch 12 with blocks of 416e6 208 against 180.
+constexpr int64_t kPatchProducts = 210000000, kPatchProductsTwo = 310000000;
 struct BlockPlan {
   BlockForm form[kBlocks];
   int tiles, c[kBlocks], n[kBlocks];  // of all blocks
@@ -122,13 +127,21 @@ BlockPlan plan_blocks_f16(const tfx_mobilenet_v1_variant& v, int64_t batch) {
   BlockPlan p{};
   const int q = (int)v.width_quarters;
   int hw = (int)(v.image_size + 1) / 2;
+  bool small[kBlocks];  // a block that the patch kernel computes faster than two launches do
   for (int b = 0; b < kBlocks; ++b) {
     p.c[b] = (b ? kChannels[b - 1] : kStemChannels) * q / 4, p.n[b] = kChannels[b] * q / 4;
     const int out = (hw + kStrides[b] - 1) / kStrides[b];
     auto fits = [&](auto supported) {
       return supported((int)batch, hw, hw, p.c[b], p.n[b], kStrides[b], out, out, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr);
     };
-    p.form[b] = fits(separable_stream_f16_supported) ? kStream : fits(separable_tile_f16_supported) ? kTile : kTwo;
+    const bool patch = fits(separable_patch_f16_supported);
+    const int64_t products = batch * out * out * p.c[b] * p.n[b];
+    small[b] = patch && products <= kPatchProductsTwo;
+    p.form[b] = patch && products <= kPatchProducts        ? kPatch
+                : fits(separable_stream_f16_supported) ? kStream
+                : fits(separable_tile_f16_supported)   ? kTile
+                : small[b]                             ? kPatch
+                                                       : kTwo;
     if (p.form[b] == kTile) {
       ++p.tiles;
       p.packed[b] = p.packed_halfs;
@@ -138,7 +151,7 @@ BlockPlan plan_blocks_f16(const tfx_mobilenet_v1_variant& v, int64_t batch) {
   }
   if (p.tiles < 3) {
     for (int b = 0; b < kBlocks; ++b)
-      if (p.form[b] == kTile) p.form[b] = kTwo;
+      if (p.form[b] == kTile) p.form[b] = small[b] ? kPatch : kTwo;
     p.tiles = 0, p.packed_halfs = 0;
   }
   return p;
@@ -823,7 +836,7 @@ int forward_f16_impl(const tfx_mobilenet_v1_variant* variant, const uint16_t* in
     conv_geometry(shape, fd, kStrides[b], kStrides[b], TFX_PAD_SAME, true, &g);
     if (aligned && form.form[b] != kTwo) {
       const bool tile = form.form[b] == kTile;
-      const auto launch = tile ? launch_separable_tile_f16 : launch_separable_stream_f16;
+      const auto launch = tile ? launch_separable_tile_f16 : form.form[b] == kPatch ? launch_separable_patch_f16 : launch_separable_stream_f16;
       rc = launch(buf[cur], weights->dw_w[b], weights->dw_b[b], tile ? packed_base + form.packed[b] : weights->pw_w[b],
                   weights->pw_b[b], end_block == b + 1 ? features : buf[cur ^ 1], (int)batch, (int)shape[1], (int)shape[2],
                   (int)shape[3], (int)cout, (int)g.out[1], (int)g.out[2], kStrides[b], (int)g.pad[0], (int)g.pad[2],
