@@ -128,8 +128,8 @@ BlockPlan plan_blocks_f16(const tfx_mobilenet_v1_variant& v, int64_t batch) {
   const int q = (int)v.width_quarters;
   int hw = (int)(v.image_size + 1) / 2;
   bool small[kBlocks];  // a block that the patch kernel computes faster than two launches do
-  for (int b = 0; b < kBlocks; ++b) {
-    p.c[b] = (b ? kChannels[b - 1] : kStemChannels) * q / 4, p.n[b] = kChannels[b] * q / 4;
+  for (int b = 1; b < kBlocks; ++b) {  // (the first runs with the stem: block_rows_f16.hip)
+    p.c[b] = kChannels[b - 1] * q / 4, p.n[b] = kChannels[b] * q / 4;
     const int out = (hw + kStrides[b] - 1) / kStrides[b];
     auto fits = [&](auto supported) {
       return supported((int)batch, hw, hw, p.c[b], p.n[b], kStrides[b], out, out, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr);
@@ -150,7 +150,7 @@ BlockPlan plan_blocks_f16(const tfx_mobilenet_v1_variant& v, int64_t batch) {
     hw = out;
   }
   if (p.tiles < 3) {
-    for (int b = 0; b < kBlocks; ++b)
+    for (int b = 1; b < kBlocks; ++b)
       if (p.form[b] == kTile) p.form[b] = small[b] ? kPatch : kTwo;
     p.tiles = 0, p.packed_halfs = 0;
   }
@@ -823,14 +823,16 @@ int forward_f16_impl(const tfx_mobilenet_v1_variant* variant, const uint16_t* in
 
   int64_t shape[4] = {batch, variant->image_size, variant->image_size, 3};
   const int64_t f0[4] = {3, 3, 3, kStemChannels * q / 4};
-  int rc = tfx_conv2d_f16(input, shape, weights->conv0_w, f0, weights->conv0_b, 2, 2, TFX_PAD_SAME, TFX_ACT_RELU6,
-                          buf[0], stream);
-  if (rc) return rc;
   ConvGeom g;
   conv_geometry(shape, f0, 2, 2, TFX_PAD_SAME, false, &g);
-  for (int i = 0; i < 4; ++i) shape[i] = g.out[i];
+  int rc = launch_stem_block_rows_f16(input, weights->conv0_w, weights->conv0_b, weights->dw_w[0], weights->dw_b[0], weights->pw_w[0],
+                                      weights->pw_b[0], end_block == 1 ? features : buf[0], (int)batch, (int)shape[1], (int)shape[2],
+                                      (int)g.out[1], (int)g.out[2], (int)g.pad[0], (int)g.pad[2], q, s);
+  if (rc || end_block == 1) return rc;
+  for (int i = 0; i < 3; ++i) shape[i] = g.out[i];
+  shape[3] = kChannels[0] * q / 4;
   int cur = 0;
-  for (int b = 0; b < blocks; ++b) {
+  for (int b = 1; b < blocks; ++b) {  // (the first came with the stem)
     const int64_t fd[4] = {3, 3, shape[3], 1};
     const int64_t cout = kChannels[b] * q / 4;
     conv_geometry(shape, fd, kStrides[b], kStrides[b], TFX_PAD_SAME, true, &g);

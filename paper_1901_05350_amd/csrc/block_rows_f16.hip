@@ -1,0 +1,287 @@
+// The stem (3x3 stride-2 convolution of the image to 8 Q channels) and the first depthwise-separable block (depthwise 3x3 +
+// bias + clamp, pointwise 1x1 to 16 Q channels + bias + clamp) on binary16 storage in one launch (Section 4.1 storage format,
+// the Section 3.9 network).
+//
+// The stem's output is the largest map but one of the network; written and read again it costs as much as the block's own
+// output.  Here a workgroup walks down a strip of rows of one image, a wavefront for every 16 columns, and keeps the four stem
+// rows that it works on in LDS: three under the depthwise filter and the one it computes for the next step, with one barrier
+// a row.  Stem rows are rounded to binary16 as the separate kernel rounds them, and only the two rows above and below a strip
+// are computed twice.
+//
+// Contraction of the stem (v_mfma_f32_16x16x32_f16, filters as the first operand): lane (li, q) supplies 8 values of pixel
+// li's window, for q < 3 the first 8 of the 9 that lie next to each other in image row q of it -- one load of 16 bytes at
+// whatever address --, for q = 3 the ninth of each row.
+//
+// The depthwise layer runs on the matrix cores too, as products with diagonal matrices: two taps x 16 channels are the 32 of a
+// contraction, of which each channel's row of the filter operand has but its own two weights.  15/16 of the multiplications are
+// with zero, and still ten such instructions (16 cycles each) replace 72 mixed-precision multiply-adds (4.4 cycles each,
+// measured); the result comes as the pointwise product's operand.  A zero times a NaN is a NaN in 15 other channels, but all
+// channels of the pixel meet in every output of the pointwise layer, so the same outputs are NaN; the map itself, behind a
+// relu6, has no infinities.
+//
+// 64 images of 224 x 224, full width: 28 us (31 under the profiler), where the stem and the block's kernel took 52 (23 + 30); the
+// image's and the output's 122 MB take 24 at the rate of a large copy.  With the depthwise layer on the vector units 33.  One
+// image: 6.4 us, two launches 8.6.
+#include "ragged.h"
+#include "stream_f16.h"
+
+namespace tfx {
+namespace {
+
+using namespace f16s;
+
+struct RowsArgs {
+  const half_t *x, *st_w, *st_b, *dw_w, *dw_b, *pw_w, *pw_b;
+  half_t* y;
+  int IH, IW, OH, OW, pt, pl, strips, rows;  // rows of a strip
+  long long image_halfs, total_halfs;  // of one image, of all
+  unsigned y_bytes;
+};
+
+struct RowsPixel {
+  int pieces;
+  constexpr int operator()(int li, int q) const { return li * pieces + q; }
+};
+template <int Q>
+constexpr int rows_pixel_pieces() {
+  for (int p = Q;; ++p)
+    if (conflict_free(RowsPixel{p})) return p;
+}
+
+template <int Q>
+__global__ __launch_bounds__(512, 4) void stem_block_rows_f16_kernel(RowsArgs g) {
+  constexpr int C = 8 * Q, N = 16 * Q, NB = Q, G = (C + 15) / 16, PX = 8 * rows_pixel_pieces<Q>();
+  extern __shared__ __align__(16) half_t ring[];  // [4][16 T + 2][PX]: stem row r in slot r % 4, column c at c + 1
+  // what a step reads once or twice stays in LDS: 128 registers for each of the 16 wavefronts of a CU
+  __shared__ __align__(16) float stem_bias[16 * G], dw_bias[16 * G], pw_bias[N];
+  __shared__ __align__(16) h8 stem_w[G][64];
+  const int lane = threadIdx.x % 64, li = lane % 16, q = lane / 16;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / 64);
+  const int cols = (int)blockDim.x / 4 + 2, slot = cols * PX;
+  const int n = blockIdx.x / g.strips, r0 = (blockIdx.x - n * g.strips) * g.rows, r1 = min(r0 + g.rows, g.OH);
+  const int ow = 16 * wave + li;
+
+  // The stem's operand.  Byte offsets of this lane's values in the image's row 0, past the end of the buffer (from where loads
+  // return 0) for a lane without any.
+  constexpr unsigned kNone = 0x80000000u;
+  const int iw0 = 2 * ow - g.pl, row_bytes = 6 * g.IW;
+  const bool left = iw0 < 0;            // (by one column) loaded from the row's start and moved up by a pixel
+  const int inside = 3 * (g.IW - iw0);  // values of a window row up to the image's end (9 or more: all)
+  const unsigned at8 = q < 3 && ow < g.OW ? (unsigned)(6 * max(iw0, 0) + q * row_bytes) : kNone;
+  const unsigned at9 = q == 3 && ow < g.OW && inside >= 9 ? (unsigned)(6 * iw0 + 16) : kNone;
+  const bool edge = (wave == 0 && g.pl > 0) || 2 * (16 * wave + 15) - g.pl + 3 > g.IW;  // of the wavefront's columns
+  const long long start = n * g.image_halfs;
+  const __amdgpu_buffer_rsrc_t xr =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<half_t*>(g.x + start), 0, (int)(2 * (g.total_halfs - start)), 0x00020000);
+  const unsigned last = (unsigned)(2 * (g.total_halfs - start) - 16);  // offset at which 16 bytes can be loaded
+  if (wave == 0) {
+#pragma unroll
+    for (int j = 0; j < G; ++j) {
+      h8 sw;
+#pragma unroll
+      for (int t = 0; t < 8; ++t) {
+        const int row = q < 3 ? 9 * q + t : 9 * (t < 3 ? t : 2) + 8, ch = 16 * j + li;
+        const half_t v = g.st_w[row * C + (ch < C ? ch : 0)];
+        sw[t] = ch < C && (q < 3 || t < 3) ? v : (half_t)0.f;
+      }
+      stem_w[j][lane] = sw;
+    }
+  }
+  // The depthwise layer as a product with diagonal matrices: k = (tap, channel) of two taps and 16 channels, row = channel.
+  // Lane (li, q) supplies tap 2 i + q / 2, channels 8 (q % 2) ... + 7 of the group to both operands; of the filter all but
+  // channel li is zero.
+  h8 dww[5][G];
+  unsigned short dwv[5][G];
+#pragma unroll
+  for (int i = 0; i < 5; ++i)
+#pragma unroll
+    for (int u = 0; u < G; ++u) {
+      const int t = min(2 * i + q / 2, 8), ch = 16 * u + li;
+      dwv[i][u] = reinterpret_cast<const unsigned short*>(g.dw_w)[t * C + (ch < C ? ch : 0)];
+    }
+#pragma unroll
+  for (int i = 0; i < 5; ++i)
+#pragma unroll
+    for (int u = 0; u < G; ++u) {
+      const bool mine = li / 8 == q % 2 && 2 * i + q / 2 < 9 && 16 * u + li < C;
+      u32x4 v;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = mine && li % 8 / 2 == e ? (unsigned)dwv[i][u] << 16 * (li % 2) : 0u;
+      dww[i][u] = __builtin_bit_cast(h8, v);
+    }
+  // block j of the output's channels: pairs in rho order (16-byte stores), a last single one as it comes
+  h8 pw[NB];
+#pragma unroll
+  for (int j = 0; j < NB; ++j) {
+    const int c = j + (j % 2 == 0) < NB ? 32 * (j / 2) + 8 * (li / 4) + 4 * (j % 2) + li % 4 : 16 * j + li;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int k = 16 * (i / 4) + 4 * q + i % 4;  // as the depthwise layer's result comes
+      const half_t v = g.pw_w[(k < C ? k : 0) * N + c];
+      pw[j][i] = k < C ? v : (half_t)0.f;
+    }
+  }
+  // the biases in the accumulators' order, and zeros left and right of the map
+  for (int i = threadIdx.x; i < 16 * G; i += (int)blockDim.x) {
+    stem_bias[i] = i < C ? (float)g.st_b[i] : 0.f;
+    dw_bias[i] = i < C ? (float)g.dw_b[i] : 0.f;
+  }
+  for (int i = threadIdx.x; i < N; i += (int)blockDim.x) {
+    const int j = i / 16, e = i % 16;
+    pw_bias[i] = (float)g.pw_b[j + (j % 2 == 0) < NB ? 32 * (j / 2) + 8 * (e / 4) + 4 * (j % 2) + e % 4 : i];
+  }
+  for (int i = threadIdx.x; i < 4 * 2 * Q; i += (int)blockDim.x) {
+    const int s = i / (2 * Q), side = i / Q % 2, piece = i % Q;
+    *reinterpret_cast<u32x4*>(ring + s * slot + (side ? cols - 1 : 0) * PX + 8 * piece) = u32x4{0, 0, 0, 0};
+  }
+  const ActClamp clamp = make_act(TFX_ACT_RELU6);
+
+  struct Window {
+    u32x4 v;
+    unsigned short n[3];
+  };
+  auto fetch = [&](int r, Window& w) __attribute__((always_inline)) {  // of stem row r; image rows outside: anything
+    const unsigned row = (unsigned)((2 * r - g.pt) * row_bytes);
+    // 16 bytes from before the end of the last image where the window's 8 values would pass it (back in place in `stem`)
+    const unsigned at = at8 + row;
+    w.v = __builtin_amdgcn_raw_buffer_load_b128(xr, at8 != kNone && (int)at > (int)last ? last : at, 0, 0);
+#pragma unroll
+    for (int t = 0; t < 3; ++t) w.n[t] = (unsigned short)__builtin_amdgcn_raw_buffer_load_b16(xr, at9 + row + t * row_bytes, 0, 0);
+  };
+  auto stem = [&](int r, const Window& w) __attribute__((always_inline)) {
+    half_t* const to = ring + (r & 3) * slot + (ow + 1) * PX + 4 * q;
+    if (r < 0 || r >= g.OH) {
+#pragma unroll
+      for (int j = 0; j < G; ++j)
+        if (16 * j + 4 * q < C) *reinterpret_cast<h4*>(to + 16 * j) = h4{0, 0, 0, 0};
+      return;
+    }
+    const int ih0 = 2 * r - g.pt;
+    u32x4 v = w.v, ninth = {(unsigned)w.n[0] | (unsigned)w.n[1] << 16, w.n[2], 0, 0};
+    if (edge) {
+      const unsigned at = at8 + (unsigned)(ih0 * row_bytes);
+      if (at8 != kNone && (int)at > (int)last) v = shift_down<half_t>(v, min((at - last) / 2, 8u));
+      const u32x4 moved = {0, v[0] << 16, __builtin_amdgcn_alignbit(v[1], v[0], 16), __builtin_amdgcn_alignbit(v[2], v[1], 16)};
+      v = left ? moved : v & first_elements<half_t>(inside);
+    }
+    if (ih0 < 0 || ih0 + 3 > g.IH) {  // a row outside the image
+      if (ih0 + q < 0 || ih0 + q >= g.IH) v = u32x4{0, 0, 0, 0};
+      if (ih0 < 0) ninth[0] &= 0xffff0000u;
+      if (ih0 + 2 >= g.IH) ninth[1] = 0;
+      if (ih0 + 1 >= g.IH) ninth[0] &= 0xffffu;
+    }
+    const h8 xv = __builtin_bit_cast(h8, q == 3 ? ninth : v);
+    f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+    for (int j = 0; j < G; ++j)
+      acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(stem_w[j][lane], xv, *reinterpret_cast<const f32x4*>(stem_bias + 16 * j + 4 * q), 0, 0, 0);
+    h8 o[1];
+    activate_and_pack(acc, clamp, o);
+    if (ow >= g.OW) o[0] = h8{0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+    for (int j = 0; j < G; ++j)
+      if (16 * j + 4 * q < C) *reinterpret_cast<h4*>(to + 16 * j) = h4{o[0][4 * j], o[0][4 * j + 1], o[0][4 * j + 2], o[0][4 * j + 3]};
+  };
+
+  // Loads and stores are counted in one order: the window of the next step is requested before this step's stores, so that
+  // waiting for it waits for no store but those of the step before.
+  Window w[3];
+#pragma unroll
+  for (int i = 0; i < 3; ++i) fetch(r0 - 1 + i, w[i]);
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < 3; ++i) stem(r0 - 1 + i, w[i]);
+  Window& next = w[0];
+  if (r0 + 1 < r1) fetch(r0 + 2, next);
+  __syncthreads();
+  const __amdgpu_buffer_rsrc_t yr = __builtin_amdgcn_make_buffer_rsrc(g.y, 0, (int)g.y_bytes, 0x00020000);
+  unsigned out = ow < g.OW ? 2u * ((unsigned)((n * g.OH + r0) * g.OW + ow) * N) : kNone;  // past the end: not stored
+  for (int r = r0; r < r1; ++r, out += 2u * g.OW * N) {
+    if (r + 1 < r1) stem(r + 2, next);
+    if (r + 2 < r1) fetch(r + 3, next);
+    f32x4 d[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+    for (int u = 0; u < G; ++u) d[u] = *reinterpret_cast<const f32x4*>(dw_bias + 16 * u + 4 * q);
+#pragma unroll
+    for (int i = 0; i < 5; ++i) {
+      // taps 2 i and 2 i + 1 (of the ninth, whose partner has zeros: itself)
+      const int t0 = 2 * i, t1 = i < 4 ? t0 + 1 : t0;
+      const int at0 = ((r + t0 / 3 + 3) & 3) * slot + t0 % 3 * PX, at1 = ((r + t1 / 3 + 3) & 3) * slot + t1 % 3 * PX;
+      const half_t* const tap = ring + (ow * PX + 8 * (q % 2)) + (q < 2 ? at0 : at1);
+#pragma unroll
+      for (int u = 0; u < G; ++u)
+        d[u] = __builtin_amdgcn_mfma_f32_16x16x32_f16(dww[i][u], *reinterpret_cast<const h8*>(tap + (2 * u + 1 < Q ? 16 * u : 16 * u - 8 * (q % 2))), d[u], 0, 0, 0);
+    }
+    h8 a[1];
+    activate_and_pack(d, clamp, a);
+    f32x4 acc[NB];
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+      acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(pw[j], a[0], *reinterpret_cast<const f32x4*>(pw_bias + 16 * j + 4 * q), 0, 0, 0);
+    if constexpr (NB >= 2) {
+      constexpr int PAIRS = NB / 2;
+      f32x4 pairs[2 * PAIRS];
+#pragma unroll
+      for (int j = 0; j < 2 * PAIRS; ++j) pairs[j] = acc[j];
+      h8 o[PAIRS];
+      activate_and_pack(pairs, clamp, o);
+#pragma unroll
+      for (int m = 0; m < PAIRS; ++m)
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, o[m]), yr, out + 64 * m + 16 * q, 0, 0);
+    }
+    if constexpr (NB % 2 == 1) {
+      typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+      h4 o;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o[e] = (half_t)apply_act(acc[NB - 1][e], clamp);
+      __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, o), yr, out + 32 * (NB - 1) + 8 * q, 0, 0);
+    }
+    __syncthreads();
+  }
+}
+
+template <int Q>
+int launch_rows(const RowsArgs& args, int batch, hipStream_t stream) {
+  const int tiles = (args.OW + 15) / 16;
+  const size_t lds_bytes = (size_t)4 * (16 * tiles + 2) * 8 * rows_pixel_pieces<Q>() * sizeof(half_t);
+  hipLaunchKernelGGL(stem_block_rows_f16_kernel<Q>, dim3((unsigned)(batch * args.strips)), dim3(64u * tiles), lds_bytes, stream, args);
+  return check_launch();
+}
+
+}  // namespace
+
+int launch_stem_block_rows_f16(const uint16_t* image, const uint16_t* st_w, const uint16_t* st_b, const uint16_t* dw_w,
+                               const uint16_t* dw_b, const uint16_t* pw_w, const uint16_t* pw_b, uint16_t* y, int batch, int ih, int iw,
+                               int oh, int ow, int pt, int pl, int q, hipStream_t stream) {
+  auto p = [](const uint16_t* v) { return reinterpret_cast<const half_t*>(v); };
+  const long long in = (long long)ih * iw * 3, out = (long long)oh * ow * 16 * q;  // halfs of an image
+  if (ow > 128 || iw < 3 || ih < 3 || reinterpret_cast<uintptr_t>(y) % 16 != 0) return TFX_ERR_UNSUPPORTED;
+  const int tiles = (ow + 15) / 16, slots = 256 * (16 / tiles);
+  // byte offsets of a launch stay below 2^31
+  const long long most = ((1ll << 30) - 1) / (in > out ? in : out);
+  for (long long first = 0; first < batch; first += most) {
+    const int images = (int)(batch - first < most ? batch - first : most);
+    // Strips of an image: rounds of resident workgroups (16 wavefronts a CU) times their rows, and five more for the two rows
+    // computed twice and for start and end.  224 x 224, one image: 112 strips 6.4 us, 56 7.5; 8: 28 or 56 11.4, 16 14.1; 16: 28 or
+    // 16 15.7, 56 19.0; 64: 8 31.1, 16 34.7, 4 37.7.
+    int strips = 1;
+    double best = 1e30;
+    for (int s = 1; s <= oh; ++s) {
+      const int rows = (oh + s - 1) / s;
+      if ((oh + rows - 1) / rows != s) continue;
+      const double cost = (double)(((long long)images * s + slots - 1) / slots) * (rows + 5);
+      if (cost < best) best = cost, strips = s;
+    }
+    const RowsArgs g{p(image) + first * in, p(st_w), p(st_b), p(dw_w), p(dw_b), p(pw_w), p(pw_b), reinterpret_cast<half_t*>(y) + first * out,
+                     ih, iw, oh, ow, pt, pl, strips, (oh + strips - 1) / strips, in, images * in, (unsigned)(2 * images * out)};
+    int rc = TFX_ERR_UNSUPPORTED;
+    if (q == 1) rc = launch_rows<1>(g, images, stream);
+    if (q == 2) rc = launch_rows<2>(g, images, stream);
+    if (q == 3) rc = launch_rows<3>(g, images, stream);
+    if (q == 4) rc = launch_rows<4>(g, images, stream);
+    if (rc) return rc;
+  }
+  return TFX_OK;
+}
+
+}  // namespace tfx

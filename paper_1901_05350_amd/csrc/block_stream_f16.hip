@@ -298,13 +298,13 @@ int launch_cfg(const half_t* x, const half_t* dw_w, const half_t* dw_b, const ha
 
 }  // namespace
 
-// Blocks 1 - 4 (channels -> filters, stride) of the full-width network, many output pixels,
+// Blocks 2 - 4 (channels -> filters, stride) of the full-width network, many output pixels,
 // 16-byte aligned operands, an input below 2^31 bytes.
 bool separable_stream_f16_supported(int batch, int h, int w, int c, int n, int stride, int oh, int ow, const void* x,
                                     const void* dw_w, const void* dw_b, const void* pw_w, const void* pw_b,
                                     const void* y) {
   const bool shape = (c == 128 && n == 128 && stride == 1) || (c == 64 && n == 128 && stride == 2) ||
-                     (c == 32 && n == 64 && stride == 1) || (c == 128 && n == 256 && stride == 2);
+                     (c == 128 && n == 256 && stride == 2);
   const void* ptrs[] = {x, dw_w, dw_b, pw_w, pw_b, y};
   bool aligned = true;
   for (const void* p : ptrs) aligned = aligned && reinterpret_cast<uintptr_t>(p) % 16 == 0;
@@ -323,7 +323,7 @@ int launch_separable_stream_f16(const uint16_t* x16, const uint16_t* dw_w16, con
   const half_t* pw_w = reinterpret_cast<const half_t*>(pw_w16);
   const half_t* pw_b = reinterpret_cast<const half_t*>(pw_b16);
   half_t* y = reinterpret_cast<half_t*>(y16);
-  const int ph = (c == 128 && n == 256 && stride == 2) ? patch_rows<128, 256, 2>() : patch_rows<32, 64, 1>();
+  const int ph = (c == 128 && n == 256 && stride == 2) ? patch_rows<128, 256, 2>() : patch_rows<64, 128, 2>();
   const WindowBlockGeom16 g{h, w, oh, ow, pt, pl, (ow + kPatchW - 1) / kPatchW, (oh + ph - 1) / ph,
                             (unsigned)((long long)batch * h * w * c * 2)};
   const long long units = (long long)batch * g.tiles_c * g.tiles_r;
@@ -333,7 +333,6 @@ int launch_separable_stream_f16(const uint16_t* x16, const uint16_t* dw_w16, con
     return launch_cfg<C, NN, SS>(x, dw_w, dw_b, pw_w, pw_b, y, g, (int)units, dw_act, pw_act, stream);
   TFX_WINDOW_BLOCK16(128, 128, 1)
   TFX_WINDOW_BLOCK16(64, 128, 2)
-  TFX_WINDOW_BLOCK16(32, 64, 1)
   TFX_WINDOW_BLOCK16(128, 256, 2)
 #undef TFX_WINDOW_BLOCK16
   return TFX_ERR_UNSUPPORTED;

@@ -357,6 +357,12 @@ int launch_separable_patch_f16(const uint16_t* x, const uint16_t* dw_w, const ui
                                const uint16_t* pw_b, uint16_t* y, int batch, int h, int w, int c, int n, int oh, int ow,
                                int stride, int pt, int pl, int dw_act, int pw_act, hipStream_t stream);
 
+// The stem and the first block of the network of width q / 4 in one launch (block_rows_f16.hip), activations relu6: images of
+// up to 256 columns, y 16-byte aligned.
+int launch_stem_block_rows_f16(const uint16_t* image, const uint16_t* st_w, const uint16_t* st_b, const uint16_t* dw_w,
+                               const uint16_t* dw_b, const uint16_t* pw_w, const uint16_t* pw_b, uint16_t* y, int batch, int ih, int iw,
+                               int oh, int ow, int pt, int pl, int q, hipStream_t stream);
+
 inline int check_launch() { return hipGetLastError() == hipSuccess ? TFX_OK : TFX_ERR_LAUNCH; }
 
 // A kernel that uses more than 64 KB of dynamic LDS has to be allowed to, once per device (the attribute

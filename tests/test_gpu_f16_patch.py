@@ -25,3 +25,25 @@ def test_patch_blocks(q, size, batch, blocks):
         keep = ~np.isnan(ref).any(axis=-1)
         if keep.any():
             end_to_end_bar(got[keep], ref[keep], "block %d" % k, 4 if k <= 5 else 8)
+
+
+@pytest.mark.parametrize("q,size,batch", [(4, 224, 1), (4, 131, 3), (3, 97, 2), (2, 256, 5), (1, 33, 2), (4, 64, 40), (1, 32, 700)])
+def test_stem_and_first_block(q, size, batch):
+    """block_rows_f16.hip against the oracle, image by image: strips of one row and of many, even and odd padding, ragged column
+    tiles, an image that ends with the buffer; a NaN's and an infinity's positions."""
+    import paper_1901_05350_amd as tfx
+    images = min(batch, 5)
+    d = inputs.mobilenet_v1_f16(seed=90 + q, batch=images, image_size=size, width_quarters=q, classes=10)
+    d["image"][images - 1, size - 1, size - 1, 2] = np.nan
+    d["image"][0, 0, 0, 0] = np.inf
+    d["image"][0, 9, size - 1, 1] = -np.inf
+    d["image"] = np.concatenate([d["image"]] * (batch // images))
+    _, _, acts = oracle.mobilenet_v1_forward_f16(d["image"][:images], d["weights"], return_activations=True)
+    model = tfx.MobileNetV1F16(d["weights"], batch=batch, image_size=size, width_quarters=q)
+    got, ref = host(model.features(dev16(d["image"]), 1)), acts[2]
+    assert np.array_equal(got.view(np.uint16).reshape(-1, images, *ref.shape[1:]).min(axis=0), got[:images].view(np.uint16))
+    got = got[:images]
+    assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.isnan(ref).any()
+    keep = ~np.isnan(ref).any(axis=-1)
+    end_to_end_bar(got[keep], ref[keep], "stem and block 1", 4)
+    assert (got[keep] != ref[keep]).mean() <= 0.005  # layers that round once: the last bit, now and then
