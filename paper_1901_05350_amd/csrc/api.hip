@@ -527,11 +527,11 @@ int forward_impl(const tfx_mobilenet_v1_variant* variant, const float* input, in
   int rc;
   int first_block = 0;
   const int64_t c0 = kChannels[0] * q / 4;
-  if (kStrides[0] == 1 &&
+  if (batch == 1 &&
       stem_block_supported(batch, (int)shape[1], (int)shape[2], (int)f0[3], (int)c0, input, weights->conv0_w,
                            weights->conv0_b, weights->dw_w[0], weights->dw_b[0], weights->pw_w[0], weights->pw_b[0],
                            end_block == 1 ? features : buf[0])) {
-    // batch 1 to 3: stem and first block in one launch (block.hip); it also clears the chain's task flags
+    // one image: stem and first block in one launch of patches (block.hip), which also clears the chain's task flags
     rc = launch_stem_block(input, weights->conv0_w, weights->conv0_b, weights->dw_w[0], weights->dw_b[0],
                            weights->pw_w[0], weights->pw_b[0], end_block == 1 ? features : buf[0], (int)batch, (int)shape[1],
                            (int)shape[2], (int)g.out[1],
@@ -545,9 +545,13 @@ int forward_impl(const tfx_mobilenet_v1_variant* variant, const float* input, in
                             (int)f0[3], (int)g.out[1], (int)g.out[2], 2, 2, (int)g.pad[0], (int)g.pad[2], TFX_ACT_RELU6,
                             static_cast<hipStream_t>(stream), static_cast<int*>(chain_ws),
                             chain_flag_words((int)variant->image_size, (int)variant->classes, q), chain_flag_stride());
-  else
-    rc = tfx_conv2d(input, shape, weights->conv0_w, f0, weights->conv0_b, 2, 2, TFX_PAD_SAME, TFX_ACT_RELU6, buf[0],
-                    stream);
+  else {
+    // stem and first block in one launch that walks down rows (block_rows.hip)
+    rc = launch_stem_block_rows(input, weights->conv0_w, weights->conv0_b, weights->dw_w[0], weights->dw_b[0], weights->pw_w[0],
+                                weights->pw_b[0], end_block == 1 ? features : buf[0], (int)batch, (int)shape[1], (int)shape[2],
+                                (int)g.out[1], (int)g.out[2], (int)g.pad[0], (int)g.pad[2], q, static_cast<hipStream_t>(stream));
+    first_block = 1;
+  }
   if (rc) return rc;
   for (int i = 0; i < 4; ++i) shape[i] = g.out[i];
   if (first_block == 1) shape[3] = c0;

@@ -272,12 +272,11 @@ int launch_cfg(const float* x, const float* dw_w, const float* dw_b, const float
 
 }  // namespace
 
-// Blocks (channels -> filters, stride) of the full-width network's 112 x 112 and 56 x 56 maps, many output pixels
+// Blocks (channels -> filters, stride) of the full-width network's 56 x 56 maps, many output pixels
 // (below that the two single-op kernels' tiles win), 16-byte aligned operands, an input below 2^31 bytes.
 bool separable_stream_supported(int batch, int h, int w, int c, int n, int stride, int oh, int ow, const void* x,
                                 const void* dw_w, const void* dw_b, const void* pw_w, const void* pw_b, const void* y) {
-  const bool shape = (c == 128 && n == 128 && stride == 1) || (c == 64 && n == 128 && stride == 2) ||
-                     (c == 32 && n == 64 && stride == 1);
+  const bool shape = (c == 128 && n == 128 && stride == 1) || (c == 64 && n == 128 && stride == 2);
   const void* ptrs[] = {x, dw_w, dw_b, pw_w, pw_b, y};
   bool aligned = true;
   for (const void* p : ptrs) aligned = aligned && reinterpret_cast<uintptr_t>(p) % 16 == 0;
@@ -297,7 +296,6 @@ int launch_separable_stream(const float* x, const float* dw_w, const float* dw_b
     return launch_cfg<C, NN, SS>(x, dw_w, dw_b, pw_w, pw_b, y, g, (int)units, dw_act, pw_act, stream);
   TFX_WINDOW_BLOCK(128, 128, 1)
   TFX_WINDOW_BLOCK(64, 128, 2)
-  TFX_WINDOW_BLOCK(32, 64, 1)
 #undef TFX_WINDOW_BLOCK
   return TFX_ERR_UNSUPPORTED;
 }

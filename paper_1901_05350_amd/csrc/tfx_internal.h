@@ -363,6 +363,11 @@ int launch_stem_block_rows_f16(const uint16_t* image, const uint16_t* st_w, cons
                                const uint16_t* dw_b, const uint16_t* pw_w, const uint16_t* pw_b, uint16_t* y, int batch, int ih, int iw,
                                int oh, int ow, int pt, int pl, int q, hipStream_t stream);
 
+// The same in fp32 (block_rows.hip).
+int launch_stem_block_rows(const float* image, const float* st_w, const float* st_b, const float* dw_w, const float* dw_b, const float* pw_w,
+                           const float* pw_b, float* y, int batch, int ih, int iw, int oh, int ow, int pt, int pl, int q,
+                           hipStream_t stream);
+
 inline int check_launch() { return hipGetLastError() == hipSuccess ? TFX_OK : TFX_ERR_LAUNCH; }
 
 // A kernel that uses more than 64 KB of dynamic LDS has to be allowed to, once per device (the attribute
