@@ -177,6 +177,12 @@ bool conv2d_gemm_supported(long long x_elems, int fh, int fw, int ci, int co);
 int launch_conv2d_gemm(const float* x, const float* w, const float* bias, float* y, int n, int h, int wd, int ci, int fh,
                        int fw, int co, int oh, int ow, int sh, int sw, int pt, int pl, int act, hipStream_t stream);
 
+// conv2d in fp32 with the input under a tile split once in LDS (conv_window.hip): the form that launch_conv2d_window takes and
+// its modelled time, or 0 where there is none.
+int conv2d_window_form(int n, int h, int wd, int ci, int fh, int fw, int co, int oh, int ow, int sh, int sw, double* us);
+int launch_conv2d_window(const float* x, const float* w, const float* bias, float* y, int n, int h, int wd, int ci, int fh, int fw,
+                         int co, int oh, int ow, int sh, int sw, int pt, int pl, int act, hipStream_t stream, int form);
+
 // Filter-stationary pointwise conv for thin filters (K*N*4 <= 128 KB) and large M.
 bool pointwise_stream_supported(int m, int k, int n, const void* x, const void* w, const void* bias, const void* y);
 int launch_pointwise_stream(const float* x, const float* w, const float* bias, float* y, int m, int k, int n, int act,
