@@ -15,6 +15,7 @@
 // bytes at a time at any alignment (ragged.h); the others element by element along k, TN adjacent columns per load.
 // A convolution's k runs over (tap, channel) with the channels of a tap padded to a multiple of PER, so that a chunk
 // never crosses a tap and any channel count works; padding and taps outside the image are zeros.
+#include "kernel_cost.h"
 #include "ragged.h"
 
 namespace tfx {
@@ -213,18 +214,22 @@ int launch(DeepArgs& g, int batch, hipStream_t stream) {
   if (total > 0x7fffffffLL) return TFX_ERR_UNSUPPORTED;
   g.total_blocks = (int)total;
   g.m_fastest = g.N > g.M ? 1 : 0;
-  // wavefronts enough that each has at most a few steps: one or two rounds of loads
-  if (g.steps <= 8) hipLaunchKernelGGL((gemm_deep_kernel<T, A_SRC, B_KC, TN, 4, 2>), dim3((unsigned)total), dim3(256), 0, stream, g);
+  // wavefronts enough that each has at most a few steps, loaded in one or two rounds; no more loads in a round than there are
+  // steps, since those past the contraction are issued too (halfs, k = 257 ... 512: 4.5 us with 8 x 4, 4.0 with 8 x 2 on
+  // average; 794 x 272 x 24 3.9 and 3.2; floats, 280 x 144 x 16 3.8 and 3.0; up to 4 steps 4 x 2 against 4 x 1 is 3 - 4 %).
+  // With 8 x 1 for 5 - 8 steps and 16 x 2 for 17 - 32 more wavefronts are started for the same loads: 4 % slower, and no change.
+  if (g.steps <= 4) hipLaunchKernelGGL((gemm_deep_kernel<T, A_SRC, B_KC, TN, 4, 1>), dim3((unsigned)total), dim3(256), 0, stream, g);
+  else if (g.steps <= 8) hipLaunchKernelGGL((gemm_deep_kernel<T, A_SRC, B_KC, TN, 4, 2>), dim3((unsigned)total), dim3(256), 0, stream, g);
+  else if (g.steps <= 16) hipLaunchKernelGGL((gemm_deep_kernel<T, A_SRC, B_KC, TN, 8, 2>), dim3((unsigned)total), dim3(512), 0, stream, g);
   else if (g.steps <= 32) hipLaunchKernelGGL((gemm_deep_kernel<T, A_SRC, B_KC, TN, 8, 4>), dim3((unsigned)total), dim3(512), 0, stream, g);
   else hipLaunchKernelGGL((gemm_deep_kernel<T, A_SRC, B_KC, TN, 16, 4>), dim3((unsigned)total), dim3(1024), 0, stream, g);
   return check_launch();
 }
 
-// two column blocks per workgroup once that still leaves a workgroup for most CUs
 template <typename T, Source A_SRC, bool B_KC>
 int launch_width(DeepArgs& g, int batch, hipStream_t stream) {
-  const long long wide = (long long)batch * ((g.M + 15) / 16) * ((g.N + 31) / 32);
-  return g.N % 2 == 0 && wide >= 160 ? launch<T, A_SRC, B_KC, 2>(g, batch, stream) : launch<T, A_SRC, B_KC, 1>(g, batch, stream);
+  return deep_two_columns((long long)batch * ((g.M + 15) / 16), g.N, g.steps) ? launch<T, A_SRC, B_KC, 2>(g, batch, stream)
+                                                                              : launch<T, A_SRC, B_KC, 1>(g, batch, stream);
 }
 
 template <typename T>

@@ -38,10 +38,17 @@ struct KernelCost {
   }
 };
 
-// gemm_deep.hip on floats, k < 128: 16 x 32 tiles once 160 of them are there, else 16 x 16.
+// gemm_deep.hip: two column blocks per workgroup once single ones are more than one for each CU, where a few CUs would have
+// two and the rest wait (halfs: 137 x 1376 x 520, 297 or 153 workgroups, 8.9 and 6.0 us; 376 x 3504 x 168 15.2 and 9.1); a
+// few more of those of 4 wavefronts, up to 8 k-steps, run side by side (floats, 128 x 120 x 600, 304 or 152: 3.1 and 3.3).
+inline bool deep_two_columns(long long rows, long long n, int steps) {
+  return n % 2 == 0 && n > 16 && rows * ((n + 15) / 16) > (steps <= 8 ? 320 : 256);
+}
+
+// gemm_deep.hip on floats, k < 128.
 inline double shallow_deep_us(long long batch, long long m, long long n, int k) {
   const long long rows = batch * ((m + 15) / 16), wide = rows * ((n + 31) / 32);
-  const bool two = n % 2 == 0 && wide >= 160;
+  const bool two = deep_two_columns(rows, n, (k + 15) / 16);
   const double c = (double)(two ? wide : rows * ((n + 15) / 16)) / 256.;
   return 3.09 + .0025 * k + (c > 1. ? c : 1.) * (two ? .299 + .0029 * k : .208 + .0017 * k);
 }
