@@ -44,6 +44,29 @@ __global__ __launch_bounds__(256) void gemm_tiny_f16_kernel(const half_t* __rest
   C[e] = (half_t)apply_act(sum + (bias != nullptr ? (float)bias[col] : 0.f), act);
 }
 
+// A slice of an operand in LDS: K-contiguous rows of kLd halfs, or (stored [K,N] or [K,M]) its 64 k-rows, each `rows` halfs and
+// kPad, which puts the four k-rows of a transposing load on different banks.
+constexpr int kPad = 32;
+constexpr int tile_halfs(bool kc, int rows) { return kc ? rows * kLd : kBK * (rows + kPad); }
+
+// Fragment of 32 rows (columns) x 16 k, from where lane 0's starts: lane (li, hh) gets 8 consecutive k from 8 hh on of row li.
+// The transposing load gives lane i of 16 the four halfs at place i % 4 of the 8-byte pieces that lanes i / 4, i / 4 + 4, ... of
+// the 16 point to: with piece l at k-row l / 4 and columns 4 (l % 4), four k of column i.
+template <bool KC, int ROWS>
+__device__ __forceinline__ int first_fragment(int row0, int lane) {
+  if constexpr (KC) return (row0 + lane % 32) * kLd + 8 * (lane / 32);
+  return (8 * (lane / 32) + lane % 16 / 4) * (ROWS + kPad) + row0 + 16 * (lane / 16 % 2) + 4 * (lane % 4);
+}
+template <bool KC, int ROWS>
+__device__ __forceinline__ h8 fragment(const half_t* first, int block, int step) {
+  if constexpr (KC) return *reinterpret_cast<const h8*>(first + 32 * block * kLd + 16 * step);
+  typedef short s4 __attribute__((ext_vector_type(4)));
+  typedef __attribute__((address_space(3))) s4 lds_s4;
+  const half_t* const p = first + 32 * block + 16 * step * (ROWS + kPad);
+  const s4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4*)(p)), hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4*)(p + 4 * (ROWS + kPad)));
+  return __builtin_bit_cast(h8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
 // Software-pipelined tile kernel.  The vector memory
 // path delivers 64 bytes per clock to a CU, so a k-slice's global loads take a large part of the
 // slice's MFMA time and must be spread evenly through it; the same holds for the LDS writes.
@@ -55,7 +78,7 @@ __global__ __launch_bounds__(256) void gemm_tiny_f16_kernel(const half_t* __rest
 // Alignment and remainders cost nothing in that loop: the 16-byte loads and stores work at any address (rows that start
 // at an odd half cost 5 - 20 % of the kernel's time, 4-byte aligned ones nothing), and only slices that reach past K,
 // or hold a [K,N] operand's last row when N % 8 != 0, go through the masked form.  (Fetched half by half,
-// 1999 x 1001 x 1023 took 42 us, now 17.)
+// 1999 x 1001 x 1023 took 42 us, now 12.5.)
 template <int WAVES_M, int WAVES_N, int TM, int TN, bool A_KC, bool B_KC>
 __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_f16_pipe_kernel(
     const half_t* __restrict__ A, const half_t* __restrict__ B, half_t* __restrict__ C, const half_t* __restrict__ bias,
@@ -64,12 +87,10 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_f16_pipe_kernel(
   constexpr int kNT = 64 * WAVES_M * WAVES_N;
   constexpr int WM = 32 * TM, WN = 32 * TN;
   constexpr int BM = WM * WAVES_M, BN = WN * WAVES_N;
-  constexpr int kTileA = BM * kLd, kTileB = BN * kLd;
+  constexpr int kTileA = tile_halfs(A_KC, BM), kTileB = tile_halfs(B_KC, BN);
   constexpr int SA = BM * 8 / kNT, SB = BN * 8 / kNT, SLOTS = SA + SB;  // 16-byte slots per thread and slice
   constexpr int STEPS = kBK / 16, MF = TM * TN;  // k-steps per slice, MFMAs per step
   static_assert(BM * 8 % kNT == 0 && BN * 8 % kNT == 0, "loader shape");
-  static_assert(B_KC || (SB == 4 && kNT / 16 == BN / 8), "the [K,N] loader moves 4 k-rows x 8 columns per thread");
-  static_assert(A_KC || (SA == 4 && kNT / 16 == BM / 8), "and so does the [K,M] loader");
   extern __shared__ __align__(16) half_t smem_h[];
   half_t* const lds_a = smem_h;
   half_t* const lds_b = smem_h + 2 * kTileA;
@@ -111,20 +132,21 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_f16_pipe_kernel(
   // clamped to the last one, so every load is unconditional and in bounds; halfs past K are zeroed
   // with a mask.  The loop body therefore has no branch.
   //
-  // An operand stored [K,N] or [K,M]: thread (kq, nb) loads k-rows 4 kq ... + 3 of columns 8 nb ... + 7 as four 16-byte
-  // slots, four lanes side by side in a row, transposes the 4 x 8 block in registers and writes, for each of the 8
-  // columns, 4 consecutive k to the K-contiguous LDS row of that column.  The block is written when its first slot comes
-  // up in the schedule, its slots are refilled one by one.  With a row for each of 16 lanes the 8-byte LDS writes would
-  // be contiguous, but L1 looks a line up once per 16 lanes and row, and the look-ups were what the kernel waited for
-  // (1999 x 1001 x 1023: 6.0 million, 23.6 us; now 17.2.  4096^3 in 128 x 128 tiles 180 us, now 160).
+  // An operand stored [K,N] or [K,M] keeps its k-rows in LDS: slot i covers row (tid + i * kNT) / (BN / 8), 16 bytes of it, and the
+  // fragments are read with the transposing LDS load.  (Turned in registers, 4 k-rows x 8 columns a thread, into the
+  // K-contiguous form, its 8-byte LDS writes, two to a bank, were what the kernel waited for: 2048 x 1024 x 1024 14.0 us,
+  // now 10.6; 4096 x 2048 x 512 23.3 and 17.7.)
   const int srow = tid / 8, scol = 8 * (tid % 8);
   constexpr int kRowStep = kNT / 8;
   typedef ragged_u32x4 u32x4;
   u32x4 reg[SLOTS];
   unsigned boff[SLOTS];  // byte offset of the slot at k0 = 0 from its operand's base (operands hold < 2^31 elements)
-  const int kq = tid / 4 % 16, nb = tid / 64 * 4 + tid % 4;
-  // past the matrix: any valid column block
-  const unsigned acol = m0 + 8 * nb < M ? (unsigned)(m0 + 8 * nb) : 0u, bcol = n0 + 8 * nb < N ? (unsigned)(n0 + 8 * nb) : 0u;
+  // row of slot i of such an operand, and its columns (past the matrix: any valid ones)
+  auto krow = [&](bool is_a, int i) { return (tid + i * kNT) / ((is_a ? BM : BN) / 8); };
+  auto kcol = [&](bool is_a, int i) {
+    const int c = 8 * ((tid + i * kNT) % ((is_a ? BM : BN) / 8));
+    return is_a ? (m0 + c < M ? (unsigned)(m0 + c) : 0u) : (n0 + c < N ? (unsigned)(n0 + c) : 0u);
+  };
 #pragma unroll
   for (int w = 0; w < SLOTS; ++w) {
     const bool is_a = w < SA;
@@ -133,7 +155,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_f16_pipe_kernel(
       const int row = min((is_a ? m0 : n0) + srow + i * kRowStep, (is_a ? M : N) - 1);
       boff[w] = 2u * ((unsigned)row * (unsigned)K + (unsigned)scol);
     } else {
-      boff[w] = 2u * ((unsigned)(4 * kq + i) * (unsigned)(is_a ? M : N) + (is_a ? acol : bcol));
+      boff[w] = 2u * ((unsigned)krow(is_a, i) * (unsigned)(is_a ? M : N) + kcol(is_a, i));
     }
   }
   const int nk = (K + kBK - 1) / kBK;
@@ -146,8 +168,8 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_f16_pipe_kernel(
     if (is_a ? A_KC : B_KC) {
       off = boff[w] / 2u + (k0 + scol < K ? (unsigned)k0 : 0u - (unsigned)scol);
     } else {
-      const int k = k0 + 4 * kq + (is_a ? w : w - SA);
-      off = (k < K ? (unsigned)k : 0u) * (unsigned)(is_a ? M : N) + (is_a ? acol : bcol);
+      const int i = is_a ? w : w - SA, k = k0 + krow(is_a, i);
+      off = (k < K ? (unsigned)k : 0u) * (unsigned)(is_a ? M : N) + kcol(is_a, i);
     }
     const unsigned at = min(off, (unsigned)(is_a ? strideA : strideB) - 8u);
     *early = off - at;
@@ -182,19 +204,11 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_f16_pipe_kernel(
     if (is_a ? A_KC : B_KC) {
       *reinterpret_cast<u32x4*>(l + (srow + i * kRowStep) * kLd + scol) =
           FULL ? reg[w] : settled(w, k0) & first_elements<half_t>(K - (k0 + scol));
-    } else if (i == 0) {
-      h8 r[4];
-#pragma unroll
-      for (int kk = 0; kk < 4; ++kk) {
-        const unsigned mask = (FULL || k0 + 4 * kq + kk < K) ? 0xffffffffu : 0u;
-        r[kk] = __builtin_bit_cast(h8, FULL ? reg[w + kk] : settled(w + kk, k0) & mask);
-      }
-      half_t* const lt = l + (8 * nb) * kLd + 4 * kq;
-#pragma unroll
-      for (int c = 0; c < 8; ++c) {
-        const h4 o = {r[0][c], r[1][c], r[2][c], r[3][c]};
-        *reinterpret_cast<h4*>(lt + c * kLd) = o;
-      }
+    } else {
+      const int row = krow(is_a, i);
+      const unsigned mask = FULL || k0 + row < K ? 0xffffffffu : 0u;
+      *reinterpret_cast<u32x4*>(l + row * ((is_a ? BM : BN) + kPad) + 8 * ((tid + i * kNT) % ((is_a ? BM : BN) / 8))) =
+          FULL ? reg[w] : settled(w, k0) & mask;
     }
   };
   constexpr std::false_type kMasked{};
@@ -205,7 +219,6 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_f16_pipe_kernel(
 #pragma unroll
     for (int w = 0; w < SLOTS; ++w) {
       store_slot(w, 0, 0, full);
-      // (the block of a [K,N] operand is stored when its first slot comes up: refill only behind that)
       load_slot(w, decltype(full)::value ? kBK : min(kBK, k_last), full);
     }
   };
@@ -218,20 +231,20 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_f16_pipe_kernel(
     const int cur = kt & 1;
     // the last two iterations refetch the last slice (unused)
     const int k_next = decltype(full)::value ? (kt + 2) * kBK : min((kt + 2) * kBK, k_last);
-    const half_t* la = lds_a + cur * kTileA + (wm0 + li) * kLd + 8 * hh;
-    const half_t* lb = lds_b + cur * kTileB + (wn0 + li) * kLd + 8 * hh;
+    const half_t* const la = lds_a + cur * kTileA + first_fragment<A_KC, BM>(wm0, lane);
+    const half_t* const lb = lds_b + cur * kTileB + first_fragment<B_KC, BN>(wn0, lane);
     h8 fa[2][TM], fb[2][TN];
 #pragma unroll
-    for (int i = 0; i < TM; ++i) fa[0][i] = *reinterpret_cast<const h8*>(la + 32 * i * kLd);
+    for (int i = 0; i < TM; ++i) fa[0][i] = fragment<A_KC, BM>(la, i, 0);
 #pragma unroll
-    for (int j = 0; j < TN; ++j) fb[0][j] = *reinterpret_cast<const h8*>(lb + 32 * j * kLd);
+    for (int j = 0; j < TN; ++j) fb[0][j] = fragment<B_KC, BN>(lb, j, 0);
 #pragma unroll
     for (int s = 0; s < STEPS; ++s) {
       if (s + 1 < STEPS) {
 #pragma unroll
-        for (int i = 0; i < TM; ++i) fa[(s + 1) & 1][i] = *reinterpret_cast<const h8*>(la + 32 * i * kLd + 16 * (s + 1));
+        for (int i = 0; i < TM; ++i) fa[(s + 1) & 1][i] = fragment<A_KC, BM>(la, i, s + 1);
 #pragma unroll
-        for (int j = 0; j < TN; ++j) fb[(s + 1) & 1][j] = *reinterpret_cast<const h8*>(lb + 32 * j * kLd + 16 * (s + 1));
+        for (int j = 0; j < TN; ++j) fb[(s + 1) & 1][j] = fragment<B_KC, BN>(lb, j, s + 1);
       }
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -264,7 +277,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_f16_pipe_kernel(
   // a time, at whatever address that is.
   const ActClamp clamp = make_act(act);
   constexpr int kLs = WN + 8;  // staging row stride in halfs
-  static_assert((size_t)WAVES_M * WAVES_N * WM * kLs <= 2 * (size_t)(BM + BN) * kLd, "staging fits in the slice buffers");
+  static_assert((size_t)WAVES_M * WAVES_N * WM * kLs <= 2 * (size_t)(kTileA + kTileB), "staging fits in the slice buffers");
   half_t* stage = smem_h + wave * WM * kLs;
 #pragma unroll
   for (int j = 0; j < TN; ++j) {
@@ -307,7 +320,7 @@ template <int WAVES_M, int WAVES_N, int TM, int TN, bool A_KC, bool B_KC>
 int launch_pipe(const half_t* a, const half_t* b, half_t* c, const half_t* bias, int batch, int m, int n, int k, int act,
                 hipStream_t stream) {
   constexpr int BM = 32 * TM * WAVES_M, BN = 32 * TN * WAVES_N, NT = 64 * WAVES_M * WAVES_N;
-  constexpr size_t lds_bytes = 2 * (size_t)(BM + BN) * kLd * sizeof(half_t);
+  constexpr size_t lds_bytes = 2 * (size_t)(tile_halfs(A_KC, BM) + tile_halfs(B_KC, BN)) * sizeof(half_t);
   static_assert(lds_bytes <= 160 * 1024, "LDS budget per workgroup");
   auto kern = gemm_f16_pipe_kernel<WAVES_M, WAVES_N, TM, TN, A_KC, B_KC>;
   static std::atomic<uint64_t> lds_allowed{0};
@@ -325,8 +338,7 @@ int launch_pipe(const half_t* a, const half_t* b, half_t* c, const half_t* bias,
   return check_launch();
 }
 
-// Small M x N (the 28x28 ... 7x7 pointwise layers of a batch-1 MobileNet: 49 ... 3136 rows): too few
-// 64 x 64 tiles for 256 CUs, and each tile is bound by memory latency, not by the matrix cores.
+// Small M x N: too few 64 x 64 tiles for 256 CUs, and each tile is bound by memory latency, not by the matrix cores.
 // 16 x 32 tiles (v_mfma_f32_16x16x32_f16), a tile as deep as K up to 512 so that the whole K panel is
 // in flight in one memory round trip, the depth split over 8 wavefronts whose partial tiles are
 // added through LDS by the 512 threads that also apply the epilogue.  A stored [M,K], B stored
@@ -453,6 +465,19 @@ int launch_small(const half_t* a, const half_t* b, half_t* c, const half_t* bias
   return check_launch();
 }
 
+// us = fixed + per_k k + c (per_tile + per_tile_k k) + per_output x 1e6 outputs, where c is 1 up to a tile for each of the 256 CUs
+// and then grows by `share` for a further tile of a CU, of which `round` counts as soon as any CU has it; `odd` operands cost the
+// loads `per_odd` of their share each.
+struct PipeCost {
+  int bm, bn;
+  double fixed, per_tile, per_tile_k, round, share, per_odd, per_output, per_k = 0.;
+  double us(long long batch, long long m, long long n, int k, int odd) const {
+    const double tiles = (double)(batch * ((m + bm - 1) / bm) * ((n + bn - 1) / bn)) / 256., up = (double)(long long)(tiles + .999999);
+    const double c = tiles <= 1. ? 1. : 1. + share * (round * up + (1. - round) * tiles - 1.);
+    return fixed + per_k * k + c * (per_tile + per_tile_k * k * (1. + per_odd * odd)) + per_output * 1e-6 * (double)(batch * m * n);
+  }
+};
+
 }  // namespace
 
 int launch_gemm_f16(const uint16_t* a16, const uint16_t* b16, uint16_t* c16, const uint16_t* bias16, int batch, int m,
@@ -467,69 +492,46 @@ int launch_gemm_f16(const uint16_t* a16, const uint16_t* b16, uint16_t* c16, con
                        a_kc ? 1 : 0, b_kc ? 1 : 0, total, act);
     return check_launch();
   }
-  auto tiles = [&](int bm, int bn) { return (long long)batch * ((m + bm - 1) / bm) * ((n + bn - 1) / bn); };
-  // a tile shape is acceptable if it wastes at most 20% more of its area on padding than 128 x 128 tiles do
-  auto fits = [&](int bm, int bn) {
-    const double pad = (double)((m + bm - 1) / bm * bm) * ((n + bn - 1) / bn * bn);
-    const double pad128 = (double)((m + 127) / 128 * 128) * ((n + 127) / 128 * 128);
-    return pad <= 1.2 * pad128;
-  };
-  // the pointwise-convolution layout, a thin or deep filter held in LDS, or small outputs
+  // the pointwise-convolution layout with a thin or deep filter held in LDS; short contractions
   if (batch == 1 && a_kc && !b_kc && pointwise_stream_f16_supported(m, k, n, a, b, c))
     return launch_pointwise_stream_f16(a16, b16, bias16, c16, m, k, n, act, stream);
   if (batch == 1 && a_kc && !b_kc && pointwise_slab_f16_supported(m, k, n, a, b, c))
     return launch_pointwise_slab_f16(a16, b16, bias16, c16, m, k, n, act, stream);
-  const bool aligned = reinterpret_cast<uintptr_t>(a) % 16 == 0 && reinterpret_cast<uintptr_t>(b) % 16 == 0;
-  if (a_kc && !b_kc && k % 8 == 0 && n % 8 == 0 && aligned && tiles(64, 64) < 128)
-    return launch_small(a, b, c, bias, batch, m, n, k, act, stream);
   if (batch == 1 && a_kc && thin_pays(m, n, k, true))
     return launch_gemm_thin_f16(a16, b16, c16, bias16, m, n, k, b_kc, act, stream);
-  // Fewer than three 128 x 128 tiles per four CUs: the contraction split over a workgroup's wavefronts, 16 x 32, 32 x 64 or
-  // 64 x 64 tiles at a time, or 64 x 64 tiles through LDS (kernel_cost.h; 1024^3: 12.3 us through LDS, 9.8 split).  Rows of
-  // an odd number of halfs along K halve what 16-byte loads deliver to a kernel that does not share them through LDS
-  // (2000 x 1000 x 1024 with B [N,K] 21 us, x 1023 53): none of the two larger ones then.
-  if (tiles(128, 128) < 192) {
-    const bool odd = k % 2 != 0 && (a_kc || b_kc);
-    const double deep = KernelCost{16, n % 2 == 0 ? 32 : 16, 3., 0., .165, .0017}.us(batch, m, n, k);
-    const double lds = a_kc && b_kc ? KernelCost{64, 64, 3.1, .0012, .55, .0027}.us(batch, m, n, k)
-                                    : KernelCost{64, 64, 3.3, .0012, 1.11, .0039}.us(batch, m, n, k);
-    const bool direct = !odd && n >= 2 && m >= 2;
-    const double us[2] = {direct ? KernelCost{64, 64, .86, 0., 2.64, .0052}.us(batch, m, n, k) : 1e30,
-                          direct ? KernelCost{32, 64, 2.75, .0018, .46, .0038}.us(batch, m, n, k) : 1e30};
-    const int form = us[0] <= us[1] ? 0 : 1;
-    if (deep <= us[form] && deep <= lds) return launch_gemm_deep_f16(a16, b16, c16, bias16, batch, m, n, k, a_kc, b_kc, act, stream);
-    if (us[form] <= lds) return launch_gemm_direct_f16(a16, b16, c16, bias16, batch, m, n, k, a_kc, b_kc, act, stream, form);
-  }
+
+  // Which kernel: the modelled time, fitted to 900 products (16 ... 4096 each way, batch 1 ... 32, every layout, half of the sizes of
+  // no multiple of 8; near the choice the rms error is 5 - 8 % for the tiles and the small kernel, 12 and 15 % for the two others
+  // that split the contraction).  Over these the choice costs 1.2 % on average against the fastest kernel of each, more than 25 %
+  // for ten of them (32 x 121 x 442, 26 of a batch: 5.2 us, 4.2 with the direct kernel).
+  const int k64 = (k + 63) / 64 * 64, k512 = (k + (k + 511) / 512 * 512) / 2;  // (the small kernel's slices are 512 deep)
+  // operands whose rows have an odd number of halfs; they halve what 16-byte loads deliver to a kernel that does not share them
+  // through LDS (2000 x 1000 x 1024 with B [N,K] 21 us, x 1023 53)
+  const int odd = (a_kc ? k : m) % 2 + (b_kc ? k : n) % 2;
+  const bool small = a_kc && !b_kc && k % 8 == 0 && n % 8 == 0 && reinterpret_cast<uintptr_t>(a) % 16 == 0 &&
+                     reinterpret_cast<uintptr_t>(b) % 16 == 0;
+  const bool direct = (k % 2 == 0 || !(a_kc || b_kc)) && n >= 2 && m >= 2;
+  enum { kDeep, kSmall, kDirect, k64x64, k64x128, k128x128, k256x256, kForms };
+  const int deep_n = deep_two_columns((long long)batch * ((m + 15) / 16), n, (k + 31) / 32) ? 32 : 16;
+  const double us[kForms] = {1.05 * PipeCost{16, deep_n, 2.75, .011, .0017, 1., 1.39, .49, 1.5}.us(batch, m, n, k, odd),
+                             small ? PipeCost{16, 32, 2.68, 0., .0019, .77, 1.07, 0., 1.5}.us(batch, m, n, k512, 0) : 1e30,
+                             direct ? PipeCost{32, 64, 2.28, .99, .0055, .32, .61, .19, .13}.us(batch, m, n, k, odd) : 1e30,
+                             PipeCost{64, 64, 3.73, .19, .0028, .78, 1.37, .27, .47, .0008}.us(batch, m, n, k64, odd),
+                             PipeCost{64, 128, 3.34, .53, .0050, .91, 1.14, .22, .52, .0002}.us(batch, m, n, k64, odd),
+                             PipeCost{128, 128, 4.20, .35, .0072, .91, 1.21, .20, .48}.us(batch, m, n, k64, odd),
+                             PipeCost{256, 256, 7.14, 1.41, .0150, .90, 2., .14, .45, .0040}.us(batch, m, n, k64, odd)};
+  int form = 0;
+  for (int f = 1; f < kForms; ++f)
+    if (us[f] < us[form]) form = f;
+  if (form == kSmall) return launch_small(a, b, c, bias, batch, m, n, k, act, stream);
+  if (form == kDeep) return launch_gemm_deep_f16(a16, b16, c16, bias16, batch, m, n, k, a_kc, b_kc, act, stream);
+  if (form == kDirect) return launch_gemm_direct_f16(a16, b16, c16, bias16, batch, m, n, k, a_kc, b_kc, act, stream, 1);
   auto pick = [&](auto akc, auto bkc) {
     constexpr bool A_KC = decltype(akc)::value, B_KC = decltype(bkc)::value;
-    // no large tiles whose last round over the CUs would be nearly empty (5 x 848 x 1544 x 720: 32 us with 260 tiles of
-    // 256 x 128, 21 with 128 x 128)
-    auto even = [&](int bm, int bn) {
-      const long long t = tiles(bm, bn);
-      return t <= 256 || t * 10 >= (t + 255) / 256 * 256 * 7;
-    };
-    // 256 x 256 tiles (8 wavefronts) once they fill half of the 256 CUs (3001^3: 144 tiles, 111 us against 159 with
-    // 128 x 128), then 256 x 128 (8 wavefronts), 128 x 128 (4 wavefronts, two workgroups per CU) from three per four CUs on
-    // (2000 x 1000 x 1024, 128 tiles: 12.6 us against 10.3 with 64 x 64), 64 x 64 below that.  With a long K, which pays
-    // back the longer start and end of a larger tile, 128 x 128 from fewer on (3428 x 694 x 1320, 162 tiles: 21.5 us
-    // against 24.2; 14 x 708 x 232 x 3992 with A [K,M], 168: 61.5 against 80).  Of an output of at most 64 rows or columns
-    // a larger tile wastes half (22 x 2070 x 20 x 992: 64 x 64 18.9 us, 256 x 128 23.7).
-    const bool narrow = m <= 64 || n <= 64;
-    if (!narrow && tiles(256, 256) >= 136 && fits(256, 256) && even(256, 256))
-      return launch_pipe<2, 4, 4, 2, A_KC, B_KC>(a, b, c, bias, batch, m, n, k, act, stream);
-    if constexpr (A_KC && B_KC)
-      if (!narrow && tiles(256, 128) >= 192 && fits(256, 128) && even(256, 128))
-        return launch_pipe<4, 2, 2, 2, A_KC, B_KC>(a, b, c, bias, batch, m, n, k, act, stream);
-    const long long t128 = tiles(128, 128), t64 = tiles(64, 64);
-    if (!narrow && (t128 >= 192 || (t128 >= 136 && k >= 1024 && 2 * t64 >= 7 * t128)))
-      return launch_pipe<2, 2, 2, 2, A_KC, B_KC>(a, b, c, bias, batch, m, n, k, act, stream);
-    // 64 x 128 where these are one round over the CUs and 64 x 64 would be two (1999 x 1001 x 1023: 15.3 us against 17.2;
-    // 21 x 202 x 220 x 653 with B [N,K]: 11.9 against 14.9)
-    if constexpr (A_KC)
-      if (k >= 256 && t64 > 256 && tiles(64, 128) <= 256 && 20 * tiles(64, 128) <= 11 * t64)
-        return launch_pipe<2, 2, 1, 2, A_KC, B_KC>(a, b, c, bias, batch, m, n, k, act, stream);
-    if constexpr (A_KC && B_KC) return launch_pipe<2, 2, 1, 1, A_KC, B_KC>(a, b, c, bias, batch, m, n, k, act, stream);
-    else return launch_pipe<2, 1, 1, 2, A_KC, B_KC>(a, b, c, bias, batch, m, n, k, act, stream);
+    if (form == k64x64) return launch_pipe<2, 2, 1, 1, A_KC, B_KC>(a, b, c, bias, batch, m, n, k, act, stream);
+    if (form == k64x128) return launch_pipe<2, 4, 1, 1, A_KC, B_KC>(a, b, c, bias, batch, m, n, k, act, stream);
+    if (form == k128x128) return launch_pipe<2, 4, 2, 1, A_KC, B_KC>(a, b, c, bias, batch, m, n, k, act, stream);
+    return launch_pipe<2, 4, 4, 2, A_KC, B_KC>(a, b, c, bias, batch, m, n, k, act, stream);
   };
   if (a_kc) return b_kc ? pick(std::true_type{}, std::true_type{}) : pick(std::true_type{}, std::false_type{});
   return b_kc ? pick(std::false_type{}, std::true_type{}) : pick(std::false_type{}, std::false_type{});
