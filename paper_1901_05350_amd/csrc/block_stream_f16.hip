@@ -1,28 +1,42 @@
 // A depthwise-separable block of the Section 3.9 network at large batch in one launch, on 16-bit float storage
 // (Section 4.1):  y = half(relu6(pointwise(half(relu6(depthwise3x3(x) + dw_b))) + pw_b)),  stride 1 or 2, SAME.
-// The fp32 kernel of block_stream.hip with the operand layout of pointwise_f16.hip: the pointwise filter is the
-// stationary operand in LDS (stream_f16.h), a unit is a 4 x 8 patch of output pixels of one image = two
-// v_mfma_f32_16x16x32_f16 slabs of 2 x 8 pixels (one slab, 2 x 8, for 128 -> 256 channels at stride 2, whose filter
-// leaves less room for windows; its 256 output channels take two passes over the operands), the wavefront copies the patch's input window, 64 or 32 channels
-// at a time, into its own piece of LDS, and lane (li, q) forms its operand of k-step s -- channels 32 s + 8 q ... + 7
-// of slab pixel (li / 8, li % 8) -- as the depthwise result of that pixel: 9 taps of 16 bytes from the window times
-// the depthwise filter (also in LDS), accumulated in fp32, clamped and rounded to binary16 exactly as the
-// depthwise kernel rounds what it stores.  The next channels of the window (and, before the MFMAs, the first ones
-// of the next unit) are on their way from memory into registers meanwhile.
+// The fp32 kernel of block_stream.hip with the operand layout of pointwise_f16.hip: the pointwise filter is the stationary
+// operand in LDS (stream_f16.h), a unit is a patch of 2 or 4 x 8 output pixels of one image = one or two
+// v_mfma_f32_16x16x32_f16 slabs of 2 x 8 pixels, and the wavefront copies the patch's input window, 32 or 64 channels at a
+// time, into its own piece of LDS.  The next channels of the window (and, before the pointwise layer, the first ones of the
+// next unit) are on their way from memory into registers meanwhile.
+//
+// The depthwise layer runs on the matrix cores, as products with diagonal matrices: two taps x 16 channels are the 32 of a
+// contraction, lane (li, q) supplying channels 8 (q % 2) ... + 7 of tap q / 2 of the pair at slab pixel (li / 8, li % 8); of the
+// filter, the other operand, each row has but its own two weights, a dword a lane in LDS.  It is accumulated in fp32, clamped and
+// rounded to binary16 as the depthwise kernel rounds what it stores, and comes as the pointwise product's operand: lane (li, q)
+// holds channels 4 q ... + 3 of the two groups of a k-step, in which order the filter is put into LDS.  A zero times a NaN is a
+// NaN in 15 other channels, but all channels of the pixel meet in every output of the pointwise layer, so the same outputs are
+// NaN; the map itself, behind a relu6, has no infinities.
+//
+// Bound by LDS and issue, with two or three wavefronts a SIMD: on the vector units a slab and 32 channels took 72 mixed multiply-
+// adds of 4.3 cycles and 18 reads of LDS, as products they take 10 of 16 cycles and 9 or 10 reads (and 10 dwords for all slabs).
+// 64 images: 56 x 56 x 128 -> 128 33.0 us -> 26.0 (102 MB, 20 us at the rate of a large copy), 112 x 112 x 64 -> 128 at stride 2
+// 37.3 -> 29.5 (154 MB, 30), 56 x 56 x 128 -> 256 at stride 2 21.7 -> 20.6 (77 MB, 15).
 #include "stream_f16.h"
-
-#include <type_traits>
 
 namespace tfx {
 namespace {
 
 using namespace f16s;
 
-constexpr int kThreads = 512, kWaves = kThreads / 64;
-constexpr int kPatchW = 8;  // a unit is PH x 8 output pixels: PH / 2 slabs of 2 x 8 (PH = 4; 2 where the windows of 4 rows do not fit)
+constexpr int kPatchW = 8;  // a unit is PH x 8 output pixels: PH / 2 slabs of 2 x 8
+
+// The three layers' units and workgroups: as many wavefronts as their windows leave room for in LDS and three a SIMD in the
+// registers.  Measured, 64 images (us): 128 -> 128: {4, 32, 768, 64} 26.0, with 128 columns a pass 26.5, of 64 channels and 512
+// threads 27.5, {4, 32, 1024, 32} 26.8.  64 -> 128: {2, 64, 640} 29.5, 512 threads 29.9, {2, 32, 512} 32.1, {4, 32, 512} 36.7.
+// 128 -> 256: {2, 32, 704} 20.6, 512 threads 22.3.
+struct WindowForm16 {
+  int rows, channels, threads, columns;  // of a unit; of a chunk of its window; of a workgroup; of a pass over the operands
+};
 template <int K, int N, int S>
-constexpr int patch_rows() {
-  return (K == 128 && N == 256 && S == 2) ? 2 : 4;
+constexpr WindowForm16 window_form() {
+  return S == 1 ? WindowForm16{4, 32, 768, 64} : N == 128 ? WindowForm16{2, 64, 640, 128} : WindowForm16{2, 32, 704, 128};
 }
 
 struct WindowBlockGeom16 {
@@ -56,33 +70,34 @@ struct WindowLayout16 {
   static constexpr int kPieces = WH * WW * QC, kLoads = (kPieces + 63) / 64;
 };
 
-template <int K, int S>
-constexpr int chunk_channels() {
-  return (S == 1 && K >= 64) ? 64 : 32;
+// The nine taps (row-major) in pairs: columns 0 and 1 of each row, column 2 of rows 0 and 1, the ninth alone.
+constexpr int kTapPairs = 5;
+__device__ __forceinline__ int tap_of(int pair, int second) {
+  return pair < 3 ? 3 * pair + second : pair == 3 ? 2 + 3 * second : 8;
 }
 
 template <int K, int N, int S>
-__global__ __launch_bounds__(kThreads) void separable_window_f16_kernel(const half_t* __restrict__ x,
+__global__ __launch_bounds__((window_form<K, N, S>().threads)) void separable_window_f16_kernel(const half_t* __restrict__ x,
                                                                         const half_t* __restrict__ dw_w,
                                                                         const half_t* __restrict__ dw_b,
                                                                         const half_t* __restrict__ pw_w,
                                                                         const half_t* __restrict__ pw_b,
                                                                         half_t* __restrict__ y, WindowBlockGeom16 g,
                                                                         int units, int dw_act, int pw_act) {
-  constexpr int CC = chunk_channels<K, S>();
-  constexpr int PH = patch_rows<K, N, S>(), SL = PH / 2;  // slabs per unit
+  constexpr WindowForm16 F = window_form<K, N, S>();
+  constexpr int kThreads = F.threads, kWaves = kThreads / 64, CC = F.channels, PH = F.rows, SL = PH / 2;  // slabs per unit
   using WL = WindowLayout16<S, CC, PH>;
   using Stage = FilterStage<K, N, kThreads>;
   constexpr int KS = K / 32, NB = N / 16, LD = Stage::LD, CH = K / CC, SPC = CC / 32;  // k-steps, blocks, chunks, steps per chunk
   constexpr int PS = WL::PS, RS = WL::RS, WW = WL::WW, LI = WL::kLoads, QC = WL::QC;
-  constexpr int NBP = NB < 8 ? NB : 8, PASSES = NB / NBP;  // 16-channel blocks per pass over the unit's operands
-  static_assert(K % CC == 0 && N % 32 == 0 && NB % NBP == 0 && N <= kThreads && 9 * K / 8 <= kThreads, "shape");
-  // pointwise filter [N][LD] halfs, its bias (N floats, in the filter's row order), depthwise filter [9][K] halfs,
-  // its bias (K floats), then one window per wavefront
+  constexpr int NBP = F.columns / 16, PASSES = NB / NBP;  // 16-channel blocks per pass over the unit's operands
+  static_assert(K % CC == 0 && N % 32 == 0 && NB % NBP == 0 && N <= kThreads && K <= kThreads, "shape");
+  // pointwise filter [N][LD] halfs, its bias (N floats, in the filter's row order), depthwise filter [tap pair][K / 16][lane]
+  // (a half in its half of a dword), its bias (K floats), then one window per wavefront
   extern __shared__ __align__(16) half_t wl[];
   float* const pwb_l = reinterpret_cast<float*>(wl + N * LD);
-  half_t* const dww_l = reinterpret_cast<half_t*>(pwb_l + N);
-  float* const dwb_l = reinterpret_cast<float*>(dww_l + 9 * K);
+  unsigned* const dww_l = reinterpret_cast<unsigned*>(pwb_l + N);
+  float* const dwb_l = reinterpret_cast<float*>(dww_l + kTapPairs * K * 4);
   half_t* const win = reinterpret_cast<half_t*>(dwb_l + K) + (threadIdx.x / 64) * WL::kHalfs;
   __shared__ int next_unit;
 
@@ -141,7 +156,13 @@ __global__ __launch_bounds__(kThreads) void separable_window_f16_kernel(const ha
   // by the counter): all in flight while the pointwise filter is transposed.
   Stage stage;
   stage.fetch(pw_w, tid);
-  const h8 dwv = *reinterpret_cast<const h8*>(dw_w + 8 * (tid < 9 * K / 8 ? tid : 0));
+  constexpr int DW = kTapPairs * K * 4, DWI = (DW + kThreads - 1) / kThreads;
+  unsigned short dwv[DWI];
+#pragma unroll
+  for (int i = 0; i < DWI; ++i) {
+    const int e = tid + i * kThreads < DW ? tid + i * kThreads : 0, eq = e % 64 / 16;
+    dwv[i] = reinterpret_cast<const unsigned short*>(dw_w)[tap_of(e / (4 * K), eq / 2) * K + e / 64 % (K / 16) * 16 + e % 16];
+  }
   const half_t pwb = (pw_b ? pw_b : pw_w)[tid < N ? tid : 0];
   const half_t dwb = (dw_b ? dw_b : pw_w)[tid < K ? tid : 0];
   if (tid == 0) next_unit = kWaves;
@@ -149,77 +170,75 @@ __global__ __launch_bounds__(kThreads) void separable_window_f16_kernel(const ha
   Place pc = place_of(cur < u1 ? cur : u0);
   Offsets oc = offsets_of(pc, cur < u1);
   load_chunk(oc, 0);
-  stage.store(wl, tid);
-  if (tid < 9 * K / 8) *reinterpret_cast<h8*>(dww_l + 8 * tid) = dwv;
+  stage.template store<true>(wl, tid);
+#pragma unroll
+  for (int i = 0; i < DWI; ++i) {
+    const int e = tid + i * kThreads, eli = e % 16, eq = e % 64 / 16, pair = e / (4 * K);
+    const bool mine = eli / 8 == eq % 2 && (pair < kTapPairs - 1 || eq < 2);
+    if (e < DW) dww_l[e] = mine ? (unsigned)dwv[i] << 16 * (eli % 2) : 0u;
+  }
   if (tid < N) pwb_l[rho(tid)] = pw_b ? (float)pwb : 0.f;
   if (tid < K) dwb_l[tid] = dw_b ? (float)dwb : 0.f;
   __syncthreads();
 
   const ActClamp dw_clamp = make_act(dw_act), pw_clamp = make_act(pw_act);
-  const float dw_lo = dw_clamp.on ? 0.f : -INFINITY;
-  // where this lane's taps start in a window: pixel (li / 8, li % 8) * S of slab 0, piece q
-  const half_t* const tap0 = win + ((li / 8) * S * RS + (li % 8) * S * PS + q) * 8;
+  // where this lane's taps start in a window: pixel (li / 8, li % 8) * S of slab 0, piece q % 2; the second of a pair of taps is
+  // the next column's, the next row's, or (the ninth tap has no
+  // partner) the same, so that a NaN outside a pixel's window meets none of its zeros
+  const half_t* const tap0 = win + ((li / 8) * S * RS + (li % 8) * S * PS + q % 2) * 8;
+  const half_t* const tap_col = tap0 + (q / 2) * PS * 8;
+  const half_t* const tap_row = tap0 + ((q / 2) * RS + 2 * PS) * 8;
+  unsigned own[4];  // the dword of an operand that holds channel li
+#pragma unroll
+  for (int e = 0; e < 4; ++e) own[e] = li % 8 / 2 == e ? ~0u : 0u;
   const half_t* const w_base = wl + li * LD + 8 * q;
 
   while (cur < u1) {
     int ticket = 0;
     if (lane == 0) ticket = atomicAdd(&next_unit, 1);
-    // depthwise layer, chunk by chunk: the chunk in the registers goes to LDS, the next one is requested, and the
-    // operands of the chunk's k-steps are formed for both slabs.  The clamp is a median of three; that
-    // instruction drops a NaN, so NaNs are looked for on the side and a wavefront that holds one repeats the
-    // layer with the exact form.
+    // depthwise layer, chunk by chunk: the chunk in the registers goes to LDS, the next one is requested, and the operands of the
+    // chunk's k-steps are formed for all slabs
     h8 a[SL][KS];
-    auto depthwise = [&](auto exact) {
-      unsigned long long nan = 0;
-      if constexpr (decltype(exact)::value) load_chunk(oc, 0);
 #pragma unroll
-      for (int ch = 0; ch < CH; ++ch) {
+    for (int ch = 0; ch < CH; ++ch) {
 #pragma unroll
-        for (int i = 0; i < LI; ++i)
-          if (LI * 64 == WL::kPieces || i + 1 < LI || lane + 64 * i < WL::kPieces)
-            *reinterpret_cast<u32x4*>(win + loff[i]) = wreg[i];
-        if (ch + 1 < CH) load_chunk(oc, ch + 1);
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        __builtin_amdgcn_wave_barrier();
+      for (int i = 0; i < LI; ++i)
+        if (LI * 64 == WL::kPieces || i + 1 < LI || lane + 64 * i < WL::kPieces)
+          *reinterpret_cast<u32x4*>(win + loff[i]) = wreg[i];
+      if (ch + 1 < CH) load_chunk(oc, ch + 1);
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
 #pragma unroll
-        for (int sc = 0; sc < SPC; ++sc) {
-          const int s = SPC * ch + sc;  // k-step: channels 32 s + 8 q ... + 7
-          const f32x4 b0 = *reinterpret_cast<const f32x4*>(dwb_l + 32 * s + 8 * q);
-          const f32x4 b1 = *reinterpret_cast<const f32x4*>(dwb_l + 32 * s + 8 * q + 4);
+      for (int sc = 0; sc < SPC; ++sc) {
+        const int s = SPC * ch + sc;  // k-step: channels 32 s ... + 31, as two groups of 16
+        f32x4 d[SL][2];
 #pragma unroll
-          for (int sl = 0; sl < SL; ++sl) {
-            float acc[8] = {b0[0], b0[1], b0[2], b0[3], b1[0], b1[1], b1[2], b1[3]};
-            // (a loop over the window's rows that is not unrolled: unrolled, the compiler reads all nine taps of
-            // both operands ahead and runs out of registers)
-#pragma unroll 1
-            for (int kh = 0; kh < 3; ++kh) {
+        for (int u = 0; u < 2; ++u) {
+          const f32x4 b = *reinterpret_cast<const f32x4*>(dwb_l + 32 * s + 16 * u + 4 * q);
 #pragma unroll
-              for (int kw = 0; kw < 3; ++kw) {
-                const h8 xv = *reinterpret_cast<const h8*>(tap0 + ((2 * sl * S + kh) * RS + kw * PS + 4 * sc) * 8);
-                const h8 wv = *reinterpret_cast<const h8*>(dww_l + (3 * kh + kw) * K + 32 * s + 8 * q);
+          for (int sl = 0; sl < SL; ++sl) d[sl][u] = b;
 #pragma unroll
-                for (int e = 0; e < 8; ++e) acc[e] = fmaf((float)xv[e], (float)wv[e], acc[e]);
-              }
+          for (int i = 0; i < kTapPairs; ++i) {
+            const unsigned wv = dww_l[(i * (K / 16) + 2 * s + u) * 64 + lane];
+            const u32x4 diagonal = {wv & own[0], wv & own[1], wv & own[2], wv & own[3]};
+#pragma unroll
+            for (int sl = 0; sl < SL; ++sl) {
+              const half_t* const at = i < 3 ? tap_col + i * RS * 8 : i == 3 ? tap_row : tap0 + (2 * RS + 2 * PS) * 8;
+              const h8 xv = *reinterpret_cast<const h8*>(at + (2 * sl * S * RS + 4 * sc + 2 * u) * 8);
+              d[sl][u] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(h8, diagonal), xv, d[sl][u], 0, 0, 0);
             }
-            h8 o;
-            if constexpr (decltype(exact)::value) {
-#pragma unroll
-              for (int e = 0; e < 8; ++e) o[e] = (half_t)apply_act(acc[e], dw_clamp);
-            } else {
-#pragma unroll
-              for (int e = 0; e < 8; e += 2) nan |= __builtin_amdgcn_ballot_w64(__builtin_isunordered(acc[e], acc[e + 1]));
-#pragma unroll
-              for (int e = 0; e < 8; ++e) o[e] = (half_t)__builtin_amdgcn_fmed3f(acc[e], dw_lo, dw_clamp.hi);
-            }
-            a[sl][s] = o;
           }
         }
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int sl = 0; sl < SL; ++sl) {
+          h8 o[1];
+          activate_and_pack(d[sl], dw_clamp, o);
+          a[sl][s] = o[0];
+        }
       }
-      return nan;
-    };
-    if (depthwise(std::false_type{}) != 0) depthwise(std::true_type{});
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+    }
 
     // the first chunk of the next unit's window is requested before the MFMAs of this one
     const int nxt = u0 + __builtin_amdgcn_readfirstlane(ticket);
@@ -227,7 +246,7 @@ __global__ __launch_bounds__(kThreads) void separable_window_f16_kernel(const ha
     const Offsets on = offsets_of(pn, nxt < u1);
     load_chunk(on, 0);
 
-    // pointwise layer, 128 output channels per pass over the operands and one k-step's filter fragments at a time
+    // pointwise layer, F.columns output channels per pass over the operands and one k-step's filter fragments at a time
     // (the scheduling barriers keep the compiler from gathering all the reads in front, which does not fit the
     // registers); the accumulators start from the bias
 #pragma unroll
@@ -271,11 +290,15 @@ __global__ __launch_bounds__(kThreads) void separable_window_f16_kernel(const ha
   }
 }
 
+static_assert(window_form<128, 256, 2>().rows == window_form<64, 128, 2>().rows, "one patch for both");
+
 template <int K, int N, int S>
 int launch_cfg(const half_t* x, const half_t* dw_w, const half_t* dw_b, const half_t* pw_w, const half_t* pw_b,
                half_t* y, const WindowBlockGeom16& g, int units, int dw_act, int pw_act, hipStream_t stream) {
-  using WL = WindowLayout16<S, chunk_channels<K, S>(), patch_rows<K, N, S>()>;
-  constexpr size_t lds_bytes = (size_t)N * filter_row_halfs(K) * 2 + N * 4 + 9 * K * 2 + K * 4 + (size_t)kWaves * WL::kHalfs * 2;
+  constexpr WindowForm16 F = window_form<K, N, S>();
+  constexpr int kThreads = F.threads, kWaves = kThreads / 64;
+  using WL = WindowLayout16<S, F.channels, F.rows>;
+  constexpr size_t lds_bytes = (size_t)N * filter_row_halfs(K) * 2 + N * 4 + kTapPairs * K * 16 + K * 4 + (size_t)kWaves * WL::kHalfs * 2;
   static_assert(lds_bytes + 64 <= 160 * 1024, "LDS budget per workgroup");
   auto kern = separable_window_f16_kernel<K, N, S>;
   static std::atomic<uint64_t> lds_allowed{0};
@@ -323,7 +346,7 @@ int launch_separable_stream_f16(const uint16_t* x16, const uint16_t* dw_w16, con
   const half_t* pw_w = reinterpret_cast<const half_t*>(pw_w16);
   const half_t* pw_b = reinterpret_cast<const half_t*>(pw_b16);
   half_t* y = reinterpret_cast<half_t*>(y16);
-  const int ph = (c == 128 && n == 256 && stride == 2) ? patch_rows<128, 256, 2>() : patch_rows<64, 128, 2>();
+  const int ph = stride == 1 ? window_form<128, 128, 1>().rows : window_form<128, 256, 2>().rows;
   const WindowBlockGeom16 g{h, w, oh, ow, pt, pl, (ow + kPatchW - 1) / kPatchW, (oh + ph - 1) / ph,
                             (unsigned)((long long)batch * h * w * c * 2)};
   const long long units = (long long)batch * g.tiles_c * g.tiles_r;

@@ -67,12 +67,15 @@ struct FilterStage {
       for (int kk = 0; kk < 4; ++kk) r[i][kk] = *reinterpret_cast<const h8*>(w + (size_t)(4 * kq + kk) * row_halfs + 8 * nb);
     }
   }
+  // PAIRS: the other operand's lane q holds k-groups q and 4 + q of every 32, the results of two 16-row products
+  template <bool PAIRS = false>
   __device__ __forceinline__ void store(half_t* wl, int tid) const {
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
       const int u = tid + i * NT;
       int nb, kq;
       place(u, &nb, &kq);
+      if constexpr (PAIRS) kq = kq / 8 * 8 + kq % 4 * 2 + kq / 4 % 2;
       if (BLOCKS % NT == 0 || i + 1 < PER || u < BLOCKS) {
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
