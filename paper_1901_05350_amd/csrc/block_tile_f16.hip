@@ -14,10 +14,16 @@
 // layers of a pass into it, in one launch of 4 us (loaded as it is stored, two columns of a k-row at a time, the
 // contraction took 11 us instead of 7, and more in all layers together than that launch).
 //
-// 64 x 14 x 14 x 512 -> 512, one layer: 17.6 us, of which 6.6 are launch and stores, 5 the depthwise layer (its loads; with
-// strips of 4 x 1, 18 pieces for four pixels, 6) and 7 the contraction (6 with its operands at hand); the two separate
-// kernels take 26 back to back and 32 in the network.
-// 64 x 28 x 28 x 256 -> 256 33 -> 25, 64 x 28 x 28 x 256 -> 512 at stride 2 20 -> 13.6, 64 x 7 x 7 x 1024 -> 1024 23 -> 20.
+// The first rows of the filter were late for every workgroup of an XCD at once, in its L2 for the first time and all waiting for
+// the same k-step: so each fetches its share of the filter's lines there while it computes the depthwise layer.  And the filter is
+// the first operand, so that a lane has 8 consecutive channels of a pixel to store (two of them, 32 stores of 4 bytes, kept the
+// memory busy after the contraction: 2.7 us, now 1.6).
+//
+// 64 x 14 x 14 x 512 -> 512, one layer: 17.2 us (18.5 without the last two), of which 1.2 are the start and the launch, 6 the
+// depthwise layer (the map's 13 MB from memory, then its arithmetic), 5.5 the contraction, 2 the stores; the two separate kernels
+// take 26 back to back and 32 in the network.  64 x 28 x 28 x 256 -> 256 33 -> 26, 64 x 28 x 28 x 256 -> 512 at stride 2 20 -> 16,
+// 64 x 7 x 7 x 1024 -> 1024 23 -> 21 (its contraction 9 - 11: a megabyte of the filter for each CU).  The whole pass of 64 images
+// 287 -> 277 us, 16 images 168 -> 164.
 #include "stream_f16.h"
 
 namespace tfx {
@@ -34,7 +40,7 @@ struct TileBlockArgs {
   half_t* y;
   int H, W, C, N, OH, OW, pt, pl;
   int row_patches, col_patches, patches, tiles_n, total;
-  unsigned x_bytes;
+  unsigned x_bytes, y_bytes;
   int dw_act, pw_act;
 };
 
@@ -73,8 +79,16 @@ __global__ __launch_bounds__(512) void separable_tile_f16_kernel(TileBlockArgs g
   }
   __syncthreads();
 
+  // The filter is in no L2 yet, and all workgroups of an XCD walk through it in the same order: each fetches its share of the lines
+  // while the depthwise layer is computed, a dword of each, instead of all waiting for every k-step in turn.
+  // (Those after the first 64 of an XCD find it there.)
+  const int of_xcd = max(1, min(g.total / kXcds, 64)), lines = C * N / 64, l0 = lines * min((int)blockIdx.x / kXcds, of_xcd - 1) / of_xcd;
+  const int line = min(l0 + min(tid, (lines - 1) / of_xcd), lines - 1);
+  auto touch = [&]() __attribute__((always_inline)) { return reinterpret_cast<const unsigned*>(g.pw_w)[32 * line]; };
+  unsigned touched = 0;
   const __amdgpu_buffer_rsrc_t xr = __builtin_amdgcn_make_buffer_rsrc(const_cast<half_t*>(g.x), 0, (int)g.x_bytes, 0x00020000);
   const ActClamp dw_clamp = make_act(g.dw_act);
+  if (tid >= PATCHES * C8) touched = touch();
   for (int item = tid; item < PATCHES * C8; item += (int)blockDim.x) {
     const int s = item / C8, c8 = item - s * C8;
     constexpr int PX = S == 1 ? 4 : 2, ROWS = S + 3, COLS = (PX - 1) * S + 3;  // columns at a time, and what they read
@@ -100,6 +114,7 @@ __global__ __launch_bounds__(512) void separable_tile_f16_kernel(TileBlockArgs g
         for (int i = 0; i < ROWS; ++i)
           win[i][j] = __builtin_amdgcn_raw_buffer_load_b128(xr, __builtin_elementwise_add_sat(row_off[i], col_off), 0, 0);
       }
+      if (item == tid && p0 == 0) touched = touch();
 #pragma unroll
       for (int p = 0; p < 2 * PX; ++p) {
         f32x4 acc[2];
@@ -120,17 +135,28 @@ __global__ __launch_bounds__(512) void separable_tile_f16_kernel(TileBlockArgs g
     }
   }
 
+  asm volatile("" ::"v"(touched));
+  __builtin_amdgcn_sched_barrier(0);
   // the filter's operands, in the order of pack_filters_kernel
   const int n0 = 64 * (tile_n * waves_n + wn);
   const int steps = C / 16, s0 = steps / WK * part, s1 = s0 + steps / WK;
-  const h8* const wp = reinterpret_cast<const h8*>(g.pw_w) + (size_t)(n0 / 64) * steps * 128 + lane;
+  const __amdgpu_buffer_rsrc_t wr = __builtin_amdgcn_make_buffer_rsrc(const_cast<half_t*>(g.pw_w), 0, C * N * 2, 0x00020000);
+  const int wp = n0 / 64 * steps * 2048;
   h8 raw[kAhead][2];
   auto load_step = [&](int s, h8 (&r)[2]) __attribute__((always_inline)) {
 #pragma unroll
-    for (int i = 0; i < 2; ++i) r[i] = wp[(2 * s + i) * 64];
+    for (int i = 0; i < 2; ++i)
+      r[i] = __builtin_bit_cast(h8, __builtin_amdgcn_raw_buffer_load_b128(wr, 16 * lane + 1024 * i, wp + 2048 * s, 0));
   };
+
 #pragma unroll
   for (int u = 0; u < kAhead; ++u) load_step(s0 + u, raw[u]);
+  // before the stores, which loads after them would wait for: the bias of this part's groups
+  constexpr int QP = 4 * TM / WK, BIASES = QP < 4 ? QP : 4;
+  static_assert(QP >= 1 && (WK == 1 || TM == 1), "a group for every part");
+  h8 bias[BIASES];
+#pragma unroll
+  for (int i = 0; i < BIASES; ++i) bias[i] = *reinterpret_cast<const h8*>(g.pw_b + n0 + 8 * h + 16 * (part * BIASES + i));
   f32x16 acc[TM][2];
 #pragma unroll
   for (int t = 0; t < TM; ++t)
@@ -138,7 +164,7 @@ __global__ __launch_bounds__(512) void separable_tile_f16_kernel(TileBlockArgs g
     for (int i = 0; i < 16; ++i) acc[t][0][i] = acc[t][1][i] = 0.f;
   __syncthreads();
 
-  // The scheduling barriers keep the loads of a step together: left to itself the compiler mixes those of four steps, and
+  // The scheduling barriers keep the loads of a step together: left to itself the compiler mixes those of several steps, and
   // the first step then waits for all of them.
   const half_t* const a_base = tile + li * LD + 8 * h;
   h8 a[2][TM];
@@ -154,27 +180,32 @@ __global__ __launch_bounds__(512) void separable_tile_f16_kernel(TileBlockArgs g
       load_step(s + u + kAhead < s1 ? s + u + kAhead : s1 - 1, raw[u]);  // past the end: the last step again, dropped
 #pragma unroll
       for (int t = 0; t < TM; ++t) {
-        acc[t][0] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[u & 1][t], b0, acc[t][0], 0, 0, 0);
-        acc[t][1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[u & 1][t], b1, acc[t][1], 0, 0, 0);
+        acc[t][0] = __builtin_amdgcn_mfma_f32_32x32x16_f16(b0, a[u & 1][t], acc[t][0], 0, 0, 0);
+        acc[t][1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(b1, a[u & 1][t], acc[t][1], 0, 0, 0);
       }
       __builtin_amdgcn_sched_barrier(0);
     }
   }
 
+  // Lane (li, h) has pixel li of each 32; group i of its accumulators is channels 16 i + 8 h ... + 7 of the wavefront's 64, the even
+  // ones in the first.
   const ActClamp pw_clamp = make_act(g.pw_act);
-  const half_t* const bias = g.pw_b + n0 + 2 * li;
-  const float bias0 = (float)bias[0], bias1 = (float)bias[1];
-  half_t* const yc = g.y + n0 + 2 * li;
-  // group q of the accumulators: the four pixels of row h of patch q
-  auto emit = [&](int q, const float (&v0)[4], const float (&v1)[4]) __attribute__((always_inline)) {
-    const Patch pt = patch[q];
-    const int count = h < pt.rows ? pt.cols : 0, first = pt.out + h * g.OW;
+  unsigned out[TM];
+  const __amdgpu_buffer_rsrc_t yr = __builtin_amdgcn_make_buffer_rsrc(g.y, 0, (int)g.y_bytes, 0x00020000);
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      typedef half_t h2 __attribute__((ext_vector_type(2)));
-      const h2 o = {(half_t)apply_act(v0[r] + bias0, pw_clamp), (half_t)apply_act(v1[r] + bias1, pw_clamp)};
-      if (r < count) *reinterpret_cast<h2*>(yc + (size_t)(first + r) * N) = o;
-    }
+  for (int t = 0; t < TM; ++t) {
+    const Patch pt = patch[4 * t + li / 8];
+    const int row = li % 8 / 4, col = li % 4;
+    // past the end, where nothing is stored, for a lane without a pixel
+    out[t] = row < pt.rows && col < pt.cols ? 2u * ((unsigned)(pt.out + row * g.OW + col) * N + n0 + 8 * h) : 0x80000000u;
+  }
+  auto emit = [&](int q, h8 bv, const float (&v0)[4], const float (&v1)[4]) __attribute__((always_inline)) {
+    f32x4 v[2];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e / 2][2 * (e % 2)] = v0[e] + (float)bv[2 * e], v[e / 2][2 * (e % 2) + 1] = v1[e] + (float)bv[2 * e + 1];
+    h8 o[1];
+    activate_and_pack(v, pw_clamp, o);
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, o[0]), yr, out[TM == 1 ? 0 : q / 4] + 32 * (q % 4), 0, 0);
   };
   if constexpr (WK == 1) {
 #pragma unroll
@@ -182,12 +213,10 @@ __global__ __launch_bounds__(512) void separable_tile_f16_kernel(TileBlockArgs g
       float v0[4], v1[4];
 #pragma unroll
       for (int r = 0; r < 4; ++r) v0[r] = acc[q / 4][0][4 * (q % 4) + r], v1[r] = acc[q / 4][1][4 * (q % 4) + r];
-      emit(q, v0, v1);
+      emit(q, bias[q % 4], v0, v1);
     }
   } else {
     // the parts' sums through LDS: part p adds up groups p QP ... of its columns
-    constexpr int QP = 4 * TM / WK;
-    static_assert(QP >= 1, "a group for every part");
     float* const sums = reinterpret_cast<float*>(tile);  // [wave][group][8][64]
     __syncthreads();
 #pragma unroll
@@ -207,7 +236,7 @@ __global__ __launch_bounds__(512) void separable_tile_f16_kernel(TileBlockArgs g
         for (int p = 0; p < WK; ++p) t += sums[(((p * waves_n + wn) * 4 * TM + q) * 8 + r) * 64 + lane];
         v[r / 4][r % 4] = t;
       }
-      emit(q, v[0], v[1]);
+      emit(q, bias[i], v[0], v[1]);
     }
   }
 }
@@ -288,12 +317,13 @@ bool separable_tile_f16_supported(int batch, int h, int w, int c, int n, int str
   const void* ptrs[] = {x, dw_w, dw_b, pw_w, pw_b, y};
   bool aligned = true;
   for (const void* p : ptrs) aligned = aligned && reinterpret_cast<uintptr_t>(p) % 16 == 0;
-  const long long patches = (long long)batch * ((oh + 1) / 2) * ((ow + 3) / 4), x_bytes = (long long)batch * h * w * c * 2;
+  const long long patches = (long long)batch * ((oh + 1) / 2) * ((ow + 3) / 4), x_bytes = (long long)batch * h * w * c * 2,
+                  y_bytes = (long long)batch * oh * ow * n * 2;
   // output pixels (with the patches' padding) from which it is the faster: every workgroup of a tile's columns computes the
   // depthwise layer again, so few pixels of a deep layer are not worth it (8 x 7 x 7 x 1024 10.7 us, 4 x 10.4; 7 apart)
   const long long least = c <= 256 ? 1024 : c <= 512 ? 700 : 850;
   return aligned && (stride == 1 || stride == 2) && c % 64 == 0 && c <= 1024 && n % 64 == 0 && n <= 1024 &&
-         x_bytes < (1ll << 31) && patches < (1ll << 27) && 8 * patches >= least;
+         x_bytes < (1ll << 31) && y_bytes < (1ll << 31) && patches < (1ll << 27) && 8 * patches >= least;
 }
 
 int launch_separable_tile_f16(const uint16_t* x, const uint16_t* dw_w, const uint16_t* dw_b, const uint16_t* packed,
@@ -302,7 +332,8 @@ int launch_separable_tile_f16(const uint16_t* x, const uint16_t* dw_w, const uin
   auto p = [](const uint16_t* q) { return reinterpret_cast<const half_t*>(q); };
   const int row_patches = (ow + 3) / 4, col_patches = (oh + 1) / 2, patches = batch * col_patches * row_patches;
   const TileBlockArgs g{p(x), p(dw_w), p(dw_b), p(packed), p(pw_b), reinterpret_cast<half_t*>(y), h, w, c, n, oh, ow, pt, pl,
-                        row_patches, col_patches, patches, 0, 0, (unsigned)((long long)batch * h * w * c * 2), dw_act, pw_act};
+                        row_patches, col_patches, patches, 0, 0, (unsigned)((long long)batch * h * w * c * 2),
+                        (unsigned)((long long)batch * oh * ow * n * 2), dw_act, pw_act};
   const TileForm f = tile_form(patches, c, n);
 #define TFX_TILE(S, TM, WK) \
   if (stride == S && f.tm == TM && f.wk == WK) return launch_tile<S, TM, WK>(g, f.waves_n, stream);
