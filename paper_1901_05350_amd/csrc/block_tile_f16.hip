@@ -293,21 +293,26 @@ int divisor(int groups, int most) {
   return 1;
 }
 
-// The tile (32 tm pixels, column groups of wavefronts, parts of the contraction): the largest that gives at least 160
-// workgroups -- one per CU is enough for the long ones -- since every workgroup reads its columns of the filter, and all of
-// a tile's workgroups compute its depthwise layer.  64 x 14 x 14 x 512 with {2, 8, 1} 18.9 us, {2, 4, 1} 23.4, {1, 8, 1}
-// 27.1; 16 images with {1, 4, 2} 9.9 (against {1, 8, 1} 11.7, {2, 8, 1} 16.0), 8 with {1, 2, 4} 8.2 ({1, 8, 1} 11.2).
+// The tile (32 tm pixels, column groups of wavefronts, parts of the contraction): the least modelled time -- a start for each round
+// of resident workgroups (8 wavefronts a CU), and for each workgroup of a CU its depthwise layer, which all workgroups of a tile
+// compute, and its columns of the filter from L2.  With the largest tile of at least 160 workgroups instead, 280 of them were two
+// rounds: 10 images 188 us, now 155; 20 219 and 182; 40 276 and 241; 20 at half width 159 and 131.  14 x 14 x 512 -> 512, us a launch: 64 images {2, 8, 1} 17.3, {1, 8, 1} 27;
+// 16 images {1, 4, 2} 9.9, {1, 8, 1} 11.7, {2, 8, 1} 16; 8 images {1, 2, 4} 8.2, {1, 8, 1} 11.2.
 struct TileForm {
   int tm, waves_n, wk;
 };
-TileForm tile_form(long long patches, int c, int n) {
+TileForm tile_form(long long patches, int c, int n, int stride) {
   const int groups = n / 64;
-  auto blocks = [&](int tm, int waves_n) { return (patches + 4 * tm - 1) / (4 * tm) * (groups / waves_n); };
-  const int wide = divisor(groups, 8), half = divisor(groups, 4), two = divisor(groups, 2);
-  if (blocks(2, wide) >= 160) return {2, wide, 1};
-  if (blocks(1, wide) >= 160 || c % 128 != 0) return {1, wide, 1};
-  if (blocks(1, half) >= 160 || c % 256 != 0) return {1, half, 2};
-  return {1, two, 4};
+  TileForm best{};
+  double least = 1e30;
+  for (const TileForm f : {TileForm{2, divisor(groups, 8), 1}, TileForm{1, divisor(groups, 8), 1}, TileForm{1, divisor(groups, 4), 2},
+                           TileForm{1, divisor(groups, 2), 4}}) {
+    if (c % (64 * f.wk) != 0) continue;
+    const long long blocks = (patches + 4 * f.tm - 1) / (4 * f.tm) * (groups / f.waves_n), slots = 256 * (8 / (f.waves_n * f.wk));
+    const double us = 2.3 * (double)((blocks + slots - 1) / slots) + (double)((blocks + 255) / 256) * c * (.011 * stride * f.tm + .93e-3 * f.waves_n);
+    if (us < least) best = f, least = us;
+  }
+  return best;
 }
 
 }  // namespace
@@ -334,7 +339,7 @@ int launch_separable_tile_f16(const uint16_t* x, const uint16_t* dw_w, const uin
   const TileBlockArgs g{p(x), p(dw_w), p(dw_b), p(packed), p(pw_b), reinterpret_cast<half_t*>(y), h, w, c, n, oh, ow, pt, pl,
                         row_patches, col_patches, patches, 0, 0, (unsigned)((long long)batch * h * w * c * 2),
                         (unsigned)((long long)batch * oh * ow * n * 2), dw_act, pw_act};
-  const TileForm f = tile_form(patches, c, n);
+  const TileForm f = tile_form(patches, c, n, stride);
 #define TFX_TILE(S, TM, WK) \
   if (stride == S && f.tm == TM && f.wk == WK) return launch_tile<S, TM, WK>(g, f.waves_n, stream);
   TFX_TILE(1, 2, 1)
