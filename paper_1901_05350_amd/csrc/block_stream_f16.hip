@@ -27,16 +27,20 @@ using namespace f16s;
 
 constexpr int kPatchW = 8;  // a unit is PH x 8 output pixels: PH / 2 slabs of 2 x 8
 
-// The three layers' units and workgroups: as many wavefronts as their windows leave room for in LDS and three a SIMD in the
+// The layers' units and workgroups: as many wavefronts as their windows leave room for in LDS and three or four a SIMD in the
 // registers.  Measured, 64 images (us): 128 -> 128: {4, 32, 768, 64} 26.0, with 128 columns a pass 26.5, of 64 channels and 512
 // threads 27.5, {4, 32, 1024, 32} 26.8.  64 -> 128: {2, 64, 640} 29.5, 512 threads 29.9, {2, 32, 512} 32.1, {4, 32, 512} 36.7.
-// 128 -> 256: {2, 32, 704} 20.6, 512 threads 22.3.
+// 128 -> 256: {2, 32, 704} 20.6, 512 threads 22.3.  96 -> 96: {4, 32, 1024, 96} 19.5, 768 threads 20.2 (two launches 51).
+// 96 -> 192: {2, 32, 768} 16.9, 512 threads 17.9 (33).  32 -> 64: {4, 32, 768} 16.1, {2, 32, 768} 17.5 (25).
 struct WindowForm16 {
   int rows, channels, threads, columns;  // of a unit; of a chunk of its window; of a workgroup; of a pass over the operands
 };
-template <int K, int N, int S>
+template <int K, int N>
 constexpr WindowForm16 window_form() {
-  return S == 1 ? WindowForm16{4, 32, 768, 64} : N == 128 ? WindowForm16{2, 64, 640, 128} : WindowForm16{2, 32, 704, 128};
+  if (K == 128) return N == 128 ? WindowForm16{4, 32, 768, 64} : WindowForm16{2, 32, 704, 128};
+  if (K == 96) return N == 96 ? WindowForm16{4, 32, 1024, 96} : WindowForm16{2, 32, 768, 96};
+  if (K == 64) return WindowForm16{2, 64, 640, 128};
+  return WindowForm16{4, 32, 768, 64};
 }
 
 struct WindowBlockGeom16 {
@@ -77,21 +81,21 @@ __device__ __forceinline__ int tap_of(int pair, int second) {
 }
 
 template <int K, int N, int S>
-__global__ __launch_bounds__((window_form<K, N, S>().threads)) void separable_window_f16_kernel(const half_t* __restrict__ x,
+__global__ __launch_bounds__((window_form<K, N>().threads)) void separable_window_f16_kernel(const half_t* __restrict__ x,
                                                                         const half_t* __restrict__ dw_w,
                                                                         const half_t* __restrict__ dw_b,
                                                                         const half_t* __restrict__ pw_w,
                                                                         const half_t* __restrict__ pw_b,
                                                                         half_t* __restrict__ y, WindowBlockGeom16 g,
                                                                         int units, int dw_act, int pw_act) {
-  constexpr WindowForm16 F = window_form<K, N, S>();
+  constexpr WindowForm16 F = window_form<K, N>();
   constexpr int kThreads = F.threads, kWaves = kThreads / 64, CC = F.channels, PH = F.rows, SL = PH / 2;  // slabs per unit
   using WL = WindowLayout16<S, CC, PH>;
   using Stage = FilterStage<K, N, kThreads>;
   constexpr int KS = K / 32, NB = N / 16, LD = Stage::LD, CH = K / CC, SPC = CC / 32;  // k-steps, blocks, chunks, steps per chunk
   constexpr int PS = WL::PS, RS = WL::RS, WW = WL::WW, LI = WL::kLoads, QC = WL::QC;
   constexpr int NBP = F.columns / 16, PASSES = NB / NBP;  // 16-channel blocks per pass over the unit's operands
-  static_assert(K % CC == 0 && N % 32 == 0 && NB % NBP == 0 && N <= kThreads && K <= kThreads, "shape");
+  static_assert(K % CC == 0 && N % 32 == 0 && NB % NBP == 0 && NBP % 2 == 0 && N <= kThreads && K <= kThreads, "shape");
   // pointwise filter [N][LD] halfs, its bias (N floats, in the filter's row order), depthwise filter [tap pair][K / 16][lane]
   // (a half in its half of a dword), its bias (K floats), then one window per wavefront
   extern __shared__ __align__(16) half_t wl[];
@@ -290,14 +294,17 @@ __global__ __launch_bounds__((window_form<K, N, S>().threads)) void separable_wi
   }
 }
 
-static_assert(window_form<128, 256, 2>().rows == window_form<64, 128, 2>().rows, "one patch for both");
-
 template <int K, int N, int S>
-int launch_cfg(const half_t* x, const half_t* dw_w, const half_t* dw_b, const half_t* pw_w, const half_t* pw_b,
-               half_t* y, const WindowBlockGeom16& g, int units, int dw_act, int pw_act, hipStream_t stream) {
-  constexpr WindowForm16 F = window_form<K, N, S>();
+int launch_cfg(const half_t* x, const half_t* dw_w, const half_t* dw_b, const half_t* pw_w, const half_t* pw_b, half_t* y, int batch,
+               int h, int w, int oh, int ow, int pt, int pl, int dw_act, int pw_act, hipStream_t stream) {
+  constexpr WindowForm16 F = window_form<K, N>();
   constexpr int kThreads = F.threads, kWaves = kThreads / 64;
   using WL = WindowLayout16<S, F.channels, F.rows>;
+  const WindowBlockGeom16 g{h, w, oh, ow, pt, pl, (ow + kPatchW - 1) / kPatchW, (oh + F.rows - 1) / F.rows,
+                            (unsigned)((long long)batch * h * w * K * 2)};
+  const long long all = (long long)batch * g.tiles_c * g.tiles_r;
+  if (all > 0x3fffffffLL) return TFX_ERR_UNSUPPORTED;
+  const int units = (int)all;
   constexpr size_t lds_bytes = (size_t)N * filter_row_halfs(K) * 2 + N * 4 + kTapPairs * K * 16 + K * 4 + (size_t)kWaves * WL::kHalfs * 2;
   static_assert(lds_bytes + 64 <= 160 * 1024, "LDS budget per workgroup");
   auto kern = separable_window_f16_kernel<K, N, S>;
@@ -322,19 +329,18 @@ int launch_cfg(const half_t* x, const half_t* dw_w, const half_t* dw_b, const ha
 
 }  // namespace
 
-// Blocks 2 - 4 (channels -> filters, stride) of the full-width network, many output pixels,
+// Blocks 2 - 4 (channels -> filters, stride) of the full-width network, 3 and 4 at 3/4 and 2, 4 and 6 at half width, many output pixels,
 // 16-byte aligned operands, an input below 2^31 bytes.
 bool separable_stream_f16_supported(int batch, int h, int w, int c, int n, int stride, int oh, int ow, const void* x,
                                     const void* dw_w, const void* dw_b, const void* pw_w, const void* pw_b,
                                     const void* y) {
-  const bool shape = (c == 128 && n == 128 && stride == 1) || (c == 64 && n == 128 && stride == 2) ||
-                     (c == 128 && n == 256 && stride == 2);
+  const bool shape = stride == 1 ? c == n && (c == 96 || c == 128) : n == 2 * c && (c == 32 || c == 64 || c == 96 || c == 128);
   const void* ptrs[] = {x, dw_w, dw_b, pw_w, pw_b, y};
   bool aligned = true;
   for (const void* p : ptrs) aligned = aligned && reinterpret_cast<uintptr_t>(p) % 16 == 0;
   const long long m = (long long)batch * oh * ow, x_bytes = (long long)batch * h * w * c * 2;
   // least output pixels from which the one launch beats the two kernels (measured on the network, per block)
-  const long long least = n == 256 ? 6272 : 16384;
+  const long long least = n > 128 ? 6272 : 16384;
   return shape && aligned && m >= least && m <= 0x3fffffffLL && x_bytes < (1ll << 31);
 }
 
@@ -347,17 +353,15 @@ int launch_separable_stream_f16(const uint16_t* x16, const uint16_t* dw_w16, con
   const half_t* pw_w = reinterpret_cast<const half_t*>(pw_w16);
   const half_t* pw_b = reinterpret_cast<const half_t*>(pw_b16);
   half_t* y = reinterpret_cast<half_t*>(y16);
-  const int ph = stride == 1 ? window_form<128, 128, 1>().rows : window_form<128, 256, 2>().rows;
-  const WindowBlockGeom16 g{h, w, oh, ow, pt, pl, (ow + kPatchW - 1) / kPatchW, (oh + ph - 1) / ph,
-                            (unsigned)((long long)batch * h * w * c * 2)};
-  const long long units = (long long)batch * g.tiles_c * g.tiles_r;
-  if (units > 0x3fffffffLL) return TFX_ERR_UNSUPPORTED;
 #define TFX_WINDOW_BLOCK16(C, NN, SS) \
   if (c == C && n == NN && stride == SS) \
-    return launch_cfg<C, NN, SS>(x, dw_w, dw_b, pw_w, pw_b, y, g, (int)units, dw_act, pw_act, stream);
+    return launch_cfg<C, NN, SS>(x, dw_w, dw_b, pw_w, pw_b, y, batch, h, w, oh, ow, pt, pl, dw_act, pw_act, stream);
   TFX_WINDOW_BLOCK16(128, 128, 1)
   TFX_WINDOW_BLOCK16(64, 128, 2)
   TFX_WINDOW_BLOCK16(128, 256, 2)
+  TFX_WINDOW_BLOCK16(96, 96, 1)
+  TFX_WINDOW_BLOCK16(96, 192, 2)
+  TFX_WINDOW_BLOCK16(32, 64, 2)
 #undef TFX_WINDOW_BLOCK16
   return TFX_ERR_UNSUPPORTED;
 }
