@@ -603,10 +603,25 @@ int forward_impl(const tfx_mobilenet_v1_variant* variant, const float* input, in
                           static_cast<hipStream_t>(stream));
     const int64_t fd[4] = {3, 3, shape[3], 1};
     const int64_t cout = kChannels[b] * q / 4;
+    conv_geometry(shape, fd, kStrides[b], kStrides[b], TFX_PAD_SAME, true, &g);
+    // few pixels: depthwise and pointwise layer in one launch, a workgroup per patch (block_patch.hip); one image whose pass is
+    // chained keeps the kernels of the chain's order
+    if ((batch > 1 || !plan.chain) && separable_patch_pays((int)batch, (int)shape[3], (int)cout, kStrides[b], (int)g.out[1], (int)g.out[2]) &&
+        separable_patch_supported((int)batch, (int)shape[1], (int)shape[2], (int)shape[3], (int)cout, kStrides[b], (int)g.out[1], (int)g.out[2],
+                                  buf[cur], weights->dw_w[b], weights->dw_b[b], weights->pw_w[b], weights->pw_b[b], block_out)) {
+      rc = launch_separable_patch(buf[cur], weights->dw_w[b], weights->dw_b[b], weights->pw_w[b], weights->pw_b[b], block_out, (int)batch,
+                                  (int)shape[1], (int)shape[2], (int)shape[3], (int)cout, (int)g.out[1], (int)g.out[2], kStrides[b],
+                                  (int)g.pad[0], (int)g.pad[2], TFX_ACT_RELU6, TFX_ACT_RELU6, static_cast<hipStream_t>(stream));
+      if (rc) return rc;
+      if (end_block == b + 1) return TFX_OK;
+      for (int i = 0; i < 3; ++i) shape[i] = g.out[i];
+      shape[3] = cout;
+      cur ^= 1;
+      continue;
+    }
     // batch 1 to 3, thin block: depthwise and pointwise layer in one launch (block.hip)
     if (separable_block_supported(batch, (int)shape[1], (int)shape[2], (int)shape[3], (int)cout, kStrides[b], buf[cur],
                                   weights->dw_w[b], weights->dw_b[b], weights->pw_w[b], weights->pw_b[b], block_out)) {
-      conv_geometry(shape, fd, kStrides[b], kStrides[b], TFX_PAD_SAME, true, &g);
       rc = launch_separable_block(buf[cur], weights->dw_w[b], weights->dw_b[b], weights->pw_w[b], weights->pw_b[b],
                                   block_out, (int)batch, (int)shape[1], (int)shape[2], (int)shape[3], (int)cout, (int)g.out[1],
                                   (int)g.out[2], kStrides[b], (int)g.pad[0], (int)g.pad[2], TFX_ACT_RELU6, TFX_ACT_RELU6,
@@ -619,7 +634,6 @@ int forward_impl(const tfx_mobilenet_v1_variant* variant, const float* input, in
       continue;
     }
     // large batch, early block: depthwise and pointwise layer in one filter-stationary launch (block_stream.hip)
-    conv_geometry(shape, fd, kStrides[b], kStrides[b], TFX_PAD_SAME, true, &g);
     if (separable_stream_supported((int)batch, (int)shape[1], (int)shape[2], (int)shape[3], (int)cout, kStrides[b],
                                    (int)g.out[1], (int)g.out[2], buf[cur], weights->dw_w[b], weights->dw_b[b],
                                    weights->pw_w[b], weights->pw_b[b], block_out)) {

@@ -328,6 +328,14 @@ int launch_separable_stream(const float* x, const float* dw_w, const float* dw_b
                             float* y, int batch, int h, int w, int c, int n, int oh, int ow, int stride, int pt, int pl,
                             int dw_act, int pw_act, hipStream_t stream);
 
+// A block of few pixels in one launch, a workgroup per 4 x 4 patch of the output and slice of its columns (block_patch.hip).
+bool separable_patch_supported(int batch, int h, int w, int c, int n, int stride, int oh, int ow, const void* x, const void* dw_w,
+                               const void* dw_b, const void* pw_w, const void* pw_b, const void* y);
+bool separable_patch_pays(int batch, int c, int n, int stride, int oh, int ow);
+int launch_separable_patch(const float* x, const float* dw_w, const float* dw_b, const float* pw_w, const float* pw_b, float* y,
+                           int batch, int h, int w, int c, int n, int oh, int ow, int stride, int pt, int pl, int dw_act, int pw_act,
+                           hipStream_t stream);
+
 // A depthwise-separable block of a batch as a depthwise kernel that writes bf16 planes and a product of planes
 // (block_planes.hip): any c % 32 == 0, n % 64 == 0.  a_planes / b_planes: planes_elems(rows, c) / planes_elems(n, c)
 // 16-bit words, 16-byte aligned, not overlapping x or y; rows = output pixels.  The depthwise layer's activation is relu6.
