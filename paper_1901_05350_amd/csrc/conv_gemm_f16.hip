@@ -9,8 +9,10 @@
 // The loop is the software pipeline of gemm_f16_pipe_kernel: k-slices of 64 halfs are double-buffered in LDS as
 // K-contiguous rows of 144 bytes; while slice kt is multiplied, one 16-byte slot after another of slice kt + 1 (fetched a
 // whole iteration earlier) moves from registers to the other LDS buffer and is refilled from slice kt + 2, spread between
-// the MFMAs.  The filter is stored [K, Co]: a thread loads 4 k-rows x 8 columns as four slots, transposes the block in
-// registers and writes 4 consecutive k per column to the K-contiguous LDS rows.
+// the MFMAs.  The filter is stored [K, Co] and keeps its k-rows in LDS; its fragments are read with the transposing LDS load (as turned
+// in registers, 4 k-rows x 8 columns a thread, its 8-byte LDS writes were waited for: 4 % less over 63 aligned convolutions with the
+// tiles as they were).  Tiles of 64 x 128 and 128 x 128 have 8 wavefronts, 64 x 64 ones 4: 10 % less over 334 convolutions (3x3,
+// 18x19x19x240 -> 152 29.1 -> 20.1 us; 47x17x42x166 -> 32 34.3 -> 24.9).
 //
 // What bounds it is the latency of a slice where workgroups are few, and the vector-ALU instructions of the addresses
 // beside the MFMAs where they are many, hence three forms of the loader:
@@ -34,6 +36,7 @@ typedef ragged_u32x4 u32x4;
 
 constexpr int kBK = 64;       // halfs per k-slice
 constexpr int kLd = kBK + 8;  // LDS row stride in halfs
+constexpr int kPad = 16;      // halfs after a k-row of the filter: the four rows of a transposing load lie on different banks
 constexpr int kXcds = 8;
 
 enum Form { kLean, kAligned, kRagged };
@@ -67,10 +70,10 @@ template <int WAVES_M, int WAVES_N, int TM, int TN, Form FORM>
 __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void conv_f16_gemm_kernel(ConvArgs g) {
   constexpr int kNT = 64 * WAVES_M * WAVES_N;
   constexpr int WM = 32 * TM, WN = 32 * TN, BM = WM * WAVES_M, BN = WN * WAVES_N;
-  constexpr int kTileA = BM * kLd, kTileB = BN * kLd;
-  constexpr int SA = BM * 8 / kNT, SB = 4, SLOTS = SA + SB;  // 16-byte slots per thread and slice
+  constexpr int kLdB = BN + kPad, kTileA = BM * kLd, kTileB = kBK * kLdB;
+  constexpr int SA = BM * 8 / kNT, SB = BN * 8 / kNT, SLOTS = SA + SB;  // 16-byte slots per thread and slice
   constexpr int STEPS = kBK / 16, MF = TM * TN;
-  static_assert(BM * 8 % kNT == 0 && kNT / 16 == BN / 8, "loader shape");
+  static_assert(BM * 8 % kNT == 0 && BN * 8 % kNT == 0, "loader shape");
   extern __shared__ __align__(16) half_t smem_h[];
   half_t* const lds_a = smem_h;  // two A buffers, then two B buffers
   half_t* const lds_b = smem_h + 2 * kTileA;
@@ -110,24 +113,27 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void conv_f16_gemm_kernel(C
       tap_ok[i] = ok;
     }
   }
-  // B slots: k-rows 4 kq ... + 3 of the slice, columns n0 + 8 nb ... + 7; past N: any column block (feeds no stored output);
-  // four lanes side by side in a row, for the look-ups in L1 (gemm_f16.hip)
-  const int kq = tid / 4 % 16, nb = tid / 64 * 4 + tid % 4;
-  const unsigned bcol = n0 + 8 * nb < N ? (unsigned)(n0 + 8 * nb) : 0u;
+  // B slot i: k-row brow + kRowsB i of the slice, columns n0 + bcol8 ... + 7; past N: any column block (feeds no stored output)
+  constexpr int kRowsB = kNT / (BN / 8);
+  const int brow = tid / (BN / 8), bcol8 = 8 * (tid % (BN / 8));
+  const unsigned bcol = n0 + bcol8 < N ? (unsigned)(n0 + bcol8) : 0u;
   const __amdgpu_buffer_rsrc_t xr = __builtin_amdgcn_make_buffer_rsrc(const_cast<half_t*>(g.x), 0, (int)(2u * g.x_total), 0x00020000);
   const __amdgpu_buffer_rsrc_t wr = __builtin_amdgcn_make_buffer_rsrc(const_cast<half_t*>(g.w), 0, (int)(2u * g.w_total), 0x00020000);
   constexpr unsigned kOutside = 0xfffffff0u;
 
   // What slot loads and stores of one slice need to know: the positions of the slice's A slots and B rows.
   struct Slice {
-    KPos a, b;
+    KPos a, b[SB];
     int k0;
   };
   auto slice_at = [&](int kt) {
     Slice s;
     s.k0 = min(kt, g.slices - 1) * kBK;  // the last two iterations fetch the last slice again (unused)
     s.a = k_position(g, FORM == kLean ? s.k0 : s.k0 + scol);
-    if constexpr (FORM == kRagged) s.b = k_position(g, s.k0 + 4 * kq);
+    if constexpr (FORM == kRagged) {
+#pragma unroll
+      for (int i = 0; i < SB; ++i) s.b[i] = k_position(g, s.k0 + brow + kRowsB * i);
+    }
     return s;
   };
   // Element offset of slot w of a slice in x / the filter.  kRagged: slots that would reach past the end of a tensor
@@ -139,11 +145,12 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void conv_f16_gemm_kernel(C
       else *in = s.a.valid > 0 && (unsigned)(ih0[w] + s.a.kh) < (unsigned)g.H && (unsigned)(iw0[w] + s.a.kw) < (unsigned)g.W;
       off = (unsigned)(origin[w] + (s.a.kh * g.W + s.a.kw) * Ci + s.a.c);
     } else if constexpr (FORM == kRagged) {
-      *in = w - SA < s.b.valid;
-      off = (unsigned)(s.b.tap * Ci + s.b.c + w - SA) * (unsigned)N + bcol;
+      const KPos& b = s.b[w < SA ? 0 : w - SA];
+      *in = b.valid > 0;
+      off = (unsigned)(b.tap * Ci + b.c) * (unsigned)N + bcol;
     } else {
       *in = true;
-      off = (unsigned)(s.k0 + 4 * kq + w - SA) * (unsigned)N + bcol;  // rows past K are past the end of the filter
+      off = (unsigned)(s.k0 + brow + kRowsB * (w - SA)) * (unsigned)N + bcol;  // rows past K are past the end of the filter
     }
     *early = 0;
     if constexpr (FORM == kRagged) {
@@ -185,17 +192,19 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void conv_f16_gemm_kernel(C
   auto store_slot = [&](int w, int buf, const u32x4& mask) {
     if (w < SA) {
       *reinterpret_cast<u32x4*>(lds_a + buf * kTileA + (srow + kRowStep * w) * kLd + scol) = masked(w, mask);
-    } else if (w == SA) {
-      h8 r[4];
-#pragma unroll
-      for (int kk = 0; kk < 4; ++kk) r[kk] = __builtin_bit_cast(h8, masked(SA + kk, mask));
-      half_t* const l = lds_b + buf * kTileB + (8 * nb) * kLd + 4 * kq;
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const h4 o = {r[0][i], r[1][i], r[2][i], r[3][i]};
-        *reinterpret_cast<h4*>(l + i * kLd) = o;
-      }
+    } else {
+      *reinterpret_cast<u32x4*>(lds_b + buf * kTileB + (brow + kRowsB * (w - SA)) * kLdB + bcol8) = masked(w, mask);
     }
+  };
+  // Fragment of 32 columns x 16 k: lane (li, hh) gets 8 consecutive k from 8 hh on of column li.  The transposing load gives lane i
+  // of 16 the four halfs at place i % 4 of the 8-byte pieces that lanes i / 4, i / 4 + 4, ... of the 16 point to: with piece l at
+  // k-row l / 4 and columns 4 (l % 4), four k of column i.
+  auto filter = [&](const half_t* first, int j, int step) {
+    typedef short s4 __attribute__((ext_vector_type(4)));
+    typedef __attribute__((address_space(3))) s4 lds_s4;
+    const half_t* const p = first + 32 * j + 16 * step * kLdB;
+    const s4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4*)(p)), hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4*)(p + 4 * kLdB));
+    return __builtin_bit_cast(h8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
   };
 
   f32x16 acc[TM][TN];
@@ -232,19 +241,19 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void conv_f16_gemm_kernel(C
     const u32x4 mask = first_elements<half_t>(valid);
     unsigned early = 0;
     const half_t* la = lds_a + cur * kTileA + (wm0 + li) * kLd + 8 * hh;
-    const half_t* lb = lds_b + cur * kTileB + (wn0 + li) * kLd + 8 * hh;
+    const half_t* lb = lds_b + cur * kTileB + (8 * hh + lane % 16 / 4) * kLdB + wn0 + 16 * (lane / 16 % 2) + 4 * (lane % 4);
     h8 fa[2][TM], fb[2][TN];
 #pragma unroll
     for (int i = 0; i < TM; ++i) fa[0][i] = *reinterpret_cast<const h8*>(la + 32 * i * kLd);
 #pragma unroll
-    for (int j = 0; j < TN; ++j) fb[0][j] = *reinterpret_cast<const h8*>(lb + 32 * j * kLd);
+    for (int j = 0; j < TN; ++j) fb[0][j] = filter(lb, j, 0);
 #pragma unroll
     for (int s = 0; s < STEPS; ++s) {
       if (s + 1 < STEPS) {
 #pragma unroll
         for (int i = 0; i < TM; ++i) fa[(s + 1) & 1][i] = *reinterpret_cast<const h8*>(la + 32 * i * kLd + 16 * (s + 1));
 #pragma unroll
-        for (int j = 0; j < TN; ++j) fb[(s + 1) & 1][j] = *reinterpret_cast<const h8*>(lb + 32 * j * kLd + 16 * (s + 1));
+        for (int j = 0; j < TN; ++j) fb[(s + 1) & 1][j] = filter(lb, j, s + 1);
       }
       __builtin_amdgcn_sched_barrier(0);  // keep those LDS reads ahead of this step's MFMAs
       // operands swapped (the filter's fragment first): a lane's registers then hold 4 consecutive output
@@ -319,7 +328,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void conv_f16_gemm_kernel(C
 template <int WAVES_M, int WAVES_N, int TM, int TN, Form FORM>
 int launch(ConvArgs& g, hipStream_t stream) {
   constexpr int BM = 32 * TM * WAVES_M, BN = 32 * TN * WAVES_N;
-  constexpr size_t lds_bytes = 2 * (size_t)(BM + BN) * kLd * sizeof(half_t);
+  constexpr size_t lds_bytes = 2 * (size_t)(BM * kLd + kBK * (BN + kPad)) * sizeof(half_t);
   const long long tiles_m = (g.M + (long long)BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
   if (tiles_m * tiles_n > 0x7fffffffLL) return TFX_ERR_UNSUPPORTED;
   auto kern = conv_f16_gemm_kernel<WAVES_M, WAVES_N, TM, TN, FORM>;
@@ -328,14 +337,6 @@ int launch(ConvArgs& g, hipStream_t stream) {
   g.tiles_n = (int)tiles_n, g.total_blocks = (int)(tiles_m * tiles_n);
   hipLaunchKernelGGL(kern, dim3((unsigned)g.total_blocks), dim3(64 * WAVES_M * WAVES_N), lds_bytes, stream, g);
   return check_launch();
-}
-
-// The cheapest of the tiled forms by kernel_cost.h (form: 0 = 128 x 128, 1 = 64 x 128, 2 = 64 x 64 tiles).
-template <Form FORM>
-int launch_tiles(ConvArgs& g, hipStream_t stream, int form) {
-  if (form == 0) return launch<2, 2, 2, 2, FORM>(g, stream);
-  if (form == 1) return launch<2, 2, 1, 2, FORM>(g, stream);
-  return launch<2, 1, 1, 2, FORM>(g, stream);
 }
 
 }  // namespace
@@ -359,24 +360,36 @@ int launch_conv2d_gemm_f16(const uint16_t* x, const uint16_t* w, const uint16_t*
   g.by_cp = fast_div((unsigned)cp), g.by_fw = fast_div((unsigned)fw), g.by_ow = fast_div((unsigned)ow), g.by_oh = fast_div((unsigned)oh);
   // (the byte offset of a filter row past K stays below 2^32)
   const bool aligned = ci % 8 == 0 && co % 8 == 0 && ((long long)fh * fw * ci + kBK) * co < (1LL << 31) && reinterpret_cast<uintptr_t>(x) % 16 == 0 && reinterpret_cast<uintptr_t>(w) % 16 == 0;
-  // the fastest by kernel_cost.h: LDS tiles of three sizes, or the contraction split over a workgroup's wavefronts with
-  // 16 x 32, 32 x 64 or 64 x 64 tiles (5x5, 13x20x20x398 -> 192: 137 us with LDS tiles, 92 split; 3x3, 2x56x56x32 -> 64:
-  // 10.8 and 6.4)
   if (fh == 1 && fw == 1 && sh == sw && pt == 0 && pl == 0 && thin_pays(g.M, co, ci, true))
     return launch_conv1x1_thin_f16(x, w, y, bias, g.M, co, ci, act, stream, h, wd, oh, ow, sh);
-  const double kp = (double)fh * fw * cp;
-  auto us = [&](const KernelCost& c) { return c.us(1, g.M, co, kp); };
-  const double cost[6] = {us({128, 128, 4.44, 0., 3.32, .0116}), us({64, 128, 4.9, 0., 1.35, .0095}),
-                          us({64, 64, 5.07, .0035, 1.36, .0048}), us({16, co % 2 == 0 ? 32 : 16, 3.26, 0., .25, .0024}),
-                          co >= 2 ? us({64, 64, 1.42, 0., 2.77, .0074}) : 1e30, co >= 2 ? us({32, 64, 2.93, .0047, .71, .0044}) : 1e30};
-  int best = 0;
-  for (int i = 1; i < 6; ++i)
-    if (cost[i] < cost[best]) best = i;
-  if (best == 3) return launch_conv2d_deep_f16(x, w, bias, y, n, h, wd, ci, fh, fw, co, oh, ow, sh, sw, pt, pl, act, stream);
-  if (best > 3)
-    return launch_conv2d_gemm_direct_f16(x, w, bias, y, n, h, wd, ci, fh, fw, co, oh, ow, sh, sw, pt, pl, act, stream, best - 4);
-  if (!aligned) return launch_tiles<kRagged>(g, stream, best);
-  return ci % 64 == 0 && fh * fw <= 32 ? launch_tiles<kLean>(g, stream, best) : launch_tiles<kAligned>(g, stream, best);
+  // The least modelled time, fitted to 334 convolutions (1x1, 3x3, 5x5, 7 ... 112 pixels a side, 8 ... 512 channels, batch 1 ... 64;
+  // near the choice the rms error is 9 - 14 %): LDS tiles of three sizes, or the contraction split over a workgroup's wavefronts
+  // with 16 x 32, 32 x 64 or 64 x 64 tiles.  Over these the choice costs 0.9 % on average against the fastest of each, more than 16 %
+  // for three (3x3, 36x13x13x160 -> 52: 17.4 us, 12.7 with 64 x 64 split).
+  // (5x5, 13x20x20x398 -> 192: 137 us with LDS tiles, 92 split; 3x3, 2x56x56x32 -> 64: 10.8 and 6.4.)
+  const int kp = fh * fw * cp, k64 = g.slices * kBK;
+  enum { kDeep, kDirect64x64, kDirect32x64, k64x64, k64x128, k128x128, kForms };
+  const int deep_n = deep_two_columns((g.M + 15) / 16, co, (kp + 31) / 32) ? 32 : 16, odd = aligned ? 0 : 1;
+  const double us[kForms] = {1.05 * PipeCost{16, deep_n, 3.42, .019, .0021, .89, 1.31, .05, 1.45}.us(1, g.M, co, kp, odd),
+                             co >= 2 ? PipeCost{64, 64, .79, 3.94, .0064, .65, .87, .30, .86}.us(1, g.M, co, kp, odd) : 1e30,
+                             co >= 2 ? PipeCost{32, 64, 1.51, 2.78, .0074, .24, .37, .31, .015, .0014}.us(1, g.M, co, kp, odd) : 1e30,
+                             PipeCost{64, 64, 4.04, .74, .0054, .34, .50, .77, .69}.us(1, g.M, co, k64, odd),
+                             PipeCost{64, 128, 3.19, 1.55, .0065, .57, .69, .72, .67}.us(1, g.M, co, k64, odd),
+                             PipeCost{128, 128, 4.52, 1.11, .0082, .72, .99, .50, .52, .0001}.us(1, g.M, co, k64, odd)};
+  int form = 0;
+  for (int f = 1; f < kForms; ++f)
+    if (us[f] < us[form]) form = f;
+  if (form == kDeep) return launch_conv2d_deep_f16(x, w, bias, y, n, h, wd, ci, fh, fw, co, oh, ow, sh, sw, pt, pl, act, stream);
+  if (form == kDirect64x64 || form == kDirect32x64)
+    return launch_conv2d_gemm_direct_f16(x, w, bias, y, n, h, wd, ci, fh, fw, co, oh, ow, sh, sw, pt, pl, act, stream, form == kDirect32x64);
+  auto tiles = [&](auto loader) {
+    constexpr Form FORM = decltype(loader)::value;
+    if (form == k64x64) return launch<2, 2, 1, 1, FORM>(g, stream);
+    if (form == k64x128) return launch<2, 4, 1, 1, FORM>(g, stream);
+    return launch<2, 4, 2, 1, FORM>(g, stream);
+  };
+  if (!aligned) return tiles(std::integral_constant<Form, kRagged>{});
+  return ci % 64 == 0 && fh * fw <= 32 ? tiles(std::integral_constant<Form, kLean>{}) : tiles(std::integral_constant<Form, kAligned>{});
 }
 
 }  // namespace tfx

@@ -465,19 +465,6 @@ int launch_small(const half_t* a, const half_t* b, half_t* c, const half_t* bias
   return check_launch();
 }
 
-// us = fixed + per_k k + c (per_tile + per_tile_k k) + per_output x 1e6 outputs, where c is 1 up to a tile for each of the 256 CUs
-// and then grows by `share` for a further tile of a CU, of which `round` counts as soon as any CU has it; `odd` operands cost the
-// loads `per_odd` of their share each.
-struct PipeCost {
-  int bm, bn;
-  double fixed, per_tile, per_tile_k, round, share, per_odd, per_output, per_k = 0.;
-  double us(long long batch, long long m, long long n, int k, int odd) const {
-    const double tiles = (double)(batch * ((m + bm - 1) / bm) * ((n + bn - 1) / bn)) / 256., up = (double)(long long)(tiles + .999999);
-    const double c = tiles <= 1. ? 1. : 1. + share * (round * up + (1. - round) * tiles - 1.);
-    return fixed + per_k * k + c * (per_tile + per_tile_k * k * (1. + per_odd * odd)) + per_output * 1e-6 * (double)(batch * m * n);
-  }
-};
-
 }  // namespace
 
 int launch_gemm_f16(const uint16_t* a16, const uint16_t* b16, uint16_t* c16, const uint16_t* bias16, int batch, int m,

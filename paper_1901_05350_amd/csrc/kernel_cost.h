@@ -38,6 +38,19 @@ struct KernelCost {
   }
 };
 
+// us = fixed + per_k k + c (per_tile + per_tile_k k) + per_output x 1e6 outputs, where c is 1 up to a tile for each of the 256 CUs
+// and then grows by `share` for a further tile of a CU, of which `round` counts as soon as any CU has it; `odd` operands cost the
+// loads `per_odd` of their share each.
+struct PipeCost {
+  int bm, bn;
+  double fixed, per_tile, per_tile_k, round, share, per_odd, per_output, per_k = 0.;
+  double us(long long batch, long long m, long long n, int k, int odd) const {
+    const double tiles = (double)(batch * ((m + bm - 1) / bm) * ((n + bn - 1) / bn)) / 256., up = (double)(long long)(tiles + .999999);
+    const double c = tiles <= 1. ? 1. : 1. + share * (round * up + (1. - round) * tiles - 1.);
+    return fixed + per_k * k + c * (per_tile + per_tile_k * k * (1. + per_odd * odd)) + per_output * 1e-6 * (double)(batch * m * n);
+  }
+};
+
 // gemm_deep.hip: two column blocks per workgroup once single ones are more than one for each CU, where a few CUs would have
 // two and the rest wait (halfs: 137 x 1376 x 520, 297 or 153 workgroups, 8.9 and 6.0 us; 376 x 3504 x 168 15.2 and 9.1); a
 // few more of those of 4 wavefronts, up to 8 k-steps, run side by side (floats, 128 x 120 x 600, 304 or 152: 3.1 and 3.3).
