@@ -3,15 +3,19 @@
 // At batch 64 the early blocks are bound by HBM, and as two kernels the depthwise layer's output makes a round
 // trip through memory (103 MB out and in again for 56 x 56 x 128) that costs as much as the block's own input and
 // output.  This is the filter-stationary pointwise kernel of pointwise.hip with its operand computed instead of
-// loaded: the pointwise filter lives in LDS ([K][N + 4] floats), the 8 wavefronts of a workgroup take units of the
+// loaded: the pointwise filter lives in LDS, split into bf16 parts (split.h), the 8 wavefronts of a workgroup take units of the
 // output from a counter in LDS, and a unit is a 2 x 8 patch of output pixels of one image -- the 16 columns of the
-// v_mfma_f32_16x16x4_f32 operand.  The wavefront copies the patch's input window, 32 channels at a time (whole
-// 128-byte lines), into a private piece of LDS, and lane (li, q) -- pixel (li / 8, li % 8) of the patch, channels
-// 16 g + 4 q ... + 3 of every group g of 16 -- forms its operand values as the depthwise result of its pixel: 9
-// taps of 16 bytes from the window times the depthwise filter, also from LDS.  The next 32 channels of the window
-// are on their way from memory into registers meanwhile.  (Taking the taps straight from memory instead was
-// measured: 72 loads of 16 half lines each per unit make the texture path the limit.)
-#include "tfx_internal.h"
+// v_mfma_f32_16x16x32_bf16 operand.  The wavefront copies the patch's input window, 32 channels at a time (whole 128-byte lines),
+// into a private piece of LDS, and lane (li, q) -- pixel (li / 8, li % 8) of the patch, channels 16 g + 4 q ... + 3 of every group
+// g of 16 -- forms its operand values as the depthwise result of its pixel: 9 taps of 16 bytes from the window times the
+// depthwise filter, also from LDS.  The next 32 channels of the window are on their way from memory into registers meanwhile.
+// (Taking the taps straight from memory instead was measured: 72 loads of 16 half lines each per unit make the texture path the
+// limit.)
+//
+// Bound by LDS (of a unit of 128 channels 147 KB for the taps, 96 for the filter) and issue.  16 images, 56 x 56 x 128 -> 128: 32.4 us
+// with the fp32 matrix instructions, whose cycles a third of it were, 24.2 with the six bf16 products; 112 x 112 x 64 -> 128 at
+// stride 2 23.0 and 19.7; the pass of 64 images 799 -> 770, of 16 300 -> 290.
+#include "split.h"
 
 #include <type_traits>
 
@@ -64,17 +68,18 @@ __global__ __launch_bounds__(kThreads) void separable_window_kernel(const float*
                                                                     float* __restrict__ y, WindowBlockGeom g, int units,
                                                                     int dw_act, int pw_act) {
   using WL = WindowLayout<S>;
-  constexpr int KG = K / 16, NB = N / 16, LD = N + 4, CH = K / kChunk;
-  constexpr int NBP = NB < 8 ? NB : 8;  // 16-column blocks per pass
+  constexpr int KG = K / 16, KS = K / 32, NB = N / 16, CH = K / kChunk;
   constexpr int PS = WL::PS, RS = WL::RS, WW = WL::WW, LI = WL::kLoads, Q = kChunk / 4;
-  static_assert((K * N / 4) % kThreads == 0 && N <= kThreads && 9 * K / 4 <= kThreads && NB % 2 == 0 && K % kChunk == 0,
-                "staging");
-  // pointwise filter [K][N + 4], its bias [N], depthwise filter [9][K], its bias [K], then one window per wavefront
+  static_assert(KS * NB * 64 % kThreads == 0 && N <= kThreads && 9 * K / 4 <= kThreads && NB % 4 == 0 && K % kChunk == 0, "staging");
+  // pointwise filter, split (split.h) and in the order of the operands, [k-step][block][part][lane] 16 bytes: lane (li, q) has column
+  // 16 j + li, k slot e channel 32 s + 16 (e / 4) + 4 q + e % 4, as the depthwise layer's results come; its bias [N], depthwise
+  // filter [9][K], its bias [K], then one window per wavefront
   extern __shared__ __align__(16) float wl[];
-  float* const pwb_l = wl + K * LD;
+  bf16x8* const pw_l = reinterpret_cast<bf16x8*>(wl);
+  float* const pwb_l = wl + KS * NB * kParts * 256;
   float* const dww_l = pwb_l + N;
   float* const dwb_l = dww_l + 9 * K;
-  __shared__ int next_unit;
+  __shared__ int next_unit, odd_filter;  // odd_filter: 1 where the split lost bits, 2 where a value is large
 
   const int tid = threadIdx.x;
   const int lane = tid % 64, li = lane % 16, q = lane / 16;
@@ -136,20 +141,39 @@ __global__ __launch_bounds__(kThreads) void separable_window_kernel(const float*
   Place pc = place_of(cur < u1 ? cur : u0);
   Offsets oc = offsets_of(pc, cur < u1);
   load_chunk(oc, 0);
+  if (tid == 0) odd_filter = 0;
   {
-    constexpr int PER = K * N / 4 / kThreads;
-    float4 t[PER];
+    constexpr int PER = KS * NB * 64 / kThreads;
+    floatx4 t[PER][2];
 #pragma unroll
-    for (int i = 0; i < PER; ++i) t[i] = reinterpret_cast<const float4*>(pw_w)[tid + i * kThreads];
+    for (int i = 0; i < PER; ++i) {
+      const int f = tid + i * kThreads, l = f % 64, j = f / 64 % NB, st = f / 64 / NB;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) t[i][e / 4][e % 4] = pw_w[(32 * st + 16 * (e / 4) + 4 * (l / 16) + e % 4) * N + 16 * j + l % 16];
+    }
     // (no branches around these loads: a thread past the end reads element 0 and its value is dropped)
     const float4 dwv = reinterpret_cast<const float4*>(dw_w)[tid < 9 * K / 4 ? tid : 0];
     const float pwb = (pw_b ? pw_b : pw_w)[tid < N ? tid : 0];
     const float dwb = (dw_b ? dw_b : pw_w)[tid < K ? tid : 0];
+    __syncthreads();
+    SplitGuard guard;
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
-      const int e = tid + i * kThreads;  // float4 index: row e / (N/4), column quad e % (N/4)
-      *reinterpret_cast<float4*>(wl + (e / (N / 4)) * LD + 4 * (e % (N / 4))) = t[i];
+      const int f = tid + i * kThreads;
+      splitx4 part[2][kParts];
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) guard.most = fabsf(t[i][u][e]) < 0x1p20f ? guard.most : INFINITY;  // (NaN too)
+        guard.split(t[i][u], part[u]);
+      }
+#pragma unroll
+      for (int p = 0; p < kParts; ++p) {
+        const u32x4 both = {part[0][p][0], part[0][p][1], part[1][p][0], part[1][p][1]};
+        pw_l[(f / 64 * kParts + p) * 64 + f % 64] = __builtin_bit_cast(bf16x8, both);
+      }
     }
+    if (guard.lost() || guard.large()) atomicOr(&odd_filter, (guard.lost() ? 1 : 0) | (guard.large() ? 2 : 0));
     if (tid < 9 * K / 4) reinterpret_cast<float4*>(dww_l)[tid] = dwv;
     if (tid < N) pwb_l[tid] = pw_b ? pwb : 0.f;
     if (tid < K) dwb_l[tid] = dw_b ? dwb : 0.f;
@@ -161,25 +185,73 @@ __global__ __launch_bounds__(kThreads) void separable_window_kernel(const float*
   // where this lane's taps start in a window: pixel (li / 8, li % 8) * S, piece q
   const float* const tap0 = win + ((li / 8) * S * RS + (li % 8) * S * PS + q) * 4;
 
-  // W blocks of 16 columns, starting at block jb, of one unit whose operand values are in a[]
-  auto columns = [&](auto wc_, const float4 (&a)[KG], float* ya, float* yb, bool oka, bool okb, int jb) {
-    constexpr int W = decltype(wc_)::value;
-    floatx4 acc[W];
+  const bool filter_lost = (odd_filter & 1) != 0, filter_large = (odd_filter & 2) != 0;
+  // All columns of one unit whose operand values are in a[].  A depthwise output is at most 6 or NaN, which stays one: with a filter
+  // below 2^20 no product overflows, and only bits lost to tiny values are looked for.
+  auto columns = [&](const float4 (&a)[KG], float* ya, float* yb, bool oka, bool okb) {
+    floatx4 acc[NB];
 #pragma unroll
-    for (int j = 0; j < W; ++j) acc[j] = *reinterpret_cast<const floatx4*>(pwb_l + 16 * (jb + j) + 4 * q);
+    for (int j = 0; j < NB; ++j) acc[j] = *reinterpret_cast<const floatx4*>(pwb_l + 16 * j + 4 * q);
+    unsigned low = 0;
 #pragma unroll
-    for (int gg = 0; gg < KG; ++gg) {
-      const float av[4] = {a[gg].x, a[gg].y, a[gg].z, a[gg].w};
+    for (int st = 0; st < KS; ++st) {
+      bf16x8 op[kParts];
+      splitx4 part[2][kParts];
 #pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        const float* wr = wl + (16 * gg + 4 * q + s) * LD + 16 * jb + li;
-#pragma unroll
-        for (int j = 0; j < W; ++j)
-          acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(wr[16 * j], av[s], acc[j], 0, 0, 0);
+      for (int u = 0; u < 2; ++u) {
+        const float4 v = a[2 * st + u];
+        split4(floatx4{v.x, v.y, v.z, v.w}, part[u], low);
       }
-      __builtin_amdgcn_sched_barrier(0);  // keep later groups' LDS reads from being hoisted
+#pragma unroll
+      for (int p = 0; p < kParts; ++p) {
+        const u32x4 both = {part[0][p][0], part[0][p][1], part[1][p][0], part[1][p][1]};
+        op[p] = __builtin_bit_cast(bf16x8, both);
+      }
+#pragma unroll
+      for (int j0 = 0; j0 < NB; j0 += 2) {
+        bf16x8 fw[2][kParts];
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+          for (int p = 0; p < kParts; ++p) fw[j][p] = pw_l[((st * NB + j0 + j) * kParts + p) * 64 + lane];
+#pragma unroll
+        for (int s = 0; s < kSplitPasses; ++s)
+#pragma unroll
+          for (int j = 0; j < 2; ++j)
+            acc[j0 + j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[j][split_pass_b(s)], op[split_pass_a(s)], acc[j0 + j], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);  // keep later blocks' LDS reads from being hoisted
+      }
     }
-    store_rows_biased<W>(acc, ya + 16 * jb, yb + 16 * jb, oka, okb, li, q, pw_clamp);
+    const float limit = small_limit(K);
+    bool small = false;
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) small = small || fabsf(acc[j][e]) < limit;
+    const bool lost = filter_lost || __builtin_amdgcn_ballot_w64((low & 0xffffu) != 0) != 0;
+    store_rows_biased<NB>(acc, ya, yb, oka, okb, li, q, pw_clamp);
+    if (filter_large || (lost && __builtin_amdgcn_ballot_w64(small) != 0)) {
+      // small results (with a large filter: all) again with the fp32 instructions, and over the first ones
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      float* const yp = li < 8 ? ya : yb;  // this lane's pixel
+      const __amdgpu_buffer_rsrc_t wr = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(pw_w), 0, 4 * K * N, 0x00020000);
+#pragma unroll 1
+      for (int j = 0; j < NB; ++j) {
+        floatx4 exact = *reinterpret_cast<const floatx4*>(pwb_l + 16 * j + 4 * q);
+#pragma unroll
+        for (int gg = 0; gg < KG; ++gg) {
+          const float av[4] = {a[gg].x, a[gg].y, a[gg].z, a[gg].w};
+#pragma unroll
+          for (int s = 0; s < 4; ++s)
+            exact = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(wr, 4 * (4 * q * N + 16 * j + li), 4 * (16 * gg + s) * N, 0)),
+                                                         av[s], exact, 0, 0, 0);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if ((li < 8 ? oka : okb) && (filter_large || fabsf(exact[e]) < limit)) yp[16 * j + 4 * q + e] = apply_act(exact[e], pw_clamp);
+      }
+    }
   };
 
   // the first chunk of a unit's window is requested before the MFMAs of the unit before it
@@ -237,9 +309,7 @@ __global__ __launch_bounds__(kThreads) void separable_window_kernel(const float*
     float* const ya = y + ((size_t)(pc.n * g.OH + oh) * g.OW + ow) * N;
     float* const yb = ya + (size_t)g.OW * N;
     const bool oka = ow < g.OW, okb = oka && oh + 1 < g.OH;
-#pragma unroll
-    for (int pp = 0; pp < NB / NBP; ++pp)  // column passes of at most 128 columns keep the accumulators few
-      columns(std::integral_constant<int, NBP>{}, a, ya, yb, oka, okb, NBP * pp);
+    columns(a, ya, yb, oka, okb);
     cur = nxt;
     pc = pn;
     oc = on;
@@ -249,7 +319,7 @@ __global__ __launch_bounds__(kThreads) void separable_window_kernel(const float*
 template <int K, int N, int S>
 int launch_cfg(const float* x, const float* dw_w, const float* dw_b, const float* pw_w, const float* pw_b, float* y,
                const WindowBlockGeom& g, int units, int dw_act, int pw_act, hipStream_t stream) {
-  constexpr size_t lds_bytes = ((size_t)K * (N + 4) + N + 10 * K + (size_t)kWaves * WindowLayout<S>::kFloats) * sizeof(float);
+  constexpr size_t lds_bytes = ((size_t)K / 32 * (N / 16) * kParts * 256 + N + 10 * K + (size_t)kWaves * WindowLayout<S>::kFloats) * sizeof(float);
   static_assert(lds_bytes + 64 <= 160 * 1024, "LDS budget per workgroup");
   auto kern = separable_window_kernel<K, N, S>;
   static std::atomic<uint64_t> lds_allowed{0};
@@ -290,7 +360,7 @@ int launch_separable_stream(const float* x, const float* dw_w, const float* dw_b
   const WindowBlockGeom g{h, w, oh, ow, pt, pl, (ow + kPatchW - 1) / kPatchW, (oh + kPatchH - 1) / kPatchH,
                           (unsigned)((long long)batch * h * w * c * 4)};
   const long long units = (long long)batch * g.tiles_c * g.tiles_r;
-  if (units > 0x3fffffffLL) return TFX_ERR_UNSUPPORTED;
+  if (units > 0x3fffffffLL || dw_act != TFX_ACT_RELU6) return TFX_ERR_UNSUPPORTED;  // (the split counts on outputs of at most 6)
 #define TFX_WINDOW_BLOCK(C, NN, SS) \
   if (c == C && n == NN && stride == SS) \
     return launch_cfg<C, NN, SS>(x, dw_w, dw_b, pw_w, pw_b, y, g, (int)units, dw_act, pw_act, stream);

@@ -1,0 +1,46 @@
+"""fp32 blocks whose split filter stays in LDS (block_stream.hip): values that the split into bf16 parts does not carry."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_1901_05350_amd import inputs
+from util import assert_close, dev, host
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("block", [2, 3])
+@pytest.mark.parametrize("what,value", [("none", 0), ("filter", np.nan), ("filter", np.inf), ("filter", 3.4e38), ("filter", 2.0 ** 20),
+                                        ("filter", 1e-36), ("filter", 1e-43), ("column", 2.0 ** -118), ("maps", 2.0 ** -116),
+                                        ("maps", 2.0 ** -131), ("maps", 2.0 ** -140)])
+def test_values_outside_the_split(block, what, value):
+    """A filter value, a whole column of the pointwise filter, or the depthwise outputs that feed a column; 25 x 25 maps, so the
+    last patches are ragged; NaNs from the image."""
+    import paper_1901_05350_amd as tfx
+    batch = 30  # more patches than workgroups of block_patch.hip are resident, fewer than two chains of kernels are for
+    d = inputs.mobilenet_v1(seed=97, batch=2, image_size=100, classes=10)
+    w, b = d["weights"], block - 1
+    d["image"][1, 50, 31, 1] = np.nan
+    if what == "filter":
+        w["pw_w"][b][0, 0, 17, 33] = value
+    if what == "column":
+        w["pw_w"][b][0, 0, :, 33] *= value
+        w["pw_b"][b][33] = 0
+    if what == "maps":
+        w["dw_w"][b][:, :, 5], w["dw_b"][b][5] = np.abs(w["dw_w"][b][:, :, 5]) * value, 0
+        w["pw_w"][b][0, 0, :, 33], w["pw_b"][b][33] = 0, 0
+        w["pw_w"][b][0, 0, 5, 33] = 3
+    _, _, acts = oracle.mobilenet_v1_forward(d["image"], w, return_activations=True)
+    image = np.concatenate([d["image"]] * (batch // 2))
+    got = host(tfx.MobileNetV1(w, batch=batch, image_size=100).features(dev(image), block))
+    bits = got.view(np.uint32).reshape(-1, 2, *got.shape[1:])
+    assert np.array_equal(bits.min(axis=0), bits[0]) and np.array_equal(bits.max(axis=0), bits[0])
+    got, ref = got[:2], acts[2 * block]
+    assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.isnan(ref).any()
+    keep = ~np.isnan(ref)
+    assert_close(got[keep], ref[keep], what)
+    if what in ("column", "maps"):
+        g, r = got[..., 33][keep[..., 33]], ref[..., 33][keep[..., 33]]
+        assert (r != 0).any()
+        # roundings of up to 128 products to 24 bits, or of a sum of nine to the smallest float (then times 3)
+        assert np.all(np.abs(g.astype(np.float64) - r) <= np.maximum(1e-5 * value * 16, 128 * 2.0 ** -149))
