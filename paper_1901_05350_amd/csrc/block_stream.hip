@@ -14,7 +14,8 @@
 //
 // Bound by LDS (of a unit of 128 channels 147 KB for the taps, 96 for the filter) and issue.  16 images, 56 x 56 x 128 -> 128: 32.4 us
 // with the fp32 matrix instructions, whose cycles a third of it were, 24.2 with the six bf16 products; 112 x 112 x 64 -> 128 at
-// stride 2 23.0 and 19.7; the pass of 64 images 799 -> 770, of 16 300 -> 290.
+// stride 2 23.0 and 19.7; the pass of 64 images 799 -> 770, of 16 300 -> 290.  Block 3 of the 3/4 width and blocks 2 and 3 of the half
+// width, as two launches before: the pass of 20 images 289 -> 279 and 204 -> 190.
 #include "split.h"
 
 #include <type_traits>
@@ -70,7 +71,7 @@ __global__ __launch_bounds__(kThreads) void separable_window_kernel(const float*
   using WL = WindowLayout<S>;
   constexpr int KG = K / 16, KS = K / 32, NB = N / 16, CH = K / kChunk;
   constexpr int PS = WL::PS, RS = WL::RS, WW = WL::WW, LI = WL::kLoads, Q = kChunk / 4;
-  static_assert(KS * NB * 64 % kThreads == 0 && N <= kThreads && 9 * K / 4 <= kThreads && NB % 4 == 0 && K % kChunk == 0, "staging");
+  static_assert(N <= kThreads && 9 * K / 4 <= kThreads && NB % 2 == 0 && K % kChunk == 0, "staging");
   // pointwise filter, split (split.h) and in the order of the operands, [k-step][block][part][lane] 16 bytes: lane (li, q) has column
   // 16 j + li, k slot e channel 32 s + 16 (e / 4) + 4 q + e % 4, as the depthwise layer's results come; its bias [N], depthwise
   // filter [9][K], its bias [K], then one window per wavefront
@@ -143,11 +144,11 @@ __global__ __launch_bounds__(kThreads) void separable_window_kernel(const float*
   load_chunk(oc, 0);
   if (tid == 0) odd_filter = 0;
   {
-    constexpr int PER = KS * NB * 64 / kThreads;
+    constexpr int PIECES = KS * NB * 64, PER = (PIECES + kThreads - 1) / kThreads;
     floatx4 t[PER][2];
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
-      const int f = tid + i * kThreads, l = f % 64, j = f / 64 % NB, st = f / 64 / NB;
+      const int f = PIECES % kThreads == 0 || tid + i * kThreads < PIECES ? tid + i * kThreads : 0, l = f % 64, j = f / 64 % NB, st = f / 64 / NB;
 #pragma unroll
       for (int e = 0; e < 8; ++e) t[i][e / 4][e % 4] = pw_w[(32 * st + 16 * (e / 4) + 4 * (l / 16) + e % 4) * N + 16 * j + l % 16];
     }
@@ -160,6 +161,7 @@ __global__ __launch_bounds__(kThreads) void separable_window_kernel(const float*
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
       const int f = tid + i * kThreads;
+      if (PIECES % kThreads != 0 && f >= PIECES) break;
       splitx4 part[2][kParts];
 #pragma unroll
       for (int u = 0; u < 2; ++u) {
@@ -342,11 +344,11 @@ int launch_cfg(const float* x, const float* dw_w, const float* dw_b, const float
 
 }  // namespace
 
-// Blocks (channels -> filters, stride) of the full-width network's 56 x 56 maps, many output pixels
-// (below that the two single-op kernels' tiles win), 16-byte aligned operands, an input below 2^31 bytes.
+// Blocks 2 and 3 (channels -> filters, stride) of the full-width network, 3 of the 3/4 width, 2, 3, 4 and 5 of the half width, many
+// output pixels (below that the two single-op kernels' tiles win), 16-byte aligned operands, an input below 2^31 bytes.
 bool separable_stream_supported(int batch, int h, int w, int c, int n, int stride, int oh, int ow, const void* x,
                                 const void* dw_w, const void* dw_b, const void* pw_w, const void* pw_b, const void* y) {
-  const bool shape = (c == 128 && n == 128 && stride == 1) || (c == 64 && n == 128 && stride == 2);
+  const bool shape = stride == 1 ? c == n && (c == 64 || c == 96 || c == 128) : n == 2 * c && (c == 32 || c == 64);
   const void* ptrs[] = {x, dw_w, dw_b, pw_w, pw_b, y};
   bool aligned = true;
   for (const void* p : ptrs) aligned = aligned && reinterpret_cast<uintptr_t>(p) % 16 == 0;
@@ -366,6 +368,9 @@ int launch_separable_stream(const float* x, const float* dw_w, const float* dw_b
     return launch_cfg<C, NN, SS>(x, dw_w, dw_b, pw_w, pw_b, y, g, (int)units, dw_act, pw_act, stream);
   TFX_WINDOW_BLOCK(128, 128, 1)
   TFX_WINDOW_BLOCK(64, 128, 2)
+  TFX_WINDOW_BLOCK(96, 96, 1)
+  TFX_WINDOW_BLOCK(64, 64, 1)
+  TFX_WINDOW_BLOCK(32, 64, 2)
 #undef TFX_WINDOW_BLOCK
   return TFX_ERR_UNSUPPORTED;
 }

@@ -44,3 +44,19 @@ def test_values_outside_the_split(block, what, value):
         assert (r != 0).any()
         # roundings of up to 128 products to 24 bits, or of a sum of nine to the smallest float (then times 3)
         assert np.all(np.abs(g.astype(np.float64) - r) <= np.maximum(1e-5 * value * 16, 128 * 2.0 ** -149))
+
+
+@pytest.mark.parametrize("q,size,blocks", [(2, 224, (2, 3)), (2, 203, (2, 3)), (3, 224, (3,)), (3, 195, (3,))])
+def test_other_widths(q, size, blocks):
+    """3/4 and half width against the oracle's maps, first and last image: ragged patches, a NaN's positions."""
+    import paper_1901_05350_amd as tfx
+    d = inputs.mobilenet_v1(seed=99, batch=2, image_size=size, width_quarters=q, classes=10)
+    d["image"][1, 60, 37, 1] = np.nan
+    _, _, acts = oracle.mobilenet_v1_forward(d["image"], d["weights"], return_activations=True)
+    model = tfx.MobileNetV1(d["weights"], batch=31, image_size=size, width_quarters=q)
+    image = dev(np.concatenate([d["image"][:1]] * 30 + [d["image"][1:]]))
+    for k in blocks:
+        got, ref = host(model.features(image, k))[[0, -1]], acts[2 * k]
+        assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.isnan(ref).any()
+        keep = ~np.isnan(ref)
+        assert_close(got[keep], ref[keep], "block %d" % k)
