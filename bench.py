@@ -31,21 +31,21 @@ PEAK_HBM = 8.0e12          # B/s
 # source it was measured on, with the digest of that file followed by the shared headers csrc/tfx_internal.h and
 # csrc/stream_f16.h; if any of them has changed since, the entry is reported as null.
 MEASURED_TRAFFIC = {
-    "batch_matmul_8x1024x1024x1024_tB": (100948049, "gemm.hip", "ee000851d7d5260abb5d10fcf7891d61b4c28fdd2acd02e94e51c17813776421"),
-    "pointwise_64x56x56x128_to_128": (206181418, "pointwise.hip", "1637e827044860fec32ccf74a12b605ca8ed91979354dfadbb93414a029ec82d"),
-    "conv3x3_64x56x56x64_to_64": (106084848, "gemm.hip", "ee000851d7d5260abb5d10fcf7891d61b4c28fdd2acd02e94e51c17813776421"),
-    "depthwise_64x112x112x64_s1_cold_rotation": (411139872, "depthwise.hip", "76bed0fac2cbea969f1ba4f325eeee395e641a680de5122b521f4df0b9c19c11"),
-    "depthwise_64x112x112x64_s2_cold_rotation": (257134394, "depthwise.hip", "76bed0fac2cbea969f1ba4f325eeee395e641a680de5122b521f4df0b9c19c11"),
-    "batch_matmul_f16_1x4096x4096x4096_tB": (235157353, "gemm_f16.hip", "e6a2173ed81b175fb73ee7060b12dfe5ae10f608d5047a0a6555fc256046f3a5"),
-    "batch_matmul_f16_8x1024x1024x1024_tB": (50540796, "gemm_f16.hip", "e6a2173ed81b175fb73ee7060b12dfe5ae10f608d5047a0a6555fc256046f3a5"),
-    "pointwise_f16_64x56x56x128_to_128": (104309503, "pointwise_f16.hip", "99ea7211fd61f80abe0a9ebc195f73ceff7204c28282c23baffa4db5e9214605"),
-    "depthwise_f16_64x112x112x64_s1_cold_rotation": (205682558, "conv_f16.hip", "b6b68ed458b6e2d1a33aa925f8bd7ee19660df6f20e6b004ceccc30cf7010b44"),
-    "depthwise_f16_64x112x112x64_s2_cold_rotation": (128559845, "conv_f16.hip", "b6b68ed458b6e2d1a33aa925f8bd7ee19660df6f20e6b004ceccc30cf7010b44"),
-    "pointwise_f16_64x14x14x512_to_512": (30190477, "pointwise_slab_f16.hip", "5d72071505f1671435a2d01d1274c5b416151f856d5c093ed8c91f6c00bf9dd9"),
-    "conv3x3_f16_64x56x56x64_to_64": (55026548, "conv_stream_f16.hip", "8d59dfe37f6d634755008a7a6791dd3ec02d89b6048ee5767a8b35054e14c6b9"),
-    "add_f32_64M": (805263867, "elementwise.hip", "33fca024b6a991f3cdd869bbf66c5939110817e5e34fedeeaa7d6a0b91a1d7e6"),
-    "add_f16_64M": (402652251, "elementwise.hip", "33fca024b6a991f3cdd869bbf66c5939110817e5e34fedeeaa7d6a0b91a1d7e6"),
-    "mobilenet_chain_kernel": (121649614, "chain.hip", "8f3eea3b0d8cf50f90edbdb0675c7edf60557fa622870fc839625a7718df8aab"),
+    "batch_matmul_8x1024x1024x1024_tB": (100947899, "gemm.hip", "5d58a535bead5c0919e3cc01afc446a3657cb135f771ae87a7bfae029fc98fca"),
+    "pointwise_64x56x56x128_to_128": (206181168, "pointwise.hip", "15d93d82fa9855c64b19908193d2cd50472e6e0aba20d65e784f74a96f0b76e5"),
+    "conv3x3_64x56x56x64_to_64": (106652563, "conv_window.hip", "da4c2bb7673a158ed1029692e76aebffca0bb00a977a28de83170707e5a30315"),
+    "depthwise_64x112x112x64_s1_cold_rotation": (411140572, "depthwise.hip", "faedd1558bbc91575c992934a882ba2827bca5bcf50bf0361d4f737b544afc97"),
+    "depthwise_64x112x112x64_s2_cold_rotation": (257145503, "depthwise.hip", "faedd1558bbc91575c992934a882ba2827bca5bcf50bf0361d4f737b544afc97"),
+    "batch_matmul_f16_1x4096x4096x4096_tB": (235162171, "gemm_f16.hip", "12967e0ef63acda6db5a836f2e9e6caf11ef871f97b3eb8f7678e68b8b10582e"),
+    "batch_matmul_f16_8x1024x1024x1024_tB": (50885674, "gemm_f16.hip", "12967e0ef63acda6db5a836f2e9e6caf11ef871f97b3eb8f7678e68b8b10582e"),
+    "pointwise_f16_64x56x56x128_to_128": (104331846, "pointwise_f16.hip", "914971820db49cc6c33ee2f0a1a3bf498dcfd8b7fd45c2e221b4f84075549b47"),
+    "depthwise_f16_64x112x112x64_s1_cold_rotation": (205682544, "conv_f16.hip", "3f776b145bebe4e56af24b2edc230d10fafb73579dd8482dbe01e8033628ddba"),
+    "depthwise_f16_64x112x112x64_s2_cold_rotation": (128537256, "conv_f16.hip", "3f776b145bebe4e56af24b2edc230d10fafb73579dd8482dbe01e8033628ddba"),
+    "pointwise_f16_64x14x14x512_to_512": (30192691, "pointwise_slab_f16.hip", "04f1aca7e65ba8ddd3e6e2a599a06f13adb80217bf944f78c3686fbd8ee22315"),
+    "conv3x3_f16_64x56x56x64_to_64": (55026527, "conv_stream_f16.hip", "cd29657bc09dc346908b8ea9bf450dcaf7bfe2085bb1046fb56db7a35cc14d36"),
+    "add_f32_64M": (805262912, "elementwise.hip", "5e53ad68fa684d685e5f837182507b289fc42bf11e36fede0ff5d76985fb795d"),
+    "add_f16_64M": (402652013, "elementwise.hip", "5e53ad68fa684d685e5f837182507b289fc42bf11e36fede0ff5d76985fb795d"),
+    "mobilenet_chain_kernel": (121645600, "chain.hip", "38ff325e754f6350b2aa41788a6568b567baf561fc1cba16a01eafd061cc3618"),
 }
 
 
