@@ -504,7 +504,7 @@ int forward_impl(const tfx_mobilenet_v1_variant* variant, const float* input, in
   // Batch 1: the blocks from the last 1/8-size map on, the pool, the fully connected layer and the
   // softmax run as one persistent kernel (chain.hip) when every pointer allows its vector loads and 256 of its
   // workgroups are resident at once on this device; its task flags are cleared by the first kernel of the pass
-  // (the stem, alone or fused with block 1).
+  // (the stem of launch_conv2d_stem or of launch_stem_block; launch_stem_block_rows clears none).
   bool flags_ok = plan.chain;  // the workspace has the flag region, and the kernels that use it may run
   if (flags_ok) {
     auto al16 = [](const void* p) { return reinterpret_cast<uintptr_t>(p) % 16 == 0; };
@@ -517,6 +517,7 @@ int forward_impl(const tfx_mobilenet_v1_variant* variant, const float* input, in
   // blocks 2 - 4 as stages of one launch and block 5 as a launch (block.hip): in the whole pass and when block 4's
   // or block 5's output is asked for
   const bool head_chain = flags_ok && plan.head && (end_block == 0 || end_block == 4 || end_block == 5);
+  bool flags_cleared = false;  // by the first kernel, for the launches that wait for flags
   void* chain_ws = ws + plan.off_chain;
 
   // stem: 3x3 stride-2 convolution to 32 alpha channels, then the 13 depthwise-separable blocks
@@ -540,12 +541,14 @@ int forward_impl(const tfx_mobilenet_v1_variant* variant, const float* input, in
                            chain || head_chain ? chain_flag_words((int)variant->image_size, (int)variant->classes, q) : 0,
                            chain_flag_stride());
     first_block = 1;
-  } else if (chain)
+    flags_cleared = chain || head_chain;
+  } else if (chain) {
     rc = launch_conv2d_stem(input, weights->conv0_w, weights->conv0_b, buf[0], 1, (int)shape[1], (int)shape[2],
                             (int)f0[3], (int)g.out[1], (int)g.out[2], 2, 2, (int)g.pad[0], (int)g.pad[2], TFX_ACT_RELU6,
                             static_cast<hipStream_t>(stream), static_cast<int*>(chain_ws),
                             chain_flag_words((int)variant->image_size, (int)variant->classes, q), chain_flag_stride());
-  else {
+    flags_cleared = true;
+  } else {
     // stem and first block in one launch that walks down rows (block_rows.hip)
     rc = launch_stem_block_rows(input, weights->conv0_w, weights->conv0_b, weights->dw_w[0], weights->dw_b[0], weights->pw_w[0],
                                 weights->pw_b[0], end_block == 1 ? features : buf[0], (int)batch, (int)shape[1], (int)shape[2],
@@ -558,7 +561,7 @@ int forward_impl(const tfx_mobilenet_v1_variant* variant, const float* input, in
   if (first_block == 1 && end_block == 1) return TFX_OK;
   int cur = 0;
   const int head_flags = block_chain_flag_words((int)shape[1], (int)shape[2]);
-  if (head_chain && first_block == 1) {
+  if (head_chain && flags_cleared && first_block == 1) {
     // blocks 2 - 4 as three stages of one launch, block 5 as a launch of its own, then the chained kernel from block 6
     // on; flags (cleared by the first kernel) and failure word are shared with it
     const size_t quarter = (size_t)((shape[1] + 1) / 2), eighth = (quarter + 1) / 2;
