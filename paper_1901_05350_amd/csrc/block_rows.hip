@@ -259,13 +259,17 @@ __global__ __launch_bounds__(512, 2) void stem_block_rows_kernel(RowsArgs g) {
   }
 }
 
+constexpr int kRowsMaxWidth = 128;  // columns of the map: 8 wavefronts of 16
+
 template <int Q>
 int launch_rows(const RowsArgs& g, int batch, hipStream_t stream) {
   auto kern = stem_block_rows_kernel<Q>;
   const int tiles = (g.OW + 15) / 16;
-  const size_t lds_bytes = (size_t)4 * (16 * tiles + 2) * 16 * rows_pixel_pieces<(8 * Q + 15) / 16>();
+  // The kernel is allowed once what its widest rows need: a later call may be wider than the first.
+  constexpr size_t column = (size_t)4 * 16 * rows_pixel_pieces<(8 * Q + 15) / 16>(), most = (kRowsMaxWidth + 2) * column;
+  const size_t lds_bytes = (16 * tiles + 2) * column;
   static std::atomic<uint64_t> lds_allowed{0};
-  if (allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds_bytes, lds_allowed) != TFX_OK) return TFX_ERR_LAUNCH;
+  if (allow_dynamic_lds(reinterpret_cast<const void*>(kern), most, lds_allowed) != TFX_OK) return TFX_ERR_LAUNCH;
   hipLaunchKernelGGL(kern, dim3((unsigned)(batch * g.strips)), dim3(64u * tiles), lds_bytes, stream, g);
   return check_launch();
 }
@@ -276,7 +280,7 @@ int launch_stem_block_rows(const float* image, const float* st_w, const float* s
                            const float* pw_b, float* y, int batch, int ih, int iw, int oh, int ow, int pt, int pl, int q,
                            hipStream_t stream) {
   const long long in = (long long)ih * iw * 3, out = (long long)oh * ow * 16 * q;  // floats of an image
-  if (ow > 128 || iw < 3 || ih < 3 || reinterpret_cast<uintptr_t>(y) % 16 != 0) return TFX_ERR_UNSUPPORTED;
+  if (ow > kRowsMaxWidth || iw < 3 || ih < 3 || reinterpret_cast<uintptr_t>(y) % 16 != 0) return TFX_ERR_UNSUPPORTED;
   const int tiles = (ow + 15) / 16, slots = 256 * ((q <= 2 ? 16 : 8) / tiles > 0 ? (q <= 2 ? 16 : 8) / tiles : 1);
   // byte offsets of a launch stay below 2^31
   const long long most = ((1ll << 29) - 1) / (in > out ? in : out);

@@ -386,7 +386,8 @@ inline int check_launch() { return hipGetLastError() == hipSuccess ? TFX_OK : TF
 
 // A kernel that uses more than 64 KB of dynamic LDS has to be allowed to, once per device (the attribute
 // belongs to the kernel's code object on the current device).  `done` is the caller's per-kernel bitmask of
-// the devices already set up; callers launch on the current device.  Safe to call from several threads.
+// the devices already set up, so `bytes` has to be the most that any launch of the kernel asks for, not what this one does;
+// callers launch on the current device.  Safe to call from several threads.
 inline int allow_dynamic_lds(const void* kernel, size_t bytes, std::atomic<uint64_t>& done) {
   if (bytes <= 64 * 1024) return TFX_OK;
   int dev = 0;

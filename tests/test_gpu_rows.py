@@ -30,6 +30,18 @@ def test_stem_and_first_block(q, size, batch):
     assert_close(got[keep], ref[keep], "stem and block 1")
 
 
+@pytest.mark.parametrize("q", [3, 4])
+def test_wider_image_after_a_narrower_one(q):
+    """The LDS of a launch follows the image's width, 73 KB at 224 pixels and 83 KB at 256: the call that a process makes first
+    must not set the limit of the later ones."""
+    import paper_1901_05350_amd as tfx
+    for size in (224, 256, 193):
+        d = inputs.mobilenet_v1(seed=96, batch=2, image_size=size, width_quarters=q, classes=10)
+        _, _, acts = oracle.mobilenet_v1_forward(d["image"], d["weights"], return_activations=True)
+        model = tfx.MobileNetV1(d["weights"], batch=2, image_size=size, width_quarters=q)
+        assert_close(host(model.features(dev(d["image"]), 1)), acts[2], "%d pixels" % size)
+
+
 @pytest.mark.parametrize("what,value", [("filter", np.nan), ("filter", np.inf), ("filter", 3.4e38), ("filter", 2.0 ** 20), ("filter", 1e-36),
                                         ("filter", 1e-43), ("column", 2.0 ** -118), ("maps", 2.0 ** -116), ("maps", 2.0 ** -131),
                                         ("maps", 2.0 ** -140)])
