@@ -529,12 +529,12 @@ int forward_impl(const tfx_mobilenet_v1_variant* variant, const float* input, in
   int first_block = 0;
   const int64_t c0 = kChannels[0] * q / 4;
   if (batch == 1 &&
-      stem_block_supported(batch, (int)shape[1], (int)shape[2], (int)f0[3], (int)c0, input, weights->conv0_w,
+      stem_block_supported((int)shape[1], (int)shape[2], (int)f0[3], (int)c0, input, weights->conv0_w,
                            weights->conv0_b, weights->dw_w[0], weights->dw_b[0], weights->pw_w[0], weights->pw_b[0],
                            end_block == 1 ? features : buf[0])) {
     // one image: stem and first block in one launch of patches (block.hip), which also clears the chain's task flags
     rc = launch_stem_block(input, weights->conv0_w, weights->conv0_b, weights->dw_w[0], weights->dw_b[0],
-                           weights->pw_w[0], weights->pw_b[0], end_block == 1 ? features : buf[0], (int)batch, (int)shape[1],
+                           weights->pw_w[0], weights->pw_b[0], end_block == 1 ? features : buf[0], (int)shape[1],
                            (int)shape[2], (int)g.out[1],
                            (int)g.out[2], (int)g.pad[0], (int)g.pad[2], (int)c0, TFX_ACT_RELU6,
                            static_cast<hipStream_t>(stream), chain || head_chain ? static_cast<int*>(chain_ws) : nullptr,

@@ -1,6 +1,6 @@
 // One depthwise-separable block (depthwise 3x3 + bias + clamp, then pointwise 1x1 + bias + clamp) of one to three
 // images as ONE kernel, for the early, thin blocks of the MobileNet v1 timed in Section 3.9 / Table 1 at batch 1, where
-// the two layers are bound by being two dependent launches and not by traffic or arithmetic.  A second form also
+// the two layers are bound by being two dependent launches and not by traffic or arithmetic.  A second form, of one image, also
 // computes the network's stem inside the first block's kernel (STEM below); and blocks 2 - 4 of the batch-1 network
 // run as three stages of one launch that hand their patches over through flags (separable_chain_kernel).
 //
@@ -462,23 +462,23 @@ int launch_separable_block(const float* x, const float* dw_w, const float* dw_b,
   return TFX_ERR_UNSUPPORTED;
 }
 
-bool stem_block_supported(long long batch, int ih, int iw, int stem_filters, int n, const void* image, const void* st_w,
+bool stem_block_supported(int ih, int iw, int stem_filters, int n, const void* image, const void* st_w,
                           const void* st_b, const void* dw_w, const void* dw_b, const void* pw_w, const void* pw_b,
                           const void* y) {
   auto al16 = [](const void* p) { return reinterpret_cast<uintptr_t>(p) % 16 == 0; };
-  return batch >= 1 && batch <= kMaxFusedBatch && stem_filters == 32 && n == 64 && ih >= 1 && iw >= 1 && (long long)ih * iw * 3 * 4 < (1ll << 31) &&
+  return stem_filters == 32 && n == 64 && ih >= 1 && iw >= 1 && (long long)ih * iw * 3 * 4 < (1ll << 31) &&
          al16(image) && al16(st_w) && al16(st_b) && al16(dw_w) && al16(dw_b) && al16(pw_w) && al16(pw_b) && al16(y);
 }
 
 int launch_stem_block(const float* image, const float* st_w, const float* st_b, const float* dw_w, const float* dw_b,
-                      const float* pw_w, const float* pw_b, float* y, int batch, int ih, int iw, int h, int w, int st_pt,
+                      const float* pw_w, const float* pw_b, float* y, int ih, int iw, int h, int w, int st_pt,
                       int st_pl, int n, int act, hipStream_t stream, int* zero_words, int zero_count, int zero_stride) {
   BlockArgs a;
   a.x = image, a.dw_w = dw_w, a.dw_b = dw_b, a.pw_w = pw_w, a.pw_b = pw_b, a.y = y;
   // the block: 3x3 stride-1 depthwise layer with SAME padding (one zero row / column before the map), then 32 -> n
   a.H = h, a.W = w, a.OH = h, a.OW = w, a.pt = 1, a.pl = 1, a.N = n;
   a.dw_act = act, a.pw_act = act;
-  a.batch = batch;
+  a.batch = 1;
   a.x_bytes = (unsigned)((long long)ih * iw * 3 * 4);
   a.x_img = (long long)ih * iw * 3;
   a.tiles_x = a.tiles_img = a.slices = a.total = 0;

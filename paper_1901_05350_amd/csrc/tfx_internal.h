@@ -243,13 +243,13 @@ int launch_separable_block(const float* x, const float* dw_w, const float* dw_b,
                            int dw_act, int pw_act, hipStream_t stream);
 
 // The stem (3x3 stride-2 convolution of the image [ih, iw, 3] to 32 channels, [h, w, 32]) and the first
-// depthwise-separable block (stride 1, 32 -> n = 64 channels) of up to three images in one launch; every layer with
+// depthwise-separable block (stride 1, 32 -> n = 64 channels) of one image in one launch; every layer with
 // bias + the activation `act`.  zero_words: as for launch_conv2d_stem.
-bool stem_block_supported(long long batch, int ih, int iw, int stem_filters, int n, const void* image, const void* st_w,
+bool stem_block_supported(int ih, int iw, int stem_filters, int n, const void* image, const void* st_w,
                           const void* st_b, const void* dw_w, const void* dw_b, const void* pw_w, const void* pw_b,
                           const void* y);
 int launch_stem_block(const float* image, const float* st_w, const float* st_b, const float* dw_w, const float* dw_b,
-                      const float* pw_w, const float* pw_b, float* y, int batch, int ih, int iw, int h, int w, int st_pt,
+                      const float* pw_w, const float* pw_b, float* y, int ih, int iw, int h, int w, int st_pt,
                       int st_pl, int n, int act, hipStream_t stream, int* zero_words, int zero_count, int zero_stride);
 
 // Depthwise convolution: generic kernel and the 3x3 / multiplier-1 / C%4==0 fast path.
