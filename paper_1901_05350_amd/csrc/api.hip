@@ -607,9 +607,9 @@ int forward_impl(const tfx_mobilenet_v1_variant* variant, const float* input, in
     const int64_t fd[4] = {3, 3, shape[3], 1};
     const int64_t cout = kChannels[b] * q / 4;
     conv_geometry(shape, fd, kStrides[b], kStrides[b], TFX_PAD_SAME, true, &g);
-    // few pixels: depthwise and pointwise layer in one launch, a workgroup per patch (block_patch.hip); one image whose pass is
-    // chained keeps the kernels of the chain's order
-    if ((batch > 1 || !plan.chain) && separable_patch_pays((int)batch, (int)shape[3], (int)cout, kStrides[b], (int)g.out[1], (int)g.out[2]) &&
+    // few pixels, two images or more: depthwise and pointwise layer in one launch, a workgroup per patch (block_patch.hip).  One
+    // image's pass is chained; where it stops at a feature map or may not be chained, it takes the kernels below.
+    if (batch > 1 && separable_patch_pays((int)batch, (int)shape[3], (int)cout, kStrides[b], (int)g.out[1], (int)g.out[2]) &&
         separable_patch_supported((int)batch, (int)shape[1], (int)shape[2], (int)shape[3], (int)cout, kStrides[b], (int)g.out[1], (int)g.out[2],
                                   buf[cur], weights->dw_w[b], weights->dw_b[b], weights->pw_w[b], weights->pw_b[b], block_out)) {
       rc = launch_separable_patch(buf[cur], weights->dw_w[b], weights->dw_b[b], weights->pw_w[b], weights->pw_b[b], block_out, (int)batch,
