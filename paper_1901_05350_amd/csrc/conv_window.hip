@@ -7,6 +7,12 @@
 // distance.  The filter is split too: per step -- 16 channels of one filter row -- its operands are written to one of two LDS
 // buffers, in their order, while the step before is multiplied.  Raw values of the next step (filter) and of the next channels
 // (window) wait in registers.
+//
+// Precision: a matrix instruction rounds its whole accumulator, so a step starts from zero and is added to the sum at its end, and
+// in it the small passes of a tap come before the hi hi pass of the tap before, while the accumulator is shorter: about
+// sqrt(4 + steps / 2) roundings (3 columns) instead of sqrt(3 K / 16).  Error against float64, normal operands, 3 x 3, K = 144 / 1944:
+// 0.72 / 1.43e-7; one chain of all steps 1.72 / 6.8e-7, gemm_direct.hip, which such shapes took before, 0.90 / 2.4e-7.  It costs 2 - 3 %
+// (39 drawn shapes: 0.786 of the time without this kernel, one chain 0.769; 8 x 73 x 73 x 80 -> 192 65.9 -> 67.9 us).
 #include "kernel_cost.h"
 #include "split.h"
 #include "ragged.h"
@@ -135,11 +141,11 @@ __global__ __launch_bounds__(kThreads, 2) void conv_window_kernel(WindowConv g) 
       }
   };
 
-  floatx16 acc[TM];
+  floatx16 sum[TM];
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
-    for (int v = 0; v < 16; ++v) acc[i][v] = 0.f;
+    for (int v = 0; v < 16; ++v) sum[i][v] = 0.f;
   const int col = n0 + 32 * wn + li;
   const float bv = g.bias != nullptr && col < g.Co ? g.bias[col] : 0.f;
 
@@ -153,20 +159,21 @@ __global__ __launch_bounds__(kThreads, 2) void conv_window_kernel(WindowConv g) 
   __syncthreads();
 
   bf16x8 fa[2][TM][kParts], fb[2][kParts];
-  auto read_a = [&](const char* window, int kh, int kw, int set) __attribute__((always_inline)) {
+  // parts [p0, p1) of a tap's operands
+  auto read_a = [&](const char* window, int kh, int kw, int set, int p0, int p1) __attribute__((always_inline)) {
     const char* const tap = window + (kh * g.cols + (g.sw == 2 ? kw / 2 + (kw % 2 ? g.half : 0) : kw)) * kPixelBytes;
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
-      for (int p = 0; p < kParts; ++p) fa[set][i][p] = *reinterpret_cast<const bf16x8*>(tap + at[i] + 32 * p);
+      for (int p = p0; p < p1; ++p) fa[set][i][p] = *reinterpret_cast<const bf16x8*>(tap + at[i] + 32 * p);
   };
-  auto read_b = [&](int buf, int kw, int set) __attribute__((always_inline)) {
+  auto read_b = [&](int buf, int kw, int set, int p0, int p1) __attribute__((always_inline)) {
     const char* const fbuf = filter + buf * kFilter + wn * kParts * 1024 + lane * 16;
 #pragma unroll
-    for (int p = 0; p < kParts; ++p) fb[set][p] = *reinterpret_cast<const bf16x8*>(fbuf + (2 * kw * kParts + p) * 1024);
+    for (int p = p0; p < p1; ++p) fb[set][p] = *reinterpret_cast<const bf16x8*>(fbuf + (2 * kw * kParts + p) * 1024);
   };
-  read_a(lds, 0, 0, 0);
-  read_b(0, 0, 0);
+  read_a(lds, 0, 0, 0, 0, kParts);
+  read_b(0, 0, 0, 0, kParts);
   // One step; PAR: set of operand registers that its first tap has (FW is odd, so they alternate).  A step's first operands
   // from the window are read ahead of the barrier before it (with one window buffer not the first step's of a chunk).
   int kh = 0, c0 = 0;
@@ -179,15 +186,31 @@ __global__ __launch_bounds__(kThreads, 2) void conv_window_kernel(WindowConv g) 
     int kh2 = kh1 + 1, c2 = c1;  // and the one after it
     if (kh2 == g.fh) kh2 = 0, c2 += kChannels;
     const bool more = s + 1 < steps, turn = more && kh1 == 0;  // the next step is one of the next channels
+    floatx16 acc[TM];  // of this step
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[i][v] = 0.f;
+    // Of the next tap's operands: the parts that are read ahead of this tap's products.  With 64 rows and 5 columns there are no
+    // registers for three high parts, and it is read behind them.
+    constexpr int kFirst = TM == 2 && FW == 5 ? 1 : 0;
+    bf16x8 ha[TM], hb;  // high parts of the tap before
+    auto high = [&]() __attribute__((always_inline)) {
+#pragma unroll
+      for (int i = 0; i < TM; ++i) acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ha[i], hb, acc[i], 0, 0, 0);
+    };
 #pragma unroll
     for (int kw = 0; kw < FW; ++kw) {
       const int set = (PAR + kw) & 1;
-      if (kw + 1 < FW) {
-        read_a(window, kh, kw + 1, set ^ 1);
-        read_b(s & 1, kw + 1, set ^ 1);
-      } else if (more && (DOUBLE || !turn)) {
-        read_a(turn ? lds + (wbuf ^ 1) * window_bytes : window, kh1, 0, set ^ 1);
-      }
+      auto ahead = [&](int p0, int p1) __attribute__((always_inline)) {
+        if (kw + 1 < FW) {
+          read_a(window, kh, kw + 1, set ^ 1, p0, p1);
+          read_b(s & 1, kw + 1, set ^ 1, p0, p1);
+        } else if (more && (DOUBLE || !turn)) {
+          read_a(turn ? lds + (wbuf ^ 1) * window_bytes : window, kh1, 0, set ^ 1, p0, p1);
+        }
+      };
+      ahead(kFirst, kParts);
       if (kw == FW / 2 && more) {
         store_filter((s + 1) & 1);
         if (s + 2 < steps) load_filter(kh2, c2);
@@ -197,19 +220,29 @@ __global__ __launch_bounds__(kThreads, 2) void conv_window_kernel(WindowConv g) 
         if (c0 + 2 * kChannels < g.Ci) load_window(c0 + 2 * kChannels);
       }
 #pragma unroll
-      for (int x = 0; x < kSplitPasses; ++x)
+      for (int x = 0; x < kSplitPasses - 1; ++x)
 #pragma unroll
         for (int i = 0; i < TM; ++i)
           acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[set][i][split_pass_a(x)], fb[set][split_pass_b(x)], acc[i], 0, 0, 0);
+      if (kw > 0) high();
+      ahead(0, kFirst);
+#pragma unroll
+      for (int i = 0; i < TM; ++i) ha[i] = fa[set][i][0];
+      hb = fb[set][0];
+      if (kw + 1 == FW) high();
     }
     __syncthreads();
     if (!DOUBLE && turn) {
       store_window(0);
       if (c1 + kChannels < g.Ci) load_window(c1 + kChannels);
       __syncthreads();
-      read_a(window, 0, 0, PAR ^ 1);
+      read_a(window, 0, 0, PAR ^ 1, 0, kParts);
     }
-    if (more) read_b((s + 1) & 1, 0, PAR ^ 1);
+    if (more) read_b((s + 1) & 1, 0, PAR ^ 1, 0, kParts);
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) sum[i][v] += acc[i][v];
     kh = kh1, c0 = c1;
   };
   for (int s = 0; s < steps; s += 2) {
@@ -217,6 +250,11 @@ __global__ __launch_bounds__(kThreads, 2) void conv_window_kernel(WindowConv g) 
     if (s + 1 < steps) multiply(s + 1, std::integral_constant<int, 1>{});
   }
 
+  // (here and not in the conditional stores, each of which would wait for the bias and so for the store before it)
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) sum[i][v] += bv;
   const ActClamp clamp = make_act(g.act);
   if (col < g.Co) {
 #pragma unroll
@@ -224,7 +262,7 @@ __global__ __launch_bounds__(kThreads, 2) void conv_window_kernel(WindowConv g) 
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
         const int row = m0 + wm0 + 32 * i + 8 * (v / 4) + 4 * h + v % 4;
-        if (row < g.M) g.y[(size_t)row * g.Co + col] = apply_act(acc[i][v] + bv, clamp);
+        if (row < g.M) g.y[(size_t)row * g.Co + col] = apply_act(sum[i][v], clamp);
       }
   }
   // Values that the split does not carry (split.h): results that are Inf or NaN, and small ones if it lost bits of an operand
@@ -233,7 +271,7 @@ __global__ __launch_bounds__(kThreads, 2) void conv_window_kernel(WindowConv g) 
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
-    for (int v = 0; v < 16; ++v) see_result(most, acc[i][v]);
+    for (int v = 0; v < 16; ++v) see_result(most, sum[i][v]);
   bool again = overflowed(most);
   float limit = 0.f;
   if (__syncthreads_or(guard.lost())) {
@@ -242,16 +280,16 @@ __global__ __launch_bounds__(kThreads, 2) void conv_window_kernel(WindowConv g) 
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) least = fminf(least, fabsf(acc[i][v] + bv));
+      for (int v = 0; v < 16; ++v) least = fminf(least, fabsf(sum[i][v]));
     again = again || least < limit;
   }
-  auto wanted = [&](float r) __attribute__((always_inline)) { return !__builtin_isfinite(r) || fabsf(r + bv) < limit; };
+  auto wanted = [&](float r) __attribute__((always_inline)) { return !__builtin_isfinite(r) || fabsf(r) < limit; };
   if (__builtin_amdgcn_ballot_w64(again) != 0) {
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
       bool any = false;
 #pragma unroll
-      for (int v = 0; v < 16; ++v) any = any || wanted(acc[i][v]);
+      for (int v = 0; v < 16; ++v) any = any || wanted(sum[i][v]);
       if (__builtin_amdgcn_ballot_w64(any) == 0) continue;
       const int row = min(m0 + wm0 + 32 * i + li, g.M - 1), t = row / g.OW, image = t / g.OH;
       const int ih0 = (t - image * g.OH) * g.sh - g.pt, iw0 = (row - t * g.OW) * g.sw - g.pl, wc = min(col, g.Co - 1);
@@ -273,7 +311,7 @@ __global__ __launch_bounds__(kThreads, 2) void conv_window_kernel(WindowConv g) 
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
         const int out = m0 + wm0 + 32 * i + 8 * (v / 4) + 4 * h + v % 4;
-        if (wanted(acc[i][v]) && out < g.M && col < g.Co) g.y[(size_t)out * g.Co + col] = apply_act(exact[v] + bv, clamp);
+        if (wanted(sum[i][v]) && out < g.M && col < g.Co) g.y[(size_t)out * g.Co + col] = apply_act(exact[v] + bv, clamp);
       }
     }
   }

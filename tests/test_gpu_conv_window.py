@@ -57,3 +57,21 @@ def test_values_outside_the_split(case):
     small = np.nan_to_num(x, nan=0, posinf=1) * np.float32(2.0 ** -115)
     up = oracle.conv2d(np.ldexp(small, 115), f, b, stride, pad_of(pad), oracle.ACT_NONE)
     assert_close(np.ldexp(run(small, np.ldexp(b, -115)), 115), up, "small %r" % (case,))
+
+
+@pytest.mark.parametrize("n,h,w,ci,co,f", [(2, 42, 42, 16, 328, 3), (3, 76, 76, 216, 128, 3), (22, 31, 31, 40, 56, 5)])
+def test_rounding_errors(n, h, w, ci, co, f):
+    """Relative 2-norm error against float64.  An output is the sum of steps of f * 16 products each.  The k-th of n equal parts of a
+    sum of independent terms is sqrt(k / n) of it in size, and a rounding adds at most 2^-24 of that: the additions of the steps come
+    to steps / 2 such errors squared, those inside the steps to fewer than 2 f together.  (One chain of all products, with six
+    roundings each 16, is over it.)"""
+    import torch
+    import paper_1901_05350_amd as tfx
+    g = torch.Generator().manual_seed(ci)
+    x, k = torch.randn((n, h, w, ci), generator=g), torch.randn((f, f, ci, co), generator=g)
+    ref = torch.nn.functional.conv2d(x.double().permute(0, 3, 1, 2), k.double().permute(3, 2, 0, 1), padding=f // 2).permute(0, 2, 3, 1).numpy()
+    got = host(tfx.tfx_conv2d(dev(x.numpy()), dev(k.numpy()), None, 1, tfx.PAD_SAME, tfx.ACT_NONE)).astype(np.float64)
+    steps = (ci + 15) // 16 * f
+    error = np.linalg.norm(got - ref) / np.linalg.norm(ref)
+    print("steps %d: %.3g" % (steps, error))
+    assert error <= 2.0 ** -24 * np.sqrt(2 * f + steps / 2)
