@@ -9,10 +9,15 @@
 // partial tiles are added through LDS behind the only barrier.  The fp32 matrix instructions do: split into bf16 parts (split.h), the
 // filter would be split again by every patch, for more than the 1 - 3 us that the instructions take here.
 //
+// Precision: these instructions round after every product, so 16 of them at a time start from zero and are added to the wavefront's
+// sum (64 with 128 columns in four rounds, see patch_halves).  Error of the pointwise sum against float64, 2 images, 128 -> 128
+// channels / 512 -> 512 / 1024 -> 1024: 7.3 / 9.5 / 10.6e-8, 8.4 / 10.5 / 13.1 with one sum a wavefront, 7.9 / 9.5 / 12.0 of the
+// kernels before; it costs 0 - 2 % of a pass (4 images 157.7 -> 161.2 us).
+//
 // What bounds it is the latency of one launch and of each round of loads (5 us and 2 - 3 a round), and from some 256 workgroups on
 // the filter's columns that each of them reads.  14 x 14 x 512 -> 512, us, against the two launches before: 2 images 7.7 (12.0), 3
 // 10.9 (14.0), 4 10.9 (15.1); 56 x 56 x 128 -> 128, 2 images 10.4 (13.1), 3 13.9 (17.4); 7 x 7 x 1024 -> 1024, 4 images 12.4 (15.8),
-// 8 17.1 (23.6).  The pass: 2 images 145 -> 113, 3 177 -> 151, 4 186 -> 162, 8 217 -> 208; 4 at half width 120 -> 91, 8 152 -> 120.
+// 8 17.1 (23.6).  The pass: 2 images 145 -> 113, 3 177 -> 151, 4 186 -> 162, 8 217 -> 208; 4 at half width 120 -> 92, 8 152 -> 120.
 #include <algorithm>
 
 #include "ragged.h"
@@ -53,23 +58,26 @@ struct PatchWindow {
         if (conflict_free(At{px, row})) return {px, row};
   }
   static constexpr Strides kStrides = find();
-  static constexpr int FLOATS = 4 * SIDE * kStrides.row, FILTER = 9 * kChannels32;
+  static constexpr int FLOATS = 4 * SIDE * kStrides.row, FILTER = 10 * kChannels32;  // (the bias behind the taps)
 };
 
-template <int S, int JN>
+// 128 columns in four rounds: no registers for a second set of sums, so those of the first two rounds lie behind the region
+constexpr bool patch_halves(int jn, int rounds) { return jn == 8 && rounds == 4; }
+
+template <int S, int JN, int ROUNDS>
 constexpr size_t patch_region_bytes() {
   const size_t in = (size_t)(PatchWindow<S>::FLOATS + PatchWindow<S>::FILTER) * sizeof(float), out = (size_t)256 * JN * sizeof(float);
-  return in > out ? in : out;
+  return (in > out ? in : out) + (patch_halves(JN, ROUNDS) ? out : 0);
 }
 
-// Wavefronts of a workgroup at most: windows of stride 2 are 12 KB each, and 128 columns, or 64 in several rounds, take more than
+// Wavefronts of a workgroup at most: windows of stride 2 are 13 KB each, and 128 columns, or 64 in several rounds, take more than
 // 128 registers.
 constexpr int most_waves(int s, int jn, int rounds) { return s == 2 || jn == 8 || (jn == 4 && rounds > 1) ? 8 : 16; }
 
 template <int S, int JN, int ROUNDS>
 __global__ __launch_bounds__(64 * most_waves(S, JN, ROUNDS)) void separable_patch_kernel(PatchArgs g) {
   typedef PatchWindow<S> P;
-  constexpr int LOADS = (P::SIDE * P::SIDE * kPieces + 63) / 64, FLOADS = (9 * kPieces + 63) / 64, G = kChannels32 / 16;
+  constexpr int LOADS = (P::SIDE * P::SIDE * kPieces + 63) / 64, FLOADS = (10 * kPieces + 63) / 64, G = kChannels32 / 16;
   constexpr int V = JN < 4 ? 1 : JN / 4;  // loads of a filter row
   extern __shared__ __align__(16) unsigned char lds[];
 
@@ -88,7 +96,8 @@ __global__ __launch_bounds__(64 * most_waves(S, JN, ROUNDS)) void separable_patc
   const int ow0 = 4 * (patch - strip * (int)g.row_patches.d), oh0 = 4 * (strip - image * (int)g.col_patches.d);
   const int C = g.C, N = g.N;
 
-  constexpr int REGION = (int)patch_region_bytes<S, JN>();
+  constexpr bool HALVES = patch_halves(JN, ROUNDS);
+  constexpr int REGION = (int)patch_region_bytes<S, JN, ROUNDS>(), SUMS = 256 * JN;
   float* const window = reinterpret_cast<float*>(lds + wave * REGION);
   float* const taps = window + P::FLOATS;
 
@@ -114,9 +123,10 @@ __global__ __launch_bounds__(64 * most_waves(S, JN, ROUNDS)) void separable_patc
   }
   const int col = n0 + JN * li < N ? n0 + JN * li : 0;  // past the last column: read, never stored
 
-  u32x4 win[LOADS], fil[FLOADS];
+  static_assert(FLOADS == 2, "the bias is in the second load");
+  const unsigned bat = (64 + lane) / kPieces == 9 ? 16u * piece : 0x80000000u;
+  u32x4 win[LOADS], fil[FLOADS], bias;
   struct Operands {
-    floatx4 bias[G];
     float w[G][4][JN];  // rows 16 u + 4 q + s
   };
   auto fetch = [&](int round, Operands& o) __attribute__((always_inline)) {
@@ -126,9 +136,7 @@ __global__ __launch_bounds__(64 * most_waves(S, JN, ROUNDS)) void separable_patc
     for (int i = 0; i < LOADS; ++i) win[i] = __builtin_amdgcn_raw_buffer_load_b128(xr, mine ? at[i] + 4u * c0 : 0x80000000u, 0, 0);
 #pragma unroll
     for (int i = 0; i < FLOADS; ++i) fil[i] = __builtin_amdgcn_raw_buffer_load_b128(fr, mine ? fat[i] + 4u * c0 : 0x80000000u, 0, 0);
-#pragma unroll
-    for (int u = 0; u < G; ++u)
-      o.bias[u] = __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(br, 4u * (unsigned)(c0 + 16 * u + 4 * q), 0, 0));
+    bias = __builtin_amdgcn_raw_buffer_load_b128(br, mine ? bat + 4u * c0 : 0x80000000u, 0, 0);
 #pragma unroll
     for (int u = 0; u < G; ++u)
 #pragma unroll
@@ -162,6 +170,7 @@ __global__ __launch_bounds__(64 * most_waves(S, JN, ROUNDS)) void separable_patc
     const float b = part == 0 ? pwb[j] : 0.f;
     acc[j] = floatx4{b, b, b, b};
   }
+  constexpr int AT = JN < 4 ? JN : 4;
   const float* const mine = window + 4 * (li / 4 * S * P::kStrides.row + li % 4 * S * P::kStrides.px + q);
 #pragma unroll
   for (int round = 0; round < ROUNDS; ++round) {
@@ -173,14 +182,14 @@ __global__ __launch_bounds__(64 * most_waves(S, JN, ROUNDS)) void separable_patc
     }
 #pragma unroll
     for (int i = 0; i < FLOADS; ++i)
-      if (64 * (i + 1) <= 9 * kPieces || 64 * i + lane < 9 * kPieces) *reinterpret_cast<u32x4*>(taps + 4 * (64 * i + lane)) = fil[i];
+      if (64 * (i + 1) <= 10 * kPieces || 64 * i + lane < 10 * kPieces) *reinterpret_cast<u32x4*>(taps + 4 * (64 * i + lane)) = i == 1 ? fil[i] | bias : fil[i];
     if (round + 1 < ROUNDS) fetch(round + 1, ops[(round + 1) % 2]);
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
     const Operands& o = ops[round % 2];
 #pragma unroll
     for (int u = 0; u < G; ++u) {
-      floatx4 d = o.bias[u];
+      floatx4 d = *reinterpret_cast<const floatx4*>(taps + kChannels32 * 9 + 16 * u + 4 * q);
 #pragma unroll
       for (int t = 0; t < 9; ++t) {
         const floatx4 xt = *reinterpret_cast<const floatx4*>(mine + 4 * (t / 3 * P::kStrides.row + t % 3 * P::kStrides.px + 4 * u));
@@ -197,9 +206,28 @@ __global__ __launch_bounds__(64 * most_waves(S, JN, ROUNDS)) void separable_patc
         for (int e = 0; e < 4; ++e) a[e] = apply_act(d[e], dw_clamp);
       }
 #pragma unroll
-      for (int s = 0; s < 4; ++s)
+      for (int j0 = 0; j0 < JN; j0 += AT) {
+        const bool begin = HALVES || round + u == 0;
+        floatx4 t[AT];
 #pragma unroll
-        for (int j = 0; j < JN; ++j) acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[s], o.w[u][s][j], acc[j], 0, 0, 0);
+        for (int j = 0; j < AT; ++j) t[j] = begin ? acc[j0 + j] : floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+          for (int j = 0; j < AT; ++j) t[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[s], o.w[u][s][j0 + j], t[j], 0, 0, 0);
+#pragma unroll
+        for (int j = 0; j < AT; ++j) acc[j0 + j] = begin ? t[j] : acc[j0 + j] + t[j];
+        __builtin_amdgcn_sched_barrier(0);  // (fewer registers)
+      }
+    }
+    if (HALVES && round == 1) {
+      float* const half = reinterpret_cast<float*>(lds + (wave + 1) * REGION) - SUMS;
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+#pragma unroll
+        for (int j = 0; j < JN; ++j) half[(v * 64 + lane) * JN + j] = acc[j][v];
+#pragma unroll
+      for (int j = 0; j < JN; ++j) acc[j] = floatx4{0.f, 0.f, 0.f, 0.f};
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
@@ -229,6 +257,10 @@ __global__ __launch_bounds__(64 * most_waves(S, JN, ROUNDS)) void separable_patc
     for (int w = 0; w < g.wk; ++w) {
       const f32x2 t = reinterpret_cast<const f32x2*>(lds + (p * g.wk + w) * REGION)[u];
       s0 += t[0], s1 += t[1];
+      if constexpr (HALVES) {
+        const f32x2 h = reinterpret_cast<const f32x2*>(lds + (p * g.wk + w + 1) * REGION - SUMS * sizeof(float))[u];
+        s0 += h[0], s1 += h[1];
+      }
     }
     const int v = u / (32 * JN), rest = u % (32 * JN);
     store(v, rest / (JN / 2), 2 * (rest % (JN / 2)), s0, s1);
@@ -251,7 +283,7 @@ int launch_patch(const PatchArgs& args, const PatchForm& f, hipStream_t stream) 
   g.slices = (g.N + 16 * JN - 1) / (16 * JN);
   g.by_slices = fast_div((unsigned)g.slices);
   g.total = (g.patches + f.wp - 1) / f.wp * g.slices;
-  const size_t lds_bytes = patch_region_bytes<S, JN>() * f.wk * f.wp;
+  const size_t lds_bytes = patch_region_bytes<S, JN, ROUNDS>() * f.wk * f.wp;
   hipLaunchKernelGGL(kern, dim3((unsigned)g.total), dim3(64u * f.wk * f.wp), lds_bytes, stream, g);
   return check_launch();
 }
@@ -288,7 +320,7 @@ bool separable_patch_supported(int batch, int h, int w, int c, int n, int stride
   bool aligned = true;
   for (const void* p : ptrs) aligned = aligned && reinterpret_cast<uintptr_t>(p) % 16 == 0;
   const long long patches = (long long)batch * ((oh + 3) / 4) * ((ow + 3) / 4), x_bytes = (long long)batch * h * w * c * 4;
-  return aligned && (stride == 1 || stride == 2) && c % 4 == 0 && c <= 1024 && n % 8 == 0 && n <= 1024 && x_bytes < (1ll << 31) &&
+  return aligned && (stride == 1 || stride == 2) && c % 4 == 0 && c <= (stride == 1 ? 1024 : 512) && n % 8 == 0 && n <= 1024 && x_bytes < (1ll << 31) &&
          patches < (1ll << 24);
 }
 
@@ -314,7 +346,7 @@ int launch_separable_patch(const float* x, const float* dw_w, const float* dw_b,
   if (stride == S && f.jn == JN && f.rounds == ROUNDS) return launch_patch<S, JN, ROUNDS>(g, f, stream);
 #define TFX_PATCHES(S, JN) TFX_PATCH(S, JN, 1) TFX_PATCH(S, JN, 2)
   TFX_PATCHES(1, 2) TFX_PATCHES(1, 4) TFX_PATCHES(1, 8) TFX_PATCHES(2, 2) TFX_PATCHES(2, 4) TFX_PATCHES(2, 8)
-  TFX_PATCH(1, 4, 4) TFX_PATCH(1, 8, 4) TFX_PATCH(2, 2, 4) TFX_PATCH(2, 4, 4) TFX_PATCH(2, 8, 4)
+  TFX_PATCH(1, 4, 4) TFX_PATCH(1, 8, 4)  // (stride 2: up to 512 channels)
 #undef TFX_PATCHES
 #undef TFX_PATCH
   return TFX_ERR_UNSUPPORTED;

@@ -27,3 +27,21 @@ def test_patch_blocks(q, size, batch, blocks):
         keep = ~np.isnan(ref)
         if keep.any():
             assert_close(got[keep], ref[keep], "block %d" % k)
+
+
+@pytest.mark.parametrize("q,size,batch,block,chain", [(4, 64, 2, 3, 16), (4, 64, 4, 8, 16), (4, 224, 8, 13, 64), (3, 200, 8, 13, 64), (1, 64, 4, 5, 16), (2, 64, 3, 10, 16)])
+def test_sums_of_few_products(q, size, batch, block, chain):
+    """One product of 4 and others of 2^-23 each, which vanish beside it: half of its last place is 2^-22.  Only those that are summed
+    in one chain with it may be lost; all other sums are exact."""
+    import paper_1901_05350_amd as tfx
+    w = inputs.mobilenet_v1(seed=85, batch=1, image_size=size, width_quarters=q, classes=10)["weights"]
+    c = w["pw_w"][block - 1].shape[2]
+    w["pw_w"][block - 2][:] = 0  # the block's input: 4 in channel 0 and 1 in the others
+    w["pw_b"][block - 2][:] = 1
+    w["pw_b"][block - 2][0] = 4
+    w["dw_w"][block - 1][:], w["dw_b"][block - 1][:], w["dw_w"][block - 1][1, 1] = 0, 0, 1
+    w["pw_w"][block - 1][:], w["pw_b"][block - 1][:], w["pw_w"][block - 1][0, 0, 0] = 2.0 ** -23, 0, 1
+    image = dev(np.zeros((batch, size, size, 3)))
+    got = host(tfx.MobileNetV1(w, batch=batch, image_size=size, width_quarters=q).features(image, block)).astype(np.float64)
+    print((got.min() - 4) * 2 ** 23, (got.max() - 4) * 2 ** 23, c)
+    assert np.all(got >= 4 + (c - chain) * 2.0 ** -23) and np.all(got <= 4 + c * 2.0 ** -23)
