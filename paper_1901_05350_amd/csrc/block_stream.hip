@@ -16,6 +16,9 @@
 // with the fp32 matrix instructions, whose cycles a third of it were, 24.2 with the six bf16 products; 112 x 112 x 64 -> 128 at
 // stride 2 23.0 and 19.7; the pass of 64 images 799 -> 770, of 16 300 -> 290.  Block 3 of the 3/4 width and blocks 2 and 3 of the half
 // width, as two launches before: the pass of 20 images 289 -> 279 and 204 -> 190.
+//
+// Error of the pointwise sum against float64: 64 -> 64 3.9e-8, 96 -> 96 4.2, 128 -> 128 12.2, 64 -> 128 4.0; with
+// the passes of one k-step after the other 8.5, 9.9, 14.6, 9.2; the kernels before this one 6.1, 6.3 - 11.7, 13.6, 10.6.
 #include "split.h"
 
 #include <type_traits>
@@ -195,32 +198,50 @@ __global__ __launch_bounds__(kThreads) void separable_window_kernel(const float*
 #pragma unroll
     for (int j = 0; j < NB; ++j) acc[j] = *reinterpret_cast<const floatx4*>(pwb_l + 16 * j + 4 * q);
     unsigned low = 0;
+    // The small passes of several k-steps come before their hi hi passes, while the accumulators are short: each instruction rounds all
+    // of one.  (Four steps at a time do not fit the registers.)
+    constexpr int kSteps = KS < 4 ? KS : 2;
+    static_assert(KS % kSteps == 0, "k-steps at a time");
 #pragma unroll
-    for (int st = 0; st < KS; ++st) {
-      bf16x8 op[kParts];
-      splitx4 part[2][kParts];
+    for (int st = 0; st < KS; st += kSteps) {
+      bf16x8 op[kSteps][kParts];
 #pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        const float4 v = a[2 * st + u];
-        split4(floatx4{v.x, v.y, v.z, v.w}, part[u], low);
-      }
+      for (int k = 0; k < kSteps; ++k) {
+        splitx4 part[2][kParts];
 #pragma unroll
-      for (int p = 0; p < kParts; ++p) {
-        const u32x4 both = {part[0][p][0], part[0][p][1], part[1][p][0], part[1][p][1]};
-        op[p] = __builtin_bit_cast(bf16x8, both);
+        for (int u = 0; u < 2; ++u) {
+          const float4 v = a[2 * (st + k) + u];
+          split4(floatx4{v.x, v.y, v.z, v.w}, part[u], low);
+        }
+#pragma unroll
+        for (int p = 0; p < kParts; ++p) {
+          const u32x4 both = {part[0][p][0], part[0][p][1], part[1][p][0], part[1][p][1]};
+          op[k][p] = __builtin_bit_cast(bf16x8, both);
+        }
       }
 #pragma unroll
       for (int j0 = 0; j0 < NB; j0 += 2) {
-        bf16x8 fw[2][kParts];
+        bf16x8 high[kSteps][2];
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-          for (int p = 0; p < kParts; ++p) fw[j][p] = pw_l[((st * NB + j0 + j) * kParts + p) * 64 + lane];
-#pragma unroll
-        for (int s = 0; s < kSplitPasses; ++s)
+        for (int k = 0; k < kSteps; ++k) {
+          bf16x8 fw[2][kParts];
 #pragma unroll
           for (int j = 0; j < 2; ++j)
-            acc[j0 + j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[j][split_pass_b(s)], op[split_pass_a(s)], acc[j0 + j], 0, 0, 0);
+#pragma unroll
+            for (int p = 0; p < kParts; ++p) fw[j][p] = pw_l[(((st + k) * NB + j0 + j) * kParts + p) * 64 + lane];
+#pragma unroll
+          for (int s = 0; s < kSplitPasses - 1; ++s)
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+              acc[j0 + j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[j][split_pass_b(s)], op[k][split_pass_a(s)], acc[j0 + j], 0, 0, 0);
+#pragma unroll
+          for (int j = 0; j < 2; ++j) high[k][j] = fw[j][0];
+          if (k + 1 < kSteps) __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int k = 0; k < kSteps; ++k)
+#pragma unroll
+          for (int j = 0; j < 2; ++j) acc[j0 + j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(high[k][j], op[k][0], acc[j0 + j], 0, 0, 0);
         __builtin_amdgcn_sched_barrier(0);  // keep later blocks' LDS reads from being hoisted
       }
     }

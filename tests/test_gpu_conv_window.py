@@ -62,9 +62,9 @@ def test_values_outside_the_split(case):
 @pytest.mark.parametrize("n,h,w,ci,co,f", [(2, 42, 42, 16, 328, 3), (3, 76, 76, 216, 128, 3), (22, 31, 31, 40, 56, 5)])
 def test_rounding_errors(n, h, w, ci, co, f):
     """Relative 2-norm error against float64.  An output is the sum of steps of f * 16 products each.  The k-th of n equal parts of a
-    sum of independent terms is sqrt(k / n) of it in size, and a rounding adds at most 2^-24 of that: the additions of the steps come
-    to steps / 2 such errors squared, those inside the steps to fewer than 2 f together.  (One chain of all products, with six
-    roundings each 16, is over it.)"""
+    sum of independent terms is sqrt(k / n) of it in size, and a rounding adds some 2^-24 of that (an addition's at most, the half of
+    what a matrix instruction, which cuts off, may): the additions of the steps come to steps / 2 such errors squared, those inside the
+    steps to fewer than 2 f together.  (One chain of all products, with six roundings each 16, is over it.)"""
     import torch
     import paper_1901_05350_amd as tfx
     g = torch.Generator().manual_seed(ci)

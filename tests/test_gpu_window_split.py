@@ -60,3 +60,21 @@ def test_other_widths(q, size, blocks):
         assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.isnan(ref).any()
         keep = ~np.isnan(ref)
         assert_close(got[keep], ref[keep], "block %d" % k)
+
+
+@pytest.mark.parametrize("q,block", [(2, 3), (3, 3), (4, 3), (4, 2)])
+def test_order_of_the_passes(q, block):
+    """A product of 4 in the first 32 channels, and in the next 32 pairs (1 + d) W (1 + d) - (1 - d) W (1 - d) whose large parts cancel:
+    of the six bf16 products only the two of a middle with a high part are left, each 15/16 of 4's last place in sum.  The matrix
+    instructions cut off what lies behind the last place: added to 4 one after the other both vanish, but one place is left of their
+    sum, for an error below one."""
+    import paper_1901_05350_amd as tfx
+    w = inputs.mobilenet_v1(seed=98, batch=1, image_size=224, width_quarters=q, classes=10)["weights"]
+    d, W = 2.0 ** -10, 15 * 2.0 ** -20
+    sign = np.tile(np.float64([1, -1]), 16)
+    w["pw_w"][block - 2][:], w["pw_b"][block - 2][:], w["pw_b"][block - 2][0], w["pw_b"][block - 2][32:64] = 0, 0, 4, 1 + sign * d
+    w["dw_w"][block - 1][:], w["dw_b"][block - 1][:], w["dw_w"][block - 1][1, 1] = 0, 0, 1
+    w["pw_w"][block - 1][:], w["pw_b"][block - 1][:] = 0, 0
+    w["pw_w"][block - 1][0, 0, 0], w["pw_w"][block - 1][0, 0, 32:64] = 1, (sign * W * (1 + sign * d))[:, None]
+    got = host(tfx.MobileNetV1(w, batch=31, image_size=224, width_quarters=q).features(dev(np.zeros((31, 224, 224, 3))), block))
+    assert np.all(np.abs(got.astype(np.float64) - (4 + 32 * W * 2 * d)) < 2.0 ** -21)
