@@ -208,19 +208,7 @@ size_t tfx_mobilenet_v1_workspace_bytes(int64_t batch);
  * rather than a number computed from unfinished data.
  * input: device [batch,224,224,3]; workspace: device, >= the size above, 256-byte
  * aligned, contents undefined before and after; probs: device [batch,1000];
- * logits: device [batch,1000] or NULL.  All kernels are enqueued on `stream`,
- * with one exception: from batch 32 on the pass runs as two parts of the batch, from
- * batch 60 on as three (each in its own part of the workspace), and all but the first
- * are enqueued on streams the library creates once per device, which wait for
- * everything queued on `stream` before the call (an event) and which `stream` waits
- * for before anything queued after the call: for the caller the call still behaves as work on `stream`, also
- * while `stream` is being captured into a graph (fork and join become edges of the
- * graph).  Independent chains of kernels fill the CUs that the last workgroups of
- * each kernel leave idle (1.03 -> 0.96 ms at batch 64).  If the streams cannot be created
- * (also: if the first such call of the process comes while `stream` is being
- * captured), or if TFX_ONE_STREAM is set in the environment, the batch runs as one
- * chain of kernels on `stream`, as below batch 32; the results then agree with the
- * split form to rounding (other tile shapes), not bit for bit. */
+ * logits: device [batch,1000] or NULL.  All kernels are enqueued on `stream`. */
 int tfx_mobilenet_v1_forward(const float* input, int64_t batch, const tfx_mobilenet_v1_weights* weights,
                              void* workspace, size_t workspace_bytes, float* probs, float* logits,
                              void* stream);
@@ -282,8 +270,7 @@ int tfx_mobilenet_v1_variant_features(const tfx_mobilenet_v1_variant* variant, c
  * allocates and frees nothing.  {224, 4, 1000} fits at batch 1 and 2; a variant / batch whose
  * tfx_mobilenet_v1_variant_workspace_bytes exceeds the array is refused with
  * TFX_ERR_WORKSPACE (nothing enqueued).  Results are bit-identical to
- * tfx_mobilenet_v1_variant_forward below batch 32 (from there on that call splits the batch
- * over two streams; this one creates no stream and runs one chain of kernels).  All calls on one GPU share the one array: calls that
+ * tfx_mobilenet_v1_variant_forward.  All calls on one GPU share the one array: calls that
  * overlap in time on one GPU (different streams or host threads) race and give
  * undefined results; calls ordered on one stream are fine.  Nothing in the array has to
  * start at zero (each kernel writes what later kernels read), so its contents between

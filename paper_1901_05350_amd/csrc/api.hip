@@ -1,11 +1,6 @@
 // C ABI of libtfx: argument validation, shape rules and kernel selection.
 // Every entry point validates on the host before any HIP call and then only enqueues
-// kernels on the caller's stream (enqueue-and-return, as the ops of Section 3.6 / 4.1);
-// the fp32 forward pass of 32 or more images also uses one or two streams of the library's
-// own, forked from and joined to the caller's (forward_whole).
-#include <cstdlib>
-#include <mutex>
-
+// kernels on the caller's stream (enqueue-and-return, as the ops of Section 3.6 / 4.1).
 #include "tfx_internal.h"
 
 namespace tfx {
@@ -96,13 +91,6 @@ constexpr size_t kAlign = 256;
 
 size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 
-struct NetPlan {
-  size_t act_floats;  // per ping-pong buffer
-  size_t off_buf[2], off_partial, off_chain, off_head, off_packed, bytes;  // off_packed: BlockPlan
-  bool chain;         // the batch-1 full-width network: room for the chained small-map kernel (chain.hip)
-  bool head;          // and for blocks 2 - 4 as stages of one launch (block.hip): their three outputs at once
-};
-
 bool valid_variant(const tfx_mobilenet_v1_variant* v) {
   return v && v->image_size >= 32 && v->image_size <= 256 && v->width_quarters >= 1 && v->width_quarters <= 4 &&
          v->classes >= 1 && v->classes <= 1024;
@@ -157,6 +145,63 @@ BlockPlan plan_blocks_f16(const tfx_mobilenet_v1_variant& v, int64_t batch) {
   return p;
 }
 
+// The same for fp32.  kBlock: patches with the whole block in registers (block.hip), one to three images.  One image's pass is chained;
+// where it stops at a feature map or may not be chained, its blocks take kBlock, kStream or kTwo.
+enum BlockForm32 { kTwo32, kPatch32, kBlock32, kStream32, kTile32 };
+struct BlockPlan32 {
+  BlockForm32 form[kBlocks], without[kBlocks];  // without: what a tile block is where there is no room for its filter
+  int tiles, c[kBlocks], n[kBlocks];
+  size_t packed[kBlocks], packed_bytes;  // the tile blocks' filters
+  void drop_tiles() {
+    for (int b = 0; b < kBlocks; ++b) form[b] = without[b];
+    tiles = 0, packed_bytes = 0;
+  }
+};
+BlockPlan32 plan_blocks(const tfx_mobilenet_v1_variant& v, int64_t batch) {
+  BlockPlan32 p{};
+  const int q = (int)v.width_quarters;
+  int hw = (int)(v.image_size + 1) / 2;
+  for (int b = 0; b < kBlocks; ++b) {
+    const int c = p.c[b] = b == 0 ? kStemChannels * q / 4 : kChannels[b - 1] * q / 4, n = p.n[b] = kChannels[b] * q / 4, s = kStrides[b];
+    const int out = (hw + s - 1) / s;
+    auto fits = [&](auto supported) {
+      return supported((int)batch, hw, hw, c, n, s, out, out, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr);
+    };
+    // The tile form stands where two launches stood, the slower ones in 284 of 299 blocks of 2 - 64 images (512 -> 512, 64 images 35 us
+    // against 66, 8 images 12.2 and 17.8; the others are up to 0.8 us apart), and the window kernel's 128 -> 128 where that has less
+    // than half a round of units (0.44 of 2048: 9.7 us against 14.1; from there on 19.5 against 16.3 to 67.6 against 71.7 at six
+    // rounds).  The patch kernel and the window kernel's thinner filters keep their blocks: their sums are the more accurate ones.
+    const bool tile = batch > 1 && fits(separable_tile_supported);
+    const int64_t units = batch * ((out + 1) / 2) * ((out + 7) / 8);
+    const bool wide = c == 128 && n == 128 && units <= 1024;
+    p.without[b] = batch > 1 && separable_patch_pays((int)batch, c, n, s, out, out) && fits(separable_patch_supported) ? kPatch32
+                   : separable_block_supported(batch, hw, hw, c, n, s, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr) ? kBlock32
+                   : fits(separable_stream_supported) ? kStream32
+                                                      : kTwo32;
+    p.form[b] = tile && (p.without[b] == kTwo32 || (wide && p.without[b] == kStream32)) ? kTile32 : p.without[b];
+    if (p.form[b] == kTile32) {
+      ++p.tiles;
+      p.packed[b] = p.packed_bytes;
+      p.packed_bytes += align_up(separable_tile_packed_bytes(c, n));
+    }
+    hw = out;
+  }
+  if (p.tiles < 3) p.drop_tiles();  // (the launch that prepares the filters)
+  return p;
+}
+
+// Workspace of tfx_mobilenet_v1_variant_forward_static: it lives in the library's code object, one copy per
+// GPU, from the moment the library is loaded on that GPU until the process ends.
+constexpr size_t kStaticScratchBytes = size_t(16) << 20;
+
+struct NetPlan {
+  size_t act_floats;  // per ping-pong buffer
+  size_t off_buf[2], off_partial, off_chain, off_head, off_packed, bytes;  // off_packed: BlockPlan, BlockPlan32
+  BlockPlan32 blocks;  // fp32
+  bool chain;         // the batch-1 full-width network: room for the chained small-map kernel (chain.hip)
+  bool head;          // and for blocks 2 - 4 as stages of one launch (block.hip): their three outputs at once
+};
+
 NetPlan plan_net(const tfx_mobilenet_v1_variant& v, int64_t batch, size_t elem_bytes = sizeof(float)) {
   NetPlan p{};
   // largest feature map: the output of the first pointwise layer (half the image size, 64 alpha channels)
@@ -180,16 +225,20 @@ NetPlan plan_net(const tfx_mobilenet_v1_variant& v, int64_t batch, size_t elem_b
   p.head = p.chain && v.width_quarters == 4 && 2 * quarter * quarter * 128 <= p.act_floats;
   if (p.head) off = align_up(off + 2 * eighth * eighth * 256 * sizeof(float));  // outputs of blocks 4 and 5
   p.off_packed = off;
-  if (elem_bytes == sizeof(uint16_t)) off += plan_blocks_f16(v, batch).packed_halfs * sizeof(uint16_t);
+  if (elem_bytes == sizeof(uint16_t)) {
+    off += plan_blocks_f16(v, batch).packed_halfs * sizeof(uint16_t);
+  } else {
+    // (a pass that fits the static workspace only without them goes without)
+    p.blocks = plan_blocks(v, batch);
+    if (off <= kStaticScratchBytes && off + p.blocks.packed_bytes > kStaticScratchBytes) p.blocks.drop_tiles();
+    off += p.blocks.packed_bytes;
+  }
   p.bytes = off;
   return p;
 }
 
 constexpr tfx_mobilenet_v1_variant kBaseVariant = {kImage, 4, kClasses};
 
-// Workspace of tfx_mobilenet_v1_variant_forward_static: it lives in the library's code object, one copy per
-// GPU, from the moment the library is loaded on that GPU until the process ends.
-constexpr size_t kStaticScratchBytes = size_t(16) << 20;
 constexpr int kMaxDevices = 64;
 
 }  // namespace
@@ -212,57 +261,6 @@ void* static_scratch() {
   if (hipGetSymbolAddress(&p, HIP_SYMBOL(scratch)) != hipSuccess || !p) return nullptr;
   ptr[dev].store(p, std::memory_order_release);
   return p;
-}
-
-// From batch 32 on the fp32 forward pass runs as two halves of the batch, the second on a stream of the library's that is
-// forked from the caller's and joined back to it with events: the layers of such a batch are kernels of 10 - 60 us whose
-// last workgroups leave most CUs idle, and an independent chain of them fills the tails (batch 32 489 -> 449 us, 64
-// 880 -> 803, with the blocks of block_planes.hip; at batch 16 no gain; nothing to gain on binary16 storage).
-constexpr int64_t kSplitBatch = 32;
-constexpr int kMaxChains = 2;
-
-int net_chains(int64_t batch) { return batch < kSplitBatch ? 1 : 2; }
-// images of part i of `chains`: the first batch % chains parts take one more
-int64_t part_images(int64_t batch, int chains, int i) { return batch / chains + (i < batch % chains ? 1 : 0); }
-
-size_t net_workspace_bytes(const tfx_mobilenet_v1_variant& v, int64_t batch) {  // enough for either form
-  const size_t whole = plan_net(v, batch).bytes;
-  const int chains = net_chains(batch);
-  if (chains == 1) return whole;
-  size_t parts = 0;
-  for (int i = 0; i < chains; ++i) parts += align_up(plan_net(v, part_images(batch, chains, i)).bytes);
-  return parts > whole ? parts : whole;
-}
-
-// The library's own streams and events, one set per device, created on the first call that wants them and kept
-// until the process ends.  Calls that use them hold the lock while they enqueue.
-struct SideStreams {
-  hipStream_t stream[kMaxChains - 1];
-  hipEvent_t fork, join[kMaxChains - 1];
-};
-std::mutex g_side_lock;
-SideStreams* side_streams(hipStream_t caller) {  // with g_side_lock held; null: none to be had
-  static SideStreams table[kMaxDevices];
-  static int state[kMaxDevices];  // 0 not tried, 1 there, 2 failed
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return nullptr;
-  if (state[dev] == 0) {
-    // nothing is created while the caller's stream is being captured into a graph (creation calls are not allowed
-    // then); a later call outside a capture creates them
-    hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(caller, &capturing) != hipSuccess || capturing != hipStreamCaptureStatusNone) {
-      (void)hipGetLastError();
-      return nullptr;
-    }
-    SideStreams& t = table[dev];
-    bool ok = hipEventCreateWithFlags(&t.fork, hipEventDisableTiming) == hipSuccess;
-    for (int i = 0; i < kMaxChains - 1 && ok; ++i)
-      ok = hipStreamCreateWithFlags(&t.stream[i], hipStreamNonBlocking) == hipSuccess &&
-           hipEventCreateWithFlags(&t.join[i], hipEventDisableTiming) == hipSuccess;
-    if (!ok) (void)hipGetLastError();
-    state[dev] = ok ? 1 : 2;
-  }
-  return state[dev] == 1 ? &table[dev] : nullptr;
 }
 
 }  // namespace
@@ -457,7 +455,7 @@ int tfx_depthwise_conv2d_f16(const uint16_t* x, const int64_t x_shape[4], const 
 
 size_t tfx_mobilenet_v1_workspace_bytes(int64_t batch) {
   if (batch < 1 || batch > 1024) return 0;
-  return net_workspace_bytes(kBaseVariant, batch);
+  return plan_net(kBaseVariant, batch).bytes;
 }
 
 int tfx_mobilenet_v1_forward(const float* input, int64_t batch, const tfx_mobilenet_v1_weights* weights,
@@ -468,7 +466,7 @@ int tfx_mobilenet_v1_forward(const float* input, int64_t batch, const tfx_mobile
 
 size_t tfx_mobilenet_v1_variant_workspace_bytes(const tfx_mobilenet_v1_variant* variant, int64_t batch) {
   if (!valid_variant(variant) || batch < 1 || batch > 1024) return 0;
-  return net_workspace_bytes(*variant, batch);
+  return plan_net(*variant, batch).bytes;
 }
 
 namespace {
@@ -599,7 +597,25 @@ int forward_impl(const tfx_mobilenet_v1_variant* variant, const float* input, in
                           static_cast<hipStream_t>(stream), launch_head, &head, 5);
     }
   }
-  for (int b = first_block; b < kBlocks; ++b) {
+  const int blocks = end_block ? end_block : kBlocks;
+  const BlockPlan32& form = plan.blocks;  // of the whole network: a feature map is the one a pass computes
+  bool aligned = true;
+  for (int b = first_block; b < blocks; ++b)
+    for (const void* p : {weights->dw_w[b], weights->dw_b[b], weights->pw_w[b], weights->pw_b[b]})
+      aligned = aligned && reinterpret_cast<uintptr_t>(p) % 16 == 0;
+  if (aligned && form.tiles > 0) {
+    const float* filters[kBlocks];
+    void* packed[kBlocks];
+    int tiles = 0, c[kBlocks], n[kBlocks];
+    for (int b = first_block; b < blocks; ++b)
+      if (form.form[b] == kTile32) {
+        filters[tiles] = weights->pw_w[b], packed[tiles] = ws + plan.off_packed + form.packed[b];
+        c[tiles] = form.c[b], n[tiles] = form.n[b];
+        ++tiles;
+      }
+    if (tiles > 0 && (rc = launch_pack_filters(tiles, filters, packed, c, n, static_cast<hipStream_t>(stream)))) return rc;
+  }
+  for (int b = first_block; b < blocks; ++b) {
     float* const block_out = end_block == b + 1 ? features : buf[cur ^ 1];
     if (chain && b == 4)
       return launch_chain(buf[cur], (int)shape[1], weights, chain_ws, head_flags, probs, logits, (int)variant->classes, q,
@@ -607,72 +623,26 @@ int forward_impl(const tfx_mobilenet_v1_variant* variant, const float* input, in
     const int64_t fd[4] = {3, 3, shape[3], 1};
     const int64_t cout = kChannels[b] * q / 4;
     conv_geometry(shape, fd, kStrides[b], kStrides[b], TFX_PAD_SAME, true, &g);
-    // few pixels, two images or more: depthwise and pointwise layer in one launch, a workgroup per patch (block_patch.hip).  One
-    // image's pass is chained; where it stops at a feature map or may not be chained, it takes the kernels below.
-    if (batch > 1 && separable_patch_pays((int)batch, (int)shape[3], (int)cout, kStrides[b], (int)g.out[1], (int)g.out[2]) &&
-        separable_patch_supported((int)batch, (int)shape[1], (int)shape[2], (int)shape[3], (int)cout, kStrides[b], (int)g.out[1], (int)g.out[2],
-                                  buf[cur], weights->dw_w[b], weights->dw_b[b], weights->pw_w[b], weights->pw_b[b], block_out)) {
-      rc = launch_separable_patch(buf[cur], weights->dw_w[b], weights->dw_b[b], weights->pw_w[b], weights->pw_b[b], block_out, (int)batch,
-                                  (int)shape[1], (int)shape[2], (int)shape[3], (int)cout, (int)g.out[1], (int)g.out[2], kStrides[b],
-                                  (int)g.pad[0], (int)g.pad[2], TFX_ACT_RELU6, TFX_ACT_RELU6, static_cast<hipStream_t>(stream));
-      if (rc) return rc;
-      if (end_block == b + 1) return TFX_OK;
-      for (int i = 0; i < 3; ++i) shape[i] = g.out[i];
-      shape[3] = cout;
-      cur ^= 1;
-      continue;
-    }
-    // batch 1 to 3, thin block: depthwise and pointwise layer in one launch (block.hip)
-    if (separable_block_supported(batch, (int)shape[1], (int)shape[2], (int)shape[3], (int)cout, kStrides[b], buf[cur],
-                                  weights->dw_w[b], weights->dw_b[b], weights->pw_w[b], weights->pw_b[b], block_out)) {
-      rc = launch_separable_block(buf[cur], weights->dw_w[b], weights->dw_b[b], weights->pw_w[b], weights->pw_b[b],
-                                  block_out, (int)batch, (int)shape[1], (int)shape[2], (int)shape[3], (int)cout, (int)g.out[1],
-                                  (int)g.out[2], kStrides[b], (int)g.pad[0], (int)g.pad[2], TFX_ACT_RELU6, TFX_ACT_RELU6,
-                                  static_cast<hipStream_t>(stream));
-      if (rc) return rc;
-      if (end_block == b + 1) return TFX_OK;
-      for (int i = 0; i < 3; ++i) shape[i] = g.out[i];
-      shape[3] = cout;
-      cur ^= 1;
-      continue;
-    }
-    // large batch, early block: depthwise and pointwise layer in one filter-stationary launch (block_stream.hip)
-    if (separable_stream_supported((int)batch, (int)shape[1], (int)shape[2], (int)shape[3], (int)cout, kStrides[b],
-                                   (int)g.out[1], (int)g.out[2], buf[cur], weights->dw_w[b], weights->dw_b[b],
-                                   weights->pw_w[b], weights->pw_b[b], block_out)) {
-      rc = launch_separable_stream(buf[cur], weights->dw_w[b], weights->dw_b[b], weights->pw_w[b], weights->pw_b[b],
-                                   block_out, (int)batch, (int)shape[1], (int)shape[2], (int)shape[3], (int)cout,
-                                   (int)g.out[1], (int)g.out[2], kStrides[b], (int)g.pad[0], (int)g.pad[2], TFX_ACT_RELU6,
-                                   TFX_ACT_RELU6, static_cast<hipStream_t>(stream));
-      if (rc) return rc;
-      if (end_block == b + 1) return TFX_OK;
-      for (int i = 0; i < 3; ++i) shape[i] = g.out[i];
-      shape[3] = cout;
-      cur ^= 1;
-      continue;
-    }
-    // From 800 000 outputs on (3 000 000 where they have few columns to share a split element) the depthwise output is
-    // handed over as bf16 planes (block_planes.hip), which lie at the end of the buffer that the block's output starts.
-    // Full width: batch 8 258 -> 223 us, 16 391 -> 303; with fewer outputs the two single-layer kernels are faster: half
-    // width, batch 8: 171 against 183.
-    {
-      const int64_t rows = batch * g.out[1] * g.out[2];
-      const size_t a_bytes = align_up(planes_elems(rows, (int)shape[3]) * 2), b_bytes = align_up(planes_elems(cout, (int)shape[3]) * 2);
-      const size_t need = a_bytes + b_bytes, have = plan.act_floats * sizeof(float) / kAlign * kAlign;
-      if (rows * cout >= (cout >= 256 ? 800000 : 3000000) && need + align_up((size_t)rows * cout * sizeof(float)) <= have &&
-          separable_planes_supported(rows, (int)shape[3], (int)cout, kStrides[b], buf[cur], weights->dw_w[b], weights->dw_b[b],
-                                     weights->pw_w[b], weights->pw_b[b], block_out)) {
-        char* const region = reinterpret_cast<char*>(buf[cur ^ 1]) + have - need;
-        rc = launch_separable_planes(buf[cur], weights->dw_w[b], weights->dw_b[b], weights->pw_w[b], weights->pw_b[b], block_out, region,
-                                     region + a_bytes, (int)batch, (int)shape[1], (int)shape[2], (int)shape[3], (int)cout, (int)g.out[1],
-                                     (int)g.out[2], kStrides[b], (int)g.pad[0], (int)g.pad[2], TFX_ACT_RELU6, static_cast<hipStream_t>(stream));
-        if (rc) return rc;
-        if (end_block == b + 1) return TFX_OK;
-        for (int i = 0; i < 3; ++i) shape[i] = g.out[i];
-        shape[3] = cout;
-        cur ^= 1;
-        continue;
+    if (aligned && form.form[b] != kTwo32) {
+      if (form.form[b] == kTile32) {
+        rc = launch_separable_tile(buf[cur], weights->dw_w[b], weights->dw_b[b], weights->pw_w[b], weights->pw_b[b],
+                                   ws + plan.off_packed + form.packed[b], block_out, (int)batch, (int)shape[1], (int)shape[2], (int)shape[3],
+                                   (int)cout, (int)g.out[1], (int)g.out[2], kStrides[b], (int)g.pad[0], (int)g.pad[2], TFX_ACT_RELU6,
+                                   static_cast<hipStream_t>(stream));
+      } else {
+        const auto launch = form.form[b] == kPatch32   ? launch_separable_patch
+                            : form.form[b] == kBlock32 ? launch_separable_block
+                                                       : launch_separable_stream;
+        rc = launch(buf[cur], weights->dw_w[b], weights->dw_b[b], weights->pw_w[b], weights->pw_b[b], block_out, (int)batch,
+                    (int)shape[1], (int)shape[2], (int)shape[3], (int)cout, (int)g.out[1], (int)g.out[2], kStrides[b], (int)g.pad[0],
+                    (int)g.pad[2], TFX_ACT_RELU6, TFX_ACT_RELU6, static_cast<hipStream_t>(stream));
       }
+      if (rc) return rc;
+      if (end_block == b + 1) return TFX_OK;
+      for (int i = 0; i < 3; ++i) shape[i] = g.out[i];
+      shape[3] = cout;
+      cur ^= 1;
+      continue;
     }
     rc = tfx_depthwise_conv2d(buf[cur], shape, weights->dw_w[b], fd, weights->dw_b[b], kStrides[b], kStrides[b],
                               TFX_PAD_SAME, TFX_ACT_RELU6, buf[cur ^ 1], stream);
@@ -693,64 +663,10 @@ int forward_impl(const tfx_mobilenet_v1_variant* variant, const float* input, in
 }
 }  // namespace
 
-namespace {
-// The whole forward pass: one chain of kernels on the caller's stream, or, from kSplitBatch on and if a second stream
-// is to be had, two half batches, each with its own part of the workspace, on two streams.
-int forward_whole(const tfx_mobilenet_v1_variant* variant, const float* input, int64_t batch,
-                  const tfx_mobilenet_v1_weights* weights, void* workspace, size_t workspace_bytes, float* probs,
-                  float* logits, void* stream, bool may_fork) {
-  // TFX_ONE_STREAM in the environment: no stream of the library's in this process (also for per-kernel profiles:
-  // overlapped kernels stretch each other's durations)
-  if (batch < kSplitBatch || !may_fork || std::getenv("TFX_ONE_STREAM") != nullptr)
-    return forward_impl(variant, input, batch, weights, workspace, workspace_bytes, probs, logits, 0, nullptr, stream);
-  if (const int bad = check_net_args(variant, input, batch, weights, workspace, probs)) return bad;
-  if (workspace_bytes < net_workspace_bytes(*variant, batch) || reinterpret_cast<uintptr_t>(workspace) % kAlign != 0)
-    return TFX_ERR_WORKSPACE;
-  hipStream_t main_stream = static_cast<hipStream_t>(stream);
-  const int chains = net_chains(batch);
-  std::unique_lock<std::mutex> guard(g_side_lock);
-  SideStreams* const side = side_streams(main_stream);
-  bool forked = side != nullptr && hipEventRecord(side->fork, main_stream) == hipSuccess;
-  int waiting = 0;  // side streams that have joined the caller's stream (or the graph it is being captured into)
-  for (; forked && waiting < chains - 1; ++waiting)
-    if (hipStreamWaitEvent(side->stream[waiting], side->fork, 0) != hipSuccess) break;
-  const bool all = forked && waiting == chains - 1;
-  const size_t image = (size_t)variant->image_size * variant->image_size * 3;
-  int rc = TFX_OK;
-  if (all) {
-    int64_t first = 0;
-    char* ws = static_cast<char*>(workspace);
-    for (int i = 0; i < chains && rc == TFX_OK; ++i) {
-      const int64_t n = part_images(batch, chains, i);
-      const size_t bytes = align_up(plan_net(*variant, n).bytes);
-      rc = forward_impl(variant, input + first * image, n, weights, ws, bytes, probs + first * variant->classes,
-                        logits ? logits + first * variant->classes : nullptr, 0, nullptr,
-                        i == 0 ? main_stream : side->stream[i - 1]);
-      first += n;
-      ws += bytes;
-    }
-  } else {
-    // no streams of the library's (creation failed, or this first large call comes inside a graph capture), or a
-    // wait could not be enqueued: one chain on the caller's stream
-    (void)hipGetLastError();
-    rc = forward_impl(variant, input, batch, weights, workspace, workspace_bytes, probs, logits, 0, nullptr, stream);
-  }
-  // every stream that waits for the fork is joined whatever happened in between, so that the caller's stream (or the
-  // graph it is being captured into) never ends with a side stream still forked
-  for (int i = 0; i < waiting; ++i)
-    if (hipEventRecord(side->join[i], side->stream[i]) != hipSuccess ||
-        hipStreamWaitEvent(main_stream, side->join[i], 0) != hipSuccess) {
-      (void)hipGetLastError();
-      if (rc == TFX_OK) rc = TFX_ERR_LAUNCH;
-    }
-  return rc;
-}
-}  // namespace
-
 int tfx_mobilenet_v1_variant_forward(const tfx_mobilenet_v1_variant* variant, const float* input, int64_t batch,
                                      const tfx_mobilenet_v1_weights* weights, void* workspace,
                                      size_t workspace_bytes, float* probs, float* logits, void* stream) {
-  return forward_whole(variant, input, batch, weights, workspace, workspace_bytes, probs, logits, stream, true);
+  return forward_impl(variant, input, batch, weights, workspace, workspace_bytes, probs, logits, 0, nullptr, stream);
 }
 
 int tfx_mobilenet_v1_variant_features_shape(const tfx_mobilenet_v1_variant* variant, int64_t batch, int end_block,
@@ -782,13 +698,12 @@ int tfx_mobilenet_v1_variant_forward_static(const tfx_mobilenet_v1_variant* vari
   if (!valid_variant(variant)) return TFX_ERR_ARG;
   if (batch < 1) return TFX_ERR_SHAPE;
   if (batch > 1024) return TFX_ERR_UNSUPPORTED;
-  if (net_workspace_bytes(*variant, batch) > kStaticScratchBytes) return TFX_ERR_WORKSPACE;
+  if (plan_net(*variant, batch).bytes > kStaticScratchBytes) return TFX_ERR_WORKSPACE;
   void* ws = static_scratch();
   if (!ws) return TFX_ERR_LAUNCH;
   // Every kernel of the forward pass writes the part of the workspace it later reads (feature maps, the fully
   // connected layer's partial sums), so nothing has to be cleared between calls.
-  // (no second stream here -- creating one allocates: one chain of kernels at every batch)
-  return forward_whole(variant, input, batch, weights, ws, kStaticScratchBytes, probs, logits, stream, false);
+  return forward_impl(variant, input, batch, weights, ws, kStaticScratchBytes, probs, logits, 0, nullptr, stream);
 }
 
 size_t tfx_mobilenet_v1_workspace_bytes_f16(const tfx_mobilenet_v1_variant* variant, int64_t batch) {

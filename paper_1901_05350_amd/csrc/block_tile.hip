@@ -1,0 +1,517 @@
+// A depthwise-separable block (depthwise 3x3 + bias + relu6, pointwise 1x1 + bias + clamp, fp32) in one launch, for the layers
+// whose pointwise filter does not fit a workgroup's LDS: the fp32 form of block_tile_f16.hip.
+//
+// The pointwise layer is a product on the binary16 matrix cores with operands split in two (pair.h).  A workgroup owns a tile of 32 TM
+// output pixels, as patches of 4 x 2, and 64 columns for each of its groups of wavefronts; all its threads compute the depthwise
+// output of the tile into LDS, split, and each wavefront multiplies the tile by its 64 columns of the filter, whose operands it loads
+// straight from L2 in the order of pack_filters_kernel.
+//
+// 64 x 14 x 14 x 512 -> 512, one layer: 33.6 us, of which 5.4 are the start and the launch, 9.5 the depthwise layer, 14.3 the contraction
+// (a megabyte of the filter for each CU through the path from L2, 73 GB/s to each; the matrix cores would take 8), 4.4 the stores; the
+// depthwise kernel and the product of bf16 parts that stood here took 66.  64 x 28 x 28 x 256 -> 256 83 -> 45, 256 -> 512 at stride 2
+// 45 -> 27, 7 x 7 x 1024 -> 1024 64 -> 39; the pass of 64 images 767 -> 562, of 16 290 -> 250, of 8 207 -> 192.
+//
+// Results that the split does not carry (pair.h) are computed again over the first ones, unless the pixel's depthwise output is NaN.
+#include "pair.h"
+
+namespace tfx {
+namespace {
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+
+constexpr int kXcds = 8, kMaxLayers = 13;
+
+struct TileArgs {
+  const float *x, *dw_w, *dw_b, *pw_w, *pw_b;
+  const half_t* packed;
+  const int* exps;
+  float* y;
+  int H, W, C, N, OH, OW, pt, pl;
+  int row_patches, col_patches, patches, tiles_n, total;
+  unsigned x_bytes, y_bytes;
+  int pw_act;
+};
+
+// S: stride; TM: 32-pixel blocks of a tile; WK: parts of the contraction (wavefront = column group + WN x part)
+template <int S, int TM, int WK>
+__global__ __launch_bounds__(512) void separable_tile_kernel(TileArgs g) {
+  static_assert(WK == 1 || TM == 1, "the parts' sums take the tile's place");
+  constexpr int PATCHES = 4 * TM, kAhead = TM == 1 ? 4 : 2;
+  // Few pixels, which leave the matrix cores idle, are computed as exactly as by the kernels that take them otherwise: all four
+  // products, and the large ones of four k-steps summed apart from those before (an instruction cuts off what lies behind the last
+  // place of its accumulator).
+  constexpr bool kFine = WK > 1;
+  struct Patch {
+    int out, cols, rows, ih, iw, image;  // first output pixel, extent inside the map; first tap's row and column, image's first row
+  };
+  extern __shared__ __align__(16) half_t tile[];  // the tile's depthwise output, two planes of [32 TM][C + 8]; later the parts' sums
+  __shared__ Patch patch[PATCHES];
+  __shared__ __align__(16) float bias[512];
+  __shared__ __align__(16) int exps[512];
+  __shared__ unsigned row_nan[TM];
+  __shared__ int lost, lost_tiny;
+
+  const int tid = threadIdx.x, lane = tid % 64, wave = __builtin_amdgcn_readfirstlane(tid / 64);
+  const int li = lane % 32, h = lane / 32;
+  const int waves_n = (int)blockDim.x / 64 / WK, wn = wave % waves_n, part = wave / waves_n;
+  int bid = blockIdx.x;
+  {  // tiles of the same pixels, and neighbouring ones, on one XCD
+    const int q = g.total / kXcds, rem = g.total % kXcds, xcd = bid % kXcds;
+    bid = xcd * q + (xcd < rem ? xcd : rem) + bid / kXcds;
+  }
+  const int tile_n = bid % g.tiles_n, tile_m = bid / g.tiles_n;
+  const int C = g.C, N = g.N, C4 = C / 4, LD = C + 8, plane = 32 * TM * LD;
+  const int first_n = 64 * tile_n * waves_n;
+
+  if (tid < PATCHES) {
+    const int i = tile_m * PATCHES + tid, row = i / g.row_patches, n = row / g.col_patches;
+    const int ow = 4 * (i % g.row_patches), oh = 2 * (row % g.col_patches);
+    Patch p;
+    p.out = (n * g.OH + oh) * g.OW + ow;
+    p.cols = i < g.patches ? (g.OW - ow < 4 ? g.OW - ow : 4) : 0;
+    p.rows = g.OH - oh < 2 ? 1 : 2;
+    p.ih = oh * S - g.pt;
+    p.iw = ow * S - g.pl;
+    p.image = n * g.H;
+    patch[tid] = p;
+  }
+  if (tid < TM) row_nan[tid] = 0;
+  if (tid == TM) lost = lost_tiny = 0;
+  for (int i = tid; i < 64 * waves_n; i += (int)blockDim.x) {
+    bias[i] = g.pw_b[first_n + i];
+    exps[i] = g.exps[first_n + i];
+  }
+  __syncthreads();
+
+  // Each workgroup fetches its share of the filter's lines into its XCD's L2 while it computes the depthwise layer, a dword of each
+  // (block_tile_f16.hip); those after the first 64 of an XCD find it there.
+  const int of_xcd = max(1, min(g.total / kXcds, 64)), lines = C * N / 32, l0 = lines * min((int)blockIdx.x / kXcds, of_xcd - 1) / of_xcd;
+  const int line = min(l0 + min(tid, (lines - 1) / of_xcd), lines - 1);
+  auto touch = [&]() __attribute__((always_inline)) { return reinterpret_cast<const unsigned*>(g.packed)[32 * line]; };
+  unsigned touched = 0;
+  const __amdgpu_buffer_rsrc_t xr = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(g.x), 0, (int)g.x_bytes, 0x00020000);
+  MapLoss loss;
+  if (tid >= PATCHES * C4) touched = touch();
+  for (int item = tid; item < PATCHES * C4; item += (int)blockDim.x) {
+    const int s = item / C4, c4 = item - s * C4;
+    constexpr int PX = S == 1 ? 4 : 2, ROWS = S + 3, COLS = (PX - 1) * S + 3;  // columns at a time, and what they read
+    f32x4 w[9];
+#pragma unroll
+    for (int t = 0; t < 9; ++t) w[t] = *reinterpret_cast<const f32x4*>(g.dw_w + (size_t)t * C + 4 * c4);
+    const f32x4 bv = *reinterpret_cast<const f32x4*>(g.dw_b + 4 * c4);
+    // byte offsets of a row and a column of x; outside the map (and for a patch outside the batch) the largest, which the
+    // saturating sum keeps: such a load is past the end and reads zeros
+    const Patch pt = patch[s];
+    unsigned row_off[ROWS];
+#pragma unroll
+    for (int i = 0; i < ROWS; ++i)
+      row_off[i] = (unsigned)(pt.ih + i) < (unsigned)g.H && pt.cols > 0 ? 4u * ((unsigned)(pt.image + pt.ih + i) * g.W * C + 4 * c4) : ~0u;
+#pragma unroll
+    for (int p0 = 0; p0 < 4; p0 += PX) {
+      f32x4 win[ROWS][COLS];
+#pragma unroll
+      for (int j = 0; j < COLS; ++j) {
+        const int iw = pt.iw + p0 * S + j;
+        const unsigned col_off = (unsigned)iw < (unsigned)g.W ? 4u * (unsigned)(iw * C) : ~0u;
+#pragma unroll
+        for (int i = 0; i < ROWS; ++i)
+          win[i][j] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(xr, __builtin_elementwise_add_sat(row_off[i], col_off), 0, 0));
+      }
+      if (item == tid && p0 == 0) touched = touch();
+#pragma unroll
+      for (int p = 0; p < 2 * PX; ++p) {
+        f32x4 acc = bv;
+#pragma unroll
+        for (int t = 0; t < 9; ++t)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) acc[e] = fmaf(win[p % 2 * S + t / 3][p / 2 * S + t % 3][e], w[t][e], acc[e]);
+        const int row = 8 * s + 4 * (p % 2) + p0 + p / 2;
+        const bool nan = __builtin_isunordered(acc[0], acc[1]) || __builtin_isunordered(acc[2], acc[3]);
+        h4 hi, lo;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float v = __builtin_amdgcn_fmed3f(acc[e], 0.f, 6.f);
+          loss.see(v);
+          half_t a, b;
+          split2(v, (float)(1 << kMapScale), a, b);
+          hi[e] = a, lo[e] = b;
+        }
+        if (nan) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) hi[e] = acc[e] == acc[e] ? hi[e] : (half_t)NAN;
+          atomicOr(&row_nan[row / 32], 1u << (row % 32));
+        }
+        *reinterpret_cast<h4*>(tile + row * LD + 4 * c4) = hi;
+        *reinterpret_cast<h4*>(tile + plane + row * LD + 4 * c4) = lo;
+      }
+    }
+  }
+  {
+    const int l = loss.lost(8 * PATCHES * C4 / (int)blockDim.x * 4 + 32);  // (all that this thread computed, for one of them)
+    if (l != 0) {
+      atomicAdd(&lost, l & kLostMost);
+      if ((l & kLostTiny) != 0) atomicOr(&lost_tiny, kLostTiny);
+    }
+  }
+
+  asm volatile("" ::"v"(touched));
+  __builtin_amdgcn_sched_barrier(0);
+  // the filter's operands, in the order of pack_filters_kernel
+  const int n0 = first_n + 64 * wn;
+  const int steps = C / 16, s0 = steps / WK * part, s1 = s0 + steps / WK;
+  const __amdgpu_buffer_rsrc_t wr = __builtin_amdgcn_make_buffer_rsrc(const_cast<half_t*>(g.packed), 0, C * N * 4, 0x00020000);
+  const int wp = n0 / 64 * steps * 4096;
+  h8 raw[kAhead][2][2];
+  auto load_step = [&](int s, h8 (&r)[2][2]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      r[i / 2][i % 2] = __builtin_bit_cast(h8, __builtin_amdgcn_raw_buffer_load_b128(wr, 16 * lane + 1024 * i, wp + 4096 * s, 0));
+  };
+#pragma unroll
+  for (int u = 0; u < kAhead; ++u) load_step(s0 + u, raw[u]);
+  f32x16 acc[TM][2], mixed[TM][2], part_sum[2];
+#pragma unroll
+  for (int t = 0; t < TM; ++t)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) acc[t][0][i] = acc[t][1][i] = mixed[t][0][i] = mixed[t][1][i] = 0.f;
+  __syncthreads();
+
+  // The scheduling barriers keep the loads of a step together (block_tile_f16.hip).
+  const half_t* const a_base = tile + li * LD + 8 * h;
+  h8 a[2][TM][2];
+  auto read = [&](int buf, int s) __attribute__((always_inline)) {
+#pragma unroll
+    for (int t = 0; t < TM; ++t)
+#pragma unroll
+      for (int p = 0; p < 2; ++p) a[buf][t][p] = *reinterpret_cast<const h8*>(a_base + p * plane + 32 * t * LD + 16 * s);
+  };
+  read(0, s0);
+  for (int s = s0; s < s1; s += kAhead) {
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) {
+      read((u + 1) & 1, s + u + 1 < s1 ? s + u + 1 : s0);
+      h8 b[2][2];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) b[i / 2][i % 2] = raw[u][i / 2][i % 2];
+      load_step(s + u + kAhead < s1 ? s + u + kAhead : s1 - 1, raw[u]);  // past the end: the last step again, dropped
+#pragma unroll
+      for (int pass = kFine ? 0 : 1; pass < 4; ++pass)  // (low, low), (low, high), (high, high), (high, low)
+#pragma unroll
+        for (int t = 0; t < TM; ++t)
+#pragma unroll
+          for (int j = 0; j < 2; ++j) {
+            const h8 at = pass == 0 ? a[u & 1][t][1] * (half_t)(1 / kLow) : a[u & 1][t][pass == 3];
+            f32x16& to = pass == 2 ? acc[t][j] : mixed[t][j];
+            if (kFine && pass == 2) part_sum[j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(b[j][0], at, u == 0 ? f32x16{} : part_sum[j], 0, 0, 0);
+            else to = __builtin_amdgcn_mfma_f32_32x32x16_f16(b[j][pass < 2], at, to, 0, 0, 0);
+          }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    if constexpr (kFine) acc[0][0] += part_sum[0], acc[0][1] += part_sum[1];
+  }
+
+  // Lane (li, h) has pixel li of each 32 and, in group i of the accumulators of column block j, channels 32 j + 8 i + 4 h ... + 3 of
+  // the wavefront's 64.
+  const ActClamp clamp = make_act(g.pw_act);
+  const float lowest = clamp.on ? 0.f : -INFINITY;
+  unsigned out[TM];
+  const __amdgpu_buffer_rsrc_t yr = __builtin_amdgcn_make_buffer_rsrc(g.y, 0, (int)g.y_bytes, 0x00020000);
+#pragma unroll
+  for (int t = 0; t < TM; ++t) {
+    const Patch pt = patch[4 * t + li / 8];
+    const int row = li % 8 / 4, col = li % 4;
+    // past the end, where nothing is stored, for a lane without a pixel
+    out[t] = row < pt.rows && col < pt.cols ? 4u * ((unsigned)(pt.out + row * g.OW + col) * N + n0 + 4 * h) : 0x80000000u;
+  }
+  constexpr int GROUPS = 8 * TM / WK;  // of four channels, for this wavefront
+  const int g0 = part * GROUPS;
+  f32x4 v[GROUPS];
+  if constexpr (WK == 1) {
+#pragma unroll
+    for (int q = 0; q < GROUPS; ++q)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        v[q][e] = fmaf(mixed[q / 8][q / 4 % 2][4 * (q % 4) + e], 1 / kLow, acc[q / 8][q / 4 % 2][4 * (q % 4) + e]);
+  } else {
+    // the parts' sums through LDS: part p adds up groups p GROUPS ... of its columns
+    f32x4* const sums = reinterpret_cast<f32x4*>(tile);  // [wave][group][64]
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      f32x4 t;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) t[e] = fmaf(mixed[0][q / 4][4 * (q % 4) + e], 1 / kLow, acc[0][q / 4][4 * (q % 4) + e]);
+      sums[(wave * 8 + q) * 64 + lane] = t;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < GROUPS; ++q) {
+      v[q] = sums[(wn * 8 + g0 + q) * 64 + lane];
+#pragma unroll
+      for (int p = 1; p < WK; ++p) v[q] += sums[((p * waves_n + wn) * 8 + g0 + q) * 64 + lane];
+    }
+  }
+  float finite = 0.f, smallest = INFINITY;  // NaN where a result is not finite; the smallest magnitude
+  int column_lost = 0, exponent = 1 << 20;
+#pragma unroll
+  for (int q = 0; q < GROUPS; ++q) {
+    const int i = 64 * wn + 8 * ((g0 + q) % 8) + 4 * h;
+    const f32x4 bv = *reinterpret_cast<const f32x4*>(bias + i);
+    const i32x4 ev = *reinterpret_cast<const i32x4*>(exps + i);
+    f32x4 o;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      v[q][e] = ldexpf(v[q][e], -(ev[e] >> 17) - kMapScale) + bv[e];
+      finite = fmaf(v[q][e], 0.f, finite);
+      smallest = fminf(smallest, fabsf(v[q][e]));
+      column_lost |= ev[e];  // (at least each of them)
+      exponent = min(exponent, ev[e] >> 17);
+      o[e] = __builtin_amdgcn_fmed3f(v[q][e], lowest, clamp.hi);
+    }
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, o), yr, out[TM == 1 ? 0 : q / 8] + 32 * ((g0 + q) % 8), 0, 0);
+  }
+  const int tile_lost = min(lost, kLostMost) | lost_tiny;
+  // (the code behind this is in no instruction cache)
+  if (__builtin_amdgcn_ballot_w64(finite != finite || smallest < loss_limit(C, exponent, more_lost(tile_lost, column_lost))) == 0) return;
+
+  // Which of a lane's results are computed again, over the first ones: a pixel at a time, its depthwise output over the lanes; then
+  // up to four columns one after the other, a sum over the lanes, or all 64, a lane for each.
+  constexpr int WORDS = (4 * GROUPS + 31) / 32;
+  unsigned again[WORDS] = {};
+#pragma unroll
+  for (int q = 0; q < GROUPS; ++q) {
+    const i32x4 ev = *reinterpret_cast<const i32x4*>(exps + 64 * wn + 8 * ((g0 + q) % 8) + 4 * h);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const bool small = fabsf(v[q][e]) < loss_limit(C, ev[e] >> 17, more_lost(tile_lost, ev[e]));
+      if ((small || !__builtin_isfinite(v[q][e])) && out[TM == 1 ? 0 : q / 8] < 0x80000000u) again[q / 8] |= 1u << (4 * (q % 8) + e);
+    }
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // behind the first results
+#pragma unroll
+  for (int t = 0; t < WORDS; ++t) {
+    unsigned long long lanes = __builtin_amdgcn_ballot_w64(again[t] != 0);
+    unsigned pixels = (unsigned)lanes | (unsigned)(lanes >> 32);
+    while (pixels != 0) {
+      const int px = __builtin_ctz(pixels);
+      pixels &= pixels - 1;
+      const int q = lane / 8 - g0;  // (g0 is 0 where there are more than 8 groups)
+      const unsigned word = __shfl(again[t], px + 32 * (lane / 4 % 2));
+      const bool mine = q >= 0 && q < GROUPS && (word >> (4 * (q & 7) + lane % 4) & 1) != 0;  // of column `lane`
+      const unsigned long long columns = __builtin_amdgcn_ballot_w64(mine);
+      const Patch p = patch[4 * t + px / 8];
+      const int ih = p.ih + px % 8 / 4 * S, iw = p.iw + px % 4 * S;
+      auto depthwise = [&](int k) __attribute__((always_inline)) {
+        float d = g.dw_b[k];
+#pragma unroll
+        for (int kk = 0; kk < 9; ++kk) {
+          const int r = ih + kk / 3, c = iw + kk % 3;
+          const bool in = (unsigned)r < (unsigned)g.H && (unsigned)c < (unsigned)g.W;
+          const float xv = g.x[in ? ((size_t)(p.image + r) * g.W + c) * C + k : 0];
+          d = in ? fmaf(xv, g.dw_w[(size_t)kk * C + k], d) : d;
+        }
+        return apply_act(d, TFX_ACT_RELU6);
+      };
+      float sum = 0.f;
+      if ((row_nan[t] >> px & 1) != 0) {
+        sum = NAN;
+      } else if (__builtin_popcountll(columns) <= 4) {
+        float d[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) d[i] = 64 * i < C ? depthwise(64 * i + lane) : 0.f;
+        for (unsigned long long rest = columns; rest != 0; rest &= rest - 1) {
+          const int col = __builtin_ctzll(rest);
+          float s = 0.f;
+#pragma unroll
+          for (int i = 0; i < 16; ++i) s = fmaf(d[i], 64 * i < C ? g.pw_w[(size_t)(64 * i + lane) * N + n0 + col] : 0.f, s);
+#pragma unroll
+          for (int m = 32; m > 0; m /= 2) s += __shfl_xor(s, m);
+          sum = lane == col ? s : sum;
+        }
+      } else {
+#pragma unroll 1
+        for (int k0 = 0; k0 < C; k0 += 64) {
+          const float d = depthwise(k0 + lane);
+          float part_sum = 0.f;
+#pragma unroll 32
+          for (int k = 0; k < 64; ++k)
+            part_sum = fmaf(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(d), k)), g.pw_w[(size_t)(k0 + k) * N + n0 + lane], part_sum);
+          sum += part_sum;
+        }
+      }
+      const unsigned to = (unsigned)__builtin_amdgcn_readlane((int)out[TM == 1 ? 0 : t], px);
+      if (mine) *reinterpret_cast<float*>(reinterpret_cast<char*>(g.y) + to + 4u * (unsigned)lane) = apply_act(sum + bias[64 * wn + lane], clamp);
+    }
+  }
+}
+
+// The operands of the contraction's k-step s (rows 16 s ... + 15) and 64 columns from 64 c on, for each lane: 8 rows from
+// 8 (lane / 32) on of column 32 j + lane % 32, part p, at piece 64 (4 (steps c + s) + 2 j + p) + lane; behind them for each column
+// 2^17 times the exponent of its scale, plus its losses (pair.h).  A workgroup for every 32 columns.
+struct PackArgs {
+  const float* w[kMaxLayers];
+  half_t* out[kMaxLayers];
+  int* exps[kMaxLayers];
+  int c[kMaxLayers], n[kMaxLayers], first[kMaxLayers + 1];  // first: workgroups of the layers before
+  int layers;
+};
+__global__ __launch_bounds__(1024) void pack_filters_kernel(PackArgs g) {
+  __shared__ float wave_most[16][32];
+  __shared__ int lost[32], tiny[32];
+  int l = 0;
+  while (l + 1 < g.layers && (int)blockIdx.x >= g.first[l + 1]) ++l;
+  const int nb = (int)blockIdx.x - g.first[l], wave = threadIdx.x / 64, lane = threadIdx.x % 64, li = lane % 32, h = lane / 32;
+  const int N = g.n[l], steps = g.c[l] / 16, n = 32 * nb + li;
+  constexpr int MOST = 4;  // steps of a wavefront, of up to 64
+  float v[MOST][8];
+  float most = 0.f;
+#pragma unroll
+  for (int u = 0; u < MOST; ++u) {
+    const int s = min(wave + 16 * u, steps - 1);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v[u][i] = g.w[l][(size_t)(16 * s + 8 * h + i) * N + n];
+  }
+#pragma unroll
+  for (int u = 0; u < MOST; ++u)
+#pragma unroll
+    for (int i = 0; i < 8; ++i) most = __builtin_isfinite(v[u][i]) ? fmaxf(most, fabsf(v[u][i])) : most;
+  most = fmaxf(most, __shfl_xor(most, 32));
+  if (h == 0) wave_most[wave][li] = most;
+  if (threadIdx.x < 32) lost[threadIdx.x] = tiny[threadIdx.x] = 0;
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < 16; ++w) most = fmaxf(most, wave_most[w][li]);
+  const int e = column_exponent(most);
+  int loses = 0;
+#pragma unroll
+  for (int u = 0; u < MOST; ++u) {
+    const int s = wave + 16 * u;
+    if (s >= steps) break;
+    h8 part[2];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      half_t a, b;
+      loses = more_lost(loses, split_filter(v[u][i], e, a, b));
+      part[0][i] = a, part[1][i] = b;
+    }
+    h8* const out = reinterpret_cast<h8*>(g.out[l]) + (size_t)64 * (4 * (steps * (nb / 2) + s) + 2 * (nb % 2)) + lane;
+    out[0] = part[0];
+    out[64] = part[1];
+  }
+  if (loses != 0) {
+    atomicAdd(&lost[li], loses & kLostMost);
+    if ((loses & kLostTiny) != 0) atomicOr(&tiny[li], kLostTiny);
+  }
+  __syncthreads();
+  if (threadIdx.x < 32) g.exps[l][n] = (e << 17) | lost[li] | tiny[li];
+}
+
+size_t tile_lds(int tm, int waves_n, int wk, int c) {
+  const size_t depth = (size_t)32 * tm * (c + 8) * 2 * sizeof(half_t), sums = wk == 1 ? 0 : (size_t)waves_n * wk * 32 * 64 * sizeof(float);
+  return depth > sums ? depth : sums;
+}
+
+template <int S, int TM, int WK>
+int launch_tile(const TileArgs& args, int waves_n, hipStream_t stream) {
+  TileArgs g = args;
+  auto kern = separable_tile_kernel<S, TM, WK>;
+  const size_t lds_bytes = tile_lds(TM, waves_n, WK, g.C);
+  static std::atomic<uint64_t> lds_allowed{0};
+  if (allow_dynamic_lds(reinterpret_cast<const void*>(kern), 150 * 1024, lds_allowed) != TFX_OK) return TFX_ERR_LAUNCH;
+  g.tiles_n = g.N / (64 * waves_n);
+  const int tiles_m = (g.patches + 4 * TM - 1) / (4 * TM);
+  g.total = tiles_m * g.tiles_n;
+  hipLaunchKernelGGL(kern, dim3((unsigned)g.total), dim3(64u * waves_n * WK), lds_bytes, stream, g);
+  return check_launch();
+}
+
+// The largest divisor of `groups` up to `most`.
+int divisor(int groups, int most) {
+  for (int d = groups < most ? groups : most; d > 1; --d)
+    if (groups % d == 0) return d;
+  return 1;
+}
+
+// The tile (32 tm pixels, column groups of wavefronts, parts of the contraction): the least modelled time -- a start; for each round of
+// resident workgroups another and the depthwise layer of a thread; for each workgroup of a CU its depthwise loads, its columns of
+// the filter from L2, its matrix instructions and stores.  Fitted to 4233 launches (2 - 64 images, every width, 3 sizes); the form it
+// takes is 2 % slower than the fastest on average, 19 % at most.  14 x 14 x 512 -> 512, us a launch: 64 images {2, 8, 1} 34, {1, 8, 1} 40;
+// 16 images {1, 4, 2} 15.6, {1, 8, 1} 18.4, {2, 8, 1} 26; 8 images {1, 2, 4} 12.2, {1, 4, 2} 13.6; 4 images {1, 1, 4} 10.6, {1, 4, 2} 13.3.
+struct TileForm {
+  int tm, waves_n, wk;
+  double us;
+};
+TileForm tile_form(long long patches, int c, int n, int stride) {
+  const int groups = n / 64;
+  TileForm best{};
+  best.us = 1e30;
+  for (int tm = 1; tm <= 2 && tm * c <= 1024; ++tm)
+    for (int wk = 1; wk <= (tm == 1 ? 4 : 1) && c % (64 * wk) == 0; wk *= 2)
+      for (int most = 8 / wk; most > 0; most /= 2) {
+        const int waves_n = divisor(groups, most), waves = waves_n * wk;
+        const long long blocks = (patches + 4 * tm - 1) / (4 * tm) * (groups / waves_n);
+        const int lds = (int)tile_lds(tm, waves_n, wk, c) + 5 * 1024, resident = 8 / waves < 160 * 1024 / lds ? 8 / waves : 160 * 1024 / lds;
+        const double rounds = (double)((blocks + 256 * resident - 1) / (256 * resident)), cu = (double)((blocks + 255) / 256);
+        const double us = 3.1 + rounds * (1.4 + .0157 * c * tm * stride / waves) +
+                          cu * (c * (1.09e-3 * tm * stride + 4.9e-3 * tm + 1.3e-3 * waves_n + .33e-3 * tm * waves_n) + .59 * tm * waves_n);
+        if (us < best.us) best = TileForm{tm, waves_n, wk, us};
+      }
+  return best;
+}
+}  // namespace
+
+size_t separable_tile_packed_bytes(int c, int n) { return ((size_t)c * n + (size_t)n) * sizeof(float); }
+
+bool separable_tile_supported(int batch, int h, int w, int c, int n, int stride, int oh, int ow, const void* x, const void* dw_w,
+                              const void* dw_b, const void* pw_w, const void* pw_b, const void* y) {
+  const void* ptrs[] = {x, dw_w, dw_b, pw_w, pw_b, y};
+  bool aligned = true;
+  for (const void* p : ptrs) aligned = aligned && reinterpret_cast<uintptr_t>(p) % 16 == 0;
+  const long long patches = (long long)batch * ((oh + 1) / 2) * ((ow + 3) / 4), x_bytes = (long long)batch * h * w * c * 4,
+                  y_bytes = (long long)batch * oh * ow * n * 4;
+  return aligned && (stride == 1 || stride == 2) && c % 64 == 0 && c <= 1024 && n % 64 == 0 && n <= 1024 &&
+         x_bytes < (1ll << 31) && y_bytes < (1ll << 31) && patches < (1ll << 27);
+}
+
+int launch_separable_tile(const float* x, const float* dw_w, const float* dw_b, const float* pw_w, const float* pw_b, const void* packed,
+                          float* y, int batch, int h, int w, int c, int n, int oh, int ow, int stride, int pt, int pl, int pw_act,
+                          hipStream_t stream) {
+  const int row_patches = (ow + 3) / 4, col_patches = (oh + 1) / 2, patches = batch * col_patches * row_patches;
+  const half_t* const parts = static_cast<const half_t*>(packed);
+  const TileArgs g{x, dw_w, dw_b, pw_w, pw_b, parts, reinterpret_cast<const int*>(parts + (size_t)2 * c * n), y, h, w, c, n, oh, ow, pt, pl,
+                   row_patches, col_patches, patches, 0, 0, (unsigned)((long long)batch * h * w * c * 4),
+                   (unsigned)((long long)batch * oh * ow * n * 4), pw_act};
+  const TileForm f = tile_form(patches, c, n, stride);
+#define TFX_TILE(S, TM, WK) \
+  if (stride == S && f.tm == TM && f.wk == WK) return launch_tile<S, TM, WK>(g, f.waves_n, stream);
+  TFX_TILE(1, 2, 1)
+  TFX_TILE(1, 1, 1)
+  TFX_TILE(1, 1, 2)
+  TFX_TILE(1, 1, 4)
+  TFX_TILE(2, 2, 1)
+  TFX_TILE(2, 1, 1)
+  TFX_TILE(2, 1, 2)
+  TFX_TILE(2, 1, 4)
+#undef TFX_TILE
+  return TFX_ERR_UNSUPPORTED;
+}
+
+int launch_pack_filters(int layers, const float* const* w, void* const* packed, const int* c, const int* n, hipStream_t stream) {
+  PackArgs g{};
+  if (layers > kMaxLayers) return TFX_ERR_UNSUPPORTED;
+  for (int i = 0; i < layers; ++i) {
+    g.w[i] = w[i];
+    g.out[i] = static_cast<half_t*>(packed[i]);
+    g.exps[i] = reinterpret_cast<int*>(g.out[i] + (size_t)2 * c[i] * n[i]);
+    g.c[i] = c[i], g.n[i] = n[i];
+    g.first[i + 1] = g.first[i] + n[i] / 32;
+  }
+  g.layers = layers;
+  hipLaunchKernelGGL(pack_filters_kernel, dim3((unsigned)g.first[layers]), dim3(1024), 0, stream, g);
+  return check_launch();
+}
+
+}  // namespace tfx

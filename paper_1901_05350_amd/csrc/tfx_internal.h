@@ -336,15 +336,15 @@ int launch_separable_patch(const float* x, const float* dw_w, const float* dw_b,
                            int batch, int h, int w, int c, int n, int oh, int ow, int stride, int pt, int pl, int dw_act, int pw_act,
                            hipStream_t stream);
 
-// A depthwise-separable block of a batch as a depthwise kernel that writes bf16 planes and a product of planes
-// (block_planes.hip): any c % 32 == 0, n % 64 == 0.  a_planes / b_planes: planes_elems(rows, c) / planes_elems(n, c)
-// 16-bit words, 16-byte aligned, not overlapping x or y; rows = output pixels.  The depthwise layer's activation is relu6.
-size_t planes_elems(long long rows, int c);
-bool separable_planes_supported(long long rows, int c, int n, int stride, const void* x, const void* dw_w, const void* dw_b,
-                                const void* pw_w, const void* pw_b, const void* y);
-int launch_separable_planes(const float* x, const float* dw_w, const float* dw_b, const float* pw_w, const float* pw_b, float* y,
-                            void* a_planes, void* b_planes, int batch, int h, int w, int c, int n, int oh, int ow, int stride, int pt,
-                            int pl, int pw_act, hipStream_t stream);
+// A block whose pointwise filter does not fit LDS, with a tile's depthwise output there instead (block_tile.hip); its activation is
+// relu6.  `packed`: separable_tile_packed_bytes(c, n), 16-byte aligned, as launch_pack_filters (up to 13 layers) filled it.
+size_t separable_tile_packed_bytes(int c, int n);
+bool separable_tile_supported(int batch, int h, int w, int c, int n, int stride, int oh, int ow, const void* x, const void* dw_w,
+                              const void* dw_b, const void* pw_w, const void* pw_b, const void* y);
+int launch_separable_tile(const float* x, const float* dw_w, const float* dw_b, const float* pw_w, const float* pw_b, const void* packed,
+                          float* y, int batch, int h, int w, int c, int n, int oh, int ow, int stride, int pt, int pl, int pw_act,
+                          hipStream_t stream);
+int launch_pack_filters(int layers, const float* const* w, void* const* packed, const int* c, const int* n, hipStream_t stream);
 
 // The same on binary16 storage (block_stream_f16.hip).
 bool separable_stream_f16_supported(int batch, int h, int w, int c, int n, int stride, int oh, int ow, const void* x,

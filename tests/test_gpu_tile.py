@@ -1,0 +1,48 @@
+"""fp32 blocks with their depthwise output in LDS (block_tile.hip): every tile form, and values that the split in two halves loses."""
+import numpy as np
+import pytest
+
+from paper_1901_05350_amd import inputs
+from tests.util import assert_close, dev, host
+
+pytestmark = pytest.mark.gpu
+
+
+# 28 x 28 in tiles of 64 pixels; 14 x 14 and 7 x 7 in tiles of 32 with the contraction in 1, 2 and 4 parts; maps of odd sizes, whose last
+# patches are cut; 3 column groups; 64 channels
+@pytest.mark.parametrize("q,size,batch,end_block", [(4, 224, 9, 5), (4, 224, 64, 13), (4, 224, 20, 13), (4, 233, 7, 12), (4, 161, 30, 7),
+                                                    (3, 201, 33, 13), (2, 131, 61, 12), (2, 224, 12, 7), (1, 224, 40, 11)])
+def test_tile_blocks(q, size, batch, end_block):
+    import paper_1901_05350_amd as tfx
+    d = inputs.mobilenet_v1(seed=71 + q, batch=2, image_size=size, width_quarters=q)
+    image = np.concatenate([d["image"]] * (batch // 2) + [d["image"][:batch % 2]])
+    got = host(tfx.MobileNetV1(d["weights"], batch=batch, image_size=size, width_quarters=q).features(dev(image), end_block))
+    one = tfx.MobileNetV1(d["weights"], batch=1, image_size=size, width_quarters=q)
+    for i in (0, 1):
+        ref = host(one.features(dev(d["image"][i:i + 1]), end_block))
+        for j in range(i, batch, 2):
+            assert_close(got[j:j + 1], ref, "image %d" % j)
+
+
+@pytest.mark.parametrize("batch", [8, 64])
+def test_tile_blocks_columns_of_lost_bits(batch):
+    """A column whose values lie 2^-32 ... 2^-70 below its largest, which multiplies zeros: what the split loses of the others is up to
+    2^-20 ... 1 of them, and the results, sums of 511 products, are theirs alone."""
+    import paper_1901_05350_amd as tfx
+    d = inputs.mobilenet_v1(seed=75, batch=8)
+    w, b = d["weights"], 7
+    w["dw_w"][b][:, :, 5], w["dw_b"][b][5] = 0, 0
+    cols = {33: -32, 100: -40, 101: -50, 511: -70}
+    for col, scale in cols.items():
+        w["pw_w"][b][0, 0, :, col] *= 2.0 ** scale
+        w["pw_w"][b][0, 0, 5, col] = 0.25
+        w["pw_b"][b][col] = 0
+    image = np.concatenate([d["image"]] * (batch // 8))
+    got = host(tfx.MobileNetV1(w, batch=batch).features(dev(image), b + 1)).astype(np.float64)
+    for i in (0, 3, batch - 1):
+        ref = host(tfx.MobileNetV1(w, batch=1).features(dev(image[i:i + 1]), b + 1)).astype(np.float64)
+        for col, scale in cols.items():
+            assert (ref[..., col] != 0).any()
+            # 512 roundings of 24 bits on either side, of terms of up to 6 x 0.5
+            assert np.all(np.abs(got[i, ..., col] - ref[0, ..., col]) <= 2 * 512 * 2.0 ** -24 * 3 * 2.0 ** scale), col
+        assert_close(got[i:i + 1], ref, "image %d" % i)
