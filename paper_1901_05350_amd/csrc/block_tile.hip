@@ -130,22 +130,22 @@ __global__ __launch_bounds__(512) void separable_tile_kernel(TileArgs g) {
           for (int e = 0; e < 4; ++e) acc[e] = fmaf(win[p % 2 * S + t / 3][p / 2 * S + t % 3][e], w[t][e], acc[e]);
         const int row = 8 * s + 4 * (p % 2) + p0 + p / 2;
         const bool nan = __builtin_isunordered(acc[0], acc[1]) || __builtin_isunordered(acc[2], acc[3]);
-        h4 hi, lo;
+        floatx4 v;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          const float v = __builtin_amdgcn_fmed3f(acc[e], 0.f, 6.f);
-          loss.see(v);
-          half_t a, b;
-          split2(v, (float)(1 << kMapScale), a, b);
-          hi[e] = a, lo[e] = b;
+          v[e] = __builtin_amdgcn_fmed3f(acc[e], 0.f, 6.f);
+          loss.see(v[e]);
         }
+        pairx4 hi, lo;
+        split2(v, (float)(1 << kMapScale), hi, lo);
         if (nan) {
-#pragma unroll
-          for (int e = 0; e < 4; ++e) hi[e] = acc[e] == acc[e] ? hi[e] : (half_t)NAN;
+          constexpr unsigned kNan = 0x7e00;
+          hi[0] = (acc[0] == acc[0] ? hi[0] & 0xffffu : kNan) | (acc[1] == acc[1] ? hi[0] & 0xffff0000u : kNan << 16);
+          hi[1] = (acc[2] == acc[2] ? hi[1] & 0xffffu : kNan) | (acc[3] == acc[3] ? hi[1] & 0xffff0000u : kNan << 16);
           atomicOr(&row_nan[row / 32], 1u << (row % 32));
         }
-        *reinterpret_cast<h4*>(tile + row * LD + 4 * c4) = hi;
-        *reinterpret_cast<h4*>(tile + plane + row * LD + 4 * c4) = lo;
+        *reinterpret_cast<pairx4*>(tile + row * LD + 4 * c4) = hi;
+        *reinterpret_cast<pairx4*>(tile + plane + row * LD + 4 * c4) = lo;
       }
     }
   }
@@ -275,7 +275,7 @@ __global__ __launch_bounds__(512) void separable_tile_kernel(TileArgs g) {
   }
   const int tile_lost = min(lost, kLostMost) | lost_tiny;
   // (the code behind this is in no instruction cache)
-  if (__builtin_amdgcn_ballot_w64(finite != finite || smallest < loss_limit(C, exponent, more_lost(tile_lost, column_lost))) == 0) return;
+  if (__builtin_amdgcn_ballot_w64(finite != finite || smallest < loss_limit(C, exponent + kMapScale, more_lost(tile_lost, column_lost))) == 0) return;
 
   // Which of a lane's results are computed again, over the first ones: a pixel at a time, its depthwise output over the lanes; then
   // up to four columns one after the other, a sum over the lanes, or all 64, a lane for each.
@@ -286,7 +286,7 @@ __global__ __launch_bounds__(512) void separable_tile_kernel(TileArgs g) {
     const i32x4 ev = *reinterpret_cast<const i32x4*>(exps + 64 * wn + 8 * ((g0 + q) % 8) + 4 * h);
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      const bool small = fabsf(v[q][e]) < loss_limit(C, ev[e] >> 17, more_lost(tile_lost, ev[e]));
+      const bool small = fabsf(v[q][e]) < loss_limit(C, (ev[e] >> 17) + kMapScale, more_lost(tile_lost, ev[e]));
       if ((small || !__builtin_isfinite(v[q][e])) && out[TM == 1 ? 0 : q / 8] < 0x80000000u) again[q / 8] |= 1u << (4 * (q % 8) + e);
     }
   }

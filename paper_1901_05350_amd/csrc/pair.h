@@ -1,4 +1,4 @@
-// fp32 products on the binary16 matrix cores, operands split in two: the blocks of block_tile.hip.
+// fp32 products on the binary16 matrix cores, operands split in two: the blocks of block_tile.hip, the products of gemm_pair.hip.
 //
 // a = h + l / 2^11 with h the nearest half and l the nearest half of 2^11 times the remainder: 22 bits and the remainder's sign, so
 // the pair misses at most the last bit of a float's 24.  Three or four products of halfs (h h, h l, l h, and l l, 2^-24 of the product
@@ -11,7 +11,7 @@
 // four k-steps summed apart) 2.43 and 3.68, 3/4 width 33 images 2.2 and 2.9.
 //
 // Binary16 has few exponents, so operands are scaled by powers of two: a depthwise output, 0 ... 6, by 2^13, a column of a filter
-// so that its largest value is in [2^14, 2^15).
+// so that its largest value is in [2^14, 2^15), an operand of a tiled product by its first slice (gemm_pair.hip).
 //
 // Values that the split does not carry: a scaled value below 2^-14 loses up to 2^-36, one below 2^-60 no more than itself.  With
 // operands below 2^16 a sum of K products, n of them with the first, then misses less than n 2^-20 + K 2^-44, which a result of 2^24
@@ -33,12 +33,21 @@ typedef _Float16 h4 __attribute__((ext_vector_type(4)));
 constexpr int kMapScale = 13;  // depthwise outputs times 2^13
 constexpr float kLow = 2048.f;  // second parts times 2^11
 
-// both parts of v scale (the remainder is exact before it is rounded)
-__device__ __forceinline__ void split2(float v, float scale, half_t& h, half_t& l) {
-  float scaled = v * scale;
-  asm("" : "+v"(scaled));  // (left to itself the compiler rounds twice, once for h and once for the remainder)
-  h = (half_t)scaled;
-  l = (half_t)fmaf((float)h, -kLow, v * (scale * kLow));
+// Both parts of a scale and b scale, the first in the low halves.  The remainder is exact before it is rounded.  (In C++ the compiler
+// converts twice, once for h and once for the remainder: six instructions a value instead of three and a half.)
+__device__ __forceinline__ void split2(float a, float b, float scale, unsigned& h, unsigned& l) {
+  const float low = scale * kLow;
+  asm("v_cvt_pk_f16_f32 %0, %1, %2" : "=v"(h) : "v"(a * scale), "v"(b * scale));
+  asm("v_fma_mixlo_f16 %0, %1, %2, %3 op_sel_hi:[1,0,0]\n\tv_fma_mixhi_f16 %0, %1, %2, %4 op_sel:[1,0,0] op_sel_hi:[1,0,0]"
+      : "=&v"(l)
+      : "v"(h), "s"(-kLow), "v"(a * low), "v"(b * low));
+}
+typedef unsigned pairx4 __attribute__((ext_vector_type(2)));  // four halfs
+__device__ __forceinline__ void split2(const floatx4& v, float scale, pairx4& h, pairx4& l) {
+  unsigned h0, h1, l0, l1;
+  split2(v[0], v[1], scale, h0, l0);
+  split2(v[2], v[3], scale, h1, l1);
+  h = pairx4{h0, h1}, l = pairx4{l0, l1};
 }
 
 // What operands lose: how many of them up to 2^-36 (kLostMost counts as all), plus kLostTiny where one loses up to 2^-60.
@@ -65,18 +74,50 @@ __device__ __forceinline__ int column_exponent(float most) {
 // both parts of a filter value in a column of exponent e; its losses
 __device__ __forceinline__ int split_filter(float w, int e, half_t& h, half_t& l) {
   const float t = ldexpf(w, e);
-  split2(t, 1.f, h, l);
   const bool finite = __builtin_isfinite(t);
-  h = finite ? h : (half_t)NAN;
-  l = finite ? l : (half_t)0.f;
+  h = finite ? (half_t)t : (half_t)NAN;
+  l = finite ? (half_t)((t - (float)(half_t)t) * kLow) : (half_t)0.f;
   return w == 0.f || !(fabsf(t) < 0x1p-14f) ? 0 : fabsf(t) < 0x1p-60f ? kLostTiny : 1;
 }
 
-// The result below which lost bits are noticed.
+// The result, of operands scaled by 2^e together, below which lost bits are noticed.
 __device__ __forceinline__ float loss_limit(int products, int e, int lost) {
   const int n = min(lost & kLostMost, products);
-  return lost == 0 ? 0.f : ldexpf(n != 0 ? (float)n : (float)products, (n != 0 ? 5 : -20) - e - kMapScale);
+  return lost == 0 ? 0.f : ldexpf(n != 0 ? (float)n : (float)products, (n != 0 ? 5 : -20) - e);
 }
+
+// Scale 2^e of an operand: its largest value in [2^14, 2^15), within what a float can hold.  `most` has the bits of that value and is
+// the same for the whole wavefront, as all that follows from it (integers, for the scalar unit).
+struct PairScale {
+  int e;
+  __device__ __forceinline__ explicit PairScale(int most) { e = most > 0 ? max(-112, min(112, 141 - (most >> 23))) : 0; }
+  __device__ __forceinline__ float scale() const { return __int_as_float((127 + e) << 23); }
+  __device__ __forceinline__ float limit() const { return ldexpf(65504.f, -e); }  // the largest magnitude that it carries
+  // bits without the sign, times two, below which a value loses up to 2^-36 when scaled, and below which no more than itself
+  __device__ __forceinline__ unsigned from() const { return (unsigned)(113 - e) << 24; }
+  __device__ __forceinline__ unsigned tiny() const { return e < 67 ? (unsigned)(67 - e) << 24 : 2u; }
+};
+
+// What a thread saw of an operand: the largest magnitude (NaN is not seen), and the least and the largest of the bits without the sign,
+// times two, less `tiny`: zeros are 2^32 - tiny, smaller ones than tiny lie above, all others below.
+struct PairSeen {
+  float most = 0.f;
+  unsigned least = ~0u, largest = 0;
+  __device__ __forceinline__ void see(const floatx4& v, unsigned tiny) {
+    asm("v_max3_f32 %0, %0, |%1|, |%2|" : "+v"(most) : "v"(v[0]), "v"(v[1]));
+    asm("v_max3_f32 %0, %0, |%1|, |%2|" : "+v"(most) : "v"(v[2]), "v"(v[3]));
+#pragma unroll
+    for (int e = 0; e < 4; e += 2) {
+      const unsigned a = (__float_as_uint(v[e]) << 1) - tiny, b = (__float_as_uint(v[e + 1]) << 1) - tiny;
+      asm("v_min3_u32 %0, %0, %1, %2" : "+v"(least) : "v"(a), "v"(b));
+      asm("v_max3_u32 %0, %0, %1, %2" : "+v"(largest) : "v"(a), "v"(b));
+    }
+  }
+  __device__ __forceinline__ bool over(const PairScale& s) const { return most > s.limit() && most < INFINITY; }
+  __device__ __forceinline__ int lost(const PairScale& s) const {
+    return (least < s.from() - s.tiny() ? kLostMost : 0) | (largest > 0u - s.tiny() ? kLostTiny : 0);
+  }
+};
 
 }  // namespace tfx
 
