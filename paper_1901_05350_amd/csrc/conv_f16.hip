@@ -6,11 +6,14 @@
 // (binary16 operands, fp32 accumulator), so no separate conversions are issued.
 #include "tfx_internal.h"
 
+#include <type_traits>
+
 namespace tfx {
 namespace {
 
 typedef _Float16 half_t;
 typedef _Float16 h8 __attribute__((ext_vector_type(8)));
+typedef _Float16 h8_any __attribute__((ext_vector_type(8), aligned(2)));  // at any element
 
 constexpr int kXcds = 8;
 
@@ -80,15 +83,19 @@ __global__ __launch_bounds__(256) void depthwise_generic_f16_kernel(const half_t
   }
 }
 
-// ---- depthwise 3x3, multiplier 1, C % 8 == 0, stride S in both dims ----------------------------
+// ---- depthwise 3x3, multiplier 1, C >= 8, stride S in both dims ---------------------------------
 // A lane owns 8 consecutive channels of one output column and RS consecutive output rows; all
-// (RS-1)*S+3 input rows x 3 taps are loaded (16 bytes each) before the first multiply.
-template <int S, int RS>
+// (RS-1)*S+3 input rows x 3 taps are loaded (16 bytes each) before the first multiply.  Where C is no
+// multiple of 8 the last lane of a pixel takes the last 8 channels, of which some are the lane's before it too
+// (both store the same values), and the 16 bytes lie at any even address: ANY.  Of its own, since the general addressing
+// costs the rest 3 % (64 x 112 x 112 x 64 37.6 us, 39.0 so; the fp32 kernel, whose loads take longer, nothing).
+template <int S, int RS, bool ANY>
 __global__ __launch_bounds__(256) void depthwise3x3_f16_kernel(const half_t* __restrict__ x,
                                                                const half_t* __restrict__ w,
                                                                const half_t* __restrict__ bias, half_t* __restrict__ y,
-                                                               int H, int W, int C8, int OH, int OW, int pt, int pl,
+                                                               int H, int W, int C8, int channels, int OH, int OW, int pt, int pl,
                                                                int act, int strips, int total) {
+  using Vec = std::conditional_t<ANY, h8_any, h8>;
   constexpr int IR = (RS - 1) * S + 3;
   int bid = blockIdx.x;
   {
@@ -98,15 +105,14 @@ __global__ __launch_bounds__(256) void depthwise3x3_f16_kernel(const half_t* __r
   }
   const int idx = bid * 256 + threadIdx.x;
   if (idx >= total) return;
-  const int c8 = idx % C8;
+  const int C = ANY ? channels : 8 * C8, c0 = ANY ? min(idx % C8 * 8, C - 8) : idx % C8 * 8;
   int r = idx / C8;
   const int ow = r % OW;
   r /= OW;
   const int strip = r % strips;
   const int n = r / strips;
-  const int C = C8 * 8;
 
-  const half_t* xn = x + (size_t)n * H * W * C + 8 * c8;
+  const half_t* xn = x + (size_t)n * H * W * C + c0;
   const int iw0 = ow * S - pl;
   const bool in0 = iw0 >= 0 && iw0 < W, in1 = iw0 + 1 >= 0 && iw0 + 1 < W, in2 = iw0 + 2 >= 0 && iw0 + 2 < W;
   const int oh0 = strip * RS;
@@ -119,16 +125,18 @@ __global__ __launch_bounds__(256) void depthwise3x3_f16_kernel(const half_t* __r
     const int ih = ih0 + i;
     const bool rok = ih >= 0 && ih < H;
     const half_t* p = xn + ((long long)ih * W + iw0) * C;
-    win[i][0] = (rok && in0) ? *reinterpret_cast<const h8*>(p) : z;
-    win[i][1] = (rok && in1) ? *reinterpret_cast<const h8*>(p + C) : z;
-    win[i][2] = (rok && in2) ? *reinterpret_cast<const h8*>(p + 2 * C) : z;
+    win[i][0] = (rok && in0) ? *reinterpret_cast<const Vec*>(p) : z;
+    win[i][1] = (rok && in1) ? *reinterpret_cast<const Vec*>(p + C) : z;
+    win[i][2] = (rok && in2) ? *reinterpret_cast<const Vec*>(p + 2 * C) : z;
   }
   typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+  typedef unsigned u32x4_any __attribute__((ext_vector_type(4), aligned(2)));
+  using Raw = std::conditional_t<ANY, u32x4_any, u32x4>;
   u32x4 wraw[9];
 #pragma unroll
-  for (int t = 0; t < 9; ++t) wraw[t] = *reinterpret_cast<const u32x4*>(w + (size_t)t * C + 8 * c8);
+  for (int t = 0; t < 9; ++t) wraw[t] = *reinterpret_cast<const Raw*>(w + (size_t)t * C + c0);
   h8 bv = z;
-  if (bias) bv = *reinterpret_cast<const h8*>(bias + 8 * c8);
+  if (bias) bv = *reinterpret_cast<const Vec*>(bias + c0);
   const ActClamp clamp = make_act(act);
 
 #pragma unroll
@@ -154,19 +162,22 @@ __global__ __launch_bounds__(256) void depthwise3x3_f16_kernel(const half_t* __r
     h8 out;
 #pragma unroll
     for (int e = 0; e < 8; ++e) out[e] = to_half(apply_act(acc[e], clamp));
-    *reinterpret_cast<h8*>(y + (((size_t)n * OH + oh0 + o) * OW + ow) * C + 8 * c8) = out;
+    *reinterpret_cast<Vec*>(y + (((size_t)n * OH + oh0 + o) * OW + ow) * C + c0) = out;
   }
 }
 
 template <int S, int RS>
-int launch_dw3x3_f16(const half_t* x, const half_t* w, const half_t* bias, half_t* y, int n, int h, int wd, int c8,
+int launch_dw3x3_f16(const half_t* x, const half_t* w, const half_t* bias, half_t* y, int n, int h, int wd, int c,
                      int oh, int ow, int pt, int pl, int act, hipStream_t stream) {
   const int strips = (oh + RS - 1) / RS;
+  const int c8 = (c + 7) / 8;
   const long long total = (long long)n * strips * ow * c8;
   if (total > 0x7fffff00LL) return TFX_ERR_UNSUPPORTED;
   const unsigned blocks = (unsigned)((total + 255) / 256);
-  hipLaunchKernelGGL((depthwise3x3_f16_kernel<S, RS>), dim3(blocks), dim3(256), 0, stream, x, w, bias, y, h, wd, c8, oh,
-                     ow, pt, pl, act, strips, (int)total);
+  const bool any = c % 8 != 0 || (reinterpret_cast<uintptr_t>(x) | reinterpret_cast<uintptr_t>(w) | reinterpret_cast<uintptr_t>(bias) |
+                                  reinterpret_cast<uintptr_t>(y)) % 16 != 0;
+  hipLaunchKernelGGL((any ? depthwise3x3_f16_kernel<S, RS, true> : depthwise3x3_f16_kernel<S, RS, false>), dim3(blocks), dim3(256), 0,
+                     stream, x, w, bias, y, h, wd, c8, c, oh, ow, pt, pl, act, strips, (int)total);
   return check_launch();
 }
 
@@ -639,21 +650,18 @@ int launch_depthwise_f16(const uint16_t* x16, const uint16_t* w16, const uint16_
                          int act, hipStream_t stream) {
   const half_t *x = H(x16), *w = H(w16), *bias = H(bias16);
   half_t* y = H(y16);
-  const bool aligned = reinterpret_cast<uintptr_t>(x) % 16 == 0 && reinterpret_cast<uintptr_t>(w) % 16 == 0 &&
-                       reinterpret_cast<uintptr_t>(y) % 16 == 0 &&
-                       (bias == nullptr || reinterpret_cast<uintptr_t>(bias) % 16 == 0);
-  if (fh == 3 && fw == 3 && mult == 1 && c % 8 == 0 && sh == sw && (sh == 1 || sh == 2) && aligned) {
-    const int c8 = c / 8;
-    const long long px = (long long)n * oh * ow * c8;  // threads at one row per thread
+  // (from 8 channels on; the general kernel, an element a thread, takes C = 558, 14 x 43 x 42 38 us and C = 30, 46 x 46 x 47 30 us)
+  if (fh == 3 && fw == 3 && mult == 1 && c >= 8 && sh == sw && (sh == 1 || sh == 2)) {
+    const long long px = (long long)n * oh * ow * ((c + 7) / 8);  // threads at one row per thread
     const long long want = 256LL * 256 * 4;            // about 4 workgroups per CU
     if (sh == 1) {
-      if (px / 6 >= want) return launch_dw3x3_f16<1, 6>(x, w, bias, y, n, h, wd, c8, oh, ow, pt, pl, act, stream);
-      if (px / 4 >= want) return launch_dw3x3_f16<1, 4>(x, w, bias, y, n, h, wd, c8, oh, ow, pt, pl, act, stream);
-      if (px / 2 >= want / 4) return launch_dw3x3_f16<1, 2>(x, w, bias, y, n, h, wd, c8, oh, ow, pt, pl, act, stream);
-      return launch_dw3x3_f16<1, 1>(x, w, bias, y, n, h, wd, c8, oh, ow, pt, pl, act, stream);
+      if (px / 6 >= want) return launch_dw3x3_f16<1, 6>(x, w, bias, y, n, h, wd, c, oh, ow, pt, pl, act, stream);
+      if (px / 4 >= want) return launch_dw3x3_f16<1, 4>(x, w, bias, y, n, h, wd, c, oh, ow, pt, pl, act, stream);
+      if (px / 2 >= want / 4) return launch_dw3x3_f16<1, 2>(x, w, bias, y, n, h, wd, c, oh, ow, pt, pl, act, stream);
+      return launch_dw3x3_f16<1, 1>(x, w, bias, y, n, h, wd, c, oh, ow, pt, pl, act, stream);
     }
-    if (px / 2 >= want / 4) return launch_dw3x3_f16<2, 2>(x, w, bias, y, n, h, wd, c8, oh, ow, pt, pl, act, stream);
-    return launch_dw3x3_f16<2, 1>(x, w, bias, y, n, h, wd, c8, oh, ow, pt, pl, act, stream);
+    if (px / 2 >= want / 4) return launch_dw3x3_f16<2, 2>(x, w, bias, y, n, h, wd, c, oh, ow, pt, pl, act, stream);
+    return launch_dw3x3_f16<2, 1>(x, w, bias, y, n, h, wd, c, oh, ow, pt, pl, act, stream);
   }
   const long long total = (long long)n * oh * ow * c * mult;
   long long blocks = (total + 255) / 256;
