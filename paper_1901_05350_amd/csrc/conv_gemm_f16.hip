@@ -11,7 +11,7 @@
 // whole iteration earlier) moves from registers to the other LDS buffer and is refilled from slice kt + 2, spread between
 // the MFMAs.  The filter is stored [K, Co] and keeps its k-rows in LDS; its fragments are read with the transposing LDS load (as turned
 // in registers, 4 k-rows x 8 columns a thread, its 8-byte LDS writes were waited for: 4 % less over 63 aligned convolutions with the
-// tiles as they were).  Tiles of 64 x 128 and 128 x 128 have 8 wavefronts, 64 x 64 ones 4: 10 % less over 334 convolutions (3x3,
+// tiles as they were).  Tiles of 64 x 128 and 128 x 128 have 8 wavefronts, 64 x 64 and 128 x 32 ones 4: 10 % less over 334 convolutions (3x3,
 // 18x19x19x240 -> 152 29.1 -> 20.1 us; 47x17x42x166 -> 32 34.3 -> 24.9).
 //
 // What bounds it is the latency of a slice where workgroups are few, and the vector-ALU instructions of the addresses
@@ -368,11 +368,20 @@ int launch_conv2d_gemm_f16(const uint16_t* x, const uint16_t* w, const uint16_t*
   // for three (3x3, 36x13x13x160 -> 52: 17.4 us, 12.7 with 64 x 64 split).
   // (5x5, 13x20x20x398 -> 192: 137 us with LDS tiles, 92 split; 3x3, 2x56x56x32 -> 64: 10.8 and 6.4.)
   const int kp = fh * fw * cp, k64 = g.slices * kBK;
-  enum { kDeep, kDirect64x64, kDirect32x64, k64x64, k64x128, k128x128, kForms };
+  enum { kDeep, kDirect64x64, kDirect32x64, k128x32, k64x64, k64x128, k128x128, kForms };
   const int deep_n = deep_two_columns((g.M + 15) / 16, co, (kp + 31) / 32) ? 32 : 16, odd = aligned ? 0 : 1;
+  // Up to 32 columns: tiles of 128 x 32 multiply half as much padding and read a row of A for them once, 20 KB a slice for 128 rows
+  // where tiles of 64 x 64 read 32.  Not where more than two of them a CU read windows of 256 channels and more, which leave L2
+  // between two taps: 3x3, 30x56x56x256 -> 16 54.5 us, 51.1 without them; 23x78x78x328 -> 16 112 and 107, -> 27 124 and 139.
+  // Nor with less than one and a half a CU: a lone workgroup of 4 wavefronts waits for its loads (15x38x38x18 -> 15 8.6 us, 5.9
+  // without, 16x48x48x11 -> 20 9.5 and 8.0).
+  // us before and with them: 28x103x103x54 -> 16 55 -> 38, 40x51x51x140 -> 16 49 -> 29, 10x87x87x96 -> 22 (5x5) 66 -> 45; of 450
+  // drawn with up to 64 columns a seventh are more than 8 % faster, none more than 5 % slower (6 %: the margin at which that holds).
+  const bool narrow = co <= 32 && g.M > 384 * 128 && (ci < 256 || g.M <= 512 * 128);
   const double us[kForms] = {1.05 * PipeCost{16, deep_n, 3.42, .019, .0021, .89, 1.31, .05, 1.45}.us(1, g.M, co, kp, odd),
                              co >= 2 ? PipeCost{64, 64, .79, 3.94, .0064, .65, .87, .30, .86}.us(1, g.M, co, kp, odd) : 1e30,
                              co >= 2 ? PipeCost{32, 64, 1.51, 2.78, .0074, .24, .37, .31, .015, .0014}.us(1, g.M, co, kp, odd) : 1e30,
+                             narrow ? 1.06 * PipeCost{128, 32, 2.47, 2.34, .0061, .2, .55, .7, 0.}.us(1, g.M, co, k64, odd) : 1e30,
                              PipeCost{64, 64, 4.04, .74, .0054, .34, .50, .77, .69}.us(1, g.M, co, k64, odd),
                              PipeCost{64, 128, 3.19, 1.55, .0065, .57, .69, .72, .67}.us(1, g.M, co, k64, odd),
                              PipeCost{128, 128, 4.52, 1.11, .0082, .72, .99, .50, .52, .0001}.us(1, g.M, co, k64, odd)};
@@ -384,6 +393,7 @@ int launch_conv2d_gemm_f16(const uint16_t* x, const uint16_t* w, const uint16_t*
     return launch_conv2d_gemm_direct_f16(x, w, bias, y, n, h, wd, ci, fh, fw, co, oh, ow, sh, sw, pt, pl, act, stream, form == kDirect32x64);
   auto tiles = [&](auto loader) {
     constexpr Form FORM = decltype(loader)::value;
+    if (form == k128x32) return launch<4, 1, 1, 1, FORM>(g, stream);
     if (form == k64x64) return launch<2, 2, 1, 1, FORM>(g, stream);
     if (form == k64x128) return launch<2, 4, 1, 1, FORM>(g, stream);
     return launch<2, 4, 2, 1, FORM>(g, stream);
