@@ -18,7 +18,9 @@ SOURCES = ["api.hip", "gemm.hip", "pointwise.hip", "conv.hip", "depthwise.hip", 
 HEADERS = [os.path.join(CSRC, "tfx_internal.h"), os.path.join(CSRC, "stream_f16.h"), os.path.join(CSRC, "ragged.h"), os.path.join(CSRC, "split.h"), os.path.join(CSRC, "pair.h"), os.path.join(CSRC, "gemm_slots.h"), os.path.join(CSRC, "kernel_cost.h"), os.path.join(HERE, "..", "include", "tfx.h")]
 FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-Wall", "-Wno-unused-function",
          # packed fp32 VALU ops are kept off on this target
-         "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
+         "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+         # the first 14 dwords of a kernel's plain arguments come in scalar registers instead of through memory, .3 - .5 us of a launch
+         "-mllvm", "-amdgpu-kernarg-preload-count=16"]
 
 
 def _hipcc():

@@ -8,28 +8,38 @@
 // as the separate kernel rounds it, and multiplies it by its rows of the pointwise filter, which are loaded straight into
 // registers before anything is waited for.  The wavefronts' partial tiles are added through LDS behind the only barrier.
 //
-// What bounds it is the latency of one launch: arguments, one round trip to memory, some 150 multiply-adds per lane and k-step
+// What bounds it is the latency of one launch: one round trip to memory, some 150 multiply-adds per lane and k-step
 // pair, one exchange through LDS, the stores.  One image, 14 x 14 x 512 -> 512: 5.5 us, where the depthwise and the pointwise
 // kernel took 3.6 + 4.6 and the gap between them; all 13 blocks of the network 69 us where the 26 kernels took 105 under the
-// profiler.
+// profiler.  The round trip for the arguments before that one is left out (PatchRest): the pass of one image 77 -> 70 us, of quarter
+// width at 128 x 128 57 -> 50, of 17 images of quarter width 91 -> 85.
 #include "ragged.h"
 #include "stream_f16.h"
+
+#include <algorithm>
 
 namespace tfx {
 namespace {
 
 using namespace f16s;
 
-constexpr int kXcds = 8;
-
 struct PatchBlockArgs {
   const half_t *x, *dw_w, *dw_b, *pw_w, *pw_b;
   half_t* y;
   int H, W, C, N, OH, OW, pt, pl;
-  int patches, slices, total, wk, wp;  // wavefronts along the channels, patches of a workgroup
-  FastDiv row_patches, col_patches, by_slices;
+  int patches, wk, wp;
+  FastDiv row_patches, col_patches;
   unsigned x_bytes;
   int dw_act, pw_act;
+};
+// What the addresses of a workgroup's loads depend on comes in the 14 dwords of arguments that a wavefront finds in its scalar
+// registers when it starts, packed for that: dimensions in halves, `form` with wk (5 bits), wp (3), pt, pl, the shifts of the two
+// divisions (5 each) and 256 / wk rounded up.  The rest, for what it does with the loads, is read while they are under way.  (The
+// column slices come first in the grid, then the patches, as y + 2^15 z: no division is left for them.)
+struct PatchRest {
+  const half_t *dw_b, *pw_b;
+  half_t* y;
+  int OH, OW, dw_act, pw_act;
 };
 
 // The window in LDS: strides of a pixel and of a row of pixels in 16-byte pieces, such that the fragment read of a tap is
@@ -66,7 +76,9 @@ constexpr size_t patch_region_bytes() {
 }
 
 template <int S, int STEPS, int JN>
-__global__ __launch_bounds__(JN == 8 ? 512 : 1024) void separable_patch_f16_kernel(PatchBlockArgs g) {
+__global__ __launch_bounds__(JN == 8 ? 512 : 1024) void separable_patch_f16_kernel(
+    const half_t* x, const half_t* dw_w, const half_t* pw_w, unsigned x_bytes, unsigned map, unsigned channels, unsigned patches, unsigned by_row,
+    unsigned by_col, unsigned per, unsigned form, PatchRest g) {
   typedef PatchWindow<S, STEPS> P;
   typedef typename HalfsOf<JN>::type hj;
   constexpr int LOADS = (P::SIDE * P::SIDE * P::PIECES + 63) / 64, FLOADS = (9 * P::PIECES + 63) / 64;
@@ -74,26 +86,21 @@ __global__ __launch_bounds__(JN == 8 ? 512 : 1024) void separable_patch_f16_kern
 
   const int lane = threadIdx.x % 64, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / 64);
   const int li = lane % 16, q = lane / 16;
-  const int p = wave / g.wk, part = wave - p * g.wk;
-  int bid = blockIdx.x;
-  {  // the column slices of a patch, and neighbouring patches, on one XCD
-    const int each = g.total / kXcds, rem = g.total % kXcds, xcd = bid % kXcds;
-    bid = xcd * each + (xcd < rem ? xcd : rem) + bid / kXcds;
-  }
-  const int group = (int)div_by((unsigned)bid, g.by_slices), n0 = (bid - group * g.slices) * 16 * JN;
-  const int patch = group * g.wp + p;
-  const bool live = patch < g.patches;
-  const int strip = (int)div_by((unsigned)patch, g.row_patches), image = (int)div_by((unsigned)strip, g.col_patches);
-  const int ow0 = 4 * (patch - strip * (int)g.row_patches.d), oh0 = 4 * (strip - image * (int)g.col_patches.d);
-  const int C = g.C, N = g.N, c0 = 32 * STEPS * part;
+  const int wk = (int)(form & 31), wp = (int)(form >> 5 & 7), pt = (int)(form >> 8 & 1), pl = (int)(form >> 9 & 1);
+  const int H = (int)(map & 0xffff), W = (int)(map >> 16), C = (int)(channels & 0xffff), N = (int)(channels >> 16);
+  const FastDiv row_patches{by_row, form >> 10 & 31, per & 0xffff}, col_patches{by_col, form >> 15 & 31, per >> 16};
+  const int p = wave * (int)(form >> 20) >> 8, part = wave - p * wk;  // (wave / wk)
+  const int n0 = (int)blockIdx.x * 16 * JN, patch = (int)(blockIdx.z << 15 | blockIdx.y) * wp + p;
+  const bool live = patch < (int)patches;
+  const int strip = (int)div_by((unsigned)patch, row_patches), image = (int)div_by((unsigned)strip, col_patches);
+  const int ow0 = 4 * (patch - strip * (int)row_patches.d), oh0 = 4 * (strip - image * (int)col_patches.d), c0 = 32 * STEPS * part;
 
   half_t* const window = reinterpret_cast<half_t*>(lds + wave * patch_region_bytes<S, STEPS, JN>());
   half_t* const taps = window + P::HALFS;
 
-  const __amdgpu_buffer_rsrc_t xr = __builtin_amdgcn_make_buffer_rsrc(const_cast<half_t*>(g.x), 0, (int)g.x_bytes, 0x00020000);
-  const __amdgpu_buffer_rsrc_t fr = __builtin_amdgcn_make_buffer_rsrc(const_cast<half_t*>(g.dw_w), 0, 18 * C, 0x00020000);
-  const __amdgpu_buffer_rsrc_t br = __builtin_amdgcn_make_buffer_rsrc(const_cast<half_t*>(g.dw_b), 0, 2 * C, 0x00020000);
-  const __amdgpu_buffer_rsrc_t wr = __builtin_amdgcn_make_buffer_rsrc(const_cast<half_t*>(g.pw_w), 0, 2 * C * N, 0x00020000);
+  const __amdgpu_buffer_rsrc_t xr = __builtin_amdgcn_make_buffer_rsrc(const_cast<half_t*>(x), 0, (int)x_bytes, 0x00020000);
+  const __amdgpu_buffer_rsrc_t fr = __builtin_amdgcn_make_buffer_rsrc(const_cast<half_t*>(dw_w), 0, 18 * C, 0x00020000);
+  const __amdgpu_buffer_rsrc_t wr = __builtin_amdgcn_make_buffer_rsrc(const_cast<half_t*>(pw_w), 0, 2 * C * N, 0x00020000);
 
   // Every load of the workgroup, before the first wait.  What lies outside the map, or past the last channel, has an offset
   // past the end and reads zeros.
@@ -102,9 +109,9 @@ __global__ __launch_bounds__(JN == 8 ? 512 : 1024) void separable_patch_f16_kern
 #pragma unroll
   for (int i = 0; i < LOADS; ++i) {
     const int px = (64 * i + lane) / P::PIECES, r = px / P::SIDE, c = px - r * P::SIDE;
-    const int ih = oh0 * S - g.pt + r, iw = ow0 * S - g.pl + c;
-    const bool ok = (unsigned)ih < (unsigned)g.H && (unsigned)iw < (unsigned)g.W && px < P::SIDE * P::SIDE && ch < C && live;
-    const unsigned off = ok ? 2u * (((unsigned)(image * g.H + ih) * g.W + iw) * C + ch) : ~0u;
+    const int ih = oh0 * S - pt + r, iw = ow0 * S - pl + c;
+    const bool ok = (unsigned)ih < (unsigned)H && (unsigned)iw < (unsigned)W && px < P::SIDE * P::SIDE && ch < C && live;
+    const unsigned off = ok ? 2u * (((unsigned)(image * H + ih) * W + iw) * C + ch) : ~0u;
     win[i] = __builtin_amdgcn_raw_buffer_load_b128(xr, off, 0, 0);
   }
 #pragma unroll
@@ -112,9 +119,6 @@ __global__ __launch_bounds__(JN == 8 ? 512 : 1024) void separable_patch_f16_kern
     const int t = (64 * i + lane) / P::PIECES;
     fil[i] = __builtin_amdgcn_raw_buffer_load_b128(fr, ch < C && t < 9 ? 2u * (unsigned)(t * C + ch) : ~0u, 0, 0);
   }
-  u32x4 dwb[STEPS];
-#pragma unroll
-  for (int s = 0; s < STEPS; ++s) dwb[s] = __builtin_amdgcn_raw_buffer_load_b128(br, 2u * (unsigned)(c0 + 32 * s + 8 * q), 0, 0);
   const int col = n0 + JN * li < N ? n0 + JN * li : 0;  // past the last column: read, never stored
   hj raw[STEPS][8];
 #pragma unroll
@@ -126,6 +130,10 @@ __global__ __launch_bounds__(JN == 8 ? 512 : 1024) void separable_patch_f16_kern
       if constexpr (JN == 4) raw[s][i] = __builtin_bit_cast(hj, __builtin_amdgcn_raw_buffer_load_b64(wr, off, 0, 0));
       if constexpr (JN == 8) raw[s][i] = __builtin_bit_cast(hj, __builtin_amdgcn_raw_buffer_load_b128(wr, off, 0, 0));
     }
+  const __amdgpu_buffer_rsrc_t br = __builtin_amdgcn_make_buffer_rsrc(const_cast<half_t*>(g.dw_b), 0, 2 * C, 0x00020000);
+  u32x4 dwb[STEPS];
+#pragma unroll
+  for (int s = 0; s < STEPS; ++s) dwb[s] = __builtin_amdgcn_raw_buffer_load_b128(br, 2u * (unsigned)(c0 + 32 * s + 8 * q), 0, 0);
   const hj pwb = *reinterpret_cast<const hj*>(g.pw_b + col);
 
 #pragma unroll
@@ -180,7 +188,7 @@ __global__ __launch_bounds__(JN == 8 ? 512 : 1024) void separable_patch_f16_kern
     if (live && oh < g.OH && ow < g.OW && cn < N)
       *reinterpret_cast<h2*>(g.y + ((size_t)(image * g.OH + oh) * g.OW + ow) * N + cn) = o;
   };
-  if (g.wk == 1) {
+  if (wk == 1) {
 #pragma unroll
     for (int v = 0; v < 4; ++v)
 #pragma unroll
@@ -196,10 +204,10 @@ __global__ __launch_bounds__(JN == 8 ? 512 : 1024) void separable_patch_f16_kern
 #pragma unroll
     for (int j = 0; j < JN; ++j) sums[(v * 64 + lane) * JN + j] = acc[j][v];
   __syncthreads();
-  for (int u = 64 * part + lane; u < 128 * JN; u += 64 * g.wk) {
+  for (int u = 64 * part + lane; u < 128 * JN; u += 64 * wk) {
     float s0 = 0.f, s1 = 0.f;
-    for (int w = 0; w < g.wk; ++w) {
-      const float2 t = reinterpret_cast<const float2*>(lds + (p * g.wk + w) * REGION)[u];
+    for (int w = 0; w < wk; ++w) {
+      const float2 t = reinterpret_cast<const float2*>(lds + (p * wk + w) * REGION)[u];
       s0 += t.x, s1 += t.y;
     }
     const int v = u / (32 * JN), rest = u % (32 * JN);
@@ -218,11 +226,13 @@ int launch_patch(const PatchBlockArgs& args, const PatchForm& f, hipStream_t str
   static std::atomic<uint64_t> lds_allowed{0};
   if (allow_dynamic_lds(reinterpret_cast<const void*>(kern), 160 * 1024, lds_allowed) != TFX_OK) return TFX_ERR_LAUNCH;
   g.wk = f.wk, g.wp = f.wp;
-  g.slices = (g.N + 16 * JN - 1) / (16 * JN);
-  g.by_slices = fast_div((unsigned)g.slices);
-  g.total = (g.patches + f.wp - 1) / f.wp * g.slices;
+  const unsigned slices = (unsigned)((g.N + 16 * JN - 1) / (16 * JN)), groups = (unsigned)((g.patches + f.wp - 1) / f.wp);
   const size_t lds_bytes = patch_region_bytes<S, STEPS, JN>() * f.wk * f.wp;
-  hipLaunchKernelGGL(kern, dim3((unsigned)g.total), dim3(64u * f.wk * f.wp), lds_bytes, stream, g);
+  const unsigned form = (unsigned)(f.wk | f.wp << 5 | g.pt << 8 | g.pl << 9) | g.row_patches.shift << 10 | g.col_patches.shift << 15 |
+                        (256u + f.wk - 1) / f.wk << 20;
+  hipLaunchKernelGGL(kern, dim3(slices, std::min(groups, 1u << 15), (groups + (1u << 15) - 1) >> 15), dim3(64u * f.wk * f.wp), lds_bytes, stream, g.x, g.dw_w, g.pw_w, g.x_bytes,
+                     (unsigned)(g.H | g.W << 16), (unsigned)(g.C | g.N << 16), (unsigned)g.patches, g.row_patches.mul, g.col_patches.mul,
+                     g.row_patches.d | g.col_patches.d << 16, form, PatchRest{g.dw_b, g.pw_b, g.y, g.OH, g.OW, g.dw_act, g.pw_act});
   return check_launch();
 }
 
@@ -249,7 +259,7 @@ bool separable_patch_f16_supported(int batch, int h, int w, int c, int n, int st
   for (const void* p : ptrs) aligned = aligned && reinterpret_cast<uintptr_t>(p) % 16 == 0;
   const long long patches = (long long)batch * ((oh + 3) / 4) * ((ow + 3) / 4), x_bytes = (long long)batch * h * w * c * 2;
   return aligned && (stride == 1 || stride == 2) && c % 8 == 0 && c <= (stride == 1 ? 1024 : 512) && n % 8 == 0 && n <= 1024 && x_bytes < (1ll << 31) &&
-         patches < (1ll << 24);  // (stride 2: a wavefront's window is 13 KB, and 8 of them fit)
+         patches < (1ll << 24) && h < 65536 && w < 65536;  // (stride 2: a wavefront's window is 13 KB, and 8 of them fit)
 }
 
 int launch_separable_patch_f16(const uint16_t* x, const uint16_t* dw_w, const uint16_t* dw_b, const uint16_t* pw_w,
@@ -258,7 +268,7 @@ int launch_separable_patch_f16(const uint16_t* x, const uint16_t* dw_w, const ui
   auto p = [](const uint16_t* q) { return reinterpret_cast<const half_t*>(q); };
   const int row_patches = (ow + 3) / 4, col_patches = (oh + 3) / 4, patches = batch * col_patches * row_patches;
   const PatchBlockArgs g{p(x), p(dw_w), p(dw_b), p(pw_w), p(pw_b), reinterpret_cast<half_t*>(y), h, w, c, n, oh, ow, pt, pl,
-                         patches, 0, 0, 0, 0, fast_div((unsigned)row_patches), fast_div((unsigned)col_patches), FastDiv{},
+                         patches, 0, 0, fast_div((unsigned)row_patches), fast_div((unsigned)col_patches),
                          (unsigned)((long long)batch * h * w * c * 2), dw_act, pw_act};
   const PatchForm f = patch_form(patches, c, n);
 #define TFX_PATCH(S, STEPS, JN) \
