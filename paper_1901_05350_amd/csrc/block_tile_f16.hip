@@ -39,14 +39,24 @@ struct TileBlockArgs {
   const half_t *x, *dw_w, *dw_b, *pw_w, *pw_b;
   half_t* y;
   int H, W, C, N, OH, OW, pt, pl;
-  int row_patches, col_patches, patches, tiles_n, total;
+  int row_patches, col_patches, patches;
   unsigned x_bytes, y_bytes;
+  int dw_act, pw_act;
+};
+// What the depthwise layer needs comes in the 14 dwords of arguments that a wavefront finds in its scalar registers when it starts,
+// dimensions in halves; the rest is read from memory while that is under way (the pass of 64 images 283.3 -> 282.4 us).
+struct TileRest {
+  const half_t *pw_w, *pw_b;
+  half_t* y;
+  unsigned y_bytes;
   int dw_act, pw_act;
 };
 
 // S: stride; TM: 32-pixel blocks of a tile; WK: parts of the contraction (wavefront = column group + WN x part)
 template <int S, int TM, int WK>
-__global__ __launch_bounds__(512) void separable_tile_f16_kernel(TileBlockArgs g) {
+__global__ __launch_bounds__(512) void separable_tile_f16_kernel(const half_t* x, const half_t* dw_w, const half_t* dw_b, unsigned x_bytes, unsigned map,
+                                                               unsigned out_map, unsigned channels, unsigned per, int patches, int total,
+                                                               unsigned form, TileRest g) {
   constexpr int PATCHES = 4 * TM;
   struct Patch {
     int out, cols, rows, ih, iw, image;  // first output pixel, extent inside the map; first tap's row and column, image's first row
@@ -56,25 +66,28 @@ __global__ __launch_bounds__(512) void separable_tile_f16_kernel(TileBlockArgs g
 
   const int tid = threadIdx.x, lane = tid % 64, wave = __builtin_amdgcn_readfirstlane(tid / 64);
   const int li = lane % 32, h = lane / 32;
-  const int waves_n = (int)blockDim.x / 64 / WK, wn = wave % waves_n, part = wave / waves_n;
+  const int H = (int)(map & 0xffff), W = (int)(map >> 16), OH = (int)(out_map & 0xffff), OW = (int)(out_map >> 16);
+  const int C = (int)(channels & 0xffff), N = (int)(channels >> 16), row_patches = (int)(per & 0xffff), col_patches = (int)(per >> 16);
+  const int pt = (int)(form & 1), pl = (int)(form >> 1 & 1), tiles_n = (int)(form >> 2 & 31);
+  const int waves_n = (int)(form >> 7), threads = 64 * waves_n * WK, wn = wave % waves_n, part = wave / waves_n;
   int bid = blockIdx.x;
   {  // tiles of the same pixels, and neighbouring ones, on one XCD
-    const int q = g.total / kXcds, rem = g.total % kXcds, xcd = bid % kXcds;
+    const int q = total / kXcds, rem = total % kXcds, xcd = bid % kXcds;
     bid = xcd * q + (xcd < rem ? xcd : rem) + bid / kXcds;
   }
-  const int tile_n = bid % g.tiles_n, tile_m = bid / g.tiles_n;
-  const int C = g.C, N = g.N, C8 = C / 8, LD = C + 8;
+  const int tile_n = bid % tiles_n, tile_m = bid / tiles_n;
+  const int C8 = C / 8, LD = C + 8;
 
   if (tid < PATCHES) {
-    const int i = tile_m * PATCHES + tid, row = i / g.row_patches, n = row / g.col_patches;
-    const int ow = 4 * (i % g.row_patches), oh = 2 * (row % g.col_patches);
+    const int i = tile_m * PATCHES + tid, row = i / row_patches, n = row / col_patches;
+    const int ow = 4 * (i % row_patches), oh = 2 * (row % col_patches);
     Patch p;
-    p.out = (n * g.OH + oh) * g.OW + ow;
-    p.cols = i < g.patches ? (g.OW - ow < 4 ? g.OW - ow : 4) : 0;
-    p.rows = g.OH - oh < 2 ? 1 : 2;
-    p.ih = oh * S - g.pt;
-    p.iw = ow * S - g.pl;
-    p.image = n * g.H;
+    p.out = (n * OH + oh) * OW + ow;
+    p.cols = i < patches ? (OW - ow < 4 ? OW - ow : 4) : 0;
+    p.rows = OH - oh < 2 ? 1 : 2;
+    p.ih = oh * S - pt;
+    p.iw = ow * S - pl;
+    p.image = n * H;
     patch[tid] = p;
   }
   __syncthreads();
@@ -82,34 +95,34 @@ __global__ __launch_bounds__(512) void separable_tile_f16_kernel(TileBlockArgs g
   // The filter is in no L2 yet, and all workgroups of an XCD walk through it in the same order: each fetches its share of the lines
   // while the depthwise layer is computed, a dword of each, instead of all waiting for every k-step in turn.
   // (Those after the first 64 of an XCD find it there.)
-  const int of_xcd = max(1, min(g.total / kXcds, 64)), lines = C * N / 64, l0 = lines * min((int)blockIdx.x / kXcds, of_xcd - 1) / of_xcd;
+  const int of_xcd = max(1, min(total / kXcds, 64)), lines = C * N / 64, l0 = lines * min((int)blockIdx.x / kXcds, of_xcd - 1) / of_xcd;
   const int line = min(l0 + min(tid, (lines - 1) / of_xcd), lines - 1);
   auto touch = [&]() __attribute__((always_inline)) { return reinterpret_cast<const unsigned*>(g.pw_w)[32 * line]; };
   unsigned touched = 0;
-  const __amdgpu_buffer_rsrc_t xr = __builtin_amdgcn_make_buffer_rsrc(const_cast<half_t*>(g.x), 0, (int)g.x_bytes, 0x00020000);
+  const __amdgpu_buffer_rsrc_t xr = __builtin_amdgcn_make_buffer_rsrc(const_cast<half_t*>(x), 0, (int)x_bytes, 0x00020000);
   const ActClamp dw_clamp = make_act(g.dw_act);
   if (tid >= PATCHES * C8) touched = touch();
-  for (int item = tid; item < PATCHES * C8; item += (int)blockDim.x) {
+  for (int item = tid; item < PATCHES * C8; item += threads) {
     const int s = item / C8, c8 = item - s * C8;
     constexpr int PX = S == 1 ? 4 : 2, ROWS = S + 3, COLS = (PX - 1) * S + 3;  // columns at a time, and what they read
     u32x4 wraw[9];
 #pragma unroll
-    for (int t = 0; t < 9; ++t) wraw[t] = *reinterpret_cast<const u32x4*>(g.dw_w + (size_t)t * C + 8 * c8);
-    const h8 bv = *reinterpret_cast<const h8*>(g.dw_b + 8 * c8);
+    for (int t = 0; t < 9; ++t) wraw[t] = *reinterpret_cast<const u32x4*>(dw_w + (size_t)t * C + 8 * c8);
+    const h8 bv = *reinterpret_cast<const h8*>(dw_b + 8 * c8);
     // byte offsets of a row and a column of x; outside the map (and for a patch outside the batch) the largest, which the
     // saturating sum keeps: such a load is past the end and reads zeros
-    const Patch pt = patch[s];
+    const Patch at = patch[s];
     unsigned row_off[ROWS];
 #pragma unroll
     for (int i = 0; i < ROWS; ++i)
-      row_off[i] = (unsigned)(pt.ih + i) < (unsigned)g.H && pt.cols > 0 ? 2u * ((unsigned)(pt.image + pt.ih + i) * g.W * C + 8 * c8) : ~0u;
+      row_off[i] = (unsigned)(at.ih + i) < (unsigned)H && at.cols > 0 ? 2u * ((unsigned)(at.image + at.ih + i) * W * C + 8 * c8) : ~0u;
 #pragma unroll
     for (int p0 = 0; p0 < 4; p0 += PX) {
       u32x4 win[ROWS][COLS];
 #pragma unroll
       for (int j = 0; j < COLS; ++j) {
-        const int iw = pt.iw + p0 * S + j;
-        const unsigned col_off = (unsigned)iw < (unsigned)g.W ? 2u * (unsigned)(iw * C) : ~0u;
+        const int iw = at.iw + p0 * S + j;
+        const unsigned col_off = (unsigned)iw < (unsigned)W ? 2u * (unsigned)(iw * C) : ~0u;
 #pragma unroll
         for (int i = 0; i < ROWS; ++i)
           win[i][j] = __builtin_amdgcn_raw_buffer_load_b128(xr, __builtin_elementwise_add_sat(row_off[i], col_off), 0, 0);
@@ -194,10 +207,10 @@ __global__ __launch_bounds__(512) void separable_tile_f16_kernel(TileBlockArgs g
   const __amdgpu_buffer_rsrc_t yr = __builtin_amdgcn_make_buffer_rsrc(g.y, 0, (int)g.y_bytes, 0x00020000);
 #pragma unroll
   for (int t = 0; t < TM; ++t) {
-    const Patch pt = patch[4 * t + li / 8];
+    const Patch at = patch[4 * t + li / 8];
     const int row = li % 8 / 4, col = li % 4;
     // past the end, where nothing is stored, for a lane without a pixel
-    out[t] = row < pt.rows && col < pt.cols ? 2u * ((unsigned)(pt.out + row * g.OW + col) * N + n0 + 8 * h) : 0x80000000u;
+    out[t] = row < at.rows && col < at.cols ? 2u * ((unsigned)(at.out + row * OW + col) * N + n0 + 8 * h) : 0x80000000u;
   }
   auto emit = [&](int q, h8 bv, const float (&v0)[4], const float (&v1)[4]) __attribute__((always_inline)) {
     f32x4 v[2];
@@ -273,16 +286,17 @@ __global__ __launch_bounds__(256) void pack_filters_kernel(PackArgs g) {
 
 template <int S, int TM, int WK>
 int launch_tile(const TileBlockArgs& args, int waves_n, hipStream_t stream) {
-  TileBlockArgs g = args;
+  const TileBlockArgs& g = args;
   auto kern = separable_tile_f16_kernel<S, TM, WK>;
   const size_t depth = (size_t)32 * TM * (g.C + 8) * sizeof(half_t), sums = WK == 1 ? 0 : (size_t)waves_n * WK * TM * 32 * 64 * sizeof(float);
   const size_t lds_bytes = depth > sums ? depth : sums;
   static std::atomic<uint64_t> lds_allowed{0};
   if (allow_dynamic_lds(reinterpret_cast<const void*>(kern), 160 * 1024 - 1024, lds_allowed) != TFX_OK) return TFX_ERR_LAUNCH;
-  g.tiles_n = g.N / (64 * waves_n);
-  const int tiles_m = (g.patches + 4 * TM - 1) / (4 * TM);
-  g.total = tiles_m * g.tiles_n;
-  hipLaunchKernelGGL(kern, dim3((unsigned)g.total), dim3(64u * waves_n * WK), lds_bytes, stream, g);
+  const int tiles_n = g.N / (64 * waves_n), total = (g.patches + 4 * TM - 1) / (4 * TM) * tiles_n;
+  auto halves = [](int low, int high) { return (unsigned)low | (unsigned)high << 16; };
+  hipLaunchKernelGGL(kern, dim3((unsigned)total), dim3(64u * waves_n * WK), lds_bytes, stream, g.x, g.dw_w, g.dw_b, g.x_bytes,
+                     halves(g.H, g.W), halves(g.OH, g.OW), halves(g.C, g.N), halves(g.row_patches, g.col_patches), g.patches, total,
+                     (unsigned)(g.pt | g.pl << 1 | tiles_n << 2 | waves_n << 7), TileRest{g.pw_w, g.pw_b, g.y, g.y_bytes, g.dw_act, g.pw_act});
   return check_launch();
 }
 
@@ -328,7 +342,7 @@ bool separable_tile_f16_supported(int batch, int h, int w, int c, int n, int str
   // depthwise layer again, so few pixels of a deep layer are not worth it (8 x 7 x 7 x 1024 10.7 us, 4 x 10.4; 7 apart)
   const long long least = c <= 256 ? 1024 : c <= 512 ? 700 : 850;
   return aligned && (stride == 1 || stride == 2) && c % 64 == 0 && c <= 1024 && n % 64 == 0 && n <= 1024 &&
-         x_bytes < (1ll << 31) && y_bytes < (1ll << 31) && patches < (1ll << 27) && 8 * patches >= least;
+         x_bytes < (1ll << 31) && y_bytes < (1ll << 31) && patches < (1ll << 27) && h < 65536 && w < 65536 && 8 * patches >= least;
 }
 
 int launch_separable_tile_f16(const uint16_t* x, const uint16_t* dw_w, const uint16_t* dw_b, const uint16_t* packed,
@@ -337,7 +351,7 @@ int launch_separable_tile_f16(const uint16_t* x, const uint16_t* dw_w, const uin
   auto p = [](const uint16_t* q) { return reinterpret_cast<const half_t*>(q); };
   const int row_patches = (ow + 3) / 4, col_patches = (oh + 1) / 2, patches = batch * col_patches * row_patches;
   const TileBlockArgs g{p(x), p(dw_w), p(dw_b), p(packed), p(pw_b), reinterpret_cast<half_t*>(y), h, w, c, n, oh, ow, pt, pl,
-                        row_patches, col_patches, patches, 0, 0, (unsigned)((long long)batch * h * w * c * 2),
+                        row_patches, col_patches, patches, (unsigned)((long long)batch * h * w * c * 2),
                         (unsigned)((long long)batch * oh * ow * n * 2), dw_act, pw_act};
   const TileForm f = tile_form(patches, c, n, stride);
 #define TFX_TILE(S, TM, WK) \
