@@ -28,16 +28,25 @@ namespace {
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int kXcds = 8, kChannels32 = 32, kPieces = kChannels32 / 4;
+constexpr int kChannels32 = 32, kPieces = kChannels32 / 4;
 
 struct PatchArgs {
   const float *x, *dw_w, *dw_b, *pw_w, *pw_b;
   float* y;
   int H, W, C, N, OH, OW, pt, pl;
-  int patches, slices, total, wk, wp;  // wavefronts along the channels, patches of a workgroup
-  FastDiv row_patches, col_patches, by_slices;
+  int patches;
+  FastDiv row_patches, col_patches;
   unsigned x_bytes;
   int dw_act, pw_act;
+};
+// The arguments as block_patch_f16.hip has them: what the addresses depend on in scalar registers from the start, the rest read while
+// the loads are under way.  Patches come first in the grid, padded to a multiple of 8, so that the column slices of a patch are on
+// one XCD and its window in one L2 (column slices first where the filter is larger than the map, as there: 2 images 114.4 us, 110.8 so).
+// us, before and now: 2 images 114.4 -> 110.8, 4 at quarter width and 192 x 192 75 -> 70.5, 16 at half width 161.6 -> 154.5.
+struct PatchRest {
+  const float *pw_w, *pw_b;
+  float* y;
+  int OH, OW, dw_act, pw_act;
 };
 
 // The window in LDS: strides of a pixel and of a row of pixels in 16-byte pieces, such that the fragment read of a tap is
@@ -75,7 +84,9 @@ constexpr size_t patch_region_bytes() {
 constexpr int most_waves(int s, int jn, int rounds) { return s == 2 || jn == 8 || (jn == 4 && rounds > 1) ? 8 : 16; }
 
 template <int S, int JN, int ROUNDS>
-__global__ __launch_bounds__(64 * most_waves(S, JN, ROUNDS)) void separable_patch_kernel(PatchArgs g) {
+__global__ __launch_bounds__(64 * most_waves(S, JN, ROUNDS)) void separable_patch_kernel(
+    const float* x, const float* dw_w, const float* dw_b, unsigned x_bytes, unsigned map, unsigned channels, unsigned patches, unsigned by_row,
+    unsigned by_col, unsigned per, unsigned form, PatchRest g) {
   typedef PatchWindow<S> P;
   constexpr int LOADS = (P::SIDE * P::SIDE * kPieces + 63) / 64, FLOADS = (10 * kPieces + 63) / 64, G = kChannels32 / 16;
   constexpr int V = JN < 4 ? 1 : JN / 4;  // loads of a filter row
@@ -83,27 +94,24 @@ __global__ __launch_bounds__(64 * most_waves(S, JN, ROUNDS)) void separable_patc
 
   const int lane = threadIdx.x % 64, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / 64);
   const int li = lane % 16, q = lane / 16;
-  const int p = wave / g.wk, part = wave - p * g.wk;
-  int bid = blockIdx.x;
-  {  // the column slices of a patch, and neighbouring patches, on one XCD
-    const int each = g.total / kXcds, rem = g.total % kXcds, xcd = bid % kXcds;
-    bid = xcd * each + (xcd < rem ? xcd : rem) + bid / kXcds;
-  }
-  const int group = (int)div_by((unsigned)bid, g.by_slices), n0 = (bid - group * g.slices) * 16 * JN;
-  const int patch = group * g.wp + p;
-  const bool live = patch < g.patches;
-  const int strip = (int)div_by((unsigned)patch, g.row_patches), image = (int)div_by((unsigned)strip, g.col_patches);
-  const int ow0 = 4 * (patch - strip * (int)g.row_patches.d), oh0 = 4 * (strip - image * (int)g.col_patches.d);
-  const int C = g.C, N = g.N;
+  const int wk = (int)(form & 31), wp = (int)(form >> 5 & 7), pt = (int)(form >> 8 & 1), pl = (int)(form >> 9 & 1);
+  const int H = (int)(map & 0xffff), W = (int)(map >> 16), C = (int)(channels & 0xffff), N = (int)(channels >> 16);
+  const FastDiv row_patches{by_row, form >> 10 & 31, per & 0xffff}, col_patches{by_col, form >> 15 & 31, per >> 16};
+  const int p = wave * (int)(form >> 20) >> 8, part = wave - p * wk;  // (wave / wk)
+  const int n0 = (int)blockIdx.y * 16 * JN, patch = (int)blockIdx.x * wp + p;
+  const bool live = patch < (int)patches;
+  if (patch - p >= (int)patches) return;  // (the grid is padded)
+  const int strip = (int)div_by((unsigned)patch, row_patches), image = (int)div_by((unsigned)strip, col_patches);
+  const int ow0 = 4 * (patch - strip * (int)row_patches.d), oh0 = 4 * (strip - image * (int)col_patches.d);
 
   constexpr bool HALVES = patch_halves(JN, ROUNDS);
   constexpr int REGION = (int)patch_region_bytes<S, JN, ROUNDS>(), SUMS = 256 * JN;
   float* const window = reinterpret_cast<float*>(lds + wave * REGION);
   float* const taps = window + P::FLOATS;
 
-  const __amdgpu_buffer_rsrc_t xr = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(g.x), 0, (int)g.x_bytes, 0x00020000);
-  const __amdgpu_buffer_rsrc_t fr = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(g.dw_w), 0, 36 * C, 0x00020000);
-  const __amdgpu_buffer_rsrc_t br = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(g.dw_b), 0, 4 * C, 0x00020000);
+  const __amdgpu_buffer_rsrc_t xr = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(x), 0, (int)x_bytes, 0x00020000);
+  const __amdgpu_buffer_rsrc_t fr = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(dw_w), 0, 36 * C, 0x00020000);
+  const __amdgpu_buffer_rsrc_t br = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(dw_b), 0, 4 * C, 0x00020000);
   const __amdgpu_buffer_rsrc_t wr = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(g.pw_w), 0, 4 * C * N, 0x00020000);
 
   // What lies outside the map, or past the last channel, has an offset past the end and reads zeros.
@@ -112,9 +120,9 @@ __global__ __launch_bounds__(64 * most_waves(S, JN, ROUNDS)) void separable_patc
 #pragma unroll
   for (int i = 0; i < LOADS; ++i) {
     const int px = (64 * i + lane) / kPieces, r = px / P::SIDE, c = px - r * P::SIDE;
-    const int ih = oh0 * S - g.pt + r, iw = ow0 * S - g.pl + c;
-    const bool ok = (unsigned)ih < (unsigned)g.H && (unsigned)iw < (unsigned)g.W && px < P::SIDE * P::SIDE && live;
-    at[i] = ok ? 4u * (((unsigned)(image * g.H + ih) * g.W + iw) * C + 4 * piece) : 0x80000000u;
+    const int ih = oh0 * S - pt + r, iw = ow0 * S - pl + c;
+    const bool ok = (unsigned)ih < (unsigned)H && (unsigned)iw < (unsigned)W && px < P::SIDE * P::SIDE && live;
+    at[i] = ok ? 4u * (((unsigned)(image * H + ih) * W + iw) * C + 4 * piece) : 0x80000000u;
   }
 #pragma unroll
   for (int i = 0; i < FLOADS; ++i) {
@@ -130,7 +138,7 @@ __global__ __launch_bounds__(64 * most_waves(S, JN, ROUNDS)) void separable_patc
     float w[G][4][JN];  // rows 16 u + 4 q + s
   };
   auto fetch = [&](int round, Operands& o) __attribute__((always_inline)) {
-    const int c0 = kChannels32 * (part + round * g.wk);
+    const int c0 = kChannels32 * (part + round * wk);
     const bool mine = c0 + 4 * piece < C;
 #pragma unroll
     for (int i = 0; i < LOADS; ++i) win[i] = __builtin_amdgcn_raw_buffer_load_b128(xr, mine ? at[i] + 4u * c0 : 0x80000000u, 0, 0);
@@ -239,7 +247,7 @@ __global__ __launch_bounds__(64 * most_waves(S, JN, ROUNDS)) void separable_patc
     if (live && oh < g.OH && ow < g.OW && cn < N)
       *reinterpret_cast<f32x2*>(g.y + ((size_t)(image * g.OH + oh) * g.OW + ow) * N + cn) = f32x2{apply_act(s0, pw_clamp), apply_act(s1, pw_clamp)};
   };
-  if (g.wk == 1) {
+  if (wk == 1) {
 #pragma unroll
     for (int v = 0; v < 4; ++v)
 #pragma unroll
@@ -252,13 +260,13 @@ __global__ __launch_bounds__(64 * most_waves(S, JN, ROUNDS)) void separable_patc
 #pragma unroll
     for (int j = 0; j < JN; ++j) sums[(v * 64 + lane) * JN + j] = acc[j][v];
   __syncthreads();
-  for (int u = 64 * part + lane; u < 128 * JN; u += 64 * g.wk) {
+  for (int u = 64 * part + lane; u < 128 * JN; u += 64 * wk) {
     float s0 = 0.f, s1 = 0.f;
-    for (int w = 0; w < g.wk; ++w) {
-      const f32x2 t = reinterpret_cast<const f32x2*>(lds + (p * g.wk + w) * REGION)[u];
+    for (int w = 0; w < wk; ++w) {
+      const f32x2 t = reinterpret_cast<const f32x2*>(lds + (p * wk + w) * REGION)[u];
       s0 += t[0], s1 += t[1];
       if constexpr (HALVES) {
-        const f32x2 h = reinterpret_cast<const f32x2*>(lds + (p * g.wk + w + 1) * REGION - SUMS * sizeof(float))[u];
+        const f32x2 h = reinterpret_cast<const f32x2*>(lds + (p * wk + w + 1) * REGION - SUMS * sizeof(float))[u];
         s0 += h[0], s1 += h[1];
       }
     }
@@ -275,16 +283,18 @@ struct PatchForm {
 
 template <int S, int JN, int ROUNDS>
 int launch_patch(const PatchArgs& args, const PatchForm& f, hipStream_t stream) {
-  PatchArgs g = args;
+  const PatchArgs& g = args;
   auto kern = separable_patch_kernel<S, JN, ROUNDS>;
   static std::atomic<uint64_t> lds_allowed{0};
   if (allow_dynamic_lds(reinterpret_cast<const void*>(kern), 160 * 1024, lds_allowed) != TFX_OK) return TFX_ERR_LAUNCH;
-  g.wk = f.wk, g.wp = f.wp;
-  g.slices = (g.N + 16 * JN - 1) / (16 * JN);
-  g.by_slices = fast_div((unsigned)g.slices);
-  g.total = (g.patches + f.wp - 1) / f.wp * g.slices;
+  const unsigned slices = (unsigned)((g.N + 16 * JN - 1) / (16 * JN)), groups = (unsigned)((g.patches + f.wp - 1) / f.wp);
   const size_t lds_bytes = patch_region_bytes<S, JN, ROUNDS>() * f.wk * f.wp;
-  hipLaunchKernelGGL(kern, dim3((unsigned)g.total), dim3(64u * f.wk * f.wp), lds_bytes, stream, g);
+  const unsigned form = (unsigned)(f.wk | f.wp << 5 | g.pt << 8 | g.pl << 9) | g.row_patches.shift << 10 | g.col_patches.shift << 15 |
+                        (256u + f.wk - 1) / f.wk << 20;
+  hipLaunchKernelGGL(kern, dim3((groups + 7) / 8 * 8, slices), dim3(64u * f.wk * f.wp), lds_bytes, stream,
+                     g.x, g.dw_w, g.dw_b, g.x_bytes, (unsigned)g.H | (unsigned)g.W << 16, (unsigned)(g.C | g.N << 16), (unsigned)g.patches,
+                     g.row_patches.mul, g.col_patches.mul, g.row_patches.d | g.col_patches.d << 16, form,
+                     PatchRest{g.pw_w, g.pw_b, g.y, g.OH, g.OW, g.dw_act, g.pw_act});
   return check_launch();
 }
 
@@ -321,7 +331,7 @@ bool separable_patch_supported(int batch, int h, int w, int c, int n, int stride
   for (const void* p : ptrs) aligned = aligned && reinterpret_cast<uintptr_t>(p) % 16 == 0;
   const long long patches = (long long)batch * ((oh + 3) / 4) * ((ow + 3) / 4), x_bytes = (long long)batch * h * w * c * 4;
   return aligned && (stride == 1 || stride == 2) && c % 4 == 0 && c <= (stride == 1 ? 1024 : 512) && n % 8 == 0 && n <= 1024 && x_bytes < (1ll << 31) &&
-         patches < (1ll << 24);
+         patches < (1ll << 24) && h < 65536 && w < 65536;
 }
 
 // Against what the block would run as, two launches mostly: 6.5 us, their products, and for large maps the depthwise output's way
@@ -339,8 +349,8 @@ int launch_separable_patch(const float* x, const float* dw_w, const float* dw_b,
                            int batch, int h, int w, int c, int n, int oh, int ow, int stride, int pt, int pl, int dw_act, int pw_act,
                            hipStream_t stream) {
   const int row_patches = (ow + 3) / 4, col_patches = (oh + 3) / 4, patches = batch * col_patches * row_patches;
-  const PatchArgs g{x, dw_w, dw_b, pw_w, pw_b, y, h, w, c, n, oh, ow, pt, pl, patches, 0, 0, 0, 0, fast_div((unsigned)row_patches),
-                    fast_div((unsigned)col_patches), FastDiv{}, (unsigned)((long long)batch * h * w * c * 4), dw_act, pw_act};
+  const PatchArgs g{x, dw_w, dw_b, pw_w, pw_b, y, h, w, c, n, oh, ow, pt, pl, patches, fast_div((unsigned)row_patches),
+                    fast_div((unsigned)col_patches), (unsigned)((long long)batch * h * w * c * 4), dw_act, pw_act};
   const PatchForm f = patch_form(patches, c, n, stride);
 #define TFX_PATCH(S, JN, ROUNDS) \
   if (stride == S && f.jn == JN && f.rounds == ROUNDS) return launch_patch<S, JN, ROUNDS>(g, f, stream);
