@@ -695,13 +695,20 @@ int launch_gemm(const float* a, const float* b, float* c, const float* bias, int
     direct[1] = KernelCost{32, 64, 2.2, .0071, .69, .0125}.us(batch, m, n, k64);
     direct[2] = KernelCost{32, 32, 2.8, .0039, .33, .0069}.us(batch, m, n, k64);
   } else {
-    // (gemm_pair.hip: fitted to 120 products; the choice is 3.9 % slower than the fastest kernel on average, 28 % at most)
-    us128 = pair ? KernelCost{128, 128, 11.5, .0019, 1.49, .028, 2}.us(batch, m, n, k) : KernelCost{128, 128, 1.5, .026, 4.7, .027, 2}.us(batch, m, n, k);
-    us64 = pair ? KernelCost{64, 64, 7., .0217, 1.17, .0067, 4}.us(batch, m, n, k) : KernelCost{64, 64, 3.6, .026, 1.27, .0102, 4}.us(batch, m, n, k);
+    us128 = KernelCost{128, 128, 1.5, .026, 4.7, .027, 2}.us(batch, m, n, k);
+    us64 = KernelCost{64, 64, 3.6, .026, 1.27, .0102, 4}.us(batch, m, n, k);
     deep = KernelCost{16, n % 2 == 0 ? 32 : 16, 3.2, 0., .245, .0035}.us(batch, m, n, k);
     direct[0] = KernelCost{64, 64, 1.33, 0., 3.36, .0148}.us(batch, m, n, k);
     direct[1] = KernelCost{32, 64, 3.05, .0010, .88, .0090}.us(batch, m, n, k);
     direct[2] = KernelCost{32, 32, 3.48, .0012, .28, .0053}.us(batch, m, n, k);
+    if (pair) {
+      // (gemm_pair.hip: fitted to 120 products; the choice is 3.9 % slower than the fastest kernel on average, 28 % at most)  Its
+      // 128 x 128 tile sums up whole contractions, as the tile it replaces did; the kernels that split them are more exact (K = 2474,
+      // 708 x 2935: 2.7e-7 and 3.3e-7) and keep theirs, but for its 64 x 64 tile, which sums in parts.
+      const bool split = std::min(std::min(deep, direct[0]), std::min(direct[1], direct[2])) < std::min(us128, us64);
+      us128 = split ? 1e30 : KernelCost{128, 128, 11.5, .0019, 1.49, .028, 2}.us(batch, m, n, k);
+      us64 = KernelCost{64, 64, 7., .0217, 1.17, .0067, 4}.us(batch, m, n, k);
+    }
   }
   // one or two products: the fp32 instructions are the more accurate ones (split.h)
   if (k <= kFewProducts) us128 = us64 = direct[0] = direct[1] = direct[2] = 1e30;

@@ -6,7 +6,8 @@
 // what bounds it now: 8 x 1024^3, of the SIMDs' cycles vector ALU 48 %, matrix pipe 28 %, at 2.2 GHz.  us, three parts and now:
 // 8 x 1024^3 91 -> 68 - 72, 4096 x 1024 x 4096 236 -> 141, 2000^3 120 -> 79, 13 x 3225 x 961 x 725 396 -> 278; short ones, whose
 // start (the scales are agreed on between two barriers) weighs more, stay in gemm.hip.
-// Error against float64, normal operands, K = 1024 / 2048 / 4096: 2.2e-7 / 3.0e-7 / 4.1e-7, three parts 4.9 / 6.9 / 10.0.
+// Error against float64, normal operands, K = 1024 / 2048 / 4096: 128 x 128 2.2e-7 / 3.0e-7 / 4.1e-7, three parts 4.9 / 6.9 / 10.0;
+// 64 x 64, whose sums are taken in parts, K = 325 / 2464 1.1e-7 / 1.6e-7, the kernels that split the contraction 1.3 / 2.7.
 #include "gemm_slots.h"
 #include "pair.h"
 
@@ -101,6 +102,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 2) void gemm_pair_kernel(
   constexpr int NT = 64 * WAVES_M * WAVES_N;
   constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;
   constexpr int TM = WM / 32, TN = WN / 32;
+  constexpr bool FINE = BM == 64;
   static_assert(WM % 32 == 0 && WN % 32 == 0 && BK == 32, "tile shape");
   using TA = PlaneTile<BM, A_KC, 2>;
   using TB = PlaneTile<BN, B_KC, 2>;
@@ -265,6 +267,20 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 2) void gemm_pair_kernel(
     }
     __syncthreads();
   };
+  // FINE: the large products of four slices are summed apart from those before, as many roundings as a sum of K / 128 parts has
+  // besides the eight of a part, not K / 16: the products that gemm_direct.hip would take otherwise stay as exact as there.
+  // (The 128 x 128 tile has no registers for it.)
+  floatx16 total[FINE ? TM : 1][FINE ? TN : 1];
+  auto fold = [&]() __attribute__((always_inline)) {
+    if constexpr (FINE) {
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+          for (int v = 0; v < 16; ++v) total[i][j][v] += acc[i][j][v], acc[i][j][v] = 0.f;
+    }
+  };
   int lost = 0;
 #pragma unroll 1
   for (int attempt = 0; attempt < 2; ++attempt) {
@@ -276,7 +292,10 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 2) void gemm_pair_kernel(
 #pragma unroll
       for (int j = 0; j < TN; ++j)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) acc[i][j][v] = mixed[i][j][v] = 0.f;
+        for (int v = 0; v < 16; ++v) {
+          acc[i][j][v] = mixed[i][j][v] = 0.f;
+          if constexpr (FINE) total[i][j][v] = 0.f;
+        }
     auto start = [&](auto full) __attribute__((always_inline)) {
       load(0, full);
       settle(0, full);
@@ -289,8 +308,12 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 2) void gemm_pair_kernel(
     else start(std::false_type{});
     __syncthreads();
     int kt = 0;
-    for (; kt + 2 < nk_full; ++kt) k_slice(kt, std::true_type{});
+    for (; kt + 2 < nk_full; ++kt) {
+      k_slice(kt, std::true_type{});
+      if (FINE && kt % 4 == 3) fold();
+    }
     for (; kt < nk; ++kt) k_slice(kt, std::false_type{});
+    fold();
     const bool over = __syncthreads_or(seen_a.over(scale_a) || seen_b.over(scale_b)) != 0;
     const int mine = seen_a.lost(scale_a) | seen_b.lost(scale_b);
     lost = __syncthreads_or(mine != 0) == 0                   ? 0
@@ -318,7 +341,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 2) void gemm_pair_kernel(
   // Epilogue: bias[col] then activation, one dword per lane per register (two 128-byte rows per store).  The median of three drops a
   // NaN; those results are computed again below.
   auto result = [&](int i, int j, int v) __attribute__((always_inline)) {
-    const float r = ldexpf(fmaf(mixed[i][j][v], 1 / kLow, acc[i][j][v]), -exponent);
+    const float r = ldexpf(fmaf(mixed[i][j][v], 1 / kLow, FINE ? total[FINE ? i : 0][FINE ? j : 0][v] : acc[i][j][v]), -exponent);
     acc[i][j][v] = r;
     finite = fmaf(r, 0.f, finite);
     return __builtin_amdgcn_fmed3f(r + bv[j], lowest, clamp.hi);
