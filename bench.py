@@ -23,6 +23,7 @@ sys.path.insert(0, ROOT)
 
 PEAK_MFMA_F32 = 157.3e12   # FLOP/s, dense fp32 matrix peak of MI355X
 PEAK_SPLIT_F32 = 2.5e15 / 6  # fp32 product as six bf16 products on the matrix cores (csrc/split.h)
+PEAK_PAIR_F32 = 2.5e15 / 3   # as three binary16 products (csrc/pair.h: long contractions)
 PEAK_MFMA_F16 = 2.5e15     # FLOP/s, dense fp16 matrix peak (fp32 accumulate)
 PEAK_HBM = 8.0e12          # B/s
 
@@ -150,7 +151,7 @@ def main():
         a, b = dev(d["a"]), dev(d["b"])
         c = tfx.tfx_batch_matmul(a, b, False, True)
         return mfma_entry(lambda: tfx.tfx_batch_matmul(a, b, False, True, out=c), 2 * 8 * 1024 ** 3, 3 * 8 * 1024 * 1024 * 4,
-                          "batch_matmul_8x1024x1024x1024_tB", PEAK_SPLIT_F32)
+                          "batch_matmul_8x1024x1024x1024_tB", PEAK_PAIR_F32)
 
     def op_pointwise(n):
         def build():
