@@ -365,7 +365,8 @@ __global__ __launch_bounds__(512) void separable_tile_kernel(const float* x, con
 
 // The operands of the contraction's k-step s (rows 16 s ... + 15) and 64 columns from 64 c on, for each lane: 8 rows from
 // 8 (lane / 32) on of column 32 j + lane % 32, part p, at piece 64 (4 (steps c + s) + 2 j + p) + lane; behind them for each column
-// 2^17 times the exponent of its scale, plus its losses (pair.h).  A workgroup for every 32 columns.
+// 2^17 times the exponent of its scale, plus its losses (pair.h).  A workgroup for every 16 columns
+// (for every 32, twice the loads of a wavefront behind its first: the pass of 8 images 192.1 us, 190.0 so).
 struct PackArgs {
   const float* w[kMaxLayers];
   half_t* out[kMaxLayers];
@@ -374,28 +375,32 @@ struct PackArgs {
   int layers;
 };
 __global__ __launch_bounds__(1024) void pack_filters_kernel(PackArgs g) {
-  __shared__ float wave_most[16][32];
-  __shared__ int lost[32], tiny[32];
+  __shared__ float wave_most[16][16];
+  __shared__ int lost[16], tiny[16];
   int l = 0;
   while (l + 1 < g.layers && (int)blockIdx.x >= g.first[l + 1]) ++l;
-  const int nb = (int)blockIdx.x - g.first[l], wave = threadIdx.x / 64, lane = threadIdx.x % 64, li = lane % 32, h = lane / 32;
-  const int N = g.n[l], steps = g.c[l] / 16, n = 32 * nb + li;
-  constexpr int MOST = 4;  // steps of a wavefront, of up to 64
+  const int wave = threadIdx.x / 64, lane = threadIdx.x % 64, li = lane % 16, q = lane / 16;
+  const int N = g.n[l], steps = g.c[l] / 16;
+  int nb = (int)blockIdx.x - g.first[l];
+  if (N % 256 == 0 && g.first[l] % 8 == 0) nb = nb / 16 * 16 + nb % 8 * 2 + nb / 8 % 2;  // the two halves of a line on one XCD
+  const int n = 16 * nb + li;
+  constexpr int MOST = 2;  // pairs of steps of a wavefront, of up to 32: lane (li, q) has rows 8 (q % 2) ... of step q / 2 of the pair
   float v[MOST][8];
   float most = 0.f;
 #pragma unroll
   for (int u = 0; u < MOST; ++u) {
-    const int s = min(wave + 16 * u, steps - 1);
+    const int s = min(2 * (wave + 16 * u) + q / 2, steps - 1);
 #pragma unroll
-    for (int i = 0; i < 8; ++i) v[u][i] = g.w[l][(size_t)(16 * s + 8 * h + i) * N + n];
+    for (int i = 0; i < 8; ++i) v[u][i] = g.w[l][(size_t)(16 * s + 8 * (q % 2) + i) * N + n];
   }
 #pragma unroll
   for (int u = 0; u < MOST; ++u)
 #pragma unroll
     for (int i = 0; i < 8; ++i) most = __builtin_isfinite(v[u][i]) ? fmaxf(most, fabsf(v[u][i])) : most;
   most = fmaxf(most, __shfl_xor(most, 32));
-  if (h == 0) wave_most[wave][li] = most;
-  if (threadIdx.x < 32) lost[threadIdx.x] = tiny[threadIdx.x] = 0;
+  most = fmaxf(most, __shfl_xor(most, 16));
+  if (q == 0) wave_most[wave][li] = most;
+  if (threadIdx.x < 16) lost[threadIdx.x] = tiny[threadIdx.x] = 0;
   __syncthreads();
 #pragma unroll
   for (int w = 0; w < 16; ++w) most = fmaxf(most, wave_most[w][li]);
@@ -403,7 +408,7 @@ __global__ __launch_bounds__(1024) void pack_filters_kernel(PackArgs g) {
   int loses = 0;
 #pragma unroll
   for (int u = 0; u < MOST; ++u) {
-    const int s = wave + 16 * u;
+    const int s = 2 * (wave + 16 * u) + q / 2;
     if (s >= steps) break;
     h8 part[2];
 #pragma unroll
@@ -412,7 +417,7 @@ __global__ __launch_bounds__(1024) void pack_filters_kernel(PackArgs g) {
       loses = more_lost(loses, split_filter(v[u][i], e, a, b));
       part[0][i] = a, part[1][i] = b;
     }
-    h8* const out = reinterpret_cast<h8*>(g.out[l]) + (size_t)64 * (4 * (steps * (nb / 2) + s) + 2 * (nb % 2)) + lane;
+    h8* const out = reinterpret_cast<h8*>(g.out[l]) + (size_t)64 * (4 * (steps * (nb / 4) + s) + 2 * (nb / 2 % 2)) + 32 * (q % 2) + 16 * (nb % 2) + li;
     out[0] = part[0];
     out[64] = part[1];
   }
@@ -421,7 +426,7 @@ __global__ __launch_bounds__(1024) void pack_filters_kernel(PackArgs g) {
     if ((loses & kLostTiny) != 0) atomicOr(&tiny[li], kLostTiny);
   }
   __syncthreads();
-  if (threadIdx.x < 32) g.exps[l][n] = (e << 17) | lost[li] | tiny[li];
+  if (threadIdx.x < 16) g.exps[l][n] = (e << 17) | lost[li] | tiny[li];
 }
 
 size_t tile_lds(int tm, int waves_n, int wk, int c) {
@@ -523,7 +528,7 @@ int launch_pack_filters(int layers, const float* const* w, void* const* packed, 
     g.out[i] = static_cast<half_t*>(packed[i]);
     g.exps[i] = reinterpret_cast<int*>(g.out[i] + (size_t)2 * c[i] * n[i]);
     g.c[i] = c[i], g.n[i] = n[i];
-    g.first[i + 1] = g.first[i] + n[i] / 32;
+    g.first[i + 1] = g.first[i] + n[i] / 16;
   }
   g.layers = layers;
   hipLaunchKernelGGL(pack_filters_kernel, dim3((unsigned)g.first[layers]), dim3(1024), 0, stream, g);
