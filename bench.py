@@ -32,21 +32,21 @@ PEAK_HBM = 8.0e12          # B/s
 # source it was measured on, with the digest of that file followed by the shared headers csrc/tfx_internal.h and
 # csrc/stream_f16.h; if any of them has changed since, the entry is reported as null.
 MEASURED_TRAFFIC = {
-    "batch_matmul_8x1024x1024x1024_tB": (100947899, "gemm.hip", "5d58a535bead5c0919e3cc01afc446a3657cb135f771ae87a7bfae029fc98fca"),
-    "pointwise_64x56x56x128_to_128": (206181168, "pointwise.hip", "15d93d82fa9855c64b19908193d2cd50472e6e0aba20d65e784f74a96f0b76e5"),
-    "conv3x3_64x56x56x64_to_64": (106652563, "conv_window.hip", "da4c2bb7673a158ed1029692e76aebffca0bb00a977a28de83170707e5a30315"),
-    "depthwise_64x112x112x64_s1_cold_rotation": (411140572, "depthwise.hip", "faedd1558bbc91575c992934a882ba2827bca5bcf50bf0361d4f737b544afc97"),
-    "depthwise_64x112x112x64_s2_cold_rotation": (257145503, "depthwise.hip", "faedd1558bbc91575c992934a882ba2827bca5bcf50bf0361d4f737b544afc97"),
-    "batch_matmul_f16_1x4096x4096x4096_tB": (235162171, "gemm_f16.hip", "12967e0ef63acda6db5a836f2e9e6caf11ef871f97b3eb8f7678e68b8b10582e"),
-    "batch_matmul_f16_8x1024x1024x1024_tB": (50885674, "gemm_f16.hip", "12967e0ef63acda6db5a836f2e9e6caf11ef871f97b3eb8f7678e68b8b10582e"),
-    "pointwise_f16_64x56x56x128_to_128": (104331846, "pointwise_f16.hip", "914971820db49cc6c33ee2f0a1a3bf498dcfd8b7fd45c2e221b4f84075549b47"),
-    "depthwise_f16_64x112x112x64_s1_cold_rotation": (205682544, "conv_f16.hip", "3f776b145bebe4e56af24b2edc230d10fafb73579dd8482dbe01e8033628ddba"),
-    "depthwise_f16_64x112x112x64_s2_cold_rotation": (128537256, "conv_f16.hip", "3f776b145bebe4e56af24b2edc230d10fafb73579dd8482dbe01e8033628ddba"),
-    "pointwise_f16_64x14x14x512_to_512": (30192691, "pointwise_slab_f16.hip", "04f1aca7e65ba8ddd3e6e2a599a06f13adb80217bf944f78c3686fbd8ee22315"),
-    "conv3x3_f16_64x56x56x64_to_64": (55026527, "conv_stream_f16.hip", "cd29657bc09dc346908b8ea9bf450dcaf7bfe2085bb1046fb56db7a35cc14d36"),
-    "add_f32_64M": (805262912, "elementwise.hip", "5e53ad68fa684d685e5f837182507b289fc42bf11e36fede0ff5d76985fb795d"),
-    "add_f16_64M": (402652013, "elementwise.hip", "5e53ad68fa684d685e5f837182507b289fc42bf11e36fede0ff5d76985fb795d"),
-    "mobilenet_chain_kernel": (121645600, "chain.hip", "38ff325e754f6350b2aa41788a6568b567baf561fc1cba16a01eafd061cc3618"),
+    "batch_matmul_8x1024x1024x1024_tB": (122214080, "gemm_pair.hip", "2d8ee5b9efd4cb35f16a1f6aed31bfd069b4f35e70793754a1695bea0edefda6"),
+    "pointwise_64x56x56x128_to_128": (206175051, "pointwise.hip", "7e5c1bcfd1229982e7f41a500a0bfd38ab2aeeff9bf358cade01cff3e5a52406"),
+    "conv3x3_64x56x56x64_to_64": (106579440, "conv_window.hip", "de0b22d51e1f330c0870687295643fa64489bfa12f0cc33c0d395bc9fc08e485"),
+    "depthwise_64x112x112x64_s1_cold_rotation": (411139334, "depthwise.hip", "cc502c08b1e3b3898b33c2d563e31644d8339477b156770ad6cbc2048154680d"),
+    "depthwise_64x112x112x64_s2_cold_rotation": (256965092, "depthwise.hip", "cc502c08b1e3b3898b33c2d563e31644d8339477b156770ad6cbc2048154680d"),
+    "batch_matmul_f16_1x4096x4096x4096_tB": (235148849, "gemm_f16.hip", "af10815aa2d5db1b1c0561148c4e8709b435aef63e81befcdc6b1c5ba6231500"),
+    "batch_matmul_f16_8x1024x1024x1024_tB": (50467023, "gemm_f16.hip", "af10815aa2d5db1b1c0561148c4e8709b435aef63e81befcdc6b1c5ba6231500"),
+    "pointwise_f16_64x56x56x128_to_128": (104411297, "pointwise_f16.hip", "6d8323ff08f5693256205b1e4c7549c555ce04d5ca93e1423d0461377d5507fa"),
+    "depthwise_f16_64x112x112x64_s1_cold_rotation": (205680159, "conv_f16.hip", "a69c20ba8f9805727b6005e561a1cd43f6b1273da54d2e6188fc5dbd3db48720"),
+    "depthwise_f16_64x112x112x64_s2_cold_rotation": (128536260, "conv_f16.hip", "a69c20ba8f9805727b6005e561a1cd43f6b1273da54d2e6188fc5dbd3db48720"),
+    "pointwise_f16_64x14x14x512_to_512": (30208887, "pointwise_slab_f16.hip", "e95e6765c8bad74cbea34e43c98f4c508e86f8e956ba166d82db5de42d312186"),
+    "conv3x3_f16_64x56x56x64_to_64": (55029622, "conv_stream_f16.hip", "f643a2f409a369c8e7638811f8a83849b138773964cc8170742c5087ca3f8a24"),
+    "add_f32_64M": (805257849, "elementwise.hip", "ef9ed56f6eb69babf5c46d391b230fe3bad94f86e99637543774e1caf54143be"),
+    "add_f16_64M": (402649930, "elementwise.hip", "ef9ed56f6eb69babf5c46d391b230fe3bad94f86e99637543774e1caf54143be"),
+    "mobilenet_chain_kernel": (121645600, "chain.hip", "7c65965b789492caf84825582f01d07d7a42e2db4bb819caa4292b0f719831a0"),
 }
 
 
