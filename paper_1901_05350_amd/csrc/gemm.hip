@@ -13,7 +13,7 @@
 //   B operand: lane l holds B[k = 8*(l/32) .. + 7][j = l % 32]
 //   D result : register v of lane l holds D[i = 8*(v/4) + 4*(l/32) + v%4][j = l % 32]
 #include "kernel_cost.h"
-#include "gemm_slots.h"
+#include "ragged.h"
 #include "split.h"
 
 #include <cmath>
@@ -23,11 +23,6 @@ namespace tfx {
 
 namespace {
 
-// Contractions from here on take gemm_pair.hip where a tiled kernel is the choice: of 174 products with K >= 128 its tiles were 1.19 times
-// as fast as those of this file, all of them from K = 216 on; 4032 x 135 x 1559 27.5 us against 21.5, 2077 x 200 x 3200 28.3 and 25.1.
-constexpr int kPairDepth = 256;
-// ... and rows up to here: its loads lie at 32-bit byte offsets from the tile's first element, 128 rows deep
-constexpr int kPairRow = (1 << 23) - 1;
 constexpr int kXcds = 8;  // workgroups are dealt round-robin to the 8 XCDs, each with its own L2
 
 // Branch-free loads for k-slices that lie entirely inside K.  A thread's slots keep a
@@ -38,6 +33,19 @@ constexpr int kXcds = 8;  // workgroups are dealt round-robin to the 8 XCDs, eac
 // alignment; a slot of a row-contiguous operand may reach past the end of its row into the next one, so the slice with
 // the last row is not one of these when the row length is no multiple of 4.
 //
+// Slots of the tiled kernel: s = tid + it * NT;
+//   KC : row s / (BK/4), k = 4 * (s % (BK/4)) .. + 3
+//   !KC: a thread's four slots are four consecutive k of the same four rows (block b = tid: rows 4 * (b % (ROWS/4)),
+//        k = 4 * (b / (ROWS/4)) + it), so that it can hand each row's four k on together
+template <int ROWS, int BK, bool KC, int NT, int NSLOT>
+__device__ __forceinline__ int slot_row(int tid, int it) {
+  static_assert(KC || (NSLOT == 4 && ROWS * BK == 16 * NT), "one 4 x 4 block per thread");
+  return KC ? (tid + it * NT) / (BK / 4) : 4 * (tid % (ROWS / 4));
+}
+template <int ROWS, int BK, bool KC, int NT>
+__device__ __forceinline__ int slot_k(int tid, int it) {
+  return KC ? 4 * ((tid + it * NT) % (BK / 4)) : 4 * (tid / (ROWS / 4)) + it;
+}
 template <int ROWS, int BK, bool KC, int NT, int NSLOT>
 __device__ __forceinline__ void slot_pointers(const float* __restrict__ g, int ld, int rows_total, int row0, int tid,
                                               const float* (&ptr)[NSLOT]) {
@@ -54,10 +62,70 @@ __device__ __forceinline__ void slot_pointers(const float* __restrict__ g, int l
     }
   }
 }
+__device__ __forceinline__ float4 load_quad(const float* p) { return __builtin_bit_cast(float4, load16(p)); }
 template <int NSLOT>
 __device__ __forceinline__ void load_tile_full(const float* (&ptr)[NSLOT], size_t k_offset, float4 (&reg)[NSLOT]) {
 #pragma unroll
   for (int it = 0; it < NSLOT; ++it) reg[it] = load_quad(ptr[it] + k_offset);
+}
+
+// The same for any k-slice and operand of at least 4 elements: the loads of a slice (every one unconditional, from a
+// valid place) and, when its registers are consumed, what makes them the slice: quads that would have left the operand
+// were fetched a few elements early and are shifted down, elements past K are zeroed.
+// CV: the operand is a convolution's filter [taps * Ci, N] seen with the channels of a tap padded to a multiple of 4
+// (`by_cp.d`), k_total channels per tap.
+struct FilterK {
+  FastDiv by_cp;
+  int taps;
+};
+template <int ROWS, int BK, bool KC, bool CV, int NT, int NSLOT>
+__device__ __forceinline__ unsigned slot_offset(int ld, int rows_total, int k_total, int row0, int k0, int tid, int it,
+                                                unsigned total, const FilterK& fk, unsigned* early, int* valid) {
+  int gr = row0 + slot_row<ROWS, BK, KC, NT, NSLOT>(tid, it), gk = k0 + slot_k<ROWS, BK, KC, NT>(tid, it);
+  unsigned off;
+  if (KC) {
+    gr = min(gr, rows_total - 1);
+    *valid = k_total - gk;
+    off = (unsigned)gr * (unsigned)ld + (unsigned)(*valid > 0 ? gk : 0);
+  } else {
+    if (gr >= rows_total) gr = 0;
+    bool in;
+    if constexpr (CV) {
+      const int tap = (int)div_by((unsigned)gk, fk.by_cp), c = gk - tap * (int)fk.by_cp.d;
+      in = tap < fk.taps && c < k_total;
+      gk = tap * k_total + c;
+    } else {
+      in = gk < k_total;
+    }
+    *valid = in ? 4 : 0;
+    off = (unsigned)(in ? gk : 0) * (unsigned)ld + (unsigned)gr;
+  }
+  const unsigned at = min(off, total - 4u);
+  *early = off - at;
+  return at;
+}
+template <int ROWS, int BK, bool KC, bool CV, int NT, int NSLOT>
+__device__ __forceinline__ void load_tile_any(const float* __restrict__ g, int ld, int rows_total, int k_total, int row0, int k0,
+                                              int tid, unsigned total, const FilterK& fk, float4 (&reg)[NSLOT]) {
+#pragma unroll
+  for (int it = 0; it < NSLOT; ++it) {
+    unsigned early;
+    int valid;
+    reg[it] = load_quad(g + slot_offset<ROWS, BK, KC, CV, NT, NSLOT>(ld, rows_total, k_total, row0, k0, tid, it, total, fk, &early, &valid));
+  }
+}
+template <int ROWS, int BK, bool KC, bool CV, int NT, int NSLOT>
+__device__ __forceinline__ void settle_tile(int ld, int rows_total, int k_total, int row0, int k0, int tid, unsigned total,
+                                            const FilterK& fk, float4 (&reg)[NSLOT]) {
+#pragma unroll
+  for (int it = 0; it < NSLOT; ++it) {
+    unsigned early;
+    int valid;
+    slot_offset<ROWS, BK, KC, CV, NT, NSLOT>(ld, rows_total, k_total, row0, k0, tid, it, total, fk, &early, &valid);
+    ragged_u32x4 v = __builtin_bit_cast(ragged_u32x4, reg[it]);
+    if (__builtin_amdgcn_ballot_w64(early != 0) != 0) v = shift_down<float>(v, early);
+    reg[it] = __builtin_bit_cast(float4, v & first_elements<float>(valid));
+  }
 }
 
 // Implicit-GEMM view of a convolution input (NHWC): GEMM row = output pixel (n, oh, ow), GEMM
@@ -188,10 +256,29 @@ __device__ __forceinline__ void load_tile_conv_lean(const float* (&p0)[NSLOT], c
   }
 }
 
+__device__ __forceinline__ float f4_get(const float4& v, int s) {
+  return s == 0 ? v.x : (s == 1 ? v.y : (s == 2 ? v.z : v.w));
+}
+
+// LDS tile of one operand of the tiled kernel: three planes (hi, mid, lo) of ROWS rows of 32 k, k contiguous, in
+// pieces of 8 k (16 bytes).  Rows of a !KC operand are stored in the order row % 4, row / 4: then the writes of a
+// wavefront, one row of every thread's 4 x 4 block at a time, and the fragment reads, 32 consecutive rows, both spread
+// over all banks with the piece order rotated as below.
+template <int ROWS, bool KC>
+struct PlaneTile {
+  static constexpr int kPlane = ROWS * 64;  // bytes
+  static constexpr int kBytes = kParts * kPlane;
+  static __device__ __forceinline__ int at(int row, int piece) {  // byte offset of a piece in its plane
+    const int r = KC ? row : (row % 4) * (ROWS / 4) + row / 4;
+    const int turn = KC ? (r / 8) & 3 : ((r / 8) ^ row) & 3;
+    return r * 64 + ((piece ^ turn) * 16);
+  }
+};
+
 // Registers -> LDS: splits a thread's slots and writes four k of a row at a time (8 bytes per plane).
 template <int ROWS, int BK, bool KC, int NT, int NSLOT>
 __device__ __forceinline__ void store_planes(char* __restrict__ lds, int tid, const float4 (&reg)[NSLOT], SplitGuard& guard) {
-  using T = PlaneTile<ROWS, KC, kParts>;
+  using T = PlaneTile<ROWS, KC>;
   static_assert(BK == 32, "rows of 32 k");
 #pragma unroll
   for (int it = 0; it < NSLOT; ++it) {
@@ -230,8 +317,8 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_mfma_kernel(
   constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;
   constexpr int TM = WM / 32, TN = WN / 32;
   static_assert(WM % 32 == 0 && WN % 32 == 0 && BK == 32, "tile shape");
-  using TA = PlaneTile<BM, A_KC, kParts>;
-  using TB = PlaneTile<BN, B_KC, kParts>;
+  using TA = PlaneTile<BM, A_KC>;
+  using TB = PlaneTile<BN, B_KC>;
   static_assert(BM * BK / 4 % NT == 0 && BN * BK / 4 % NT == 0, "loader shape");
   constexpr int SA = BM * BK / 4 / NT, SB = BN * BK / 4 / NT;
 
@@ -684,7 +771,6 @@ int launch_gemm(const float* a, const float* b, float* c, const float* bias, int
   }
   // Which kernel (kernel_cost.h).  Below 128 the contraction has constants of its own, in whole slices of the LDS tiles and
   // whole steps of the wavefronts that split it.
-  const bool pair = k >= kPairDepth && std::max(std::max(m, n), k) <= kPairRow;
   double us128, us64, deep, direct[3];
   if (k < 128) {
     const int k32 = (k + 31) / 32 * 32, k64 = k < 64 ? 64 : k;
@@ -701,14 +787,6 @@ int launch_gemm(const float* a, const float* b, float* c, const float* bias, int
     direct[0] = KernelCost{64, 64, 1.33, 0., 3.36, .0148}.us(batch, m, n, k);
     direct[1] = KernelCost{32, 64, 3.05, .0010, .88, .0090}.us(batch, m, n, k);
     direct[2] = KernelCost{32, 32, 3.48, .0012, .28, .0053}.us(batch, m, n, k);
-    if (pair) {
-      // (gemm_pair.hip: fitted to 120 products; the choice is 3.9 % slower than the fastest kernel on average, 28 % at most)  Its
-      // 128 x 128 tile sums up whole contractions, as the tile it replaces did; the kernels that split them are more exact (K = 2474,
-      // 708 x 2935: 2.7e-7 and 3.3e-7) and keep theirs, but for its 64 x 64 tile, which sums in parts.
-      const bool split = std::min(std::min(deep, direct[0]), std::min(direct[1], direct[2])) < std::min(us128, us64);
-      us128 = split ? 1e30 : KernelCost{128, 128, 11.5, .0019, 1.49, .028, 2}.us(batch, m, n, k);
-      us64 = KernelCost{64, 64, 7., .0217, 1.17, .0067, 4}.us(batch, m, n, k);
-    }
   }
   // one or two products: the fp32 instructions are the more accurate ones (split.h)
   if (k <= kFewProducts) us128 = us64 = direct[0] = direct[1] = direct[2] = 1e30;
@@ -722,8 +800,6 @@ int launch_gemm(const float* a, const float* b, float* c, const float* bias, int
       return wide ? launch_m16_direct<2>(a, b, c, bias, m, n, k, act, stream)
                   : launch_m16_direct<1>(a, b, c, bias, m, n, k, act, stream);
   }
-  if (pair && (us128 == best || us64 == best))
-    return launch_gemm_pair(a, b, c, bias, batch, m, n, k, a_kc, b_kc, act, stream, us128 == best ? 128 : 64);
   if (us128 == best) return launch_layout<128, 128, 32, 2, 2>(a, b, c, bias, batch, m, n, k, a_kc, b_kc, act, stream);
   if (us64 == best) return launch_layout<64, 64, 32, 1, 2>(a, b, c, bias, batch, m, n, k, a_kc, b_kc, act, stream);
   if (deep == best) return launch_gemm_deep(a, b, c, bias, batch, m, n, k, a_kc, b_kc, act, stream);

@@ -1,4 +1,4 @@
-// fp32 products on the binary16 matrix cores, operands split in two: the blocks of block_tile.hip, the products of gemm_pair.hip.
+// fp32 products on the binary16 matrix cores, operands split in two: the blocks of block_tile.hip.
 //
 // a = h + l / 2^11 with h the nearest half and l the nearest half of 2^11 times the remainder: 22 bits and the remainder's sign, so
 // the pair misses at most the last bit of a float's 24.  Three or four products of halfs (h h, h l, l h, and l l, 2^-24 of the product
@@ -11,7 +11,8 @@
 // four k-steps summed apart) 2.43 and 3.68, 3/4 width 33 images 2.2 and 2.9.
 //
 // Binary16 has few exponents, so operands are scaled by powers of two: a depthwise output, 0 ... 6, by 2^13, a column of a filter
-// so that its largest value is in [2^14, 2^15), an operand of a tiled product by its first slice (gemm_pair.hip).
+// so that its largest value is in [2^14, 2^15).  That holds here, where one operand has bounds and the other a scale a column.  Matrix
+// products do not: with a scale a tile, one value of 1000 among normal ones sent 8 x 1024^3 from 78 to 347 us (three bf16 parts 92).
 //
 // Values that the split does not carry: a scaled value below 2^-14 loses up to 2^-36, one below 2^-60 no more than itself.  With
 // operands below 2^16 a sum of K products, n of them with the first, then misses less than n 2^-20 + K 2^-44, which a result of 2^24
@@ -28,7 +29,6 @@ namespace tfx {
 
 typedef _Float16 half_t;
 typedef _Float16 h8 __attribute__((ext_vector_type(8)));
-typedef _Float16 h4 __attribute__((ext_vector_type(4)));
 
 constexpr int kMapScale = 13;  // depthwise outputs times 2^13
 constexpr float kLow = 2048.f;  // second parts times 2^11
@@ -85,39 +85,6 @@ __device__ __forceinline__ float loss_limit(int products, int e, int lost) {
   const int n = min(lost & kLostMost, products);
   return lost == 0 ? 0.f : ldexpf(n != 0 ? (float)n : (float)products, (n != 0 ? 5 : -20) - e);
 }
-
-// Scale 2^e of an operand: its largest value in [2^14, 2^15), within what a float can hold.  `most` has the bits of that value and is
-// the same for the whole wavefront, as all that follows from it (integers, for the scalar unit).
-struct PairScale {
-  int e;
-  __device__ __forceinline__ explicit PairScale(int most) { e = most > 0 ? max(-112, min(112, 141 - (most >> 23))) : 0; }
-  __device__ __forceinline__ float scale() const { return __int_as_float((127 + e) << 23); }
-  __device__ __forceinline__ float limit() const { return ldexpf(65504.f, -e); }  // the largest magnitude that it carries
-  // bits without the sign, times two, below which a value loses up to 2^-36 when scaled, and below which no more than itself
-  __device__ __forceinline__ unsigned from() const { return (unsigned)(113 - e) << 24; }
-  __device__ __forceinline__ unsigned tiny() const { return e < 67 ? (unsigned)(67 - e) << 24 : 2u; }
-};
-
-// What a thread saw of an operand: the largest magnitude (NaN is not seen), and the least and the largest of the bits without the sign,
-// times two, less `tiny`: zeros are 2^32 - tiny, smaller ones than tiny lie above, all others below.
-struct PairSeen {
-  float most = 0.f;
-  unsigned least = ~0u, largest = 0;
-  __device__ __forceinline__ void see(const floatx4& v, unsigned tiny) {
-    asm("v_max3_f32 %0, %0, |%1|, |%2|" : "+v"(most) : "v"(v[0]), "v"(v[1]));
-    asm("v_max3_f32 %0, %0, |%1|, |%2|" : "+v"(most) : "v"(v[2]), "v"(v[3]));
-#pragma unroll
-    for (int e = 0; e < 4; e += 2) {
-      const unsigned a = (__float_as_uint(v[e]) << 1) - tiny, b = (__float_as_uint(v[e + 1]) << 1) - tiny;
-      asm("v_min3_u32 %0, %0, %1, %2" : "+v"(least) : "v"(a), "v"(b));
-      asm("v_max3_u32 %0, %0, %1, %2" : "+v"(largest) : "v"(a), "v"(b));
-    }
-  }
-  __device__ __forceinline__ bool over(const PairScale& s) const { return most > s.limit() && most < INFINITY; }
-  __device__ __forceinline__ int lost(const PairScale& s) const {
-    return (least < s.from() - s.tiny() ? kLostMost : 0) | (largest > 0u - s.tiny() ? kLostTiny : 0);
-  }
-};
 
 }  // namespace tfx
 

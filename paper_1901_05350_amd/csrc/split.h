@@ -29,6 +29,7 @@
 namespace tfx {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float floatx16 __attribute__((ext_vector_type(16)));
 
 constexpr int kParts = 3, kFewProducts = 2;
 

@@ -35,7 +35,6 @@ __device__ __forceinline__ float apply_act(float v, const ActClamp& c) {
 __device__ __forceinline__ float apply_act(float v, int act) { return apply_act(v, make_act(act)); }
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
-typedef float floatx16 __attribute__((ext_vector_type(16)));
 
 // Value held by the lane 8 places away within the lane's group of 16 (l % 16 <-> (l % 16) ^ 8): DPP row rotate by 8.
 __device__ __forceinline__ float swap8(float v) {
@@ -160,10 +159,6 @@ int launch_gemm_direct_f16(const uint16_t* a, const uint16_t* b, uint16_t* c, co
 int launch_conv2d_gemm_direct_f16(const uint16_t* x, const uint16_t* w, const uint16_t* bias, uint16_t* y, int n, int h, int wd,
                                   int ci, int fh, int fw, int co, int oh, int ow, int sh, int sw, int pt, int pl, int act,
                                   hipStream_t stream, int form);
-
-// Products of long contractions on operands split in two (gemm_pair.hip): tiles of 128 x 128 or 64 x 64, operands of at least 4 elements.
-int launch_gemm_pair(const float* a, const float* b, float* c, const float* bias, int batch, int m, int n, int k, bool a_kc, bool b_kc,
-                     int act, hipStream_t stream, int tile);
 
 // A short contraction (gemm_thin.hip), K <= 32 floats or 64 halfs (one batch, A stored [M,K]), operands of at least 8 elements;
 // the conv form: the pixels that a 1x1 convolution of that stride reads of an [n, h, w, k] image as the rows (m = n oh ow, no

@@ -1,5 +1,5 @@
-"""fp32 products on operands split in two halves (gemm_pair.hip): edges of tiles and slices, and values that the split's scales do not
-carry.  The bound is K roundings to 24 bits of the sums of magnitudes on either side, twice that where a value loses its last bits."""
+"""fp32 products of K >= 256 (gemm.hip and the kernels that it chooses from): edges of tiles and slices, and values of very different
+size in one product.  The bound is K roundings to 24 bits of the sums of magnitudes on either side."""
 import numpy as np
 import pytest
 
@@ -38,7 +38,7 @@ def test_pair_products(b, m, k, n, ta, tb):
 
 @pytest.mark.parametrize("n", [1280, 449])
 def test_pair_products_larger_values_behind_the_first_slice(n):
-    """The scales come from the first 32 of K: zeros there, or values 2^8 ... 2^60 smaller than what follows (the tile is computed again)."""
+    """The first 32 of K, a slice of the tiled kernels: zeros, or values 2^8 ... 2^60 smaller than what follows."""
     rng = np.random.default_rng(7)
     for factor in (0.0, 2.0 ** -8, 2.0 ** -20, 2.0 ** -60):
         a, w = operands(rng, 1, 1300, 500, n, False, False)
