@@ -45,3 +45,9 @@ def test_sums_of_few_products(q, size, batch, block, chain):
     got = host(tfx.MobileNetV1(w, batch=batch, image_size=size, width_quarters=q).features(image, block)).astype(np.float64)
     print((got.min() - 4) * 2 ** 23, (got.max() - 4) * 2 ** 23, c)
     assert np.all(got >= 4 + (c - chain) * 2.0 ** -23) and np.all(got <= 4 + c * 2.0 ** -23)
+
+
+@pytest.mark.parametrize("q,size,batch,blocks", [(3, 192, 2, (6, 7, 11)), (3, 224, 5, (13,)), (3, 60, 20, (7,)), (3, 64, 10, (13,))])
+def test_patches_that_no_eight_xcds_share_evenly(q, size, batch, blocks):
+    """10, 18 or 20 patches, whose column slices come first in the grid."""
+    test_patch_blocks(q, size, batch, blocks)
