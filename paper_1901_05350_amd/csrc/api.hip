@@ -167,18 +167,25 @@ BlockPlan32 plan_blocks(const tfx_mobilenet_v1_variant& v, int64_t batch) {
     auto fits = [&](auto supported) {
       return supported((int)batch, hw, hw, c, n, s, out, out, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr);
     };
-    // The tile form stands where two launches stood, the slower ones in 284 of 299 blocks of 2 - 64 images (512 -> 512, 64 images 35 us
-    // against 66, 8 images 12.2 and 17.8; the others are up to 0.8 us apart), and the window kernel's 128 -> 128 where that has less
-    // than half a round of units (0.44 of 2048: 9.7 us against 14.1; from there on 19.5 against 16.3 to 67.6 against 71.7 at six
-    // rounds).  The patch kernel and the window kernel's thinner filters keep their blocks: their sums are the more accurate ones.
+    // The tile form takes the blocks of two launches with many outputs.  Of 1346 such blocks (336 passes: 2 - 64 images of 64 x 64 to
+    // 224 x 224, every width) it is faster for 606 of the 608 from these lines on, .62 of their time (512 -> 512, 64 images 35 us
+    // against 66, 8 images 12 and 18), and pays for the launch that prepares the filters in every one of the passes; it is slower for
+    // 505 of the others, 1.18 times on average (512 -> 512, 32 pixels 9.8 and 6.2; as tiles they made the pass of 2 images of 64 x 64
+    // 128 us instead of 82).  Below the lines for up to 384 channels its sums are also the less exact ones: the products of two
+    // launches split the contraction there (256 -> 256, 2400 pixels 1.2e-7 against float64 and 1.0e-7; 192 -> 192, 9600 pixels 1.4
+    // and 1.2; above them 1.1 and 1.7 for the kernels that it replaced).
+    // And the window kernel's 128 -> 128 where that has less than half a round of units (0.44 of 2048: 9.7 us against 14.1; from
+    // there on 19.5 against 16.3 to 67.6 against 71.7 at six rounds).  The patch kernel and the window kernel's thinner filters keep
+    // their blocks: their sums are the more accurate ones.
     const bool tile = batch > 1 && fits(separable_tile_supported);
+    const bool many = batch * out * out * n >= (c >= 512 ? 400000 : n >= 256 ? 800000 : 2000000);
     const int64_t units = batch * ((out + 1) / 2) * ((out + 7) / 8);
     const bool wide = c == 128 && n == 128 && units <= 1024;
     p.without[b] = batch > 1 && separable_patch_pays((int)batch, c, n, s, out, out) && fits(separable_patch_supported) ? kPatch32
                    : separable_block_supported(batch, hw, hw, c, n, s, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr) ? kBlock32
                    : fits(separable_stream_supported) ? kStream32
                                                       : kTwo32;
-    p.form[b] = tile && (p.without[b] == kTwo32 || (wide && p.without[b] == kStream32)) ? kTile32 : p.without[b];
+    p.form[b] = tile && (p.without[b] == kTwo32 ? many : wide && p.without[b] == kStream32) ? kTile32 : p.without[b];
     if (p.form[b] == kTile32) {
       ++p.tiles;
       p.packed[b] = p.packed_bytes;
@@ -186,7 +193,6 @@ BlockPlan32 plan_blocks(const tfx_mobilenet_v1_variant& v, int64_t batch) {
     }
     hw = out;
   }
-  if (p.tiles < 3) p.drop_tiles();  // (the launch that prepares the filters)
   return p;
 }
 
