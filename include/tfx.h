@@ -229,7 +229,8 @@ typedef struct {
 } tfx_mobilenet_v1_variant;
 
 /* Workspace bytes for `batch` images of a variant; 0 if the variant or batch is
- * invalid.  Host-only. */
+ * invalid.  From batch 2 on a workspace is large enough for every smaller batch of 2 or more.
+ * Host-only. */
 size_t tfx_mobilenet_v1_variant_workspace_bytes(const tfx_mobilenet_v1_variant* variant, int64_t batch);
 
 /* As tfx_mobilenet_v1_forward for a variant: input device
@@ -267,10 +268,12 @@ int tfx_mobilenet_v1_variant_features(const tfx_mobilenet_v1_variant* variant, c
  * library runs on holds until the process ends, from the moment the runtime loads the
  * library's device code there (at the latest during the first call of this entry point
  * on that GPU, which also looks up the array's device address once).  The call
- * allocates and frees nothing.  {224, 4, 1000} fits at batch 1 and 2; a variant / batch whose
- * tfx_mobilenet_v1_variant_workspace_bytes exceeds the array is refused with
- * TFX_ERR_WORKSPACE (nothing enqueued).  Results are bit-identical to
- * tfx_mobilenet_v1_variant_forward.  All calls on one GPU share the one array: calls that
+ * allocates and frees nothing.  {224, 4, 1000} fits at batch 1 and 2; a variant / batch that
+ * does not fit the array is refused with TFX_ERR_WORKSPACE (nothing enqueued).  Results are
+ * bit-identical to tfx_mobilenet_v1_variant_forward wherever that one's
+ * tfx_mobilenet_v1_variant_workspace_bytes is at most the array.  A pass that fits only
+ * without the re-ordered filters that a larger workspace holds (images of 33 to 38 pixels, 87 to 226
+ * of them, few classes) goes without, and agrees to rounding.  All calls on one GPU share the one array: calls that
  * overlap in time on one GPU (different streams or host threads) race and give
  * undefined results; calls ordered on one stream are fine.  Nothing in the array has to
  * start at zero (each kernel writes what later kernels read), so its contents between

@@ -186,8 +186,9 @@ BlockPlan32 plan_blocks(const tfx_mobilenet_v1_variant& v, int64_t batch) {
                    : fits(separable_stream_supported) ? kStream32
                                                       : kTwo32;
     p.form[b] = tile && (p.without[b] == kTwo32 ? many : wide && p.without[b] == kStream32) ? kTile32 : p.without[b];
-    if (p.form[b] == kTile32) {
-      ++p.tiles;
+    if (p.form[b] == kTile32) ++p.tiles;
+    // (room for the wide block's at any batch: a workspace is large enough for every smaller batch, one image apart)
+    if (p.form[b] == kTile32 || (tile && c == 128 && n == 128 && p.form[b] == kStream32)) {
       p.packed[b] = p.packed_bytes;
       p.packed_bytes += align_up(separable_tile_packed_bytes(c, n));
     }
@@ -208,7 +209,8 @@ struct NetPlan {
   bool head;          // and for blocks 2 - 4 as stages of one launch (block.hip): their three outputs at once
 };
 
-NetPlan plan_net(const tfx_mobilenet_v1_variant& v, int64_t batch, size_t elem_bytes = sizeof(float)) {
+// most: a workspace whose size is given (the static one); an fp32 pass that fits it only without the tile blocks' filters goes without.
+NetPlan plan_net(const tfx_mobilenet_v1_variant& v, int64_t batch, size_t elem_bytes = sizeof(float), size_t most = 0) {
   NetPlan p{};
   // largest feature map: the output of the first pointwise layer (half the image size, 64 alpha channels)
   const size_t half = (size_t)(v.image_size + 1) / 2;
@@ -234,9 +236,8 @@ NetPlan plan_net(const tfx_mobilenet_v1_variant& v, int64_t batch, size_t elem_b
   if (elem_bytes == sizeof(uint16_t)) {
     off += plan_blocks_f16(v, batch).packed_halfs * sizeof(uint16_t);
   } else {
-    // (a pass that fits the static workspace only without them goes without)
     p.blocks = plan_blocks(v, batch);
-    if (off <= kStaticScratchBytes && off + p.blocks.packed_bytes > kStaticScratchBytes) p.blocks.drop_tiles();
+    if (off <= most && off + p.blocks.packed_bytes > most) p.blocks.drop_tiles();
     off += p.blocks.packed_bytes;
   }
   p.bytes = off;
@@ -490,14 +491,14 @@ int check_net_args(const tfx_mobilenet_v1_variant* variant, const float* input, 
 }
 
 // The forward pass; end_block = 0: the whole network into probs / logits; end_block = 1 .. 13: stop after that
-// depthwise-separable block, whose output goes to `features` instead of the workspace.
+// depthwise-separable block, whose output goes to `features` instead of the workspace.  most: plan_net's.
 int forward_impl(const tfx_mobilenet_v1_variant* variant, const float* input, int64_t batch,
                  const tfx_mobilenet_v1_weights* weights, void* workspace, size_t workspace_bytes, float* probs,
-                 float* logits, int end_block, float* features, void* stream) {
+                 float* logits, int end_block, float* features, void* stream, size_t most = 0) {
   if (const int bad = check_net_args(variant, input, batch, weights, workspace,
                                      end_block == 0 ? (const void*)probs : (const void*)features))
     return bad;
-  const NetPlan plan = plan_net(*variant, batch);
+  const NetPlan plan = plan_net(*variant, batch, sizeof(float), most);
   if (workspace_bytes < plan.bytes || reinterpret_cast<uintptr_t>(workspace) % kAlign != 0) return TFX_ERR_WORKSPACE;
   const int q = (int)variant->width_quarters;
 
@@ -704,12 +705,12 @@ int tfx_mobilenet_v1_variant_forward_static(const tfx_mobilenet_v1_variant* vari
   if (!valid_variant(variant)) return TFX_ERR_ARG;
   if (batch < 1) return TFX_ERR_SHAPE;
   if (batch > 1024) return TFX_ERR_UNSUPPORTED;
-  if (plan_net(*variant, batch).bytes > kStaticScratchBytes) return TFX_ERR_WORKSPACE;
+  if (plan_net(*variant, batch, sizeof(float), kStaticScratchBytes).bytes > kStaticScratchBytes) return TFX_ERR_WORKSPACE;
   void* ws = static_scratch();
   if (!ws) return TFX_ERR_LAUNCH;
   // Every kernel of the forward pass writes the part of the workspace it later reads (feature maps, the fully
   // connected layer's partial sums), so nothing has to be cleared between calls.
-  return forward_impl(variant, input, batch, weights, ws, kStaticScratchBytes, probs, logits, 0, nullptr, stream);
+  return forward_impl(variant, input, batch, weights, ws, kStaticScratchBytes, probs, logits, 0, nullptr, stream, kStaticScratchBytes);
 }
 
 size_t tfx_mobilenet_v1_workspace_bytes_f16(const tfx_mobilenet_v1_variant* variant, int64_t batch) {

@@ -46,3 +46,18 @@ def test_tile_blocks_columns_of_lost_bits(batch):
             # 512 roundings of 24 bits on either side, of terms of up to 6 x 0.5
             assert np.all(np.abs(got[i, ..., col] - ref[0, ..., col]) <= 2 * 512 * 2.0 ** -24 * 3 * 2.0 ** scale), col
         assert_close(got[i:i + 1], ref, "image %d" % i)
+
+
+def test_static_pass_that_fits_without_tiles_only():
+    """88 images of 33 x 33: tiles in a workspace of the caller's, two launches in the static one."""
+    import torch
+    import paper_1901_05350_amd as tfx
+    d = inputs.mobilenet_v1(seed=77, batch=4, image_size=33, classes=10)
+    model = tfx.MobileNetV1(d["weights"], batch=88, image_size=33)
+    assert tfx.tfx_mobilenet_v1_variant_workspace_bytes(model.variant, 88) > tfx.tfx_mobilenet_v1_static_scratch_bytes()
+    image = dev(np.concatenate([d["image"]] * 22))
+    probs, logits = (torch.zeros((88, 10), dtype=torch.float32, device="cuda") for _ in range(2))
+    tfx.tfx_mobilenet_v1_variant_forward_static(model.variant, image, model.struct, probs, logits)
+    want = model.forward(image)
+    assert_close(host(logits), host(want[1]), "logits")
+    assert_close(host(probs), host(want[0]), "probs")
