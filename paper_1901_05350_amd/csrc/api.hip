@@ -606,16 +606,18 @@ int forward_impl(const tfx_mobilenet_v1_variant* variant, const float* input, in
   }
   const int blocks = end_block ? end_block : kBlocks;
   const BlockPlan32& form = plan.blocks;  // of the whole network: a feature map is the one a pass computes
-  bool aligned = true;
-  for (int b = first_block; b < blocks; ++b)
+  auto aligned = [&](int b) {  // else the block runs as two launches, which take any element
+    bool ok = true;
     for (const void* p : {weights->dw_w[b], weights->dw_b[b], weights->pw_w[b], weights->pw_b[b]})
-      aligned = aligned && reinterpret_cast<uintptr_t>(p) % 16 == 0;
-  if (aligned && form.tiles > 0) {
+      ok = ok && reinterpret_cast<uintptr_t>(p) % 16 == 0;
+    return ok;
+  };
+  if (form.tiles > 0) {
     const float* filters[kBlocks];
     void* packed[kBlocks];
     int tiles = 0, c[kBlocks], n[kBlocks];
     for (int b = first_block; b < blocks; ++b)
-      if (form.form[b] == kTile32) {
+      if (form.form[b] == kTile32 && aligned(b)) {
         filters[tiles] = weights->pw_w[b], packed[tiles] = ws + plan.off_packed + form.packed[b];
         c[tiles] = form.c[b], n[tiles] = form.n[b];
         ++tiles;
@@ -630,7 +632,7 @@ int forward_impl(const tfx_mobilenet_v1_variant* variant, const float* input, in
     const int64_t fd[4] = {3, 3, shape[3], 1};
     const int64_t cout = kChannels[b] * q / 4;
     conv_geometry(shape, fd, kStrides[b], kStrides[b], TFX_PAD_SAME, true, &g);
-    if (aligned && form.form[b] != kTwo32) {
+    if (form.form[b] != kTwo32 && aligned(b)) {
       if (form.form[b] == kTile32) {
         rc = launch_separable_tile(buf[cur], weights->dw_w[b], weights->dw_b[b], weights->pw_w[b], weights->pw_b[b],
                                    ws + plan.off_packed + form.packed[b], block_out, (int)batch, (int)shape[1], (int)shape[2], (int)shape[3],
