@@ -173,12 +173,12 @@ BlockPlan32 plan_blocks(const tfx_mobilenet_v1_variant& v, int64_t batch) {
     // 505 of the others, 1.18 times on average (512 -> 512, 32 pixels 9.8 and 6.2; as tiles they made the pass of 2 images of 64 x 64
     // 128 us instead of 82).  Below the lines for up to 384 channels its sums are also the less exact ones: the products of two
     // launches split the contraction there (256 -> 256, 2400 pixels 1.2e-7 against float64 and 1.0e-7; 192 -> 192, 10496 pixels 1.3
-    // and 1.1; above them 1.3 and 2.0 for the kernels that it replaced).
+    // and 1.1; above them 1.3 and 2.0 for the kernels that it replaced; 96 -> 192, 12544 pixels 1.2e-7 and .9, 15680 pixels 1.2 and 1.3).
     // And the window kernel's 128 -> 128 where that has less than half a round of units (0.44 of 2048: 9.7 us against 14.1; from
     // there on 19.5 against 16.3 to 67.6 against 71.7 at six rounds).  The patch kernel and the window kernel's thinner filters keep
     // their blocks: their sums are the more accurate ones.
     const bool tile = batch > 1 && fits(separable_tile_supported);
-    const bool many = batch * out * out * n >= (c >= 512 ? 400000 : n >= 256 ? 800000 : 2100000);
+    const bool many = batch * out * out * n >= (c >= 512 ? 400000 : n >= 256 ? 800000 : c >= 192 ? 2100000 : 3000000);
     const int64_t units = batch * ((out + 1) / 2) * ((out + 7) / 8);
     const bool wide = c == 128 && n == 128 && units <= 1024;
     p.without[b] = batch > 1 && separable_patch_pays((int)batch, c, n, s, out, out) && fits(separable_patch_supported) ? kPatch32

@@ -11,6 +11,9 @@
 // depthwise kernel and the product of bf16 parts that stood here took 66.  64 x 28 x 28 x 256 -> 256 83 -> 45, 256 -> 512 at stride 2
 // 45 -> 27, 7 x 7 x 1024 -> 1024 64 -> 39; the pass of 64 images 767 -> 562, of 16 290 -> 250, of 8 207 -> 192.
 //
+// 96 channels, an odd number of k-step pairs, take two blocks of 32 pixels (96 -> 192 of the 3/4 width: 20 images 28.1 us as two launches,
+// 13.0 so).
+//
 // Results that the split does not carry (pair.h) are computed again over the first ones, unless the pixel's depthwise output is NaN.
 #include "pair.h"
 
@@ -336,12 +339,12 @@ __global__ __launch_bounds__(512) void separable_tile_kernel(const float* x, con
       } else if (__builtin_popcountll(columns) <= 4) {
         float d[16];
 #pragma unroll
-        for (int i = 0; i < 16; ++i) d[i] = 64 * i < C ? depthwise(64 * i + lane) : 0.f;
+        for (int i = 0; i < 16; ++i) d[i] = 64 * i + lane < C ? depthwise(64 * i + lane) : 0.f;
         for (unsigned long long rest = columns; rest != 0; rest &= rest - 1) {
           const int col = __builtin_ctzll(rest);
           float s = 0.f;
 #pragma unroll
-          for (int i = 0; i < 16; ++i) s = fmaf(d[i], 64 * i < C ? g.pw_w[(size_t)(64 * i + lane) * N + n0 + col] : 0.f, s);
+          for (int i = 0; i < 16; ++i) s = fmaf(d[i], 64 * i + lane < C ? g.pw_w[(size_t)(64 * i + lane) * N + n0 + col] : 0.f, s);
 #pragma unroll
           for (int m = 32; m > 0; m /= 2) s += __shfl_xor(s, m);
           sum = lane == col ? s : sum;
@@ -349,11 +352,13 @@ __global__ __launch_bounds__(512) void separable_tile_kernel(const float* x, con
       } else {
 #pragma unroll 1
         for (int k0 = 0; k0 < C; k0 += 64) {
-          const float d = depthwise(k0 + lane);
+          const float d = k0 + lane < C ? depthwise(k0 + lane) : 0.f;
           float part_sum = 0.f;
-#pragma unroll 32
-          for (int k = 0; k < 64; ++k)
-            part_sum = fmaf(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(d), k)), g.pw_w[(size_t)(k0 + k) * N + n0 + lane], part_sum);
+#pragma unroll 1
+          for (int k1 = 0; k1 < 64 && k0 + k1 < C; k1 += 32)
+#pragma unroll
+            for (int k = 0; k < 32; ++k)
+              part_sum = fmaf(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(d), k1 + k)), g.pw_w[(size_t)(k0 + k1 + k) * N + n0 + lane], part_sum);
           sum += part_sum;
         }
       }
@@ -469,8 +474,8 @@ TileForm tile_form(long long patches, int c, int n, int stride) {
   const int groups = n / 64;
   TileForm best{};
   best.us = 1e30;
-  for (int tm = 1; tm <= 2 && tm * c <= 1024; ++tm)
-    for (int wk = 1; wk <= (tm == 1 ? 4 : 1) && c % (64 * wk) == 0; wk *= 2)
+  for (int tm = c % 64 == 0 ? 1 : 2; tm <= 2 && tm * c <= 1024; ++tm)  // (k-steps of a part are taken four at a time, or two with tm = 2)
+    for (int wk = 1; wk <= (tm == 1 ? 4 : 1) && (wk == 1 || c % (64 * wk) == 0); wk *= 2)
       for (int most = 8 / wk; most > 0; most /= 2) {
         const int waves_n = divisor(groups, most), waves = waves_n * wk;
         const long long blocks = (patches + 4 * tm - 1) / (4 * tm) * (groups / waves_n);
@@ -493,7 +498,7 @@ bool separable_tile_supported(int batch, int h, int w, int c, int n, int stride,
   for (const void* p : ptrs) aligned = aligned && reinterpret_cast<uintptr_t>(p) % 16 == 0;
   const long long patches = (long long)batch * ((oh + 1) / 2) * ((ow + 3) / 4), x_bytes = (long long)batch * h * w * c * 4,
                   y_bytes = (long long)batch * oh * ow * n * 4;
-  return aligned && (stride == 1 || stride == 2) && c % 64 == 0 && c <= 1024 && n % 64 == 0 && n <= 1024 &&
+  return aligned && (stride == 1 || stride == 2) && c >= 64 && (c % 64 == 0 ? c <= 1024 : c % 32 == 0 && c <= 512) && n % 64 == 0 && n <= 1024 &&
          x_bytes < (1ll << 31) && y_bytes < (1ll << 31) && patches < (1ll << 27) && h < 65536 && w < 65536;
 }
 

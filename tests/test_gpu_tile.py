@@ -77,3 +77,29 @@ def test_one_weight_off_16_bytes_changes_one_block():
     assert_close(host(got[1]), host(want[1]), "logits")
     ratio = time_ratio(lambda m: m.forward(image), model, other)
     assert ratio < 1.15, ratio
+
+
+@pytest.mark.parametrize("size,batch", [(224, 20), (231, 25)])
+def test_tile_block_of_96_channels(size, batch):
+    """Six k-steps; columns of small values, whose results are computed again: one of a wavefront's 64 (a sum over its lanes, of which
+    half have a second channel), and all of them."""
+    import paper_1901_05350_amd as tfx
+    d = inputs.mobilenet_v1(seed=79, batch=2, image_size=size, width_quarters=3)
+    w, b = d["weights"], 3
+    w["dw_w"][b][:, :, 5], w["dw_b"][b][5] = 0, 0
+    cols = {3: -40, **{i: -50 for i in range(64, 128)}}
+    for col, scale in cols.items():
+        w["pw_w"][b][0, 0, :, col] = np.abs(w["pw_w"][b][0, 0, :, col]) * 2.0 ** scale
+        w["pw_w"][b][0, 0, 5, col] = 0.25
+        w["pw_b"][b][col] = 0
+    image = np.concatenate([d["image"]] * (batch // 2) + [d["image"][:batch % 2]])
+    got = host(tfx.MobileNetV1(w, batch=batch, image_size=size, width_quarters=3).features(dev(image), b + 1)).astype(np.float64)
+    one = tfx.MobileNetV1(w, batch=1, image_size=size, width_quarters=3)
+    for i in (0, 1):
+        ref = host(one.features(dev(d["image"][i:i + 1]), b + 1)).astype(np.float64)
+        assert all((ref[..., col] != 0).any() for col in cols)  # (positive weights)
+        for j in range(i, batch, 2):
+            assert_close(got[j:j + 1], ref, "image %d" % j)
+            for col, scale in cols.items():
+                # 96 roundings of 24 bits on either side, of terms of up to 6 x 1
+                assert np.all(np.abs(got[j, ..., col] - ref[0, ..., col]) <= 2 * 96 * 2.0 ** -24 * 6 * 2.0 ** scale), col
