@@ -103,3 +103,25 @@ def test_tile_block_of_96_channels(size, batch):
             for col, scale in cols.items():
                 # 96 roundings of 24 bits on either side, of terms of up to 6 x 1
                 assert np.all(np.abs(got[j, ..., col] - ref[0, ..., col]) <= 2 * 96 * 2.0 ** -24 * 6 * 2.0 ** scale), col
+
+
+@pytest.mark.parametrize("q,batch,block", [(4, 8, 8), (4, 64, 8), (4, 64, 13), (3, 24, 4), (2, 64, 9), (4, 16, 4)])
+def test_one_term_keeps_22_bits(q, batch, block):
+    """A block that moves channels about, times powers of two: what is left of a value of 24 bits in two halves, the first of 11 bits and
+    the second of 11 of the 12 that a remainder can have: half a unit of the second, 2^-23, and the rounding of the result."""
+    import paper_1901_05350_amd as tfx
+    d = inputs.mobilenet_v1(seed=76, batch=2, width_quarters=q)
+    w, b = d["weights"], block - 1
+    n, stride = w["pw_w"][b].shape[3], 2 if block in (2, 4, 6, 12) else 1
+    c = w["pw_w"][b].shape[2]
+    rng = np.random.default_rng(block)
+    row, power = rng.integers(0, c, n), 2.0 ** rng.integers(-9, 1, n)
+    w["dw_w"][b][:], w["dw_b"][b][:], w["pw_w"][b][:], w["pw_b"][b][:] = 0, 0, 0, 0
+    w["dw_w"][b][1 if stride == 1 else 0, 1 if stride == 1 else 0] = 1  # the value itself; at stride 2 SAME pads behind the map only
+    w["pw_w"][b][0, 0, row, np.arange(n)] = power
+    image = np.concatenate([d["image"]] * (batch // 2))
+    model = tfx.MobileNetV1(w, batch=batch, width_quarters=q)
+    x = host(model.features(dev(image), block - 1)).astype(np.float64)[:, ::stride, ::stride]
+    got = host(model.features(dev(image), block)).astype(np.float64)
+    want = x[..., row] * power
+    assert (want > 0).any() and np.all(np.abs(got - want) <= 1.5 * 2.0 ** -23 * want)
