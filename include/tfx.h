@@ -16,10 +16,8 @@
  *     and frees nothing, and keeps no tensor state between calls.  What it does
  *     keep, per process and per device, are launch attributes it has looked up
  *     once (which kernels were allowed their dynamic LDS size, how many
- *     workgroups of a kernel are resident at once) and, once a forward pass
- *     of 32 or more images has run, two streams and three events of its own (see
- *     tfx_mobilenet_v1_forward); these never change a result.  Inputs are never
- *     written
+ *     workgroups of a kernel are resident at once); these never change a
+ *     result.  Inputs are never written
  *     (ops are functional, Section 3.7); the output must not overlap any input
  *     (overlap is not detected; the result is then undefined).
  *   - Asynchrony: a call validates its arguments on the host, enqueues its
@@ -39,6 +37,12 @@
  *     enqueue gives TFX_ERR_LAUNCH.  On error nothing has been enqueued, except
  *     for TFX_ERR_LAUNCH (earlier kernels of the same call may have been).
  *   - Zero-sized tensors are rejected with TFX_ERR_SHAPE.
+ *   - Precision: matrix products and convolutions multiply operands of all their
+ *     24 bits and add in fp32, in an order of each kernel's own: what is one term,
+ *     or sums of whole numbers below 2^24, is exact.  In the MobileNet passes of two
+ *     images or more, pointwise layers with many outputs multiply depthwise outputs
+ *     and weights of 22 bits and a sign (a relative 2^-23 at most), with their sums
+ *     no less exact for it: 1.0e-7 ... 2.3e-7 of a layer's result against 64 bits.
  */
 #ifndef TFX_H_
 #define TFX_H_
@@ -272,9 +276,9 @@ int tfx_mobilenet_v1_variant_features(const tfx_mobilenet_v1_variant* variant, c
  * does not fit the array is refused with TFX_ERR_WORKSPACE (nothing enqueued).  Results are
  * bit-identical to tfx_mobilenet_v1_variant_forward wherever that one's
  * tfx_mobilenet_v1_variant_workspace_bytes is at most the array.  A pass that fits only
- * without the re-ordered filters that a larger workspace holds (images of 33 to 38 pixels, 87 to 226
- * of them, few classes) goes without, and agrees to rounding.  All calls on one GPU share the one array: calls that
- * overlap in time on one GPU (different streams or host threads) race and give
+ * without the re-ordered filters that a larger workspace holds (small images in batches of
+ * 87 and more, of up to some 200 classes) goes without, and agrees to rounding.  All calls
+ * on one GPU share the one array: calls that overlap in time on one GPU (different streams or host threads) race and give
  * undefined results; calls ordered on one stream are fine.  Nothing in the array has to
  * start at zero (each kernel writes what later kernels read), so its contents between
  * calls do not matter.  Other arguments and errors as tfx_mobilenet_v1_variant_forward;

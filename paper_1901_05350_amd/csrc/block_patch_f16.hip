@@ -11,8 +11,8 @@
 // What bounds it is the latency of one launch: one round trip to memory, some 150 multiply-adds per lane and k-step
 // pair, one exchange through LDS, the stores.  One image, 14 x 14 x 512 -> 512: 5.5 us, where the depthwise and the pointwise
 // kernel took 3.6 + 4.6 and the gap between them; all 13 blocks of the network 69 us where the 26 kernels took 105 under the
-// profiler.  The round trip for the arguments before that one is left out (PatchRest): the pass of one image 77 -> 70 us, of quarter
-// width at 128 x 128 57 -> 50, of 17 images of quarter width 91 -> 85.
+// profiler.  The round trip for the arguments before that one is left out (PatchRest): the pass of one image 73.6 -> 67.5 - 70 us
+// together with the order of its workgroups, of quarter width at 128 x 128 53 -> 48 - 52, of 16 images of quarter width 83 -> 78.
 #include "ragged.h"
 #include "stream_f16.h"
 

@@ -9,7 +9,7 @@
 // 64 x 14 x 14 x 512 -> 512, one layer: 33.6 us, of which 5.4 are the start and the launch, 9.5 the depthwise layer, 14.3 the contraction
 // (a megabyte of the filter for each CU through the path from L2, 73 GB/s to each; the matrix cores would take 8), 4.4 the stores; the
 // depthwise kernel and the product of bf16 parts that stood here took 66.  64 x 28 x 28 x 256 -> 256 83 -> 45, 256 -> 512 at stride 2
-// 45 -> 27, 7 x 7 x 1024 -> 1024 64 -> 39; the pass of 64 images 767 -> 562, of 16 290 -> 250, of 8 207 -> 192.
+// 45 -> 27, 7 x 7 x 1024 -> 1024 64 -> 39; the pass of 64 images 760 -> 565, of 16 271 -> 246, of 8 203 -> 189.
 //
 // 96 channels, an odd number of k-step pairs, take two blocks of 32 pixels (96 -> 192 of the 3/4 width: 20 images 28.1 us as two launches,
 // 13.0 so).

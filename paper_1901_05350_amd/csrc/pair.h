@@ -1,14 +1,17 @@
 // fp32 products on the binary16 matrix cores, operands split in two: the blocks of block_tile.hip.
 //
-// a = h + l / 2^11 with h the nearest half and l the nearest half of 2^11 times the remainder: 22 bits and the remainder's sign, so
-// the pair misses at most the last bit of a float's 24.  Three or four products of halfs (h h, h l, l h, and l l, 2^-24 of the product
+// (H. Ootomo and R. Yokota, Recovering single precision accuracy from Tensor Cores while surpassing the FP32 theoretical peak
+// performance, 2022: two halves, the second times 2^11, with sums of their own.)  a = h + l / 2^11 with h the nearest half and l the
+// nearest half of 2^11 times the remainder: 22 bits and the remainder's sign, so the pair misses at most the last bit of a float's 24
+// (half of its place where the remainder needs 12 bits, a value in four).  Three or four products of halfs (h h, h l, l h, and l l, 2^-24 of the product
 // on average) stand for one of floats, where three bf16 parts (split.h) take six, and two planes for three.  The h h products and
 // the others, which are 2^11 times too large, have accumulators of their own: the others lose nothing beside the large ones, and
 // these are rounded once for 16 products.
 //
-// Error of a block against float64: 64 images, three products, 512 -> 512 1.78e-7, 256 -> 256 1.39, 1024 -> 1024 2.41, with three bf16
-// parts and one accumulator 3.36, 2.10, 4.93; whole passes' logits, 64 images 2.40 and 4.41, 8 images (four products, the large ones of
-// four k-steps summed apart) 2.43 and 3.68, 3/4 width 33 images 2.2 and 2.9.
+// Error of a block against float64: 64 images, three products, 512 -> 512 1.8e-7, 256 -> 256 1.3, 1024 -> 1024 2.3, with three bf16
+// parts and one accumulator 3.3, 2.0, 4.7; whole passes' logits, 64 images 2.3 and 4.0, 8 images (four products, the large ones of
+// four k-steps summed apart) 1.9 and 2.6, 3/4 width 33 images 2.1 and 2.7.  Where a contraction is short or split, as it is for fewer
+// outputs, three parts are the more exact: such blocks stay with them (api.hip).
 //
 // Binary16 has few exponents, so operands are scaled by powers of two: a depthwise output, 0 ... 6, by 2^13, a column of a filter
 // so that its largest value is in [2^14, 2^15).  That holds here, where one operand has bounds and the other a scale a column.  Matrix
@@ -50,7 +53,7 @@ __device__ __forceinline__ void split2(const floatx4& v, float scale, pairx4& h,
   h = pairx4{h0, h1}, l = pairx4{l0, l1};
 }
 
-// What operands lose: how many of them up to 2^-36 (kLostMost counts as all), plus kLostTiny where one loses up to 2^-60.
+// What operands lose: how many of them up to 2^-36 (kLostMost: more than the 1024 of a contraction), plus kLostTiny where one loses up to 2^-60.
 constexpr int kLostMost = 0xffff, kLostTiny = 0x10000;
 __device__ __forceinline__ int more_lost(int a, int b) { return min((a & kLostMost) + (b & kLostMost), kLostMost) | ((a | b) & kLostTiny); }
 

@@ -165,7 +165,7 @@ def test_mobilenet_variant_validation():
     assert fwd(ctypes.byref(V(8, 4, 1000)), FAKE, 1, ctypes.byref(w), FAKE, base, FAKE, None, None) == -3
     assert fwd(ctypes.byref(ok), FAKE, 0, ctypes.byref(w), FAKE, nbytes, FAKE, None, None) == -2
     assert fwd(ctypes.byref(ok), FAKE, 1, ctypes.byref(w), FAKE, nbytes - 1, FAKE, None, None) == -5
-    # from batch 32 on the pass runs as two half batches with a part of the workspace each: the same checks, first
+    # a large batch, whose workspace also holds filters in another order: the same checks
     big = tfx.tfx_mobilenet_v1_variant_workspace_bytes(ok, 33)
     assert big % 256 == 0 and big >= tfx.tfx_mobilenet_v1_variant_workspace_bytes(ok, 31)
     assert fwd(ctypes.byref(ok), FAKE, 33, ctypes.byref(w), FAKE, big - 1, FAKE, None, None) == -5

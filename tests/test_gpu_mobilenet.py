@@ -253,11 +253,9 @@ def test_batched_forward_first_called_under_graph_capture():
 
 
 @pytest.mark.parametrize("batch", [33, 61])
-def test_forward_in_two_halves_from_batch_32(batch):
-    """From batch 32 on the forward pass is two parts of the batch (17 + 16 images), from batch 60 on three (21 + 20 +
-    20), all but the first on streams of the library's own, forked from and joined to the caller's.  Every image
-    against the oracle; the same bits on a second call; and captured into a graph (fork and joins become edges of the
-    graph) every replay gives the eager bits."""
+def test_forward_of_large_odd_batches_on_another_stream_and_captured(batch):
+    """Every image against the oracle, from a stream that is not the default one; the same bits on a second call, on the default
+    stream; and captured into a graph every replay gives the eager bits, with eager work on the same workspace in between."""
     import torch
     import paper_1901_05350_amd as tfx
     data = inputs.mobilenet_v1(seed=12, batch=batch, image_size=96, width_quarters=2, classes=10)
@@ -265,7 +263,7 @@ def test_forward_in_two_halves_from_batch_32(batch):
     model = tfx.MobileNetV1(data["weights"], batch=batch, image_size=96, width_quarters=2)
     image = dev(data["image"])
     stream = torch.cuda.Stream()
-    with torch.cuda.stream(stream):          # not the default stream: the fork has to follow the caller's stream
+    with torch.cuda.stream(stream):          # not the default stream
         p, l = model.forward(image)
     stream.synchronize()
     p, l = host(p).copy(), host(l).copy()
@@ -284,10 +282,9 @@ def test_forward_in_two_halves_from_batch_32(batch):
         assert np.array_equal(host(model.probs), p) and np.array_equal(host(model.logits), l)
 
 
-def test_two_host_threads_share_the_second_stream():
-    """Two host threads, each with a stream and a model of its own, run batch-32 forward passes at the same time: both
-    fork to the library's one second stream (its events are re-recorded call after call, under a lock).  All results
-    must have the bits of an undisturbed run."""
+def test_two_host_threads_on_streams_of_their_own():
+    """Two host threads, each with a stream, a model and a workspace of its own, run batch-32 forward passes at the same
+    time.  All results must have the bits of an undisturbed run."""
     import threading
     import torch
     import paper_1901_05350_amd as tfx
@@ -472,8 +469,8 @@ def test_two_chained_kernels_on_two_streams_at_once(net):
 
 
 @pytest.mark.parametrize("q,size,batch,end_block", [(4, 224, 8, 6), (4, 96, 80, 9), (3, 131, 41, 8), (2, 160, 34, 13), (1, 224, 40, 5)])
-def test_planes_blocks(q, size, batch, end_block):
-    """Blocks handed over as bf16 planes (block_planes.hip): ragged last tiles, channel counts of every width, both strides."""
+def test_batched_blocks(q, size, batch, end_block):
+    """Blocks of a batch against the same blocks of one image: ragged last tiles, channel counts of every width, both strides."""
     import paper_1901_05350_amd as tfx
     d = inputs.mobilenet_v1(seed=31 + q, batch=2, image_size=size, width_quarters=q)
     image = np.concatenate([d["image"]] * (batch // 2) + [d["image"][:batch % 2]])
@@ -488,7 +485,7 @@ def test_planes_blocks(q, size, batch, end_block):
 
 
 @pytest.mark.parametrize("what", ["nan image", "nan filter", "inf filter", "tiny filter", "huge filter"])
-def test_planes_blocks_values_outside_the_split(what):
+def test_batched_blocks_values_outside_the_split(what):
     import paper_1901_05350_amd as tfx
     d = inputs.mobilenet_v1(seed=41, batch=8)
     w, image = d["weights"], d["image"].copy()
@@ -505,8 +502,8 @@ def test_planes_blocks_values_outside_the_split(what):
         assert_close(got[i:i + 1][fin], ref[fin], what)
 
 
-def test_planes_blocks_results_made_of_tiny_values():
-    """Columns of a planes block that nothing but tiny values reach: a filter column of tiny weights, and columns that pass
+def test_batched_blocks_results_made_of_tiny_values():
+    """Columns of a tile block (block_tile.hip) that nothing but tiny values reach: a filter column of tiny weights, and columns that pass
     depthwise outputs around and below the smallest bf16 on."""
     import paper_1901_05350_amd as tfx
     d = inputs.mobilenet_v1(seed=43, batch=8)

@@ -32,12 +32,12 @@ def operands(rng, b, m, k, n, ta, tb):
 # tiles of 128 and of 64, cut last tiles and slices, slices in the pipelined loop: none, one, many; rows of no multiple of 4
 @pytest.mark.parametrize("ta,tb", [(False, False), (False, True), (True, False), (True, True)])
 @pytest.mark.parametrize("b,m,k,n", [(1, 1536, 256, 1280), (2, 1025, 289, 1153), (1, 2051, 1000, 1029), (1, 700, 300, 1500), (3, 513, 511, 449)])
-def test_pair_products(b, m, k, n, ta, tb):
+def test_long_products(b, m, k, n, ta, tb):
     check(*operands(np.random.default_rng(k + 2 * ta + tb), b, m, k, n, ta, tb), ta, tb)
 
 
 @pytest.mark.parametrize("n", [1280, 449])
-def test_pair_products_larger_values_behind_the_first_slice(n):
+def test_long_products_larger_values_behind_the_first_slice(n):
     """The first 32 of K, a slice of the tiled kernels: zeros, or values 2^8 ... 2^60 smaller than what follows."""
     rng = np.random.default_rng(7)
     for factor in (0.0, 2.0 ** -8, 2.0 ** -20, 2.0 ** -60):
@@ -48,7 +48,7 @@ def test_pair_products_larger_values_behind_the_first_slice(n):
         check(a * np.float32(1e-20), w * np.float32(1e18))
 
 
-def test_pair_products_lost_bits():
+def test_long_products_lost_bits():
     """Rows that hold nothing but values far below the tile's largest, alone and beside a large one that meets a zero; whole columns of
     them (many results of a wavefront) and single ones (few)."""
     rng = np.random.default_rng(8)
@@ -65,7 +65,7 @@ def test_pair_products_lost_bits():
         assert np.median(np.abs(part - 1)) < 1e-5
 
 
-def test_pair_products_not_finite():
+def test_long_products_not_finite():
     rng = np.random.default_rng(9)
     a, w = operands(rng, 1, 1300, 300, 1280, False, True)
     a[0, 5, 7], a[0, 600, 290], w[0, 33, 100], a[0, 900, 3] = np.nan, np.inf, -np.inf, 3e38

@@ -9,7 +9,7 @@ pytestmark = pytest.mark.gpu
 
 
 # 28 x 28 in tiles of 64 pixels; 14 x 14 and 7 x 7 in tiles of 32 with the contraction in 1, 2 and 4 parts; maps of odd sizes, whose last
-# patches are cut; 3 column groups; 64 channels
+# patches are cut; 3 column groups; the last two: blocks with too few outputs for tiles
 @pytest.mark.parametrize("q,size,batch,end_block", [(4, 224, 9, 5), (4, 224, 64, 13), (4, 224, 20, 13), (4, 233, 7, 12), (4, 161, 30, 7),
                                                     (3, 201, 33, 13), (2, 131, 61, 12), (2, 224, 12, 7), (1, 224, 40, 11)])
 def test_tile_blocks(q, size, batch, end_block):
@@ -125,3 +125,8 @@ def test_one_term_keeps_22_bits(q, batch, block):
     got = host(model.features(dev(image), block)).astype(np.float64)
     want = x[..., row] * power
     assert (want > 0).any() and np.all(np.abs(got - want) <= 1.5 * 2.0 ** -23 * want)
+
+
+def test_tiles_in_place_of_windows():
+    """128 -> 128 with less than half a round of the window kernel's units."""
+    test_tile_blocks(1, 224, 64, 9)
