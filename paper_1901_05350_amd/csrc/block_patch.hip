@@ -43,9 +43,10 @@ struct PatchArgs {
 // the loads are under way.  Patches come first in the grid, padded to a multiple of 8, so that the column slices of a patch are on
 // one XCD and its window in one L2 (column slices first where the filter is larger than the map, as there: 2 images 114.4 us, 110.8 so).
 // us, before and now: 2 images 114.4 -> 110.8, 4 at quarter width and 192 x 192 75 -> 70.5, 16 at half width 161.6 -> 154.5.
-// An XCD then has whole groups of patches, up to one more than another.  Where that puts another workgroup on a CU of the fullest, the
-// column slices come first (bit 29 of `form`), which go to the XCDs evenly, as where all fit into one round only so: 20 patches of
-// 768 -> 768, 12 slices, 21.6 us with patches first and 13.4 so; 18 of 384 -> 384 7.7 and 6.2, of 192 -> 384 7.0 and 6.1.
+// An XCD then has whole groups of patches, up to one more than another.  Where that puts another workgroup on a CU of the fullest, as
+// where all fit into one round only if they are dealt evenly, the grid is not padded and the column slices of a patch go to several XCDs:
+// 20 patches of 768 -> 768, 12 slices, 21.4 us padded and 13.1 so; 18 of 384 -> 384 7.4 and 6.1, of 192 -> 384 6.8 and 5.8.
+// (Column slices first instead, a bit for the kernel to select by: as fast there, and .05 us more in every launch.)
 struct PatchRest {
   const float *pw_w, *pw_b;
   float* y;
@@ -100,9 +101,8 @@ __global__ __launch_bounds__(64 * most_waves(S, JN, ROUNDS)) void separable_patc
   const int wk = (int)(form & 31), wp = (int)(form >> 5 & 7), pt = (int)(form >> 8 & 1), pl = (int)(form >> 9 & 1);
   const int H = (int)(map & 0xffff), W = (int)(map >> 16), C = (int)(channels & 0xffff), N = (int)(channels >> 16);
   const FastDiv row_patches{by_row, form >> 10 & 31, per & 0xffff}, col_patches{by_col, form >> 15 & 31, per >> 16};
-  const int p = wave * (int)(form >> 20 & 511) >> 8, part = wave - p * wk;  // (wave / wk)
-  const bool columns_first = (form >> 29 & 1) != 0;
-  const int n0 = (int)(columns_first ? blockIdx.x : blockIdx.y) * 16 * JN, patch = (int)(columns_first ? blockIdx.y : blockIdx.x) * wp + p;
+  const int p = wave * (int)(form >> 20) >> 8, part = wave - p * wk;  // (wave / wk)
+  const int n0 = (int)blockIdx.y * 16 * JN, patch = (int)blockIdx.x * wp + p;
   const bool live = patch < (int)patches;
   if (patch - p >= (int)patches) return;  // (the grid is padded)
   const int strip = (int)div_by((unsigned)patch, row_patches), image = (int)div_by((unsigned)strip, col_patches);
@@ -293,10 +293,10 @@ int launch_patch(const PatchArgs& args, const PatchForm& f, hipStream_t stream) 
   if (allow_dynamic_lds(reinterpret_cast<const void*>(kern), 160 * 1024, lds_allowed) != TFX_OK) return TFX_ERR_LAUNCH;
   const unsigned slices = (unsigned)((g.N + 16 * JN - 1) / (16 * JN)), groups = (unsigned)((g.patches + f.wp - 1) / f.wp);
   const size_t lds_bytes = patch_region_bytes<S, JN, ROUNDS>() * f.wk * f.wp;
-  const bool columns_first = f.one_round && ((groups + 7) / 8 * slices + 31) / 32 > (groups * slices + 255) / 256;  // (32 CUs of an XCD)
+  const bool crowded = f.one_round && ((groups + 7) / 8 * slices + 31) / 32 > (groups * slices + 255) / 256;  // (32 CUs of an XCD)
   const unsigned form = (unsigned)(f.wk | f.wp << 5 | g.pt << 8 | g.pl << 9) | g.row_patches.shift << 10 | g.col_patches.shift << 15 |
-                        (256u + f.wk - 1) / f.wk << 20 | (columns_first ? 1u << 29 : 0u);
-  const dim3 grid = columns_first ? dim3(slices, groups) : dim3((groups + 7) / 8 * 8, slices);
+                        (256u + f.wk - 1) / f.wk << 20;
+  const dim3 grid(crowded ? groups : (groups + 7) / 8 * 8, slices);
   hipLaunchKernelGGL(kern, grid, dim3(64u * f.wk * f.wp), lds_bytes, stream,
                      g.x, g.dw_w, g.dw_b, g.x_bytes, (unsigned)g.H | (unsigned)g.W << 16, (unsigned)(g.C | g.N << 16), (unsigned)g.patches,
                      g.row_patches.mul, g.col_patches.mul, g.row_patches.d | g.col_patches.d << 16, form,

@@ -49,5 +49,5 @@ def test_sums_of_few_products(q, size, batch, block, chain):
 
 @pytest.mark.parametrize("q,size,batch,blocks", [(3, 192, 2, (6, 7, 11)), (3, 224, 5, (13,)), (3, 60, 20, (7,)), (3, 64, 10, (13,))])
 def test_patches_that_no_eight_xcds_share_evenly(q, size, batch, blocks):
-    """10, 18 or 20 patches, whose column slices come first in the grid."""
+    """10, 18 or 20 patches, whose grid is not padded to a multiple of the XCDs."""
     test_patch_blocks(q, size, batch, blocks)
