@@ -31,21 +31,21 @@ PEAK_HBM = 8.0e12          # B/s
 # source it was measured on, with the digest of that file followed by the shared headers csrc/tfx_internal.h and
 # csrc/stream_f16.h; if any of them has changed since, the entry is reported as null.
 MEASURED_TRAFFIC = {
-    "batch_matmul_8x1024x1024x1024_tB": (100947899, "gemm.hip", "5d58a535bead5c0919e3cc01afc446a3657cb135f771ae87a7bfae029fc98fca"),
-    "pointwise_64x56x56x128_to_128": (206175051, "pointwise.hip", "7e5c1bcfd1229982e7f41a500a0bfd38ab2aeeff9bf358cade01cff3e5a52406"),
-    "conv3x3_64x56x56x64_to_64": (106579440, "conv_window.hip", "de0b22d51e1f330c0870687295643fa64489bfa12f0cc33c0d395bc9fc08e485"),
-    "depthwise_64x112x112x64_s1_cold_rotation": (411139334, "depthwise.hip", "cc502c08b1e3b3898b33c2d563e31644d8339477b156770ad6cbc2048154680d"),
-    "depthwise_64x112x112x64_s2_cold_rotation": (256965092, "depthwise.hip", "cc502c08b1e3b3898b33c2d563e31644d8339477b156770ad6cbc2048154680d"),
-    "batch_matmul_f16_1x4096x4096x4096_tB": (235148849, "gemm_f16.hip", "af10815aa2d5db1b1c0561148c4e8709b435aef63e81befcdc6b1c5ba6231500"),
-    "batch_matmul_f16_8x1024x1024x1024_tB": (50467023, "gemm_f16.hip", "af10815aa2d5db1b1c0561148c4e8709b435aef63e81befcdc6b1c5ba6231500"),
-    "pointwise_f16_64x56x56x128_to_128": (104411297, "pointwise_f16.hip", "6d8323ff08f5693256205b1e4c7549c555ce04d5ca93e1423d0461377d5507fa"),
-    "depthwise_f16_64x112x112x64_s1_cold_rotation": (205680159, "conv_f16.hip", "a69c20ba8f9805727b6005e561a1cd43f6b1273da54d2e6188fc5dbd3db48720"),
-    "depthwise_f16_64x112x112x64_s2_cold_rotation": (128536260, "conv_f16.hip", "a69c20ba8f9805727b6005e561a1cd43f6b1273da54d2e6188fc5dbd3db48720"),
-    "pointwise_f16_64x14x14x512_to_512": (30208887, "pointwise_slab_f16.hip", "e95e6765c8bad74cbea34e43c98f4c508e86f8e956ba166d82db5de42d312186"),
-    "conv3x3_f16_64x56x56x64_to_64": (55029622, "conv_stream_f16.hip", "f643a2f409a369c8e7638811f8a83849b138773964cc8170742c5087ca3f8a24"),
-    "add_f32_64M": (805257849, "elementwise.hip", "ef9ed56f6eb69babf5c46d391b230fe3bad94f86e99637543774e1caf54143be"),
-    "add_f16_64M": (402649930, "elementwise.hip", "ef9ed56f6eb69babf5c46d391b230fe3bad94f86e99637543774e1caf54143be"),
-    "mobilenet_chain_kernel": (121645600, "chain.hip", "7c65965b789492caf84825582f01d07d7a42e2db4bb819caa4292b0f719831a0"),
+    "batch_matmul_8x1024x1024x1024_tB": (100945872, "gemm.hip", "3683a33c69a8c10260b991c68ce64474568e1219594a7a6ca962d11bff60a112"),
+    "pointwise_64x56x56x128_to_128": (206175054, "pointwise.hip", "0786f0fa8f45dfb58d0402e749498f2f40e9cd4a2965ee7c2b262d0337b92530"),
+    "conv3x3_64x56x56x64_to_64": (106588825, "conv_window.hip", "b1cef4db5d94f66e41776d5f1ea1cb2e71d0f4322be361e704751c6cc5b8331b"),
+    "depthwise_64x112x112x64_s1_cold_rotation": (411138451, "depthwise.hip", "69e804e38e8e66e812c813a77a32232f4a47700a9b0cd94645939e940ae0fb0f"),
+    "depthwise_64x112x112x64_s2_cold_rotation": (256964940, "depthwise.hip", "69e804e38e8e66e812c813a77a32232f4a47700a9b0cd94645939e940ae0fb0f"),
+    "batch_matmul_f16_1x4096x4096x4096_tB": (235148909, "gemm_f16.hip", "ac467c0bcfaf1516bd090ea4cc9cb84f9f05f99d8de07cdbc24a50f8782665fc"),
+    "batch_matmul_f16_8x1024x1024x1024_tB": (50826958, "gemm_f16.hip", "ac467c0bcfaf1516bd090ea4cc9cb84f9f05f99d8de07cdbc24a50f8782665fc"),
+    "pointwise_f16_64x56x56x128_to_128": (104208130, "pointwise_f16.hip", "b077a63bffab0a0f92b5673dcb92d54284bf858f5a5102c7ea06f9761064e8eb"),
+    "depthwise_f16_64x112x112x64_s1_cold_rotation": (205680194, "conv_f16.hip", "a267891a7ea2142ea82b78a560a13d1eb27118e53444c2e9187b64a442df0a2c"),
+    "depthwise_f16_64x112x112x64_s2_cold_rotation": (128536811, "conv_f16.hip", "a267891a7ea2142ea82b78a560a13d1eb27118e53444c2e9187b64a442df0a2c"),
+    "pointwise_f16_64x14x14x512_to_512": (30160066, "pointwise_slab_f16.hip", "6e5992d2635a084d114d0721839526dcbcafc29d58f015394ec7465f2f87fd37"),
+    "conv3x3_f16_64x56x56x64_to_64": (55030555, "conv_stream_f16.hip", "334fd69dd3a1d6a572a62d4ec5c7ee42d554c76725c439293e38063cdf0d4562"),
+    "add_f32_64M": (805257910, "elementwise.hip", "89a064c751cfd1cb4a7b88a3fcd0bf1ddd48488fbf09e57d99982c47fe40b7c6"),
+    "add_f16_64M": (402650123, "elementwise.hip", "89a064c751cfd1cb4a7b88a3fcd0bf1ddd48488fbf09e57d99982c47fe40b7c6"),
+    "mobilenet_chain_kernel": (121626407, "chain.hip", "e75852ec1d456949f83b18e983df79955bf4640f56b1ffbbda4e4859f34a541d"),
 }
 
 
