@@ -61,3 +61,29 @@ def test_bias_that_is_not_finite(n, h, co, act):
     size = np.abs(x.reshape(-1, 288)).astype(np.float64) @ np.abs(w[0, 0]).astype(np.float64) + np.abs(b)
     ref = ref if act == 0 else np.clip(ref, 0, np.inf if act == 1 else 6)
     assert np.all(np.abs(got[:, rest] - ref[:, rest]) <= 2 * 289 * 2.0 ** -24 * size[:, rest])  # 289 roundings on either side
+
+
+@pytest.mark.parametrize("act", [0, 1, 2])
+@pytest.mark.parametrize("n,h,co", [(64, 14, 512), (31, 13, 515), (4, 14, 512), (5, 13, 197), (1, 7, 1000)])
+def test_epilogue_of_results_computed_again(n, h, co, act):
+    """NaN and infinities in the image and the filter, columns that nothing but tiny weights reach, single and side by side, and a bias
+    that takes a sum away again."""
+    import paper_1901_05350_amd as tfx
+    rng = np.random.default_rng(7 * co + act)
+    x, w = rng.uniform(-1, 1, (n * h * h, 288)).astype(np.float32), (rng.standard_normal((288, co)) * .08).astype(np.float32)
+    b = rng.standard_normal(co).astype(np.float32)
+    w[:, [2, 90] + list(range(128, 160))] *= np.float32(2.0 ** -118)
+    b[[2, 90] + list(range(128, 160))] = 0
+    b[40] = -np.float32(x[17].astype(np.float64) @ w[:, 40].astype(np.float64))
+    x[5, 7], x[40, 100], w[9, 60] = np.nan, np.inf, -np.inf
+    with np.errstate(all="ignore"):
+        ref = x.astype(np.float64) @ w.astype(np.float64) + b
+    size = np.nan_to_num(np.abs(x.astype(np.float64)), posinf=0) @ np.nan_to_num(np.abs(w.astype(np.float64)), posinf=0) + np.abs(b)
+    ref = ref if act == 0 else np.clip(ref, 0, np.inf if act == 1 else 6)
+    got = host(tfx.tfx_conv2d(dev(x.reshape(n, h, h, 288)), dev(w.reshape(1, 1, 288, co)), dev(b), 1, tfx.PAD_SAME, act)).reshape(-1, co)
+    assert np.array_equal(np.isnan(got), np.isnan(ref))
+    inf = np.isinf(ref)
+    assert np.array_equal(got[inf], ref[inf].astype(np.float32))
+    fin = np.isfinite(ref)
+    assert np.all(np.abs(got[fin] - ref[fin]) <= 2 * 289 * 2.0 ** -24 * size[fin] + 289 * 2.0 ** -149)  # 289 roundings on either side
+    assert (got[:, 2] != 0).any() and (got[:, 128:160] != 0).any()
