@@ -207,7 +207,7 @@ size_t tfx_mobilenet_v1_workspace_bytes(int64_t batch);
  * one kernel each.  At batch 1 and full width blocks 2 - 4 share one launch and the
  * blocks from the sixth on, the pool, the fully connected layer and the softmax run
  * as one kernel; the workgroups of these two kernels hand results to each other
- * through flags in the workspace.  Every wait in them is bounded, and if one ever
+ * through words of the workspace.  Every wait in them is bounded, and if one ever
  * gives up (a workgroup that never got to run) every output of the call is NaN
  * rather than a number computed from unfinished data.
  * input: device [batch,224,224,3]; workspace: device, >= the size above, 256-byte

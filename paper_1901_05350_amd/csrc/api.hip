@@ -508,7 +508,7 @@ int forward_impl(const tfx_mobilenet_v1_variant* variant, const float* input, in
 
   // Batch 1: the blocks from the last 1/8-size map on, the pool, the fully connected layer and the
   // softmax run as one persistent kernel (chain.hip) when every pointer allows its vector loads and 256 of its
-  // workgroups are resident at once on this device; its task flags are cleared by the first kernel of the pass
+  // workgroups are resident at once on this device; what its tasks wait for is prepared by the first kernel of the pass
   // (the stem of launch_conv2d_stem or of launch_stem_block; launch_stem_block_rows clears none).
   bool flags_ok = plan.chain;  // the workspace has the flag region, and the kernels that use it may run
   if (flags_ok) {
@@ -524,6 +524,14 @@ int forward_impl(const tfx_mobilenet_v1_variant* variant, const float* input, in
   const bool head_chain = flags_ok && plan.head && (end_block == 0 || end_block == 4 || end_block == 5);
   bool flags_cleared = false;  // by the first kernel, for the launches that wait for flags
   void* chain_ws = ws + plan.off_chain;
+  ChainClear clear;
+  if (chain || head_chain) {
+    clear = ChainClear{static_cast<int*>(chain_ws), chain_flag_words((int)variant->image_size), block_chain_flag_stride(), nullptr, 0};
+    if (chain) {
+      const ChainFill fill = chain_fill((int)variant->image_size, (int)variant->classes, q, 4, chain_ws);
+      clear.fill = static_cast<uint4*>(fill.at), clear.fill_pieces = (unsigned)(fill.bytes / 16);
+    }
+  }
 
   // stem: 3x3 stride-2 convolution to 32 alpha channels, then the 13 depthwise-separable blocks
   int64_t shape[4] = {batch, variant->image_size, variant->image_size, 3};
@@ -537,21 +545,18 @@ int forward_impl(const tfx_mobilenet_v1_variant* variant, const float* input, in
       stem_block_supported((int)shape[1], (int)shape[2], (int)f0[3], (int)c0, input, weights->conv0_w,
                            weights->conv0_b, weights->dw_w[0], weights->dw_b[0], weights->pw_w[0], weights->pw_b[0],
                            end_block == 1 ? features : buf[0])) {
-    // one image: stem and first block in one launch of patches (block.hip), which also clears the chain's task flags
+    // one image: stem and first block in one launch of patches (block.hip), which also prepares what later launches wait for
     rc = launch_stem_block(input, weights->conv0_w, weights->conv0_b, weights->dw_w[0], weights->dw_b[0],
                            weights->pw_w[0], weights->pw_b[0], end_block == 1 ? features : buf[0], (int)shape[1],
                            (int)shape[2], (int)g.out[1],
                            (int)g.out[2], (int)g.pad[0], (int)g.pad[2], (int)c0, TFX_ACT_RELU6,
-                           static_cast<hipStream_t>(stream), chain || head_chain ? static_cast<int*>(chain_ws) : nullptr,
-                           chain || head_chain ? chain_flag_words((int)variant->image_size, (int)variant->classes, q) : 0,
-                           chain_flag_stride());
+                           static_cast<hipStream_t>(stream), chain || head_chain ? clear : ChainClear());
     first_block = 1;
     flags_cleared = chain || head_chain;
   } else if (chain) {
     rc = launch_conv2d_stem(input, weights->conv0_w, weights->conv0_b, buf[0], 1, (int)shape[1], (int)shape[2],
                             (int)f0[3], (int)g.out[1], (int)g.out[2], 2, 2, (int)g.pad[0], (int)g.pad[2], TFX_ACT_RELU6,
-                            static_cast<hipStream_t>(stream), static_cast<int*>(chain_ws),
-                            chain_flag_words((int)variant->image_size, (int)variant->classes, q), chain_flag_stride());
+                            static_cast<hipStream_t>(stream), clear);
     flags_cleared = true;
   } else {
     // stem and first block in one launch that walks down rows (block_rows.hip)
@@ -565,7 +570,6 @@ int forward_impl(const tfx_mobilenet_v1_variant* variant, const float* input, in
   if (first_block == 1) shape[3] = c0;
   if (first_block == 1 && end_block == 1) return TFX_OK;
   int cur = 0;
-  const int head_flags = block_chain_flag_words((int)shape[1], (int)shape[2]);
   if (head_chain && flags_cleared && first_block == 1) {
     // blocks 2 - 4 as three stages of one launch, block 5 as a launch of its own, then the chained kernel from block 6
     // on; flags (cleared by the first kernel) and failure word are shared with it
@@ -589,7 +593,7 @@ int forward_impl(const tfx_mobilenet_v1_variant* variant, const float* input, in
         int flag_base;
         hipStream_t stream;
       } head{buf[0], b2_out, b3_out, b4_out, b5_out, (int)shape[1], (int)shape[2], (int)eighth, with_b5, weights,
-             static_cast<int*>(chain_ws), chain_head_flag_base((int)variant->image_size, (int)variant->classes),
+             static_cast<int*>(chain_ws), 1,
              static_cast<hipStream_t>(stream)};
       auto launch_head = [](void* p) -> int {
         const Head& a = *static_cast<const Head*>(p);
@@ -600,7 +604,7 @@ int forward_impl(const tfx_mobilenet_v1_variant* variant, const float* input, in
                                       256, 256, a.eighth, a.eighth, 1, 1, 1, TFX_ACT_RELU6, TFX_ACT_RELU6, a.stream);
       };
       if (end_block != 0) return launch_ordered(static_cast<hipStream_t>(stream), launch_head, &head);
-      return launch_chain(b5_out, (int)eighth, weights, chain_ws, head_flags, probs, logits, (int)variant->classes, q,
+      return launch_chain(b5_out, (int)variant->image_size, weights, chain_ws, probs, logits, (int)variant->classes, q,
                           static_cast<hipStream_t>(stream), launch_head, &head, 5);
     }
   }
@@ -627,7 +631,7 @@ int forward_impl(const tfx_mobilenet_v1_variant* variant, const float* input, in
   for (int b = first_block; b < blocks; ++b) {
     float* const block_out = end_block == b + 1 ? features : buf[cur ^ 1];
     if (chain && b == 4)
-      return launch_chain(buf[cur], (int)shape[1], weights, chain_ws, head_flags, probs, logits, (int)variant->classes, q,
+      return launch_chain(buf[cur], (int)variant->image_size, weights, chain_ws, probs, logits, (int)variant->classes, q,
                           static_cast<hipStream_t>(stream));
     const int64_t fd[4] = {3, 3, shape[3], 1};
     const int64_t cout = kChannels[b] * q / 4;

@@ -47,8 +47,7 @@ struct BlockArgs {
   const float* st_w;
   const float* st_b;
   int IH, IW, st_pt, st_pl, st_act;
-  int* zero_words;  // optional: zero_count words, zero_stride words apart, cleared by this kernel
-  int zero_count, zero_stride;
+  ChainClear clear;  // optional, by workgroups behind the first `total`
 };
 
 // Hand-over between blocks that run as stages of one launch (separable_chain_kernel): a workgroup's patch x slice
@@ -128,8 +127,6 @@ __device__ __forceinline__ void block_body(const BlockArgs& a, const int bid, fl
     }
     if (tid < 27 * 8) wv = *reinterpret_cast<const float4*>(a.st_w + 4 * tid);
     else if (tid < 28 * 8) wv = *reinterpret_cast<const float4*>(a.st_b + 4 * (tid - 27 * 8));
-    if (a.zero_count > 0)
-      for (int i = bid * NT + tid; i < a.zero_count; i += a.total * NT) a.zero_words[(size_t)i * a.zero_stride] = 0;
   }
   const int wy0 = 4 * ty * S - a.pt, wx0 = 4 * tx * S - a.pl;
   auto load_window = [&]() {
@@ -386,6 +383,8 @@ __global__ __launch_bounds__(64 * WK * WN) void separable_block_kernel(const Blo
   __shared__ __align__(16) float lds[BlockShape<C, WK, WN, CB, S>::kLds];
   __shared__ float img[STEM ? 13 * kImgRow : 1];
   __shared__ __align__(16) float wst[STEM ? 28 * kWstRow : 4];  // [27][32 of 48] filter, [32] bias
+  if constexpr (STEM)
+    if ((int)blockIdx.x >= a.total) return clear_for_chain(a.clear, (blockIdx.x - a.total) * blockDim.x + threadIdx.x, (gridDim.x - a.total) * blockDim.x);
   block_body<C, WK, WN, CB, S, STEM, false, false>(a, blockIdx.x, lds, img, wst, BlockLink{}, nullptr);
 }
 
@@ -421,7 +420,9 @@ int launch_cfg(BlockArgs a, hipStream_t stream) {
   const long long total = (long long)a.batch * a.tiles_img * a.slices;
   if (total > 0x7fffffffLL) return TFX_ERR_UNSUPPORTED;
   a.total = (int)total;
-  hipLaunchKernelGGL((separable_block_kernel<C, WK, WN, CB, S, STEM>), dim3((unsigned)a.total), dim3(64 * WK * WN), 0, stream, a);
+  unsigned grid = (unsigned)a.total;
+  if (STEM) grid += (a.clear.fill_pieces / 4 + (unsigned)a.clear.zero_count + 64 * WK * WN - 1) / (64 * WK * WN);
+  hipLaunchKernelGGL((separable_block_kernel<C, WK, WN, CB, S, STEM>), dim3(grid), dim3(64 * WK * WN), 0, stream, a);
   return check_launch();
 }
 
@@ -450,7 +451,6 @@ int launch_separable_block(const float* x, const float* dw_w, const float* dw_b,
   a.tiles_x = a.tiles_img = a.slices = a.total = 0;
   a.y_img = 0;
   a.st_w = a.st_b = nullptr, a.IH = a.IW = a.st_pt = a.st_pl = a.st_act = 0;
-  a.zero_words = nullptr, a.zero_count = 0, a.zero_stride = 1;
 #define TFX_BLOCK_CASE(CC, WK, WN, CB)                                       \
   if (c == CC && stride == 1) return launch_cfg<CC, WK, WN, CB, 1>(a, stream); \
   if (c == CC && stride == 2) return launch_cfg<CC, WK, WN, CB, 2>(a, stream);
@@ -472,7 +472,7 @@ bool stem_block_supported(int ih, int iw, int stem_filters, int n, const void* i
 
 int launch_stem_block(const float* image, const float* st_w, const float* st_b, const float* dw_w, const float* dw_b,
                       const float* pw_w, const float* pw_b, float* y, int ih, int iw, int h, int w, int st_pt,
-                      int st_pl, int n, int act, hipStream_t stream, int* zero_words, int zero_count, int zero_stride) {
+                      int st_pl, int n, int act, hipStream_t stream, const ChainClear& clear) {
   BlockArgs a;
   a.x = image, a.dw_w = dw_w, a.dw_b = dw_b, a.pw_w = pw_w, a.pw_b = pw_b, a.y = y;
   // the block: 3x3 stride-1 depthwise layer with SAME padding (one zero row / column before the map), then 32 -> n
@@ -484,7 +484,7 @@ int launch_stem_block(const float* image, const float* st_w, const float* st_b, 
   a.tiles_x = a.tiles_img = a.slices = a.total = 0;
   a.y_img = 0;
   a.st_w = st_w, a.st_b = st_b, a.IH = ih, a.IW = iw, a.st_pt = st_pt, a.st_pl = st_pl, a.st_act = act;
-  a.zero_words = zero_words, a.zero_count = zero_count, a.zero_stride = zero_stride;
+  a.clear = clear;
   return launch_cfg<32, 2, 2, 2, 1, true>(a, stream);
 }
 
@@ -508,7 +508,6 @@ BlockArgs plain_args(const float* x, const float* dw_w, const float* dw_b, const
   a.total = a.tiles_img * a.slices;
   a.y_img = (long long)a.OH * a.OW * n;
   a.st_w = a.st_b = nullptr, a.IH = a.IW = a.st_pt = a.st_pl = a.st_act = 0;
-  a.zero_words = nullptr, a.zero_count = 0, a.zero_stride = 1;
   return a;
 }
 }  // namespace

@@ -9,22 +9,23 @@
 //   pointwise task  = a 16-row x 16*TN-column tile of the pixel x channel GEMM, K split over the
 //                     8 wavefronts, operands loaded straight into MFMA registers (the scheme of
 //                     gemm_m16_direct_kernel), partial tiles added through LDS,
-//   pool + fully connected task = 32 input channels x 128 classes, softmax = one task.
-// There is no grid-wide barrier.  A task waits only for the tasks whose output it reads: every task
-// has a flag word; the producer sets it after its stores have been acknowledged, the consumer polls the
-// (at most a few dozen) flags it needs, one per lane.  Measured on the MI355X, a chain of such steps
-// costs 1.6 us per step against 1.9 us for a kernel boundary in a graph and 2.5 us in a stream, and the
-// per-kernel start-up (argument loads, address set-up, filter fetch) disappears: filters are fetched
-// before the wait.
+//   pool + fully connected task = 128 input channels x 128 classes, softmax = one task.
+// There is no grid-wide barrier, and there are no flags.  Every step's output has memory of its own, which the first kernel of the pass
+// fills with ones (chain_fill); a task writes each word of its output once, never as all ones (a NaN is stored as the one NaN
+// 0x7fc00000), and a reader loads what it needs until no word of it is all ones.  What is read is what is waited for: no
+// acknowledgement of the producer's stores, no barrier and no flag behind them, no second trip to memory behind a flag.  One full-width
+// image of 224 x 224: the whole pass 91.1 us with a flag word for each task, 81.2 without, quarter width at 128 x 128 77.7 and 59.9.
+// A pointwise task polls a word of each depthwise task first and loads its operand then: eight wavefronts' whole operands asked for
+// again and again keep the memory busy (3/4 width at 192 x 192 86.3 us, 83.0 so).  Divisions of a step's critical path
+// come from the host as multiplications (81.0 -> 78.3; quarter width 60.2 -> 55.2).  Tried and slower: filters fetched a step ahead, in
+// front of a wait (loads return in order within a wavefront, so the polls return behind them: 90.4), the two kinds of tasks in
+// workgroups of their own, two to a CU (82 - 90), offsets and filters of the next step computed before this one's wait (83 - 87).
 //
 // Visibility between workgroups on different XCDs (each XCD has its own L2) without cache write-back /
 // invalidate instructions: every activation that one task writes and another reads moves through
 // device-coherent accesses (the sc1 cache policy of agent-scope atomics: stores write through to
-// the memory side, loads do not hit a stale line), as do the flags.  A producer waits for its stores
-// (vmcnt 0), the workgroup meets at a barrier, then one thread sets the flag; a consumer sees the flag,
-// the workgroup meets at a barrier, then loads.  Filters and biases are read-only and use ordinary
-// cached loads.  No location written inside the kernel is written twice (every step has its own
-// output region), so a slow reader can never see a later value.
+// the memory side, loads do not hit a stale line).  Filters and biases are read-only and use ordinary cached loads; they are
+// fetched before the wait.
 //
 // Every wait is bounded: a poll loop gives up after kSpinLimit rounds (seconds), sets a failure word that makes
 // every other wait give up too, and the softmax task then writes NaN to every output, so a workgroup that was
@@ -35,115 +36,24 @@
 #include <cstdlib>
 #include <mutex>
 
-#include "tfx_internal.h"
+#include "ragged.h"
 
 namespace tfx {
 namespace {
 
-constexpr int kComputeThreads = 512;  // 8 wavefronts that compute
-constexpr int kComputeWaves = kComputeThreads / 64;
-constexpr int kChainThreads = kComputeThreads + 64;  // + one helper wavefront: polls flags, sets flags, warms L2
+constexpr int kChainThreads = 512;
+constexpr int kChainWaves = kChainThreads / 64;
 constexpr int kChainGrid = 256;
 constexpr int kChainBlocks = 9;       // at most blocks 5 .. 13 of the network (0-based 4 .. 12)
 constexpr int kFirstChainBlock = 4;   // a launch starts there or one block later (both read a 1/8-size map of 256 channels)
 constexpr int kSpinLimit = 1 << 22;  // polls before a wait gives up (each poll is a memory round trip: seconds)
 constexpr int kFcSliceChannels = 128;  // input channels of the fully connected layer per task (2 to 8 slices)
 constexpr int kFcColBlock = 128;      // classes per fully connected task
-constexpr int kFlagStride = 32;       // words between flags: one flag per 128-byte line.  Flags of neighbouring tasks
-                                      // are set by different CUs at almost the same time; packed into one line their
-                                      // write-throughs queue up behind each other (measured: 1.5 us until the last of
-                                      // 16 is visible, against 0.6 us with a line each)
+constexpr unsigned kEmpty = ~0u;       // a word of the chain's memory that no task has written yet
 constexpr int kSc1 = 16;              // cache-policy operand of the buffer builtins: device-coherent access
 
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-
-struct ChainBlock {
-  const float *dw_w, *dw_b, *pw_w, *pw_b;
-  int in_hw, out_hw, stride, pad;  // square maps; pad = zero rows / columns before the image
-  int cin, cout;
-  int tn;                          // 16-column blocks per pointwise tile
-  int in_tn;                       // the same of the step that produced this block's input
-  unsigned in_off, mid_off, out_off;  // float offsets in the chain workspace: input (0 for the first block, whose
-                                   // input is a buffer of its own), depthwise output, pointwise output
-  int flag_in, flag_mid, flag_out; // first flag of the tasks producing the input (-1: complete before launch),
-                                   // the depthwise output, the pointwise output
-};
-
-struct ChainParams {
-  ChainBlock blk[kChainBlocks];
-  const float* in0;     // input of the first block (written by an earlier kernel)
-  unsigned in0_bytes;
-  float* act;           // chain workspace: every step's output
-  unsigned act_bytes;
-  int* flags;           // word 0: failure; task t's flag is word kFlagStride * t (t >= 1)
-  const float *fc_w, *fc_b;
-  unsigned partial_off; // float offset in act: [feat / 128][classes] partial logits
-  float *probs, *logits;
-  int classes, feat, last_hw;
-  int flag_fc;          // first flag of the fully connected tasks
-  int spin_limit;       // polls before a wait gives up
-  int nblocks;          // blocks in blk[]
-};
-
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* p, unsigned bytes) {
-  // raw buffer (stride 0): an access at or past `bytes` returns 0 / is dropped by the hardware
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, 0x00020000);
-}
-__device__ __forceinline__ float ld_f32(__amdgpu_buffer_rsrc_t r, unsigned byte_off) {
-  return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, (int)byte_off, 0, kSc1));
-}
-__device__ __forceinline__ float4 ld_f32x4(__amdgpu_buffer_rsrc_t r, unsigned byte_off) {
-  const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, (int)byte_off, 0, kSc1);
-  return make_float4(__uint_as_float(v.x), __uint_as_float(v.y), __uint_as_float(v.z), __uint_as_float(v.w));
-}
-__device__ __forceinline__ void st_f32(__amdgpu_buffer_rsrc_t r, unsigned byte_off, float v) {
-  __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), r, (int)byte_off, 0, kSc1);
-}
-__device__ __forceinline__ void st_f32x2(__amdgpu_buffer_rsrc_t r, unsigned byte_off, float a, float b) {
-  u32x2 v;
-  v.x = __float_as_uint(a);
-  v.y = __float_as_uint(b);
-  __builtin_amdgcn_raw_buffer_store_b64(v, r, (int)byte_off, 0, kSc1);
-}
-
-__device__ __forceinline__ int flag_load(const int* f) {
-  return __hip_atomic_load(f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ void flag_store(int* f, int v) {
-  __hip_atomic_store(f, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// Wait until the producer tasks (rows r_lo..r_hi) x (columns c_lo..c_hi) of a step with `tiles_n` column tiles
-// have set their flags.  Only the helper wavefront polls, one flag per lane: loads return in order within a
-// wavefront, so a poll issued by a compute wavefront would wait behind that wavefront's filter loads.  Ends with a
-// workgroup barrier.
-__device__ __forceinline__ void wait_tiles(int* flags, int spin_limit, int first, int tiles_n, int r_lo, int r_hi,
-                                           int c_lo, int c_hi) {
-  if (threadIdx.x >= kComputeThreads) {
-    const int nc = c_hi - c_lo + 1, n = (r_hi - r_lo + 1) * nc;
-    for (int i = threadIdx.x - kComputeThreads; i < n; i += 64) {
-      const int* f = flags + (size_t)(first + (r_lo + i / nc) * tiles_n + c_lo + i % nc) * kFlagStride;
-      int spin = 0;
-      while (flag_load(f) == 0) {
-        if (++spin > spin_limit) {
-          flag_store(flags, 1);
-          break;
-        }
-        if ((spin & 255) == 0 && flag_load(flags) != 0) break;
-        __builtin_amdgcn_s_sleep(1);
-      }
-    }
-  }
-  __syncthreads();
-}
-
-// After a task's stores: wait for their acknowledgement, meet, publish.
-__device__ __forceinline__ void publish(int* flags, int index) {
-  __builtin_amdgcn_s_waitcnt(0);  // vmcnt = expcnt = lgkmcnt = 0
-  __syncthreads();
-  if (threadIdx.x == kComputeThreads) flag_store(flags + (size_t)index * kFlagStride, 1);
-}
 
 // Tasks of a step with tiles_m x tiles_c tiles are dealt to workgroups so that a row tile's tasks fall on
 // workgroups with the same id modulo 8, i.e. (workgroups are dealt to the 8 XCDs round robin) on one XCD -- or, with
@@ -152,95 +62,148 @@ __device__ __forceinline__ void publish(int* flags, int index) {
 // owns faster than the memory side does (measured: 1.3 against 1.8 us per dependent step).  Correctness does not
 // depend on where workgroups run.  Workgroup w takes the virtual tasks vt = w, w + 256, ...; vt % 8 is the XCD.
 struct TaskMap {
-  int tiles_m, tiles_c, mode, f, count;
+  int tiles_m, tiles_c, mode, shift, count;
+  FastDiv by_c;  // division by tiles_c
 };
-__device__ __forceinline__ TaskMap make_task_map(int tiles_m, int tiles_c) {
-  TaskMap m;
-  m.tiles_m = tiles_m;
-  m.tiles_c = tiles_c;
+TaskMap make_task_map(int tiles_m, int tiles_c) {
+  TaskMap m{tiles_m, tiles_c, 2, 0, tiles_m * tiles_c, fast_div((unsigned)tiles_c)};  // mode 2: plain order
   if (tiles_m >= 8) {
-    m.mode = 0, m.f = 1, m.count = 8 * ((tiles_m + 7) / 8) * tiles_c;  // vt = r % 8 + 8 ((r / 8) tiles_c + c)
+    m.mode = 0, m.count = 8 * ((tiles_m + 7) / 8) * tiles_c;  // vt = r % 8 + 8 ((r / 8) tiles_c + c)
   } else if (tiles_m == 1 || tiles_m == 2 || tiles_m == 4) {
-    m.mode = 1, m.f = 8 / tiles_m, m.count = 8 * ((tiles_c + m.f - 1) / m.f);  // XCD = r f + c % f, slot = c / f
-  } else {
-    m.mode = 2, m.f = 1, m.count = tiles_m * tiles_c;  // plain order
+    const int f = 8 / tiles_m;  // XCD = r f + c % f, slot = c / f
+    m.mode = 1, m.shift = f == 8 ? 3 : f == 4 ? 2 : 1, m.count = 8 * ((tiles_c + f - 1) / f);
   }
   return m;
 }
 __device__ __forceinline__ bool task_of(const TaskMap& m, int vt, int* r, int* c) {
+  const int u = m.mode == 2 ? vt : vt / 8, by = (int)div_by((unsigned)u, m.by_c), rest = u - by * m.tiles_c;
   if (m.mode == 0) {
-    *r = vt % 8 + 8 * ((vt / 8) / m.tiles_c);
-    *c = (vt / 8) % m.tiles_c;
+    *r = vt % 8 + 8 * by;
+    *c = rest;
   } else if (m.mode == 1) {
-    *r = (vt % 8) / m.f;
-    *c = (vt / 8) * m.f + (vt % 8) % m.f;
+    *r = (vt % 8) >> m.shift;
+    *c = (u << m.shift) + (vt & ((1 << m.shift) - 1));
   } else {
-    *r = vt / m.tiles_c;
-    *c = vt % m.tiles_c;
+    *r = by;
+    *c = rest;
   }
   return *r < m.tiles_m && *c < m.tiles_c;
 }
 
-// ---- depthwise 3x3 + bias + ReLU6: 16 output pixels x 32 channels, one output per compute thread ----
-__device__ __forceinline__ void dw_task(const ChainParams& P, const ChainBlock& B, int r, int c,
+struct ChainBlock {
+  const float *dw_w, *dw_b, *pw_w, *pw_b;
+  int in_hw, out_hw, stride, pad;  // square maps; pad = zero rows / columns before the image
+  int cin, cout;
+  int tn;                          // 16-column blocks per pointwise tile
+  FastDiv by_hw;                   // division by out_hw
+  TaskMap dw_map, pw_map;
+  unsigned in_off, mid_off, out_off;  // float offsets in the chain workspace: input (0 for the first block, whose
+                                   // input is a buffer of its own), depthwise output, pointwise output
+};
+
+struct ChainParams {
+  ChainBlock blk[kChainBlocks];
+  const float* in0;     // input of the first block (written by an earlier kernel)
+  unsigned in0_bytes;
+  float* act;           // chain workspace: every step's output
+  unsigned act_bytes;
+  int* failed;          // a wait has given up
+  const float *fc_w, *fc_b;
+  unsigned partial_off; // float offset in act: [feat / 128][classes] partial logits
+  float *probs, *logits;
+  int classes, feat, last_hw;
+  int spin_limit;       // polls before a wait gives up
+  int nblocks;          // blocks in blk[]
+};
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* p, unsigned bytes) {
+  // raw buffer (stride 0): an access at or past `bytes` returns 0 / is dropped by the hardware
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, 0x00020000);
+}
+__device__ __forceinline__ unsigned ld_word(__amdgpu_buffer_rsrc_t r, unsigned byte_off) {
+  return __builtin_amdgcn_raw_buffer_load_b32(r, (int)byte_off, 0, kSc1);
+}
+__device__ __forceinline__ u32x4 ld_words4(__amdgpu_buffer_rsrc_t r, unsigned byte_off) {
+  return __builtin_amdgcn_raw_buffer_load_b128(r, (int)byte_off, 0, kSc1);
+}
+// (all NaNs become one, which is not kEmpty)
+__device__ __forceinline__ unsigned word_of(float v) { return v == v ? __float_as_uint(v) : 0x7fc00000u; }
+__device__ __forceinline__ void st_f32(__amdgpu_buffer_rsrc_t r, unsigned byte_off, float v) {
+  __builtin_amdgcn_raw_buffer_store_b32(word_of(v), r, (int)byte_off, 0, kSc1);
+}
+__device__ __forceinline__ void st_f32x2(__amdgpu_buffer_rsrc_t r, unsigned byte_off, float a, float b) {
+  __builtin_amdgcn_raw_buffer_store_b64(u32x2{word_of(a), word_of(b)}, r, (int)byte_off, 0, kSc1);
+}
+
+// Runs load(), which fetches what this lane needs and says whether any word of it is still empty, until no lane of the wavefront
+// misses any.  Bounded: a wait that gives up sets the failure word, which ends every other wait soon.
+template <typename F>
+__device__ __forceinline__ void load_written(int* failed, int spin_limit, F load) {
+  int spin = 0;
+  while (__builtin_amdgcn_ballot_w64(load()) != 0) {
+    if (++spin > spin_limit) {
+      __hip_atomic_store(failed, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      break;
+    }
+    if ((spin & 255) == 0 && __hip_atomic_load(failed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) break;
+    asm volatile("" ::: "memory");
+  }
+}
+
+// ---- depthwise 3x3 + bias + ReLU6: 16 output pixels x 32 channels, one output per thread ----
+// wait: the input comes from a task of this launch
+__device__ __forceinline__ void dw_task(const ChainParams& P, const ChainBlock& B, int r, int c, bool wait,
                                         __amdgpu_buffer_rsrc_t in, __amdgpu_buffer_rsrc_t act) {
-  const int tiles_c = B.cin / 32;
   const int m_out = B.out_hw * B.out_hw;
   const int t = threadIdx.x, px = (t / 32) % 16, ch = 32 * c + t % 32;
-  const bool compute = t < kComputeThreads;
   // filter taps and bias first: they do not depend on anybody
   float w[9];
 #pragma unroll
-  for (int k = 0; k < 9; ++k) w[k] = compute ? B.dw_w[k * B.cin + ch] : 0.f;
-  const float bias = compute ? B.dw_b[ch] : 0.f;
+  for (int k = 0; k < 9; ++k) w[k] = B.dw_w[k * B.cin + ch];
+  const float bias = B.dw_b[ch];
 
-  if (B.flag_in >= 0) {
-    // input rows under the 16 output pixels, as whole rows of the input map -> producer row tiles of 16 pixels
-    const int p_lo = 16 * r, p_hi = min(16 * r + 15, m_out - 1);
-    const int iy_lo = max((p_lo / B.out_hw) * B.stride - B.pad, 0);
-    const int iy_hi = min((p_hi / B.out_hw) * B.stride - B.pad + 2, B.in_hw - 1);
-    const int w16 = 16 * B.in_tn;  // channels per producer tile
-    wait_tiles(P.flags, P.spin_limit, B.flag_in, B.cin / w16, iy_lo * B.in_hw / 16, (iy_hi * B.in_hw + B.in_hw - 1) / 16,
-               32 * c / w16, (32 * c + 31) / w16);
-  }
-  if (compute) {
-    const int p = 16 * r + px;
-    const bool live = p < m_out;
-    const int oy = p / B.out_hw, ox = p % B.out_hw;
-    const int iy0 = oy * B.stride - B.pad, ix0 = ox * B.stride - B.pad;
-    float v[9];
-    bool ok[9];
+  const int p = 16 * r + px;
+  const bool live = p < m_out;
+  const int oy = (int)div_by((unsigned)p, B.by_hw), ox = p - oy * B.out_hw;
+  const int iy0 = oy * B.stride - B.pad, ix0 = ox * B.stride - B.pad;
+  float v[9];
+  unsigned off[9];
+  bool ok[9];
 #pragma unroll
-    for (int kh = 0; kh < 3; ++kh)
+  for (int kh = 0; kh < 3; ++kh)
 #pragma unroll
-      for (int kw = 0; kw < 3; ++kw) {
-        const int iy = iy0 + kh, ix = ix0 + kw;
-        ok[kh * 3 + kw] = live && iy >= 0 && iy < B.in_hw && ix >= 0 && ix < B.in_hw;
-        // a tap outside the image reads past the end of the buffer: the hardware returns 0, no branch
-        const unsigned off =
-            ok[kh * 3 + kw] ? (B.in_off + (unsigned)((iy * B.in_hw + ix) * B.cin + ch)) * 4u : 0x80000000u;
-        v[kh * 3 + kw] = ld_f32(in, off);
-      }
-    float acc = bias;
+    for (int kw = 0; kw < 3; ++kw) {
+      const int iy = iy0 + kh, ix = ix0 + kw;
+      ok[kh * 3 + kw] = live && iy >= 0 && iy < B.in_hw && ix >= 0 && ix < B.in_hw;
+      // a tap outside the image reads past the end of the buffer: the hardware returns 0, no branch
+      off[kh * 3 + kw] = ok[kh * 3 + kw] ? (B.in_off + (unsigned)((iy * B.in_hw + ix) * B.cin + ch)) * 4u : 0x80000000u;
+    }
+  load_written(P.failed, P.spin_limit, [&]() __attribute__((always_inline)) {
+    unsigned most = 0;
 #pragma unroll
-    for (int k = 0; k < 9; ++k) acc = ok[k] ? fmaf(v[k], w[k], acc) : acc;
-    ActClamp clamp;
-    clamp.on = true;
-    clamp.hi = 6.0f;
-    if (live) st_f32(act, (B.mid_off + (unsigned)(p * B.cin + ch)) * 4u, apply_act(acc, clamp));
-  }
-  publish(P.flags, B.flag_mid + r * tiles_c + c);
+    for (int k = 0; k < 9; ++k) {
+      const unsigned w1 = ld_word(in, off[k]);
+      v[k] = __uint_as_float(w1), most = max(most, w1);
+    }
+    return wait && most == kEmpty;
+  });
+  float acc = bias;
+#pragma unroll
+  for (int k = 0; k < 9; ++k) acc = ok[k] ? fmaf(v[k], w[k], acc) : acc;
+  ActClamp clamp;
+  clamp.on = true;
+  clamp.hi = 6.0f;
+  if (live) st_f32(act, (B.mid_off + (unsigned)(p * B.cin + ch)) * 4u, apply_act(acc, clamp));
 }
 
-// ---- pointwise 1x1 + bias + ReLU6: 16 x (16 TN) tile, K = WAVES x CHUNK split over the first WAVES compute
+// ---- pointwise 1x1 + bias + ReLU6: 16 x (16 TN) tile, K = WAVES x CHUNK split over the first WAVES 
 // wavefronts (all 8 where K is a multiple of 128; 4 for the K = 64 and K = 192 of the narrower networks) ----
 template <int CHUNK, int TN, int WAVES>
 __device__ __forceinline__ void pw_task(const ChainParams& P, const ChainBlock& B, int tile_m, int tile_n,
                                         __amdgpu_buffer_rsrc_t act, float* red) {
   constexpr int G = CHUNK / 16;
   const int K = B.cin, N = B.cout, M = B.out_hw * B.out_hw;
-  const int tiles_n = N / (16 * TN);
-  const int tid = threadIdx.x, wk = (tid / 64) % kComputeWaves, lane = tid % 64, li = lane % 16, q = lane / 16;
+  const int tid = threadIdx.x, wk = (tid / 64) % kChainWaves, lane = tid % 64, li = lane % 16, q = lane / 16;
   const bool compute = tid < 64 * WAVES;
   const int m0 = 16 * tile_m, n0 = 16 * TN * tile_n;
 
@@ -269,15 +232,23 @@ __device__ __forceinline__ void pw_task(const ChainParams& P, const ChainBlock& 
 #pragma unroll
   for (int j = 0; j < TN; ++j) ebias[j] = tid < 256 ? B.pw_b[ecol + j] : 0.f;
 
-  // the depthwise tasks of this row tile, all channel groups
-  wait_tiles(P.flags, P.spin_limit, B.flag_mid, K / 32, tile_m, tile_m, 0, K / 32 - 1);
-
   if (compute) {
     const int arow = min(m0 + li, M - 1);  // rows past M repeat the last one (they feed outputs that are not stored)
     const unsigned a_off = (B.mid_off + (unsigned)(arow * K + wk * CHUNK + 4 * q)) * 4u;
-    float4 a[G];
+    u32x4 a[G];
+    {  // a word of each depthwise task first: eight wavefronts' whole operands, asked for again and again, keep the memory busy
+      const unsigned last = (B.mid_off + (unsigned)(min(m0 + 15, M - 1) * K + wk * CHUNK + 32 * (li % ((CHUNK + 31) / 32)))) * 4u;
+      load_written(P.failed, P.spin_limit, [&]() __attribute__((always_inline)) { return ld_word(act, last) == kEmpty; });
+    }
+    load_written(P.failed, P.spin_limit, [&]() __attribute__((always_inline)) {
+      unsigned most = 0;
 #pragma unroll
-    for (int g = 0; g < G; ++g) a[g] = ld_f32x4(act, a_off + 64u * g);
+      for (int g = 0; g < G; ++g) {
+        a[g] = ld_words4(act, a_off + 64u * g);
+        most = max(max(max(a[g][0], a[g][1]), max(a[g][2], a[g][3])), most);
+      }
+      return most == kEmpty;
+    });
 
     floatx4 acc[2][TN];
 #pragma unroll
@@ -288,12 +259,11 @@ __device__ __forceinline__ void pw_task(const ChainParams& P, const ChainBlock& 
         for (int v = 0; v < 4; ++v) acc[c][j][v] = 0.f;
 #pragma unroll
     for (int g = 0; g < G; ++g) {
-      const float av[4] = {a[g].x, a[g].y, a[g].z, a[g].w};
 #pragma unroll
       for (int s = 0; s < 4; ++s)
 #pragma unroll
         for (int j = 0; j < TN; ++j)
-          acc[s & 1][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[s], b[g][s][j], acc[s & 1][j], 0, 0, 0);
+          acc[s & 1][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a[g][s]), b[g][s][j], acc[s & 1][j], 0, 0, 0);
     }
 #pragma unroll
     for (int j = 0; j < TN; ++j)
@@ -317,7 +287,6 @@ __device__ __forceinline__ void pw_task(const ChainParams& P, const ChainBlock& 
     if constexpr (TN == 2) st_f32x2(act, off, o[0], o[1]);
     else st_f32(act, off, o[0]);
   }
-  publish(P.flags, B.flag_out + tile_m * tiles_n + tile_n);  // its barrier also protects `red` from the next task's writes
 }
 
 __device__ __forceinline__ float block_sum_or_max(float v, bool is_max, float* scratch) {
@@ -331,7 +300,7 @@ __device__ __forceinline__ float block_sum_or_max(float v, bool is_max, float* s
   __syncthreads();
   float r = scratch[0];
 #pragma unroll
-  for (int i = 1; i < kComputeWaves; ++i) r = is_max ? fmaxf(r, scratch[i]) : r + scratch[i];
+  for (int i = 1; i < kChainWaves; ++i) r = is_max ? fmaxf(r, scratch[i]) : r + scratch[i];
   return r;
 }
 
@@ -352,9 +321,11 @@ __device__ __forceinline__ void pw_task_for(const ChainParams& P, const ChainBlo
 template <int Q>
 __global__ __launch_bounds__(kChainThreads) void mobilenet_chain_kernel(const ChainParams P) {
   constexpr int kSlices = 2 * Q;
-  __shared__ float red[kComputeWaves * 2 * 4 * 64];  // 16 KB: split-K partial tiles; reused by the tail
+  // 2 x 16 KB: split-K partial tiles, of one task and the next (between a task's reads and the writes of the task after the next lies
+  // the barrier of the next); reused by the tail
+  __shared__ float red2[2][kChainWaves * 2 * 4 * 64];
   const int wg = blockIdx.x, tid = threadIdx.x;
-  const bool compute = tid < kComputeThreads;
+  int turn = 0;
   {
     // The block descriptors are read at every block change, on the critical path, and the first touch of a line of
     // the kernel argument segment misses the scalar cache: touch every line now.
@@ -369,7 +340,7 @@ __global__ __launch_bounds__(kChainThreads) void mobilenet_chain_kernel(const Ch
   const __amdgpu_buffer_rsrc_t act = make_rsrc(P.act, P.act_bytes);
 
   // this workgroup's slice of the fully connected weights (128 input channels x 128 classes, 32 values per
-  // compute thread), fetched now: nothing in the kernel depends on it for the next 50 us
+  // thread), fetched now: nothing in the kernel depends on it for the next 50 us
   const int fc_tasks_c = (P.classes + kFcColBlock - 1) / kFcColBlock;
   const int fc_tasks = kSlices * fc_tasks_c;
   constexpr int kper = 128;  // input channels per task, 8 per thread
@@ -393,18 +364,19 @@ __global__ __launch_bounds__(kChainThreads) void mobilenet_chain_kernel(const Ch
       }
     }
   };
-  if (wg < fc_tasks && compute) load_fc(wg, fw);
+  if (wg < fc_tasks) load_fc(wg, fw);
   for (int bi = 0; bi < P.nblocks; ++bi) {
     const ChainBlock& B = P.blk[bi];
-    const int tiles_m = (B.out_hw * B.out_hw + 15) / 16;
-    const TaskMap dw_map = make_task_map(tiles_m, B.cin / 32), pw_map = make_task_map(tiles_m, B.cout / (16 * B.tn));
+    const TaskMap &dw_map = B.dw_map, &pw_map = B.pw_map;
     for (int vt = wg; vt < dw_map.count; vt += kChainGrid) {
       int r, c;
-      if (task_of(dw_map, vt, &r, &c)) dw_task(P, B, r, c, bi == 0 ? in0 : act, act);
+      if (task_of(dw_map, vt, &r, &c)) dw_task(P, B, r, c, bi > 0, bi == 0 ? in0 : act, act);
     }
     for (int vt = wg; vt < pw_map.count; vt += kChainGrid) {
       int r, c;
       if (!task_of(pw_map, vt, &r, &c)) continue;
+      float* const red = red2[turn];
+      turn ^= 1;
       if (B.cin == 64 * Q) pw_task_for<64 * Q>(P, B, r, c, act, red);
       else if (B.cin == 128 * Q) pw_task_for<128 * Q>(P, B, r, c, act, red);
       else pw_task_for<256 * Q>(P, B, r, c, act, red);
@@ -414,25 +386,28 @@ __global__ __launch_bounds__(kChainThreads) void mobilenet_chain_kernel(const Ch
   // ---- average pool + fully connected: task (ks, cb) = 128 input channels x 128 classes ----
   const ChainBlock& L = P.blk[P.nblocks - 1];
   const int hw2 = P.last_hw * P.last_hw;
+  float* const red = red2[0];
+  __syncthreads();
   for (int task = wg; task < fc_tasks; task += kChainGrid) {
     const int ks = task / fc_tasks_c, cb = task % fc_tasks_c;
-    if (task != wg && compute) load_fc(task, fw);
-    // the last pointwise layer's tiles holding channels kper ks .. kper ks + kper - 1, every pixel row tile
-    const int w16 = 16 * L.tn;
-    wait_tiles(P.flags, P.spin_limit, L.flag_out, L.cout / w16, 0, (hw2 + 15) / 16 - 1, kper * ks / w16,
-               (kper * ks + kper - 1) / w16);
+    if (task != wg) load_fc(task, fw);
     float* pooled = red;             // [128]
     float* psum = red + 128;         // [4][128]
     float* fsum = red + 128 + 512;   // [16][128]
-    if (compute) {
+    {
       // thread (pixel group pg of 4, channel chn of 128) sums pixels pg, pg + 4, ... (at most 64 pixels)
       const int chn = tid % 128, pg = tid / 128;
       float x[16];
+      load_written(P.failed, P.spin_limit, [&]() __attribute__((always_inline)) {
+        unsigned most = 0;
 #pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        const int p = pg + 4 * i;
-        x[i] = ld_f32(act, p < hw2 ? (L.out_off + (unsigned)(p * P.feat + kper * ks + chn)) * 4u : 0x80000000u);
-      }
+        for (int i = 0; i < 16; ++i) {
+          const int p = pg + 4 * i;
+          const unsigned word = ld_word(act, p < hw2 ? (L.out_off + (unsigned)(p * P.feat + kper * ks + chn)) * 4u : 0x80000000u);
+          x[i] = __uint_as_float(word), most = max(most, word);
+        }
+        return most == kEmpty;
+      });
       float s = 0.f;
 #pragma unroll
       for (int i = 0; i < 16; ++i) s += x[i];
@@ -441,7 +416,7 @@ __global__ __launch_bounds__(kChainThreads) void mobilenet_chain_kernel(const Ch
     __syncthreads();
     if (tid < 128) pooled[tid] = (psum[tid] + psum[128 + tid] + psum[256 + tid] + psum[384 + tid]) / (float)hw2;
     __syncthreads();
-    if (compute) {
+    {
       const int kq = tid / 32, c4 = tid % 32;
       float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
@@ -462,36 +437,41 @@ __global__ __launch_bounds__(kChainThreads) void mobilenet_chain_kernel(const Ch
       const int col = kFcColBlock * cb + tid;
       if (col < P.classes) st_f32(act, (P.partial_off + (unsigned)(ks * P.classes + col)) * 4u, s);
     }
-    publish(P.flags, P.flag_fc + task);
+    __syncthreads();
   }
 
-  // ---- bias + softmax: one task, two classes per compute thread ----
+  // ---- bias + softmax: one task, two classes per thread ----
   if (wg == 0) {
-    wait_tiles(P.flags, P.spin_limit, P.flag_fc, fc_tasks_c, 0, kSlices - 1, 0, fc_tasks_c - 1);
     float l[2];
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-      const int j = tid + kComputeThreads * h;
-      const bool in = compute && j < P.classes;
+      const int j = tid + kChainThreads * h;
+      const bool in = j < P.classes;
       float part[kSlices];
+      load_written(P.failed, P.spin_limit, [&]() __attribute__((always_inline)) {
+        unsigned most = 0;
 #pragma unroll
-      for (int s = 0; s < kSlices; ++s)
-        part[s] = ld_f32(act, in ? (P.partial_off + (unsigned)(s * P.classes + j)) * 4u : 0x80000000u);
+        for (int s = 0; s < kSlices; ++s) {
+          const unsigned word = ld_word(act, in ? (P.partial_off + (unsigned)(s * P.classes + j)) * 4u : 0x80000000u);
+          part[s] = __uint_as_float(word), most = max(most, word);
+        }
+        return most == kEmpty;
+      });
       float v = in ? P.fc_b[j] : 0.f;
 #pragma unroll
       for (int s = 0; s < kSlices; ++s) v += part[s];
       l[h] = in ? v : -INFINITY;
     }
-    const bool failed = flag_load(P.flags) != 0;
+    const bool failed = __hip_atomic_load(P.failed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
     const float mx = block_sum_or_max(fmaxf(l[0], l[1]), true, red);
     float e[2];
 #pragma unroll
-    for (int h = 0; h < 2; ++h) e[h] = (compute && tid + kComputeThreads * h < P.classes) ? __expf(l[h] - mx) : 0.f;
+    for (int h = 0; h < 2; ++h) e[h] = tid + kChainThreads * h < P.classes ? __expf(l[h] - mx) : 0.f;
     const float sum = block_sum_or_max(e[0] + e[1], false, red + 16);
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-      const int j = tid + kComputeThreads * h;
-      if (compute && j < P.classes) {
+      const int j = tid + kChainThreads * h;
+      if (j < P.classes) {
         const float nan = __uint_as_float(0x7fc00000u);
         if (P.logits) P.logits[j] = failed ? nan : l[h];
         P.probs[j] = failed ? nan : e[h] / sum;
@@ -501,7 +481,6 @@ __global__ __launch_bounds__(kChainThreads) void mobilenet_chain_kernel(const Ch
 }
 
 struct ChainPlanHost {
-  int flags;            // number of flag words
   size_t act_floats;    // chain workspace in floats
 };
 
@@ -548,10 +527,9 @@ constexpr int kNetStrides[13] = {1, 2, 1, 2, 1, 2, 1, 1, 1, 1, 1, 2, 1};
 // Sizes of the chained part for an input map of in_hw x in_hw x 64 q (the output of block 4) at width q / 4.
 ChainPlanHost chain_layout(int in_hw, int classes, int q, ChainParams* P, int first = kFirstChainBlock) {
   ChainPlanHost h{};
-  int flags = 1;  // [0] = failure word
   size_t off = 0;
   const int nblocks = 13 - first;
-  int hw = in_hw, cin = kNetChannels[first - 1] * q / 4, prev_flags = -1, prev_tn = 2;
+  int hw = in_hw, cin = kNetChannels[first - 1] * q / 4;
   size_t prev_out = 0;
   for (int bi = 0; bi < nblocks; ++bi) {
     const int net = first + bi, s = kNetStrides[net], cout = kNetChannels[net] * q / 4;
@@ -563,55 +541,55 @@ ChainPlanHost chain_layout(int in_hw, int classes, int q, ChainParams* P, int fi
     const int tn = (tiles_m * (cout / 32) >= 160 && cin < 1024) ? 2 : 1;
     if (P) {
       ChainBlock& B = P->blk[bi];
-      B.in_hw = hw, B.out_hw = out_hw, B.stride = s, B.pad = pad, B.cin = cin, B.cout = cout, B.tn = tn, B.in_tn = prev_tn;
-      B.flag_in = prev_flags;
-      B.flag_mid = flags;
-      B.flag_out = flags + tiles_m * (cin / 32);
+      B.in_hw = hw, B.out_hw = out_hw, B.stride = s, B.pad = pad, B.cin = cin, B.cout = cout, B.tn = tn;
+      B.by_hw = fast_div((unsigned)out_hw);
+      B.dw_map = make_task_map(tiles_m, cin / 32), B.pw_map = make_task_map(tiles_m, cout / (16 * tn));
       B.in_off = (unsigned)prev_out;
       B.mid_off = (unsigned)off;
       B.out_off = (unsigned)(off + (size_t)m * cin);
     }
     prev_out = off + (size_t)m * cin;
-    prev_flags = flags + tiles_m * (cin / 32);
-    flags = prev_flags + tiles_m * (cout / (16 * tn));
     off += (size_t)m * cin + (size_t)m * cout;
-    hw = out_hw, cin = cout, prev_tn = tn;
+    hw = out_hw, cin = cout;
   }
   const int slices = cin / kFcSliceChannels;
-  const int fc_tasks = slices * ((classes + kFcColBlock - 1) / kFcColBlock);
   if (P) {
-    P->flag_fc = flags;
     P->partial_off = (unsigned)off;
     P->last_hw = hw;
     P->feat = cin;
     P->classes = classes;
     P->nblocks = nblocks;
   }
-  flags += fc_tasks;
   off += (size_t)slices * classes;
-  h.flags = flags;
   h.act_floats = off;
   return h;
 }
 }  // namespace
 
+// The chain's memory: flag words -- the failure word, then those of the launch that runs blocks 2 - 4 as stages (block.hip) --, then
+// every step's output.
+namespace {
+size_t flag_region(int image_size) {
+  const int half = (image_size + 1) / 2;
+  return (size_t)(1 + block_chain_flag_words(half, half)) * block_chain_flag_stride() * sizeof(int);
+}
+int eighth_of(int image_size) {
+  const int half = (image_size + 1) / 2, quarter = (half + 1) / 2;
+  return (quarter + 1) / 2;
+}
+}  // namespace
 size_t chain_workspace_bytes(int image_size, int classes, int width_quarters) {
-  const int half = (image_size + 1) / 2, quarter = (half + 1) / 2, eighth = (quarter + 1) / 2;
-  const ChainPlanHost h = chain_layout(eighth, classes, width_quarters, nullptr);
-  const size_t flag_bytes = (size_t)(h.flags + block_chain_flag_words(half, half)) * kFlagStride * sizeof(int);
-  return flag_bytes + (h.act_floats * sizeof(float) + 255) / 256 * 256;
+  return flag_region(image_size) + chain_fill(image_size, classes, width_quarters, kFirstChainBlock, nullptr).bytes;
 }
-
-// The flags at the start of the chain workspace: `count` words, chain_flag_stride() words apart, that must be zero
-// when the first kernel that uses them starts: the chain kernel's own (word 0 = failure word), then, from
-// chain_head_flag_base() on, those of the launch that runs blocks 2 - 4 as stages (block.hip).
-int chain_flag_words(int image_size, int classes, int width_quarters) {
-  const int half = (image_size + 1) / 2, quarter = (half + 1) / 2, eighth = (quarter + 1) / 2;
-  return chain_layout(eighth, classes, width_quarters, nullptr).flags + block_chain_flag_words(half, half);
+ChainFill chain_fill(int image_size, int classes, int width_quarters, int first_block, void* chain_ws) {
+  // (the memory is laid out for the longer chain; a launch that starts one block later uses a part of it)
+  const ChainPlanHost h = chain_layout(eighth_of(image_size), classes, width_quarters, nullptr, kFirstChainBlock);
+  const ChainPlanHost used = first_block == kFirstChainBlock ? h : chain_layout(eighth_of(image_size), classes, width_quarters, nullptr, first_block);
+  return ChainFill{static_cast<char*>(chain_ws) + flag_region(image_size), (used.act_floats * sizeof(float) + 255) / 256 * 256};
 }
-int chain_head_flag_base(int image_size, int classes) {
-  const int half = (image_size + 1) / 2, quarter = (half + 1) / 2, eighth = (quarter + 1) / 2;
-  return chain_layout(eighth, classes, 4, nullptr).flags;
+int chain_flag_words(int image_size) {
+  const int half = (image_size + 1) / 2;
+  return 1 + block_chain_flag_words(half, half);
 }
 int chain_spin_limit() {
   // Test hook: TFX_CHAIN_SPIN_LIMIT=<n> makes every wait give up after n polls, which exercises the failure
@@ -622,7 +600,6 @@ int chain_spin_limit() {
   }
   return kSpinLimit;
 }
-int chain_flag_stride() { return kFlagStride; }
 
 namespace {
 // Chain kernels of one process are kept from overlapping on a device.  The last stream that launched one is
@@ -667,16 +644,14 @@ int launch_ordered(hipStream_t stream, int (*fn)(void*), void* arg) {
   return fn(arg);
 }
 
-int launch_chain(const float* in0, int in_hw, const tfx_mobilenet_v1_weights* w, void* chain_ws, int head_flags,
+int launch_chain(const float* in0, int image_size, const tfx_mobilenet_v1_weights* w, void* chain_ws,
                  float* probs, float* logits, int classes, int width_quarters, hipStream_t stream, int (*before)(void*),
                  void* before_arg, int first_block) {
   if (first_block != kFirstChainBlock && first_block != kFirstChainBlock + 1) return TFX_ERR_ARG;
   if (width_quarters < 1 || width_quarters > 4) return TFX_ERR_ARG;
   ChainParams P{};
-  // the workspace is laid out for the longer chain; a launch that starts one block later uses a part of it
-  const ChainPlanHost h = chain_layout(in_hw, classes, width_quarters, nullptr);
+  const int in_hw = eighth_of(image_size);
   const ChainPlanHost used = chain_layout(in_hw, classes, width_quarters, &P, first_block);
-  if (used.flags > h.flags || used.act_floats > h.act_floats) return TFX_ERR_LAUNCH;
   for (int bi = 0; bi < P.nblocks; ++bi) {
     const int net = first_block + bi;
     P.blk[bi].dw_w = w->dw_w[net];
@@ -684,12 +659,11 @@ int launch_chain(const float* in0, int in_hw, const tfx_mobilenet_v1_weights* w,
     P.blk[bi].pw_w = w->pw_w[net];
     P.blk[bi].pw_b = w->pw_b[net];
   }
-  const size_t flag_bytes = (size_t)(h.flags + head_flags) * kFlagStride * sizeof(int);
   P.in0 = in0;
   P.in0_bytes = (unsigned)((size_t)in_hw * in_hw * (kNetChannels[first_block - 1] * width_quarters / 4) * sizeof(float));
-  P.flags = static_cast<int*>(chain_ws);
-  P.act = reinterpret_cast<float*>(static_cast<char*>(chain_ws) + flag_bytes);
-  P.act_bytes = (unsigned)(h.act_floats * sizeof(float));
+  P.failed = static_cast<int*>(chain_ws);
+  P.act = static_cast<float*>(chain_fill(image_size, classes, width_quarters, first_block, chain_ws).at);
+  P.act_bytes = (unsigned)(used.act_floats * sizeof(float));
   P.fc_w = w->fc_w;
   P.fc_b = w->fc_b;
   P.probs = probs;

@@ -49,11 +49,8 @@ template <int CO>
 __global__ __launch_bounds__(256) void conv2d_stem_kernel(const float* __restrict__ x, const float* __restrict__ w,
                                                           const float* __restrict__ bias, float* __restrict__ y, int N,
                                                           int H, int W, int OH, int OW, int sh, int sw, int pt, int pl,
-                                                          int act, int total, int* __restrict__ zero_words,
-                                                          int zero_count, int zero_stride) {
-  // optional: clear a small array of words for a later kernel of the same forward pass (its task flags)
-  for (int i = (int)(blockIdx.x * 256 + threadIdx.x); i < zero_count; i += (int)gridDim.x * 256)
-    zero_words[(size_t)i * zero_stride] = 0;
+                                                          int act, int total, ChainClear clear) {
+  clear_for_chain(clear, blockIdx.x * 256 + threadIdx.x, gridDim.x * 256);  // (optional)
   constexpr int G = CO / 8;
   constexpr int WPT = (27 * CO + 255) / 256;  // filter floats staged per thread
   __shared__ __align__(16) float wl[27 * CO];
@@ -144,12 +141,9 @@ template <int CO>
 __global__ __launch_bounds__(256) void conv2d_stem_mfma_kernel(const float* __restrict__ x, const float* __restrict__ w,
                                                                const float* __restrict__ bias, float* __restrict__ y,
                                                                int N, int H, int W, int OH, int OW, int sh, int sw, int pt,
-                                                               int pl, int act, int* __restrict__ zero_words,
-                                                               int zero_count, int zero_stride) {
+                                                               int pl, int act, ChainClear clear) {
   constexpr int NB = CO / 16;
-  // optional: clear a small array of words for a later kernel of the same forward pass (its task flags)
-  for (int i = (int)(blockIdx.x * 256 + threadIdx.x); i < zero_count; i += (int)gridDim.x * 256)
-    zero_words[(size_t)i * zero_stride] = 0;
+  clear_for_chain(clear, blockIdx.x * 256 + threadIdx.x, gridDim.x * 256);  // (optional)
   static_assert(CO % 32 == 0, "column blocks are stored in pairs");
   const int lane = threadIdx.x % 64, li = lane % 16, q = lane / 16;
   const int segs = (OW + 15) / 16;
@@ -250,8 +244,7 @@ bool conv2d_stem_supported(int ci, int fh, int fw, int co, int sh, int sw) {
 }
 
 int launch_conv2d_stem(const float* x, const float* w, const float* bias, float* y, int n, int h, int wd, int co,
-                       int oh, int ow, int sh, int sw, int pt, int pl, int act, hipStream_t stream, int* zero_words,
-                       int zero_count, int zero_stride) {
+                       int oh, int ow, int sh, int sw, int pt, int pl, int act, hipStream_t stream, const ChainClear& clear) {
   // 32 filters, 16-byte aligned y and bias: the matrix-core form
   if (co == 32 && reinterpret_cast<uintptr_t>(y) % 16 == 0 && reinterpret_cast<uintptr_t>(bias) % 16 == 0) {
     const long long slabs = (long long)n * oh * ((ow + 15) / 16);
@@ -259,7 +252,7 @@ int launch_conv2d_stem(const float* x, const float* w, const float* bias, float*
     long long blocks = (slabs + 3) / 4;
     if (blocks > 256 * 8) blocks = 256 * 8;  // 8 workgroups of 4 wavefronts per CU, then the slab loop
     hipLaunchKernelGGL(conv2d_stem_mfma_kernel<32>, dim3((unsigned)blocks), dim3(256), 0, stream, x, w, bias, y, n, h, wd,
-                       oh, ow, sh, sw, pt, pl, act, zero_words, zero_count, zero_stride);
+                       oh, ow, sh, sw, pt, pl, act, clear);
     return check_launch();
   }
   const long long total = (long long)n * oh * ow * (co / 8);
@@ -267,7 +260,7 @@ int launch_conv2d_stem(const float* x, const float* w, const float* bias, float*
   const unsigned blocks = (unsigned)((total + 255) / 256);
 #define TFX_STEM(CO)                                                                                              \
   hipLaunchKernelGGL(conv2d_stem_kernel<CO>, dim3(blocks), dim3(256), 0, stream, x, w, bias, y, n, h, wd, oh, ow, \
-                     sh, sw, pt, pl, act, (int)total, zero_words, zero_count, zero_stride)
+                     sh, sw, pt, pl, act, (int)total, clear)
   switch (co) {
     case 8: TFX_STEM(8); break;
     case 16: TFX_STEM(16); break;

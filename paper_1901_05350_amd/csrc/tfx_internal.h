@@ -195,29 +195,41 @@ int launch_conv2d_direct(const float* x, const float* w, const float* bias, floa
 
 // 3x3 stride-2 convolution with 3 input channels (the MobileNet stem).
 bool conv2d_stem_supported(int ci, int fh, int fw, int co, int sh, int sw);
-// zero_words / zero_count / zero_stride: optional: the kernel also clears zero_count 32-bit words, zero_stride
-// words apart (matrix-core form only: 32 filters, 16-byte aligned y and bias).
+// What the first kernel of a pass prepares for kernels whose workgroups wait for each other: `zero_count` words, zero_stride words
+// apart, to zero (flags), and `fill_pieces` pieces of 16 bytes to ones (memory whose words are empty until they are written).
+struct ChainClear {
+  int* zero_words = nullptr;
+  int zero_count = 0, zero_stride = 1;
+  uint4* fill = nullptr;
+  unsigned fill_pieces = 0;
+};
+__device__ __forceinline__ void clear_for_chain(const ChainClear& c, unsigned thread, unsigned threads) {
+  for (unsigned i = thread; i < (unsigned)c.zero_count; i += threads) c.zero_words[(size_t)i * c.zero_stride] = 0;
+  for (unsigned i = thread; i < c.fill_pieces; i += threads) c.fill[i] = make_uint4(~0u, ~0u, ~0u, ~0u);
+}
+// clear: optional (matrix-core form only: 32 filters, 16-byte aligned y and bias).
 int launch_conv2d_stem(const float* x, const float* w, const float* bias, float* y, int n, int h, int wd, int co,
                        int oh, int ow, int sh, int sw, int pt, int pl, int act, hipStream_t stream,
-                       int* zero_words = nullptr, int zero_count = 0, int zero_stride = 1);
+                       const ChainClear& clear = ChainClear());
 
 // The 28 x 28 ... 7 x 7 blocks, pool, fully connected layer and softmax of the batch-1 network (any of the four
 // widths) as one persistent kernel (chain.hip).  chain_ws: chain_workspace_bytes() bytes, 256-byte aligned; its first
-// chain_flag_words() words at a spacing of chain_flag_stride() words are zero when the kernel starts.  in0: the
-// output of block 4 (in_hw x in_hw x 64 width_quarters).
+// chain_flag_words() words at a spacing of block_chain_flag_stride() words are zero when the kernel starts (the failure word, then the
+// flags of blocks 2 - 4 as stages), and what chain_fill() says is filled with ones.  in0: the output of block 4.
 bool chain_supported(int image_size, int width_quarters, int classes, long long batch);
 bool chain_resident(int width_quarters);
 size_t chain_workspace_bytes(int image_size, int classes, int width_quarters);
-int chain_flag_words(int image_size, int classes, int width_quarters);
-int chain_head_flag_base(int image_size, int classes);  // full width only: where the flags of blocks 2 - 4 as stages begin
-int chain_flag_stride();
+int chain_flag_words(int image_size);
+struct ChainFill {
+  void* at;
+  size_t bytes;
+};
+ChainFill chain_fill(int image_size, int classes, int width_quarters, int first_block, void* chain_ws);
 int chain_spin_limit();
-// head_flags: flag words behind the chain kernel's own at the start of chain_ws (block_chain_flag_words).
 // before(before_arg), if given, enqueues a launch that has to stay directly in front of the chain kernel on `stream`
 // (it is called once the stream has been ordered behind other streams' chain kernels) and returns a tfx_status.
 // first_block: 4 (the chain starts with block 5, in0 = the output of block 4) or 5 (block 6, in0 = output of block 5).
-int launch_chain(const float* in0, int in_hw, const tfx_mobilenet_v1_weights* w, void* chain_ws, int head_flags,
-                 float* probs, float* logits, int classes, int width_quarters, hipStream_t stream,
+int launch_chain(const float* in0, int image_size, const tfx_mobilenet_v1_weights* w, void* chain_ws, float* probs, float* logits, int classes, int width_quarters, hipStream_t stream,
                  int (*before)(void*) = nullptr, void* before_arg = nullptr, int first_block = 4);
 // fn(arg) enqueues a kernel of waiting workgroups on `stream`; the stream is first ordered behind the last such
 // kernel of any other stream (two of them side by side could each hold the CUs the other's producers need).
@@ -244,13 +256,13 @@ int launch_separable_block(const float* x, const float* dw_w, const float* dw_b,
 
 // The stem (3x3 stride-2 convolution of the image [ih, iw, 3] to 32 channels, [h, w, 32]) and the first
 // depthwise-separable block (stride 1, 32 -> n = 64 channels) of one image in one launch; every layer with
-// bias + the activation `act`.  zero_words: as for launch_conv2d_stem.
+// bias + the activation `act`.  clear: as for launch_conv2d_stem.
 bool stem_block_supported(int ih, int iw, int stem_filters, int n, const void* image, const void* st_w,
                           const void* st_b, const void* dw_w, const void* dw_b, const void* pw_w, const void* pw_b,
                           const void* y);
 int launch_stem_block(const float* image, const float* st_w, const float* st_b, const float* dw_w, const float* dw_b,
                       const float* pw_w, const float* pw_b, float* y, int ih, int iw, int h, int w, int st_pt,
-                      int st_pl, int n, int act, hipStream_t stream, int* zero_words, int zero_count, int zero_stride);
+                      int st_pl, int n, int act, hipStream_t stream, const ChainClear& clear);
 
 // Depthwise convolution: generic kernel and the 3x3 / multiplier-1 / C%4==0 fast path.
 int launch_depthwise(const float* x, const float* w, const float* bias, float* y, int n, int h, int wd, int c,
