@@ -174,6 +174,7 @@ __global__ __launch_bounds__(JN == 8 ? 512 : 1024) void separable_patch_f16_kern
       for (int e = 0; e < 8; ++e) d[e / 4][e % 4] = fmaf((float)xt[e], (float)wt[e], d[e / 4][e % 4]);
     }
     h8 a[1];
+    __builtin_amdgcn_sched_barrier(0);  // (else loads move down into the taps, one image 69.1 us instead of 68.4)
     activate_and_pack(d, dw_clamp, a);
 #pragma unroll
     for (int j = 0; j < JN; ++j) {
