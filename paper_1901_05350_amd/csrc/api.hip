@@ -100,7 +100,7 @@ bool valid_variant(const tfx_mobilenet_v1_variant* v) {
 // 4 x 4 patch (block_patch_f16.hip), with the filters stationary in LDS (block_stream_f16.hip: large batch, early block) or
 // with the depthwise output there (block_tile_f16.hip), or as two.  The pointwise filters of the tile form are put in its
 // order by one launch in front, for which one or two such blocks do not pay.  (All operands are taken to be aligned.)
-enum BlockForm { kTwo, kPatch, kStream, kTile };
+enum BlockForm { kTwo, kPatch, kStream, kTile, kStem };
 // Multiplications of the pointwise layer up to which the patch form is the fastest: each column slice of a patch computes its
 // depthwise layer again, so its time grows with both.  Full width, batch 4 (14 x 14 x 512 -> 512 205e6) 102 us against 122
 // without that block, batch 6 (308e6) 150 against 145; 3/4 width, whose other form is two launches for most blocks, batch 16
@@ -130,6 +130,10 @@ BlockPlan plan_blocks_f16(const tfx_mobilenet_v1_variant& v, int64_t batch) {
                 : fits(separable_tile_f16_supported)   ? kTile
                 : small[b]                             ? kPatch
                                                        : kTwo;
+    // The second block with the stem: us a pass, separate and together, full width 16 images 151 / 146, 64 images 257 / 253; 3/4 width 16
+    // images 138 / 130, 64 of 192 x 192 218 / 203.  Half width, 32 images 132 / 131, quarter width, 64 of 160 x 160 107 / 115.  8 images and
+    // fewer (full width 126.5 / 122, one 67.6 / 68.2) stay separate: there a pass and its feature maps have a launch for each block.
+    if (b == 1 && q >= 3 && batch * out * out >= 30000) p.form[b] = kStem;
     if (p.form[b] == kTile) {
       ++p.tiles;
       p.packed[b] = p.packed_halfs;
@@ -774,14 +778,21 @@ int forward_f16_impl(const tfx_mobilenet_v1_variant* variant, const uint16_t* in
   const int64_t f0[4] = {3, 3, 3, kStemChannels * q / 4};
   ConvGeom g;
   conv_geometry(shape, f0, 2, 2, TFX_PAD_SAME, false, &g);
+  const int64_t fd2[4] = {3, 3, kChannels[0] * q / 4, 1};
+  const int64_t map[4] = {batch, g.out[1], g.out[2], fd2[2]};
+  ConvGeom g2;
+  conv_geometry(map, fd2, kStrides[1], kStrides[1], TFX_PAD_SAME, true, &g2);
+  const SecondBlock<uint16_t> second{weights->dw_w[1], weights->dw_b[1], weights->pw_w[1], weights->pw_b[1],
+                                     (int)g2.out[1], (int)g2.out[2], (int)g2.pad[0], (int)g2.pad[2]};
+  const int leading = form.form[1] == kStem && end_block != 1 ? 2 : 1;  // blocks that come with the stem
   int rc = launch_stem_block_rows_f16(input, weights->conv0_w, weights->conv0_b, weights->dw_w[0], weights->dw_b[0], weights->pw_w[0],
-                                      weights->pw_b[0], end_block == 1 ? features : buf[0], (int)batch, (int)shape[1], (int)shape[2],
-                                      (int)g.out[1], (int)g.out[2], (int)g.pad[0], (int)g.pad[2], q, s);
-  if (rc || end_block == 1) return rc;
-  for (int i = 0; i < 3; ++i) shape[i] = g.out[i];
-  shape[3] = kChannels[0] * q / 4;
+                                      weights->pw_b[0], end_block == leading ? features : buf[0], (int)batch, (int)shape[1], (int)shape[2],
+                                      (int)g.out[1], (int)g.out[2], (int)g.pad[0], (int)g.pad[2], q, s, leading == 2 ? &second : nullptr);
+  if (rc || end_block == leading) return rc;
+  for (int i = 0; i < 3; ++i) shape[i] = leading == 2 ? g2.out[i] : g.out[i];
+  shape[3] = kChannels[leading - 1] * q / 4;
   int cur = 0;
-  for (int b = 1; b < blocks; ++b) {  // (the first came with the stem)
+  for (int b = leading; b < blocks; ++b) {
     const int64_t fd[4] = {3, 3, shape[3], 1};
     const int64_t cout = kChannels[b] * q / 4;
     conv_geometry(shape, fd, kStrides[b], kStrides[b], TFX_PAD_SAME, true, &g);

@@ -384,10 +384,17 @@ int launch_separable_patch_f16(const uint16_t* x, const uint16_t* dw_w, const ui
                                int stride, int pt, int pl, int dw_act, int pw_act, hipStream_t stream);
 
 // The stem and the first block of the network of width q / 4 in one launch (block_rows_f16.hip), activations relu6: images of
-// up to 256 columns, y 16-byte aligned.
+// up to 256 columns, y 16-byte aligned.  second: optional, the block behind it (3x3 at stride 2, 16 q -> 32 q channels), whose output
+// [batch, oh, ow, 32 q] then is what goes to y.
+template <typename T>
+struct SecondBlock {
+  const T *dw_w, *dw_b, *pw_w, *pw_b;
+  int oh, ow, pt, pl;
+};
 int launch_stem_block_rows_f16(const uint16_t* image, const uint16_t* st_w, const uint16_t* st_b, const uint16_t* dw_w,
                                const uint16_t* dw_b, const uint16_t* pw_w, const uint16_t* pw_b, uint16_t* y, int batch, int ih, int iw,
-                               int oh, int ow, int pt, int pl, int q, hipStream_t stream);
+                               int oh, int ow, int pt, int pl, int q, hipStream_t stream,
+                               const SecondBlock<uint16_t>* second = nullptr);
 
 // The same in fp32 (block_rows.hip).
 int launch_stem_block_rows(const float* image, const float* st_w, const float* st_b, const float* dw_w, const float* dw_b, const float* pw_w,
