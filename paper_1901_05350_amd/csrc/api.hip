@@ -209,7 +209,7 @@ struct NetPlan {
   size_t act_floats;  // per ping-pong buffer
   size_t off_buf[2], off_partial, off_chain, off_head, off_packed, bytes;  // off_packed: BlockPlan, BlockPlan32
   BlockPlan32 blocks;  // fp32
-  bool chain;         // the batch-1 full-width network: room for the chained small-map kernel (chain.hip)
+  bool chain;         // one image: room for the chained small-map kernel (chain.hip)
   bool head;          // and for blocks 2 - 4 as stages of one launch (block.hip): their three outputs at once
 };
 
@@ -239,6 +239,11 @@ NetPlan plan_net(const tfx_mobilenet_v1_variant& v, int64_t batch, size_t elem_b
   p.off_packed = off;
   if (elem_bytes == sizeof(uint16_t)) {
     off += plan_blocks_f16(v, batch).packed_halfs * sizeof(uint16_t);
+    p.chain = chain_supported((int)v.image_size, (int)v.width_quarters, (int)v.classes, batch);
+    if (p.chain) {
+      p.off_chain = align_up(off);
+      off = p.off_chain + chain_workspace_bytes_f16((int)v.image_size, (int)v.classes, (int)v.width_quarters);
+    }
   } else {
     p.blocks = plan_blocks(v, batch);
     if (off <= most && off + p.blocks.packed_bytes > most) p.blocks.drop_tiles();
@@ -759,12 +764,16 @@ int forward_f16_impl(const tfx_mobilenet_v1_variant* variant, const uint16_t* in
   for (int b = 0; b < blocks; ++b)
     for (const void* p : {weights->dw_w[b], weights->dw_b[b], weights->pw_w[b], weights->pw_b[b]})
       aligned = aligned && reinterpret_cast<uintptr_t>(p) % 16 == 0;
+  // One image: the blocks from the fifth or sixth on and the tail as one persistent kernel, as in fp32
+  const int chain_first = q == 4 ? 5 : 4;
+  const bool chain = aligned && end_block == 0 && plan.chain && reinterpret_cast<uintptr_t>(weights->fc_w) % 16 == 0 && chain_resident(q, true);
+  const int separate = chain ? chain_first : blocks;  // blocks that are launches
   uint16_t* const packed_base = reinterpret_cast<uint16_t*>(ws + plan.off_packed);
   if (aligned && form.tiles > 0) {
     const uint16_t* filters[kBlocks];
     uint16_t* packed[kBlocks];
     int tiles = 0, c[kBlocks], n[kBlocks];
-    for (int b = 0; b < blocks; ++b)
+    for (int b = 0; b < separate; ++b)
       if (form.form[b] == kTile) {
         filters[tiles] = weights->pw_w[b], packed[tiles] = packed_base + form.packed[b];
         c[tiles] = form.c[b], n[tiles] = form.n[b];
@@ -785,14 +794,19 @@ int forward_f16_impl(const tfx_mobilenet_v1_variant* variant, const uint16_t* in
   const SecondBlock<uint16_t> second{weights->dw_w[1], weights->dw_b[1], weights->pw_w[1], weights->pw_b[1],
                                      (int)g2.out[1], (int)g2.out[2], (int)g2.pad[0], (int)g2.pad[2]};
   const int leading = form.form[1] == kStem && end_block != 1 ? 2 : 1;  // blocks that come with the stem
+  ChainClear clear;
+  if (chain) {
+    const ChainFill fill = chain_fill_f16((int)variant->image_size, (int)variant->classes, q, chain_first, ws + plan.off_chain);
+    clear = ChainClear{reinterpret_cast<int*>(ws + plan.off_chain), 1, 1, static_cast<uint4*>(fill.at), (unsigned)(fill.bytes / 16)};
+  }
   int rc = launch_stem_block_rows_f16(input, weights->conv0_w, weights->conv0_b, weights->dw_w[0], weights->dw_b[0], weights->pw_w[0],
                                       weights->pw_b[0], end_block == leading ? features : buf[0], (int)batch, (int)shape[1], (int)shape[2],
-                                      (int)g.out[1], (int)g.out[2], (int)g.pad[0], (int)g.pad[2], q, s, leading == 2 ? &second : nullptr);
+                                      (int)g.out[1], (int)g.out[2], (int)g.pad[0], (int)g.pad[2], q, s, leading == 2 ? &second : nullptr, clear);
   if (rc || end_block == leading) return rc;
   for (int i = 0; i < 3; ++i) shape[i] = leading == 2 ? g2.out[i] : g.out[i];
   shape[3] = kChannels[leading - 1] * q / 4;
   int cur = 0;
-  for (int b = leading; b < blocks; ++b) {
+  for (int b = leading; b < separate; ++b) {
     const int64_t fd[4] = {3, 3, shape[3], 1};
     const int64_t cout = kChannels[b] * q / 4;
     conv_geometry(shape, fd, kStrides[b], kStrides[b], TFX_PAD_SAME, true, &g);
@@ -823,6 +837,8 @@ int forward_f16_impl(const tfx_mobilenet_v1_variant* variant, const uint16_t* in
     shape[3] = cout;
     cur ^= 1;
   }
+  if (chain)
+    return launch_chain_f16(buf[cur], (int)variant->image_size, weights, ws + plan.off_chain, probs, logits, (int)variant->classes, q, chain_first, s);
   return launch_pool_fc_softmax_f16(buf[cur], weights->fc_w, weights->fc_b, partial, logits, probs, (int)batch,
                                     (int)(shape[1] * shape[2]), (int)shape[3], (int)variant->classes, s);
 }

@@ -47,6 +47,8 @@ struct RowsArgs {
   // the second block, where it comes too
   const half_t *dw2_w, *dw2_b, *pw2_w, *pw2_b;
   int OH2, OW2, pt2, pl2;
+  ChainClear clear;  // optional, by workgroups behind the first `strip_groups`
+  int strip_groups;
 };
 
 struct RowsPixel {
@@ -78,6 +80,8 @@ __device__ __forceinline__ h8 other_half(const h8& v) {  // of lane (li + 8) % 1
 
 template <int Q, bool TWO>
 __global__ __launch_bounds__(512, 4) void stem_block_rows_f16_kernel(RowsArgs g) {
+  if ((int)blockIdx.x >= g.strip_groups)
+    return clear_for_chain(g.clear, (blockIdx.x - g.strip_groups) * blockDim.x + threadIdx.x, (gridDim.x - g.strip_groups) * blockDim.x);
   constexpr int C = 8 * Q, N = 16 * Q, NB = Q, G = (C + 15) / 16, PX = 8 * rows_pixel_pieces<Q, TWO>();
   using L2 = SecondLds<Q>;
   extern __shared__ __align__(16) half_t ring[];  // [4][16 T + 2][PX]: stem row r in slot r % 4, column c at c + 1
@@ -438,12 +442,13 @@ constexpr size_t rows_lds_bytes(int tiles) {
   return ((size_t)4 * (16 * tiles + 2) * 8 * rows_pixel_pieces<Q, TWO>() + (TWO ? SecondLds<Q>(tiles).end : 0)) * sizeof(half_t);
 }
 template <int Q, bool TWO>
-int launch_rows(const RowsArgs& args, int batch, hipStream_t stream) {
+int launch_rows(const RowsArgs& args, hipStream_t stream) {
   const int tiles = (args.OW + 15) / 16;
   auto kern = stem_block_rows_f16_kernel<Q, TWO>;
   static std::atomic<uint64_t> lds_allowed{0};
   if (TWO && allow_dynamic_lds(reinterpret_cast<const void*>(kern), rows_lds_bytes<Q, TWO>(8), lds_allowed) != TFX_OK) return TFX_ERR_LAUNCH;
-  hipLaunchKernelGGL(kern, dim3((unsigned)(batch * args.strips)), dim3(64u * tiles), (rows_lds_bytes<Q, TWO>(tiles)), stream, args);
+  const unsigned clearing = (args.clear.fill_pieces / 4 + (unsigned)args.clear.zero_count + 64 * tiles - 1) / (64 * tiles);
+  hipLaunchKernelGGL(kern, dim3((unsigned)args.strip_groups + clearing), dim3(64u * tiles), (rows_lds_bytes<Q, TWO>(tiles)), stream, args);
   return check_launch();
 }
 
@@ -451,7 +456,7 @@ int launch_rows(const RowsArgs& args, int batch, hipStream_t stream) {
 
 int launch_stem_block_rows_f16(const uint16_t* image, const uint16_t* st_w, const uint16_t* st_b, const uint16_t* dw_w,
                                const uint16_t* dw_b, const uint16_t* pw_w, const uint16_t* pw_b, uint16_t* y, int batch, int ih, int iw,
-                               int oh, int ow, int pt, int pl, int q, hipStream_t stream, const SecondBlock<uint16_t>* second) {
+                               int oh, int ow, int pt, int pl, int q, hipStream_t stream, const SecondBlock<uint16_t>* second, const ChainClear& clear) {
   auto p = [](const uint16_t* v) { return reinterpret_cast<const half_t*>(v); };
   const int out_rows = second ? second->oh : oh;
   const long long in = (long long)ih * iw * 3, out = second ? (long long)second->oh * second->ow * 32 * q : (long long)oh * ow * 16 * q;  // halfs of an image
@@ -481,16 +486,16 @@ int launch_stem_block_rows_f16(const uint16_t* image, const uint16_t* st_w, cons
     }
     RowsArgs g{p(image) + first * in, p(st_w), p(st_b), p(dw_w), p(dw_b), p(pw_w), p(pw_b), reinterpret_cast<half_t*>(y) + first * out,
                ih, iw, oh, ow, pt, pl, strips, (out_rows + strips - 1) / strips, in, images * in, (unsigned)(2 * images * out),
-               nullptr, nullptr, nullptr, nullptr, 0, 0, 0, 0};
+               nullptr, nullptr, nullptr, nullptr, 0, 0, 0, 0, first == 0 ? clear : ChainClear(), images * strips};
     if (second) {
       g.dw2_w = p(second->dw_w), g.dw2_b = p(second->dw_b), g.pw2_w = p(second->pw_w), g.pw2_b = p(second->pw_b);
       g.OH2 = second->oh, g.OW2 = second->ow, g.pt2 = second->pt, g.pl2 = second->pl;
     }
     int rc = TFX_ERR_UNSUPPORTED;
-    if (q == 1 && !second) rc = launch_rows<1, false>(g, images, stream);
-    if (q == 2 && !second) rc = launch_rows<2, false>(g, images, stream);
-    if (q == 3) rc = second ? launch_rows<3, true>(g, images, stream) : launch_rows<3, false>(g, images, stream);
-    if (q == 4) rc = second ? launch_rows<4, true>(g, images, stream) : launch_rows<4, false>(g, images, stream);
+    if (q == 1 && !second) rc = launch_rows<1, false>(g, stream);
+    if (q == 2 && !second) rc = launch_rows<2, false>(g, stream);
+    if (q == 3) rc = second ? launch_rows<3, true>(g, stream) : launch_rows<3, false>(g, stream);
+    if (q == 4) rc = second ? launch_rows<4, true>(g, stream) : launch_rows<4, false>(g, stream);
     if (rc) return rc;
   }
   return TFX_OK;

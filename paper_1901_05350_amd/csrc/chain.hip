@@ -21,6 +21,14 @@
 // front of a wait (loads return in order within a wavefront, so the polls return behind them: 90.4), the two kinds of tasks in
 // workgroups of their own, two to a CU (82 - 90), offsets and filters of the next step computed before this one's wait (83 - 87).
 //
+// On binary16 storage (ChainParams<half_t>) a word is two channels: depthwise tasks have 64, a pointwise instruction takes 32 values of K,
+// sums are floats and every layer rounds once.  The five launches in front (stem and block 1, which also fills; blocks 2 - 5) and
+// this kernel, 38 us, take 63.3 us where 15 launches took 67.6 (of 3.4 us of host time each); 3/4 width 224 x 224 65.5 -> 58.8, half
+// width 128 x 128 52.2 -> 46.3, quarter width 48.1 -> 42.7.
+//
+// Tiles of 16 or 32 columns: whichever takes fewer rounds of tasks.  With 32 from 160 such tasks on, some of 9 ... 13 row tiles, dealt to
+// 8 XCDs, were two rounds: 3/4 width 192 x 192 80.9 -> 72.6 us, binary16 full width 192 x 192 67.8 -> 59.6.
+//
 // Visibility between workgroups on different XCDs (each XCD has its own L2) without cache write-back /
 // invalidate instructions: every activation that one task writes and another reads moves through
 // device-coherent accesses (the sc1 cache policy of agent-scope atomics: stores write through to
@@ -40,6 +48,9 @@
 
 namespace tfx {
 namespace {
+
+typedef _Float16 half_t;
+typedef _Float16 h8 __attribute__((ext_vector_type(8)));
 
 constexpr int kChainThreads = 512;
 constexpr int kChainWaves = kChainThreads / 64;
@@ -90,27 +101,29 @@ __device__ __forceinline__ bool task_of(const TaskMap& m, int vt, int* r, int* c
   return *r < m.tiles_m && *c < m.tiles_c;
 }
 
+template <typename T>  // of the storage: float or half_t
 struct ChainBlock {
-  const float *dw_w, *dw_b, *pw_w, *pw_b;
+  const T *dw_w, *dw_b, *pw_w, *pw_b;
   int in_hw, out_hw, stride, pad;  // square maps; pad = zero rows / columns before the image
   int cin, cout;
   int tn;                          // 16-column blocks per pointwise tile
   FastDiv by_hw;                   // division by out_hw
   TaskMap dw_map, pw_map;
-  unsigned in_off, mid_off, out_off;  // float offsets in the chain workspace: input (0 for the first block, whose
+  unsigned in_off, mid_off, out_off;  // element offsets in the chain workspace: input (0 for the first block, whose
                                    // input is a buffer of its own), depthwise output, pointwise output
 };
 
+template <typename T>
 struct ChainParams {
-  ChainBlock blk[kChainBlocks];
-  const float* in0;     // input of the first block (written by an earlier kernel)
+  ChainBlock<T> blk[kChainBlocks];
+  const T* in0;         // input of the first block (written by an earlier kernel)
   unsigned in0_bytes;
-  float* act;           // chain workspace: every step's output
+  void* act;            // chain workspace: every step's output
   unsigned act_bytes;
   int* failed;          // a wait has given up
-  const float *fc_w, *fc_b;
-  unsigned partial_off; // float offset in act: [feat / 128][classes] partial logits
-  float *probs, *logits;
+  const T *fc_w, *fc_b;
+  unsigned partial_at;  // byte offset in act: [feat / 128][classes] partial logits, floats
+  T *probs, *logits;
   int classes, feat, last_hw;
   int spin_limit;       // polls before a wait gives up
   int nblocks;          // blocks in blk[]
@@ -152,7 +165,7 @@ __device__ __forceinline__ void load_written(int* failed, int spin_limit, F load
 
 // ---- depthwise 3x3 + bias + ReLU6: 16 output pixels x 32 channels, one output per thread ----
 // wait: the input comes from a task of this launch
-__device__ __forceinline__ void dw_task(const ChainParams& P, const ChainBlock& B, int r, int c, bool wait,
+__device__ __forceinline__ void dw_task(const ChainParams<float>& P, const ChainBlock<float>& B, int r, int c, bool wait,
                                         __amdgpu_buffer_rsrc_t in, __amdgpu_buffer_rsrc_t act) {
   const int m_out = B.out_hw * B.out_hw;
   const int t = threadIdx.x, px = (t / 32) % 16, ch = 32 * c + t % 32;
@@ -196,10 +209,57 @@ __device__ __forceinline__ void dw_task(const ChainParams& P, const ChainBlock& 
   if (live) st_f32(act, (B.mid_off + (unsigned)(p * B.cin + ch)) * 4u, apply_act(acc, clamp));
 }
 
+// The same on halfs: 16 output pixels x 64 channels, two (a word) per thread, sums in fp32 and one rounding.
+__device__ __forceinline__ unsigned half_bits(half_t v) { return v == v ? (unsigned)__builtin_bit_cast(unsigned short, v) : 0x7e00u; }
+__device__ __forceinline__ unsigned word_of(float a, float b) { return half_bits((half_t)a) | half_bits((half_t)b) << 16; }
+typedef _Float16 h2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ void dw_task(const ChainParams<half_t>& P, const ChainBlock<half_t>& B, int r, int c, bool wait,
+                                        __amdgpu_buffer_rsrc_t in, __amdgpu_buffer_rsrc_t act) {
+  const int m_out = B.out_hw * B.out_hw;
+  const int t = threadIdx.x, px = (t / 32) % 16, ch = 64 * c + 2 * (t % 32);
+  unsigned w[9];
+#pragma unroll
+  for (int k = 0; k < 9; ++k) w[k] = *reinterpret_cast<const unsigned*>(B.dw_w + k * B.cin + ch);
+  const unsigned bias = *reinterpret_cast<const unsigned*>(B.dw_b + ch);
+
+  const int p = 16 * r + px;
+  const bool live = p < m_out;
+  const int oy = (int)div_by((unsigned)p, B.by_hw), ox = p - oy * B.out_hw;
+  const int iy0 = oy * B.stride - B.pad, ix0 = ox * B.stride - B.pad;
+  unsigned v[9], off[9];
+  bool ok[9];
+#pragma unroll
+  for (int k = 0; k < 9; ++k) {
+    const int iy = iy0 + k / 3, ix = ix0 + k % 3;
+    ok[k] = live && iy >= 0 && iy < B.in_hw && ix >= 0 && ix < B.in_hw;
+    off[k] = ok[k] ? (B.in_off + (unsigned)((iy * B.in_hw + ix) * B.cin + ch)) * 2u : 0x80000000u;  // (past the end: 0)
+  }
+  load_written(P.failed, P.spin_limit, [&]() __attribute__((always_inline)) {
+    unsigned most = 0;
+#pragma unroll
+    for (int k = 0; k < 9; ++k) v[k] = ld_word(in, off[k]), most = max(most, v[k]);
+    return wait && most == kEmpty;
+  });
+  const h2 b = __builtin_bit_cast(h2, bias);
+  float acc[2] = {(float)b[0], (float)b[1]};
+#pragma unroll
+  for (int k = 0; k < 9; ++k) {
+    const h2 x = __builtin_bit_cast(h2, v[k]), f = __builtin_bit_cast(h2, w[k]);
+#pragma unroll
+    for (int e = 0; e < 2; ++e) acc[e] = ok[k] ? fmaf((float)x[e], (float)f[e], acc[e]) : acc[e];
+  }
+  ActClamp clamp;
+  clamp.on = true;
+  clamp.hi = 6.0f;
+  if (live)
+    __builtin_amdgcn_raw_buffer_store_b32(word_of(apply_act(acc[0], clamp), apply_act(acc[1], clamp)), act,
+                                          (int)((B.mid_off + (unsigned)(p * B.cin + ch)) * 2u), 0, kSc1);
+}
+
 // ---- pointwise 1x1 + bias + ReLU6: 16 x (16 TN) tile, K = WAVES x CHUNK split over the first WAVES 
 // wavefronts (all 8 where K is a multiple of 128; 4 for the K = 64 and K = 192 of the narrower networks) ----
 template <int CHUNK, int TN, int WAVES>
-__device__ __forceinline__ void pw_task(const ChainParams& P, const ChainBlock& B, int tile_m, int tile_n,
+__device__ __forceinline__ void pw_task(const ChainParams<float>& P, const ChainBlock<float>& B, int tile_m, int tile_n,
                                         __amdgpu_buffer_rsrc_t act, float* red) {
   constexpr int G = CHUNK / 16;
   const int K = B.cin, N = B.cout, M = B.out_hw * B.out_hw;
@@ -289,6 +349,89 @@ __device__ __forceinline__ void pw_task(const ChainParams& P, const ChainBlock& 
   }
 }
 
+// The same on halfs, 32 values of K an instruction.  A filter value is one of a lane's eight of consecutive rows: words of two columns
+// (single halfs with TN == 1) come from eight rows and are put together in registers.
+template <int CHUNK, int TN, int WAVES>
+__device__ __forceinline__ void pw_task(const ChainParams<half_t>& P, const ChainBlock<half_t>& B, int tile_m, int tile_n,
+                                        __amdgpu_buffer_rsrc_t act, float* red) {
+  constexpr int G = CHUNK / 32;
+  const int K = B.cin, N = B.cout, M = B.out_hw * B.out_hw;
+  const int tid = threadIdx.x, wk = (tid / 64) % kChainWaves, lane = tid % 64, li = lane % 16, q = lane / 16;
+  const bool compute = tid < 64 * WAVES;
+  const int m0 = 16 * tile_m, n0 = 16 * TN * tile_n;
+
+  const half_t* bp = B.pw_w + (size_t)(wk * CHUNK + 8 * q) * N + n0 + TN * li;
+  unsigned raw[G][8];
+  if (compute) {
+#pragma unroll
+    for (int g = 0; g < G; ++g)
+#pragma unroll
+      for (int s = 0; s < 8; ++s) {
+        const half_t* p = bp + (size_t)(32 * g + s) * N;
+        if constexpr (TN == 2) raw[g][s] = *reinterpret_cast<const unsigned*>(p);
+        else raw[g][s] = *reinterpret_cast<const unsigned short*>(p);
+      }
+  }
+  const int ev = tid / 64, el = tid % 64;
+  const int erow = m0 + 4 * (el / 16) + ev, ecol = n0 + TN * (el % 16);
+  float ebias[TN];
+#pragma unroll
+  for (int j = 0; j < TN; ++j) ebias[j] = tid < 256 ? (float)B.pw_b[ecol + j] : 0.f;
+
+  if (compute) {
+    const int arow = min(m0 + li, M - 1);
+    const unsigned a_off = (B.mid_off + (unsigned)(arow * K + wk * CHUNK + 8 * q)) * 2u;
+    u32x4 a[G];
+    {  // (a word of each depthwise task first, as above)
+      const unsigned last = (B.mid_off + (unsigned)(min(m0 + 15, M - 1) * K + wk * CHUNK + 32 * (li % G))) * 2u;
+      load_written(P.failed, P.spin_limit, [&]() __attribute__((always_inline)) { return ld_word(act, last) == kEmpty; });
+    }
+    load_written(P.failed, P.spin_limit, [&]() __attribute__((always_inline)) {
+      unsigned most = 0;
+#pragma unroll
+      for (int g = 0; g < G; ++g) {
+        a[g] = ld_words4(act, a_off + 64u * g);
+        most = max(max(max(a[g][0], a[g][1]), max(a[g][2], a[g][3])), most);
+      }
+      return most == kEmpty;
+    });
+
+    floatx4 acc[2][TN] = {};
+#pragma unroll
+    for (int g = 0; g < G; ++g)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) {
+        u32x4 b;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          b[i] = __builtin_amdgcn_perm(raw[g][2 * i + 1], raw[g][2 * i], j == 0 ? 0x05040100u : 0x07060302u);
+        acc[g & 1][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(h8, a[g]), __builtin_bit_cast(h8, b), acc[g & 1][j], 0, 0, 0);
+      }
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) red[((wk * TN + j) * 4 + v) * 64 + lane] = acc[0][j][v] + acc[1][j][v];
+  }
+  __syncthreads();
+  if (tid < 256) {
+    ActClamp clamp;
+    clamp.on = true;
+    clamp.hi = 6.0f;
+    float o[2];
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+      float sum = ebias[j];
+#pragma unroll
+      for (int w = 0; w < WAVES; ++w) sum += red[((w * TN + j) * 4 + ev) * 64 + el];
+      o[j] = apply_act(sum, clamp);
+    }
+    // (TN == 1: the next lane's column, for the even ones; a word is written whole)
+    if constexpr (TN == 1) o[1] = __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(o[0]), 0xb1, 0xf, 0xf, true));
+    if (erow < M && (TN == 2 || el % 2 == 0))
+      __builtin_amdgcn_raw_buffer_store_b32(word_of(o[0], o[1]), act, (int)((B.out_off + (unsigned)(erow * N + ecol)) * 2u), 0, kSc1);
+  }
+}
+
 __device__ __forceinline__ float block_sum_or_max(float v, bool is_max, float* scratch) {
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) {
@@ -305,22 +448,39 @@ __device__ __forceinline__ float block_sum_or_max(float v, bool is_max, float* s
 }
 
 // The pointwise task for a layer of K input channels: the K split, and 32-column tiles only below K = 1024.
-template <int K>
-__device__ __forceinline__ void pw_task_for(const ChainParams& P, const ChainBlock& B, int r, int c,
+template <typename T, int K>
+__device__ __forceinline__ void pw_task_for(const ChainParams<T>& P, const ChainBlock<T>& B, int r, int c,
                                             __amdgpu_buffer_rsrc_t act, float* red) {
-  constexpr int WAVES = K % 128 == 0 ? 8 : 4, CHUNK = K / WAVES;
-  static_assert(CHUNK % 16 == 0 && CHUNK <= 128, "a wavefront takes whole groups of 16 values of K");
+  constexpr int STEP = sizeof(T) == 2 ? 32 : 16;  // a wavefront takes whole steps
+  constexpr int WAVES = K % (8 * STEP) == 0 ? 8 : sizeof(T) == 2 && K % (6 * STEP) == 0 ? 6 : K % (4 * STEP) == 0 ? 4 : 2;
+  constexpr int CHUNK = K / WAVES;
+  static_assert(CHUNK % STEP == 0 && CHUNK <= 128, "a wavefront takes whole steps of K");
   if constexpr (K < 1024) {
     if (B.tn == 2) return pw_task<CHUNK, 2, WAVES>(P, B, r, c, act, red);
   }
   pw_task<CHUNK, 1, WAVES>(P, B, r, c, act, red);
 }
 
+// Four weights of the fully connected layer as they are stored.
+template <typename T>
+struct FcWeights;
+template <>
+struct FcWeights<float> {
+  typedef float4 V;
+  static __device__ __forceinline__ float get(const V& v, int e) { return (&v.x)[e]; }
+};
+template <>
+struct FcWeights<half_t> {
+  typedef _Float16 V __attribute__((ext_vector_type(4)));
+  static __device__ __forceinline__ float get(const V& v, int e) { return (float)v[e]; }
+};
+
 // Q = width multiplier in quarters: the chained blocks have 64 Q, 128 Q and 256 Q input channels, the fully
 // connected layer 256 Q = 2 Q slices of 128.
-template <int Q>
-__global__ __launch_bounds__(kChainThreads) void mobilenet_chain_kernel(const ChainParams P) {
+template <typename T, int Q>
+__global__ __launch_bounds__(kChainThreads) void mobilenet_chain_kernel(const ChainParams<T> P) {
   constexpr int kSlices = 2 * Q;
+  constexpr bool kHalf = sizeof(T) == 2;
   // 2 x 16 KB: split-K partial tiles, of one task and the next (between a task's reads and the writes of the task after the next lies
   // the barrier of the next); reused by the tail
   __shared__ float red2[2][kChainWaves * 2 * 4 * 64];
@@ -333,7 +493,7 @@ __global__ __launch_bounds__(kChainThreads) void mobilenet_chain_kernel(const Ch
     KernargInts karg = (KernargInts)__builtin_amdgcn_kernarg_segment_ptr();
     int warm = 0;
 #pragma unroll
-    for (int i = 0; i < (int)sizeof(ChainParams) / 4; i += 16) warm += karg[i];
+    for (int i = 0; i < (int)sizeof(ChainParams<T>) / 4; i += 16) warm += karg[i];
     asm volatile("" ::"s"(warm));
   }
   const __amdgpu_buffer_rsrc_t in0 = make_rsrc(P.in0, P.in0_bytes);
@@ -344,29 +504,26 @@ __global__ __launch_bounds__(kChainThreads) void mobilenet_chain_kernel(const Ch
   const int fc_tasks_c = (P.classes + kFcColBlock - 1) / kFcColBlock;
   const int fc_tasks = kSlices * fc_tasks_c;
   constexpr int kper = 128;  // input channels per task, 8 per thread
-  float4 fw[8];
-#pragma unroll
-  for (int i = 0; i < 8; ++i) fw[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+  typedef typename FcWeights<T>::V Weights;
+  Weights fw[8] = {};
   const bool fvec = P.classes % 4 == 0;
-  auto load_fc = [&](int task, float4 (&dst)[8]) {
+  auto load_fc = [&](int task, Weights (&dst)[8]) {
     const int ks = task / fc_tasks_c, cb = task % fc_tasks_c;
     const int col = kFcColBlock * cb + 4 * (tid % 32), k0 = kper * ks + 8 * ((tid / 32) % 16);
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-      const float* p = P.fc_w + (size_t)(k0 + i) * P.classes + col;
+      const T* p = P.fc_w + (size_t)(k0 + i) * P.classes + col;
       if (fvec && col + 3 < P.classes) {
-        dst[i] = *reinterpret_cast<const float4*>(p);
+        dst[i] = *reinterpret_cast<const Weights*>(p);
       } else {
-        dst[i].x = col < P.classes ? p[0] : 0.f;
-        dst[i].y = col + 1 < P.classes ? p[1] : 0.f;
-        dst[i].z = col + 2 < P.classes ? p[2] : 0.f;
-        dst[i].w = col + 3 < P.classes ? p[3] : 0.f;
+        dst[i] = Weights{col < P.classes ? p[0] : (T)0.f, col + 1 < P.classes ? p[1] : (T)0.f, col + 2 < P.classes ? p[2] : (T)0.f,
+                         col + 3 < P.classes ? p[3] : (T)0.f};
       }
     }
   };
   if (wg < fc_tasks) load_fc(wg, fw);
   for (int bi = 0; bi < P.nblocks; ++bi) {
-    const ChainBlock& B = P.blk[bi];
+    const ChainBlock<T>& B = P.blk[bi];
     const TaskMap &dw_map = B.dw_map, &pw_map = B.pw_map;
     for (int vt = wg; vt < dw_map.count; vt += kChainGrid) {
       int r, c;
@@ -377,14 +534,14 @@ __global__ __launch_bounds__(kChainThreads) void mobilenet_chain_kernel(const Ch
       if (!task_of(pw_map, vt, &r, &c)) continue;
       float* const red = red2[turn];
       turn ^= 1;
-      if (B.cin == 64 * Q) pw_task_for<64 * Q>(P, B, r, c, act, red);
-      else if (B.cin == 128 * Q) pw_task_for<128 * Q>(P, B, r, c, act, red);
-      else pw_task_for<256 * Q>(P, B, r, c, act, red);
+      if (B.cin == 64 * Q) pw_task_for<T, 64 * Q>(P, B, r, c, act, red);
+      else if (B.cin == 128 * Q) pw_task_for<T, 128 * Q>(P, B, r, c, act, red);
+      else pw_task_for<T, 256 * Q>(P, B, r, c, act, red);
     }
   }
 
   // ---- average pool + fully connected: task (ks, cb) = 128 input channels x 128 classes ----
-  const ChainBlock& L = P.blk[P.nblocks - 1];
+  const ChainBlock<T>& L = P.blk[P.nblocks - 1];
   const int hw2 = P.last_hw * P.last_hw;
   float* const red = red2[0];
   __syncthreads();
@@ -392,29 +549,43 @@ __global__ __launch_bounds__(kChainThreads) void mobilenet_chain_kernel(const Ch
     const int ks = task / fc_tasks_c, cb = task % fc_tasks_c;
     if (task != wg) load_fc(task, fw);
     float* pooled = red;             // [128]
-    float* psum = red + 128;         // [4][128]
-    float* fsum = red + 128 + 512;   // [16][128]
+    float* psum = red + 128;         // [4][128], halfs: [8][128]
+    float* fsum = red + 128 + 1024;  // [16][128]
+    constexpr int PG = kHalf ? 8 : 4, PX = 64 / PG, WORDS = kChainThreads / PG;
     {
-      // thread (pixel group pg of 4, channel chn of 128) sums pixels pg, pg + 4, ... (at most 64 pixels)
-      const int chn = tid % 128, pg = tid / 128;
-      float x[16];
+      // thread (pixel group pg of PG, word of WORDS: a channel, halfs: two) sums pixels pg, pg + PG, ... (at most 64 pixels)
+      const int word = tid % WORDS, pg = tid / WORDS, chn = (kHalf ? 2 : 1) * word;
+      unsigned x[PX];
       load_written(P.failed, P.spin_limit, [&]() __attribute__((always_inline)) {
         unsigned most = 0;
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          const int p = pg + 4 * i;
-          const unsigned word = ld_word(act, p < hw2 ? (L.out_off + (unsigned)(p * P.feat + kper * ks + chn)) * 4u : 0x80000000u);
-          x[i] = __uint_as_float(word), most = max(most, word);
+        for (int i = 0; i < PX; ++i) {
+          const int p = pg + PG * i;
+          x[i] = ld_word(act, p < hw2 ? (L.out_off + (unsigned)(p * P.feat + kper * ks + chn)) * (unsigned)sizeof(T) : 0x80000000u);
+          most = max(most, x[i]);
         }
         return most == kEmpty;
       });
-      float s = 0.f;
+      float s[2] = {0.f, 0.f};
 #pragma unroll
-      for (int i = 0; i < 16; ++i) s += x[i];
-      psum[pg * 128 + chn] = s;
+      for (int i = 0; i < PX; ++i) {
+        if constexpr (kHalf) {
+          const h2 v = __builtin_bit_cast(h2, x[i]);
+          s[0] += (float)v[0], s[1] += (float)v[1];
+        } else {
+          s[0] += __uint_as_float(x[i]);
+        }
+      }
+      psum[pg * 128 + chn] = s[0];
+      if constexpr (kHalf) psum[pg * 128 + chn + 1] = s[1];
     }
     __syncthreads();
-    if (tid < 128) pooled[tid] = (psum[tid] + psum[128 + tid] + psum[256 + tid] + psum[384 + tid]) / (float)hw2;
+    if (tid < 128) {
+      float s = psum[tid];
+#pragma unroll
+      for (int i = 1; i < PG; ++i) s += psum[128 * i + tid];
+      pooled[tid] = (float)(T)(s / (float)hw2);  // (the pooled vector is a tensor of the storage type)
+    }
     __syncthreads();
     {
       const int kq = tid / 32, c4 = tid % 32;
@@ -422,10 +593,10 @@ __global__ __launch_bounds__(kChainThreads) void mobilenet_chain_kernel(const Ch
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
         const float pv = pooled[8 * kq + i];
-        s.x = fmaf(pv, fw[i].x, s.x);
-        s.y = fmaf(pv, fw[i].y, s.y);
-        s.z = fmaf(pv, fw[i].z, s.z);
-        s.w = fmaf(pv, fw[i].w, s.w);
+        s.x = fmaf(pv, FcWeights<T>::get(fw[i], 0), s.x);
+        s.y = fmaf(pv, FcWeights<T>::get(fw[i], 1), s.y);
+        s.z = fmaf(pv, FcWeights<T>::get(fw[i], 2), s.z);
+        s.w = fmaf(pv, FcWeights<T>::get(fw[i], 3), s.w);
       }
       *reinterpret_cast<float4*>(fsum + kq * 128 + 4 * c4) = s;
     }
@@ -435,7 +606,7 @@ __global__ __launch_bounds__(kChainThreads) void mobilenet_chain_kernel(const Ch
 #pragma unroll
       for (int g = 0; g < 16; ++g) s += fsum[g * 128 + tid];
       const int col = kFcColBlock * cb + tid;
-      if (col < P.classes) st_f32(act, (P.partial_off + (unsigned)(ks * P.classes + col)) * 4u, s);
+      if (col < P.classes) st_f32(act, P.partial_at + (unsigned)(ks * P.classes + col) * 4u, s);
     }
     __syncthreads();
   }
@@ -452,15 +623,15 @@ __global__ __launch_bounds__(kChainThreads) void mobilenet_chain_kernel(const Ch
         unsigned most = 0;
 #pragma unroll
         for (int s = 0; s < kSlices; ++s) {
-          const unsigned word = ld_word(act, in ? (P.partial_off + (unsigned)(s * P.classes + j)) * 4u : 0x80000000u);
+          const unsigned word = ld_word(act, in ? P.partial_at + (unsigned)(s * P.classes + j) * 4u : 0x80000000u);
           part[s] = __uint_as_float(word), most = max(most, word);
         }
         return most == kEmpty;
       });
-      float v = in ? P.fc_b[j] : 0.f;
+      float v = in ? (float)P.fc_b[j] : 0.f;
 #pragma unroll
       for (int s = 0; s < kSlices; ++s) v += part[s];
-      l[h] = in ? v : -INFINITY;
+      l[h] = in ? (float)(T)v : -INFINITY;  // (halfs: the softmax is taken of the stored logits)
     }
     const bool failed = __hip_atomic_load(P.failed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
     const float mx = block_sum_or_max(fmaxf(l[0], l[1]), true, red);
@@ -473,16 +644,12 @@ __global__ __launch_bounds__(kChainThreads) void mobilenet_chain_kernel(const Ch
       const int j = tid + kChainThreads * h;
       if (j < P.classes) {
         const float nan = __uint_as_float(0x7fc00000u);
-        if (P.logits) P.logits[j] = failed ? nan : l[h];
-        P.probs[j] = failed ? nan : e[h] / sum;
+        if (P.logits) P.logits[j] = (T)(failed ? nan : l[h]);
+        P.probs[j] = (T)(failed ? nan : e[h] / sum);
       }
     }
   }
 }
-
-struct ChainPlanHost {
-  size_t act_floats;    // chain workspace in floats
-};
 
 }  // namespace
 
@@ -493,28 +660,31 @@ bool chain_supported(int image_size, int width_quarters, int classes, long long 
 }
 
 namespace {
-typedef void (*ChainKernel)(const ChainParams);
-ChainKernel chain_kernel(int width_quarters) {
+template <typename T>
+using ChainKernel = void (*)(const ChainParams<T>);
+template <typename T>
+ChainKernel<T> chain_kernel(int width_quarters) {
   switch (width_quarters) {
-    case 1: return mobilenet_chain_kernel<1>;
-    case 2: return mobilenet_chain_kernel<2>;
-    case 3: return mobilenet_chain_kernel<3>;
-    default: return mobilenet_chain_kernel<4>;
+    case 1: return mobilenet_chain_kernel<T, 1>;
+    case 2: return mobilenet_chain_kernel<T, 2>;
+    case 3: return mobilenet_chain_kernel<T, 3>;
+    default: return mobilenet_chain_kernel<T, 4>;
   }
 }
 }  // namespace
 
 // Whether 256 workgroups of the chain kernel are resident at once on the current device (looked up once per device).
-bool chain_resident(int width_quarters) {
-  static std::atomic<int> states[4][64];  // 0 unknown, 1 yes, 2 no
+bool chain_resident(int width_quarters, bool half) {
+  static std::atomic<int> states[8][64];  // 0 unknown, 1 yes, 2 no
   int dev = 0;
   if (width_quarters < 1 || width_quarters > 4 || hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return false;
-  std::atomic<int>* const state = states[width_quarters - 1];
+  std::atomic<int>* const state = states[width_quarters - 1 + (half ? 4 : 0)];
   const int s = state[dev].load(std::memory_order_acquire);
   if (s) return s == 1;
   int cus = 0, per_cu = 0;
+  const void* const kernel = half ? reinterpret_cast<const void*>(chain_kernel<half_t>(width_quarters)) : reinterpret_cast<const void*>(chain_kernel<float>(width_quarters));
   bool ok = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
-            hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, chain_kernel(width_quarters), kChainThreads, 0) == hipSuccess;
+            hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, kChainThreads, 0) == hipSuccess;
   ok = ok && (long long)cus * per_cu >= kChainGrid;
   state[dev].store(ok ? 1 : 2, std::memory_order_release);
   return ok;
@@ -524,9 +694,10 @@ namespace {
 constexpr int kNetChannels[13] = {64, 128, 128, 256, 256, 512, 512, 512, 512, 512, 512, 1024, 1024};
 constexpr int kNetStrides[13] = {1, 2, 1, 2, 1, 2, 1, 1, 1, 1, 1, 2, 1};
 
-// Sizes of the chained part for an input map of in_hw x in_hw x 64 q (the output of block 4) at width q / 4.
-ChainPlanHost chain_layout(int in_hw, int classes, int q, ChainParams* P, int first = kFirstChainBlock) {
-  ChainPlanHost h{};
+// Bytes of the chained part for an input map of in_hw x in_hw x 64 q (the output of block 4) at width q / 4.
+template <typename T>
+size_t chain_layout(int in_hw, int classes, int q, ChainParams<T>* P, int first) {
+  constexpr int kTaskChannels = 128 / (int)sizeof(T);  // of a depthwise task
   size_t off = 0;
   const int nblocks = 13 - first;
   int hw = in_hw, cin = kNetChannels[first - 1] * q / 4;
@@ -537,13 +708,14 @@ ChainPlanHost chain_layout(int in_hw, int classes, int q, ChainParams* P, int fi
     const int need = (out_hw - 1) * s + 3 - hw;
     const int pad = need > 0 ? need / 2 : 0;
     const int m = out_hw * out_hw, tiles_m = (m + 15) / 16;
-    // 16-column tiles when 32-column ones would leave CUs idle (always for K = 1024: 32 values of K per lane)
-    const int tn = (tiles_m * (cout / 32) >= 160 && cin < 1024) ? 2 : 1;
+    // 32-column tiles where 16-column ones take more rounds of tasks (never for K = 1024: 32 values of K per lane)
+    auto rounds = [&](int columns) { return (make_task_map(tiles_m, cout / columns).count + kChainGrid - 1) / kChainGrid; };
+    const int tn = cin < 1024 && rounds(16) > rounds(32) ? 2 : 1;
     if (P) {
-      ChainBlock& B = P->blk[bi];
+      ChainBlock<T>& B = P->blk[bi];
       B.in_hw = hw, B.out_hw = out_hw, B.stride = s, B.pad = pad, B.cin = cin, B.cout = cout, B.tn = tn;
       B.by_hw = fast_div((unsigned)out_hw);
-      B.dw_map = make_task_map(tiles_m, cin / 32), B.pw_map = make_task_map(tiles_m, cout / (16 * tn));
+      B.dw_map = make_task_map(tiles_m, cin / kTaskChannels), B.pw_map = make_task_map(tiles_m, cout / (16 * tn));
       B.in_off = (unsigned)prev_out;
       B.mid_off = (unsigned)off;
       B.out_off = (unsigned)(off + (size_t)m * cin);
@@ -554,15 +726,13 @@ ChainPlanHost chain_layout(int in_hw, int classes, int q, ChainParams* P, int fi
   }
   const int slices = cin / kFcSliceChannels;
   if (P) {
-    P->partial_off = (unsigned)off;
+    P->partial_at = (unsigned)(off * sizeof(T));
     P->last_hw = hw;
     P->feat = cin;
     P->classes = classes;
     P->nblocks = nblocks;
   }
-  off += (size_t)slices * classes;
-  h.act_floats = off;
-  return h;
+  return off * sizeof(T) + (size_t)slices * classes * sizeof(float);
 }
 }  // namespace
 
@@ -578,14 +748,20 @@ int eighth_of(int image_size) {
   return (quarter + 1) / 2;
 }
 }  // namespace
+ChainFill chain_fill(int image_size, int classes, int width_quarters, int first_block, void* chain_ws) {
+  return ChainFill{static_cast<char*>(chain_ws) + flag_region(image_size),
+                   (chain_layout<float>(eighth_of(image_size), classes, width_quarters, nullptr, first_block) + 255) / 256 * 256};
+}
+ChainFill chain_fill_f16(int image_size, int classes, int width_quarters, int first_block, void* chain_ws) {
+  return ChainFill{static_cast<char*>(chain_ws) + 256,  // (the failure word)
+                   (chain_layout<half_t>(eighth_of(image_size), classes, width_quarters, nullptr, first_block) + 255) / 256 * 256};
+}
+// (laid out for the longer chain; a launch that starts one block later uses a part of it)
 size_t chain_workspace_bytes(int image_size, int classes, int width_quarters) {
   return flag_region(image_size) + chain_fill(image_size, classes, width_quarters, kFirstChainBlock, nullptr).bytes;
 }
-ChainFill chain_fill(int image_size, int classes, int width_quarters, int first_block, void* chain_ws) {
-  // (the memory is laid out for the longer chain; a launch that starts one block later uses a part of it)
-  const ChainPlanHost h = chain_layout(eighth_of(image_size), classes, width_quarters, nullptr, kFirstChainBlock);
-  const ChainPlanHost used = first_block == kFirstChainBlock ? h : chain_layout(eighth_of(image_size), classes, width_quarters, nullptr, first_block);
-  return ChainFill{static_cast<char*>(chain_ws) + flag_region(image_size), (used.act_floats * sizeof(float) + 255) / 256 * 256};
+size_t chain_workspace_bytes_f16(int image_size, int classes, int width_quarters) {
+  return 256 + chain_fill_f16(image_size, classes, width_quarters, kFirstChainBlock, nullptr).bytes;
 }
 int chain_flag_words(int image_size) {
   const int half = (image_size + 1) / 2;
@@ -644,28 +820,30 @@ int launch_ordered(hipStream_t stream, int (*fn)(void*), void* arg) {
   return fn(arg);
 }
 
-int launch_chain(const float* in0, int image_size, const tfx_mobilenet_v1_weights* w, void* chain_ws,
-                 float* probs, float* logits, int classes, int width_quarters, hipStream_t stream, int (*before)(void*),
-                 void* before_arg, int first_block) {
+namespace {
+template <typename T, typename W>
+int launch_chain_of(const T* in0, int image_size, const W* w, void* chain_ws, const ChainFill& fill, T* probs, T* logits, int classes,
+                    int width_quarters, hipStream_t stream, int (*before)(void*), void* before_arg, int first_block) {
   if (first_block != kFirstChainBlock && first_block != kFirstChainBlock + 1) return TFX_ERR_ARG;
   if (width_quarters < 1 || width_quarters > 4) return TFX_ERR_ARG;
-  ChainParams P{};
+  ChainParams<T> P{};
   const int in_hw = eighth_of(image_size);
-  const ChainPlanHost used = chain_layout(in_hw, classes, width_quarters, &P, first_block);
+  const size_t used = chain_layout<T>(in_hw, classes, width_quarters, &P, first_block);
+  auto t = [](const auto* p) { return reinterpret_cast<const T*>(p); };
   for (int bi = 0; bi < P.nblocks; ++bi) {
     const int net = first_block + bi;
-    P.blk[bi].dw_w = w->dw_w[net];
-    P.blk[bi].dw_b = w->dw_b[net];
-    P.blk[bi].pw_w = w->pw_w[net];
-    P.blk[bi].pw_b = w->pw_b[net];
+    P.blk[bi].dw_w = t(w->dw_w[net]);
+    P.blk[bi].dw_b = t(w->dw_b[net]);
+    P.blk[bi].pw_w = t(w->pw_w[net]);
+    P.blk[bi].pw_b = t(w->pw_b[net]);
   }
   P.in0 = in0;
-  P.in0_bytes = (unsigned)((size_t)in_hw * in_hw * (kNetChannels[first_block - 1] * width_quarters / 4) * sizeof(float));
+  P.in0_bytes = (unsigned)((size_t)in_hw * in_hw * (kNetChannels[first_block - 1] * width_quarters / 4) * sizeof(T));
   P.failed = static_cast<int*>(chain_ws);
-  P.act = static_cast<float*>(chain_fill(image_size, classes, width_quarters, first_block, chain_ws).at);
-  P.act_bytes = (unsigned)(used.act_floats * sizeof(float));
-  P.fc_w = w->fc_w;
-  P.fc_b = w->fc_b;
+  P.act = fill.at;
+  P.act_bytes = (unsigned)used;
+  P.fc_w = t(w->fc_w);
+  P.fc_b = t(w->fc_b);
   P.probs = probs;
   P.logits = logits;
   P.spin_limit = chain_spin_limit();
@@ -679,8 +857,23 @@ int launch_chain(const float* in0, int image_size, const tfx_mobilenet_v1_weight
     const int rc = before(before_arg);
     if (rc != TFX_OK) return rc;
   }
-  hipLaunchKernelGGL(chain_kernel(width_quarters), dim3(kChainGrid), dim3(kChainThreads), 0, stream, P);
+  hipLaunchKernelGGL(chain_kernel<T>(width_quarters), dim3(kChainGrid), dim3(kChainThreads), 0, stream, P);
   return check_launch();
+}
+}  // namespace
+
+int launch_chain(const float* in0, int image_size, const tfx_mobilenet_v1_weights* w, void* chain_ws, float* probs, float* logits,
+                 int classes, int width_quarters, hipStream_t stream, int (*before)(void*), void* before_arg, int first_block) {
+  return launch_chain_of<float>(in0, image_size, w, chain_ws, chain_fill(image_size, classes, width_quarters, first_block, chain_ws),
+                                probs, logits, classes, width_quarters, stream, before, before_arg, first_block);
+}
+
+int launch_chain_f16(const uint16_t* in0, int image_size, const tfx_mobilenet_v1_weights_f16* w, void* chain_ws, uint16_t* probs,
+                     uint16_t* logits, int classes, int width_quarters, int first_block, hipStream_t stream) {
+  return launch_chain_of<half_t>(reinterpret_cast<const half_t*>(in0), image_size, w, chain_ws,
+                                 chain_fill_f16(image_size, classes, width_quarters, first_block, chain_ws),
+                                 reinterpret_cast<half_t*>(probs), reinterpret_cast<half_t*>(logits), classes, width_quarters, stream,
+                                 nullptr, nullptr, first_block);
 }
 
 }  // namespace tfx

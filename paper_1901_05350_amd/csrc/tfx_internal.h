@@ -217,7 +217,7 @@ int launch_conv2d_stem(const float* x, const float* w, const float* bias, float*
 // chain_flag_words() words at a spacing of block_chain_flag_stride() words are zero when the kernel starts (the failure word, then the
 // flags of blocks 2 - 4 as stages), and what chain_fill() says is filled with ones.  in0: the output of block 4.
 bool chain_supported(int image_size, int width_quarters, int classes, long long batch);
-bool chain_resident(int width_quarters);
+bool chain_resident(int width_quarters, bool half = false);
 size_t chain_workspace_bytes(int image_size, int classes, int width_quarters);
 int chain_flag_words(int image_size);
 struct ChainFill {
@@ -226,6 +226,11 @@ struct ChainFill {
 };
 ChainFill chain_fill(int image_size, int classes, int width_quarters, int first_block, void* chain_ws);
 int chain_spin_limit();
+// The same on binary16 storage.  The one flag word is the failure word, at the start of chain_ws.
+size_t chain_workspace_bytes_f16(int image_size, int classes, int width_quarters);
+ChainFill chain_fill_f16(int image_size, int classes, int width_quarters, int first_block, void* chain_ws);
+int launch_chain_f16(const uint16_t* in0, int image_size, const tfx_mobilenet_v1_weights_f16* w, void* chain_ws, uint16_t* probs,
+                     uint16_t* logits, int classes, int width_quarters, int first_block, hipStream_t stream);
 // before(before_arg), if given, enqueues a launch that has to stay directly in front of the chain kernel on `stream`
 // (it is called once the stream has been ordered behind other streams' chain kernels) and returns a tfx_status.
 // first_block: 4 (the chain starts with block 5, in0 = the output of block 4) or 5 (block 6, in0 = output of block 5).
@@ -385,7 +390,7 @@ int launch_separable_patch_f16(const uint16_t* x, const uint16_t* dw_w, const ui
 
 // The stem and the first block of the network of width q / 4 in one launch (block_rows_f16.hip), activations relu6: images of
 // up to 256 columns, y 16-byte aligned.  second: optional, the block behind it (3x3 at stride 2, 16 q -> 32 q channels), whose output
-// [batch, oh, ow, 32 q] then is what goes to y.
+// [batch, oh, ow, 32 q] then is what goes to y.  clear: as for launch_conv2d_stem.
 template <typename T>
 struct SecondBlock {
   const T *dw_w, *dw_b, *pw_w, *pw_b;
@@ -394,7 +399,7 @@ struct SecondBlock {
 int launch_stem_block_rows_f16(const uint16_t* image, const uint16_t* st_w, const uint16_t* st_b, const uint16_t* dw_w,
                                const uint16_t* dw_b, const uint16_t* pw_w, const uint16_t* pw_b, uint16_t* y, int batch, int ih, int iw,
                                int oh, int ow, int pt, int pl, int q, hipStream_t stream,
-                               const SecondBlock<uint16_t>* second = nullptr);
+                               const SecondBlock<uint16_t>* second = nullptr, const ChainClear& clear = ChainClear());
 
 // The same in fp32 (block_rows.hip).
 int launch_stem_block_rows(const float* image, const float* st_w, const float* st_b, const float* dw_w, const float* dw_b, const float* pw_w,
