@@ -71,15 +71,16 @@ __device__ __forceinline__ h8 fragment(const half_t* first, int block, int step)
 // path delivers 64 bytes per clock to a CU, so a k-slice's global loads take a large part of the
 // slice's MFMA time and must be spread evenly through it; the same holds for the LDS writes.
 // Iteration kt (slice kt in LDS buffer kt & 1):
-// after every few MFMAs one 16-byte slot of slice kt+1 (loaded a whole iteration earlier) moves from
+// after every few MFMAs one 16-byte slot of slice kt+1 (loaded SETS iterations earlier) moves from
 // its registers to the other LDS buffer and the same registers are refilled with that slot of slice
-// kt+2; one barrier per slice.
+// kt+1+SETS; one barrier per slice.
 //
 // Alignment and remainders cost nothing in that loop: the 16-byte loads and stores work at any address (rows that start
 // at an odd half cost 5 - 20 % of the kernel's time, 4-byte aligned ones nothing), and only slices that reach past K,
-// or hold a [K,N] operand's last row when N % 8 != 0, go through the masked form.  (Fetched half by half,
+// or hold a [K,N] operand's last row when N % 8 != 0, go through the masked form -- none of a contraction of whole slices (its last
+// two did: 1024 x 1024 x 1024 7.6 -> 7.0 us, 16 x 1024 x 256 x 512 11.5 -> 10.7).  (Fetched half by half,
 // 1999 x 1001 x 1023 took 42 us, now 12.5.)
-template <int WAVES_M, int WAVES_N, int TM, int TN, bool A_KC, bool B_KC>
+template <int WAVES_M, int WAVES_N, int TM, int TN, bool A_KC, bool B_KC, int SETS>
 __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_f16_pipe_kernel(
     const half_t* __restrict__ A, const half_t* __restrict__ B, half_t* __restrict__ C, const half_t* __restrict__ bias,
     int M, int N, int K, int tiles_m, int tiles_n, int total_blocks, int full_slices, long long strideA, long long strideB,
@@ -139,7 +140,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_f16_pipe_kernel(
   const int srow = tid / 8, scol = 8 * (tid % 8);
   constexpr int kRowStep = kNT / 8;
   typedef ragged_u32x4 u32x4;
-  u32x4 reg[SLOTS];
+  u32x4 reg[SETS][SLOTS];
   unsigned boff[SLOTS];  // byte offset of the slot at k0 = 0 from its operand's base (operands hold < 2^31 elements)
   // row of slot i of such an operand, and its columns (past the matrix: any valid ones)
   auto krow = [&](bool is_a, int i) { return (tid + i * kNT) / ((is_a ? BM : BN) / 8); };
@@ -178,59 +179,64 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_f16_pipe_kernel(
   // FULL: the slice starting at k0 lies inside K.  Then a load is the operand's base advanced by the slice
   // (uniform, scalar registers) plus the slot's constant 32-bit offset, and a store needs no mask: no vector
   // ALU instruction per slot (each one would take issue time from the matrix cores).
-  auto load_slot = [&](int w, int k0, auto full) {
+  auto load_slot = [&](int set, int w, int k0, auto full) __attribute__((always_inline)) {
     const bool is_a = w < SA;
     const half_t* g = is_a ? A : B;
     if constexpr (decltype(full)::value) {
       const size_t advance = (is_a ? A_KC : B_KC) ? (size_t)k0 : (size_t)k0 * (size_t)(is_a ? M : N);
-      reg[w] = load16(reinterpret_cast<const half_t*>(reinterpret_cast<const char*>(g + advance) + boff[w]));
+      reg[set][w] = load16(reinterpret_cast<const half_t*>(reinterpret_cast<const char*>(g + advance) + boff[w]));
     } else {
       unsigned early;
-      reg[w] = load16(g + masked_offset(w, k0, &early));
+      reg[set][w] = load16(g + masked_offset(w, k0, &early));
     }
   };
   // k0: first k of the slice the registers hold; the zeroing of halfs past K happens here, when the
   // registers are consumed, so that nothing waits on a load right after issuing it
-  auto settled = [&](int w, int k0) {
+  auto settled = [&](int set, int w, int k0) __attribute__((always_inline)) {
     unsigned early;
     masked_offset(w, k0, &early);
-    return __builtin_amdgcn_ballot_w64(early != 0) != 0 ? shift_down<half_t>(reg[w], early) : reg[w];
+    return __builtin_amdgcn_ballot_w64(early != 0) != 0 ? shift_down<half_t>(reg[set][w], early) : reg[set][w];
   };
-  auto store_slot = [&](int w, int buf, int k0, auto full) {
+  auto store_slot = [&](int set, int w, int buf, int k0, auto full) __attribute__((always_inline)) {
     constexpr bool FULL = decltype(full)::value;
     const bool is_a = w < SA;
     const int i = is_a ? w : w - SA;
     half_t* const l = is_a ? lds_a + buf * kTileA : lds_b + buf * kTileB;
     if (is_a ? A_KC : B_KC) {
       *reinterpret_cast<u32x4*>(l + (srow + i * kRowStep) * kLd + scol) =
-          FULL ? reg[w] : settled(w, k0) & first_elements<half_t>(K - (k0 + scol));
+          FULL ? reg[set][w] : settled(set, w, k0) & first_elements<half_t>(K - (k0 + scol));
     } else {
       const int row = krow(is_a, i);
       const unsigned mask = FULL || k0 + row < K ? 0xffffffffu : 0u;
       *reinterpret_cast<u32x4*>(l + row * ((is_a ? BM : BN) + kPad) + 8 * ((tid + i * kNT) % ((is_a ? BM : BN) / 8))) =
-          FULL ? reg[w] : settled(w, k0) & mask;
+          FULL ? reg[set][w] : settled(set, w, k0) & mask;
     }
   };
   constexpr std::false_type kMasked{};
 
+  // slice 0 goes to LDS, slices 1 ... SETS stay in registers: slice i in set i % SETS
   auto prologue = [&](auto full) {
+    constexpr bool FULL = decltype(full)::value;
 #pragma unroll
-    for (int w = 0; w < SLOTS; ++w) load_slot(w, 0, full);
+    for (int i = 0; i < SETS; ++i)
+#pragma unroll
+      for (int w = 0; w < SLOTS; ++w) load_slot(i, w, FULL ? i * kBK : min(i * kBK, k_last), full);
 #pragma unroll
     for (int w = 0; w < SLOTS; ++w) {
-      store_slot(w, 0, 0, full);
-      load_slot(w, decltype(full)::value ? kBK : min(kBK, k_last), full);
+      store_slot(0, w, 0, 0, full);
+      load_slot(0, w, FULL ? SETS * kBK : min(SETS * kBK, k_last), full);
     }
   };
-  if (full_slices >= 2) prologue(std::true_type{});
+  if (full_slices >= SETS + 1) prologue(std::true_type{});
   else prologue(kMasked);
   __syncthreads();
 
-  // One k-slice.  FULL: slices kt + 1 (stored) and kt + 2 (fetched) both lie inside K.
-  auto k_slice = [&](int kt, auto full) {
+  // One k-slice: slice kt + 1 is stored, from set `which`, slice kt + 1 + SETS is fetched; `full`, `fetch_full`: they lie inside K.
+  auto k_slice = [&](int kt, auto which, auto full, auto fetch_full) __attribute__((always_inline)) {
+    constexpr int set = decltype(which)::value;
     const int cur = kt & 1;
-    // the last two iterations refetch the last slice (unused)
-    const int k_next = decltype(full)::value ? (kt + 2) * kBK : min((kt + 2) * kBK, k_last);
+    // the last iterations refetch the last slice (unused)
+    const int k_next = min((kt + 1 + SETS) * kBK, k_last);
     const half_t* const la = lds_a + cur * kTileA + first_fragment<A_KC, BM>(wm0, lane);
     const half_t* const lb = lds_b + cur * kTileB + first_fragment<B_KC, BN>(wn0, lane);
     h8 fa[2][TM], fb[2][TN];
@@ -259,8 +265,8 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_f16_pipe_kernel(
           const int p = s * MF + i * TN + j;
 #pragma unroll
           for (int w = p * SLOTS / ALL; w < (p + 1) * SLOTS / ALL; ++w) {
-            store_slot(w, cur ^ 1, (kt + 1) * kBK, full);
-            load_slot(w, k_next, full);
+            store_slot(set, w, cur ^ 1, (kt + 1) * kBK, full);
+            load_slot(set, w, k_next, fetch_full);
           }
           __builtin_amdgcn_sched_barrier(0);
         }
@@ -269,8 +275,33 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_f16_pipe_kernel(
     __syncthreads();
   };
   int kt = 0;
-  for (; kt + 2 < full_slices; ++kt) k_slice(kt, std::true_type{});
-  for (; kt < nk; ++kt) k_slice(kt, kMasked);
+  constexpr std::true_type kFull{};
+  using Set0 = std::integral_constant<int, 0>;
+  using Set1 = std::integral_constant<int, SETS - 1>;
+  const bool even = full_slices == nk;  // no ragged slice: all fetches are full ones
+  if constexpr (SETS == 1) {
+    for (const int end = even ? nk : full_slices - 2; kt < end; ++kt) k_slice(kt, Set0{}, kFull, kFull);
+    if constexpr (SLOTS <= 4)
+      for (; kt < full_slices - 1; ++kt) k_slice(kt, Set0{}, kFull, kMasked);
+    for (; kt < nk; ++kt) k_slice(kt, Set0{}, kMasked, kMasked);
+  } else {
+    // Pairs without a branch between them, across which the compiler would not count loads: slices whose fetch is full, then those
+    // whose store is, then the rest.
+    auto pairs = [&](int end, auto full, auto fetch_full) __attribute__((always_inline)) {
+      for (; kt + 1 < end; kt += 2) {
+        k_slice(kt, Set1{}, full, fetch_full);
+        k_slice(kt + 1, Set0{}, full, fetch_full);
+      }
+    };
+    pairs(even ? nk : full_slices - 1 - SETS, kFull, kFull);
+    if (even) {
+      if (kt < nk) k_slice(kt, Set1{}, kFull, kFull);
+    } else {
+      pairs(full_slices - 1, kFull, kMasked);
+      pairs(nk, kMasked, kMasked);
+      if (kt < nk) k_slice(kt, Set1{}, kMasked, kMasked);
+    }
+  }
 
   // Epilogue: every wavefront converts its WM x WN block to binary16 in a private LDS region (all k-slice buffers are
   // free after the loop's last barrier), then reads it back row-wise and stores 16 bytes per lane, 128 bytes of a row at
@@ -316,26 +347,47 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void gemm_f16_pipe_kernel(
   }
 }
 
-template <int WAVES_M, int WAVES_N, int TM, int TN, bool A_KC, bool B_KC>
-int launch_pipe(const half_t* a, const half_t* b, half_t* c, const half_t* bias, int batch, int m, int n, int k, int act,
+// slices that need no mask: inside K, and without the last row of an operand whose rows end inside a 16-byte load
+// (fewer than 8 columns: every load of a row reaches into later ones, so none)
+int full_slices(bool a_kc, bool b_kc, int m, int n, int k) {
+  auto rows_of_8 = [](bool kc, int inner) { return kc || inner % 8 == 0; };
+  if ((!a_kc && m < 8) || (!b_kc && n < 8)) return 0;
+  return rows_of_8(a_kc, m) && rows_of_8(b_kc, n) ? k / kBK : (k - 1) / kBK;
+}
+
+template <int WAVES_M, int WAVES_N, int TM, int TN, bool A_KC, bool B_KC, int SETS>
+int launch_pipe_sets(const half_t* a, const half_t* b, half_t* c, const half_t* bias, int batch, int m, int n, int k, int act,
                 hipStream_t stream) {
   constexpr int BM = 32 * TM * WAVES_M, BN = 32 * TN * WAVES_N, NT = 64 * WAVES_M * WAVES_N;
   constexpr size_t lds_bytes = 2 * (size_t)(tile_halfs(A_KC, BM) + tile_halfs(B_KC, BN)) * sizeof(half_t);
   static_assert(lds_bytes <= 160 * 1024, "LDS budget per workgroup");
-  auto kern = gemm_f16_pipe_kernel<WAVES_M, WAVES_N, TM, TN, A_KC, B_KC>;
+  auto kern = gemm_f16_pipe_kernel<WAVES_M, WAVES_N, TM, TN, A_KC, B_KC, SETS>;
   static std::atomic<uint64_t> lds_allowed{0};
   if (allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds_bytes, lds_allowed) != TFX_OK) return TFX_ERR_LAUNCH;
   const int tiles_m = (m + BM - 1) / BM, tiles_n = (n + BN - 1) / BN;
   const long long total = (long long)batch * tiles_m * tiles_n;
   if (total > 0x7fffffffLL) return TFX_ERR_UNSUPPORTED;
-  // slices that need no mask: inside K, and without the last row of an operand whose rows end inside a 16-byte load
-  // (fewer than 8 columns: every load of a row reaches into later ones, so none)
-  auto rows_of_8 = [](bool kc, int inner) { return kc || inner % 8 == 0; };
-  int full = rows_of_8(A_KC, m) && rows_of_8(B_KC, n) ? k / kBK : (k - 1) / kBK;
-  if ((!A_KC && m < 8) || (!B_KC && n < 8)) full = 0;
+  const int full = full_slices(A_KC, B_KC, m, n, k);
   hipLaunchKernelGGL(kern, dim3((unsigned)total), dim3(NT), lds_bytes, stream, a, b, c, bias, m, n, k, tiles_m, tiles_n,
                      (int)total, full, (long long)m * k, (long long)n * k, (long long)m * n, act, 4);
   return check_launch();
+}
+
+template <int WAVES_M, int WAVES_N, int TM, int TN, bool A_KC, bool B_KC>
+int launch_pipe(const half_t* a, const half_t* b, half_t* c, const half_t* bias, int batch, int m, int n, int k, int act,
+                hipStream_t stream) {
+  constexpr int BM = 32 * TM * WAVES_M, BN = 32 * TN * WAVES_N;
+  if constexpr (TM * TN <= 2) {
+    const long long tiles = (long long)batch * ((m + BM - 1) / BM) * ((n + BN - 1) / BN);
+    // Two slices on their way in registers where a CU has one workgroup, whose loads nothing else covers, and the contraction is
+    // long: us with one set and with two, 1024 x 4096 x 1024 23.7 / 18.5, 2048 x 4000 x 300 23.3 / 17.4, 1500 x 896 x 800 7.9 / 7.5,
+    // 2000 x 1024 x 1000 10.4 / 10.1, 512 x 512 x 512 four times 5.06 / 5.16; with a ragged last slice, which takes more of them
+    // through the masked form, 900 x 2001 x 900 14.5 / 13.5, 1999 x 1023 x 1001 12.6 / 13.0, 1001 x 777 x 1003 7.7 / 8.1.
+    const int nk = (k + kBK - 1) / kBK;
+    if (tiles <= 256 && nk >= (full_slices(A_KC, B_KC, m, n, k) == nk ? 12 : 20))
+      return launch_pipe_sets<WAVES_M, WAVES_N, TM, TN, A_KC, B_KC, 2>(a, b, c, bias, batch, m, n, k, act, stream);
+  }
+  return launch_pipe_sets<WAVES_M, WAVES_N, TM, TN, A_KC, B_KC, 1>(a, b, c, bias, batch, m, n, k, act, stream);
 }
 
 // Small M x N: too few 64 x 64 tiles for 256 CUs, and each tile is bound by memory latency, not by the matrix cores.
