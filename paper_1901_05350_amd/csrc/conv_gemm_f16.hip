@@ -7,8 +7,8 @@
 // Products are accumulated in fp32 (v_mfma_f32_32x32x16_f16), the result is rounded once.
 //
 // The loop is the software pipeline of gemm_f16_pipe_kernel: k-slices of 64 halfs are double-buffered in LDS as
-// K-contiguous rows of 144 bytes; while slice kt is multiplied, one 16-byte slot after another of slice kt + 1 (fetched a
-// whole iteration earlier) moves from registers to the other LDS buffer and is refilled from slice kt + 2, spread between
+// K-contiguous rows of 144 bytes; while slice kt is multiplied, one 16-byte slot after another of slice kt + 1 (fetched
+// SETS iterations earlier) moves from registers to the other LDS buffer and is refilled from slice kt + 1 + SETS, spread between
 // the MFMAs.  The filter is stored [K, Co] and keeps its k-rows in LDS; its fragments are read with the transposing LDS load (as turned
 // in registers, 4 k-rows x 8 columns a thread, its 8-byte LDS writes were waited for: 4 % less over 63 aligned convolutions with the
 // tiles as they were).  Tiles of 64 x 128 and 128 x 128 have 8 wavefronts, 64 x 64 and 128 x 32 ones 4: 10 % less over 334 convolutions (3x3,
@@ -66,7 +66,7 @@ __device__ __forceinline__ KPos k_position(const ConvArgs& g, int kk) {
 }
 
 // WAVES_M x WAVES_N wavefronts, each TM x TN blocks of 32 x 32.
-template <int WAVES_M, int WAVES_N, int TM, int TN, Form FORM>
+template <int WAVES_M, int WAVES_N, int TM, int TN, Form FORM, int SETS>
 __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void conv_f16_gemm_kernel(ConvArgs g) {
   constexpr int kNT = 64 * WAVES_M * WAVES_N;
   constexpr int WM = 32 * TM, WN = 32 * TN, BM = WM * WAVES_M, BN = WN * WAVES_N;
@@ -128,7 +128,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void conv_f16_gemm_kernel(C
   };
   auto slice_at = [&](int kt) {
     Slice s;
-    s.k0 = min(kt, g.slices - 1) * kBK;  // the last two iterations fetch the last slice again (unused)
+    s.k0 = min(kt, g.slices - 1) * kBK;  // the last iterations fetch the last slice again (unused)
     s.a = k_position(g, FORM == kLean ? s.k0 : s.k0 + scol);
     if constexpr (FORM == kRagged) {
 #pragma unroll
@@ -162,38 +162,38 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void conv_f16_gemm_kernel(C
     return off;
   };
 
-  u32x4 reg[SLOTS];
-  bool inside[SLOTS];  // kRagged: whether the slot in the registers is one (else zeros)
+  u32x4 reg[SETS][SLOTS];  // slices on their way
+  bool inside[SETS][SLOTS];  // kRagged: whether the slot in the registers is one (else zeros)
   // returns nonzero in a lane whose slot was fetched early
-  auto load_slot = [&](int w, const Slice& s) {
+  auto load_slot = [&](int set, int w, const Slice& s) __attribute__((always_inline)) {
     unsigned early;
-    const unsigned off = slot_offset(w, s, &early, &inside[w]);
+    const unsigned off = slot_offset(w, s, &early, &inside[set][w]);
     // (a buffer load that is not 16-byte aligned is slower than a global one: 3x3, 60x60x100 -> 100 at batch 20 77 against 57 us)
-    if constexpr (FORM == kRagged) reg[w] = load16((w < SA ? g.x : g.w) + off);
-    else reg[w] = __builtin_amdgcn_raw_buffer_load_b128(w < SA ? xr : wr, inside[w] ? (int)(2u * off) : (int)kOutside, 0, 0);
+    if constexpr (FORM == kRagged) reg[set][w] = load16((w < SA ? g.x : g.w) + off);
+    else reg[set][w] = __builtin_amdgcn_raw_buffer_load_b128(w < SA ? xr : wr, inside[set][w] ? (int)(2u * off) : (int)kOutside, 0, 0);
     return early;
   };
   // once per slice, almost never taken (the last rows of a tensor): shifts what was fetched early down
-  auto settle = [&](const Slice& s, unsigned any_early) {
+  auto settle = [&](int set, const Slice& s, unsigned any_early) __attribute__((always_inline)) {
     if (FORM != kRagged || __builtin_amdgcn_ballot_w64(any_early != 0) == 0) return;
 #pragma unroll
     for (int w = 0; w < SLOTS; ++w) {
       unsigned early;
       bool in;
       slot_offset(w, s, &early, &in);
-      reg[w] = shift_down<half_t>(reg[w], early);
+      reg[set][w] = shift_down<half_t>(reg[set][w], early);
     }
   };
-  auto masked = [&](int w, const u32x4& mask) {
-    if constexpr (FORM != kRagged) return reg[w];
+  auto masked = [&](int set, int w, const u32x4& mask) __attribute__((always_inline)) {
+    if constexpr (FORM != kRagged) return reg[set][w];
     const u32x4 zero = {0u, 0u, 0u, 0u};
-    return inside[w] ? (w < SA ? reg[w] & mask : reg[w]) : zero;
+    return inside[set][w] ? (w < SA ? reg[set][w] & mask : reg[set][w]) : zero;
   };
-  auto store_slot = [&](int w, int buf, const u32x4& mask) {
+  auto store_slot = [&](int set, int w, int buf, const u32x4& mask) __attribute__((always_inline)) {
     if (w < SA) {
-      *reinterpret_cast<u32x4*>(lds_a + buf * kTileA + (srow + kRowStep * w) * kLd + scol) = masked(w, mask);
+      *reinterpret_cast<u32x4*>(lds_a + buf * kTileA + (srow + kRowStep * w) * kLd + scol) = masked(set, w, mask);
     } else {
-      *reinterpret_cast<u32x4*>(lds_b + buf * kTileB + (brow + kRowsB * (w - SA)) * kLdB + bcol8) = masked(w, mask);
+      *reinterpret_cast<u32x4*>(lds_b + buf * kTileB + (brow + kRowsB * (w - SA)) * kLdB + bcol8) = masked(set, w, mask);
     }
   };
   // Fragment of 32 columns x 16 k: lane (li, hh) gets 8 consecutive k from 8 hh on of column li.  The transposing load gives lane i
@@ -216,29 +216,37 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void conv_f16_gemm_kernel(C
       for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
 
   // valid halfs of the A slots in the registers (kRagged)
-  int valid;
-  {
-    const Slice first = slice_at(0), second = slice_at(1);
+  int valid[SETS];
+  auto fetch = [&](int set, int kt) __attribute__((always_inline)) {
+    const Slice at = slice_at(kt);
     unsigned early = 0;
 #pragma unroll
-    for (int w = 0; w < SLOTS; ++w) early |= load_slot(w, first);
-    settle(first, early);
-    early = 0;
-    const u32x4 mask = first_elements<half_t>(first.a.valid);
+    for (int w = 0; w < SLOTS; ++w) early |= load_slot(set, w, at);
+    settle(set, at, early);
+    valid[set] = at.a.valid;
+  };
+  // slice 0 goes to LDS, slices 1 ... SETS stay in registers: slice i in set i % SETS
+#pragma unroll
+  for (int i = 0; i < SETS; ++i) fetch(i, i);
+  {
+    const u32x4 mask = first_elements<half_t>(valid[0]);
+    const Slice at = slice_at(SETS);
+    unsigned early = 0;
 #pragma unroll
     for (int w = 0; w < SLOTS; ++w) {
-      store_slot(w, 0, mask);
-      early |= load_slot(w, second);
+      store_slot(0, w, 0, mask);
+      early |= load_slot(0, w, at);
     }
-    settle(second, early);
-    valid = second.a.valid;
+    settle(0, at, early);
+    valid[0] = at.a.valid;
   }
   __syncthreads();
 
-  for (int kt = 0; kt < g.slices; ++kt) {
+  auto k_slice = [&](int kt, auto which) __attribute__((always_inline)) {
+    constexpr int set = decltype(which)::value;  // of slice kt + 1
     const int cur = kt & 1;
-    const Slice after = slice_at(kt + 2);
-    const u32x4 mask = first_elements<half_t>(valid);
+    const Slice after = slice_at(kt + 1 + SETS);
+    const u32x4 mask = first_elements<half_t>(valid[set]);
     unsigned early = 0;
     const half_t* la = lds_a + cur * kTileA + (wm0 + li) * kLd + 8 * hh;
     const half_t* lb = lds_b + cur * kTileB + (8 * hh + lane % 16 / 4) * kLdB + wn0 + 16 * (lane / 16 % 2) + 4 * (lane % 4);
@@ -267,17 +275,24 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void conv_f16_gemm_kernel(C
           const int p = s * MF + i * TN + j;
 #pragma unroll
           for (int w = p * SLOTS / ALL; w < (p + 1) * SLOTS / ALL; ++w) {
-            store_slot(w, cur ^ 1, mask);
-            early |= load_slot(w, after);
+            store_slot(set, w, cur ^ 1, mask);
+            early |= load_slot(set, w, after);
           }
           __builtin_amdgcn_sched_barrier(0);
         }
       }
     }
-    settle(after, early);
-    valid = after.a.valid;
+    settle(set, after, early);
+    valid[set] = after.a.valid;
     __syncthreads();
-  }
+  };
+  int kt = 0;  // (pairs without a branch between them, across which the compiler would not count loads)
+  if constexpr (SETS == 2)
+    for (; kt + 1 < g.slices; kt += 2) {
+      k_slice(kt, std::integral_constant<int, 1>{});
+      k_slice(kt + 1, std::integral_constant<int, 0>{});
+    }
+  for (; kt < g.slices; ++kt) k_slice(kt, std::integral_constant<int, SETS - 1>{});
 
   // acc[i][j][v] is the output at row m0 + wm0 + 32 i + li, column n0 + wn0 + 32 j + 8 (v / 4) + 4 hh + v % 4.  Every
   // wavefront converts its block to binary16 in a private LDS region (the slice buffers are free after the loop's last
@@ -325,18 +340,28 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N) void conv_f16_gemm_kernel(C
   }
 }
 
-template <int WAVES_M, int WAVES_N, int TM, int TN, Form FORM>
-int launch(ConvArgs& g, hipStream_t stream) {
+template <int WAVES_M, int WAVES_N, int TM, int TN, Form FORM, int SETS>
+int launch_sets(ConvArgs& g, hipStream_t stream) {
   constexpr int BM = 32 * TM * WAVES_M, BN = 32 * TN * WAVES_N;
   constexpr size_t lds_bytes = 2 * (size_t)(BM * kLd + kBK * (BN + kPad)) * sizeof(half_t);
   const long long tiles_m = (g.M + (long long)BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
   if (tiles_m * tiles_n > 0x7fffffffLL) return TFX_ERR_UNSUPPORTED;
-  auto kern = conv_f16_gemm_kernel<WAVES_M, WAVES_N, TM, TN, FORM>;
+  auto kern = conv_f16_gemm_kernel<WAVES_M, WAVES_N, TM, TN, FORM, SETS>;
   static std::atomic<uint64_t> lds_allowed{0};
   if (allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds_bytes, lds_allowed) != TFX_OK) return TFX_ERR_LAUNCH;
   g.tiles_n = (int)tiles_n, g.total_blocks = (int)(tiles_m * tiles_n);
   hipLaunchKernelGGL(kern, dim3((unsigned)g.total_blocks), dim3(64 * WAVES_M * WAVES_N), lds_bytes, stream, g);
   return check_launch();
+}
+template <int WAVES_M, int WAVES_N, int TM, int TN, Form FORM>
+int launch(ConvArgs& g, hipStream_t stream) {
+  constexpr int BM = 32 * TM * WAVES_M, BN = 32 * TN * WAVES_N;
+  const long long tiles = ((g.M + (long long)BM - 1) / BM) * ((g.N + BN - 1) / BN);
+  // Two slices on their way in registers where a CU has one workgroup, whose loads nothing else covers, and the contraction is
+  // long: 3x3, 8x14x14x512 -> 512 27.7 -> 21.1 us, 28x28x512 -> 512 27.7 -> 20.6, 2x64x64x256 -> 96 14.8 -> 13.4, 6x24x24x129 -> 257
+  // 17.9 -> 17.6; none of 19 from 12 slices on slower.
+  if (tiles <= 256 && g.slices >= 12) return launch_sets<WAVES_M, WAVES_N, TM, TN, FORM, 2>(g, stream);
+  return launch_sets<WAVES_M, WAVES_N, TM, TN, FORM, 1>(g, stream);
 }
 
 }  // namespace
