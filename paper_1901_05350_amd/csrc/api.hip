@@ -151,7 +151,7 @@ BlockPlan plan_blocks_f16(const tfx_mobilenet_v1_variant& v, int64_t batch) {
 
 // The same for fp32.  kBlock: patches with the whole block in registers (block.hip), one to three images.  One image's pass is chained;
 // where it stops at a feature map or may not be chained, its blocks take kBlock, kStream or kTwo.
-enum BlockForm32 { kTwo32, kPatch32, kBlock32, kStream32, kTile32 };
+enum BlockForm32 { kTwo32, kPatch32, kBlock32, kStream32, kTile32, kStem32 };
 struct BlockPlan32 {
   BlockForm32 form[kBlocks], without[kBlocks];  // without: what a tile block is where there is no room for its filter
   int tiles, c[kBlocks], n[kBlocks];
@@ -190,6 +190,10 @@ BlockPlan32 plan_blocks(const tfx_mobilenet_v1_variant& v, int64_t batch) {
                    : fits(separable_stream_supported) ? kStream32
                                                       : kTwo32;
     p.form[b] = tile && (p.without[b] == kTwo32 ? many : wide && p.without[b] == kStream32) ? kTile32 : p.without[b];
+    // The second block with the stem, us a pass, separate and together: full width 3 images 147 / 143, 8 191 / 187, 64 570 / 523; 3/4 width
+    // 16 of 192 x 192 221 / 201; half width 32 200 / 194; quarter width 32 155 / 138.  Below 9000 pixels few strips of few rows, which
+    // compute most of theirs twice: 2 images 110 / 111, 4 of 128 x 128 96 / 100, 3 of 96 x 96 87 / 93.
+    if (b == 1 && batch > 1 && batch * out * out >= 9000 && stem_two_blocks_supported(hw, q)) p.form[b] = p.without[b] = kStem32;
     if (p.form[b] == kTile32) ++p.tiles;
     // (room for the wide block's at any batch: a workspace is large enough for every smaller batch, one image apart)
     if (p.form[b] == kTile32 || (tile && c == 128 && n == 128 && p.form[b] == kStream32)) {
@@ -569,15 +573,23 @@ int forward_impl(const tfx_mobilenet_v1_variant* variant, const float* input, in
     flags_cleared = true;
   } else {
     // stem and first block in one launch that walks down rows (block_rows.hip)
+    // (and the second, which the plan then says)
+    const int64_t fd2[4] = {3, 3, c0, 1}, map[4] = {batch, g.out[1], g.out[2], c0};
+    ConvGeom g2;
+    conv_geometry(map, fd2, kStrides[1], kStrides[1], TFX_PAD_SAME, true, &g2);
+    const SecondBlock<float> second{weights->dw_w[1], weights->dw_b[1], weights->pw_w[1], weights->pw_b[1],
+                                    (int)g2.out[1], (int)g2.out[2], (int)g2.pad[0], (int)g2.pad[2]};
+    first_block = plan.blocks.form[1] == kStem32 && end_block != 1 ? 2 : 1;
     rc = launch_stem_block_rows(input, weights->conv0_w, weights->conv0_b, weights->dw_w[0], weights->dw_b[0], weights->pw_w[0],
-                                weights->pw_b[0], end_block == 1 ? features : buf[0], (int)batch, (int)shape[1], (int)shape[2],
-                                (int)g.out[1], (int)g.out[2], (int)g.pad[0], (int)g.pad[2], q, static_cast<hipStream_t>(stream));
-    first_block = 1;
+                                weights->pw_b[0], end_block == first_block ? features : buf[0], (int)batch, (int)shape[1], (int)shape[2],
+                                (int)g.out[1], (int)g.out[2], (int)g.pad[0], (int)g.pad[2], q, static_cast<hipStream_t>(stream),
+                                first_block == 2 ? &second : nullptr);
+    if (first_block == 2) g = g2;
   }
   if (rc) return rc;
   for (int i = 0; i < 4; ++i) shape[i] = g.out[i];
-  if (first_block == 1) shape[3] = c0;
-  if (first_block == 1 && end_block == 1) return TFX_OK;
+  if (first_block > 0) shape[3] = kChannels[first_block - 1] * q / 4;
+  if (first_block > 0 && end_block == first_block) return TFX_OK;
   int cur = 0;
   if (head_chain && flags_cleared && first_block == 1) {
     // blocks 2 - 4 as three stages of one launch, block 5 as a launch of its own, then the chained kernel from block 6

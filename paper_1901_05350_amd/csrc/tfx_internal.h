@@ -404,7 +404,8 @@ int launch_stem_block_rows_f16(const uint16_t* image, const uint16_t* st_w, cons
 // The same in fp32 (block_rows.hip).
 int launch_stem_block_rows(const float* image, const float* st_w, const float* st_b, const float* dw_w, const float* dw_b, const float* pw_w,
                            const float* pw_b, float* y, int batch, int ih, int iw, int oh, int ow, int pt, int pl, int q,
-                           hipStream_t stream);
+                           hipStream_t stream, const SecondBlock<float>* second = nullptr);
+bool stem_two_blocks_supported(int ow, int q);  // whether it takes a second block behind a map of ow columns
 
 inline int check_launch() { return hipGetLastError() == hipSuccess ? TFX_OK : TFX_ERR_LAUNCH; }
 

@@ -1,0 +1,78 @@
+"""fp32 networks whose second block runs in the stem's launch (block_rows.hip): maps of odd and even extents, ragged last columns, strips
+of odd length, values that the split of the second pointwise product does not carry."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_1901_05350_amd import inputs
+from util import assert_close, dev, host
+
+pytestmark = pytest.mark.gpu
+
+
+def features(d, batch, size, q, weights=None):
+    """The map of block 2 for `batch` copies of the images in turn, and the oracle's for each image."""
+    import paper_1901_05350_amd as tfx
+    w = weights or d["weights"]
+    ref = oracle.mobilenet_v1_forward(d["image"], w, return_activations=True)[2][4]
+    model = tfx.MobileNetV1(w, batch=batch, image_size=size, width_quarters=q)
+    count = d["image"].shape[0]
+    image = np.concatenate([d["image"]] * ((batch + count - 1) // count))[:batch]
+    return host(model.features(dev(image), 2)), ref
+
+
+@pytest.mark.parametrize("q,size,batch", [(4, 224, 3), (4, 97, 15), (3, 192, 4), (3, 101, 15), (2, 66, 33), (2, 255, 3), (1, 130, 9), (1, 256, 3),
+                                          (3, 256, 3), (4, 64, 36), (4, 225, 3)])
+def test_two_blocks_with_the_stem(q, size, batch):
+    d = inputs.mobilenet_v1(seed=93, batch=2, image_size=size, width_quarters=q, classes=10)
+    got, ref = features(d, batch, size, q)
+    for i in range(batch):
+        assert_close(got[i], ref[i % 2], "image %d" % i)
+
+
+@pytest.mark.parametrize("q", [1, 3, 4])
+@pytest.mark.parametrize("what", ["a tiny value in a column", "a column of tiny values", "a large value", "all tiny", "tiny maps"])
+def test_values_outside_the_split(q, what):
+    size, batch = 128, 9
+    d = inputs.mobilenet_v1(seed=94, batch=1, image_size=size, width_quarters=q, classes=10)
+    w = {k: ([t.copy() for t in v] if isinstance(v, list) else v.copy()) for k, v in d["weights"].items()}
+    f = w["pw_w"][1][0, 0]
+    w["pw_b"][1][:] = 0
+    if what == "a tiny value in a column":
+        f[3, 5] = 3e-38
+    elif what == "a column of tiny values":
+        f[:, 7] = np.float32(1e-38) * np.arange(1, f.shape[0] + 1, dtype=np.float32)
+    elif what == "a large value":
+        f[2, 9] = 3e7
+    elif what == "all tiny":
+        f *= np.float32(1e-37)
+    else:
+        w["dw_w"][1] *= np.float32(1e-37)
+        w["dw_b"][1][:] = 0
+    got, ref = features(d, batch, size, q, w)
+    for i in range(batch):
+        # a result made of tiny values is right in its own size
+        scale = np.abs(ref[0]).max(axis=(0, 1))
+        scale = np.where(scale > 0, scale, 1).astype(np.float64)
+        assert_close(got[i].astype(np.float64) / scale, ref[0] / scale, what)
+
+
+@pytest.mark.parametrize("where", ["image", "pw_w", "dw_w", "pw_b"])
+def test_nan_and_inf(where):
+    """What a NaN or an infinity reaches, and nothing else."""
+    size, batch, q = 128, 9, 4
+    d = inputs.mobilenet_v1(seed=95, batch=2, image_size=size, width_quarters=q, classes=10)
+    for value in (np.nan, np.inf, -np.inf):
+        w = {k: ([t.copy() for t in v] if isinstance(v, list) else v.copy()) for k, v in d["weights"].items()}
+        image = d["image"].copy()
+        if where == "image":
+            image[1, 40, 51, 2] = value
+        else:
+            w[where][1].reshape(-1, w[where][1].shape[-1] if where != "dw_w" else w[where][1].shape[2])[0, 6] = value
+        got, ref = features(dict(d, image=image), batch, size, q, w)
+        for i in range(batch):
+            r = ref[i % 2]
+            assert np.array_equal(np.isnan(got[i]), np.isnan(r)), (where, value, i)
+            ok = ~np.isnan(r)
+            if ok.any():  # (a NaN of the depthwise filter reaches every output)
+                assert_close(got[i][ok], r[ok], "%s %s" % (where, value))
