@@ -15,7 +15,7 @@ OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libtfx.so")
 CALL = os.path.join(HERE, "_call.so")
 SOURCES = ["api.hip", "gemm.hip", "pointwise.hip", "conv.hip", "depthwise.hip", "tail.hip", "elementwise.hip", "gemm_f16.hip", "gemm_deep.hip", "gemm_direct.hip", "gemm_thin.hip", "conv_f16.hip", "pointwise_f16.hip", "pointwise_slab_f16.hip", "conv_gemm_f16.hip", "conv_stream_f16.hip", "chain.hip", "block.hip", "block_stream.hip", "block_tile.hip", "block_stream_f16.hip", "block_tile_f16.hip", "block_patch.hip", "block_patch_f16.hip", "block_rows_f16.hip", "block_rows.hip", "conv_window.hip"]
-HEADERS = [os.path.join(CSRC, "tfx_internal.h"), os.path.join(CSRC, "stream_f16.h"), os.path.join(CSRC, "ragged.h"), os.path.join(CSRC, "split.h"), os.path.join(CSRC, "pair.h"), os.path.join(CSRC, "kernel_cost.h"), os.path.join(HERE, "..", "include", "tfx.h")]
+HEADERS = [os.path.join(CSRC, "tfx_internal.h"), os.path.join(CSRC, "stream_f16.h"), os.path.join(CSRC, "ragged.h"), os.path.join(CSRC, "split.h"), os.path.join(CSRC, "pair.h"), os.path.join(CSRC, "pack.h"), os.path.join(CSRC, "kernel_cost.h"), os.path.join(HERE, "..", "include", "tfx.h")]
 FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-Wall", "-Wno-unused-function",
          # packed fp32 VALU ops are kept off on this target
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",

@@ -1,6 +1,7 @@
 // C ABI of libtfx: argument validation, shape rules and kernel selection.
 // Every entry point validates on the host before any HIP call and then only enqueues
 // kernels on the caller's stream (enqueue-and-return, as the ops of Section 3.6 / 4.1).
+#include "pack.h"
 #include "tfx_internal.h"
 
 namespace tfx {
@@ -546,6 +547,18 @@ int forward_impl(const tfx_mobilenet_v1_variant* variant, const float* input, in
     }
   }
 
+  const int blocks = end_block ? end_block : kBlocks;
+  const BlockPlan32& form = plan.blocks;  // of the whole network: a feature map is the one a pass computes
+  auto aligned = [&](int b) {  // else the block runs as two launches, which take any element
+    bool ok = true;
+    for (const void* p : {weights->dw_w[b], weights->dw_b[b], weights->pw_w[b], weights->pw_b[b]})
+      ok = ok && reinterpret_cast<uintptr_t>(p) % 16 == 0;
+    return ok;
+  };
+  PackList filters;  // of the tile blocks, in their order from the stem's launch on (more than one image)
+  for (int b = 1; b < blocks; ++b)
+    if (form.tiles > 0 && form.form[b] == kTile32 && aligned(b)) filters.add(weights->pw_w[b], ws + plan.off_packed + form.packed[b], form.c[b], form.n[b]);
+
   // stem: 3x3 stride-2 convolution to 32 alpha channels, then the 13 depthwise-separable blocks
   int64_t shape[4] = {batch, variant->image_size, variant->image_size, 3};
   const int64_t f0[4] = {3, 3, 3, kStemChannels * q / 4};
@@ -583,7 +596,7 @@ int forward_impl(const tfx_mobilenet_v1_variant* variant, const float* input, in
     rc = launch_stem_block_rows(input, weights->conv0_w, weights->conv0_b, weights->dw_w[0], weights->dw_b[0], weights->pw_w[0],
                                 weights->pw_b[0], end_block == first_block ? features : buf[0], (int)batch, (int)shape[1], (int)shape[2],
                                 (int)g.out[1], (int)g.out[2], (int)g.pad[0], (int)g.pad[2], q, static_cast<hipStream_t>(stream),
-                                first_block == 2 ? &second : nullptr);
+                                first_block == 2 ? &second : nullptr, filters);
     if (first_block == 2) g = g2;
   }
   if (rc) return rc;
@@ -628,26 +641,6 @@ int forward_impl(const tfx_mobilenet_v1_variant* variant, const float* input, in
       return launch_chain(b5_out, (int)variant->image_size, weights, chain_ws, probs, logits, (int)variant->classes, q,
                           static_cast<hipStream_t>(stream), launch_head, &head, 5);
     }
-  }
-  const int blocks = end_block ? end_block : kBlocks;
-  const BlockPlan32& form = plan.blocks;  // of the whole network: a feature map is the one a pass computes
-  auto aligned = [&](int b) {  // else the block runs as two launches, which take any element
-    bool ok = true;
-    for (const void* p : {weights->dw_w[b], weights->dw_b[b], weights->pw_w[b], weights->pw_b[b]})
-      ok = ok && reinterpret_cast<uintptr_t>(p) % 16 == 0;
-    return ok;
-  };
-  if (form.tiles > 0) {
-    const float* filters[kBlocks];
-    void* packed[kBlocks];
-    int tiles = 0, c[kBlocks], n[kBlocks];
-    for (int b = first_block; b < blocks; ++b)
-      if (form.form[b] == kTile32 && aligned(b)) {
-        filters[tiles] = weights->pw_w[b], packed[tiles] = ws + plan.off_packed + form.packed[b];
-        c[tiles] = form.c[b], n[tiles] = form.n[b];
-        ++tiles;
-      }
-    if (tiles > 0 && (rc = launch_pack_filters(tiles, filters, packed, c, n, static_cast<hipStream_t>(stream)))) return rc;
   }
   for (int b = first_block; b < blocks; ++b) {
     float* const block_out = end_block == b + 1 ? features : buf[cur ^ 1];

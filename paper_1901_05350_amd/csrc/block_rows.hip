@@ -13,6 +13,7 @@
 // at a time by a filter that lies split in LDS.  That takes a CU's LDS for one workgroup, whose seven wavefronts issue on 1.75 SIMDs
 // each: 64 images of 224 x 224 at full width 102 us, bound by issue and latency (a row 3 us), where this launch and the second block's
 // took 73 + 62 and moved the 205 MB between them twice; 8 images 24.6 and 32.7.
+#include "pack.h"
 #include "split.h"
 
 namespace tfx {
@@ -29,6 +30,7 @@ struct RowsArgs {
   // the second block, where it comes too
   const float *dw2_w, *dw2_b, *pw2_w, *pw2_b;
   int OH2, OW2, pt2, pl2;
+  int strip_groups;  // workgroups with strips
 };
 
 // Pixel stride of the ring in 16-byte pieces: the least without bank conflicts when lane (li, q) reads piece q of pixel li.
@@ -65,13 +67,17 @@ struct SecondLds {
       : map(0), halo(16 * t * PX), filter(halo + 2 * t * N), taps(filter + KS * NB2 * kParts * 64 * 4), end(taps + 9 * N) {}
 };
 
-template <int Q, bool TWO>
-__global__ __launch_bounds__(512, 2) void stem_block_rows_kernel(RowsArgs g) {
+// Filters: PackList (TWO only: the passes that have some), for workgroups behind the strips' ones to put in order, or NoFilters.
+struct NoFilters {};
+template <int Q, bool TWO, typename Filters>
+__global__ __launch_bounds__(512, 2) void stem_block_rows_kernel(RowsArgs g, Filters filters) {
   using L2 = SecondLds<Q>;
   __shared__ __align__(16) float dw2_bias[TWO ? L2::N : 4], pw2_bias[TWO ? L2::N2 : 4];
   __shared__ int odd_filter2;  // bit 0: bits lost, bit 1: a large value
   constexpr int C = 8 * Q, N = 16 * Q, NB = Q, G = (C + 15) / 16, PX = 4 * rows_pixel_pieces<Q, TWO>();
   extern __shared__ __align__(16) float ring[];  // [4][16 T + 2][PX]: stem row r in slot r % 4, column c at c + 1
+  if constexpr (std::is_same_v<Filters, PackList>)
+    if ((int)blockIdx.x >= g.strip_groups) return pack_filters<5>(filters, (int)blockIdx.x - g.strip_groups, ring);
   // what a step reads once or twice stays in LDS
   __shared__ __align__(16) float stem_w[7][64][G], stem_bias[16 * G], dw_bias[16 * G], pw_bias[N];
   const int lane = threadIdx.x % 64, li = lane % 16, q = lane / 16;
@@ -476,6 +482,11 @@ __global__ __launch_bounds__(512, 2) void stem_block_rows_kernel(RowsArgs g) {
   }
 }
 
+__global__ __launch_bounds__(1024) void pack_filters_kernel(PackList filters) {
+  __shared__ float scratch[kPackScratch / sizeof(float)];
+  pack_filters<2, 16>(filters, (int)blockIdx.x, scratch);
+}
+
 constexpr int kRowsMaxWidth = 128;  // columns of the map: 8 wavefronts of 16
 
 template <int Q, bool TWO>
@@ -491,16 +502,25 @@ constexpr int rows_max_tiles() {
   return t;
 }
 
-template <int Q, bool TWO>
-int launch_rows(const RowsArgs& g, int batch, hipStream_t stream) {
-  auto kern = stem_block_rows_kernel<Q, TWO>;
+template <int Q, bool TWO, typename Filters>
+int launch_rows_kernel(const RowsArgs& g, int groups, const Filters& filters, hipStream_t stream) {
+  auto kern = stem_block_rows_kernel<Q, TWO, Filters>;
   const int tiles = (g.OW + 15) / 16;
   // The kernel is allowed once what its widest rows need: a later call may be wider than the first.
   static std::atomic<uint64_t> lds_allowed{0};
   constexpr size_t most = rows_lds_bytes<Q, TWO>(rows_max_tiles<Q, TWO>());
   if (allow_dynamic_lds(reinterpret_cast<const void*>(kern), most, lds_allowed) != TFX_OK) return TFX_ERR_LAUNCH;
-  hipLaunchKernelGGL(kern, dim3((unsigned)(batch * g.strips)), dim3(64u * tiles), (rows_lds_bytes<Q, TWO>(tiles)), stream, g);
+  static_assert(!TWO || rows_lds_bytes<Q, TWO>(1) >= kPackScratch, "room to order the filters");
+  hipLaunchKernelGGL(kern, dim3((unsigned)groups), dim3(64u * tiles), (rows_lds_bytes<Q, TWO>(tiles)), stream, g, filters);
   return check_launch();
+}
+
+// filters: null, or what workgroups of this launch put in order
+template <int Q>
+int launch_rows(const RowsArgs& g, bool two, const PackList* filters, hipStream_t stream) {
+  if (!two) return launch_rows_kernel<Q, false>(g, g.strip_groups, NoFilters(), stream);
+  if (filters == nullptr) return launch_rows_kernel<Q, true>(g, g.strip_groups, NoFilters(), stream);
+  return launch_rows_kernel<Q, true>(g, g.strip_groups + filters->groups(), *filters, stream);
 }
 
 }  // namespace
@@ -512,7 +532,7 @@ bool stem_two_blocks_supported(int ow, int q) {
 
 int launch_stem_block_rows(const float* image, const float* st_w, const float* st_b, const float* dw_w, const float* dw_b, const float* pw_w,
                            const float* pw_b, float* y, int batch, int ih, int iw, int oh, int ow, int pt, int pl, int q,
-                           hipStream_t stream, const SecondBlock<float>* second) {
+                           hipStream_t stream, const SecondBlock<float>* second, const PackList& filters) {
   const int out_rows = second ? second->oh : oh;
   const long long in = (long long)ih * iw * 3, out = second ? (long long)second->oh * second->ow * 32 * q : (long long)oh * ow * 16 * q;  // floats of an image
   if (ow > kRowsMaxWidth || iw < 3 || ih < 3 || reinterpret_cast<uintptr_t>(y) % 16 != 0) return TFX_ERR_UNSUPPORTED;
@@ -543,17 +563,27 @@ int launch_stem_block_rows(const float* image, const float* st_w, const float* s
     }
     RowsArgs g{image + first * in, st_w, st_b, dw_w, dw_b, pw_w, pw_b, y + first * out, ih, iw, oh, ow, pt, pl, strips,
                (out_rows + strips - 1) / strips, (unsigned)(4 * in), (unsigned)(4 * images * in), (unsigned)(4 * images * out),
-               nullptr, nullptr, nullptr, nullptr, 0, 0, 0, 0};
+               nullptr, nullptr, nullptr, nullptr, 0, 0, 0, 0, images * strips};
     if (second) {
       g.dw2_w = second->dw_w, g.dw2_b = second->dw_b, g.pw2_w = second->pw_w, g.pw2_b = second->pw_b;
       g.OH2 = second->oh, g.OW2 = second->ow, g.pt2 = second->pt, g.pl2 = second->pl;
     }
+    // The tile blocks' filters: workgroups of this launch where it leaves CUs idle, and with 7 wavefronts and more, which hold a column of
+    // 1024 rows in one go; else a launch of its own.  us a pass, so and in this launch: full width 224 x 224 4 images 150.6 / 146.2, 8 187.0 /
+    // 186.3, 16 242.9 / 238.9, 64 513.3 / 511.5, 192 x 192 12 images 200.1 / 192.7, 160 x 160 8 images 160.2 / 154.6; but, without idle CUs,
+    // 160 x 160 48 images 311 / 315, 96 x 96 64 images 242 / 249.
+    const bool with = first == 0 && second && filters.groups() > 0 && (tiles >= 7 || images * strips <= slots / 8 * 7);
+    const PackList* const list = with ? &filters : nullptr;
     int rc = TFX_ERR_UNSUPPORTED;
-    if (q == 1) rc = second ? launch_rows<1, true>(g, images, stream) : launch_rows<1, false>(g, images, stream);
-    if (q == 2) rc = second ? launch_rows<2, true>(g, images, stream) : launch_rows<2, false>(g, images, stream);
-    if (q == 3) rc = second ? launch_rows<3, true>(g, images, stream) : launch_rows<3, false>(g, images, stream);
-    if (q == 4) rc = second ? launch_rows<4, true>(g, images, stream) : launch_rows<4, false>(g, images, stream);
+    if (q == 1) rc = launch_rows<1>(g, second != nullptr, list, stream);
+    if (q == 2) rc = launch_rows<2>(g, second != nullptr, list, stream);
+    if (q == 3) rc = launch_rows<3>(g, second != nullptr, list, stream);
+    if (q == 4) rc = launch_rows<4>(g, second != nullptr, list, stream);
     if (rc) return rc;
+    if (first == 0 && filters.groups() > 0 && !with) {
+      hipLaunchKernelGGL(pack_filters_kernel, dim3((unsigned)filters.groups()), dim3(1024), 0, stream, filters);
+      if (const int bad = check_launch()) return bad;
+    }
   }
   return TFX_OK;
 }

@@ -4,7 +4,7 @@
 // The pointwise layer is a product on the binary16 matrix cores with operands split in two (pair.h).  A workgroup owns a tile of 32 TM
 // output pixels, as patches of 4 x 2, and 64 columns for each of its groups of wavefronts; all its threads compute the depthwise
 // output of the tile into LDS, split, and each wavefront multiplies the tile by its 64 columns of the filter, whose operands it loads
-// straight from L2 in the order of pack_filters_kernel.
+// straight from L2 in the order of pack_filters (pack.h).
 //
 // 64 x 14 x 14 x 512 -> 512, one layer: 33.6 us, of which 5.4 are the start and the launch, 9.5 the depthwise layer, 14.3 the contraction
 // (a megabyte of the filter for each CU through the path from L2, 73 GB/s to each; the matrix cores would take 8), 4.4 the stores; the
@@ -25,7 +25,7 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int kXcds = 8, kMaxLayers = 13;
+constexpr int kXcds = 8;
 
 struct TileArgs {
   const float *x, *dw_w, *dw_b, *pw_w, *pw_b;
@@ -177,7 +177,7 @@ __global__ __launch_bounds__(512) void separable_tile_kernel(const float* x, con
 
   asm volatile("" ::"v"(touched));
   __builtin_amdgcn_sched_barrier(0);
-  // the filter's operands, in the order of pack_filters_kernel
+  // the filter's operands, in the order of pack_filters (pack.h)
   const int n0 = first_n + 64 * wn;
   const int steps = C / 16, s0 = steps / WK * part, s1 = s0 + steps / WK;
   const __amdgpu_buffer_rsrc_t wr = __builtin_amdgcn_make_buffer_rsrc(const_cast<half_t*>(g.packed), 0, C * N * 4, 0x00020000);
@@ -368,72 +368,6 @@ __global__ __launch_bounds__(512) void separable_tile_kernel(const float* x, con
   }
 }
 
-// The operands of the contraction's k-step s (rows 16 s ... + 15) and 64 columns from 64 c on, for each lane: 8 rows from
-// 8 (lane / 32) on of column 32 j + lane % 32, part p, at piece 64 (4 (steps c + s) + 2 j + p) + lane; behind them for each column
-// 2^17 times the exponent of its scale, plus its losses (pair.h).  A workgroup for every 16 columns
-// (for every 32, twice the loads of a wavefront behind its first: the pass of 8 images 192.1 us, 190.0 so).
-struct PackArgs {
-  const float* w[kMaxLayers];
-  half_t* out[kMaxLayers];
-  int* exps[kMaxLayers];
-  int c[kMaxLayers], n[kMaxLayers], first[kMaxLayers + 1];  // first: workgroups of the layers before
-  int layers;
-};
-__global__ __launch_bounds__(1024) void pack_filters_kernel(PackArgs g) {
-  __shared__ float wave_most[16][16];
-  __shared__ int lost[16], tiny[16];
-  int l = 0;
-  while (l + 1 < g.layers && (int)blockIdx.x >= g.first[l + 1]) ++l;
-  const int wave = threadIdx.x / 64, lane = threadIdx.x % 64, li = lane % 16, q = lane / 16;
-  const int N = g.n[l], steps = g.c[l] / 16;
-  int nb = (int)blockIdx.x - g.first[l];
-  if (N % 256 == 0 && g.first[l] % 8 == 0) nb = nb / 16 * 16 + nb % 8 * 2 + nb / 8 % 2;  // the two halves of a line on one XCD
-  const int n = 16 * nb + li;
-  constexpr int MOST = 2;  // pairs of steps of a wavefront, of up to 32: lane (li, q) has rows 8 (q % 2) ... of step q / 2 of the pair
-  float v[MOST][8];
-  float most = 0.f;
-#pragma unroll
-  for (int u = 0; u < MOST; ++u) {
-    const int s = min(2 * (wave + 16 * u) + q / 2, steps - 1);
-#pragma unroll
-    for (int i = 0; i < 8; ++i) v[u][i] = g.w[l][(size_t)(16 * s + 8 * (q % 2) + i) * N + n];
-  }
-#pragma unroll
-  for (int u = 0; u < MOST; ++u)
-#pragma unroll
-    for (int i = 0; i < 8; ++i) most = __builtin_isfinite(v[u][i]) ? fmaxf(most, fabsf(v[u][i])) : most;
-  most = fmaxf(most, __shfl_xor(most, 32));
-  most = fmaxf(most, __shfl_xor(most, 16));
-  if (q == 0) wave_most[wave][li] = most;
-  if (threadIdx.x < 16) lost[threadIdx.x] = tiny[threadIdx.x] = 0;
-  __syncthreads();
-#pragma unroll
-  for (int w = 0; w < 16; ++w) most = fmaxf(most, wave_most[w][li]);
-  const int e = column_exponent(most);
-  int loses = 0;
-#pragma unroll
-  for (int u = 0; u < MOST; ++u) {
-    const int s = 2 * (wave + 16 * u) + q / 2;
-    if (s >= steps) break;
-    h8 part[2];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      half_t a, b;
-      loses = more_lost(loses, split_filter(v[u][i], e, a, b));
-      part[0][i] = a, part[1][i] = b;
-    }
-    h8* const out = reinterpret_cast<h8*>(g.out[l]) + (size_t)64 * (4 * (steps * (nb / 4) + s) + 2 * (nb / 2 % 2)) + 32 * (q % 2) + 16 * (nb % 2) + li;
-    out[0] = part[0];
-    out[64] = part[1];
-  }
-  if (loses != 0) {
-    atomicAdd(&lost[li], loses & kLostMost);
-    if ((loses & kLostTiny) != 0) atomicOr(&tiny[li], kLostTiny);
-  }
-  __syncthreads();
-  if (threadIdx.x < 16) g.exps[l][n] = (e << 17) | lost[li] | tiny[li];
-}
-
 size_t tile_lds(int tm, int waves_n, int wk, int c) {
   const size_t depth = (size_t)32 * tm * (c + 8) * 2 * sizeof(half_t), sums = wk == 1 ? 0 : (size_t)waves_n * wk * 32 * 64 * sizeof(float);
   return depth > sums ? depth : sums;
@@ -523,21 +457,6 @@ int launch_separable_tile(const float* x, const float* dw_w, const float* dw_b, 
   TFX_TILE(2, 1, 4)
 #undef TFX_TILE
   return TFX_ERR_UNSUPPORTED;
-}
-
-int launch_pack_filters(int layers, const float* const* w, void* const* packed, const int* c, const int* n, hipStream_t stream) {
-  PackArgs g{};
-  if (layers > kMaxLayers) return TFX_ERR_UNSUPPORTED;
-  for (int i = 0; i < layers; ++i) {
-    g.w[i] = w[i];
-    g.out[i] = static_cast<half_t*>(packed[i]);
-    g.exps[i] = reinterpret_cast<int*>(g.out[i] + (size_t)2 * c[i] * n[i]);
-    g.c[i] = c[i], g.n[i] = n[i];
-    g.first[i + 1] = g.first[i] + n[i] / 16;
-  }
-  g.layers = layers;
-  hipLaunchKernelGGL(pack_filters_kernel, dim3((unsigned)g.first[layers]), dim3(1024), 0, stream, g);
-  return check_launch();
 }
 
 }  // namespace tfx

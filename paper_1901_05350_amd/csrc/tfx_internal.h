@@ -354,14 +354,13 @@ int launch_separable_patch(const float* x, const float* dw_w, const float* dw_b,
                            hipStream_t stream);
 
 // A block whose pointwise filter does not fit LDS, with a tile's depthwise output there instead (block_tile.hip); its activation is
-// relu6.  `packed`: separable_tile_packed_bytes(c, n), 16-byte aligned, as launch_pack_filters (up to 13 layers) filled it.
+// relu6.  `packed`: separable_tile_packed_bytes(c, n), 16-byte aligned, in the order of pack.h.
 size_t separable_tile_packed_bytes(int c, int n);
 bool separable_tile_supported(int batch, int h, int w, int c, int n, int stride, int oh, int ow, const void* x, const void* dw_w,
                               const void* dw_b, const void* pw_w, const void* pw_b, const void* y);
 int launch_separable_tile(const float* x, const float* dw_w, const float* dw_b, const float* pw_w, const float* pw_b, const void* packed,
                           float* y, int batch, int h, int w, int c, int n, int oh, int ow, int stride, int pt, int pl, int pw_act,
                           hipStream_t stream);
-int launch_pack_filters(int layers, const float* const* w, void* const* packed, const int* c, const int* n, hipStream_t stream);
 
 // The same on binary16 storage (block_stream_f16.hip).
 bool separable_stream_f16_supported(int batch, int h, int w, int c, int n, int stride, int oh, int ow, const void* x,
@@ -401,10 +400,10 @@ int launch_stem_block_rows_f16(const uint16_t* image, const uint16_t* st_w, cons
                                int oh, int ow, int pt, int pl, int q, hipStream_t stream,
                                const SecondBlock<uint16_t>* second = nullptr, const ChainClear& clear = ChainClear());
 
-// The same in fp32 (block_rows.hip).
+// The same in fp32 (block_rows.hip); it also puts the filters of later tile blocks in their order (pack.h).
 int launch_stem_block_rows(const float* image, const float* st_w, const float* st_b, const float* dw_w, const float* dw_b, const float* pw_w,
                            const float* pw_b, float* y, int batch, int ih, int iw, int oh, int ow, int pt, int pl, int q,
-                           hipStream_t stream, const SecondBlock<float>* second = nullptr);
+                           hipStream_t stream, const SecondBlock<float>* second, const struct PackList& filters);
 bool stem_two_blocks_supported(int ow, int q);  // whether it takes a second block behind a map of ow columns
 
 inline int check_launch() { return hipGetLastError() == hipSuccess ? TFX_OK : TFX_ERR_LAUNCH; }

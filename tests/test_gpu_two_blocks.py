@@ -76,3 +76,18 @@ def test_nan_and_inf(where):
             ok = ~np.isnan(r)
             if ok.any():  # (a NaN of the depthwise filter reaches every output)
                 assert_close(got[i][ok], r[ok], "%s %s" % (where, value))
+
+
+@pytest.mark.parametrize("q,size,batch,end_block", [(4, 192, 12, 13), (4, 160, 8, 9), (4, 128, 24, 11), (3, 200, 16, 10), (4, 224, 4, 9)])
+def test_filters_put_in_order_by_the_same_launch(q, size, batch, end_block):
+    """Tile blocks behind it, against the same blocks of one image: 4 to 7 wavefronts, filters of up to 1024 rows (read in two parts by 6)."""
+    import paper_1901_05350_amd as tfx
+    d = inputs.mobilenet_v1(seed=96, batch=2, image_size=size, width_quarters=q, classes=10)
+    model = tfx.MobileNetV1(d["weights"], batch=batch, image_size=size, width_quarters=q)
+    one = tfx.MobileNetV1(d["weights"], batch=1, image_size=size, width_quarters=q)
+    model.workspace.fill_(255)
+    got = host(model.features(dev(np.concatenate([d["image"]] * (batch // 2))), end_block))
+    for i in (0, 1):
+        ref = host(one.features(dev(d["image"][i:i + 1]), end_block))
+        for j in range(i, batch, 2):
+            assert_close(got[j:j + 1], ref, "image %d" % j)
