@@ -303,11 +303,12 @@ typedef struct {
   const uint16_t* fc_b;
 } tfx_mobilenet_v1_weights_f16;
 
-/* Workspace bytes of tfx_mobilenet_v1_forward_f16 (0 if the variant or batch is invalid). */
+/* Workspace bytes of tfx_mobilenet_v1_forward_f16 (0 if the variant or batch is invalid); large enough for one image too. */
 size_t tfx_mobilenet_v1_workspace_bytes_f16(const tfx_mobilenet_v1_variant* variant, int64_t batch);
 
 /* input: device [batch,image_size,image_size,3] binary16; probs / logits: device
- * [batch,classes] binary16 (logits may be NULL); workspace as for the fp32 entry point. */
+ * [batch,classes] binary16 (logits may be NULL); workspace as for the fp32 entry point.  One image's blocks from
+ * the fifth or sixth on run as one kernel whose workgroups wait for each other, as there. */
 int tfx_mobilenet_v1_forward_f16(const tfx_mobilenet_v1_variant* variant, const uint16_t* input, int64_t batch,
                                  const tfx_mobilenet_v1_weights_f16* weights, void* workspace,
                                  size_t workspace_bytes, uint16_t* probs, uint16_t* logits, void* stream);

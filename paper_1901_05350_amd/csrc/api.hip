@@ -735,7 +735,9 @@ int tfx_mobilenet_v1_variant_forward_static(const tfx_mobilenet_v1_variant* vari
 
 size_t tfx_mobilenet_v1_workspace_bytes_f16(const tfx_mobilenet_v1_variant* variant, int64_t batch) {
   if (!valid_variant(variant) || batch < 1 || batch > 1024) return 0;
-  return plan_net(*variant, batch, sizeof(uint16_t)).bytes;
+  // (one image may need more than a few: the chained kernel's memory)
+  const size_t one = plan_net(*variant, 1, sizeof(uint16_t)).bytes, all = plan_net(*variant, batch, sizeof(uint16_t)).bytes;
+  return one > all ? one : all;
 }
 
 }  // extern "C"

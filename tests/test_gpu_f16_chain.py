@@ -93,3 +93,18 @@ def test_captured_and_on_two_streams():
                 models[i].forward(images[i])
     for i in range(2):
         assert np.array_equal(host(models[i].logits), want[i])
+
+
+def test_one_image_in_a_workspace_of_two():
+    import ctypes
+    import torch
+    import paper_1901_05350_amd as tfx
+    from paper_1901_05350_amd import binding
+    d = inputs.mobilenet_v1_f16(seed=87, batch=1, image_size=96, width_quarters=2, classes=10)
+    probs, logits = oracle.mobilenet_v1_forward_f16(d["image"], d["weights"])
+    model = tfx.MobileNetV1F16(d["weights"], batch=1, image_size=96, width_quarters=2)
+    size = tfx.lib().tfx_mobilenet_v1_workspace_bytes_f16(ctypes.byref(binding.TfxVariant(96, 2, 10)), 2)
+    model.workspace = torch.full((size,), 255, dtype=torch.uint8, device="cuda:0")
+    p, l = model.forward(dev16(d["image"]))
+    bar(host(l), logits, 8, "logits")
+    bar(host(p), probs, 16, "probs")
