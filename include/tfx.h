@@ -209,7 +209,10 @@ size_t tfx_mobilenet_v1_workspace_bytes(int64_t batch);
  * as one kernel; the workgroups of these two kernels hand results to each other
  * through words of the workspace.  Every wait in them is bounded, and if one ever
  * gives up (a workgroup that never got to run) every output of the call is NaN
- * rather than a number computed from unfinished data.
+ * rather than a number computed from unfinished data.  Calls on several streams are
+ * ordered against each other where the device does not hold their workgroups at once;
+ * replays of captured full-width calls of one image on several streams are the
+ * caller's to order.
  * input: device [batch,224,224,3]; workspace: device, >= the size above, 256-byte
  * aligned, contents undefined before and after; probs: device [batch,1000];
  * logits: device [batch,1000] or NULL.  All kernels are enqueued on `stream`. */
@@ -308,7 +311,8 @@ size_t tfx_mobilenet_v1_workspace_bytes_f16(const tfx_mobilenet_v1_variant* vari
 
 /* input: device [batch,image_size,image_size,3] binary16; probs / logits: device
  * [batch,classes] binary16 (logits may be NULL); workspace as for the fp32 entry point.  One image's blocks from
- * the fifth or sixth on run as one kernel whose workgroups wait for each other, as there. */
+ * the fifth or sixth on run as one kernel whose workgroups wait for each other, as there, but none has to be running
+ * for another one to end: calls and replays of captured calls may overlap on any streams. */
 int tfx_mobilenet_v1_forward_f16(const tfx_mobilenet_v1_variant* variant, const uint16_t* input, int64_t batch,
                                  const tfx_mobilenet_v1_weights_f16* weights, void* workspace,
                                  size_t workspace_bytes, uint16_t* probs, uint16_t* logits, void* stream);

@@ -530,7 +530,7 @@ int forward_impl(const tfx_mobilenet_v1_variant* variant, const float* input, in
     flags_ok = al16(input) && al16(weights->conv0_b) && al16(weights->fc_w) && al16(weights->fc_b);
     for (int i = 0; i < kBlocks && flags_ok; ++i)
       flags_ok = al16(weights->dw_w[i]) && al16(weights->dw_b[i]) && al16(weights->pw_w[i]) && al16(weights->pw_b[i]);
-    flags_ok = flags_ok && chain_resident(q);
+    flags_ok = flags_ok && chain_grids(q) > 0;
   }
   const bool chain = flags_ok && end_block == 0;
   // blocks 2 - 4 as stages of one launch and block 5 as a launch (block.hip): in the whole pass and when block 4's
@@ -773,7 +773,7 @@ int forward_f16_impl(const tfx_mobilenet_v1_variant* variant, const uint16_t* in
       aligned = aligned && reinterpret_cast<uintptr_t>(p) % 16 == 0;
   // One image: the blocks from the fifth or sixth on and the tail as one persistent kernel, as in fp32
   const int chain_first = q == 4 ? 5 : 4;
-  const bool chain = aligned && end_block == 0 && plan.chain && reinterpret_cast<uintptr_t>(weights->fc_w) % 16 == 0 && chain_resident(q, true);
+  const bool chain = aligned && end_block == 0 && plan.chain && reinterpret_cast<uintptr_t>(weights->fc_w) % 16 == 0 && chain_grids(q, true) > 0;
   const int separate = chain ? chain_first : blocks;  // blocks that are launches
   uint16_t* const packed_base = reinterpret_cast<uint16_t*>(ws + plan.off_packed);
   if (aligned && form.tiles > 0) {

@@ -35,12 +35,17 @@
 // the memory side, loads do not hit a stale line).  Filters and biases are read-only and use ordinary cached loads; they are
 // fetched before the wait.
 //
-// Every wait is bounded: a poll loop gives up after kSpinLimit rounds (seconds), sets a failure word that makes
-// every other wait give up too, and the softmax task then writes NaN to every output, so a workgroup that was
-// never scheduled cannot hang the GPU and cannot yield plausible numbers.  The grid (256 workgroups, one per CU) is
-// only launched where all of it is resident at once (chain_resident), and two such kernels never run side by side
-// in one process: launch_chain orders them across streams (see there), because two half-resident grids would wait
-// for workgroups that the other one keeps from being scheduled.
+// No workgroup has to be resident for another one to end (but in fp32 at full width, see kLeaves): a workgroup whose input does not come
+// for kPatience polls (who has it to write is not running) leaves its tasks, and then computes every task of every step itself, in order,
+// where each input is one that it has written before.  What is written twice is written with the same bits.  So any number of these
+// kernels may run side by side -- replays of captured passes on several streams, other processes -- and grids that keep each other's
+// workgroups from the CUs end late, by 6 - 9 ms, but right.  (Binary16, one image, us: full width 224 x 224 62.7 without, 62.9 with, 3/4
+// width 192 x 192 54.4, 54.6.)  The grid (256 workgroups, one per CU) is launched where all of it is resident at once (chain_grids), and
+// launch_chain orders calls across streams such that no more of them run than the device holds: only replays of captured passes come to that.
+//
+// Every wait is bounded besides: a poll loop gives up after kSpinLimit rounds (seconds), sets a failure word that makes
+// every other wait give up too, and the softmax task then writes NaN to every output: no hang, and no plausible numbers.
+#include <algorithm>
 #include <cstdlib>
 #include <mutex>
 
@@ -58,8 +63,10 @@ constexpr int kChainGrid = 256;
 constexpr int kChainBlocks = 9;       // at most blocks 5 .. 13 of the network (0-based 4 .. 12)
 constexpr int kFirstChainBlock = 4;   // a launch starts there or one block later (both read a 1/8-size map of 256 channels)
 constexpr int kSpinLimit = 1 << 22;  // polls before a wait gives up (each poll is a memory round trip: seconds)
+constexpr int kPatience = 4096;      // polls before a workgroup computes what it waits for itself (milliseconds)
 constexpr int kFcSliceChannels = 128;  // input channels of the fully connected layer per task (2 to 8 slices)
 constexpr int kFcColBlock = 128;      // classes per fully connected task
+constexpr int kFcTasks = 64;          // at most: 8 slices x 8 blocks of classes
 constexpr unsigned kEmpty = ~0u;       // a word of the chain's memory that no task has written yet
 constexpr int kSc1 = 16;              // cache-policy operand of the buffer builtins: device-coherent access
 
@@ -126,6 +133,7 @@ struct ChainParams {
   T *probs, *logits;
   int classes, feat, last_hw;
   int spin_limit;       // polls before a wait gives up
+  int patience;         // and before the workgroup does everything itself
   int nblocks;          // blocks in blk[]
 };
 
@@ -148,24 +156,53 @@ __device__ __forceinline__ void st_f32x2(__amdgpu_buffer_rsrc_t r, unsigned byte
   __builtin_amdgcn_raw_buffer_store_b64(u32x2{word_of(a), word_of(b)}, r, (int)byte_off, 0, kSc1);
 }
 
+// Whether a kernel's workgroups leave the tasks whose input does not come.  Full width in fp32 do not: their pass has a launch in front
+// (blocks 2 - 4 as stages, block.hip) whose workgroups have to be resident anyway, and 78.2 us would be 78.8.
+template <typename T, int Q>
+constexpr bool kLeaves = sizeof(T) == 2 || Q < 4;
+
+// What bounds this wavefront's waits.
+template <bool LEAVES>
+struct Waits {
+  int* failed;     // a wait has given up (device memory)
+  int spin_limit, patience;
+  int* left;       // in LDS, set where this wavefront leaves a task because its input did not come
+};
+
 // Runs load(), which fetches what this lane needs and says whether any word of it is still empty, until no lane of the wavefront
-// misses any.  Bounded: a wait that gives up sets the failure word, which ends every other wait soon.
-template <typename F>
-__device__ __forceinline__ void load_written(int* failed, int spin_limit, F load) {
+// misses any; false: they did not come.  A wait that gives up sets the failure word, which ends every other wait soon.
+template <bool LEAVES, typename F>
+__device__ __forceinline__ bool load_written(Waits<LEAVES>& waits, F load) {
+  const int most = LEAVES ? min(__builtin_amdgcn_readfirstlane(waits.patience), waits.spin_limit) : waits.spin_limit;
   int spin = 0;
-  while (__builtin_amdgcn_ballot_w64(load()) != 0) {
-    if (++spin > spin_limit) {
-      __hip_atomic_store(failed, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      break;
+  while (__builtin_expect(__builtin_amdgcn_ballot_w64(load()) != 0, 0)) {
+    if (spin >= most || ((++spin & 255) == 0 && __builtin_amdgcn_readfirstlane(__hip_atomic_load(waits.failed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) != 0)) {
+      if (spin >= waits.spin_limit) __hip_atomic_store(waits.failed, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (!LEAVES) return true;  // (what is computed of it is NaN in the end)
+      waits.patience = 0;  // the wavefront's other tasks are left at once
+      *waits.left = 1;
+      return false;
     }
-    if ((spin & 255) == 0 && __hip_atomic_load(failed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) break;
     asm volatile("" ::: "memory");
   }
+  return true;
+}
+
+// `word` is one of kChainWaves in LDS, a wavefront's own; behind a barrier: whether a wavefront's is `value`.
+__device__ __forceinline__ bool any_wave(const int* word, int value) {
+  return __builtin_amdgcn_ballot_w64(word[threadIdx.x % kChainWaves] == value) != 0;
+}
+// Whether a pointwise task's result v stands for a sum of words that have not come: they are empty, which as a value is a NaN.  (Nothing
+// is looked up for any other result.)
+template <bool LEAVES>
+__device__ __forceinline__ bool not_computed(float v, const int* left, int task) {
+  return LEAVES && __builtin_amdgcn_ballot_w64(v != v) != 0 && any_wave(left, task) && v != v;
 }
 
 // ---- depthwise 3x3 + bias + ReLU6: 16 output pixels x 32 channels, one output per thread ----
 // wait: the input comes from a task of this launch
-__device__ __forceinline__ void dw_task(const ChainParams<float>& P, const ChainBlock<float>& B, int r, int c, bool wait,
+template <bool LEAVES>
+__device__ __forceinline__ void dw_task(Waits<LEAVES>& waits, const ChainBlock<float>& B, int r, int c, bool wait,
                                         __amdgpu_buffer_rsrc_t in, __amdgpu_buffer_rsrc_t act) {
   const int m_out = B.out_hw * B.out_hw;
   const int t = threadIdx.x, px = (t / 32) % 16, ch = 32 * c + t % 32;
@@ -191,7 +228,7 @@ __device__ __forceinline__ void dw_task(const ChainParams<float>& P, const Chain
       // a tap outside the image reads past the end of the buffer: the hardware returns 0, no branch
       off[kh * 3 + kw] = ok[kh * 3 + kw] ? (B.in_off + (unsigned)((iy * B.in_hw + ix) * B.cin + ch)) * 4u : 0x80000000u;
     }
-  load_written(P.failed, P.spin_limit, [&]() __attribute__((always_inline)) {
+  const bool have = load_written(waits, [&]() __attribute__((always_inline)) {
     unsigned most = 0;
 #pragma unroll
     for (int k = 0; k < 9; ++k) {
@@ -206,14 +243,15 @@ __device__ __forceinline__ void dw_task(const ChainParams<float>& P, const Chain
   ActClamp clamp;
   clamp.on = true;
   clamp.hi = 6.0f;
-  if (live) st_f32(act, (B.mid_off + (unsigned)(p * B.cin + ch)) * 4u, apply_act(acc, clamp));
+  if (have && live) st_f32(act, (B.mid_off + (unsigned)(p * B.cin + ch)) * 4u, apply_act(acc, clamp));
 }
 
 // The same on halfs: 16 output pixels x 64 channels, two (a word) per thread, sums in fp32 and one rounding.
 __device__ __forceinline__ unsigned half_bits(half_t v) { return v == v ? (unsigned)__builtin_bit_cast(unsigned short, v) : 0x7e00u; }
 __device__ __forceinline__ unsigned word_of(float a, float b) { return half_bits((half_t)a) | half_bits((half_t)b) << 16; }
 typedef _Float16 h2 __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ void dw_task(const ChainParams<half_t>& P, const ChainBlock<half_t>& B, int r, int c, bool wait,
+template <bool LEAVES>
+__device__ __forceinline__ void dw_task(Waits<LEAVES>& waits, const ChainBlock<half_t>& B, int r, int c, bool wait,
                                         __amdgpu_buffer_rsrc_t in, __amdgpu_buffer_rsrc_t act) {
   const int m_out = B.out_hw * B.out_hw;
   const int t = threadIdx.x, px = (t / 32) % 16, ch = 64 * c + 2 * (t % 32);
@@ -234,7 +272,7 @@ __device__ __forceinline__ void dw_task(const ChainParams<half_t>& P, const Chai
     ok[k] = live && iy >= 0 && iy < B.in_hw && ix >= 0 && ix < B.in_hw;
     off[k] = ok[k] ? (B.in_off + (unsigned)((iy * B.in_hw + ix) * B.cin + ch)) * 2u : 0x80000000u;  // (past the end: 0)
   }
-  load_written(P.failed, P.spin_limit, [&]() __attribute__((always_inline)) {
+  const bool have = load_written(waits, [&]() __attribute__((always_inline)) {
     unsigned most = 0;
 #pragma unroll
     for (int k = 0; k < 9; ++k) v[k] = ld_word(in, off[k]), most = max(most, v[k]);
@@ -251,16 +289,16 @@ __device__ __forceinline__ void dw_task(const ChainParams<half_t>& P, const Chai
   ActClamp clamp;
   clamp.on = true;
   clamp.hi = 6.0f;
-  if (live)
+  if (have && live)
     __builtin_amdgcn_raw_buffer_store_b32(word_of(apply_act(acc[0], clamp), apply_act(acc[1], clamp)), act,
                                           (int)((B.mid_off + (unsigned)(p * B.cin + ch)) * 2u), 0, kSc1);
 }
 
 // ---- pointwise 1x1 + bias + ReLU6: 16 x (16 TN) tile, K = WAVES x CHUNK split over the first WAVES 
 // wavefronts (all 8 where K is a multiple of 128; 4 for the K = 64 and K = 192 of the narrower networks) ----
-template <int CHUNK, int TN, int WAVES>
-__device__ __forceinline__ void pw_task(const ChainParams<float>& P, const ChainBlock<float>& B, int tile_m, int tile_n,
-                                        __amdgpu_buffer_rsrc_t act, float* red) {
+template <int CHUNK, int TN, int WAVES, bool LEAVES>
+__device__ __forceinline__ void pw_task(Waits<LEAVES>& waits, const ChainBlock<float>& B, int tile_m, int tile_n,
+                                        __amdgpu_buffer_rsrc_t act, float* red, int* left, int task) {
   constexpr int G = CHUNK / 16;
   const int K = B.cin, N = B.cout, M = B.out_hw * B.out_hw;
   const int tid = threadIdx.x, wk = (tid / 64) % kChainWaves, lane = tid % 64, li = lane % 16, q = lane / 16;
@@ -298,9 +336,9 @@ __device__ __forceinline__ void pw_task(const ChainParams<float>& P, const Chain
     u32x4 a[G];
     {  // a word of each depthwise task first: eight wavefronts' whole operands, asked for again and again, keep the memory busy
       const unsigned last = (B.mid_off + (unsigned)(min(m0 + 15, M - 1) * K + wk * CHUNK + 32 * (li % ((CHUNK + 31) / 32)))) * 4u;
-      load_written(P.failed, P.spin_limit, [&]() __attribute__((always_inline)) { return ld_word(act, last) == kEmpty; });
+      (void)load_written(waits, [&]() __attribute__((always_inline)) { return ld_word(act, last) == kEmpty; });
     }
-    load_written(P.failed, P.spin_limit, [&]() __attribute__((always_inline)) {
+    const bool have = load_written(waits, [&]() __attribute__((always_inline)) {
       unsigned most = 0;
 #pragma unroll
       for (int g = 0; g < G; ++g) {
@@ -309,6 +347,7 @@ __device__ __forceinline__ void pw_task(const ChainParams<float>& P, const Chain
       }
       return most == kEmpty;
     });
+    if (!have) left[wk] = task;
 
     floatx4 acc[2][TN];
 #pragma unroll
@@ -331,7 +370,7 @@ __device__ __forceinline__ void pw_task(const ChainParams<float>& P, const Chain
       for (int v = 0; v < 4; ++v) red[((wk * TN + j) * 4 + v) * 64 + lane] = acc[0][j][v] + acc[1][j][v];
   }
   __syncthreads();
-  if (tid < 256 && erow < M) {
+  if (tid < 256) {
     ActClamp clamp;
     clamp.on = true;
     clamp.hi = 6.0f;
@@ -343,6 +382,7 @@ __device__ __forceinline__ void pw_task(const ChainParams<float>& P, const Chain
       for (int w = 0; w < WAVES; ++w) sum += red[((w * TN + j) * 4 + ev) * 64 + el];
       o[j] = apply_act(sum, clamp);
     }
+    if (not_computed<LEAVES>(o[0], left, task) || erow >= M) return;
     const unsigned off = (B.out_off + (unsigned)(erow * N + ecol)) * 4u;
     if constexpr (TN == 2) st_f32x2(act, off, o[0], o[1]);
     else st_f32(act, off, o[0]);
@@ -351,9 +391,9 @@ __device__ __forceinline__ void pw_task(const ChainParams<float>& P, const Chain
 
 // The same on halfs, 32 values of K an instruction.  A filter value is one of a lane's eight of consecutive rows: words of two columns
 // (single halfs with TN == 1) come from eight rows and are put together in registers.
-template <int CHUNK, int TN, int WAVES>
-__device__ __forceinline__ void pw_task(const ChainParams<half_t>& P, const ChainBlock<half_t>& B, int tile_m, int tile_n,
-                                        __amdgpu_buffer_rsrc_t act, float* red) {
+template <int CHUNK, int TN, int WAVES, bool LEAVES>
+__device__ __forceinline__ void pw_task(Waits<LEAVES>& waits, const ChainBlock<half_t>& B, int tile_m, int tile_n,
+                                        __amdgpu_buffer_rsrc_t act, float* red, int* left, int task) {
   constexpr int G = CHUNK / 32;
   const int K = B.cin, N = B.cout, M = B.out_hw * B.out_hw;
   const int tid = threadIdx.x, wk = (tid / 64) % kChainWaves, lane = tid % 64, li = lane % 16, q = lane / 16;
@@ -384,9 +424,9 @@ __device__ __forceinline__ void pw_task(const ChainParams<half_t>& P, const Chai
     u32x4 a[G];
     {  // (a word of each depthwise task first, as above)
       const unsigned last = (B.mid_off + (unsigned)(min(m0 + 15, M - 1) * K + wk * CHUNK + 32 * (li % G))) * 2u;
-      load_written(P.failed, P.spin_limit, [&]() __attribute__((always_inline)) { return ld_word(act, last) == kEmpty; });
+      (void)load_written(waits, [&]() __attribute__((always_inline)) { return ld_word(act, last) == kEmpty; });
     }
-    load_written(P.failed, P.spin_limit, [&]() __attribute__((always_inline)) {
+    const bool have = load_written(waits, [&]() __attribute__((always_inline)) {
       unsigned most = 0;
 #pragma unroll
       for (int g = 0; g < G; ++g) {
@@ -395,6 +435,7 @@ __device__ __forceinline__ void pw_task(const ChainParams<half_t>& P, const Chai
       }
       return most == kEmpty;
     });
+    if (!have) left[wk] = task;
 
     floatx4 acc[2][TN] = {};
 #pragma unroll
@@ -427,7 +468,7 @@ __device__ __forceinline__ void pw_task(const ChainParams<half_t>& P, const Chai
     }
     // (TN == 1: the next lane's column, for the even ones; a word is written whole)
     if constexpr (TN == 1) o[1] = __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(o[0]), 0xb1, 0xf, 0xf, true));
-    if (erow < M && (TN == 2 || el % 2 == 0))
+    if (!not_computed<LEAVES>(o[0], left, task) && erow < M && (TN == 2 || el % 2 == 0))
       __builtin_amdgcn_raw_buffer_store_b32(word_of(o[0], o[1]), act, (int)((B.out_off + (unsigned)(erow * N + ecol)) * 2u), 0, kSc1);
   }
 }
@@ -448,17 +489,17 @@ __device__ __forceinline__ float block_sum_or_max(float v, bool is_max, float* s
 }
 
 // The pointwise task for a layer of K input channels: the K split, and 32-column tiles only below K = 1024.
-template <typename T, int K>
-__device__ __forceinline__ void pw_task_for(const ChainParams<T>& P, const ChainBlock<T>& B, int r, int c,
-                                            __amdgpu_buffer_rsrc_t act, float* red) {
+template <typename T, int K, bool LEAVES>
+__device__ __forceinline__ void pw_task_for(Waits<LEAVES>& waits, const ChainBlock<T>& B, int r, int c,
+                                            __amdgpu_buffer_rsrc_t act, float* red, int* left, int task) {
   constexpr int STEP = sizeof(T) == 2 ? 32 : 16;  // a wavefront takes whole steps
   constexpr int WAVES = K % (8 * STEP) == 0 ? 8 : sizeof(T) == 2 && K % (6 * STEP) == 0 ? 6 : K % (4 * STEP) == 0 ? 4 : 2;
   constexpr int CHUNK = K / WAVES;
   static_assert(CHUNK % STEP == 0 && CHUNK <= 128, "a wavefront takes whole steps of K");
   if constexpr (K < 1024) {
-    if (B.tn == 2) return pw_task<CHUNK, 2, WAVES>(P, B, r, c, act, red);
+    if (B.tn == 2) return pw_task<CHUNK, 2, WAVES>(waits, B, r, c, act, red, left, task);
   }
-  pw_task<CHUNK, 1, WAVES>(P, B, r, c, act, red);
+  pw_task<CHUNK, 1, WAVES>(waits, B, r, c, act, red, left, task);
 }
 
 // Four weights of the fully connected layer as they are stored.
@@ -480,12 +521,15 @@ struct FcWeights<half_t> {
 template <typename T, int Q>
 __global__ __launch_bounds__(kChainThreads) void mobilenet_chain_kernel(const ChainParams<T> P) {
   constexpr int kSlices = 2 * Q;
-  constexpr bool kHalf = sizeof(T) == 2;
+  constexpr bool kHalf = sizeof(T) == 2, kMayLeave = kLeaves<T, Q>;
   // 2 x 16 KB: split-K partial tiles, of one task and the next (between a task's reads and the writes of the task after the next lies
   // the barrier of the next); reused by the tail
   __shared__ float red2[2][kChainWaves * 2 * 4 * 64];
+  // Each wavefront's own: whether it has left a task of the steps, of the last one, and by turn the number of a pointwise task that it left.
+  __shared__ int left[4][kChainWaves];
   const int wg = blockIdx.x, tid = threadIdx.x;
-  int turn = 0;
+  if (kMayLeave && tid % 64 < 4) left[tid % 64][tid / 64] = 0;
+  Waits<kMayLeave> waits{P.failed, P.spin_limit, P.patience, &left[0][tid / 64]};
   {
     // The block descriptors are read at every block change, on the critical path, and the first touch of a line of
     // the kernel argument segment misses the scalar cache: touch every line now.
@@ -522,104 +566,125 @@ __global__ __launch_bounds__(kChainThreads) void mobilenet_chain_kernel(const Ch
     }
   };
   if (wg < fc_tasks) load_fc(wg, fw);
-  for (int bi = 0; bi < P.nblocks; ++bi) {
-    const ChainBlock<T>& B = P.blk[bi];
-    const TaskMap &dw_map = B.dw_map, &pw_map = B.pw_map;
-    for (int vt = wg; vt < dw_map.count; vt += kChainGrid) {
-      int r, c;
-      if (task_of(dw_map, vt, &r, &c)) dw_task(P, B, r, c, bi > 0, bi == 0 ? in0 : act, act);
+  // tasks first, first + stride, ... of every step
+  int count = 0;
+  auto steps = [&](int first, int stride) __attribute__((always_inline)) {
+    for (int bi = 0; bi < P.nblocks; ++bi) {
+      const ChainBlock<T>& B = P.blk[bi];
+      const TaskMap &dw_map = B.dw_map, &pw_map = B.pw_map;
+      for (int vt = first; vt < dw_map.count; vt += stride) {
+        int r, c;
+        if (task_of(dw_map, vt, &r, &c)) dw_task(waits, B, r, c, bi > 0, bi == 0 ? in0 : act, act);
+      }
+      for (int vt = first; vt < pw_map.count; vt += stride) {
+        int r, c;
+        if (!task_of(pw_map, vt, &r, &c)) continue;
+        ++count;
+        const int turn = count % 2;
+        float* const red = red2[turn];
+        if (B.cin == 64 * Q) pw_task_for<T, 64 * Q>(waits, B, r, c, act, red, left[2 + turn], count);
+        else if (B.cin == 128 * Q) pw_task_for<T, 128 * Q>(waits, B, r, c, act, red, left[2 + turn], count);
+        else pw_task_for<T, 256 * Q>(waits, B, r, c, act, red, left[2 + turn], count);
+      }
     }
-    for (int vt = wg; vt < pw_map.count; vt += kChainGrid) {
-      int r, c;
-      if (!task_of(pw_map, vt, &r, &c)) continue;
-      float* const red = red2[turn];
-      turn ^= 1;
-      if (B.cin == 64 * Q) pw_task_for<T, 64 * Q>(P, B, r, c, act, red);
-      else if (B.cin == 128 * Q) pw_task_for<T, 128 * Q>(P, B, r, c, act, red);
-      else pw_task_for<T, 256 * Q>(P, B, r, c, act, red);
-    }
-  }
+  };
 
   // ---- average pool + fully connected: task (ks, cb) = 128 input channels x 128 classes ----
   const ChainBlock<T>& L = P.blk[P.nblocks - 1];
   const int hw2 = P.last_hw * P.last_hw;
   float* const red = red2[0];
-  __syncthreads();
-  for (int task = wg; task < fc_tasks; task += kChainGrid) {
-    const int ks = task / fc_tasks_c, cb = task % fc_tasks_c;
-    if (task != wg) load_fc(task, fw);
-    float* pooled = red;             // [128]
-    float* psum = red + 128;         // [4][128], halfs: [8][128]
-    float* fsum = red + 128 + 1024;  // [16][128]
-    constexpr int PG = kHalf ? 8 : 4, PX = 64 / PG, WORDS = kChainThreads / PG;
-    {
-      // thread (pixel group pg of PG, word of WORDS: a channel, halfs: two) sums pixels pg, pg + PG, ... (at most 64 pixels)
-      const int word = tid % WORDS, pg = tid / WORDS, chn = (kHalf ? 2 : 1) * word;
-      unsigned x[PX];
-      load_written(P.failed, P.spin_limit, [&]() __attribute__((always_inline)) {
-        unsigned most = 0;
+  // own: after its own steps, of which a wavefront may have left one; false: then, or where the last step's words do not come
+  auto fully_connected = [&](bool own) __attribute__((always_inline)) {
+    waits.left = &left[1][tid / 64];
+    __syncthreads();
+    if (kMayLeave && own && any_wave(left[0], 1)) return false;
+    if (wg < fc_tasks) {
+      const int ks = wg / fc_tasks_c, cb = wg % fc_tasks_c;
+      float* pooled = red;             // [128]
+      float* psum = red + 128;         // [4][128], halfs: [8][128]
+      float* fsum = red + 128 + 1024;  // [16][128]
+      constexpr int PG = kHalf ? 8 : 4, PX = 64 / PG, WORDS = kChainThreads / PG;
+      {
+        // thread (pixel group pg of PG, word of WORDS: a channel, halfs: two) sums pixels pg, pg + PG, ... (at most 64 pixels)
+        const int word = tid % WORDS, pg = tid / WORDS, chn = (kHalf ? 2 : 1) * word;
+        unsigned x[PX];
+        (void)load_written(waits, [&]() __attribute__((always_inline)) {
+          unsigned most = 0;
+#pragma unroll
+          for (int i = 0; i < PX; ++i) {
+            const int p = pg + PG * i;
+            x[i] = ld_word(act, p < hw2 ? (L.out_off + (unsigned)(p * P.feat + kper * ks + chn)) * (unsigned)sizeof(T) : 0x80000000u);
+            most = max(most, x[i]);
+          }
+          return most == kEmpty;
+        });
+        float s[2] = {0.f, 0.f};
 #pragma unroll
         for (int i = 0; i < PX; ++i) {
-          const int p = pg + PG * i;
-          x[i] = ld_word(act, p < hw2 ? (L.out_off + (unsigned)(p * P.feat + kper * ks + chn)) * (unsigned)sizeof(T) : 0x80000000u);
-          most = max(most, x[i]);
+          if constexpr (kHalf) {
+            const h2 v = __builtin_bit_cast(h2, x[i]);
+            s[0] += (float)v[0], s[1] += (float)v[1];
+          } else {
+            s[0] += __uint_as_float(x[i]);
+          }
         }
-        return most == kEmpty;
-      });
-      float s[2] = {0.f, 0.f};
+        psum[pg * 128 + chn] = s[0];
+        if constexpr (kHalf) psum[pg * 128 + chn + 1] = s[1];
+      }
+      __syncthreads();
+      if (tid < 128) {
+        float s = psum[tid];
 #pragma unroll
-      for (int i = 0; i < PX; ++i) {
-        if constexpr (kHalf) {
-          const h2 v = __builtin_bit_cast(h2, x[i]);
-          s[0] += (float)v[0], s[1] += (float)v[1];
-        } else {
-          s[0] += __uint_as_float(x[i]);
+        for (int i = 1; i < PG; ++i) s += psum[128 * i + tid];
+        pooled[tid] = (float)(T)(s / (float)hw2);  // (the pooled vector is a tensor of the storage type)
+      }
+      __syncthreads();
+      {
+        const int kq = tid / 32, c4 = tid % 32;
+        float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          const float pv = pooled[8 * kq + i];
+          s.x = fmaf(pv, FcWeights<T>::get(fw[i], 0), s.x);
+          s.y = fmaf(pv, FcWeights<T>::get(fw[i], 1), s.y);
+          s.z = fmaf(pv, FcWeights<T>::get(fw[i], 2), s.z);
+          s.w = fmaf(pv, FcWeights<T>::get(fw[i], 3), s.w);
         }
+        *reinterpret_cast<float4*>(fsum + kq * 128 + 4 * c4) = s;
       }
-      psum[pg * 128 + chn] = s[0];
-      if constexpr (kHalf) psum[pg * 128 + chn + 1] = s[1];
-    }
-    __syncthreads();
-    if (tid < 128) {
-      float s = psum[tid];
+      __syncthreads();
+      const bool some_left = kMayLeave && own && any_wave(left[1], 1);
+      if (tid < kFcColBlock) {
+        float s = 0.f;
 #pragma unroll
-      for (int i = 1; i < PG; ++i) s += psum[128 * i + tid];
-      pooled[tid] = (float)(T)(s / (float)hw2);  // (the pooled vector is a tensor of the storage type)
-    }
-    __syncthreads();
-    {
-      const int kq = tid / 32, c4 = tid % 32;
-      float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const float pv = pooled[8 * kq + i];
-        s.x = fmaf(pv, FcWeights<T>::get(fw[i], 0), s.x);
-        s.y = fmaf(pv, FcWeights<T>::get(fw[i], 1), s.y);
-        s.z = fmaf(pv, FcWeights<T>::get(fw[i], 2), s.z);
-        s.w = fmaf(pv, FcWeights<T>::get(fw[i], 3), s.w);
+        for (int g = 0; g < 16; ++g) s += fsum[g * 128 + tid];
+        const int col = kFcColBlock * cb + tid;
+        if (col < P.classes && !some_left) st_f32(act, P.partial_at + (unsigned)(ks * P.classes + col) * 4u, s);
       }
-      *reinterpret_cast<float4*>(fsum + kq * 128 + 4 * c4) = s;
+      __syncthreads();
+      if (some_left) return false;
     }
-    __syncthreads();
-    if (tid < kFcColBlock) {
-      float s = 0.f;
-#pragma unroll
-      for (int g = 0; g < 16; ++g) s += fsum[g * 128 + tid];
-      const int col = kFcColBlock * cb + tid;
-      if (col < P.classes) st_f32(act, P.partial_at + (unsigned)(ks * P.classes + col) * 4u, s);
-    }
-    __syncthreads();
+    return true;
+  };
+
+  steps(wg, kChainGrid);
+  if (!fully_connected(true)) {  // an input did not come: every task
+    waits.patience = 0x7fffffff;
+    steps(0, 1);
+    if (wg < fc_tasks) load_fc(wg, fw);
+    (void)fully_connected(false);
   }
 
   // ---- bias + softmax: one task, two classes per thread ----
   if (wg == 0) {
+    waits.patience = 0x7fffffff;  // (what it waits for is left to nobody: its workgroups end without it)
     float l[2];
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       const int j = tid + kChainThreads * h;
       const bool in = j < P.classes;
       float part[kSlices];
-      load_written(P.failed, P.spin_limit, [&]() __attribute__((always_inline)) {
+      (void)load_written(waits, [&]() __attribute__((always_inline)) {
         unsigned most = 0;
 #pragma unroll
         for (int s = 0; s < kSlices; ++s) {
@@ -673,21 +738,21 @@ ChainKernel<T> chain_kernel(int width_quarters) {
 }
 }  // namespace
 
-// Whether 256 workgroups of the chain kernel are resident at once on the current device (looked up once per device).
-bool chain_resident(int width_quarters, bool half) {
-  static std::atomic<int> states[8][64];  // 0 unknown, 1 yes, 2 no
+// How many grids of the chain kernel are resident at once on the current device, at most 2 (looked up once per device).
+int chain_grids(int width_quarters, bool half) {
+  static std::atomic<int> states[8][64];  // 0 unknown, else one more than the grids
   int dev = 0;
-  if (width_quarters < 1 || width_quarters > 4 || hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return false;
+  if (width_quarters < 1 || width_quarters > 4 || hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 0;
   std::atomic<int>* const state = states[width_quarters - 1 + (half ? 4 : 0)];
   const int s = state[dev].load(std::memory_order_acquire);
-  if (s) return s == 1;
+  if (s) return s - 1;
   int cus = 0, per_cu = 0;
   const void* const kernel = half ? reinterpret_cast<const void*>(chain_kernel<half_t>(width_quarters)) : reinterpret_cast<const void*>(chain_kernel<float>(width_quarters));
-  bool ok = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
-            hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, kChainThreads, 0) == hipSuccess;
-  ok = ok && (long long)cus * per_cu >= kChainGrid;
-  state[dev].store(ok ? 1 : 2, std::memory_order_release);
-  return ok;
+  const bool ok = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
+                  hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, kChainThreads, 0) == hipSuccess;
+  const int grids = !ok ? 0 : (int)std::min(2ll, (long long)cus * per_cu / kChainGrid);
+  state[dev].store(1 + grids, std::memory_order_release);
+  return grids;
 }
 
 namespace {
@@ -777,46 +842,72 @@ int chain_spin_limit() {
   return kSpinLimit;
 }
 
+int chain_workgroups() {
+  // Test hook: TFX_CHAIN_WORKGROUPS=<n> leaves out the workgroups from the nth on (those of the fully connected layer are the first
+  // 64), as if they never got to run.
+  if (const char* e = getenv("TFX_CHAIN_WORKGROUPS")) {
+    const long v = strtol(e, nullptr, 10);
+    if (v >= kFcTasks && v <= kChainGrid) return (int)v;
+  }
+  return kChainGrid;
+}
+
 namespace {
-// Chain kernels of one process are kept from overlapping on a device.  The last stream that launched one is
-// remembered per device; a launch on another stream first records an event behind everything queued on that
-// stream and makes the new stream wait for it.  Launches that stay on one stream (the usual case) pay nothing.
-// A stream that is being captured into a graph is left alone (an event of another stream cannot be recorded into
-// the capture): replays of such graphs on several streams at once are the caller's to order.
+// Kernels of waiting workgroups of one process are ordered across streams such that all that run are resident, on two tracks per
+// device: the kernels of one track never overlap.  One of which two grids are resident at once takes one track -- that of its stream if
+// there is one, else the two in turn --, any other one both.  For each track the last stream is remembered; a launch on
+// another stream first records an event behind everything queued on that stream and makes the new stream wait for it.  Launches that
+// stay on one stream, and of the former kind those of two streams, pay nothing.  One binary16 image, us each on 1, 2 and 4 streams: full width
+// 224 x 224 62.8, 38.8, 51, with one track 62.7, 51.1, 58.6, as launches that do not wait 68.7, 53, 53; quarter width 128 x 128 44, 25, 48;
+// 43.7, 47, 46.5; 56, 56, 54.  (With more than two streams some share a hardware queue, in which a wait holds up both.)
+// A stream that is being captured into a graph is left alone: an event of another stream cannot be recorded into the capture.  Replays of
+// such passes, full width 224 x 224: 67.6, 39.9, 40, as launches 73.3, 42.8, 40.  (Those of the fp32 pass at full width, whose workgroups do wait
+// for each other to run, are the caller's to order.)
 struct ChainOrder {
   std::mutex lock;
-  hipStream_t last[64];
+  hipStream_t last[64][2];
   hipEvent_t event[64];
-  bool launched[64], have_event[64];
+  bool launched[64][2], have_event[64];
+  int turn[64];
 };
 ChainOrder g_order;
 
-void order_after_other_streams(int dev, hipStream_t stream) {
+void order_after_other_streams(int dev, hipStream_t stream, bool one_track) {
   hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(stream, &capturing) != hipSuccess || capturing != hipStreamCaptureStatusNone) {
     (void)hipGetLastError();
     return;
   }
-  if (g_order.launched[dev] && g_order.last[dev] != stream) {
-    if (!g_order.have_event[dev])
-      g_order.have_event[dev] = hipEventCreateWithFlags(&g_order.event[dev], hipEventDisableTiming) == hipSuccess;
-    // a stream that has been destroyed since is refused by the runtime: nothing of it can still be running
-    if (g_order.have_event[dev] && hipEventRecord(g_order.event[dev], g_order.last[dev]) == hipSuccess)
-      (void)hipStreamWaitEvent(stream, g_order.event[dev], 0);
-    (void)hipGetLastError();
+  bool* const launched = g_order.launched[dev];
+  hipStream_t* const last = g_order.last[dev];
+  int first = 0, end = 2;
+  if (one_track) {
+    for (first = 0; first < 2 && !(launched[first] && last[first] == stream);) ++first;
+    if (first == 2) first = g_order.turn[dev] ^= 1;
+    end = first + 1;
   }
-  g_order.last[dev] = stream;
-  g_order.launched[dev] = true;
+  for (int i = first; i < end; ++i) {
+    if (launched[i] && last[i] != stream) {
+      if (!g_order.have_event[dev])
+        g_order.have_event[dev] = hipEventCreateWithFlags(&g_order.event[dev], hipEventDisableTiming) == hipSuccess;
+      // a stream that has been destroyed since is refused by the runtime: nothing of it can still be running
+      if (g_order.have_event[dev] && hipEventRecord(g_order.event[dev], last[i]) == hipSuccess)
+        (void)hipStreamWaitEvent(stream, g_order.event[dev], 0);
+      (void)hipGetLastError();
+    }
+    last[i] = stream;
+    launched[i] = true;
+  }
 }
 }  // namespace
 
 // Runs fn(arg) -- which enqueues a kernel whose workgroups wait for each other -- once `stream` has been ordered behind
-// the last such kernel of any other stream.
+// the last such kernels of other streams.
 int launch_ordered(hipStream_t stream, int (*fn)(void*), void* arg) {
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return TFX_ERR_LAUNCH;
   std::lock_guard<std::mutex> guard(g_order.lock);
-  order_after_other_streams(dev, stream);
+  order_after_other_streams(dev, stream, false);
   return fn(arg);
 }
 
@@ -847,17 +938,18 @@ int launch_chain_of(const T* in0, int image_size, const W* w, void* chain_ws, co
   P.probs = probs;
   P.logits = logits;
   P.spin_limit = chain_spin_limit();
+  P.patience = kPatience;
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return TFX_ERR_LAUNCH;
   std::lock_guard<std::mutex> guard(g_order.lock);
-  order_after_other_streams(dev, stream);
+  order_after_other_streams(dev, stream, before == nullptr && chain_grids(width_quarters, sizeof(T) == 2) >= 2);
   // a launch of waiting workgroups that belongs in front of this one (blocks 2 - 4 as stages, block.hip) is enqueued
   // under the same lock, so that the pair is ordered against other streams' pairs as one
   if (before != nullptr) {
     const int rc = before(before_arg);
     if (rc != TFX_OK) return rc;
   }
-  hipLaunchKernelGGL(chain_kernel<T>(width_quarters), dim3(kChainGrid), dim3(kChainThreads), 0, stream, P);
+  hipLaunchKernelGGL(chain_kernel<T>(width_quarters), dim3(chain_workgroups()), dim3(kChainThreads), 0, stream, P);
   return check_launch();
 }
 }  // namespace

@@ -217,7 +217,7 @@ int launch_conv2d_stem(const float* x, const float* w, const float* bias, float*
 // chain_flag_words() words at a spacing of block_chain_flag_stride() words are zero when the kernel starts (the failure word, then the
 // flags of blocks 2 - 4 as stages), and what chain_fill() says is filled with ones.  in0: the output of block 4.
 bool chain_supported(int image_size, int width_quarters, int classes, long long batch);
-bool chain_resident(int width_quarters, bool half = false);
+int chain_grids(int width_quarters, bool half = false);  // how many grids of it the device holds at once
 size_t chain_workspace_bytes(int image_size, int classes, int width_quarters);
 int chain_flag_words(int image_size);
 struct ChainFill {
