@@ -11,8 +11,8 @@
 // TWO: the second block too, as in block_rows_f16.hip: a wavefront keeps its 16 columns of one row of the first block's output in LDS,
 // adds what the row gives to 8 columns of the second depthwise layer, at stride 2, in registers, and multiplies the rows of that two
 // at a time by a filter that lies split in LDS.  That takes a CU's LDS for one workgroup, whose seven wavefronts issue on 1.75 SIMDs
-// each: 64 images of 224 x 224 at full width 102 us, bound by issue and latency (a row 3 us), where this launch and the second block's
-// took 73 + 62 and moved the 205 MB between them twice; 8 images 24.6 and 32.7.
+// each: 64 images of 224 x 224 at full width 102 us (and 21 for the filters behind, pack.h), bound by issue and latency (a row 3 us), where this launch and
+// the second block's took 73 + 62 and moved the 205 MB between them twice; 8 images 24.6 and 32.7.
 #include "pack.h"
 #include "split.h"
 
@@ -570,8 +570,9 @@ int launch_stem_block_rows(const float* image, const float* st_w, const float* s
     }
     // The tile blocks' filters: workgroups of this launch where it leaves CUs idle, and with 7 wavefronts and more, which hold a column of
     // 1024 rows in one go; else a launch of its own.  us a pass, so and in this launch: full width 224 x 224 4 images 150.6 / 146.2, 8 187.0 /
-    // 186.3, 16 242.9 / 238.9, 64 513.3 / 511.5, 192 x 192 12 images 200.1 / 192.7, 160 x 160 8 images 160.2 / 154.6; but, without idle CUs,
-    // 160 x 160 48 images 311 / 315, 96 x 96 64 images 242 / 249.
+    // 186.3, 16 242.2 / 239.3, 192 x 192 12 images 200.1 / 192.7, 160 x 160 8 images 160.2 / 154.6.  Without idle CUs they come behind the
+    // strips, one to a CU: 224 x 224 48 images 445 / 442, 64 517.5 / 516.5, 24 294 / 295, 32 325.5 / 326, 3/4 width 64 398.5 / 399, of which
+    // 5 us and less are the difference of two runs; with fewer wavefronts 160 x 160 48 images 311 / 315, 96 x 96 64 images 242 / 249.
     const bool with = first == 0 && second && filters.groups() > 0 && (tiles >= 7 || images * strips <= slots / 8 * 7);
     const PackList* const list = with ? &filters : nullptr;
     int rc = TFX_ERR_UNSUPPORTED;

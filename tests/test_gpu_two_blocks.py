@@ -91,3 +91,48 @@ def test_filters_put_in_order_by_the_same_launch(q, size, batch, end_block):
         ref = host(one.features(dev(d["image"][i:i + 1]), end_block))
         for j in range(i, batch, 2):
             assert_close(got[j:j + 1], ref, "image %d" % j)
+
+
+@pytest.mark.parametrize("q,size,batch,end_block", [(4, 160, 48, 9), (4, 96, 64, 12), (2, 128, 64, 12)])
+def test_filters_put_in_order_by_a_launch_of_their_own(q, size, batch, end_block):
+    """Where the strips leave no CU idle; the tile blocks behind it against the same blocks of one image."""
+    import paper_1901_05350_amd as tfx
+    from test_gpu_f16_conv import launches
+    d = inputs.mobilenet_v1(seed=98, batch=2, image_size=size, width_quarters=q, classes=10)
+    model = tfx.MobileNetV1(d["weights"], batch=batch, image_size=size, width_quarters=q)
+    one = tfx.MobileNetV1(d["weights"], batch=1, image_size=size, width_quarters=q)
+    model.workspace.fill_(255)
+    image = dev(np.concatenate([d["image"]] * (batch // 2)))
+    got = host(model.features(image, end_block))
+    assert launches(lambda: model.features(image, end_block))[1][2] == (1024, 1, 1)
+    for i in (0, 1):
+        ref = host(one.features(dev(d["image"][i:i + 1]), end_block))
+        for j in range(i, batch, 2):
+            assert_close(got[j:j + 1], ref, "image %d" % j)
+
+
+def shifted(tensors, struct, names, block):
+    """The named weights of one block one element behind a 16-byte boundary."""
+    import torch
+    for name in names:
+        t = tensors[name][block]
+        flat = torch.zeros(t.numel() + 1, dtype=t.dtype, device=t.device)
+        flat[1:] = t.reshape(-1)
+        tensors[name][block] = flat[1:].view(t.shape)
+        getattr(struct, name)[block] = tensors[name][block].data_ptr()
+        assert tensors[name][block].data_ptr() % 16 != 0
+
+
+@pytest.mark.parametrize("half,q,size,batch", [(False, 4, 160, 6), (False, 1, 130, 9), (False, 3, 97, 15), (True, 4, 224, 10), (True, 3, 101, 47)])
+@pytest.mark.parametrize("block", [0, 1])
+def test_weights_off_16_bytes(half, q, size, batch, block):
+    """The launch with two blocks takes them element by element: the same bits."""
+    import paper_1901_05350_amd as tfx
+    from util import dev16
+    make, net, up = (inputs.mobilenet_v1_f16, tfx.MobileNetV1F16, dev16) if half else (inputs.mobilenet_v1, tfx.MobileNetV1, dev)
+    d = make(seed=99, batch=2, image_size=size, width_quarters=q, classes=10)
+    model = net(d["weights"], batch=batch, image_size=size, width_quarters=q)
+    image = up(np.concatenate([d["image"]] * ((batch + 1) // 2))[:batch])
+    want = host(model.features(image, 2))
+    shifted(model.tensors, model.struct, ("dw_w", "dw_b", "pw_w", "pw_b"), block)
+    assert np.array_equal(host(model.features(image, 2)), want)
