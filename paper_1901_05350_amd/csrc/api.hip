@@ -132,8 +132,9 @@ BlockPlan plan_blocks_f16(const tfx_mobilenet_v1_variant& v, int64_t batch) {
                 : small[b]                             ? kPatch
                                                        : kTwo;
     // The second block with the stem: us a pass, separate and together, full width 16 images 151 / 146, 64 images 257 / 253; 3/4 width 16
-    // images 138 / 130, 64 of 192 x 192 218 / 203.  Half width, 32 images 132 / 131, quarter width, 64 of 160 x 160 107 / 115.  8 images and
-    // fewer (full width 126.5 / 122, one 67.6 / 68.2) stay separate: there a pass and its feature maps have a launch for each block.
+    // images 138 / 130, 64 of 192 x 192 218 / 203.  Half width, 32 images 132 / 131, quarter width, 64 of 160 x 160 107 / 115.  The two cross
+    // between one image (full width 67.6 / 68.2) and 8 (126.5 / 122); the line lies behind 8 because a pass of up to 8 images and its
+    // feature maps have a launch for each block, which costs 3.6 % there.
     if (b == 1 && q >= 3 && batch * out * out >= 30000) p.form[b] = kStem;
     if (p.form[b] == kTile) {
       ++p.tiles;
@@ -766,7 +767,8 @@ int forward_f16_impl(const tfx_mobilenet_v1_variant* variant, const uint16_t* in
   hipStream_t const s = static_cast<hipStream_t>(stream);
 
   const int blocks = end_block ? end_block : kBlocks;
-  const BlockPlan form = plan_blocks_f16(*variant, batch);  // of the whole network: a feature map is the one a pass computes
+  // of the whole network: a feature map is the one a pass computes (but for the chained blocks of one image, whose last bits differ)
+  const BlockPlan form = plan_blocks_f16(*variant, batch);
   bool aligned = true;
   for (int b = 0; b < blocks; ++b)
     for (const void* p : {weights->dw_w[b], weights->dw_b[b], weights->pw_w[b], weights->pw_b[b]})

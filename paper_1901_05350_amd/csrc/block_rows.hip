@@ -151,17 +151,18 @@ __global__ __launch_bounds__(512, 2) void stem_block_rows_kernel(RowsArgs g, Fil
       const int k = i % (16 * G);
       dw_taps[i / (16 * G)][k] = k < C ? g.dw_w[i / (16 * G) * C + k] : 0.f;
     }
-  } else
+  } else {
 #pragma unroll
-  for (int t = 0; t < 9; ++t)
+    for (int t = 0; t < 9; ++t)
 #pragma unroll
-    for (int u = 0; u < G; ++u)
+      for (int u = 0; u < G; ++u)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int k = 16 * u + 4 * q + e;
-        const float v = g.dw_w[t * C + (k < C ? k : 0)];
-        dww[kTapsInLds ? 0 : t][u][e] = k < C ? v : 0.f;
-      }
+        for (int e = 0; e < 4; ++e) {
+          const int k = 16 * u + 4 * q + e;
+          const float v = g.dw_w[t * C + (k < C ? k : 0)];
+          dww[kTapsInLds ? 0 : t][u][e] = k < C ? v : 0.f;
+        }
+  }
   for (int i = threadIdx.x; i < 16 * G; i += (int)blockDim.x) {
     stem_bias[i] = i < C ? g.st_b[i] : 0.f;
     dw_bias[i] = i < C ? g.dw_b[i] : 0.f;

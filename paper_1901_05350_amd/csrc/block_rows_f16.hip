@@ -28,8 +28,8 @@
 // beside), adds what the row gives to 8 columns of the second depthwise layer in registers, and multiplies the rows of that two at a
 // time.  LDS bounds it (38 reads of 16 bytes a lane and row, 70 % of the cycles) beside the vector units; two workgroups of seven
 // wavefronts need 128 registers a lane and 80 KB, so part of the filters is in LDS and part of the diagonal operands is made in each
-// step.  64 images 46.8 us, the two launches 27 + 29; with all filters in registers and one workgroup on a CU 49.8, windows
-// requested two steps ahead made no difference.
+// step; 1 register (3/4 width 7) that still does not fit is spilled.  64 images 46.8 us, the two launches 27 + 29; with all filters in
+// registers and one workgroup on a CU 49.8, windows requested two steps ahead made no difference.
 #include "ragged.h"
 #include "stream_f16.h"
 

@@ -39,8 +39,8 @@
 // for kPatience polls (who has it to write is not running) leaves its tasks, and then computes every task of every step itself, in order,
 // where each input is one that it has written before.  What is written twice is written with the same bits.  So any number of these
 // kernels may run side by side -- replays of captured passes on several streams, other processes -- and grids that keep each other's
-// workgroups from the CUs end late, by 6 - 9 ms, but right.  (Binary16, one image, us: full width 224 x 224 62.7 without, 62.9 with, 3/4
-// width 192 x 192 54.4, 54.6.)  The grid (256 workgroups, one per CU) is launched where all of it is resident at once (chain_grids), and
+// workgroups from the CUs end late, by 6 - 9 ms, but right.  (Binary16, one image, us: full width 224 x 224 63.4 without, 63.6 with, 3/4
+// width 192 x 192 54.6, 55.0, quarter width 128 x 128 42.6, 42.6.)  The grid (256 workgroups, one per CU) is launched where all of it is resident at once (chain_grids), and
 // launch_chain orders calls across streams such that no more of them run than the device holds: only replays of captured passes come to that.
 //
 // Every wait is bounded besides: a poll loop gives up after kSpinLimit rounds (seconds), sets a failure word that makes
@@ -205,7 +205,7 @@ template <bool LEAVES>
 __device__ __forceinline__ void dw_task(Waits<LEAVES>& waits, const ChainBlock<float>& B, int r, int c, bool wait,
                                         __amdgpu_buffer_rsrc_t in, __amdgpu_buffer_rsrc_t act) {
   const int m_out = B.out_hw * B.out_hw;
-  const int t = threadIdx.x, px = (t / 32) % 16, ch = 32 * c + t % 32;
+  const int t = threadIdx.x, px = t / 32, ch = 32 * c + t % 32;
   // filter taps and bias first: they do not depend on anybody
   float w[9];
 #pragma unroll
@@ -254,7 +254,7 @@ template <bool LEAVES>
 __device__ __forceinline__ void dw_task(Waits<LEAVES>& waits, const ChainBlock<half_t>& B, int r, int c, bool wait,
                                         __amdgpu_buffer_rsrc_t in, __amdgpu_buffer_rsrc_t act) {
   const int m_out = B.out_hw * B.out_hw;
-  const int t = threadIdx.x, px = (t / 32) % 16, ch = 64 * c + 2 * (t % 32);
+  const int t = threadIdx.x, px = t / 32, ch = 64 * c + 2 * (t % 32);
   unsigned w[9];
 #pragma unroll
   for (int k = 0; k < 9; ++k) w[k] = *reinterpret_cast<const unsigned*>(B.dw_w + k * B.cin + ch);
@@ -301,7 +301,7 @@ __device__ __forceinline__ void pw_task(Waits<LEAVES>& waits, const ChainBlock<f
                                         __amdgpu_buffer_rsrc_t act, float* red, int* left, int task) {
   constexpr int G = CHUNK / 16;
   const int K = B.cin, N = B.cout, M = B.out_hw * B.out_hw;
-  const int tid = threadIdx.x, wk = (tid / 64) % kChainWaves, lane = tid % 64, li = lane % 16, q = lane / 16;
+  const int tid = threadIdx.x, wk = tid / 64, lane = tid % 64, li = lane % 16, q = lane / 16;
   const bool compute = tid < 64 * WAVES;
   const int m0 = 16 * tile_m, n0 = 16 * TN * tile_n;
 
@@ -396,7 +396,7 @@ __device__ __forceinline__ void pw_task(Waits<LEAVES>& waits, const ChainBlock<h
                                         __amdgpu_buffer_rsrc_t act, float* red, int* left, int task) {
   constexpr int G = CHUNK / 32;
   const int K = B.cin, N = B.cout, M = B.out_hw * B.out_hw;
-  const int tid = threadIdx.x, wk = (tid / 64) % kChainWaves, lane = tid % 64, li = lane % 16, q = lane / 16;
+  const int tid = threadIdx.x, wk = tid / 64, lane = tid % 64, li = lane % 16, q = lane / 16;
   const bool compute = tid < 64 * WAVES;
   const int m0 = 16 * tile_m, n0 = 16 * TN * tile_n;
 
@@ -553,7 +553,7 @@ __global__ __launch_bounds__(kChainThreads) void mobilenet_chain_kernel(const Ch
   const bool fvec = P.classes % 4 == 0;
   auto load_fc = [&](int task, Weights (&dst)[8]) {
     const int ks = task / fc_tasks_c, cb = task % fc_tasks_c;
-    const int col = kFcColBlock * cb + 4 * (tid % 32), k0 = kper * ks + 8 * ((tid / 32) % 16);
+    const int col = kFcColBlock * cb + 4 * (tid % 32), k0 = kper * ks + 8 * (tid / 32);
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
       const T* p = P.fc_w + (size_t)(k0 + i) * P.classes + col;

@@ -207,7 +207,8 @@ __device__ __forceinline__ void clear_for_chain(const ChainClear& c, unsigned th
   for (unsigned i = thread; i < (unsigned)c.zero_count; i += threads) c.zero_words[(size_t)i * c.zero_stride] = 0;
   for (unsigned i = thread; i < c.fill_pieces; i += threads) c.fill[i] = make_uint4(~0u, ~0u, ~0u, ~0u);
 }
-// clear: optional (matrix-core form only: 32 filters, 16-byte aligned y and bias).
+// clear: optional.  Both forms of the kernel do it, and the chained kernel's results depend on it: a word that still holds an earlier
+// pass's value is taken for this one's.  (The narrower networks' 8, 16 and 24 filters take the form without matrix cores.)
 int launch_conv2d_stem(const float* x, const float* w, const float* bias, float* y, int n, int h, int wd, int co,
                        int oh, int ow, int sh, int sw, int pt, int pl, int act, hipStream_t stream,
                        const ChainClear& clear = ChainClear());
