@@ -844,7 +844,7 @@ int chain_spin_limit() {
 
 int chain_workgroups() {
   // Test hook: TFX_CHAIN_WORKGROUPS=<n> leaves out the workgroups from the nth on (those of the fully connected layer are the first
-  // 64), as if they never got to run.
+  // 64), as if they never got to run, where the others do without them (kLeaves).
   if (const char* e = getenv("TFX_CHAIN_WORKGROUPS")) {
     const long v = strtol(e, nullptr, 10);
     if (v >= kFcTasks && v <= kChainGrid) return (int)v;
@@ -949,7 +949,8 @@ int launch_chain_of(const T* in0, int image_size, const W* w, void* chain_ws, co
     const int rc = before(before_arg);
     if (rc != TFX_OK) return rc;
   }
-  hipLaunchKernelGGL(chain_kernel<T>(width_quarters), dim3(chain_workgroups()), dim3(kChainThreads), 0, stream, P);
+  const bool leaves = sizeof(T) == 2 || width_quarters < 4;  // kLeaves
+  hipLaunchKernelGGL(chain_kernel<T>(width_quarters), dim3(leaves ? chain_workgroups() : kChainGrid), dim3(kChainThreads), 0, stream, P);
   return check_launch();
 }
 }  // namespace
