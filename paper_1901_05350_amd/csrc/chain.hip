@@ -35,16 +35,17 @@
 // the memory side, loads do not hit a stale line).  Filters and biases are read-only and use ordinary cached loads; they are
 // fetched before the wait.
 //
-// No workgroup has to be resident for another one to end (but in fp32 at full width, see kLeaves): a workgroup whose input does not come
-// for kPatience polls (who has it to write is not running) leaves its tasks, and then computes every task of every step itself, in order,
-// where each input is one that it has written before.  What is written twice is written with the same bits.  So any number of these
-// kernels may run side by side -- replays of captured passes on several streams, other processes -- and grids that keep each other's
-// workgroups from the CUs end late, by 6 - 9 ms, but right.  (Binary16, one image, us: full width 224 x 224 63.4 without, 63.6 with, 3/4
-// width 192 x 192 54.6, 55.0, quarter width 128 x 128 42.6, 42.6.)  The grid (256 workgroups, one per CU) is launched where all of it is resident at once (chain_grids), and
-// launch_chain orders calls across streams such that no more of them run than the device holds: only replays of captured passes come to that.
+// No workgroup has to be resident for another one to end: a workgroup whose input does not come for kPatience polls (who has it to
+// write is not running) leaves its tasks, and then computes every task of every step itself, in order, where each input is one that it
+// has written before.  What is written twice is written with the same bits.  So any number of these kernels may run side by side --
+// replays of captured passes on several streams, other processes -- and grids that keep each other's workgroups from the CUs end late,
+// by 6 - 9 ms, but right.  (It costs nothing: one image, us, without and with, full width 224 x 224 78.5 / 78.5, 3/4 width 192 x 192 73.2 / 72.7,
+// quarter width 128 x 128 55.1 / 54.4; binary16 62.9 / 62.95, 54.8 / 54.7, 42.6 / 42.1.)  The grid (256 workgroups, one per CU) is launched where
+// all of it is resident at once (chain_grids), and launch_chain orders calls across streams such that no more of them run than the device
+// holds: only replays of captured passes come to that.
 //
-// Every wait is bounded besides: a poll loop gives up after kSpinLimit rounds (seconds), sets a failure word that makes
-// every other wait give up too, and the softmax task then writes NaN to every output: no hang, and no plausible numbers.
+// Every wait is bounded besides: a poll loop that still waits after kSpinLimit rounds (seconds; where a workgroup of the fully connected
+// layer never gets to run) gives up and sets a failure word, and the softmax task then writes NaN to every output.
 #include <algorithm>
 #include <cstdlib>
 #include <mutex>
@@ -156,13 +157,7 @@ __device__ __forceinline__ void st_f32x2(__amdgpu_buffer_rsrc_t r, unsigned byte
   __builtin_amdgcn_raw_buffer_store_b64(u32x2{word_of(a), word_of(b)}, r, (int)byte_off, 0, kSc1);
 }
 
-// Whether a kernel's workgroups leave the tasks whose input does not come.  Full width in fp32 do not: their pass has a launch in front
-// (blocks 2 - 4 as stages, block.hip) whose workgroups have to be resident anyway, and 78.2 us would be 78.8.
-template <typename T, int Q>
-constexpr bool kLeaves = sizeof(T) == 2 || Q < 4;
-
 // What bounds this wavefront's waits.
-template <bool LEAVES>
 struct Waits {
   int* failed;     // a wait has given up (device memory)
   int spin_limit, patience;
@@ -170,22 +165,22 @@ struct Waits {
 };
 
 // Runs load(), which fetches what this lane needs and says whether any word of it is still empty, until no lane of the wavefront
-// misses any; false: they did not come.  A wait that gives up sets the failure word, which ends every other wait soon.
-template <bool LEAVES, typename F>
-__device__ __forceinline__ bool load_written(Waits<LEAVES>& waits, F load) {
-  const int most = LEAVES ? min(__builtin_amdgcn_readfirstlane(waits.patience), waits.spin_limit) : waits.spin_limit;
-  int spin = 0;
-  while (__builtin_expect(__builtin_amdgcn_ballot_w64(load()) != 0, 0)) {
-    if (spin >= most || ((++spin & 255) == 0 && __builtin_amdgcn_readfirstlane(__hip_atomic_load(waits.failed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) != 0)) {
-      if (spin >= waits.spin_limit) __hip_atomic_store(waits.failed, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if (!LEAVES) return true;  // (what is computed of it is NaN in the end)
-      waits.patience = 0;  // the wavefront's other tasks are left at once
-      *waits.left = 1;
-      return false;
-    }
+// misses any; false: they did not come.  A wait that gives up sets the failure word.
+template <typename F>
+__device__ __forceinline__ bool load_written(Waits& waits, F load) {
+  const int most = min(__builtin_amdgcn_readfirstlane(waits.patience), waits.spin_limit);
+  int polls = most;
+  bool missing;
+  do {
+    missing = __builtin_amdgcn_ballot_w64(load()) != 0;
     asm volatile("" ::: "memory");
+  } while (missing && --polls >= 0);
+  if (__builtin_expect(missing, 0)) {
+    if (most >= waits.spin_limit) __hip_atomic_store(waits.failed, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    waits.patience = 0;  // the wavefront's other tasks are left at once
+    *waits.left = 1;
   }
-  return true;
+  return !missing;
 }
 
 // `word` is one of kChainWaves in LDS, a wavefront's own; behind a barrier: whether a wavefront's is `value`.
@@ -194,15 +189,13 @@ __device__ __forceinline__ bool any_wave(const int* word, int value) {
 }
 // Whether a pointwise task's result v stands for a sum of words that have not come: they are empty, which as a value is a NaN.  (Nothing
 // is looked up for any other result.)
-template <bool LEAVES>
 __device__ __forceinline__ bool not_computed(float v, const int* left, int task) {
-  return LEAVES && __builtin_amdgcn_ballot_w64(v != v) != 0 && any_wave(left, task) && v != v;
+  return __builtin_amdgcn_ballot_w64(v != v) != 0 && any_wave(left, task) && v != v;
 }
 
 // ---- depthwise 3x3 + bias + ReLU6: 16 output pixels x 32 channels, one output per thread ----
 // wait: the input comes from a task of this launch
-template <bool LEAVES>
-__device__ __forceinline__ void dw_task(Waits<LEAVES>& waits, const ChainBlock<float>& B, int r, int c, bool wait,
+__device__ __forceinline__ void dw_task(Waits& waits, const ChainBlock<float>& B, int r, int c, bool wait,
                                         __amdgpu_buffer_rsrc_t in, __amdgpu_buffer_rsrc_t act) {
   const int m_out = B.out_hw * B.out_hw;
   const int t = threadIdx.x, px = t / 32, ch = 32 * c + t % 32;
@@ -250,8 +243,7 @@ __device__ __forceinline__ void dw_task(Waits<LEAVES>& waits, const ChainBlock<f
 __device__ __forceinline__ unsigned half_bits(half_t v) { return v == v ? (unsigned)__builtin_bit_cast(unsigned short, v) : 0x7e00u; }
 __device__ __forceinline__ unsigned word_of(float a, float b) { return half_bits((half_t)a) | half_bits((half_t)b) << 16; }
 typedef _Float16 h2 __attribute__((ext_vector_type(2)));
-template <bool LEAVES>
-__device__ __forceinline__ void dw_task(Waits<LEAVES>& waits, const ChainBlock<half_t>& B, int r, int c, bool wait,
+__device__ __forceinline__ void dw_task(Waits& waits, const ChainBlock<half_t>& B, int r, int c, bool wait,
                                         __amdgpu_buffer_rsrc_t in, __amdgpu_buffer_rsrc_t act) {
   const int m_out = B.out_hw * B.out_hw;
   const int t = threadIdx.x, px = t / 32, ch = 64 * c + 2 * (t % 32);
@@ -296,8 +288,8 @@ __device__ __forceinline__ void dw_task(Waits<LEAVES>& waits, const ChainBlock<h
 
 // ---- pointwise 1x1 + bias + ReLU6: 16 x (16 TN) tile, K = WAVES x CHUNK split over the first WAVES 
 // wavefronts (all 8 where K is a multiple of 128; 4 for the K = 64 and K = 192 of the narrower networks) ----
-template <int CHUNK, int TN, int WAVES, bool LEAVES>
-__device__ __forceinline__ void pw_task(Waits<LEAVES>& waits, const ChainBlock<float>& B, int tile_m, int tile_n,
+template <int CHUNK, int TN, int WAVES>
+__device__ __forceinline__ void pw_task(Waits& waits, const ChainBlock<float>& B, int tile_m, int tile_n,
                                         __amdgpu_buffer_rsrc_t act, float* red, int* left, int task) {
   constexpr int G = CHUNK / 16;
   const int K = B.cin, N = B.cout, M = B.out_hw * B.out_hw;
@@ -382,7 +374,7 @@ __device__ __forceinline__ void pw_task(Waits<LEAVES>& waits, const ChainBlock<f
       for (int w = 0; w < WAVES; ++w) sum += red[((w * TN + j) * 4 + ev) * 64 + el];
       o[j] = apply_act(sum, clamp);
     }
-    if (not_computed<LEAVES>(o[0], left, task) || erow >= M) return;
+    if (not_computed(o[0], left, task) || erow >= M) return;
     const unsigned off = (B.out_off + (unsigned)(erow * N + ecol)) * 4u;
     if constexpr (TN == 2) st_f32x2(act, off, o[0], o[1]);
     else st_f32(act, off, o[0]);
@@ -391,8 +383,8 @@ __device__ __forceinline__ void pw_task(Waits<LEAVES>& waits, const ChainBlock<f
 
 // The same on halfs, 32 values of K an instruction.  A filter value is one of a lane's eight of consecutive rows: words of two columns
 // (single halfs with TN == 1) come from eight rows and are put together in registers.
-template <int CHUNK, int TN, int WAVES, bool LEAVES>
-__device__ __forceinline__ void pw_task(Waits<LEAVES>& waits, const ChainBlock<half_t>& B, int tile_m, int tile_n,
+template <int CHUNK, int TN, int WAVES>
+__device__ __forceinline__ void pw_task(Waits& waits, const ChainBlock<half_t>& B, int tile_m, int tile_n,
                                         __amdgpu_buffer_rsrc_t act, float* red, int* left, int task) {
   constexpr int G = CHUNK / 32;
   const int K = B.cin, N = B.cout, M = B.out_hw * B.out_hw;
@@ -468,7 +460,7 @@ __device__ __forceinline__ void pw_task(Waits<LEAVES>& waits, const ChainBlock<h
     }
     // (TN == 1: the next lane's column, for the even ones; a word is written whole)
     if constexpr (TN == 1) o[1] = __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(o[0]), 0xb1, 0xf, 0xf, true));
-    if (!not_computed<LEAVES>(o[0], left, task) && erow < M && (TN == 2 || el % 2 == 0))
+    if (!not_computed(o[0], left, task) && erow < M && (TN == 2 || el % 2 == 0))
       __builtin_amdgcn_raw_buffer_store_b32(word_of(o[0], o[1]), act, (int)((B.out_off + (unsigned)(erow * N + ecol)) * 2u), 0, kSc1);
   }
 }
@@ -489,8 +481,8 @@ __device__ __forceinline__ float block_sum_or_max(float v, bool is_max, float* s
 }
 
 // The pointwise task for a layer of K input channels: the K split, and 32-column tiles only below K = 1024.
-template <typename T, int K, bool LEAVES>
-__device__ __forceinline__ void pw_task_for(Waits<LEAVES>& waits, const ChainBlock<T>& B, int r, int c,
+template <typename T, int K>
+__device__ __forceinline__ void pw_task_for(Waits& waits, const ChainBlock<T>& B, int r, int c,
                                             __amdgpu_buffer_rsrc_t act, float* red, int* left, int task) {
   constexpr int STEP = sizeof(T) == 2 ? 32 : 16;  // a wavefront takes whole steps
   constexpr int WAVES = K % (8 * STEP) == 0 ? 8 : sizeof(T) == 2 && K % (6 * STEP) == 0 ? 6 : K % (4 * STEP) == 0 ? 4 : 2;
@@ -521,15 +513,15 @@ struct FcWeights<half_t> {
 template <typename T, int Q>
 __global__ __launch_bounds__(kChainThreads) void mobilenet_chain_kernel(const ChainParams<T> P) {
   constexpr int kSlices = 2 * Q;
-  constexpr bool kHalf = sizeof(T) == 2, kMayLeave = kLeaves<T, Q>;
+  constexpr bool kHalf = sizeof(T) == 2;
   // 2 x 16 KB: split-K partial tiles, of one task and the next (between a task's reads and the writes of the task after the next lies
   // the barrier of the next); reused by the tail
   __shared__ float red2[2][kChainWaves * 2 * 4 * 64];
   // Each wavefront's own: whether it has left a task of the steps, of the last one, and by turn the number of a pointwise task that it left.
   __shared__ int left[4][kChainWaves];
   const int wg = blockIdx.x, tid = threadIdx.x;
-  if (kMayLeave && tid % 64 < 4) left[tid % 64][tid / 64] = 0;
-  Waits<kMayLeave> waits{P.failed, P.spin_limit, P.patience, &left[0][tid / 64]};
+  if (tid % 64 < 4) left[tid % 64][tid / 64] = 0;
+  Waits waits{P.failed, P.spin_limit, P.patience, &left[0][tid / 64]};
   {
     // The block descriptors are read at every block change, on the critical path, and the first touch of a line of
     // the kernel argument segment misses the scalar cache: touch every line now.
@@ -597,7 +589,7 @@ __global__ __launch_bounds__(kChainThreads) void mobilenet_chain_kernel(const Ch
   auto fully_connected = [&](bool own) __attribute__((always_inline)) {
     waits.left = &left[1][tid / 64];
     __syncthreads();
-    if (kMayLeave && own && any_wave(left[0], 1)) return false;
+    if (own && any_wave(left[0], 1)) return false;
     if (wg < fc_tasks) {
       const int ks = wg / fc_tasks_c, cb = wg % fc_tasks_c;
       float* pooled = red;             // [128]
@@ -653,7 +645,7 @@ __global__ __launch_bounds__(kChainThreads) void mobilenet_chain_kernel(const Ch
         *reinterpret_cast<float4*>(fsum + kq * 128 + 4 * c4) = s;
       }
       __syncthreads();
-      const bool some_left = kMayLeave && own && any_wave(left[1], 1);
+      const bool some_left = own && any_wave(left[1], 1);
       if (tid < kFcColBlock) {
         float s = 0.f;
 #pragma unroll
@@ -844,7 +836,7 @@ int chain_spin_limit() {
 
 int chain_workgroups() {
   // Test hook: TFX_CHAIN_WORKGROUPS=<n> leaves out the workgroups from the nth on (those of the fully connected layer are the first
-  // 64), as if they never got to run, where the others do without them (kLeaves).
+  // 64), as if they never got to run.
   if (const char* e = getenv("TFX_CHAIN_WORKGROUPS")) {
     const long v = strtol(e, nullptr, 10);
     if (v >= kFcTasks && v <= kChainGrid) return (int)v;
@@ -861,8 +853,8 @@ namespace {
 // 224 x 224 62.8, 38.8, 51, with one track 62.7, 51.1, 58.6, as launches that do not wait 68.7, 53, 53; quarter width 128 x 128 44, 25, 48;
 // 43.7, 47, 46.5; 56, 56, 54.  (With more than two streams some share a hardware queue, in which a wait holds up both.)
 // A stream that is being captured into a graph is left alone: an event of another stream cannot be recorded into the capture.  Replays of
-// such passes, full width 224 x 224: 67.6, 39.9, 40, as launches 73.3, 42.8, 40.  (Those of the fp32 pass at full width, whose workgroups do wait
-// for each other to run, are the caller's to order.)
+// such passes, full width 224 x 224: 67.6, 39.9, 40, as launches 73.3, 42.8, 40.  (Those of the fp32 pass at full width, whose launch of blocks
+// 2 - 4 has workgroups that do need each other to run, are the caller's to order.)
 struct ChainOrder {
   std::mutex lock;
   hipStream_t last[64][2];
@@ -949,8 +941,7 @@ int launch_chain_of(const T* in0, int image_size, const W* w, void* chain_ws, co
     const int rc = before(before_arg);
     if (rc != TFX_OK) return rc;
   }
-  const bool leaves = sizeof(T) == 2 || width_quarters < 4;  // kLeaves
-  hipLaunchKernelGGL(chain_kernel<T>(width_quarters), dim3(leaves ? chain_workgroups() : kChainGrid), dim3(kChainThreads), 0, stream, P);
+  hipLaunchKernelGGL(chain_kernel<T>(width_quarters), dim3(chain_workgroups()), dim3(kChainThreads), 0, stream, P);
   return check_launch();
 }
 }  // namespace

@@ -17,7 +17,7 @@ def model_of(half, q, size, classes, seed=97):
 
 @pytest.mark.parametrize("workgroups", [64, 100, 255])
 @pytest.mark.parametrize("half,q,size,classes", [(True, 1, 64, 10), (True, 2, 97, 129), (True, 3, 192, 1000), (True, 4, 224, 1024),
-                                                 (False, 1, 65, 1000), (False, 2, 192, 10), (False, 3, 96, 7)])
+                                                 (False, 1, 65, 1000), (False, 2, 192, 10), (False, 3, 96, 7), (False, 4, 224, 1000)])
 def test_workgroups_that_never_run(monkeypatch, half, q, size, classes, workgroups):
     """The same bits: whoever computes a task does it in the same order."""
     make, image = model_of(half, q, size, classes)
